@@ -211,14 +211,18 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   // (the matrix-core kernels address a unit's rows with 32-bit byte offsets: up to 4M tokens of 256 bytes)
-  const bool mfma = params->dtype == ROCO_BF16 && params->head_dim == 128 && L_max <= (1 << 22) &&
-                    env_int("ROCO_PREFILL_SIMPLE", 0) == 0;
+  const bool wide_bf16 = params->dtype == ROCO_BF16 && params->head_dim == 128;
+  // Up to 64 tokens a tiny fp32 prompt is one tile: splitting it into planes costs more than its products (both passes of
+  // fp32 / 128 at 16 units x 48 tokens: 19 us against 29).
+  const bool simple = env_int("ROCO_PREFILL_SIMPLE", 0) != 0 || (wide_bf16 && L_max > (1 << 22)) ||
+                      (params->dtype == ROCO_F32 && L_max <= 64 && prefill_is_tiny(a));
   if (want_lse) {  // the kernels keep base-2 normalisers
     const size_t count = static_cast<size_t>(params->units) * group * L_max;
     if (launch_lse_to_base2(lse_given, a.lse, count, s) != hipSuccess) return ROCO_EHIP;
   }
-  hipError_t e = mfma ? launch_prefill_attention_mfma(a, s)
-                      : launch_prefill_attention_simple(params->dtype, params->head_dim, a, s);
+  hipError_t e = simple      ? launch_prefill_attention_simple(params->dtype, params->head_dim, a, s)
+                 : wide_bf16 ? launch_prefill_attention_mfma(a, s)
+                             : launch_prefill_attention_planes(params->dtype, params->head_dim, a, s);
   if (e != hipSuccess) return ROCO_EHIP;
   if (a.pol.keeps_last_score()) {
     e = launch_prefill_last_row(params->dtype, params->head_dim, a, s);

@@ -148,6 +148,17 @@ hipError_t launch_set_overlap(int units, int slots_a, const int32_t* pos_a, cons
                               int32_t* inter, int32_t* uni, hipStream_t s);
 hipError_t launch_prefill_attention_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);
 hipError_t launch_prefill_attention_mfma(const PrefillArgs& a, hipStream_t s);  // bf16, head_dim 128
+hipError_t launch_prefill_attention_planes(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);  // the other forms
+// fp32 prompts of few scores: the vector-ALU row pass, one wave per query and as many waves as queries, is done before a
+// workgroup of the matrix-core pass with output has walked its tiles one after the other (fp32 / 64 with output, us: 4 units
+// x 256 tokens 12 against 20, 1 x 512 19 against 29, 16 x 128 11 against 15; but 16 x 256 23 against 20, 256 x 48 17 against 12).
+inline bool prefill_is_tiny(const PrefillArgs& a) {
+  return static_cast<double>(a.units) * a.group * a.L_max * a.L_max <= 524288.0;
+}
+void launch_prefill_rows_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);  // fp32
+// second shares of PrefillArgs::ksplit / qsplit merged into the first ones
+void launch_merge_key_shares(const PrefillArgs& a, hipStream_t s);
+void launch_sum_query_shares(const PrefillArgs& a, hipStream_t s);
 // overwrites PrefillArgs::acc2 with the attention row of each unit's last prompt token (kImpLast)
 hipError_t launch_lse_to_base2(const float* lse_ln, float* lse_log2, size_t n, hipStream_t s);
 hipError_t launch_prefill_last_row(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);

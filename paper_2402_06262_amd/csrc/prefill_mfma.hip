@@ -20,6 +20,7 @@
 
 #include "kernels.hpp"
 #include "mfma.hpp"
+#include "prefill_tiles.hpp"
 #include "profile.hpp"
 #include "stream.hpp"
 #include "tile_ring.hpp"
@@ -100,87 +101,6 @@ __device__ __forceinline__ void load_owned(uint4* own, const char* base, int row
 #pragma unroll
   for (int kk = 0; kk < kKSteps; ++kk)
     own[kk] = load16(base + static_cast<size_t>(row) * kRowBytes + kk * 32 + (lane >> 5) * 16);
-}
-
-// Workgroup -> (unit, block-pair) mapping.  The hardware hands consecutive workgroup ids to the 8 accelerator
-// dies in turn and each die has its own L2, so the workgroups of one unit (which all stream the same K or Q
-// tiles, at about the same time) are given ids that are congruent modulo 8: they land on one die and all but
-// the first fetch of a tile hit its L2.  The grid is one-dimensional over ceil(units/8)*8 x pairs ids.
-__device__ __forceinline__ bool locate(int units, int pairs, int& unit, int& pair) {
-  const int lin = blockIdx.x;
-  const int die = lin & 7, seq = lin >> 3;
-  unit = (seq / pairs) * 8 + die;
-  pair = seq % pairs;
-  return unit < units;
-}
-// The same for (unit, query head) pairs, u = unit * group + head: the heads of a unit stream the same keys (and
-// values), so they all go to the die unit % 8.  The grid covers ceil(units / 8) * 8 * group * pairs ids.
-__device__ __forceinline__ bool locate_heads(int units, int group, int pairs, int& u, int& pair) {
-  int v;  // virtual index: die v % 8, and on a die the heads of one unit before the next unit's
-  if (!locate(((units + 7) / 8) * 8 * group, pairs, v, pair)) return false;
-  const int unit = (v / (8 * group)) * 8 + (v & 7), head = (v >> 3) % group;
-  u = unit * group + head;
-  return unit < units;
-}
-
-// Online log-sum-exp update of one lane with the 16 scores of a tile.
-//   INTERIOR: every key of the tile is visible to every query of the group and none is inside a recency window:
-//             3 vector instructions per score (multiply-add, exponential, add) plus 8 for the maximum.
-// l = sum 2^(t - m) is a floating-point number, so m need not be the running maximum: any reference that keeps the
-// terms from overflowing gives the same sum to rounding.  The terms of a tile are first taken against the reference
-// as it stands (3 instructions per score and nothing else: `sum`); only if some lane's share comes out above 2^64
-// -- the first tile, whose reference is -inf, and a row whose scores later rise by more than 64 powers of two --
-// is the tile redone with the reference raised to its maximum.
-__device__ __forceinline__ void lazy_finish(float sum, const f32x16& s, float sc, float& m, float& l) {
-  if (__builtin_amdgcn_ballot_w64(!(sum <= 0x1p64f)) == 0) {
-    l += sum;
-  } else {
-    const float m_new = fmaxf(m, max16(s) * sc);
-    const float neg_new = -m_new;
-    float t0 = 0.0f, t1 = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      t0 += fast_exp2(fmaf(s[r], sc, neg_new));
-      t1 += fast_exp2(fmaf(s[r + 1], sc, neg_new));
-    }
-    l = fmaf(l, fast_exp2(m - m_new), t0 + t1);
-    m = m_new;
-  }
-}
-
-template <bool INTERIOR>
-__device__ __forceinline__ void lse_update(const f32x16& s, float sc, int kb, int half, int qi, int w, float rb,
-                                           float& m, float& l) {
-  if (INTERIOR) {
-    const float neg = -m;
-    float sum0 = 0.0f, sum1 = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      sum0 += fast_exp2(fmaf(s[r], sc, neg));
-      sum1 += fast_exp2(fmaf(s[r + 1], sc, neg));
-    }
-    lazy_finish(sum0 + sum1, s, sc, m, l);
-  } else {
-    float tv[16];
-    float mb = -INFINITY;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
-      float x = s[r] * sc;
-      if (w > 0 && qi - key < w) x += rb;
-      if (key > qi) x = -INFINITY;
-      tv[r] = x;
-      mb = fmaxf(mb, x);
-    }
-    const float m_new = fmaxf(m, mb);
-    if (m_new > -INFINITY) {
-      float sum = 0.0f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sum += fast_exp2(tv[r] - m_new);
-      l = l * fast_exp2(m - m_new) + sum;
-      m = m_new;
-    }
-  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -408,48 +328,6 @@ __global__ __launch_bounds__(256, 2) void prefill_rows_mfma(PrefillArgs a) {
       if (half == 0 && qi1 < len) lse_out[ubase + qi1] = mn + log2f(tot);
     }
   }
-}
-
-// Column-statistics update of one lane (one key) with the 16 scores of a tile (16 queries).  COUNT: the second
-// statistic is the number of queries that gave the key more than their row's average, p * (i + 1) > 1 (section
-// 4.1, quantised score), instead of the sum of squares.
-template <bool INTERIOR, bool COUNT>
-__device__ __forceinline__ void column_update(const f32x16& s, const float* lse_tile, const float* rinv_tile, float sc,
-                                              int ib, int half, int kj, int len, int w, float rb, float& s1, float& s2) {
-  float a1 = 0.0f, a2 = 0.0f, b1 = 0.0f, b2 = 0.0f;
-#pragma unroll
-  for (int g4 = 0; g4 < 4; ++g4) {
-    const float4 ls = *reinterpret_cast<const float4*>(lse_tile + 8 * g4 + 4 * half);
-    const float lv[4] = {ls.x, ls.y, ls.z, ls.w};
-    float rv[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // COUNT: 1 / (tokens the query attended), staged with the normalisers
-    if (COUNT) {
-      const float4 rs = *reinterpret_cast<const float4*>(rinv_tile + 8 * g4 + 4 * half);
-      rv[0] = rs.x; rv[1] = rs.y; rv[2] = rs.z; rv[3] = rs.w;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float x = fmaf(s[4 * g4 + e], sc, -lv[e]);
-      float p;
-      if (INTERIOR) {
-        p = fast_exp2(x);
-      } else {
-        const int qi = ib + 8 * g4 + 4 * half + e;
-        if (w > 0 && qi - kj < w) x += rb;
-        p = fast_exp2(x);
-        if (qi < kj || qi >= len) p = 0.0f;
-      }
-      float second;
-      if (COUNT) {
-        second = p > rv[e] ? 1.0f : 0.0f;  // p * (i + 1) > 1
-      } else {
-        second = p * p;
-      }
-      if (e & 1) { b1 += p; b2 = COUNT ? b2 + second : fmaf(p, p, b2); }
-      else       { a1 += p; a2 = COUNT ? a2 + second : fmaf(p, p, a2); }
-    }
-  }
-  s1 += a1 + b1;
-  s2 += a2 + b2;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -728,36 +606,6 @@ __device__ __forceinline__ void tile_load_two(Staged<WAVES>& s, const char* base
   }
 }
 
-// The 16 probabilities of a tile (one key, 16 queries of one head) added into `pb` (cleared before the first head).
-template <bool INTERIOR>
-__device__ __forceinline__ void column_probs(const f32x16& s, const float* lse_tile, float sc, int ib, int half,
-                                             int kj, int len, int w, float rb, f32x16& pb) {
-  if (!INTERIOR) {
-    // The masks of this (rare) path depend only on values known before the branch that leads here; the compiler
-    // would compute all of them ahead of that branch, on every tile.  An opaque copy of the block index keeps them here.
-    asm volatile("" : "+s"(ib));
-  }
-#pragma unroll
-  for (int g4 = 0; g4 < 4; ++g4) {
-    const float4 ls = *reinterpret_cast<const float4*>(lse_tile + 8 * g4 + 4 * half);
-    const float lv[4] = {ls.x, ls.y, ls.z, ls.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float x = fmaf(s[4 * g4 + e], sc, -lv[e]);
-      float p;
-      if (INTERIOR) {
-        p = fast_exp2(x);
-      } else {
-        const int qi = ib + 8 * g4 + 4 * half + e;
-        if (w > 0 && qi - kj < w) x += rb;
-        p = fast_exp2(x);
-        if (qi < kj || qi >= len) p = 0.0f;
-      }
-      pb[4 * g4 + e] += p;
-    }
-  }
-}
-
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void prefill_columns_gqa_mfma(PrefillArgs a) {
   constexpr int kOwn = Shape<WAVES>::kOwn;
@@ -885,54 +733,6 @@ __global__ __launch_bounds__(WAVES * kWave) void prefill_columns_gqa_mfma(Prefil
 // sub-tile; that row is given to query hf * 16 / G + r / G of the sub-tile, head r % G).  The sum over the heads is
 // then a sum down a few registers of one result tile: nothing is carried from tile to tile, and the kernel keeps the
 // register budget -- three waves per SIMD -- of the ungrouped column pass.
-template <int G> struct GroupedRows {
-  static constexpr int kPerHalf = 16 / G;      // queries per lane half in a 32-row sub-tile
-  static constexpr int kPerSub = 32 / G;       // query positions per sub-tile
-  static constexpr int kPerTile = 64 / G;      // query positions per 64-row tile
-  // LDS row of a tile -> local query position and head
-  __device__ static void locate(int row, int& ql, int& h) {
-    const int sub = row >> 5, rr = row & 31;
-    const int hf = (rr >> 2) & 1, r = 4 * (rr >> 3) + (rr & 3);
-    ql = sub * kPerSub + hf * kPerHalf + r / G;
-    h = r % G;
-  }
-};
-
-template <bool INTERIOR, int G>
-__device__ __forceinline__ void column_update_grouped(const f32x16& s, const float* lse_tile, float sc, int ib, int half,
-                                                      int kj, int len, int w, float rb, const Policy& pol,
-                                                      float& s1, float& s2) {
-  if (!INTERIOR) asm volatile("" : "+s"(ib));  // keeps this path's masks out of the code before the branch (see column_probs)
-  constexpr int kPerHalf = GroupedRows<G>::kPerHalf;
-  float p[16];
-#pragma unroll
-  for (int g4 = 0; g4 < 4; ++g4) {
-    const float4 ls = *reinterpret_cast<const float4*>(lse_tile + 8 * g4 + 4 * half);
-    const float lv[4] = {ls.x, ls.y, ls.z, ls.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 4 * g4 + e;
-      float x = fmaf(s[r], sc, -lv[e]);
-      if (INTERIOR) {
-        p[r] = fast_exp2(x);
-      } else {
-        const int qi = ib + half * kPerHalf + r / G;
-        if (w > 0 && qi - kj < w) x += rb;
-        p[r] = (qi < kj || qi >= len) ? 0.0f : fast_exp2(x);
-      }
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < kPerHalf; ++q) {
-    float sum = p[q * G];
-#pragma unroll
-    for (int h = 1; h < G; ++h) sum += p[q * G + h];
-    const float pbar = sum * (1.0f / static_cast<float>(G));
-    s1 += pbar;
-    s2 = pol.second_statistic(s2, pbar, static_cast<float>(ib + half * kPerHalf + q + 1));
-  }
-}
-
 template <int WAVES, int G>
 __global__ __launch_bounds__(WAVES * kWave) void prefill_columns_gqa_pow2_mfma(PrefillArgs a) {
   using GR = GroupedRows<G>;
@@ -1606,7 +1406,7 @@ hipError_t launch_t(const PrefillArgs& a, hipStream_t s) {
     ProfScope ps(kProfPrefillRows, s);
     hipLaunchKernelGGL(prefill_rows_mfma, rows_grid, dim3(WAVES * kWave), 0, s, b);
     if (b.ksplit > 1)
-      hipLaunchKernelGGL(merge_key_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, b);
+      launch_merge_key_shares(b, s);
   }
   {
     ProfScope ps(kProfPrefillColumns, s);
@@ -1615,7 +1415,7 @@ hipError_t launch_t(const PrefillArgs& a, hipStream_t s) {
       hipLaunchKernelGGL(prefill_columns_mfma<true>, grid, dim3(WAVES * kWave), 0, s, b);
     else hipLaunchKernelGGL(prefill_columns_mfma<false>, grid, dim3(WAVES * kWave), 0, s, b);
     if (b.qsplit > 1)
-      hipLaunchKernelGGL(sum_query_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, b);
+      launch_sum_query_shares(b, s);
   }
   return hipGetLastError();
 }
@@ -1651,12 +1451,19 @@ hipError_t launch_with_output(const PrefillArgs& a, hipStream_t s) {
     else if (a.pol.counts_above_average()) hipLaunchKernelGGL(prefill_columns_mfma<true>, cgrid, dim3(4 * kWave), 0, s, c);
     else hipLaunchKernelGGL(prefill_columns_mfma<false>, cgrid, dim3(4 * kWave), 0, s, c);
     if (c.qsplit > 1)
-      hipLaunchKernelGGL(sum_query_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, c);
+      launch_sum_query_shares(c, s);
   }
   return hipGetLastError();
 }
 
 }  // namespace
+
+void launch_merge_key_shares(const PrefillArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(merge_key_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, a);
+}
+void launch_sum_query_shares(const PrefillArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(sum_query_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, a);
+}
 
 hipError_t launch_mfma_probe(int workgroups, int iters, int mode, float* sink, hipStream_t s) {
   ProfScope ps(kProfMfmaProbe, s);

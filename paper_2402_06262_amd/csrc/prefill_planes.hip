@@ -1,0 +1,832 @@
+// Prefill attention statistics on the gfx950 matrix cores for fp32 storage and for head_dim 64.
+//
+// The two passes of prefill_mfma.hip (row normalisers, column statistics) and the same orientation: a workgroup of four
+// waves owns 32 or 64 rows of one operand per wave, in registers, as B operands of v_mfma_f32_32x32x16_bf16; the other
+// operand streams past them through LDS; in the 32x32 result tile the owned row is the lane and the streamed rows run
+// down the 16 accumulator registers, so the reductions of a pass cross no lanes.
+//
+// fp32 operands are taken apart into three bf16 planes, x = hi + mid + lo, each the round-to-nearest bf16 of what the
+// planes before it left over: 24 significand bits in all, the width of fp32.  A product keeps the six terms of 2^-16 and
+// above (hi hi, hi mid, mid hi, hi lo, lo hi, mid mid; every one is exact in fp32) and drops those of 2^-24.  The five
+// small terms run on accumulator chains of their own and are added to the hi-hi sum once per tile, so a logit sees one
+// rounding per 16 products at its own magnitude.  Six bf16 instructions cover 16 k-elements in 192 matrix cycles; the
+// fp32 instruction (32x32x2) needs 512.
+//
+// What bounds the passes: bf16 / head_dim 64 has 4 matrix instructions (128 cycles) per 32x32 tile against 16 x 16
+// vector cycles in the row pass and 16 x 20 in the column pass (multiply-add, exponential at half rate, additions), so
+// it is bound by vector issue; fp32 has 24 (head_dim 64) or 48 matrix instructions and is bound by the matrix pipe.  Two
+// or more workgroups per compute unit overlap the one pipe's work with the other's; nothing is pipelined by hand.
+//
+// Infinities and NaN: a plane product may not meet an infinity with a zero plane (0 x inf), so the two smaller planes of
+// an infinite or NaN element are zero, and once a workgroup has met such an element its cross terms take hi planes in
+// which it counts as zero: it contributes through hi x hi alone, as in a plain fp32 product.  The attention output
+// does likewise with V, whose infinities must reach only the queries that see them.  (Elements below 2^-109 lose their
+// lower planes to bf16's subnormal range: they matter only against partners above 2^85.)
+#include "kernels.hpp"
+#include "mfma.hpp"
+#include "prefill_tiles.hpp"
+#include "profile.hpp"
+#include "stream.hpp"
+
+namespace roco {
+namespace {
+
+using mfma::bf16x8;
+using mfma::f32x16;
+using mfma::column_probs;
+using mfma::column_update;
+using mfma::column_update_grouped;
+using mfma::GroupedRows;
+using mfma::lds_read_transposed;
+using mfma::locate;
+using mfma::locate_heads;
+using mfma::lse_update;
+using mfma::max16;
+
+constexpr int kThreads = 256;
+
+// Rows of a streamed tile: as many as leave room for the resident workgroups (bf16: 128, fewer barriers per row; the kernels
+// with an output tile or head sums next to their scores take 64).
+template <int DT, int D> constexpr int kRows = DT == kBF16 ? 128 : D == 128 ? 32 : 64;
+template <int DT, int D> constexpr int kRowsSmall = DT == kF32 && D == 128 ? 32 : 64;
+
+// Geometry of a streamed tile: TR rows of NP bf16 planes in LDS.
+template <int DT, int D, int ROWS> struct Planes {
+  static constexpr int NP = DT == kF32 ? 3 : 1;
+  static constexpr int KS = D / 16;                         // k-steps of the 32x32x16 instruction
+  static constexpr int TR = ROWS;
+  static constexpr int SUBS = TR / 32;
+  static constexpr int ROW = 2 * D;                         // bytes of a plane row
+  static constexpr int PLANE = TR * ROW;
+  static constexpr int TILE = NP * PLANE;
+  static constexpr int ROWV = ROW + 64;                     // V rows: transpose reads then hit distinct banks (mfma.hpp)
+  static constexpr int PLANEV = TR * ROWV;
+  static constexpr int TILEV = NP * PLANEV;
+  static constexpr int IN_ROW = D * (DT == kF32 ? 4 : 2);   // bytes of a row in memory
+  static constexpr int CPR = IN_ROW / 16;                   // 16-byte chunks per row
+  static constexpr int PIECES = TR * CPR / kThreads;        // chunks per thread and tile
+  static_assert(TR * CPR % kThreads == 0, "a tile is dealt evenly to the threads");
+};
+
+// 16-byte chunk `ch` of plane row `row`: stored in a slot that makes the 128-bit fragment reads (16 consecutive rows, same
+// chunk) fall on 16 distinct groups of banks.  Rows of 128 bytes share the banks of two rows, hence the shift.
+template <int D> __device__ __forceinline__ int chunk_offset(int row, int ch) {
+  return row * 2 * D + ((D == 64 ? ch ^ ((row >> 1) & 7) : ch ^ (row & 15)) << 4);
+}
+
+__device__ __forceinline__ uint32_t bf16_bits(float f) {
+  return static_cast<uint32_t>(__builtin_bit_cast(uint16_t, static_cast<__bf16>(f)));
+}
+__device__ __forceinline__ float bf16_value(uint32_t h) { return __uint_as_float(h << 16); }
+
+// One fp32 value as bf16 planes, whatever it is; true if it is an infinity or NaN (then the smaller planes are zero).
+__device__ __forceinline__ bool split_any(uint32_t bits, uint32_t* h) {
+  const float x = __uint_as_float(bits);
+  const uint32_t mag = bits & 0x7fffffffu;
+  if (mag >= 0x7f800000u) {
+    h[0] = (bits >> 16) | (mag > 0x7f800000u ? 0x40u : 0u);  // a NaN stays one
+    h[1] = h[2] = 0u;
+    return true;
+  }
+  h[0] = mag >= 0x7f000000u ? bits >> 16 : bf16_bits(x);  // truncated near the top of the range: rounding may overflow
+  const float r1 = x - bf16_value(h[0]);
+  h[1] = bf16_bits(r1);
+  h[2] = bf16_bits(r1 - bf16_value(h[1]));
+  return false;
+}
+// Four fp32 values as three planes of four bf16 values; true if one of them is an infinity or NaN.
+__device__ __forceinline__ bool split4(const uint4& w, uint2* p) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  auto pack = [](f32x2 v) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2)); };
+  auto less = [](f32x2 v, uint32_t h) {  // what a plane leaves over: exact
+    return f32x2{v.x - __uint_as_float(h << 16), v.y - __uint_as_float(h & 0xffff0000u)};
+  };
+  f32x2 a = {__uint_as_float(w.x), __uint_as_float(w.y)}, b = {__uint_as_float(w.z), __uint_as_float(w.w)};
+  p[0] = make_uint2(pack(a), pack(b));
+  a = less(a, p[0].x);
+  b = less(b, p[0].y);
+  // An infinity, a NaN or a value so large that its first plane rounds to infinity leaves a remainder that is not finite.
+  const bool top = !(fabsf(((a.x + a.y) + b.x) + b.y) < INFINITY);
+  p[1] = make_uint2(pack(a), pack(b));
+  a = less(a, p[1].x);
+  b = less(b, p[1].y);
+  p[2] = make_uint2(pack(a), pack(b));
+  if (!top) return false;
+  const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+  uint32_t h[4][3];
+  bool odd = false;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) odd |= split_any(u[e], h[e]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) p[k] = make_uint2(h[0][k] | (h[1][k] << 16), h[2][k] | (h[3][k] << 16));
+  return odd;
+}
+// Infinities and NaN of two packed bf16 values replaced by zero.
+__device__ __forceinline__ uint32_t finite2(uint32_t v) {
+  uint32_t r = v;
+  if ((v & 0x7f80u) == 0x7f80u) r &= 0xffff0000u;
+  if ((v & 0x7f800000u) == 0x7f800000u) r &= 0xffffu;
+  return r;
+}
+__device__ __forceinline__ uint4 finite8(uint4 v) {
+  asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));  // stays in the rare branch that asked for it
+  return make_uint4(finite2(v.x), finite2(v.y), finite2(v.z), finite2(v.w));
+}
+__device__ __forceinline__ bool has_odd2(uint32_t v) {
+  return (v & 0x7f80u) == 0x7f80u || (v & 0x7f800000u) == 0x7f800000u;
+}
+
+__device__ __forceinline__ f32x16 mm(const uint4& x, const uint4& y, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
+}
+
+// A thread's chunks of a tile on their way from memory to LDS.
+template <int DT, int D, int ROWS> struct Pieces {
+  using P = Planes<DT, D, ROWS>;
+  uint4 w[P::PIECES];
+  __device__ __forceinline__ void load(const char* base, int row0, int last_row) {
+#pragma unroll
+    for (int i = 0; i < P::PIECES; ++i) {
+      const int idx = threadIdx.x + kThreads * i;
+      const int row = min(row0 + idx / P::CPR, last_row);  // rows past the end are masked by the caller
+      w[i] = load16(base + static_cast<size_t>(row) * P::IN_ROW + (idx % P::CPR) * 16);
+    }
+  }
+  // Rows of a tile that holds TR / G query positions from `pos0` on for G heads (see GroupedRows), head h at base + h * stride.
+  template <int G> __device__ __forceinline__ void load_heads(const char* base, size_t stride, int pos0, int last_pos) {
+#pragma unroll
+    for (int i = 0; i < P::PIECES; ++i) {
+      const int idx = threadIdx.x + kThreads * i;
+      int ql, h;
+      GroupedRows<G>::locate(idx / P::CPR & 63, ql, h);
+      const int pos = min(pos0 + ql + (idx / P::CPR >> 6) * (64 / G), last_pos);
+      w[i] = load16(base + h * stride + static_cast<size_t>(pos) * P::IN_ROW + (idx % P::CPR) * 16);
+    }
+  }
+  // Into the planes of a K or Q tile; true if this thread met an infinity or NaN (fp32 only: bf16 products need no care).
+  __device__ __forceinline__ bool store(char* tile) const {
+    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < P::PIECES; ++i) {
+      const int idx = threadIdx.x + kThreads * i;
+      const int row = idx / P::CPR, c = idx % P::CPR;
+      if constexpr (DT == kBF16) {
+        *reinterpret_cast<uint4*>(tile + chunk_offset<D>(row, c)) = w[i];
+      } else {
+        uint2 p[3];
+        odd |= split4(w[i], p);
+        char* at = tile + chunk_offset<D>(row, c >> 1) + (c & 1) * 8;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(at + k * P::PLANE) = p[k];
+      }
+    }
+    return odd;
+  }
+  // Into the planes of a V tile (rows of ROWV bytes).
+  __device__ __forceinline__ bool store_values(char* tile) const {
+    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < P::PIECES; ++i) {
+      const int idx = threadIdx.x + kThreads * i;
+      const int row = idx / P::CPR, c = idx % P::CPR;
+      if constexpr (DT == kBF16) {
+        odd |= has_odd2(w[i].x) || has_odd2(w[i].y) || has_odd2(w[i].z) || has_odd2(w[i].w);
+        *reinterpret_cast<uint4*>(tile + row * P::ROWV + c * 16) = w[i];
+      } else {
+        uint2 p[3];
+        odd |= split4(w[i], p);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(tile + k * P::PLANEV + row * P::ROWV + c * 8) = p[k];
+      }
+    }
+    return odd;
+  }
+};
+
+// This lane's row of one group of 32 owned rows, as B operands.
+template <int DT, int D> struct Owned {
+  using P = Planes<DT, D, 64>;
+  uint4 f[P::NP][P::KS];
+  // true if the lane met an infinity or NaN
+  __device__ __forceinline__ bool load(const char* base, int row, int last_row) {
+    const int half = (threadIdx.x & (kWave - 1)) >> 5;
+    const char* at = base + static_cast<size_t>(min(row, last_row)) * P::IN_ROW;
+    bool odd = false;
+#pragma unroll
+    for (int kk = 0; kk < P::KS; ++kk) {
+      if constexpr (DT == kBF16) {
+        f[0][kk] = load16(at + kk * 32 + half * 16);
+      } else {
+        uint2 a[3], b[3];
+        odd |= split4(load16(at + kk * 64 + half * 32), a);
+        odd |= split4(load16(at + kk * 64 + half * 32 + 16), b);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) f[k][kk] = make_uint4(a[k].x, a[k].y, b[k].x, b[k].y);
+      }
+    }
+    return odd;
+  }
+};
+
+// Score tile: the 32 streamed rows of sub-tile `sub` against 32 owned rows.  ODD: an infinity or NaN is about (see the
+// head of the file).
+template <int DT, int D, int ROWS, bool ODD>
+__device__ __forceinline__ f32x16 score_tile(const char* tile, int sub, const Owned<DT, D>& own) {
+  using P = Planes<DT, D, ROWS>;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int row = sub * 32 + (lane & 31);
+  const f32x16 zero = {0};
+  f32x16 acc;
+  auto frag = [&](int plane, int kk) {
+    return *reinterpret_cast<const uint4*>(tile + plane * P::PLANE + chunk_offset<D>(row, 2 * kk + (lane >> 5)));
+  };
+  if constexpr (DT == kBF16) {
+#pragma unroll
+    for (int kk = 0; kk < P::KS; ++kk) acc = mm(frag(0, kk), own.f[0][kk], kk == 0 ? zero : acc);
+  } else {
+    // The small terms share one chain: a second one would let a wave issue them back to back, but the registers it takes
+    // are worth more as a third resident wave (fp32 / 64, 64 units x 2048 tokens: 112 us per pass against 137).
+    f32x16 small = zero;
+#pragma unroll
+    for (int kk = 0; kk < P::KS; ++kk) {
+      const uint4 h = frag(0, kk), m = frag(1, kk), l = frag(2, kk);
+      const uint4 hs = ODD ? finite8(h) : h, oh = ODD ? finite8(own.f[0][kk]) : own.f[0][kk];
+      small = mm(l, oh, small);
+      small = mm(hs, own.f[2][kk], small);
+      acc = mm(h, own.f[0][kk], kk == 0 ? zero : acc);
+      small = mm(m, own.f[1][kk], small);
+      small = mm(hs, own.f[1][kk], small);
+      small = mm(m, oh, small);
+    }
+    acc += small;
+  }
+  return acc;
+}
+template <int ROWS, int DT, int D>
+__device__ __forceinline__ f32x16 score_tile(bool odd, const char* tile, int sub, const Owned<DT, D>& own) {
+  if (DT == kF32 && odd) return score_tile<DT, D, ROWS, true>(tile, sub, own);
+  return score_tile<DT, D, ROWS, false>(tile, sub, own);
+}
+
+// Blocks of owned rows of a workgroup: paired, it takes the p-th longest and the p-th shortest (equal work whatever the
+// position under the causal diagonal), else one.  Returns false when there is none for this id and pass.
+__device__ __forceinline__ bool pick_block(bool paired, int pass, int pair_id, int n_blocks, bool long_last, int& blk) {
+  if (!paired) {
+    if (pass == 1 || pair_id >= n_blocks) return false;
+    blk = long_last ? n_blocks - 1 - pair_id : pair_id;  // the longest streams start first
+    return true;
+  }
+  const int far = n_blocks - 1 - pair_id;
+  if (far < pair_id || (pass == 1 && far == pair_id)) return false;
+  blk = (pass == 0) == long_last ? far : pair_id;
+  return true;
+}
+
+// The four waves of a workgroup share its owned rows and the streamed tiles: PARTS = 1, every wave owns 32 rows of its own
+// and takes all sub-tiles of 32 streamed rows; PARTS = 2, waves w and w + 2 own the same 32 rows and take every other
+// sub-tile (twice the workgroups of half the length for the same rows), and their results meet in LDS at the end.
+template <int PARTS> struct Shares {
+  static constexpr int GROUPS = 4 / PARTS;
+  static constexpr int kOwn = 32 * GROUPS;
+};
+
+// ------------------------------------------------------------------------------------------------
+// pass 1: lse[i] = log2 sum_{j<=i} 2^(t_ij)
+template <int DT, int D, int PARTS>
+__global__ __launch_bounds__(kThreads, DT == kBF16 ? 4 : D == 64 ? 3 : 2) void prefill_rows_planes(PrefillArgs a) {
+  using P = Planes<DT, D, kRows<DT, D>>;
+  constexpr int kOwn = Shares<PARTS>::kOwn, GROUPS = Shares<PARTS>::GROUPS;
+  __shared__ __attribute__((aligned(16))) char tiles[2][P::TILE];
+  __shared__ float other[2][PARTS == 2 ? kOwn : 1];
+  __shared__ int odd_s;
+  int u, id;
+  if (!locate_heads(a.units, a.group, a.pairs * a.ksplit, u, id)) return;
+  const int seg = id % a.ksplit, pair_id = id / a.ksplit;
+  float* const lse_out = seg == 0 ? a.lse : a.acc;  // second share: see merge_key_shares (group = 1 only)
+  const int uk = u / a.group;
+  const int len = a.len[uk];
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int half = lane >> 5, grp = wave % GROUPS, part = wave / GROUPS;
+  const size_t ubase = static_cast<size_t>(u) * a.L_max;
+  const char* Qb = static_cast<const char*>(a.Q) + ubase * P::IN_ROW;
+  const char* Kb = static_cast<const char*>(a.K) + static_cast<size_t>(uk) * a.L_max * P::IN_ROW;
+  const float sc = a.scale_log2;
+  const int w = a.recency_window;
+  const float rb = a.recency_bias_log2;
+  const int n_blocks = (len + kOwn - 1) / kOwn;
+  if (threadIdx.x == 0) odd_s = 0;
+
+  for (int pass = 0; pass < 2; ++pass) {
+    int blk;
+    if (!pick_block(a.paired != 0, pass, pair_id, n_blocks, true, blk)) break;
+    const int q0 = blk * kOwn;
+    const int qg = q0 + 32 * grp, qi = qg + (lane & 31);  // first query of the wave's group, this lane's query
+    const int n_tiles = (min(len, q0 + kOwn) - 1) / P::TR + 1;
+    int t_lo = 0, t_hi = n_tiles - 1;  // this workgroup's share of the key tiles (possibly none)
+    if (a.ksplit > 1) {
+      const int per = (n_tiles + a.ksplit - 1) / a.ksplit;
+      t_lo = seg * per;
+      t_hi = min(t_hi, t_lo + per - 1);
+    }
+    Pieces<DT, D, P::TR> st;
+    if (t_lo <= t_hi) st.load(Kb, t_lo * P::TR, len - 1);
+    __syncthreads();  // the previous block has finished with the tiles; odd_s is cleared
+    Owned<DT, D> own;
+    bool odd = own.load(Qb, qi, len - 1);
+    float m = -INFINITY, l = 0.0f;
+    for (int t = t_lo; t <= t_hi; ++t) {
+      char* const tile = tiles[(t - t_lo) & 1];
+      odd |= st.store(tile);
+      if (DT == kF32 && odd) odd_s = 1;
+      __syncthreads();  // tile t is in LDS; everybody is done with tile t - 1, whose buffer tile t + 1 takes
+      if (t + 1 <= t_hi) st.load(Kb, (t + 1) * P::TR, len - 1);
+      const bool odd_tile = DT == kF32 && __builtin_amdgcn_readfirstlane(odd_s) != 0;
+#pragma unroll
+      for (int i = 0; i < P::SUBS / PARTS; ++i) {
+        const int sub = part + PARTS * i;
+        const int kb = t * P::TR + sub * 32;
+        if (kb > qg + 31) continue;  // wholly above the diagonal
+        const f32x16 s = score_tile<P::TR>(odd_tile, tile, sub, own);
+        if (kb + 31 + w <= qg) lse_update<true>(s, sc, kb, half, qi, w, rb, m, l);
+        else lse_update<false>(s, sc, kb, half, qi, w, rb, m, l);
+      }
+    }
+    auto join = [&](float mo, float lo) {  // sums over other keys of the same query
+      const float mn = fmaxf(m, mo);
+      l = (m > -INFINITY ? l * fast_exp2(m - mn) : 0.0f) + (mo > -INFINITY ? lo * fast_exp2(mo - mn) : 0.0f);
+      m = mn;
+    };
+    const float mo = __shfl_xor(m, 32, kWave), lo = __shfl_xor(l, 32, kWave);
+    join(mo, lo);
+    if constexpr (PARTS == 2) {
+      if (part == 1 && half == 0) { other[0][32 * grp + lane] = m; other[1][32 * grp + lane] = l; }
+      __syncthreads();
+      if (part == 0 && half == 0) join(other[0][32 * grp + lane], other[1][32 * grp + lane]);
+    }
+    if (part == 0 && half == 0 && qi < len) lse_out[ubase + qi] = m + log2f(l);  // -inf for a share without keys
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// pass 2: Acc[j] = sum_i Pbar[i,j], Acc2[j] = sum_i Pbar[i,j]^2 (or the count of above-average queries), Pbar the mean over
+// the unit's query heads.  A workgroup owns a block of keys and walks the query tiles from the end of the prompt down to
+// its own keys; grouped, a tile position is taken head by head and the sum over the heads stays in the lane's registers.
+// HEADS: 1, or 0 for any group (head by head), or 2, 4, 8, 16 for that group with the head sum inside a result tile.
+template <int DT, int D, int PARTS, int HEADS>
+__global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D == 64 && HEADS != 0 ? 3 : 2) void prefill_columns_planes(PrefillArgs a) {
+  using P = Planes<DT, D, HEADS == 0 ? kRowsSmall<DT, D> : kRows<DT, D>>;
+  constexpr int kOwn = Shares<PARTS>::kOwn, GROUPS = Shares<PARTS>::GROUPS, NSUB = P::SUBS / PARTS;
+  constexpr int PER = HEADS > 1 ? HEADS : 1;               // heads per query position of a tile
+  constexpr int QT = P::TR / PER, QS = 32 / PER;           // query positions per tile and per sub-tile
+  __shared__ __attribute__((aligned(16))) char tiles[2][P::TILE];
+  __shared__ __attribute__((aligned(16))) float lse_s[2][P::TR], rinv_s[2][P::TR];  // rinv: 1 / (tokens the query attended)
+  __shared__ float other[2][PARTS == 2 ? kOwn : 1];
+  __shared__ int odd_s;
+  int u, id;
+  if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
+  const int seg = id % a.qsplit, pair_id = id / a.qsplit;
+  float* const out1 = seg == 0 ? a.acc : reinterpret_cast<float*>(a.var_key);  // second share: see sum_query_shares
+  float* const out2 = seg == 0 ? a.acc2 : reinterpret_cast<float*>(a.mas_key);
+  const int G = HEADS != 1 ? a.group : 1;
+  const float inv_heads = 1.0f / static_cast<float>(G);
+  const bool count = a.pol.counts_above_average();
+  const int len = a.len[u];
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int half = lane >> 5, grp = wave % GROUPS, part = wave / GROUPS;
+  const size_t ubase = static_cast<size_t>(u) * a.L_max;
+  const char* Kb = static_cast<const char*>(a.K) + ubase * P::IN_ROW;
+  const char* Qu = static_cast<const char*>(a.Q) + ubase * G * P::IN_ROW;  // [G][L_max][d]
+  const float* lse_u = a.lse + ubase * G;
+  const float sc = a.scale_log2;
+  const int w = a.recency_window;
+  const float rb = a.recency_bias_log2;
+  const int n_blocks = (len + kOwn - 1) / kOwn;
+  if (threadIdx.x == 0) odd_s = 0;
+
+  for (int pass = 0; pass < 2; ++pass) {
+    int blk;
+    if (!pick_block(a.paired != 0, pass, pair_id, n_blocks, false, blk)) break;
+    const int j0 = blk * kOwn;
+    const int kg = j0 + 32 * grp, kj = kg + (lane & 31);  // first key of the wave's group, this lane's key
+    int t_first = j0 / QT, t_last = (len - 1) / QT;
+    if (a.qsplit > 1) {  // this workgroup's share of the query tiles (possibly none)
+      const int per = (t_last - t_first + a.qsplit) / a.qsplit;
+      t_first += seg * per;
+      t_last = min(t_last, t_first + per - 1);
+    }
+    Pieces<DT, D, P::TR> st;
+    float st_lse = 0.0f;
+    auto fetch = [&](int t, int h) {
+      int lse_h = h, lse_q = threadIdx.x;
+      if constexpr (HEADS > 1) {
+        st.template load_heads<PER>(Qu, static_cast<size_t>(a.L_max) * P::IN_ROW, t * QT, len - 1);
+        GroupedRows<PER>::locate(threadIdx.x & 63, lse_q, lse_h);
+        lse_q += (static_cast<int>(threadIdx.x) >> 6) * (64 / PER);
+      } else {
+        st.load(Qu + static_cast<size_t>(h) * a.L_max * P::IN_ROW, t * QT, len - 1);
+      }
+      if (threadIdx.x < P::TR) st_lse = lse_u[static_cast<size_t>(lse_h) * a.L_max + min(t * QT + lse_q, len - 1)];
+    };
+    if (t_first <= t_last) fetch(t_last, 0);
+    __syncthreads();  // the previous block has finished with the tiles; odd_s is cleared
+    Owned<DT, D> own;
+    bool odd = own.load(Kb, kj, len - 1);
+    float s1 = 0.0f, s2 = 0.0f;
+    f32x16 pb[HEADS == 0 ? NSUB : 1];  // sums over the heads of a tile's probabilities
+
+    int b = 0;
+    for (int t = t_last; t >= t_first; --t) {
+      for (int h = 0; h < (HEADS == 0 ? G : 1); ++h) {
+        char* const tile = tiles[b];
+        odd |= st.store(tile);
+        if (DT == kF32 && odd) odd_s = 1;
+        if (threadIdx.x < P::TR) {
+          lse_s[b][threadIdx.x] = st_lse;
+          if (count && HEADS == 1) rinv_s[b][threadIdx.x] = 1.0f / static_cast<float>(t * P::TR + static_cast<int>(threadIdx.x) + 1);
+        }
+        __syncthreads();
+        if (HEADS == 0 && h + 1 < G) fetch(t, h + 1);
+        else if (t > t_first) fetch(t - 1, 0);
+        const bool odd_tile = DT == kF32 && __builtin_amdgcn_readfirstlane(odd_s) != 0;
+#pragma unroll
+        for (int i = 0; i < NSUB; ++i) {
+          const int sub = part + PARTS * i;
+          const int ib = t * QT + sub * QS;  // first query position of the sub-tile; its last one is ib + QS - 1
+          if (ib + QS - 1 < kg || ib >= len) continue;  // no query of the sub-tile reaches the wave's keys
+          const f32x16 c = score_tile<P::TR>(odd_tile, tile, sub, own);
+          const bool interior = ib + QS - 1 < len && ib >= kg + 31 + w;
+          const float* lt = &lse_s[b][sub * 32];
+          if constexpr (HEADS > 1) {
+            if (interior) column_update_grouped<true, PER>(c, lt, sc, ib, half, kj, len, w, rb, a.pol, s1, s2);
+            else column_update_grouped<false, PER>(c, lt, sc, ib, half, kj, len, w, rb, a.pol, s1, s2);
+          } else if constexpr (HEADS == 0) {
+            if (h == 0) pb[i] = f32x16{0};
+            if (interior) column_probs<true>(c, lt, sc, ib, half, kj, len, w, rb, pb[i]);
+            else column_probs<false>(c, lt, sc, ib, half, kj, len, w, rb, pb[i]);
+            if (h == G - 1) {  // every head has been added
+              float e1 = 0.0f, e2 = 0.0f;
+              if (count) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                  const float p = pb[i][e] * inv_heads;
+                  e1 += p;
+                  e2 += p * static_cast<float>(ib + 8 * (e >> 2) + 4 * half + (e & 3) + 1) > 1.0f ? 1.0f : 0.0f;
+                }
+              } else {  // (the last-query score of kImpLast is written over the squares later: prefill_last_row)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                  const float p = pb[i][e] * inv_heads;
+                  e1 += p;
+                  e2 = fmaf(p, p, e2);
+                }
+              }
+              s1 += e1;
+              s2 += e2;
+            }
+          } else {
+            const float* rt = &rinv_s[b][sub * 32];
+            if (count) column_update<false, true>(c, lt, rt, sc, ib, half, kj, len, w, rb, s1, s2);
+            else if (interior) column_update<true, false>(c, lt, rt, sc, ib, half, kj, len, w, rb, s1, s2);
+            else column_update<false, false>(c, lt, rt, sc, ib, half, kj, len, w, rb, s1, s2);
+          }
+        }
+        b ^= 1;
+      }
+    }
+    s1 += __shfl_xor(s1, 32, kWave);
+    s2 += __shfl_xor(s2, 32, kWave);
+    if constexpr (PARTS == 2) {
+      if (part == 1 && half == 0) { other[0][32 * grp + lane] = s1; other[1][32 * grp + lane] = s2; }
+      __syncthreads();
+      if (part == 0 && half == 0) { s1 += other[0][32 * grp + lane]; s2 += other[1][32 * grp + lane]; }
+    }
+    if (part == 0 && half == 0 && kj < len) { out1[ubase + kj] = s1; out2[ubase + kj] = s2; }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// pass 1 with the attention output O_i = sum_j P[i,j] v_j (see prefill_rows_out_mfma for the operand layouts).  fp32:
+// the probabilities are taken apart into planes like V, the six products of 32 keys run on a chain of their own and are
+// added to the output once, so an output component sees one rounding per 32 keys.
+template <int DT, int D, int PARTS>
+__global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void prefill_rows_out_planes(PrefillArgs a) {
+  using P = Planes<DT, D, kRowsSmall<DT, D>>;
+  constexpr int kOwn = Shares<PARTS>::kOwn, GROUPS = Shares<PARTS>::GROUPS;
+  constexpr int NBUF = DT == kBF16 ? 2 : 1;  // fp32: one tile of K and V planes fills what two workgroups leave each other
+  constexpr int DB = D / 32;
+  __shared__ __attribute__((aligned(16))) char tilesK[NBUF][P::TILE];
+  __shared__ __attribute__((aligned(16))) char tilesV[NBUF][P::TILEV];
+  __shared__ float other[2][PARTS == 2 ? GROUPS * kWave : 1];
+  __shared__ int odd_s, odd_v;
+  int u, blk_id;
+  if (!locate_heads(a.units, a.group, a.pairs, u, blk_id)) return;
+  const int uk = u / a.group;
+  const int len = a.len[uk];
+  const int n_blocks = (len + kOwn - 1) / kOwn;
+  if (blk_id >= n_blocks) return;
+  const int blk = n_blocks - 1 - blk_id;  // long rows first
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int half = lane >> 5, grp = wave % GROUPS, part = wave / GROUPS;
+  const size_t ubase = static_cast<size_t>(u) * a.L_max;
+  const size_t kbase = static_cast<size_t>(uk) * a.L_max;
+  const char* Kb = static_cast<const char*>(a.K) + kbase * P::IN_ROW;
+  const char* Vb = static_cast<const char*>(a.V) + kbase * P::IN_ROW;
+  const float sc = a.scale_log2;
+  const int w = a.recency_window;
+  const float rb = a.recency_bias_log2;
+  const int q0 = blk * kOwn;
+  const int qw0 = q0 + 32 * grp;
+  const int qi = qw0 + (lane & 31);
+  if (threadIdx.x == 0) odd_s = odd_v = 0;
+  Pieces<DT, D, P::TR> stK, stV;
+  stK.load(Kb, 0, len - 1);
+  stV.load(Vb, 0, len - 1);
+  __syncthreads();
+  Owned<DT, D> own;
+  bool odd = own.load(static_cast<const char*>(a.Q) + ubase * P::IN_ROW, qi, len - 1);
+  float m = -INFINITY, l = 0.0f;
+  f32x16 o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) o[db] = f32x16{0};
+  // transpose reads of a V^T fragment: 16-lane group g reads columns 16 (g % 2) .. +15, key rows 4 (g / 2) .. +3
+  const int i16 = lane & 15, g16 = lane >> 4;
+  const int tr_off = ((g16 >> 1) * 4 + (i16 >> 2)) * P::ROWV + ((g16 & 1) * 16 + (i16 & 3) * 4) * 2;
+
+  const int n_tiles = (min(len, q0 + kOwn) - 1) / P::TR + 1;
+  for (int t = 0; t < n_tiles; ++t) {
+    char* const tileK = tilesK[NBUF == 2 ? t & 1 : 0];
+    char* const tileV = tilesV[NBUF == 2 ? t & 1 : 0];
+    if (NBUF == 1 && t > 0) __syncthreads();  // everybody is done with the previous tile
+    odd |= stK.store(tileK);
+    if (DT == kF32 && odd) odd_s = 1;
+    if (stV.store_values(tileV)) odd_v = 1;
+    __syncthreads();
+    if (t + 1 < n_tiles) {
+      stK.load(Kb, (t + 1) * P::TR, len - 1);
+      stV.load(Vb, (t + 1) * P::TR, len - 1);
+    }
+    const bool odd_tile = DT == kF32 && __builtin_amdgcn_readfirstlane(odd_s) != 0;
+    const bool odd_values = __builtin_amdgcn_readfirstlane(odd_v) != 0;
+#pragma unroll
+    for (int i = 0; i < P::SUBS / PARTS; ++i) {
+      const int sub = part + PARTS * i;
+      const int kb = t * P::TR + sub * 32;
+      if (kb > qw0 + 31) continue;  // wholly above the diagonal for every query of this wave
+      const f32x16 s = score_tile<P::TR>(odd_tile, tileK, sub, own);
+      // ---- probabilities against the reference m (lazily raised: see prefill_rows_out_mfma) and their sum
+      const bool interior = kb + 31 + w <= qw0;
+      float pv[16];
+      float sum = 0.0f;
+      bool done = false;
+      if (interior) {
+        const float neg = -m;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          pv[r] = fast_exp2(fmaf(s[r], sc, neg));
+          sum += pv[r];
+        }
+        done = __builtin_amdgcn_ballot_w64(!(sum <= 0x1p16f)) == 0;
+      }
+      if (!done) {
+        float mb = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float x = s[r] * sc;
+          if (!interior) {
+            const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
+            if (w > 0 && qi - key < w) x += rb;
+            if (key > qi) x = -INFINITY;
+          }
+          pv[r] = x;
+          mb = fmaxf(mb, x);
+        }
+        mb = fmaxf(mb, __shfl_xor(mb, 32, kWave));  // both lane halves feed one matrix product: one reference
+        const float m_new = fmaxf(m, mb);
+        const float ref = m_new > -INFINITY ? m_new : 0.0f;  // no finite logit yet: every term is 2^-inf = 0
+        if (__any(m_new > m)) {
+          const float alpha = m_new > -INFINITY ? fast_exp2(m - m_new) : 1.0f;
+          l *= alpha;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+        }
+        m = m_new;
+        sum = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          pv[r] = fast_exp2(pv[r] - ref);
+          sum += pv[r];
+        }
+      }
+      l += sum;
+      bf16x8 pf[P::NP][2];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        pf[0][r >> 3][r & 7] = static_cast<__bf16>(pv[r]);
+        if constexpr (DT == kF32) {
+          const float r1 = pv[r] - static_cast<float>(pf[0][r >> 3][r & 7]);
+          pf[1][r >> 3][r & 7] = static_cast<__bf16>(r1);
+          pf[2][r >> 3][r & 7] = static_cast<__bf16>(r1 - static_cast<float>(pf[1][r >> 3][r & 7]));
+        }
+      }
+      // ---- O^T += V^T . P^T, two 16-key steps x DB blocks of 32 head dimensions
+      auto values = [&](int plane, int ks, int db) {
+        const char* vt = tileV + plane * P::PLANEV + (sub * 32 + ks * 16) * P::ROWV + tr_off + db * 64;
+        const uint2 lo = lds_read_transposed(vt), hi = lds_read_transposed(vt + 8 * P::ROWV);
+        return make_uint4(lo.x, lo.y, hi.x, hi.y);
+      };
+      auto multiply = [&](auto odd_tag) {
+        constexpr bool ODD = decltype(odd_tag)::value;
+        if constexpr (DT == kBF16) {
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+              const uint4 v = values(0, ks, db);
+              o[db] = mm(ODD ? finite8(v) : v, __builtin_bit_cast(uint4, pf[0][ks]), o[db]);
+            }
+        } else {
+          auto p = [&](int plane, int ks) { return __builtin_bit_cast(uint4, pf[plane][ks]); };
+#pragma unroll
+          for (int d2 = 0; d2 < DB; d2 += 2) {  // two chains at a time
+            f32x16 c[2];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {  // the small terms first, the hi x hi products last
+              uint4 h[2], mid[2], lo[2];
+#pragma unroll
+              for (int e = 0; e < 2; ++e) {
+                h[e] = values(0, ks, d2 + e);
+                if (ODD) h[e] = finite8(h[e]);
+                mid[e] = values(1, ks, d2 + e);
+                lo[e] = values(2, ks, d2 + e);
+              }
+#pragma unroll
+              for (int e = 0; e < 2; ++e) c[e] = mm(lo[e], p(0, ks), ks == 0 ? f32x16{0} : c[e]);
+#pragma unroll
+              for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(2, ks), c[e]);
+#pragma unroll
+              for (int e = 0; e < 2; ++e) c[e] = mm(mid[e], p(1, ks), c[e]);
+#pragma unroll
+              for (int e = 0; e < 2; ++e) c[e] = mm(mid[e], p(0, ks), c[e]);
+#pragma unroll
+              for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(1, ks), c[e]);
+#pragma unroll
+              for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(0, ks), c[e]);
+            }
+            o[d2] += c[0];
+            o[d2 + 1] += c[1];
+          }
+        }
+      };
+      if (!odd_values) {
+        multiply(std::integral_constant<bool, false>{});
+      } else {
+        multiply(std::integral_constant<bool, true>{});
+        // infinities and NaN of V, one key at a time, for the queries that see the key
+        for (int key = 0; key < 32; ++key) {
+          float mine = 0.0f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mine = (8 * (r >> 2) + (r & 3)) == (key & ~4) ? pv[r] : mine;
+          const float pk = __shfl(mine, (lane & 31) + 32 * ((key >> 2) & 1), kWave);
+          if (kb + key > qi) continue;
+          const char* vr = tileV + (sub * 32 + key) * P::ROWV;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const uint32_t hv = *reinterpret_cast<const uint16_t*>(vr + (db * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * 2);
+              if ((hv & 0x7f80u) == 0x7f80u) o[db][r] += pk * bf16_value(hv);
+            }
+        }
+      }
+    }
+  }
+  l += __shfl_xor(l, 32, kWave);  // each lane half summed different keys of the same query
+  if constexpr (PARTS == 2) {  // waves w and w + 2 hold the sums over every other 32 keys of the same queries
+    static_assert(NBUF * P::TILE >= GROUPS * DB * 16 * kWave * 4, "the partner's output fits the K tiles");
+    float* const mo = reinterpret_cast<float*>(&tilesK[0][0]) + grp * (DB * 16 * kWave) + lane;
+    __syncthreads();  // everybody is done with the tiles
+    if (part == 1) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mo[(db * 16 + r) * kWave] = o[db][r];
+      other[0][grp * kWave + lane] = m;
+      other[1][grp * kWave + lane] = l;
+    }
+    __syncthreads();
+    if (part == 1) return;
+    const float m1 = other[0][grp * kWave + lane], l1 = other[1][grp * kWave + lane];
+    const float M = fmaxf(m, m1);
+    const float w0 = m > -INFINITY ? fast_exp2(m - M) : 0.0f, w1 = m1 > -INFINITY ? fast_exp2(m1 - M) : 0.0f;
+    l = l * w0 + l1 * w1;
+    m = M;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        o[db][r] = (w0 > 0.0f ? o[db][r] * w0 : 0.0f) + (w1 > 0.0f ? mo[(db * 16 + r) * kWave] * w1 : 0.0f);
+  }
+  if (qi < len) {
+    if (half == 0) a.lse[ubase + qi] = m + log2f(l);
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const size_t at = (ubase + qi) * D + db * 32 + 8 * g4 + 4 * half;
+        const float v0 = o[db][4 * g4] * inv, v1 = o[db][4 * g4 + 1] * inv, v2 = o[db][4 * g4 + 2] * inv, v3 = o[db][4 * g4 + 3] * inv;
+        if constexpr (DT == kBF16) {
+          *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.O) + at) =
+              make_uint2(f32_to_bf16(v0) | (static_cast<uint32_t>(f32_to_bf16(v1)) << 16),
+                         f32_to_bf16(v2) | (static_cast<uint32_t>(f32_to_bf16(v3)) << 16));
+        } else {
+          *reinterpret_cast<float4*>(static_cast<float*>(a.O) + at) = make_float4(v0, v1, v2, v3);
+        }
+      }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+struct Launch { int pairs, paired, split, parts; };
+
+// Schedule of a pass over `streams` (unit, head) streams of up to L_max rows.  `target` workgroups fill the chip (all of
+// them resident); the base schedule has one per pair of a long and a short block of 128 owned rows.  Too few: the waves of
+// a workgroup share 64 rows (parts = 2), and / or two workgroups take half of a block's streamed tiles each (split = 2, where
+// the planes of the second share have room), and single blocks instead of pairs when even that leaves compute units idle.
+Launch schedule(long long streams, int L_max, int target, bool may_part, bool may_split, bool part_first) {
+  const int n128 = (L_max + 127) / 128;
+  const long long base = streams * ((n128 + 1) / 2);
+  Launch l = {0, 1, 1, 1};
+  if (base < target) {
+    const bool both = 2 * base < target;
+    if (may_part && (part_first || both || !may_split)) l.parts = 2;
+    if (may_split && (!part_first || both || !may_part) && n128 > 1) l.split = 2;
+  }
+  const int n_blocks = l.parts == 2 ? (L_max + 63) / 64 : n128;
+  l.paired = streams * ((n_blocks + 1) / 2) * l.split >= 256 ? 1 : 0;
+  l.pairs = l.paired ? (n_blocks + 1) / 2 : n_blocks;
+  return l;
+}
+unsigned ids(const PrefillArgs& a, int heads, const Launch& l) {
+  return static_cast<unsigned>((a.units + 7) / 8 * 8 * heads * l.pairs * l.split);
+}
+
+template <int DT, int D, int PARTS>
+void launch_rows(const PrefillArgs& b, unsigned n, hipStream_t s) {
+  if (b.O != nullptr) hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, PARTS>), dim3(n), dim3(kThreads), 0, s, b);
+  else hipLaunchKernelGGL((prefill_rows_planes<DT, D, PARTS>), dim3(n), dim3(kThreads), 0, s, b);
+}
+template <int DT, int D, int PARTS>
+void launch_columns(const PrefillArgs& b, unsigned n, hipStream_t s) {
+  switch (b.group) {
+    case 1: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 1>), dim3(n), dim3(kThreads), 0, s, b); break;
+    case 2: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 2>), dim3(n), dim3(kThreads), 0, s, b); break;
+    case 4: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 4>), dim3(n), dim3(kThreads), 0, s, b); break;
+    case 8: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 8>), dim3(n), dim3(kThreads), 0, s, b); break;
+    case 16: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 16>), dim3(n), dim3(kThreads), 0, s, b); break;
+    default: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 0>), dim3(n), dim3(kThreads), 0, s, b); break;
+  }
+}
+
+template <int DT, int D>
+hipError_t launch_t(const PrefillArgs& a, hipStream_t s) {
+  constexpr int kShared = kRows<DT, D> > 32 ? 2 : 1;  // a tile of one sub-tile has nothing to share
+  constexpr int kTarget = DT == kBF16 ? 1024 : 512;
+  constexpr bool kPartFirst = DT == kBF16;
+  const bool rows_simple = DT == kF32 && a.O != nullptr && prefill_is_tiny(a);
+  if (rows_simple) {
+    launch_prefill_rows_simple(DT, D, a, s);
+  } else if (!a.skip_rows) {
+    ProfScope ps(kProfPrefillRows, s);
+    Launch l = schedule(static_cast<long long>(a.units) * a.group, a.L_max, kTarget, kShared == 2, a.group == 1, kPartFirst);
+    if (a.O != nullptr) l = {0, 0, 1, kShared};
+    if (a.O != nullptr) l.pairs = (a.L_max + 128 / l.parts - 1) / (128 / l.parts);
+    PrefillArgs b = a;
+    b.pairs = l.pairs; b.paired = l.paired; b.ksplit = l.split;
+    if (l.parts == 2) launch_rows<DT, D, kShared>(b, ids(a, a.group, l), s);
+    else launch_rows<DT, D, 1>(b, ids(a, a.group, l), s);
+    if (l.split > 1) launch_merge_key_shares(b, s);
+  }
+  ProfScope ps(kProfPrefillColumns, s);
+  const Launch l = schedule(a.units, a.L_max, kTarget, kShared == 2, true, kPartFirst);
+  PrefillArgs b = a;
+  b.pairs = l.pairs; b.paired = l.paired; b.qsplit = l.split;
+  if (l.parts == 2) launch_columns<DT, D, kShared>(b, ids(a, 1, l), s);
+  else launch_columns<DT, D, 1>(b, ids(a, 1, l), s);
+  if (l.split > 1) launch_sum_query_shares(b, s);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prefill_attention_planes(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s) {
+  if (dtype == kF32 && head_dim == 64) return launch_t<kF32, 64>(a, s);
+  if (dtype == kF32 && head_dim == 128) return launch_t<kF32, 128>(a, s);
+  if (dtype == kBF16 && head_dim == 64) return launch_t<kBF16, 64>(a, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace roco

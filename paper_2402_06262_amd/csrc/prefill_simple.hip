@@ -1,6 +1,7 @@
 // Prefill attention statistics on the plain vector ALUs, for every supported dtype / head_dim.
 //
-// This is the general path (fp32 storage, head_dim 64) and the cross-check for the matrix-core path.
+// The path of fp32 prompts too small for the matrix cores to pay (see prefill_is_tiny), of bf16 / 128 prompts above 4M
+// tokens, and the cross-check for the matrix-core paths.
 // Two passes, because a column statistic needs the final normaliser of every row it sums over:
 //   pass 1: one wave per query row i streams keys 0..i with an online softmax and stores the row's base-2
 //           log-sum-exp (and the attention output, if asked)                     (section 2.1, eq. 1; causal)
@@ -128,13 +129,16 @@ __global__ __launch_bounds__(kThreads) void prefill_columns_simple(PrefillArgs a
 }
 
 template <int DT, int D>
+void launch_rows_t(const PrefillArgs& a, hipStream_t s) {
+  ProfScope ps(kProfPrefillRows, s);
+  const dim3 grid((a.L_max + kWaves - 1) / kWaves, static_cast<unsigned>(a.units) * a.group);
+  hipLaunchKernelGGL((prefill_rows_simple<DT, D>), grid, dim3(kThreads), 0, s, a);
+}
+
+template <int DT, int D>
 hipError_t launch_t(const PrefillArgs& a, hipStream_t s) {
   const dim3 grid((a.L_max + kWaves - 1) / kWaves, a.units);
-  if (!a.skip_rows) {
-    ProfScope ps(kProfPrefillRows, s);
-    const dim3 rows_grid(grid.x, static_cast<unsigned>(a.units) * a.group);
-    hipLaunchKernelGGL((prefill_rows_simple<DT, D>), rows_grid, dim3(kThreads), 0, s, a);
-  }
+  if (!a.skip_rows) launch_rows_t<DT, D>(a, s);
   {
     ProfScope ps(kProfPrefillColumns, s);
     hipLaunchKernelGGL((prefill_columns_simple<DT, D>), grid, dim3(kThreads), 0, s, a);
@@ -231,6 +235,11 @@ hipError_t launch_prefill_last_row(int dtype, int head_dim, const PrefillArgs& a
   else if (dtype == kBF16 && head_dim == 128) hipLaunchKernelGGL((prefill_last_row<kBF16, 128>), grid, block, 0, s, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+void launch_prefill_rows_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s) {
+  if (dtype == kF32 && head_dim == 64) launch_rows_t<kF32, 64>(a, s);
+  else launch_rows_t<kF32, 128>(a, s);
 }
 
 hipError_t launch_prefill_attention_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s) {

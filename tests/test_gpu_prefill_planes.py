@@ -1,0 +1,145 @@
+"""The matrix-core prefill of fp32 storage and of head_dim 64: edges of its tiles (32 streamed rows, 64 / 128 rows per tile,
+blocks of 64 / 128 owned rows), both ways of sharing a block between waves and workgroups, every way of summing the heads of
+a group, and inputs that are not finite or near the ends of fp32's range."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import test_gpu_gqa as TG
+import test_gpu_parity as TP
+from inputs import round_to_bf16
+from oracle import roco_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+FORMS = [("f32", 64), ("bf16", 64), ("f32", 128)]
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+@pytest.mark.parametrize("L,lens", [(65, [65, 1, 64, 33, 32]), (130, [130, 129, 128, 127, 63]), (300, [300, 257, 256, 191, 2])])
+@pytest.mark.parametrize("want_out", [False, True])
+def test_edges_of_tiles_and_blocks(dtype, d, L, lens, want_out):
+    B = max(16, L // 3)
+    TP.run_workload(dtype, d, 5, lens, L, B, 7, 2, seed=71 + L, want_out=want_out, tag=f"planes-{dtype}-{d}-{L}")
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+@pytest.mark.parametrize("units,L", [(1, 1030), (140, 200), (300, 260)])
+def test_every_schedule(dtype, d, units, L):
+    """Few units (shared blocks, halves of the streamed tiles), some, and enough for pairs of blocks per workgroup."""
+    rng = np.random.default_rng(units)
+    lens = [L] + [int(x) for x in rng.integers(L // 2, L + 1, size=units - 1)]
+    P = TP._parity()
+    B, s, sc = L // 2, 9, 1.0 / math.sqrt(d)
+    Q, K, V = (rng.standard_normal((units, L, d)).astype(np.float32) for _ in range(3))
+    if dtype == "bf16":
+        Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
+    sess = P.make_session(units, d, B, s, dtype, 0.0, 24, 0.5)
+    for want_out in (False, True):
+        g = P.gpu_prefill(sess, Q, K, V, lens, want_out)
+        for u in (0, units // 2, units - 1):
+            P.check_prefill_unit(g, u, Q[u], K[u], V[u], lens[u], B, s, sc, dtype, 24, 0.5, want_out)
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+@pytest.mark.parametrize("group", [2, 3, 4, 8, 16])
+def test_heads_of_a_group(dtype, d, group):
+    for want_out in (False, True):
+        TG.run_grouped_prefill(dtype, d, group, [150, 97], 150, 48, 6, seed=90 + group, steps=2, recency=group == 8,
+                               tag=f"planes-group-{group}", want_out=want_out)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("f32", 128)])
+def test_thresholded_count(dtype, d):
+    TP.run_workload(dtype, d, 3, [200, 131, 64], 200, 60, 60, 2, seed=77, policy=orc.Policy("aqas", "all"), tag="planes-count")
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+@pytest.mark.parametrize("group", [3, 4])
+def test_thresholded_count_of_a_group(dtype, d, group, monkeypatch):
+    """Against the vector-ALU passes: a count may differ by the queries whose probability is within rounding of the mean."""
+    P = TP._parity()
+    rng = np.random.default_rng(8)
+    units, L, B = 2, 190, 190
+    Q = rng.standard_normal((units, group, L, d)).astype(np.float32) + 0.25
+    K, V = (rng.standard_normal((units, L, d)).astype(np.float32) for _ in range(2))
+    if dtype == "bf16":
+        Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
+    res = []
+    for simple in ("1", "0"):
+        monkeypatch.setenv("ROCO_PREFILL_SIMPLE", simple)
+        sess = P.make_session(units, d, B, B, dtype, policy=orc.Policy("aqas", "all"))
+        res.append(P.gpu_prefill_gqa(sess, group, Q, K, V, [L, L - 33])["stats"])
+    np.testing.assert_allclose(res[1][:, 0], res[0][:, 0], rtol=1e-5, atol=1e-7)
+    assert np.max(np.abs(res[1][:, 1] - res[0][:, 1])) <= 1.0
+    assert np.mean(res[1][:, 1] != res[0][:, 1]) < 0.01
+
+
+def _both_paths(monkeypatch, dtype, d, Q, K, V, lens, B=96, s=16):
+    P = TP._parity()
+    units, L = K.shape[0], K.shape[1]
+    out = []
+    for simple in ("1", "0"):
+        monkeypatch.setenv("ROCO_PREFILL_SIMPLE", simple)
+        sess = P.make_session(units, d, B, s, dtype)
+        out.append(P.gpu_prefill(sess, Q, K, V, lens, True))
+    return out
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+def test_infinities_and_nan_go_where_a_plain_product_sends_them(dtype, d, monkeypatch):
+    """An element that is not finite reaches the rows that see it and no others, on the matrix cores as on the vector ALUs.
+    B > L: nothing is evicted, so positions can be compared one to one."""
+    rng = np.random.default_rng(5)
+    units, L, B = 6, 1100, 1200  # (large enough for the matrix-core row pass with output)
+    Q, K, V = (rng.standard_normal((units, L, d)).astype(np.float32) for _ in range(3))
+    if dtype == "bf16":
+        Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
+    Q[:, :, 3] = 1.0
+    K[0, 40, 3] = -np.inf       # a key no query attends (query 40 included)
+    K[1, 700, 3] = np.inf       # rows from 700 on are NaN
+    V[2, 555, 7] = np.inf       # dimension 7 of the rows from 555 on
+    V[2, 600, 8] = -np.inf
+    V[3, 65, d - 1] = np.nan
+    Q[4, 300] = np.nan          # one row, and the statistics of the keys up to it
+    K[5, 10, 5] = np.nan
+    want, got = _both_paths(monkeypatch, dtype, d, Q, K, V, [L] * 5 + [L - 3], B=B)
+    tol = 2e-2 if dtype == "bf16" else 1e-5
+    for key in ("O", "stats"):
+        a, b = np.asarray(want[key], np.float64), np.asarray(got[key], np.float64)
+        assert np.array_equal(np.isnan(a), np.isnan(b)), key
+        assert np.array_equal(np.isinf(a), np.isinf(b)), key
+        fine = np.isfinite(a)
+        assert np.array_equal(a[np.isinf(a)], b[np.isinf(b)]), key
+        np.testing.assert_allclose(b[fine], a[fine], rtol=tol, atol=tol * 0.1, err_msg=key)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_ends_of_the_fp32_range(d, monkeypatch):
+    """Key elements up to the largest fp32 value (whose first plane may not round up to infinity) against the smallest
+    normal one, keys and queries scaled against each other, large and small values: results are of ordinary relative size."""
+    rng = np.random.default_rng(6)
+    units, L, B = 4, 1024, 1024
+    Q, K, V = (rng.standard_normal((units, L, d)).astype(np.float32) for _ in range(3))
+    K[0, :, 3] = rng.uniform(1e38, 3.4028e38, L).astype(np.float32) * np.sign(K[0, :, 3])
+    Q[0, :, 3] = np.float32(2.0 ** -126)
+    K[1] *= np.float32(2.0 ** -60)
+    Q[1] *= np.float32(2.0 ** 60)
+    V[2] *= np.float32(1e30)
+    V[3] *= np.float32(1e-30)
+    want, got = _both_paths(monkeypatch, "f32", d, Q, K, V, [L] * units, B=B)
+    for key in ("O", "stats"):
+        a, b = np.asarray(want[key], np.float64), np.asarray(got[key], np.float64)
+        assert np.array_equal(np.isfinite(a), np.isfinite(b)), key
+        fine = np.isfinite(a)
+        # 1e-5 relative to the row's largest: sums of up to 1024 fp32 terms, sqrt(1024) * 2^-24 and a margin of five
+        scale = np.max(np.abs(np.where(fine, a, 0.0)), axis=-1, keepdims=True)
+        assert np.all(np.abs(np.where(fine, b - a, 0.0)) <= 1e-5 * np.maximum(scale, 1e-30)), key
+
+
+def test_tiny_prompts_take_the_vector_passes_and_agree(monkeypatch):
+    """Both sides of the size rules of fp32 prompts: 64 tokens and 2^19 = units x heads x L^2."""
+    for units, L in ((2, 64), (2, 65), (8, 256), (9, 256)):
+        TP.run_workload("f32", 64, units, [L] * units, L, L // 2, 5, 1, seed=units + L, tag="planes-tiny")
