@@ -42,10 +42,12 @@ constexpr int kQ = 32;            // query rows per matrix tile
 static_assert(kMaxBlock == 2 * kQ, "a step holds at most two tiles of query rows");
 
 // ------------------------------------------------------------------------------------------------
-template <int NT>
-__global__ __launch_bounds__(NT) void block_prepare(BlockArgs a) {
+// LDS: the ranking keys are in LDS (B <= kMaxDecodeBudgetLds), here and in block_finish.  The two selections share one copy
+// of the search: a launch starts with a cold instruction cache.
+template <int NT, bool LDS>
+__global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
   extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
-  __shared__ uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
   __shared__ uint32_t scan_sh[NT / kWave + 1];
   __shared__ int slot_of[kMaxBlock];
   const int u = blockIdx.x, tid = threadIdx.x;
@@ -58,21 +60,29 @@ __global__ __launch_bounds__(NT) void block_prepare(BlockArgs a) {
   float* cnt = acc2 + B;
   int32_t* pos = a.pos + static_cast<size_t>(u) * B;
   int32_t* bidx = a.blk_idx + static_cast<size_t>(u) * B;
-  uint32_t* var_key = (B <= kMaxDecodeBudgetLds) ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
-  uint32_t* mas_key = var_key + B;
+  uint32_t* const var_key = LDS ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
+  uint32_t* const mas_key = var_key + B;
 
   if (tid < kMaxBlock) slot_of[tid] = 0;
   KSmallest scope = {0u, 0u}, out = {0u, 0u};
   // one eviction from a full cache: the victim was already chosen when the statistics were last updated
   const int hint = (E == 1 && n == B) ? a.next_slot[u] : -1;
   if (E > 0 && hint < 0) {
+#pragma unroll 1
     for (int i = tid; i < n; i += NT) ranking_keys(acc[i], acc2[i], cnt[i], pos[i], a.pol, mas_key[i], var_key[i]);
     __syncthreads();
     const uint32_t m = min(static_cast<uint32_t>(n), static_cast<uint32_t>(a.pol.scope_size(a.scope, n)) + static_cast<uint32_t>(E) - 1u);
-    scope = select_k_smallest<NT>([&](int i) { return var_key[i]; }, n, m, sel_sh);
-    out = select_k_smallest<NT>(
-        [&](int i) -> uint32_t { return scope.has(var_key[i], i) ? mas_key[i] : 0xffffffffu; }, n,
-        static_cast<uint32_t>(E), sel_sh);
+#pragma unroll 1
+    for (int phase = 0; phase < 2; ++phase) {
+      const KSmallest r = select_k_smallest<NT>(
+          [&](int i) -> uint32_t {
+            const uint32_t vk = var_key[i];
+            return phase == 0 ? vk : scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
+          },
+          n, phase == 0 ? m : static_cast<uint32_t>(E), sel_sh);
+      if (phase == 0) scope = r;
+      else out = r;
+    }
   }
   auto is_target = [&](int j) -> bool {
     if (j >= n) return j < n_new;  // still-empty slot taken by the block
@@ -85,10 +95,12 @@ __global__ __launch_bounds__(NT) void block_prepare(BlockArgs a) {
   const int c = (B + NT - 1) / NT;
   const int lo = min(B, tid * c), hi = min(B, lo + c);
   uint32_t mine = 0;
+#pragma unroll 1
   for (int j = lo; j < hi; ++j) mine += (j < n_new && is_target(j)) ? 1u : 0u;
   uint32_t total;
   uint32_t rank = block_exclusive_scan<NT>(mine, scan_sh, total);
   const int qp0 = a.qpos0[u];
+#pragma unroll 1
   for (int j = lo; j < hi; ++j) {
     int bi = -1;
     if (j < n_new && is_target(j) && rank < static_cast<uint32_t>(b)) {
@@ -108,6 +120,7 @@ __global__ __launch_bounds__(NT) void block_prepare(BlockArgs a) {
   // the block's K / V rows go into their slots: 16 bytes per lane
   const int lpr = a.row_bytes / 16;  // lanes per row: 8, 16 or 32
   const size_t in_base = static_cast<size_t>(u) * b * a.row_bytes;
+#pragma unroll 1
   for (int i = tid / lpr; i < b; i += NT / lpr) {
     const size_t dst = (static_cast<size_t>(u) * B + slot_of[i]) * a.row_bytes + (tid % lpr) * 16;
     const size_t src = in_base + static_cast<size_t>(i) * a.row_bytes + (tid % lpr) * 16;
@@ -637,16 +650,19 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
 // One workgroup per unit: it walks all slots of the unit two per thread and sweep, keeps the ranking keys in LDS and
 // chooses the next victim itself.  (Spreading the update over slot chunks and selecting in a launch of its own
 // measured slower for every number of query rows: the extra launch costs more than the longer sweep.)
-// CHUNKED: the logits of four query rows are loaded at a time (chosen by the host where it measured faster: grouped
-// queries, and more than 32 rows).
-template <int DT, int D, bool CHUNKED>
-__global__ __launch_bounds__(kFinThreads) void block_finish(BlockArgs a) {
+// R: logits of this many query rows are loaded at a time.  A larger R hides more of their latency in a longer loop body,
+// which has to be fetched first (a launch starts with a cold instruction cache): of 2 / 4 / 8, 64 rows of 4 heads on 128 units
+// took 51 / 46 / 44 us, 16 rows of one head on 512 units 28.7 / 29.7 / 30.5.
+template <int DT, int D, int R, bool LDS>
+__global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   constexpr int NT = kFinThreads;
   constexpr int kSlots = 2 * NT;  // slots per sweep
   extern __shared__ uint32_t lds_keys[];  // [2][B] ranking keys when B <= kMaxDecodeBudgetLds
-  __shared__ uint32_t sel_sh[kSelectLdsWords];
-  __shared__ unsigned long long best_sh[NT / kWave];
-  __shared__ float Mq[kMaxBlock], invq[kMaxBlock];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ uint2 best_sh[NT / kWave];
+  __shared__ float2 norm[kMaxBlock];  // reference and 1 / sum of every query row
+  __shared__ float2 part_ml[kMaxBlockSplits * kMaxBlock];
+  __shared__ float weight[kMaxBlockSplits * kMaxBlock];
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B, nq = a.queries, S = a.splits, QR = a.qrows;
   int n = a.n_used[u];
@@ -663,16 +679,28 @@ __global__ __launch_bounds__(kFinThreads) void block_finish(BlockArgs a) {
   const float* pl = a.part_l + static_cast<size_t>(u) * S * QR;
   const float* po = a.part_o + static_cast<size_t>(u) * S * QR * D;
 
-  if (tid < nq) {  // per query row: merge the splits' normalisers in split order
-    float M = -INFINITY;
-    for (int s = 0; s < S; ++s) M = fmaxf(M, pm[s * QR + tid]);
-    float L = 0.0f;
-    for (int s = 0; s < S; ++s) {
-      const float ms = pm[s * QR + tid];
-      L += (ms > -INFINITY) ? pl[s * QR + tid] * fast_exp2(ms - M) : 0.0f;
+  // The splits' normalisers of a query row come in with one load per (split, row) and are merged from LDS in split order;
+  // a loop of dependent trips to memory per row would cost more than the rest of the merge.
+  static_assert(kMaxBlockSplits * kMaxBlock <= NT, "one thread per (split, row)");
+  const int my_row = tid & (QR - 1);  // (split, row) in the order of the planes
+  const bool merges = tid < S * QR && my_row < nq;
+  float2 mine = make_float2(-INFINITY, 0.0f);
+  if (merges) {
+    mine = make_float2(pm[tid], pl[tid]);
+    part_ml[tid] = mine;
+  }
+  __syncthreads();
+  if (merges) {
+    float M = -INFINITY, L = 0.0f;
+#pragma unroll 1
+    for (int i = my_row; i < S * QR; i += QR) M = fmaxf(M, part_ml[i].x);
+#pragma unroll 1
+    for (int i = my_row; i < S * QR; i += QR) {
+      const float2 ml = part_ml[i];
+      L += (ml.x > -INFINITY) ? ml.y * fast_exp2(ml.x - M) : 0.0f;
     }
-    Mq[tid] = M;
-    invq[tid] = 1.0f / L;
+    weight[tid] = (mine.x > -INFINITY) ? fast_exp2(mine.x - M) : 0.0f;
+    if (tid < nq) norm[tid] = make_float2(M, 1.0f / L);
   }
   __syncthreads();  // every thread has read n_used and next_slot
   if (a.single && tid == 0) {
@@ -683,15 +711,23 @@ __global__ __launch_bounds__(kFinThreads) void block_finish(BlockArgs a) {
     if (a.evicted_slot) a.evicted_slot[u] = evicted ? fresh : -1;
     if (a.evicted_pos) a.evicted_pos[u] = evicted ? old_pos : -1;
   }
-  // outputs of this workgroup's query rows
+  // outputs: all splits' partials of an element are requested together
+#pragma unroll 1
   for (int idx = tid; idx < nq * D; idx += NT) {
     const int q = idx / D, dd = idx % D;
+    float part[kMaxBlockSplits];
+#pragma unroll
+    for (int s = 0; s < kMaxBlockSplits; ++s)
+      if (s < S) part[s] = po[(static_cast<size_t>(s) * QR + q) * D + dd];
     float o = 0.0f;
-    for (int s = 0; s < S; ++s) {
-      const float ms = pm[s * QR + q];
-      o += (ms > -INFINITY) ? po[(static_cast<size_t>(s) * QR + q) * D + dd] * fast_exp2(ms - Mq[q]) : 0.0f;
+#pragma unroll
+    for (int s = 0; s < kMaxBlockSplits; ++s) {
+      if (s < S) {
+        const float wgt = weight[s * QR + q];
+        o += wgt > 0.0f ? part[s] * wgt : 0.0f;
+      }
     }
-    store_elem<DT>(a.out, (static_cast<size_t>(u) * nq + q) * D + dd, o * invq[q]);
+    store_elem<DT>(a.out, (static_cast<size_t>(u) * nq + q) * D + dd, o * norm[q].y);
   }
   // statistics: every slot receives, per block token that attended it, the head-mean of the probabilities
   float* acc = a.stats + static_cast<size_t>(u) * 3 * B;
@@ -699,10 +735,12 @@ __global__ __launch_bounds__(kFinThreads) void block_finish(BlockArgs a) {
   float* cnt = acc2 + B;
   const float* z = a.z + static_cast<size_t>(u) * QR * B;
   const bool full = n >= B;
-  uint32_t* var_key = (B <= kMaxDecodeBudgetLds) ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
-  uint32_t* mas_key = var_key + B;
+  uint32_t* const var_key = LDS ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
+  uint32_t* const mas_key = var_key + B;
   const bool by_pos = a.pol.needs_pos();
+  const bool squares = !a.pol.keeps_last_score() && !a.pol.counts_above_average();
   // B is a multiple of 4 on this path, so a pair of slots is inside [0, B).
+#pragma unroll 1
   for (int j = tid * 2; j < n; j += kSlots) {
   const int2 bi = a.single ? make_int2(-1, -1)
                                        : *reinterpret_cast<const int2*>(a.blk_idx + static_cast<size_t>(u) * B + j);
@@ -714,52 +752,34 @@ __global__ __launch_bounds__(kFinThreads) void block_finish(BlockArgs a) {
 #pragma unroll
   for (int e = 0; e < 2; ++e)
     if (j + e == fresh) { s1[e] = 0.0f; s2[e] = 0.0f; sc[e] = 0.0f; }  // the new token starts from zero
-  auto book = [&](const float* mean, int t) {  // token t of the block has attended: its head-mean goes to the slots
+  // The query rows (token-major, a token's heads side by side) are taken R at a time.
+  float mean[2] = {0.0f, 0.0f};  // sum over the query heads of the token under way of p
+  int t = 0, h = 0;
+#pragma unroll 1
+  for (int q0 = 0; q0 < nq; q0 += R) {
+    float2 zz[R];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      if (j + e < n && biv[e] <= t) {  // older tokens have index -1: attended by every row
-        const float p = mean[e] * inv_heads;  // group-wise averaged probability (exact for one head)
-        s1[e] += p;
-        s2[e] = a.pol.second_statistic(s2[e], p, static_cast<float>(n - a.block + t + 1));  // what row t attended
-        sc[e] += 1.0f;
-      }
-    }
-  };
-  if (!CHUNKED) {
-    for (int t = 0; t < a.block; ++t) {
-      float mean[2] = {0.0f, 0.0f};  // sum over the token's query heads of p
-      for (int h = 0; h < heads; ++h) {
-        const int q = t * heads + h;
-        const float2 zz = *reinterpret_cast<const float2*>(z + static_cast<size_t>(q) * B + j);
-        const float M = Mq[q], inv = invq[q];
-        mean[0] += fast_exp2(zz.x - M) * inv;
-        mean[1] += fast_exp2(zz.y - M) * inv;
-      }
-      book(mean, t);
-    }
-  } else {
-    // The query rows (token-major, a token's heads side by side) are taken four at a time, so that four logit
-    // loads are in flight per thread instead of one.
-    float mean[2] = {0.0f, 0.0f};  // sum over the query heads of the token under way of p
-    int t = 0, h = 0;
-    for (int q0 = 0; q0 < nq; q0 += 4) {
-      float2 zz[4];
+    for (int i = 0; i < R; ++i)
+      zz[i] = *reinterpret_cast<const float2*>(z + static_cast<size_t>(min(q0 + i, nq - 1)) * B + j);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        zz[i] = *reinterpret_cast<const float2*>(z + static_cast<size_t>(min(q0 + i, nq - 1)) * B + j);
+    for (int i = 0; i < R; ++i) {
+      if (q0 + i < nq) {
+        const float2 mi = norm[q0 + i];
+        mean[0] += fast_exp2(zz[i].x - mi.x) * mi.y;
+        mean[1] += fast_exp2(zz[i].y - mi.x) * mi.y;
+        if (++h == heads) {  // the token's last head: its head-mean goes to the slots it attended
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int q = q0 + i;
-        if (q < nq) {
-          const float M = Mq[q], inv = invq[q];
-          mean[0] += fast_exp2(zz[i].x - M) * inv;
-          mean[1] += fast_exp2(zz[i].y - M) * inv;
-          if (++h == heads) {  // the token's last head
-            book(mean, t);
-            mean[0] = mean[1] = 0.0f;
-            h = 0;
-            ++t;
+          for (int e = 0; e < 2; ++e) {
+            if (j + e < n && biv[e] <= t) {  // older tokens have index -1: attended by every row
+              const float p = mean[e] * inv_heads;  // group-wise averaged probability (exact for one head)
+              s1[e] += p;
+              s2[e] = squares ? s2[e] + p * p : a.pol.second_statistic(s2[e], p, static_cast<float>(n - a.block + t + 1));
+              sc[e] += 1.0f;
+            }
+            mean[e] = 0.0f;
           }
+          h = 0;
+          ++t;
         }
       }
     }
@@ -794,18 +814,20 @@ static bool single_step_off() {
   return e != nullptr && e[0] == '0';
 }
 
+template <int DT, int D, int R>
+void launch_block_finish(const BlockArgs& a, hipStream_t s) {
+  const size_t key_lds = key_lds_bytes(a.B);
+  // (if the limit is refused, the launch fails and is reported)
+  (void)allow_key_lds(reinterpret_cast<const void*>(block_finish<DT, D, R, true>), key_lds);
+  if (key_lds != 0) hipLaunchKernelGGL((block_finish<DT, D, R, true>), dim3(a.units), dim3(kFinThreads), key_lds, s, a);
+  else hipLaunchKernelGGL((block_finish<DT, D, R, false>), dim3(a.units), dim3(kFinThreads), 0, s, a);
+}
 template <int DT, int D>
 void launch_block_tail(const BlockArgs& a, hipStream_t s) {
   ProfScope ps(kProfBlockFinish, s);
-  const size_t key_lds = key_lds_bytes(a.B);
-  // (if the limit is refused, the launch fails and is reported)
-  if (a.heads > 1 || a.queries > 32) {
-    (void)allow_key_lds(reinterpret_cast<const void*>(block_finish<DT, D, true>), key_lds);
-    hipLaunchKernelGGL((block_finish<DT, D, true>), dim3(a.units), dim3(kFinThreads), key_lds, s, a);
-  } else {
-    (void)allow_key_lds(reinterpret_cast<const void*>(block_finish<DT, D, false>), key_lds);
-    hipLaunchKernelGGL((block_finish<DT, D, false>), dim3(a.units), dim3(kFinThreads), key_lds, s, a);
-  }
+  if (a.queries > 32) launch_block_finish<DT, D, 8>(a, s);
+  else if (a.heads > 1) launch_block_finish<DT, D, 4>(a, s);
+  else launch_block_finish<DT, D, 2>(a, s);
 }
 
 template <int DT, int D, int QMAX>
@@ -838,8 +860,8 @@ hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStrea
   // A single-token step on the matrix-core path needs no block_prepare.
   a.single = (a.block == 1 && dtype == kBF16 && head_dim == 128 && !single_step_off()) ? 1 : 0;
   const size_t key_lds = key_lds_bytes(a.B);
-  if (!allow_key_lds(reinterpret_cast<const void*>(block_prepare<512>), key_lds) ||
-      !allow_key_lds(reinterpret_cast<const void*>(block_prepare<kPrepThreads>), key_lds))
+  if (!allow_key_lds(reinterpret_cast<const void*>(block_prepare<512, true>), key_lds) ||
+      !allow_key_lds(reinterpret_cast<const void*>(block_prepare<kPrepThreads, true>), key_lds))
     return hipErrorInvalidValue;
   constexpr size_t kAttLds = 2 * static_cast<size_t>(kTileBytes + kTileBytesV);  // 74 KiB: above the default dynamic limit
   const bool mfma_path = dtype == kBF16 && head_dim == 128;
@@ -852,8 +874,10 @@ hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStrea
     ProfScope ps(kProfBlockPrepare, s);
     // Two 1024-thread workgroups do not run side by side on a compute unit here (measured: the second half of 512
     // units starts when the first has finished); with more units than compute units 512 threads are faster.
-    if (a.units > 256) hipLaunchKernelGGL(block_prepare<512>, dim3(a.units), dim3(512), key_lds, s, a);
-    else hipLaunchKernelGGL(block_prepare<kPrepThreads>, dim3(a.units), dim3(kPrepThreads), key_lds, s, a);
+    const dim3 grid(a.units);
+    if (key_lds == 0) hipLaunchKernelGGL((block_prepare<kPrepThreads, false>), grid, dim3(kPrepThreads), 0, s, a);
+    else if (a.units > 256) hipLaunchKernelGGL((block_prepare<512, true>), grid, dim3(512), key_lds, s, a);
+    else hipLaunchKernelGGL((block_prepare<kPrepThreads, true>), grid, dim3(kPrepThreads), key_lds, s, a);
   }
   if (mfma_path) {
     {

@@ -104,6 +104,39 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
   return v;
 }
 
+// Minimum over the 64 lanes of a wave, the same way.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+  auto other = [](uint32_t x, auto ctrl, auto row_mask) {
+    return static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(-1, static_cast<int>(x), decltype(ctrl)::value, decltype(row_mask)::value, 0xF, false));
+  };
+  using std::integral_constant;
+  v = min(v, other(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{}));
+  v = min(v, other(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{}));
+  v = min(v, other(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{}));
+  v = min(v, other(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{}));
+  v = min(v, other(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{}));
+  v = min(v, other(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{}));
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), kWave - 1));
+}
+
+// Index of the smallest key over all threads of the block (the lowest index among equal keys): every thread brings its
+// own best and gets the answer.  `sh` needs one entry per wave.  The waves' minima are reduced by the code that made them.
+template <int NT> __device__ __forceinline__ uint32_t block_argmin(uint32_t key, uint32_t idx, uint2* sh) {
+  const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll 1
+  for (int round = 0;; ++round) {
+    const uint32_t k = wave_min(key);
+    const uint32_t i = wave_min(key == k ? idx : 0xffffffffu);
+    if (round == 1) return i;
+    if (lane == 0) sh[threadIdx.x / kWave] = make_uint2(k, i);
+    __syncthreads();
+    const uint2 v = lane < NT / kWave ? sh[lane] : make_uint2(0xffffffffu, 0xffffffffu);
+    key = v.x;
+    idx = v.y;
+  }
+}
+
 // Exclusive prefix sum of one value per thread over the whole block, in thread order.
 // `sh` needs NT/64 + 1 words; returns the block total through `total`.
 template <int NT>
@@ -127,75 +160,107 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // ---------------------------------------------------------------- k-smallest selection
 // Non-negative IEEE floats order like their bit patterns read as uint32, so selection runs on
 // integers and is exact.  radix_select finds the k-th smallest key (k is 1-based, 1 <= k <= n) among
-// key_of(0..n-1), 8-bit digits from the top; it also returns how many keys are strictly smaller and how
-// many are equal.  Two histograms alternate (the idle one is cleared while the other is scanned), which
-// leaves three barriers per digit; and as soon as the chosen bin holds no more keys than a wave has lanes the
-// remaining digits are not counted: one wave ranks those keys directly.  `sh` needs kSelectLdsWords words of
-// LDS.  All threads of the block call it.
-constexpr int kSelectLdsWords = 2 * 256 + 12;
+// key_of(0..n-1), digits of 11, 11 and 10 bits from the top; it also returns how many keys are strictly smaller and how
+// many are equal.  What it costs is its barriers and its passes over the keys, so the first digit is wide: sign, exponent
+// and the two leading mantissa bits spread a unit's variances or scores over bins of a quarter octave, and usually few
+// enough keys share the chosen one that no second digit is counted -- as soon as a bin holds at most kSelectRanked keys they
+// are gathered and searched without another barrier.  A thread clears the bins it owns while it reads them, so a digit takes three barriers.
+// The largest key, 0xffffffff, is the mark of elements that do not take part: it is not counted (thousands of additions to
+// one bin would be served one after the other).
+// `sh` needs kSelectLdsWords words of LDS.  All threads of the block call it.
+constexpr int kSelectBins = 2048;
+constexpr int kSelectRanked = 128;
+constexpr int kSelectLdsWords = kSelectBins + 16 + 8;
+static_assert(kSelectRanked == 2 * kWave, "two candidates per lane");
 
-template <int NT, class KeyFn>
-__device__ void radix_select(KeyFn key_of, int n, uint32_t k, uint32_t* sh,
+// UNROLL: of the passes over the keys, 1 for keys in LDS (short code), more where they come from memory.
+template <int NT, int UNROLL, class KeyFn>
+__device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, uint32_t* sh,
                              uint32_t& kth, uint32_t& n_less, uint32_t& n_equal) {
-  static_assert(NT >= 256 && NT % kWave == 0, "one thread per histogram bin");
-  uint32_t* wtot = sh + 512;  // inclusive totals of the four scanning waves
-  uint32_t* res = sh + 516;   // bin, keys below the bin, keys in the bin, the key itself and a counter (early exit)
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  static_assert(NT <= 1024 && kSelectBins % NT == 0, "whole bins per thread");
+  constexpr int OWN = kSelectBins / NT;   // consecutive bins per thread
+  uint32_t* const wtot = sh + kSelectBins;        // totals of the waves' bins
+  uint32_t* const res = wtot + 16;                // bin, keys below the bin, keys in the bin, candidates gathered
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   __syncthreads();  // `sh` may still be in use by a previous call
-  if (tid < 256) sh[tid] = 0;
+#pragma unroll
+  for (int i = 0; i < OWN; ++i) sh[tid * OWN + i] = 0;
   __syncthreads();
   uint32_t prefix = 0, mask = 0, kk = k, less = 0, neq = 0;
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    uint32_t* hist = sh + ((pass & 1) ? 256 : 0);
-    uint32_t* idle = sh + ((pass & 1) ? 0 : 256);
+#pragma unroll 1
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+    const uint32_t digit = pass < 2 ? 2047u : 1023u;
+#pragma unroll UNROLL
     for (int i = tid; i < n; i += NT) {
       const uint32_t key = key_of(i);
-      if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+      if ((key & mask) == prefix && key != 0xffffffffu) atomicAdd(&sh[(key >> shift) & digit], 1u);
     }
     __syncthreads();
-    uint32_t h = 0;
-    if (tid < 256) {
-      h = hist[tid];
-      idle[tid] = 0;  // ready for the next digit
+    uint32_t h[OWN], sum = 0;
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+      h[i] = sh[tid * OWN + i];
+      sh[tid * OWN + i] = 0;  // ready for the next digit
+      sum += h[i];
     }
-    uint32_t incl = wave_inclusive_scan(h);
-    if (tid < 256 && lane == kWave - 1) wtot[wave] = incl;
+    uint32_t excl = wave_inclusive_scan(sum);
+    if (lane == kWave - 1) wtot[wave] = excl;
+    excl -= sum;
     __syncthreads();
-    if (tid < 256) {
-      for (int w = 0; w < wave; ++w) incl += wtot[w];
-      const uint32_t excl = incl - h;
-      if (excl < kk && kk <= incl) { res[0] = tid; res[1] = excl; res[2] = h; res[4] = 0; }
+    {  // the totals of the waves before this one: one read, one scan
+      const uint32_t t = wave_inclusive_scan(lane < NT / kWave ? wtot[lane] : 0u);
+      if (wave > 0) excl += __builtin_amdgcn_readlane(t, wave - 1);
+      const uint32_t counted = __builtin_amdgcn_readlane(t, NT / kWave - 1);
+      if (kk > counted) {  // among the keys that are not counted (first digit only: later ones lie inside a counted bin)
+        kth = 0xffffffffu;
+        n_less = counted;
+        n_equal = n - counted;
+        return;
+      }
+    }
+    if (excl < kk && kk <= excl + sum) {  // the chosen bin is one of this thread's
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) {
+        if (excl < kk && kk <= excl + h[i]) { res[0] = tid * OWN + i; res[1] = excl; res[2] = h[i]; res[3] = 0; }
+        excl += h[i];
+      }
     }
     __syncthreads();
     prefix |= res[0] << shift;
-    mask |= 255u << shift;
+    mask |= digit << shift;
     less += res[1];
     kk -= res[1];
     neq = res[2];
-    if (neq <= kWave && pass < 3) {
-      // At most a wave's worth of candidates is left: they are gathered (into the idle histogram, which is clear)
-      // and ranked by one wave directly, every lane counting the candidates below and equal to its own.
-      uint32_t* cand = idle;
+    if (neq <= kSelectRanked && pass < 2) {
+      // Few candidates are left: they are gathered (into the bins, which are clear and not needed any more), and every
+      // wave finishes on its own, two candidates per lane, bit by bit from the top of what is left of the keys: the
+      // candidates with a zero there are the lower ones.  Ballots and scalar counts only, no further barrier, and the
+      // search ends as soon as one candidate is left.
+#pragma unroll UNROLL
       for (int i = tid; i < n; i += NT) {
         const uint32_t key = key_of(i);
-        if ((key & mask) == prefix) cand[atomicAdd(&res[4], 1u)] = key;
+        if ((key & mask) == prefix) sh[atomicAdd(&res[3], 1u)] = key;
       }
       __syncthreads();
-      if (tid < kWave) {
-        const uint32_t mine = tid < neq ? cand[tid] : 0xffffffffu;
-        uint32_t lt = 0, eq = 0;
-        for (uint32_t m = 0; m < neq; ++m) {
-          const uint32_t other = cand[m];
-          lt += other < mine ? 1u : 0u;
-          eq += other == mine ? 1u : 0u;
+      const uint32_t c0 = sh[lane], c1 = sh[lane + kWave];
+      uint64_t in0 = neq >= 64 ? ~0ull : (1ull << neq) - 1ull;
+      uint64_t in1 = neq > 64 ? (neq == 128 ? ~0ull : (1ull << (neq - 64)) - 1ull) : 0ull;
+      uint32_t left = neq;
+#pragma unroll 1
+      for (int bit = shift - 1; bit >= 0 && left > 1; --bit) {
+        const uint64_t z0 = in0 & ~__builtin_amdgcn_ballot_w64((c0 >> bit) & 1u);
+        const uint64_t z1 = in1 & ~__builtin_amdgcn_ballot_w64((c1 >> bit) & 1u);
+        const uint32_t zeros = __builtin_popcountll(z0) + __builtin_popcountll(z1);
+        if (kk <= zeros) {
+          in0 = z0; in1 = z1; left = zeros;
+        } else {
+          in0 &= ~z0; in1 &= ~z1; left -= zeros;
+          kk -= zeros; less += zeros;
         }
-        if (tid < neq && lt < kk && kk <= lt + eq) { res[1] = lt; res[2] = eq; res[3] = mine; }  // equal lanes agree
       }
-      __syncthreads();
-      prefix = res[3];
-      less += res[1];
-      neq = res[2];
+      prefix = in0 != 0 ? __builtin_amdgcn_readlane(c0, __builtin_ctzll(in0)) : __builtin_amdgcn_readlane(c1, __builtin_ctzll(in1));
+      neq = left;
       break;
     }
   }
@@ -214,23 +279,31 @@ struct KSmallest {
   }
 };
 
-template <int NT, class KeyFn>
+template <int NT, int UNROLL = 1, class KeyFn>
 __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t* sh) {
   // everything is wanted (the policies whose scope is the whole cache, say): nothing to select
   if (k >= static_cast<uint32_t>(n)) return KSmallest{0xffffffffu, 0xffffffffu};
-  KSmallest r;
-  uint32_t n_less, n_equal;
-  radix_select<NT>(key_of, n, k, sh, r.kth, n_less, n_equal);
-  const uint32_t take = k - n_less;  // how many of the keys equal to kth belong to the selection
-  if (take == n_equal) {
-    r.index_limit = 0xffffffffu;
-  } else {
-    // ties straddle the boundary: the `take` lowest indices among the equal keys win
+  // At most two rounds through one copy of the search (these kernels start cold: a second copy is instructions to fetch):
+  // the k-th smallest key, then, if ties straddle the boundary, which of the equal keys belong: the lowest indices.
+  KSmallest r = {0u, 0xffffffffu};
+  uint32_t take = k;
+#pragma unroll 1
+  for (int round = 0; round < 2; ++round) {
     const uint32_t kth = r.kth;
-    uint32_t lim, a, b;
-    radix_select<NT>([&](int i) { return key_of(i) == kth ? static_cast<uint32_t>(i) : 0xffffffffu; },
-                     n, take, sh, lim, a, b);
-    r.index_limit = lim;
+    uint32_t found, n_less, n_equal;
+    radix_select<NT, UNROLL>(
+        [&](int i) {
+          const uint32_t key = key_of(i);
+          return round == 0 ? key : key == kth ? static_cast<uint32_t>(i) : 0xffffffffu;
+        },
+        n, take, sh, found, n_less, n_equal);
+    if (round == 1) {
+      r.index_limit = found;
+    } else {
+      r.kth = found;
+      take = k - n_less;  // how many of the keys equal to kth belong to the selection
+      if (take == n_equal) break;
+    }
   }
   return r;
 }
@@ -239,30 +312,19 @@ __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t
 // slot on equal keys).  Every thread of the block calls it and gets the same answer.
 template <int NT>
 __device__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, int scope,
-                                   uint32_t* sel_sh, unsigned long long* best_sh) {
+                                   uint32_t* sel_sh, uint2* best_sh) {
   const int tid = threadIdx.x;
   const KSmallest sc = select_k_smallest<NT>([&](int i) { return var_key[i]; }, B,
                                              static_cast<uint32_t>(scope), sel_sh);
-  unsigned long long best = ~0ull;
+  uint32_t key = 0xffffffffu, idx = 0xffffffffu;
+#pragma unroll 1
   for (int i = tid; i < B; i += NT) {
     if (sc.has(var_key[i], i)) {
-      const unsigned long long cand =
-          (static_cast<unsigned long long>(mas_key[i]) << 32) | static_cast<uint32_t>(i);
-      best = cand < best ? cand : best;
+      const uint32_t k = mas_key[i];
+      if (k < key || idx == 0xffffffffu) { key = k; idx = static_cast<uint32_t>(i); }
     }
   }
-#pragma unroll
-  for (int m = 1; m < kWave; m <<= 1) {
-    const unsigned long long o = __shfl_xor(best, m, kWave);
-    best = o < best ? o : best;
-  }
-  __syncthreads();
-  if ((tid & (kWave - 1)) == 0) best_sh[tid / kWave] = best;
-  __syncthreads();
-  unsigned long long b = best_sh[0];
-#pragma unroll
-  for (int w = 1; w < NT / kWave; ++w) b = best_sh[w] < b ? best_sh[w] : b;
-  return static_cast<int>(b & 0xffffffffu);
+  return static_cast<int>(block_argmin<NT>(key, idx, best_sh));
 }
 
 // Ranking keys of one cached token: the token of lowest importance key among the tokens of lowest scope key
@@ -274,24 +336,24 @@ __device__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_
 // use for "outside the scope".
 __device__ __forceinline__ void ranking_keys(float acc, float acc2, float count, int pos, const Policy& pol,
                                              uint32_t& mas_key, uint32_t& var_key) {
+  const bool by_variance = pol.scope_kind == kScopeStd;
+  float mas = 0.0f;
+  if (by_variance || pol.importance == kImpMas) mas = __fdiv_rn(acc, count);
   if (pol.importance == kImpMas) {
-    mas_key = __float_as_uint(__fdiv_rn(acc, count));
-  } else if (pol.importance == kImpAas) {
-    mas_key = acc > 0.0f ? __float_as_uint(acc) : 0u;
-  } else if (pol.importance == kImpLast || pol.importance == kImpCount) {
-    mas_key = acc2 > 0.0f ? __float_as_uint(acc2) : 0u;
-  } else {
+    mas_key = __float_as_uint(mas);
+  } else if (pol.importance == kImpOldest) {
     mas_key = pos < pol.sinks ? 0xfffffffeu : static_cast<uint32_t>(pos);
+  } else {
+    const float score = pol.importance == kImpAas ? acc : acc2;
+    mas_key = score > 0.0f ? __float_as_uint(score) : 0u;
   }
-  if (pol.scope_kind == kScopeStd) {
-    const float mas = __fdiv_rn(acc, count);
+  var_key = 0u;
+  if (by_variance) {
     const float ex2 = __fdiv_rn(acc2, count);
     const float var = __fsub_rn(ex2, __fmul_rn(mas, mas));
-    var_key = var > 0.0f ? __float_as_uint(var) : 0u;
+    if (var > 0.0f) var_key = __float_as_uint(var);
   } else if (pol.scope_kind == kScopeWindow) {
     var_key = static_cast<uint32_t>(pos);
-  } else {
-    var_key = 0u;
   }
 }
 

@@ -191,6 +191,7 @@ __device__ __forceinline__ void update_statistics(float* acc, float* acc2, float
         }
       }
     }
+#pragma unroll 1
     for (int j = ((ahead != nullptr ? PF * NT : 0) + tid) * 4; j < n; j += NT * 4) {
       float4 a1 = *reinterpret_cast<const float4*>(acc + j);
       float4 a2 = *reinterpret_cast<const float4*>(acc2 + j);
@@ -201,6 +202,7 @@ __device__ __forceinline__ void update_statistics(float* acc, float* acc2, float
       *reinterpret_cast<float4*>(cnt + j) = cc;
     }
   } else {
+#pragma unroll 1
     for (int j = tid; j < n; j += NT) {
       float s1 = acc[j], s2 = acc2[j], sc = cnt[j];
       if (j == slot) { s1 = 0.0f; s2 = 0.0f; sc = 0.0f; }
@@ -215,11 +217,12 @@ __device__ __forceinline__ void update_statistics(float* acc, float* acc2, float
 }
 
 // ------------------------------------------------------------------------------------------------
-template <int DT, int D, int NT>
+// LDS: the ranking keys are in LDS (B <= kMaxDecodeBudgetLds).
+template <int DT, int D, int NT, bool LDS>
 __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
   extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
-  __shared__ uint32_t sel_sh[kSelectLdsWords];
-  __shared__ unsigned long long best_sh[NT / kWave];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ uint2 best_sh[NT / kWave];
   __shared__ float mrg_m[kMaxSplits], mrg_l[kMaxSplits];
   __shared__ float mrg_o[NT / D][D];
   static_assert(NT >= kMaxSplits && NT % D == 0, "one thread per split, whole groups per dimension");
@@ -241,8 +244,10 @@ __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
   }
   __syncthreads();
   float M = -INFINITY;
+#pragma unroll 1
   for (int s = 0; s < S; ++s) M = fmaxf(M, mrg_m[s]);
   float Lsum = 0.0f;
+#pragma unroll 1
   for (int s = 0; s < S; ++s) Lsum += (mrg_m[s] > -INFINITY) ? mrg_l[s] * fast_exp2(mrg_m[s] - M) : 0.0f;
   const float inv = 1.0f / Lsum;
 
@@ -252,6 +257,7 @@ __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
     const int g = tid / D, dd = tid % D;
     const float* po = a.part_o + static_cast<size_t>(u) * S * D;
     float o = 0.0f;
+#pragma unroll 1
     for (int s = g; s < S; s += G) o += (mrg_m[s] > -INFINITY) ? po[s * D + dd] * fast_exp2(mrg_m[s] - M) : 0.0f;
     mrg_o[g][dd] = o;
     __syncthreads();
@@ -268,8 +274,8 @@ __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
   float* cnt = acc2 + B;
   const float* z = a.z + static_cast<size_t>(u) * B;
   int32_t* pos = a.pos + static_cast<size_t>(u) * B;
-  uint32_t* var_key = (B <= kMaxDecodeBudgetLds) ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
-  uint32_t* mas_key = var_key + B;
+  uint32_t* const var_key = LDS ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
+  uint32_t* const mas_key = var_key + B;
 
   // Bookkeeping first: the load counter is in order, so a load issued after the statistics stores could only be
   // waited for together with them, and every wave would sit at the barrier below for the stores' round trip.
@@ -301,8 +307,8 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   constexpr int NT = kFusedThreads, WAVES = NT / kWave;
   constexpr int PASS = WAVES * U * G::R;
   extern __shared__ __attribute__((aligned(16))) uint32_t lds_dyn[];  // [2][B] ranking keys, then [B] base-2 logits
-  __shared__ uint32_t sel_sh[kSelectLdsWords];
-  __shared__ unsigned long long best_sh[WAVES];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ uint2 best_sh[WAVES];
   __shared__ float sm_m[WAVES], sm_l[WAVES];
   __shared__ float sm_acc[WAVES][D];
 
@@ -403,8 +409,8 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
 __global__ __launch_bounds__(kFinishThreads) void select_victims(DecodeArgs a) {
   constexpr int NT = kFinishThreads;
   extern __shared__ uint32_t lds_keys[];
-  __shared__ uint32_t sel_sh[kSelectLdsWords];
-  __shared__ unsigned long long best_sh[NT / kWave];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ uint2 best_sh[NT / kWave];
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B;
   if (a.n_used[u] < B) {
@@ -466,6 +472,14 @@ void launch_attend(const DecodeArgs& a, hipStream_t s) {
   else hipLaunchKernelGGL((decode_attend<DT, D, U, false, false>), grid, block, 0, s, a);
 }
 
+template <int DT, int D, int NT>
+hipError_t launch_finish(const DecodeArgs& a, size_t key_lds, hipStream_t s) {
+  if (!allow_key_lds(reinterpret_cast<const void*>(decode_finish<DT, D, NT, true>), key_lds)) return hipErrorInvalidValue;
+  if (key_lds != 0) hipLaunchKernelGGL((decode_finish<DT, D, NT, true>), dim3(a.units), dim3(NT), key_lds, s, a);
+  else hipLaunchKernelGGL((decode_finish<DT, D, NT, false>), dim3(a.units), dim3(NT), 0, s, a);
+  return hipGetLastError();
+}
+
 template <int DT, int D>
 hipError_t launch_decode_t(const DecodeArgs& a, hipStream_t s) {
   const size_t lds = key_lds_bytes(a.B);
@@ -490,16 +504,8 @@ hipError_t launch_decode_t(const DecodeArgs& a, hipStream_t s) {
     // A unit's statistics and selection are one workgroup's work: 1024 threads when there is at most one unit per
     // compute unit and enough slots to share out (measured: faster from 1024 slots on, e.g. 34 -> 28 us per step at
     // 40 units x 4096 slots, 78 -> 64 at 64 x 8192), else 256.
-    if (a.B >= 1024 && a.units <= 256) {
-      if (!allow_key_lds(reinterpret_cast<const void*>(decode_finish<DT, D, 1024>), lds)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((decode_finish<DT, D, 1024>), dim3(a.units), dim3(1024), lds, s, a);
-    } else {
-      if (!allow_key_lds(reinterpret_cast<const void*>(decode_finish<DT, D, kFinishThreads>), lds))
-        return hipErrorInvalidValue;
-      hipLaunchKernelGGL((decode_finish<DT, D, kFinishThreads>), dim3(a.units), dim3(kFinishThreads), lds, s, a);
-    }
+    return a.B >= 1024 && a.units <= 256 ? launch_finish<DT, D, 1024>(a, lds, s) : launch_finish<DT, D, kFinishThreads>(a, lds, s);
   }
-  return hipGetLastError();
 }
 
 }  // namespace

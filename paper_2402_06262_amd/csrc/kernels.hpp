@@ -36,7 +36,7 @@ constexpr int kDecodeSelectThreads = 256;
 constexpr int kMaxFusedBudget = 4096;       // largest budget of the one-kernel decode step (keys and logits in LDS)
 constexpr int kMaxDecodeBudgetLds = 16384;  // ranking keys of a unit are kept in LDS up to here (128 KiB), else in the workspace
 constexpr size_t kDefaultDynamicLds = 65536;  // LDS a kernel may use without raising its limit first
-constexpr size_t kStaticLdsAllowance = 8192;  // upper bound on the statically declared LDS of the kernels that ask
+constexpr size_t kStaticLdsAllowance = 16384;  // upper bound on the statically declared LDS of the kernels that ask
 
 // Dynamic LDS for the ranking keys of one unit (0: they go to the workspace); raises the kernel's limit when the
 // request, together with what the kernel declares statically, may be above the default one.  Returns false if the

@@ -21,12 +21,17 @@ constexpr int kSelThreads = 1024;
 constexpr int kGatherThreads = 256;
 constexpr int kGatherRows = 64;  // cache rows per gather workgroup
 
-__global__ __launch_bounds__(kSelThreads) void prefill_select(PrefillArgs a) {
+// A launch of this kernel starts with a cold instruction cache and walks through its code once, so the code is kept short:
+// the three selections (scope, victims, first decode victim) share one copy of the search, loops over keys in LDS are not
+// unrolled, and where the keys are is a template parameter so that they are read with LDS instructions.
+// LDS: both keys of a token in LDS (2; up to 16384 tokens), the one of the scope (1; up to 32768), none (0).
+template <int LDS>
+__global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) {
   constexpr int NT = kSelThreads;
   extern __shared__ uint32_t lds_keys[];  // [2][L_max] ranking keys when L_max <= kMaxDecodeBudgetLds
-  __shared__ uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
   __shared__ uint32_t scan_sh[NT / kWave + 1];
-  __shared__ unsigned long long best_sh[NT / kWave];
+  __shared__ uint2 best_sh[NT / kWave];
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B;
   const int n = a.len[u];
@@ -34,25 +39,18 @@ __global__ __launch_bounds__(kSelThreads) void prefill_select(PrefillArgs a) {
   const float* acc = a.acc + ubase;
   const float* acc2 = a.acc2 + ubase;
   // every radix pass reads every key: in LDS they cost a fraction of a trip to the L2 each
-  const bool keys_in_lds = a.L_max <= kMaxDecodeBudgetLds;
-  uint32_t* var_key = keys_in_lds ? lds_keys : a.var_key + ubase;
-  uint32_t* mas_key = keys_in_lds ? lds_keys + a.L_max : a.mas_key + ubase;
+  uint32_t* const var_key = LDS > 0 ? lds_keys : a.var_key + ubase;
+  uint32_t* const mas_key = LDS == 2 ? lds_keys + a.L_max : a.mas_key + ubase;
+  constexpr int kUnroll = LDS == 2 ? 1 : 4;
   float* oacc = a.stats + static_cast<size_t>(u) * 3 * B;
   float* oacc2 = oacc + B;
   float* ocnt = oacc2 + B;
   int32_t* pos = a.pos + static_cast<size_t>(u) * B;
 
   const int kept = n < B ? n : B;
-  if (n <= B) {
-    for (int i = tid; i < n; i += NT) {
-      pos[i] = i;
-      oacc[i] = acc[i];
-      oacc2[i] = acc2[i];
-      ocnt[i] = static_cast<float>(n - i);
-    }
-  } else {
-    const uint32_t E = static_cast<uint32_t>(n - B);
-    const uint32_t m = min(static_cast<uint32_t>(n), static_cast<uint32_t>(a.pol.scope_size(a.scope, n)) + E - 1u);
+  const uint32_t E = static_cast<uint32_t>(n - kept);
+  if (n >= B) {
+#pragma unroll kUnroll
     for (int i = tid; i < n; i += NT) {
       uint32_t mk, vk;
       ranking_keys(acc[i], acc2[i], static_cast<float>(n - i), i, a.pol, mk, vk);
@@ -60,26 +58,63 @@ __global__ __launch_bounds__(kSelThreads) void prefill_select(PrefillArgs a) {
       mas_key[i] = mk;
     }
     __syncthreads();
-    const KSmallest scope = select_k_smallest<NT>([&](int i) { return var_key[i]; }, n, m, sel_sh);
-    auto key2 = [&](int i) -> uint32_t { return scope.has(var_key[i], i) ? mas_key[i] : 0xffffffffu; };
-    const KSmallest out = select_k_smallest<NT>(key2, n, E, sel_sh);
-    // ordered compaction: thread t owns the contiguous positions [t*c, (t+1)*c)
-    const int c = (n + NT - 1) / NT;
-    const int lo = min(n, tid * c), hi = min(n, lo + c);
-    uint32_t mine = 0;
-    for (int i = lo; i < hi; ++i) mine += out.has(key2(i), i) ? 0u : 1u;
-    uint32_t total;
-    uint32_t dst = block_exclusive_scan<NT>(mine, scan_sh, total);
-    for (int i = lo; i < hi; ++i) {
-      if (!out.has(key2(i), i) && dst < static_cast<uint32_t>(B)) {
-        pos[dst] = i;
-        oacc[dst] = acc[i];
-        oacc2[dst] = acc2[i];
-        ocnt[dst] = static_cast<float>(n - i);
-        ++dst;
+  }
+  // Phase 0: the scope of the eviction; 1: the victims; 2: the scope of the first decode step, among the retained tokens
+  // (whose keys do not change and whose order is that of their slots, so the compacted statistics need not be read back).
+  KSmallest scope = {0u, 0u}, out = {0u, 0u}, next = {0u, 0u};
+  auto evicted = [&](int i) { return E > 0 && out.has(scope.has(var_key[i], i) ? mas_key[i] : 0xffffffffu, i); };
+  if (n >= B) {
+#pragma unroll 1
+    for (int phase = E > 0 ? 0 : 2; phase < 3; ++phase) {
+      const uint32_t k = phase == 1 ? E
+                         : phase == 0 ? min(static_cast<uint32_t>(n), static_cast<uint32_t>(a.pol.scope_size(a.scope, n)) + E - 1u)
+                                      : static_cast<uint32_t>(a.pol.scope_size(a.scope, B));
+      if (phase == 2 && k >= static_cast<uint32_t>(kept)) {  // every retained token is in the scope
+        next = KSmallest{0xffffffffu, 0xffffffffu};
+        break;
       }
+      const KSmallest r = select_k_smallest<NT, kUnroll>(
+          [&](int i) -> uint32_t {
+            const uint32_t vk = var_key[i];
+            if (phase == 0) return vk;
+            const uint32_t in_scope = E > 0 && scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
+            if (phase == 1) return in_scope;
+            return E > 0 && out.has(in_scope, i) ? 0xffffffffu : vk;
+          },
+          n, k, sel_sh);
+      if (phase == 0) scope = r;
+      else if (phase == 1) out = r;
+      else next = r;
     }
   }
+  // ordered compaction: thread t owns the contiguous positions [t*c, (t+1)*c)
+  const int c = (n + NT - 1) / NT;
+  const int lo = min(n, tid * c), hi = min(n, lo + c);
+  uint32_t mine = 0;
+  uint32_t best_key = 0xffffffffu, best = 0xffffffffu;  // importance and position of the first decode victim
+#pragma unroll 1
+  for (int i = lo; i < hi; ++i) {
+    if (evicted(i)) continue;
+    ++mine;
+    if (n >= B && next.has(var_key[i], i)) {
+      const uint32_t k = mas_key[i];
+      if (k < best_key || best == 0xffffffffu) { best_key = k; best = static_cast<uint32_t>(i); }
+    }
+  }
+  uint32_t total;
+  const uint32_t first = block_exclusive_scan<NT>(mine, scan_sh, total);
+  uint32_t dst = first;
+#pragma unroll 1
+  for (int i = lo; i < hi; ++i) {
+    if (!evicted(i) && dst < static_cast<uint32_t>(B)) {
+      pos[dst] = i;
+      oacc[dst] = acc[i];
+      oacc2[dst] = acc2[i];
+      ocnt[dst] = static_cast<float>(n - i);
+      ++dst;
+    }
+  }
+#pragma unroll 1
   for (int i = kept + tid; i < B; i += NT) {
     pos[i] = -1;
     oacc[i] = 0.0f;
@@ -87,36 +122,17 @@ __global__ __launch_bounds__(kSelThreads) void prefill_select(PrefillArgs a) {
     ocnt[i] = 0.0f;
   }
   if (tid == 0) a.n_used[u] = kept;
-  // the first decode step on a full cache needs its victim: choose it now, from the compacted statistics
-  if (kept == B) {
-    __syncthreads();  // the compacted planes written above are visible to the whole block
-    for (int i = tid; i < B; i += NT) ranking_keys(oacc[i], oacc2[i], ocnt[i], pos[i], a.pol, mas_key[i], var_key[i]);
-    __syncthreads();
-    const KSmallest sc = select_k_smallest<NT>([&](int i) { return var_key[i]; }, B,
-                                               static_cast<uint32_t>(a.pol.scope_size(a.scope, B)), sel_sh);
-    unsigned long long best = ~0ull;
-    for (int i = tid; i < B; i += NT) {
-      if (sc.has(var_key[i], i)) {
-        const unsigned long long cand =
-            (static_cast<unsigned long long>(mas_key[i]) << 32) | static_cast<uint32_t>(i);
-        best = cand < best ? cand : best;
-      }
-    }
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) {
-      const unsigned long long o = __shfl_xor(best, m, kWave);
-      best = o < best ? o : best;
-    }
-    __syncthreads();
-    if ((tid & (kWave - 1)) == 0) best_sh[tid / kWave] = best;
-    __syncthreads();
-    if (tid == 0) {
-      unsigned long long b = best_sh[0];
-      for (int w = 1; w < NT / kWave; ++w) b = best_sh[w] < b ? best_sh[w] : b;
-      a.next_slot[u] = static_cast<int>(b & 0xffffffffu);
-    }
-  } else if (tid == 0) {
-    a.next_slot[u] = -1;
+  if (kept < B) {
+    if (tid == 0) a.next_slot[u] = -1;
+    return;
+  }
+  // the first decode step on a full cache needs its victim
+  const int victim = static_cast<int>(block_argmin<NT>(best_key, best, best_sh));
+  if (victim >= lo && victim < hi) {  // its owner knows which slot it went to
+    uint32_t slot = first;
+#pragma unroll 1
+    for (int i = lo; i < victim; ++i) slot += evicted(i) ? 0u : 1u;
+    a.next_slot[u] = static_cast<int>(slot);
   }
 }
 
@@ -152,7 +168,7 @@ __global__ __launch_bounds__(kGatherThreads) void prefill_gather(PrefillArgs a) 
 __global__ __launch_bounds__(kSelThreads) void select_retained(DecodeArgs a, int keep, int32_t* mask_out) {
   constexpr int NT = kSelThreads;
   extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
-  __shared__ uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B;
   const int n = min(a.n_used[u], B);
@@ -243,9 +259,17 @@ hipError_t launch_select_retained(const DecodeArgs& a, int keep, int32_t* mask, 
 hipError_t launch_prefill_select_compact(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s) {
   {
     ProfScope ps(kProfPrefillSelect, s);
-    const size_t key_lds = key_lds_bytes(a.L_max);  // the budget's keys for the first decode victim fit too: B < L_max
-    if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select), key_lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(prefill_select, dim3(a.units), dim3(kSelThreads), key_lds, s, a);
+    const size_t key_lds = key_lds_bytes(a.L_max);
+    if (key_lds != 0) {
+      if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<2>), key_lds)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(prefill_select<2>, dim3(a.units), dim3(kSelThreads), key_lds, s, a);
+    } else if (a.L_max <= 2 * kMaxDecodeBudgetLds) {  // one key per token still fits (40 units x 32768 tokens: 156 us against 200)
+      const size_t one = static_cast<size_t>(a.L_max) * sizeof(uint32_t);
+      if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<1>), one)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(prefill_select<1>, dim3(a.units), dim3(kSelThreads), one, s, a);
+    } else {
+      hipLaunchKernelGGL(prefill_select<0>, dim3(a.units), dim3(kSelThreads), 0, s, a);
+    }
   }
   ProfScope ps(kProfPrefillGather, s);
   const int row_bytes = head_dim * (dtype == kBF16 ? 2 : 4);

@@ -1,0 +1,92 @@
+"""The k-smallest search behind every eviction, through calls whose statistics the test chooses: keys that share digits, ties
+across the boundary, more candidates than are searched directly, and prompts whose ranking keys leave LDS one by one."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _keys(kind, n, rng):
+    if kind == "equal":
+        return np.full(n, 0.25, np.float32)
+    if kind == "low_bits":  # one value but for the lowest three bits: all three digits are counted, ties in each
+        return (np.float32(1.5).view(np.uint32) + rng.integers(0, 8, n).astype(np.uint32)).view(np.float32)
+    if kind == "middle_bits":
+        return (np.float32(1.5).view(np.uint32) + (rng.integers(0, 700, n).astype(np.uint32) << 9)).view(np.float32)
+    if kind == "two_values":
+        return np.where(rng.random(n) < 0.5, np.float32(0.0), np.float32(3e38)).astype(np.float32)
+    return np.exp(rng.uniform(-60, 60, n)).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["equal", "low_bits", "middle_bits", "two_values", "wide"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 128, 129, 1024, 2047, 4100, 16384, 16400])
+def test_lowest_keys_go_first_and_ties_by_slot(kind, n):
+    import paper_2402_06262_amd as roco
+    rng = np.random.default_rng([n, len(kind)])
+    units = 3
+    p = roco.RocoParams(units, 64, n, 1, roco.ROCO_F32, importance=roco.ROCO_IMPORTANCE_AAS, scope_kind=roco.ROCO_SCOPE_ALL)
+    acc = np.stack([_keys(kind, n, rng) for _ in range(units)])
+    stats = torch.from_numpy(np.stack([acc, acc, np.ones_like(acc)], axis=1)).cuda()
+    n_used = torch.full((units,), n, dtype=torch.int32, device="cuda")
+    mask = torch.empty((units, n), dtype=torch.int32, device="cuda")
+    ws = torch.empty(roco.decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    order = np.argsort(acc, axis=1, kind="stable")
+    for keep in sorted({n - 1, n // 2, n // 3, max(0, n - 129), min(n, 1), 0}):
+        roco.roco_select_retained(p, keep, stats, None, n_used, mask, ws)
+        want = np.ones((units, n), np.int32)
+        for u in range(units):
+            want[u, order[u, :n - keep]] = 0
+        assert np.array_equal(mask.cpu().numpy(), want), (kind, n, keep)
+    victim = torch.empty((units,), dtype=torch.int32, device="cuda")
+    roco.roco_select_victims(p, stats, None, n_used, victim, ws)
+    assert np.array_equal(victim.cpu().numpy(), order[:, 0])
+
+
+@pytest.mark.parametrize("scope", [1, 5, 64, 500])
+def test_victim_is_the_least_important_token_of_the_scope(scope):
+    import paper_2402_06262_amd as roco
+    rng = np.random.default_rng(scope)
+    units, n = 4, 512
+    acc = rng.uniform(0.1, 2.0, (units, n)).astype(np.float32)
+    cnt = rng.integers(1, 400, (units, n)).astype(np.float32)
+    mas = acc / cnt
+    acc2 = (cnt * (mas * mas * rng.uniform(1.25, 4.0, (units, n)).astype(np.float32))).astype(np.float32)
+    acc[:, 100:140] = acc[:, 99:100]  # ties in both keys
+    cnt[:, 100:140], acc2[:, 100:140] = cnt[:, 99:100], acc2[:, 99:100]
+    mas = acc / cnt
+    var = np.maximum(acc2 / cnt - mas * mas, np.float32(0.0))
+    p = roco.RocoParams(units, 64, n, scope, roco.ROCO_F32)
+    stats = torch.from_numpy(np.stack([acc, acc2, cnt], axis=1)).cuda()
+    n_used = torch.full((units,), n, dtype=torch.int32, device="cuda")
+    victim = torch.empty((units,), dtype=torch.int32, device="cuda")
+    ws = torch.empty(roco.decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    roco.roco_select_victims(p, stats, None, n_used, victim, ws)
+    for u in range(units):
+        inside = np.sort(np.argsort(var[u], kind="stable")[:scope])
+        assert int(victim[u]) == inside[np.argmin(mas[u][inside])]
+
+
+@pytest.mark.parametrize("L", [300, 16384, 16385, 32768, 32769])
+def test_prompts_on_both_sides_of_what_lds_holds(L):
+    """Recency with sinks: what stays is known without the statistics -- the sinks and the last tokens, in order; the first
+    decode step evicts the oldest token that is no sink."""
+    import paper_2402_06262_amd as roco
+    units, B, sinks = 2, 200, 3
+    lens = [L, max(B, L - 77)]
+    p = roco.RocoParams(units, 64, B, 1, roco.ROCO_BF16, importance=roco.ROCO_IMPORTANCE_OLDEST,
+                        scope_kind=roco.ROCO_SCOPE_ALL, sinks=sinks)
+    g = torch.Generator(device="cuda").manual_seed(L)
+    Q, K, V = (torch.randn((units, L, 64), generator=g, device="cuda").bfloat16() for _ in range(3))
+    c = roco.alloc_cache(p)
+    ws = torch.empty(roco.prefill_workspace_bytes(p, L), dtype=torch.uint8, device="cuda")
+    roco.roco_prefill_compress(p, Q, K, V, torch.tensor(lens, dtype=torch.int32, device="cuda"), L, c.K, c.V, c.stats,
+                               c.pos, c.n_used, c.next_slot, None, ws)
+    for u, n in enumerate(lens):
+        want = torch.tensor(list(range(sinks)) + list(range(n - B + sinks, n)))
+        assert torch.equal(c.pos[u].cpu().long(), want)
+        assert torch.equal(c.stats[u, 2].cpu(), (n - want).float())
+        assert torch.equal(c.K[u].cpu(), K[u].cpu()[want])
+        total = float(c.stats[u, 0].double().sum())
+        assert 0.0 < total < n
+        assert int(c.next_slot[u]) == sinks
