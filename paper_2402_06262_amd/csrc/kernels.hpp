@@ -84,6 +84,7 @@ struct PrefillArgs {
   int skip_rows;         // 1: lse already holds the row normalisers, pass 1 is not run
   int qsplit;            // matrix-core path: 1, or 2 = two workgroups share a block's queries (set by its launcher)
   int ksplit;            // matrix-core path, row pass: 1, or 2 = two workgroups share a block's keys (ditto)
+  int two_shares;        // 1: acc / acc2 hold half of the column sums, var_key / mas_key the other (set by the passes' launcher)
   float scale_log2;
   int recency_window;
   float recency_bias_log2;
@@ -147,8 +148,9 @@ hipError_t launch_set_overlap(int units, int slots_a, const int32_t* pos_a, cons
                               int slots_b, const int32_t* pos_b, const int32_t* mask_b, const int32_t* n_b, int max_pos,
                               int32_t* inter, int32_t* uni, hipStream_t s);
 hipError_t launch_prefill_attention_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);
-hipError_t launch_prefill_attention_mfma(const PrefillArgs& a, hipStream_t s);  // bf16, head_dim 128
-hipError_t launch_prefill_attention_planes(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);  // the other forms
+// The matrix-core passes: bf16 / 128, and the other forms.  Both may leave PrefillArgs::two_shares set for prefill_select.
+hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s);
+hipError_t launch_prefill_attention_planes(int dtype, int head_dim, PrefillArgs& a, hipStream_t s);
 // fp32 prompts of few scores: the vector-ALU row pass, one wave per query and as many waves as queries, is done before a
 // workgroup of the matrix-core pass with output has walked its tiles one after the other (fp32 / 64 with output, us: 4 units
 // x 256 tokens 12 against 20, 1 x 512 19 against 29, 16 x 128 11 against 15; but 16 x 256 23 against 20, 256 x 48 17 against 12).
@@ -158,7 +160,10 @@ inline bool prefill_is_tiny(const PrefillArgs& a) {
 void launch_prefill_rows_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);  // fp32
 // second shares of PrefillArgs::ksplit / qsplit merged into the first ones
 void launch_merge_key_shares(const PrefillArgs& a, hipStream_t s);
-void launch_sum_query_shares(const PrefillArgs& a, hipStream_t s);
+// The selection adds the two shares of the column sums itself where it keeps its ranking keys in LDS, not in the planes of
+// the second share, and nothing else comes between; else a kernel of its own does (5 us of a call).
+inline bool selection_adds_shares(const PrefillArgs& a) { return a.L_max <= kMaxDecodeBudgetLds && !a.pol.keeps_last_score(); }
+void join_query_shares(PrefillArgs& a, hipStream_t s);
 // overwrites PrefillArgs::acc2 with the attention row of each unit's last prompt token (kImpLast)
 hipError_t launch_lse_to_base2(const float* lse_ln, float* lse_log2, size_t n, hipStream_t s);
 hipError_t launch_prefill_last_row(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);

@@ -1392,7 +1392,7 @@ void launch_columns_grouped(const PrefillArgs& b, dim3 grid, hipStream_t s) {
 }
 
 template <int WAVES>
-hipError_t launch_t(const PrefillArgs& a, hipStream_t s) {
+hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
   constexpr int kOwn = Shape<WAVES>::kOwn;
   const int n_blocks = (a.L_max + kOwn - 1) / kOwn;
   PrefillArgs b = a;
@@ -1415,13 +1415,13 @@ hipError_t launch_t(const PrefillArgs& a, hipStream_t s) {
       hipLaunchKernelGGL(prefill_columns_mfma<true>, grid, dim3(WAVES * kWave), 0, s, b);
     else hipLaunchKernelGGL(prefill_columns_mfma<false>, grid, dim3(WAVES * kWave), 0, s, b);
     if (b.qsplit > 1)
-      launch_sum_query_shares(b, s);
+      join_query_shares(a, s);
   }
   return hipGetLastError();
 }
 
 // Rows pass that also writes O, followed by the ordinary columns pass.
-hipError_t launch_with_output(const PrefillArgs& a, hipStream_t s) {
+hipError_t launch_with_output(PrefillArgs& a, hipStream_t s) {
   constexpr int WAVES = 4;
   constexpr int kOwnQ = 32 * WAVES;
   constexpr size_t kLds = 2 * static_cast<size_t>(kTileBytes + kTileBytesV);  // 74 KiB: above the default dynamic limit
@@ -1451,7 +1451,7 @@ hipError_t launch_with_output(const PrefillArgs& a, hipStream_t s) {
     else if (a.pol.counts_above_average()) hipLaunchKernelGGL(prefill_columns_mfma<true>, cgrid, dim3(4 * kWave), 0, s, c);
     else hipLaunchKernelGGL(prefill_columns_mfma<false>, cgrid, dim3(4 * kWave), 0, s, c);
     if (c.qsplit > 1)
-      launch_sum_query_shares(c, s);
+      join_query_shares(a, s);
   }
   return hipGetLastError();
 }
@@ -1461,8 +1461,9 @@ hipError_t launch_with_output(const PrefillArgs& a, hipStream_t s) {
 void launch_merge_key_shares(const PrefillArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(merge_key_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, a);
 }
-void launch_sum_query_shares(const PrefillArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(sum_query_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, a);
+void join_query_shares(PrefillArgs& a, hipStream_t s) {
+  if (selection_adds_shares(a)) a.two_shares = 1;
+  else hipLaunchKernelGGL(sum_query_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, a);
 }
 
 hipError_t launch_mfma_probe(int workgroups, int iters, int mode, float* sink, hipStream_t s) {
@@ -1478,7 +1479,7 @@ hipError_t launch_mfma_probe(int workgroups, int iters, int mode, float* sink, h
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_attention_mfma(const PrefillArgs& a, hipStream_t s) {
+hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s) {
   if (a.O != nullptr) return launch_with_output(a, s);
   // 256 owned rows per workgroup (512 halved the streamed traffic but left one workgroup per compute unit, all of
   // whose waves wait at the same barriers: measured slower on the serving workload).

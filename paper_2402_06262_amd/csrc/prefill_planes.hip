@@ -792,7 +792,7 @@ void launch_columns(const PrefillArgs& b, unsigned n, hipStream_t s) {
 }
 
 template <int DT, int D>
-hipError_t launch_t(const PrefillArgs& a, hipStream_t s) {
+hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
   constexpr int kShared = kRows<DT, D> > 32 ? 2 : 1;  // a tile of one sub-tile has nothing to share
   constexpr int kTarget = DT == kBF16 ? 1024 : 512;
   constexpr bool kPartFirst = DT == kBF16;
@@ -816,13 +816,13 @@ hipError_t launch_t(const PrefillArgs& a, hipStream_t s) {
   b.pairs = l.pairs; b.paired = l.paired; b.qsplit = l.split;
   if (l.parts == 2) launch_columns<DT, D, kShared>(b, ids(a, 1, l), s);
   else launch_columns<DT, D, 1>(b, ids(a, 1, l), s);
-  if (l.split > 1) launch_sum_query_shares(b, s);
+  if (l.split > 1) join_query_shares(a, s);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_prefill_attention_planes(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s) {
+hipError_t launch_prefill_attention_planes(int dtype, int head_dim, PrefillArgs& a, hipStream_t s) {
   if (dtype == kF32 && head_dim == 64) return launch_t<kF32, 64>(a, s);
   if (dtype == kF32 && head_dim == 128) return launch_t<kF32, 128>(a, s);
   if (dtype == kBF16 && head_dim == 64) return launch_t<kBF16, 64>(a, s);

@@ -36,8 +36,17 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
   const int B = a.B;
   const int n = a.len[u];
   const size_t ubase = static_cast<size_t>(u) * a.L_max;
-  const float* acc = a.acc + ubase;
-  const float* acc2 = a.acc2 + ubase;
+  // the column sums, in one or two shares
+  const bool two = LDS == 2 && a.two_shares != 0;
+  const float* const first1 = a.acc + ubase;
+  const float* const first2 = a.acc2 + ubase;
+  const float* const second1 = reinterpret_cast<const float*>(a.var_key) + ubase;
+  const float* const second2 = reinterpret_cast<const float*>(a.mas_key) + ubase;
+  auto sums = [&](int i) {
+    float2 s = make_float2(first1[i], first2[i]);
+    if (two) { s.x += second1[i]; s.y += second2[i]; }
+    return s;
+  };
   // every radix pass reads every key: in LDS they cost a fraction of a trip to the L2 each
   uint32_t* const var_key = LDS > 0 ? lds_keys : a.var_key + ubase;
   uint32_t* const mas_key = LDS == 2 ? lds_keys + a.L_max : a.mas_key + ubase;
@@ -53,7 +62,8 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
 #pragma unroll kUnroll
     for (int i = tid; i < n; i += NT) {
       uint32_t mk, vk;
-      ranking_keys(acc[i], acc2[i], static_cast<float>(n - i), i, a.pol, mk, vk);
+      const float2 s = sums(i);
+      ranking_keys(s.x, s.y, static_cast<float>(n - i), i, a.pol, mk, vk);
       var_key[i] = vk;
       mas_key[i] = mk;
     }
@@ -108,8 +118,9 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
   for (int i = lo; i < hi; ++i) {
     if (!evicted(i) && dst < static_cast<uint32_t>(B)) {
       pos[dst] = i;
-      oacc[dst] = acc[i];
-      oacc2[dst] = acc2[i];
+      const float2 s = sums(i);
+      oacc[dst] = s.x;
+      oacc2[dst] = s.y;
       ocnt[dst] = static_cast<float>(n - i);
       ++dst;
     }
