@@ -1072,11 +1072,22 @@ __global__ __launch_bounds__(256) void sum_query_shares(PrefillArgs a) {
 // at row i/4, column 4*(i%4) of the block, lane i receives rows 0..3 of column i.)  The k-slot order of both
 // operands follows the accumulator layout of the score tile: slots 0-3 are keys 4h..4h+3 and slots 4-7 are keys
 // 8+4h..8+4h+3 of a 16-key step, h = lane / 32.
+//
+// Every fragment read from LDS feeds one matrix instruction here, and a wave's scores, exponentials and products depend on
+// one another in turn, so what fills the matrix and vector pipes is other waves: the kernel is built for three per SIMD.
+// K and V tiles of 32 keys come straight into a three-stage LDS ring (no staging registers; 48 KiB per workgroup, requested
+// two tiles ahead).  A V row is stored unpadded with its 64-byte groups rotated by the row, chunk c of row r in slot
+// c ^ 4 (r % 4), so that the four rows of a transpose read fall on distinct banks.
+struct OutRing {
+  static constexpr int kRows = 32, kStages = 3;
+  static constexpr int kTileBytes = kRows * kRowBytes;   // 8 KiB of K, then 8 KiB of V
+  static constexpr int kStageBytes = 2 * kTileBytes;
+};
 
-template <int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void prefill_rows_out_mfma(PrefillArgs a) {
-  constexpr int kOwnQ = 32 * WAVES;  // one group of 32 queries per wave
-  extern __shared__ __attribute__((aligned(16))) char lds_dyn[];  // K[2] then V[2] tiles
+__global__ __launch_bounds__(256, 3) void prefill_rows_out_mfma(PrefillArgs a) {
+  constexpr int kOwnQ = 128;  // one group of 32 queries per wave
+  constexpr int NS = OutRing::kStages;
+  __shared__ __attribute__((aligned(1024))) char ring[NS * OutRing::kStageBytes];
   int u, blk_id;
   if (!locate_heads(a.units, a.group, a.pairs, u, blk_id)) return;  // u counts (unit, query head) pairs
   const int uk = u / a.group;  // the unit: its keys, values and length
@@ -1084,12 +1095,16 @@ __global__ __launch_bounds__(WAVES * kWave) void prefill_rows_out_mfma(PrefillAr
   const int n_blocks = (len + kOwnQ - 1) / kOwnQ;
   if (blk_id >= n_blocks) return;
   const int blk = n_blocks - 1 - blk_id;  // long rows first
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int half = lane >> 5;
+  const uint32_t ring_addr = lds_address(ring);
   const size_t ubase = static_cast<size_t>(u) * a.L_max;
+  const size_t kbase = static_cast<size_t>(uk) * a.L_max * kRowBytes;
   const char* Qb = static_cast<const char*>(a.Q) + ubase * kRowBytes;
-  const char* Kb = static_cast<const char*>(a.K) + static_cast<size_t>(uk) * a.L_max * kRowBytes;
-  const char* Vb = static_cast<const char*>(a.V) + static_cast<size_t>(uk) * a.L_max * kRowBytes;
+  // rows past the end come back as zeros
+  const v4i32 kbuf = make_buffer(static_cast<const char*>(a.K) + kbase, static_cast<uint32_t>(len) * kRowBytes);
+  const v4i32 vbuf = make_buffer(static_cast<const char*>(a.V) + kbase, static_cast<uint32_t>(len) * kRowBytes);
   const float sc = a.scale_log2;
   const int w = a.recency_window;
   const float rb = a.recency_bias_log2;
@@ -1097,120 +1112,140 @@ __global__ __launch_bounds__(WAVES * kWave) void prefill_rows_out_mfma(PrefillAr
   const int q0 = blk * kOwnQ;
   const int qw0 = q0 + 32 * wave;
   const int qi = qw0 + (lane & 31);
+  const int n_tiles = (min(len, q0 + kOwnQ) - 1) / OutRing::kRows + 1;
+
+  // this lane's chunks of a tile: a wave loads rows 8 w .. 8 w + 7 of K and of V, four rows per instruction
+  int koff[2], voff[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = 8 * wave + 4 * i + (lane >> 4);
+    koff[i] = r * kRowBytes + (((lane & 15) ^ (r & 15)) << 4);
+    voff[i] = r * kRowBytes + (((lane & 15) ^ ((r & 3) << 2)) << 4);
+  }
+  auto request = [&](int t, int stage) {  // four loads per wave
+    const uint32_t dst = ring_addr + stage * OutRing::kStageBytes + wave * 2048;
+    const int soff = __builtin_amdgcn_readfirstlane(t * OutRing::kTileBytes);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) load16_to_lds(kbuf, dst + i * 1024, koff[i], soff);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) load16_to_lds(vbuf, dst + OutRing::kTileBytes + i * 1024, voff[i], soff);
+  };
+  request(0, 0);
+  if (1 < n_tiles) request(1, 1);
   uint4 own[kKSteps];
   load_owned(own, Qb, qi, len - 1);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the owned rows are in before the loop (see prefill_rows_mfma)
   float m = -INFINITY, l = 0.0f;
   f32x16 o[4];
 #pragma unroll
   for (int db = 0; db < 4; ++db) o[db] = f32x16{0};
 
-  const int tr_off = transposed_fragment_offset();
-
-  const int last_key = min(len, q0 + kOwnQ) - 1;
-  const int n_tiles = last_key / kTile + 1;
-  Staged<WAVES> stK, stV;
-  tile_load(stK, Kb, 0, len - 1);
-  tile_load(stV, Vb, 0, len - 1);
-  for (int t = 0; t < n_tiles; ++t) {
-    char* const tileK = lds_dyn + (t & 1) * kTileBytes;
-    char* const tileV = lds_dyn + 2 * kTileBytes + (t & 1) * kTileBytesV;
-    tile_store(stK, tileK);
-    tile_store<WAVES, kLdsRowV>(stV, tileV);
-    __syncthreads();
-    if (t + 1 < n_tiles) {
-      tile_load(stK, Kb, (t + 1) * kTile, len - 1);
-      tile_load(stV, Vb, (t + 1) * kTile, len - 1);
-    }
+  // fragment reads: K row lane % 32, chunk 2 kk + half; V transposed, rows 4 (lane / 32) + (lane % 16) / 4 (+ 8), the lane's
+  // 8 bytes of columns 32 db + 16 (lane / 16 % 2) + 4 (lane % 4)
+  int kfrag[kKSteps], vfrag[4];
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      const int kb = t * kTile + sub * 32;
-      if (kb > qw0 + 31) continue;  // wholly above the diagonal for every query of this wave
-      // ---- scores of 32 keys x 32 queries
-      f32x16 sacc;
-      {
-        const char* p = tileK + (sub * 32 + (lane & 31)) * kLdsRow + half * 16;
-        const f32x16 zero = {0};
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p)), __builtin_bit_cast(bf16x8, own[0]), zero, 0, 0, 0);
+  for (int kk = 0; kk < kKSteps; ++kk) kfrag[kk] = (lane & 31) * kRowBytes + (((2 * kk + half) ^ (lane & 15)) << 4);
+  {
+    const int rr = (lane & 15) >> 2;
 #pragma unroll
-        for (int kk = 1; kk < kKSteps; ++kk)
-          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p + kk * 32)),
-              __builtin_bit_cast(bf16x8, own[kk]), sacc, 0, 0, 0);
-      }
-      // ---- probabilities against the reference m, as a B operand (bf16), and their sum
-      const bool interior = kb + 31 + w <= qw0;  // wholly visible and wholly outside the recency window
-      bf16x8 pfrag[2];
-      float sum = 0.0f;
-      bool done = false;
-      if (interior) {
-        // The reference need not be the running maximum (see lse_update): the terms are taken against it as it
-        // stands, and only a half-tile whose sum leaves the safe range -- the first one, whose reference is -inf,
-        // and scores that rise by more than 16 powers of two later on -- takes the path below that raises it.  (The
-        // bound is kept low here because the probabilities multiply V: the unnormalised output stays within 2^16 * n
-        // times the largest |v|.)
-        const float neg = -m;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float pv = fast_exp2(fmaf(sacc[r], sc, neg));
-          sum += pv;
-          pfrag[r >> 3][r & 7] = static_cast<__bf16>(pv);
-        }
-        done = __builtin_amdgcn_ballot_w64(!(sum <= 0x1p16f)) == 0;
-      }
-      if (!done) {
-        float tv[16];
-        float mb = -INFINITY;
-        if (interior) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) tv[r] = sacc[r] * sc;
-          mb = max16(sacc) * sc;
-        } else {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
-            float x = sacc[r] * sc;
-            if (w > 0 && qi - key < w) x += rb;
-            if (key > qi) x = -INFINITY;
-            tv[r] = x;
-            mb = fmaxf(mb, x);
-          }
-        }
-        // the two lane halves feed one matrix product, so they must share the reference
-        mb = fmaxf(mb, __shfl_xor(mb, 32, kWave));
-        const float m_new = fmaxf(m, mb);  // finite: the first half-tile holds key 0, which every query sees
-        if (__any(m_new > m)) {
-          const float alpha = fast_exp2(m - m_new);  // 0 when m is still -inf
-          l *= alpha;
-#pragma unroll
-          for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-        }
-        m = m_new;
-        sum = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float pv = fast_exp2(tv[r] - m_new);
-          sum += pv;
-          pfrag[r >> 3][r & 7] = static_cast<__bf16>(pv);
-        }
-      }
-      l += sum;
-      // ---- O^T += V^T . P^T : two 16-key steps x four blocks of 32 head dimensions
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const char* vt = tileV + (sub * 32 + ks * 16) * kLdsRowV + tr_off;
-#pragma unroll
-        for (int db = 0; db < 4; ++db) {
-          const uint2 lo = lds_read_transposed(vt + db * 64);                // keys 4h .. 4h+3 of the step
-          const uint2 hi = lds_read_transposed(vt + 8 * kLdsRowV + db * 64);  // keys 8+4h .. 8+4h+3
-          const uint4 afrag = make_uint4(lo.x, lo.y, hi.x, hi.y);
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, afrag), pfrag[ks], o[db], 0, 0, 0);
-        }
-      }
-    }
+    for (int db = 0; db < 4; ++db)
+      vfrag[db] = OutRing::kTileBytes + (4 * half + rr) * kRowBytes + ((db ^ rr) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
   }
+
+  auto tile = [&](auto stage_tag, int t) {
+    constexpr int S = decltype(stage_tag)::value;
+    if (t + 1 < n_tiles) wait_loads<4>();  // the next tile may still be on its way
+    else wait_loads<0>();
+    __syncthreads();  // tile t is in LDS, and everybody has issued its last read of tile t - 1
+    if (t + 2 < n_tiles) request(t + 2, (S + 2) % NS);
+    const char* const st = ring + S * OutRing::kStageBytes;
+    const int kb = t * OutRing::kRows;
+    if (kb > qw0 + 31) return;  // wholly above the diagonal for every query of this wave
+    // ---- scores of 32 keys x 32 queries
+    f32x16 sacc = {0};
+#pragma unroll
+    for (int kk = 0; kk < kKSteps; ++kk)
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(st + kfrag[kk])), __builtin_bit_cast(bf16x8, own[kk]),
+          sacc, 0, 0, 0);
+    // ---- probabilities against the reference m, as a B operand (bf16), and their sum
+    const bool interior = kb + 31 + w <= qw0;  // wholly visible and wholly outside the recency window
+    bf16x8 pfrag[2];
+    float sum = 0.0f;
+    bool done = false;
+    if (interior) {
+      // The reference need not be the running maximum (see lse_update): the terms are taken against it as it
+      // stands, and only a tile whose sum leaves the safe range -- the first one, whose reference is -inf,
+      // and scores that rise by more than 16 powers of two later on -- takes the path below that raises it.  (The
+      // bound is kept low here because the probabilities multiply V: the unnormalised output stays within 2^16 * n
+      // times the largest |v|.)
+      const float neg = -m;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float pv = fast_exp2(fmaf(sacc[r], sc, neg));
+        sum += pv;
+        pfrag[r >> 3][r & 7] = static_cast<__bf16>(pv);
+      }
+      done = __builtin_amdgcn_ballot_w64(!(sum <= 0x1p16f)) == 0;
+    }
+    if (!done) {
+      float mb = -INFINITY;
+      if (interior) {
+        mb = max16(sacc) * sc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sacc[r] *= sc;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
+          float x = sacc[r] * sc;
+          if (w > 0 && qi - key < w) x += rb;
+          if (key > qi) x = -INFINITY;
+          sacc[r] = x;
+          mb = fmaxf(mb, x);
+        }
+      }
+      // the two lane halves feed one matrix product, so they must share the reference
+      mb = fmaxf(mb, __shfl_xor(mb, 32, kWave));
+      const float m_new = fmaxf(m, mb);  // finite: the first tile holds key 0, which every query sees
+      if (__any(m_new > m)) {
+        const float alpha = fast_exp2(m - m_new);  // 0 when m is still -inf
+        l *= alpha;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      }
+      m = m_new;
+      sum = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float pv = fast_exp2(sacc[r] - m_new);
+        sum += pv;
+        pfrag[r >> 3][r & 7] = static_cast<__bf16>(pv);
+      }
+    }
+    l += sum;
+    // ---- O^T += V^T . P^T : two 16-key steps x four blocks of 32 head dimensions
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int db = 0; db < 4; ++db) {
+        const char* const vt = st + vfrag[db] + ks * (16 * kRowBytes);
+        const uint2 lo = lds_read_transposed(vt);                  // keys 4h .. 4h+3 of the step
+        const uint2 hi = lds_read_transposed(vt + 8 * kRowBytes);  // keys 8+4h .. 8+4h+3
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y)),
+                                                        pfrag[ks], o[db], 0, 0, 0);
+      }
+  };
+  int t = 0;
+  for (; t + 2 < n_tiles; t += 3) {
+    tile(StageTag<0>{}, t);
+    tile(StageTag<1>{}, t + 1);
+    tile(StageTag<2>{}, t + 2);
+  }
+  if (t < n_tiles) tile(StageTag<0>{}, t);
+  if (t + 1 < n_tiles) tile(StageTag<1>{}, t + 1);
   // each lane half summed different keys of the same query
   l += __shfl_xor(l, 32, kWave);
   if (qi < len) {
@@ -1422,21 +1457,13 @@ hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
 
 // Rows pass that also writes O, followed by the ordinary columns pass.
 hipError_t launch_with_output(PrefillArgs& a, hipStream_t s) {
-  constexpr int WAVES = 4;
-  constexpr int kOwnQ = 32 * WAVES;
-  constexpr size_t kLds = 2 * static_cast<size_t>(kTileBytes + kTileBytesV);  // 74 KiB: above the default dynamic limit
-  // set on every call: cheap, and right on whichever device is current
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(prefill_rows_out_mfma<WAVES>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kLds)) != hipSuccess)
-    return hipErrorInvalidValue;
   PrefillArgs b = a;
   b.paired = 0;
-  b.pairs = (a.L_max + kOwnQ - 1) / kOwnQ;  // workgroup ids per unit
+  b.pairs = (a.L_max + 127) / 128;  // workgroup ids per unit
   {
     ProfScope ps(kProfPrefillRows, s);
-    hipLaunchKernelGGL(prefill_rows_out_mfma<WAVES>,
-                       dim3(static_cast<unsigned>((a.units + 7) / 8 * 8 * a.group * b.pairs)), dim3(WAVES * kWave), kLds,
-                       s, b);
+    hipLaunchKernelGGL(prefill_rows_out_mfma, dim3(static_cast<unsigned>((a.units + 7) / 8 * 8 * a.group * b.pairs)),
+                       dim3(256), 0, s, b);
   }
   constexpr int kOwn = Shape<4>::kOwn;
   const int n_blocks = (a.L_max + kOwn - 1) / kOwn;
