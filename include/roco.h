@@ -100,8 +100,8 @@ size_t roco_prefill_workspace_bytes(const roco_params* params, int32_t L_max);
 size_t roco_decode_workspace_bytes(const roco_params* params);
 
 /* Kernels one roco_decode_step call launches for these params (for benchmarks that attribute time and bytes):
- * 1 = one workgroup per unit does the whole step (enough units to fill the chip, budget small enough for its
- * logits and ranking keys to sit in LDS); 2 = slot ranges of a unit on several workgroups, then a merge /
+ * 1 = one workgroup per unit does the whole step (enough units to fill the chip or few bytes per unit, budget small
+ * enough for its logits and ranking keys to sit in LDS); 2 = slot ranges of a unit on several workgroups, then a merge /
  * statistics / selection kernel.  Negative code on invalid params. */
 int roco_decode_step_launches(const roco_params* params);
 
@@ -378,8 +378,9 @@ int roco_probe_mfma(int32_t workgroups, int32_t iters, int32_t operands, float* 
 /*
  * Environment switches (read on the host at every call; meant for tests and tuning, the defaults are the measured
  * choices).  None of them changes what a call computes, only which kernels and launch shapes do it.
- *   ROCO_DECODE_FUSED=0|1      decode step as the split pair / as one kernel (default: one kernel from 128 units on
- *                              when budget <= 4096); roco_decode_step_launches reports the choice
+ *   ROCO_DECODE_FUSED=0|1      decode step as the split pair / as one kernel (default: one kernel from 128 units on when
+ *                              budget <= 4096, and for units of up to 192 KiB of keys and values);
+ *                              roco_decode_step_launches reports the choice
  *   ROCO_DECODE_SPLITS=n       splits of the budget in the split pair (default: until about 128 workgroups exist)
  *   ROCO_DECODE_UNROLL=2|4|8   cache rows in flight per lane group (default 8)
  *   ROCO_DECODE_ROTATE=0|1     staggered start row per workgroup (default 1)

@@ -135,10 +135,15 @@ bool streaming_loads(const roco_params* p) {
 
 // One workgroup per unit once the units cover half of the compute units (measured, bf16, d = 128: 31 vs 34 us per
 // step at 128 units x 2048 slots and 19 vs 23 at 128 x 1024, but 30 vs 24 at 64 x 2048 and 54 vs 36 at 64 x 4096,
-// where a workgroup per unit leaves most of the chip without work).
+// where a workgroup per unit leaves most of the chip without work), and wherever a unit's keys and values are so few that
+// the second launch costs more than a compute unit needs for them (one kernel against two, us per step in a graph, 4 / 40
+// units: 32 KiB 8.8 / 9.2 against 11.1 / 11.6; 128 KiB 9.9 / 10.4 against 11.4 / 12.0; 256 KiB 12.7 / 13.1 against
+// 12.5 / 13.1 with bf16 / 128, 11.4 / 11.8 against 11.8 / 12.3 with fp32 / 64; 512 KiB 18 against 13 to 17).
 bool decode_is_fused(const roco_params* p) {
   const int want = env_int("ROCO_DECODE_FUSED", -1);
-  return (want < 0 ? p->units >= 128 : want != 0) && p->budget <= kMaxFusedBudget;
+  const size_t row = static_cast<size_t>(p->head_dim) * (p->dtype == ROCO_BF16 ? 2 : 4);
+  const bool little = 2 * row * p->budget <= (192u << 10);
+  return (want < 0 ? p->units >= 128 || little : want != 0) && p->budget <= kMaxFusedBudget;
 }
 
 }  // namespace

@@ -90,3 +90,15 @@ def test_prompts_on_both_sides_of_what_lds_holds(L):
         total = float(c.stats[u, 0].double().sum())
         assert 0.0 < total < n
         assert int(c.next_slot[u]) == sinks
+
+
+@pytest.mark.parametrize("dtype,d,B", [("bf16", 128, 384), ("bf16", 128, 385), ("f32", 64, 384), ("f32", 64, 385),
+                                       ("f32", 128, 192), ("f32", 128, 193), ("bf16", 64, 768), ("bf16", 64, 769)])
+def test_decode_steps_on_both_sides_of_the_one_kernel_rule(dtype, d, B):
+    """Units of up to 192 KiB of keys and values take one kernel per step whatever their number."""
+    import paper_2402_06262_amd as roco
+    import test_gpu_parity as TP
+    row = d * (2 if dtype == "bf16" else 4)
+    p = roco.RocoParams(3, d, B, 9, roco.ROCO_BF16 if dtype == "bf16" else roco.ROCO_F32)
+    assert roco.decode_step_launches(p) == (1 if 2 * B * row <= 192 * 1024 else 2)
+    TP.run_workload(dtype, d, 3, [B + 5, B, B - 2], B + 5, B, 9, 4, seed=B, want_out=False, tag=f"one-kernel-{dtype}-{d}-{B}")
