@@ -171,6 +171,15 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+def _ptrs(*ts):
+    """Device addresses of several tensors: `_ptr` of each, without a call per tensor where all of them are tensors (a
+    small decode step takes less time than its fourteen calls did: 6.3 -> 5.6 us of host time)."""
+    try:
+        return [None if t is None else t.data_ptr() if t.is_contiguous() else _ptr(t) for t in ts]
+    except AttributeError:  # a plain address among them
+        return [_ptr(t) for t in ts]
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
@@ -184,10 +193,10 @@ def roco_prefill_compress(params: RocoParams, Q, K, V, length, L_max: int, K_cac
                           n_used, next_slot, O, workspace, workspace_bytes: Optional[int] = None, stream=None) -> None:
     """See include/roco.h.  Tensors are device tensors; `O` may be None."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
+        workspace_bytes = workspace.nbytes
     rc = load_library().roco_prefill_compress(
-        ctypes.byref(params), _ptr(Q), _ptr(K), _ptr(V), _ptr(length), int(L_max), _ptr(K_cache),
-        _ptr(V_cache), _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot), _ptr(O), _ptr(workspace),
+        ctypes.byref(params), *_ptrs(Q, K, V, length), int(L_max),
+        *_ptrs(K_cache, V_cache, stats, pos, n_used, next_slot, O, workspace),
         int(workspace_bytes),
         _stream(stream))
     if rc != 0:
@@ -199,11 +208,12 @@ def roco_decode_step(params: RocoParams, q, k_new, v_new, qpos, K_cache, V_cache
                      stream=None) -> None:
     """See include/roco.h.  `evicted_slot` / `evicted_pos` may be None."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
+        workspace_bytes = workspace.nbytes
     rc = load_library().roco_decode_step(
-        ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(qpos), _ptr(K_cache), _ptr(V_cache),
-        _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot), _ptr(out), _ptr(evicted_slot), _ptr(evicted_pos),
-        _ptr(workspace), int(workspace_bytes), _stream(stream))
+        ctypes.byref(params),
+        *_ptrs(q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot,
+               out, evicted_slot, evicted_pos, workspace),
+        int(workspace_bytes), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_decode_step")
 
@@ -212,8 +222,9 @@ def roco_decode_step_static(params: RocoParams, q, k_new, v_new, qpos, K_cache, 
                             next_slot, out, evicted_slot, evicted_pos, stream=None) -> None:
     """See include/roco.h: the decode step on the library's own static scratch (no workspace, no allocation)."""
     rc = load_library().roco_decode_step_static(
-        ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(qpos), _ptr(K_cache), _ptr(V_cache),
-        _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot), _ptr(out), _ptr(evicted_slot), _ptr(evicted_pos),
+        ctypes.byref(params),
+        *_ptrs(q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot,
+               out, evicted_slot, evicted_pos),
         _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_decode_step_static")
@@ -228,10 +239,10 @@ def roco_prefill_compress_gqa(params: RocoParams, group: int, Q, K, V, lens, L_m
                               stream=None) -> None:
     """See include/roco.h: prefill with one-step eviction for key/value heads shared by `group` query heads."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
+        workspace_bytes = workspace.nbytes
     rc = load_library().roco_prefill_compress_gqa(
-        ctypes.byref(params), int(group), _ptr(Q), _ptr(K), _ptr(V), _ptr(lens), int(L_max), _ptr(K_cache),
-        _ptr(V_cache), _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot), _ptr(O), _ptr(workspace),
+        ctypes.byref(params), int(group), *_ptrs(Q, K, V, lens), int(L_max),
+        *_ptrs(K_cache, V_cache, stats, pos, n_used, next_slot, O, workspace),
         int(workspace_bytes), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_prefill_compress_gqa")
@@ -242,10 +253,11 @@ def roco_prefill_compress_lse(params: RocoParams, group: int, Q, K, V, lens, L_m
                               stream=None) -> None:
     """See include/roco.h: prefill-compress from row normalisers the caller's attention kernel already produced."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
+        workspace_bytes = workspace.nbytes
     rc = load_library().roco_prefill_compress_lse(
-        ctypes.byref(params), int(group), _ptr(Q), _ptr(K), _ptr(V), _ptr(lens), int(L_max), _ptr(lse), _ptr(K_cache),
-        _ptr(V_cache), _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot), _ptr(workspace), int(workspace_bytes),
+        ctypes.byref(params), int(group), *_ptrs(Q, K, V, lens), int(L_max),
+        *_ptrs(lse, K_cache, V_cache, stats, pos, n_used, next_slot, workspace),
+        int(workspace_bytes),
         _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_prefill_compress_lse")
@@ -268,11 +280,12 @@ def roco_encode_block(params: RocoParams, block: int, q, k_new, v_new, qpos0, K_
                       stream=None) -> None:
     """See include/roco.h: free and encode `block` tokens within one eviction step."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
+        workspace_bytes = workspace.nbytes
     rc = load_library().roco_encode_block(
-        ctypes.byref(params), int(block), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(qpos0), _ptr(K_cache),
-        _ptr(V_cache), _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot), _ptr(out), _ptr(evicted_slot),
-        _ptr(evicted_pos), _ptr(workspace), int(workspace_bytes), _stream(stream))
+        ctypes.byref(params), int(block),
+        *_ptrs(q, k_new, v_new, qpos0, K_cache, V_cache, stats, pos, n_used, next_slot,
+               out, evicted_slot, evicted_pos, workspace),
+        int(workspace_bytes), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_encode_block")
 
@@ -282,11 +295,12 @@ def roco_encode_block_gqa(params: RocoParams, block: int, group: int, q, k_new, 
                           workspace_bytes: Optional[int] = None, stream=None) -> None:
     """See include/roco.h: block-wise step of key/value heads shared by `group` query heads each."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
+        workspace_bytes = workspace.nbytes
     rc = load_library().roco_encode_block_gqa(
-        ctypes.byref(params), int(block), int(group), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(qpos0), _ptr(K_cache),
-        _ptr(V_cache), _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot), _ptr(out), _ptr(evicted_slot),
-        _ptr(evicted_pos), _ptr(workspace), int(workspace_bytes), _stream(stream))
+        ctypes.byref(params), int(block), int(group),
+        *_ptrs(q, k_new, v_new, qpos0, K_cache, V_cache, stats, pos, n_used, next_slot,
+               out, evicted_slot, evicted_pos, workspace),
+        int(workspace_bytes), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_encode_block_gqa")
 
@@ -296,11 +310,12 @@ def roco_decode_step_gqa(params: RocoParams, group: int, q, k_new, v_new, qpos, 
                          stream=None) -> None:
     """See include/roco.h: one decode step of key/value heads shared by `group` query heads each."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
+        workspace_bytes = workspace.nbytes
     rc = load_library().roco_decode_step_gqa(
-        ctypes.byref(params), int(group), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(qpos), _ptr(K_cache),
-        _ptr(V_cache), _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot), _ptr(out), _ptr(evicted_slot),
-        _ptr(evicted_pos), _ptr(workspace), int(workspace_bytes), _stream(stream))
+        ctypes.byref(params), int(group),
+        *_ptrs(q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot,
+               out, evicted_slot, evicted_pos, workspace),
+        int(workspace_bytes), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_decode_step_gqa")
 
@@ -309,8 +324,8 @@ def roco_probe_cache_read(params: RocoParams, K_cache, V_cache, workspace, works
                           stream=None) -> None:
     """See include/roco.h: the loads of the decode attention kernel, and nothing else (benchmark aid)."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
-    rc = load_library().roco_probe_cache_read(ctypes.byref(params), _ptr(K_cache), _ptr(V_cache), _ptr(workspace),
+        workspace_bytes = workspace.nbytes
+    rc = load_library().roco_probe_cache_read(ctypes.byref(params), *_ptrs(K_cache, V_cache, workspace),
                                               int(workspace_bytes), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_probe_cache_read")
@@ -329,9 +344,9 @@ def roco_probe_mfma(workgroups: int, iters: int, sink, stream=None, random_opera
 
 def roco_set_overlap(pos_a, mask_a, n_used_a, pos_b, mask_b, n_used_b, max_pos: int, inter, uni, stream=None) -> None:
     """See include/roco.h: |A and B| and |A or B| per unit of two sets of cached positions (masks may be None)."""
-    rc = load_library().roco_set_overlap(int(pos_a.shape[0]), int(pos_a.shape[1]), _ptr(pos_a), _ptr(mask_a), _ptr(n_used_a),
-                                         int(pos_b.shape[1]), _ptr(pos_b), _ptr(mask_b), _ptr(n_used_b), int(max_pos),
-                                         _ptr(inter), _ptr(uni), _stream(stream))
+    rc = load_library().roco_set_overlap(int(pos_a.shape[0]), int(pos_a.shape[1]), *_ptrs(pos_a, mask_a, n_used_a),
+                                         int(pos_b.shape[1]), *_ptrs(pos_b, mask_b, n_used_b), int(max_pos),
+                                         *_ptrs(inter, uni), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_set_overlap")
 
@@ -340,9 +355,10 @@ def roco_select_victims(params: RocoParams, stats, pos, n_used, next_slot, works
                         workspace_bytes: Optional[int] = None, stream=None) -> None:
     """See include/roco.h: recompute next_slot from stats / pos / n_used."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
-    rc = load_library().roco_select_victims(ctypes.byref(params), _ptr(stats), _ptr(pos), _ptr(n_used), _ptr(next_slot),
-                                            _ptr(workspace), int(workspace_bytes), _stream(stream))
+        workspace_bytes = workspace.nbytes
+    rc = load_library().roco_select_victims(ctypes.byref(params),
+        *_ptrs(stats, pos, n_used, next_slot, workspace),
+        int(workspace_bytes), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_select_victims")
 
@@ -351,9 +367,10 @@ def roco_select_retained(params: RocoParams, keep: int, stats, pos, n_used, mask
                          workspace_bytes: Optional[int] = None, stream=None) -> None:
     """See include/roco.h: mask of the tokens that survive a shrink of every unit to `keep` tokens."""
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size()
-    rc = load_library().roco_select_retained(ctypes.byref(params), int(keep), _ptr(stats), _ptr(pos), _ptr(n_used),
-                                             _ptr(mask), _ptr(workspace), int(workspace_bytes), _stream(stream))
+        workspace_bytes = workspace.nbytes
+    rc = load_library().roco_select_retained(ctypes.byref(params), int(keep),
+        *_ptrs(stats, pos, n_used, mask, workspace),
+        int(workspace_bytes), _stream(stream))
     if rc != 0:
         raise RocoError(rc, "roco_select_retained")
 
