@@ -97,32 +97,36 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
       else next = r;
     }
   }
-  // ordered compaction: thread t owns the contiguous positions [t*c, (t+1)*c)
-  const int c = (n + NT - 1) / NT;
-  const int lo = min(n, tid * c), hi = min(n, lo + c);
-  uint32_t mine = 0;
+  // ordered compaction, NT positions at a time: a token's slot is the number of retained tokens before it, counted by ballots
+  // inside a wave and by the waves' totals in LDS before it
   uint32_t best_key = 0xffffffffu, best = 0xffffffffu;  // importance and position of the first decode victim
+  uint32_t before = 0;  // retained tokens of earlier rounds
+  uint32_t best_slot = 0;
 #pragma unroll 1
-  for (int i = lo; i < hi; ++i) {
-    if (evicted(i)) continue;
-    ++mine;
-    if (n >= B && next.has(var_key[i], i)) {
-      const uint32_t k = mas_key[i];
-      if (k < best_key || best == 0xffffffffu) { best_key = k; best = static_cast<uint32_t>(i); }
-    }
-  }
-  uint32_t total;
-  const uint32_t first = block_exclusive_scan<NT>(mine, scan_sh, total);
-  uint32_t dst = first;
-#pragma unroll 1
-  for (int i = lo; i < hi; ++i) {
-    if (!evicted(i) && dst < static_cast<uint32_t>(B)) {
+  for (int base = 0; base < n; base += NT) {
+    const int i = base + tid;
+    const bool in = i < n;
+    float2 s = make_float2(0.0f, 0.0f);
+    if (in) s = sums(i);
+    const bool keep = in && !evicted(i);
+    const uint64_t votes = __builtin_amdgcn_ballot_w64(keep);
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    __syncthreads();  // the previous round's totals have been read
+    if (lane == 0) scan_sh[wave] = __builtin_popcountll(votes);
+    __syncthreads();
+    const uint32_t totals = wave_inclusive_scan(lane < NT / kWave ? scan_sh[lane] : 0u);
+    uint32_t dst = before + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(votes >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(votes), 0));
+    if (wave > 0) dst += __builtin_amdgcn_readlane(totals, __builtin_amdgcn_readfirstlane(wave) - 1);
+    before += __builtin_amdgcn_readlane(totals, NT / kWave - 1);
+    if (keep && dst < static_cast<uint32_t>(B)) {
       pos[dst] = i;
-      const float2 s = sums(i);
       oacc[dst] = s.x;
       oacc2[dst] = s.y;
       ocnt[dst] = static_cast<float>(n - i);
-      ++dst;
+      if (n >= B && next.has(var_key[i], i)) {
+        const uint32_t k = mas_key[i];
+        if (k < best_key || best == 0xffffffffu) { best_key = k; best = static_cast<uint32_t>(i); best_slot = dst; }
+      }
     }
   }
 #pragma unroll 1
@@ -138,13 +142,8 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
     return;
   }
   // the first decode step on a full cache needs its victim
-  const int victim = static_cast<int>(block_argmin<NT>(best_key, best, best_sh));
-  if (victim >= lo && victim < hi) {  // its owner knows which slot it went to
-    uint32_t slot = first;
-#pragma unroll 1
-    for (int i = lo; i < victim; ++i) slot += evicted(i) ? 0u : 1u;
-    a.next_slot[u] = static_cast<int>(slot);
-  }
+  const uint32_t victim = block_argmin<NT>(best_key, best, best_sh);
+  if (victim == best) a.next_slot[u] = static_cast<int>(best_slot);  // its owner knows which slot it went to
 }
 
 template <int ROW_BYTES>
@@ -274,7 +273,7 @@ hipError_t launch_prefill_select_compact(int dtype, int head_dim, const PrefillA
     if (key_lds != 0) {
       if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<2>), key_lds)) return hipErrorInvalidValue;
       hipLaunchKernelGGL(prefill_select<2>, dim3(a.units), dim3(kSelThreads), key_lds, s, a);
-    } else if (a.L_max <= 2 * kMaxDecodeBudgetLds) {  // one key per token still fits (40 units x 32768 tokens: 156 us against 200)
+    } else if (a.L_max <= 2 * kMaxDecodeBudgetLds) {  // one key per token still fits (40 units x 32768 tokens: 125 us against 200)
       const size_t one = static_cast<size_t>(a.L_max) * sizeof(uint32_t);
       if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<1>), one)) return hipErrorInvalidValue;
       hipLaunchKernelGGL(prefill_select<1>, dim3(a.units), dim3(kSelThreads), one, s, a);
