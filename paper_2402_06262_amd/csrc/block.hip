@@ -63,6 +63,15 @@ __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
   uint32_t* const var_key = LDS ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
   uint32_t* const mas_key = var_key + B;
 
+  // The block's K / V rows (16 bytes per lane, a power of two of lanes per row) are requested now and stored at the end: the
+  // first NT / lanes rows are under way while the victims are chosen (16 tokens on 512 units: 23.4 -> 21.5 us).
+  const int lanes_log2 = __builtin_ctz(a.row_bytes) - 4;
+  const int my_row = tid >> lanes_log2, my_col = (tid & ((1 << lanes_log2) - 1)) * 16;
+  const size_t in_base = static_cast<size_t>(u) * b * a.row_bytes + my_col;
+  auto new_row = [&](const void* rows, int i) { return load16(static_cast<const char*>(rows) + in_base + static_cast<size_t>(i) * a.row_bytes); };
+  const int safe_row = min(my_row, b - 1);
+  uint4 k_row = new_row(a.k_new, safe_row), v_row = new_row(a.v_new, safe_row);
+
   if (tid < kMaxBlock) slot_of[tid] = 0;
   KSmallest scope = {0u, 0u}, out = {0u, 0u};
   // one eviction from a full cache: the victim was already chosen when the statistics were last updated
@@ -117,15 +126,13 @@ __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
     bidx[j] = bi;
   }
   __syncthreads();
-  // the block's K / V rows go into their slots: 16 bytes per lane
-  const int lpr = a.row_bytes / 16;  // lanes per row: 8, 16 or 32
-  const size_t in_base = static_cast<size_t>(u) * b * a.row_bytes;
 #pragma unroll 1
-  for (int i = tid / lpr; i < b; i += NT / lpr) {
-    const size_t dst = (static_cast<size_t>(u) * B + slot_of[i]) * a.row_bytes + (tid % lpr) * 16;
-    const size_t src = in_base + static_cast<size_t>(i) * a.row_bytes + (tid % lpr) * 16;
-    *reinterpret_cast<uint4*>(static_cast<char*>(a.K) + dst) = load16(static_cast<const char*>(a.k_new) + src);
-    *reinterpret_cast<uint4*>(static_cast<char*>(a.V) + dst) = load16(static_cast<const char*>(a.v_new) + src);
+  for (int i = my_row; i < b;) {
+    const size_t dst = (static_cast<size_t>(u) * B + slot_of[i]) * a.row_bytes + my_col;
+    *reinterpret_cast<uint4*>(static_cast<char*>(a.K) + dst) = k_row;
+    *reinterpret_cast<uint4*>(static_cast<char*>(a.V) + dst) = v_row;
+    i += NT >> lanes_log2;
+    if (i < b) { k_row = new_row(a.k_new, i); v_row = new_row(a.v_new, i); }
   }
   if (tid == 0) a.n_used[u] = n_new;
 }
