@@ -222,7 +222,7 @@ def side_workloads(torch, roco, seed, which):
                                      "frac": tf / MFMA_BF16_PEAK_TFLOPS, "flops": flops}
         else:
             r["roofline_prefill"] = {"bound": "alu", "achieved": tf, "peak": None, "unit": "TFLOP/s", "frac": None,
-                                     "note": "fp32 / head_dim 64 takes the vector-ALU passes; 4 units: latency, no claim"}
+                                     "note": "4 units: latency, no claim"}
         if steps:
             qpos = (torch.arange(steps, dtype=torch.int32, device="cuda")[:, None] + L).expand(steps, U).contiguous()
             out = torch.empty((U, d), dtype=dt, device="cuda")
