@@ -221,7 +221,7 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
   // Up to 64 tokens a tiny fp32 prompt is one tile: splitting it into planes costs more than its products (both passes of
   // fp32 / 128 at 16 units x 48 tokens: 19 us against 29).
   const bool simple = env_int("ROCO_PREFILL_SIMPLE", 0) != 0 || (wide_bf16 && L_max > (1 << 22)) ||
-                      (params->dtype == ROCO_F32 && L_max <= 64 && prefill_is_tiny(a));
+                      (params->dtype == ROCO_F32 && L_max <= 64 && prefill_is_tiny(a, 524288.0));
   if (want_lse) {  // the kernels keep base-2 normalisers
     const size_t count = static_cast<size_t>(params->units) * group * L_max;
     if (launch_lse_to_base2(lse_given, a.lse, count, s) != hipSuccess) return ROCO_EHIP;

@@ -1,6 +1,6 @@
 // Prefill attention statistics on the plain vector ALUs, for every supported dtype / head_dim.
 //
-// The path of fp32 prompts too small for the matrix cores to pay (see prefill_is_tiny), of bf16 / 128 prompts above 4M
+// The path of prompts too small for the matrix cores to pay (see prefill_rows_are_tiny), of bf16 / 128 prompts above 4M
 // tokens, and the cross-check for the matrix-core paths.
 // Two passes, because a column statistic needs the final normaliser of every row it sums over:
 //   pass 1: one wave per query row i streams keys 0..i with an online softmax and stores the row's base-2
@@ -238,7 +238,8 @@ hipError_t launch_prefill_last_row(int dtype, int head_dim, const PrefillArgs& a
 }
 
 void launch_prefill_rows_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s) {
-  if (dtype == kF32 && head_dim == 64) launch_rows_t<kF32, 64>(a, s);
+  if (dtype == kBF16) launch_rows_t<kBF16, 64>(a, s);  // (bf16 / 128 has passes of its own)
+  else if (head_dim == 64) launch_rows_t<kF32, 64>(a, s);
   else launch_rows_t<kF32, 128>(a, s);
 }
 

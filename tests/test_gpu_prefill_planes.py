@@ -140,6 +140,10 @@ def test_ends_of_the_fp32_range(d, monkeypatch):
 
 
 def test_tiny_prompts_take_the_vector_passes_and_agree(monkeypatch):
-    """Both sides of the size rules of fp32 prompts: 64 tokens and 2^19 = units x heads x L^2."""
+    """Both sides of the size rules: 64 tokens, 2^19 = units x heads x L^2 (fp32 with output), 2^17 (bf16 with output, fp32
+    without up to 128 tokens)."""
     for units, L in ((2, 64), (2, 65), (8, 256), (9, 256)):
         TP.run_workload("f32", 64, units, [L] * units, L, L // 2, 5, 1, seed=units + L, tag="planes-tiny")
+    for units, L in ((8, 128), (9, 128), (2, 129)):
+        TP.run_workload("f32", 128, units, [L] * units, L, L // 2, 5, 1, seed=units + L, want_out=False, tag="planes-tiny")
+        TP.run_workload("bf16", 64, units, [L] * units, L, L // 2, 5, 1, seed=units + L, tag="planes-tiny")
