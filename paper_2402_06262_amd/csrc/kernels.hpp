@@ -155,13 +155,13 @@ hipError_t launch_prefill_attention_planes(int dtype, int head_dim, PrefillArgs&
 // workgroup of the matrix-core pass has walked its tiles one after the other.  Row pass, us, vector against matrix:
 // fp32 / 64 with output 4 units x 256 tokens 12 / 20, 1 x 512 19 / 29, 16 x 128 11 / 15, but 16 x 256 23 / 20 and 256 x 48
 // 17 / 12; bf16 / 64 with output 4 x 128 8 / 10.5, 1 x 256 10.3 / 11.6, but 4 x 256 12.1 / 11.9; fp32 / 128 without output
-// 4 x 128 12.8 / 14.6, but 16 x 128 14.9 / 14.7 and 1 x 256 20 / 16.
+// 4 x 128 12.8 / 14.6, but 16 x 128 14.9 / 14.7 and 1 x 256 20 / 16; 2 x 140 of fp32 / 64 9.5 / 12.4, of / 128 13.8 / 14.7.
 inline bool prefill_is_tiny(const PrefillArgs& a, double scores) {
   return static_cast<double>(a.units) * a.group * a.L_max * a.L_max <= scores;
 }
 inline bool prefill_rows_are_tiny(const PrefillArgs& a, bool fp32) {
   if (a.O != nullptr) return prefill_is_tiny(a, fp32 ? 524288.0 : 131072.0);
-  return fp32 && a.L_max <= 128 && prefill_is_tiny(a, 131072.0);
+  return fp32 && a.L_max <= 144 && prefill_is_tiny(a, 131072.0);
 }
 void launch_prefill_rows_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);  // the row pass alone
 // second shares of PrefillArgs::ksplit / qsplit merged into the first ones
