@@ -165,8 +165,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // and the two leading mantissa bits spread a unit's variances or scores over bins of a quarter octave, and usually few
 // enough keys share the chosen one that no second digit is counted -- as soon as a bin holds at most kSelectRanked keys they
 // are gathered and searched without another barrier.  A thread clears the bins it owns while it reads them, so a digit takes three barriers.
-// The largest key, 0xffffffff, is the mark of elements that do not take part: it is not counted (thousands of additions to
-// one bin would be served one after the other).
+// The largest key, 0xffffffff, is the mark of elements that do not take part: it is neither counted (thousands of additions
+// to one bin would be served one after the other) nor gathered, also where its neighbours, the keys of attention sinks, are.
 // `sh` needs kSelectLdsWords words of LDS.  All threads of the block call it.
 constexpr int kSelectBins = 2048;
 constexpr int kSelectRanked = 128;
@@ -187,6 +187,7 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, ui
   for (int i = 0; i < OWN; ++i) sh[tid * OWN + i] = 0;
   __syncthreads();
   uint32_t prefix = 0, mask = 0, kk = k, less = 0, neq = 0;
+  auto takes_part = [&](uint32_t key) { return (key & mask) == prefix && key != 0xffffffffu; };
 #pragma unroll 1
   for (int pass = 0; pass < 3; ++pass) {
     const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
@@ -194,7 +195,7 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, ui
 #pragma unroll UNROLL
     for (int i = tid; i < n; i += NT) {
       const uint32_t key = key_of(i);
-      if ((key & mask) == prefix && key != 0xffffffffu) atomicAdd(&sh[(key >> shift) & digit], 1u);
+      if (takes_part(key)) atomicAdd(&sh[(key >> shift) & digit], 1u);
     }
     __syncthreads();
     uint32_t h[OWN], sum = 0;
@@ -240,7 +241,7 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, ui
 #pragma unroll UNROLL
       for (int i = tid; i < n; i += NT) {
         const uint32_t key = key_of(i);
-        if ((key & mask) == prefix) sh[atomicAdd(&res[3], 1u)] = key;
+        if (takes_part(key)) sh[atomicAdd(&res[3], 1u)] = key;
       }
       __syncthreads();
       const uint32_t c0 = sh[lane], c1 = sh[lane + kWave];

@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import roco_oracle as orc
+
 pytestmark = pytest.mark.gpu
 
 
@@ -102,3 +104,82 @@ def test_decode_steps_on_both_sides_of_the_one_kernel_rule(dtype, d, B):
     p = roco.RocoParams(3, d, B, 9, roco.ROCO_BF16 if dtype == "bf16" else roco.ROCO_F32)
     assert roco.decode_step_launches(p) == (1 if 2 * B * row <= 192 * 1024 else 2)
     TP.run_workload(dtype, d, 3, [B + 5, B, B - 2], B + 5, B, 9, 4, seed=B, want_out=False, tag=f"one-kernel-{dtype}-{d}-{B}")
+
+
+# Window and variance scopes with no more than `sinks` tokens beyond the victims: the last victim is a sink, whose key is next
+# to the mark of the tokens outside the scope, of which there are up to 4 thousand.
+SINKS = [(300, 200, 1, 4), (4096, 1024, 4, 4), (8192, 4096, 1, 4), (16400, 8200, 1, 4), (700, 500, 150, 200)]
+
+
+def _sink_policy(kind):
+    import paper_2402_06262_amd as roco
+    return roco.ROCO_SCOPE_WINDOW if kind == "window" else roco.ROCO_SCOPE_STD
+
+
+@pytest.mark.parametrize("kind", ["window", "std"])
+@pytest.mark.parametrize("n,keep,scope,sinks", SINKS)
+def test_sinks_are_evicted_only_when_nothing_else_is_in_the_scope(kind, n, keep, scope, sinks):
+    import paper_2402_06262_amd as roco
+    units = 3
+    p = roco.RocoParams(units, 64, n, scope, roco.ROCO_F32, importance=roco.ROCO_IMPORTANCE_OLDEST,
+                        scope_kind=_sink_policy(kind), sinks=sinks)
+    pos = np.broadcast_to(np.arange(n, dtype=np.int32), (units, n)).copy()
+    pos[1] = pos[1][::-1]  # the sinks in the last slots
+    # one query seen by every token: acc2 - acc^2 is the variance, exact in fp32 and growing with the position
+    var = pos.astype(np.float32)
+    stats = torch.from_numpy(np.stack([np.zeros_like(var), var, np.ones_like(var)], axis=1)).cuda()
+    n_used = torch.full((units,), n, dtype=torch.int32, device="cuda")
+    mask = torch.empty((units, n), dtype=torch.int32, device="cuda")
+    ws = torch.empty(roco.decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    roco.roco_select_retained(p, keep, stats, torch.from_numpy(pos).cuda(), n_used, mask, ws)
+    got = mask.cpu().numpy()
+    for u in range(units):
+        imp = np.where(pos[u] < sinks, np.inf, pos[u].astype(np.float64))
+        want = np.ones(n, np.int32)
+        want[orc.select_evictions(imp, pos[u].astype(np.float64), scope, n - keep)] = 0
+        assert (imp[want == 0] == np.inf).any()  # a sink is among the victims
+        assert np.array_equal(got[u], want), u
+
+
+@pytest.mark.parametrize("n,keep,scope,sinks", SINKS)
+def test_prompt_that_evicts_a_sink(n, keep, scope, sinks):
+    import paper_2402_06262_amd as roco
+    units = 2
+    p = roco.RocoParams(units, 64, keep, scope, roco.ROCO_BF16, importance=roco.ROCO_IMPORTANCE_OLDEST,
+                        scope_kind=roco.ROCO_SCOPE_WINDOW, sinks=sinks)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    Q, K, V = (torch.randn((units, n, 64), generator=g, device="cuda").bfloat16() for _ in range(3))
+    c = roco.alloc_cache(p)
+    ws = torch.empty(roco.prefill_workspace_bytes(p, n), dtype=torch.uint8, device="cuda")
+    roco.roco_prefill_compress(p, Q, K, V, torch.full((units,), n, dtype=torch.int32, device="cuda"), n, c.K, c.V, c.stats,
+                               c.pos, c.n_used, c.next_slot, None, ws)
+    pos = np.arange(n)
+    imp = np.where(pos < sinks, np.inf, pos.astype(np.float64))
+    kept = np.setdiff1d(pos, orc.select_evictions(imp, pos.astype(np.float64), scope, n - keep))
+    assert kept[0] > 0 and len(kept) == keep  # the first sink is gone
+    first = int(orc.select_victim(imp[kept], kept.astype(np.float64), scope))
+    for u in range(units):
+        assert np.array_equal(c.pos[u].cpu().numpy(), kept)
+        assert torch.equal(c.K[u].cpu(), K[u].cpu()[torch.from_numpy(kept)])
+        assert int(c.next_slot[u]) == first
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("n,scope", [(256, 2), (4096, 4)])
+def test_block_that_evicts_a_sink(dtype, d, n, scope):
+    import parity as P
+    import paper_2402_06262_amd as roco
+    units, block, sinks = 2, 16, 4
+    rng = np.random.default_rng(n)
+    sess = P.make_session(units, d, n, scope, dtype, policy=orc.Policy("oldest", "window", sinks))
+    K, V = (rng.standard_normal((units, n, d)).astype(np.float32) for _ in range(2))
+    P.gpu_prefill(sess, K, K, V, [n] * units, False)
+    new = [rng.standard_normal((units, block, d)).astype(np.float32) for _ in range(3)]
+    ws = torch.empty(roco.block_workspace_bytes(sess.params, block), dtype=torch.uint8, device="cuda")
+    _, slots, evicted = P.gpu_encode_block(sess, block, *new, [n] * units, ws)
+    pos = np.arange(n)
+    imp = np.where(pos < sinks, np.inf, pos.astype(np.float64))
+    want = orc.select_evictions(imp, pos.astype(np.float64), scope, block)
+    assert want[0] == 0
+    for u in range(units):
+        assert np.array_equal(np.sort(slots[u]), want) and np.array_equal(np.sort(evicted[u]), want)
