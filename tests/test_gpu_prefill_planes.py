@@ -147,3 +147,21 @@ def test_tiny_prompts_take_the_vector_passes_and_agree(monkeypatch):
     for units, L in ((8, 128), (9, 128), (2, 129)):
         TP.run_workload("f32", 128, units, [L] * units, L, L // 2, 5, 1, seed=units + L, want_out=False, tag="planes-tiny")
         TP.run_workload("bf16", 64, units, [L] * units, L, L // 2, 5, 1, seed=units + L, tag="planes-tiny")
+
+
+@pytest.mark.parametrize("L,lens", [(90, [90, 65]), (450, [450, 333]), (1500, [1500, 1027])])
+def test_bf16_output_is_rounded_once(L, lens):
+    """head_dim 64: the probabilities are fp32 numbers whatever kernel a prompt's size selects, so an output is the float64
+    result rounded to bf16 but where that lies within fp32's error of a rounding boundary.  Bound: errors of 1e-5 of the row's
+    rms (fp32 sums, as for fp32 storage) against boundaries 2^-8 of a value apart reach one in 0.5 % of the values of that
+    size, more of the smaller ones: 2 % in all.  Probabilities rounded to bf16 before the product miss a third of them."""
+    P = TP._parity()
+    rng = np.random.default_rng(L)
+    units, d = len(lens), 64
+    Q, K, V = (round_to_bf16(rng.standard_normal((units, L, d)).astype(np.float32)) for _ in range(3))
+    sess = P.make_session(units, d, L, 5, "bf16")
+    O = P.gpu_prefill(sess, Q, K, V, lens, True)["O"]
+    for u, n in enumerate(lens):
+        want = orc.prefill_statistics(Q[u], K[u], V[u], n, 1.0 / math.sqrt(d), want_out=True).out
+        exact = torch.from_numpy(want).bfloat16().float().numpy()
+        assert np.mean(O[u, :n] != exact) < 0.02
