@@ -706,7 +706,8 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
       const float2 ml = part_ml[i];
       L += (ml.x > -INFINITY) ? ml.y * fast_exp2(ml.x - M) : 0.0f;
     }
-    weight[tid] = (mine.x > -INFINITY) ? fast_exp2(mine.x - M) : 0.0f;
+    // (a split that attended nothing has no partials; a weight that underflows still meets an infinite partial)
+    weight[tid] = (mine.x > -INFINITY) ? fast_exp2(mine.x - M) : -1.0f;
     if (tid < nq) norm[tid] = make_float2(M, 1.0f / L);
   }
   __syncthreads();  // every thread has read n_used and next_slot
@@ -731,7 +732,7 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
     for (int s = 0; s < kMaxBlockSplits; ++s) {
       if (s < S) {
         const float wgt = weight[s * QR + q];
-        o += wgt > 0.0f ? part[s] * wgt : 0.0f;
+        o += wgt < 0.0f ? 0.0f : part[s] * wgt;
       }
     }
     store_elem<DT>(a.out, (static_cast<size_t>(u) * nq + q) * D + dd, o * norm[q].y);
