@@ -509,8 +509,8 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
 // pass 1 with the attention output O_i = sum_j P[i,j] v_j (see prefill_rows_out_mfma for the operand layouts).  The
 // probabilities are fp32 numbers and are taken apart into three planes: a bf16 V, which is one plane, takes three products
 // of 32 keys (one, of bf16 probabilities, misrounds 40 % of the outputs where three misround 0.03 %; 32 units x 2048 tokens:
-// whole call 106 us with one, 145 with three), an fp32 V, taken apart likewise, takes six.  Those six run on a chain of their own and are added to the output
-// once, so an output component sees one rounding per 32 keys.
+// whole call 106 us with one, 145 with three), an fp32 V, taken apart likewise, takes six.  Those six run on a chain of their
+// own and are added to the output once, so an output component sees one rounding per 32 keys.
 template <int DT, int D, int PARTS>
 __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void prefill_rows_out_planes(PrefillArgs a) {
   using P = Planes<DT, D, kRowsSmall<DT, D>>;
@@ -726,14 +726,16 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
     if (part == 1) return;
     const float m1 = other[0][grp * kWave + lane], l1 = other[1][grp * kWave + lane];
     const float M = fmaxf(m, m1);
-    const float w0 = m > -INFINITY ? fast_exp2(m - M) : 0.0f, w1 = m1 > -INFINITY ? fast_exp2(m1 - M) : 0.0f;
+    // (a part that attended nothing has no sums; a weight that underflows still meets an infinite sum)
+    const bool some0 = m > -INFINITY, some1 = m1 > -INFINITY;
+    const float w0 = some0 ? fast_exp2(m - M) : 0.0f, w1 = some1 ? fast_exp2(m1 - M) : 0.0f;
     l = l * w0 + l1 * w1;
     m = M;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        o[db][r] = (w0 > 0.0f ? o[db][r] * w0 : 0.0f) + (w1 > 0.0f ? mo[(db * 16 + r) * kWave] * w1 : 0.0f);
+        o[db][r] = (some0 ? o[db][r] * w0 : 0.0f) + (some1 ? mo[(db * 16 + r) * kWave] * w1 : 0.0f);
   }
   if (qi < len) {
     if (half == 0) a.lse[ubase + qi] = m + log2f(l);

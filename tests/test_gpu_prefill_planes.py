@@ -116,6 +116,28 @@ def test_infinities_and_nan_go_where_a_plain_product_sends_them(dtype, d, monkey
         np.testing.assert_allclose(b[fine], a[fine], rtol=tol, atol=tol * 0.1, err_msg=key)
 
 
+@pytest.mark.parametrize("dtype,d", FORMS)
+def test_an_infinite_value_of_a_far_lower_logit_stays_in_the_output(dtype, d, monkeypatch):
+    """Every other 32 keys lie 260 powers of two below the rest, so what one half of a workgroup's waves summed has a weight
+    that underflows: an infinity among its values is not finite in the rows that see it (0 x inf), as on the vector ALUs."""
+    rng = np.random.default_rng(4)
+    units, L = 3, 1100
+    Q = np.full((units, L, d), 4.0 * math.sqrt(128.0 / d), np.float32)
+    K, V = Q.copy(), rng.standard_normal((units, L, d)).astype(np.float32)
+    if dtype == "bf16":
+        Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
+    K[0, np.arange(L) // 32 % 2 == 1] *= -1.0
+    K[1, np.arange(L) // 32 % 2 == 0] *= -1.0
+    V[0, 40, 7] = np.inf
+    V[1, 70, 7] = np.inf
+    want, got = _both_paths(monkeypatch, dtype, d, Q, K, V, [L] * units, B=L)
+    for u, key in ((0, 40), (1, 70)):
+        for O in (want["O"], got["O"]):
+            assert not np.isfinite(O[u, key + 64:, 7]).any()
+            assert np.isfinite(O[u, :key, 7]).all() and np.isfinite(np.delete(O[u], 7, axis=1)).all()
+    assert np.isfinite(got["O"][2]).all()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_ends_of_the_fp32_range(d, monkeypatch):
     """Key elements up to the largest fp32 value (whose first plane may not round up to infinity) against the smallest
