@@ -17,11 +17,12 @@
 // it is bound by vector issue; fp32 has 24 (head_dim 64) or 48 matrix instructions and is bound by the matrix pipe.  Two
 // or more workgroups per compute unit overlap the one pipe's work with the other's; nothing is pipelined by hand.
 //
-// Infinities and NaN: a plane product may not meet an infinity with a zero plane (0 x inf), so the two smaller planes of
-// an infinite or NaN element are zero, and once a workgroup has met such an element its cross terms take hi planes in
-// which it counts as zero: it contributes through hi x hi alone, as in a plain fp32 product.  The attention output
-// does likewise with V, whose infinities must reach only the queries that see them.  (Elements below 2^-109 lose their
-// lower planes to bf16's subnormal range: they matter only against partners above 2^85.)
+// What three planes do not hold exactly -- infinities and NaN, values from 2^127 on, which may round to infinity, nonzero
+// values below 2^-110, whose last bits are below bf16's range -- stays off the matrix cores: a wave that owns such a row, and every
+// wave for a streamed tile that holds one, multiplies the fp32 numbers themselves on the vector ALUs.  So does the product with
+// such values of V, an infinite bf16 one included, which may reach only the queries that see its key.  (32 units x 2048 tokens
+// of nothing but such values: 2.3 ms without and 3.4 with output for fp32 / 64, 3.8 and 11.6 for fp32 / 128, where the passes
+// of prefill_simple.hip take 2.1 and 4.2.  Probabilities below 2^-110 of their row's reference keep an error of 2^-134 of it.)
 #include "kernels.hpp"
 #include "mfma.hpp"
 #include "prefill_tiles.hpp"
@@ -74,28 +75,8 @@ template <int D> __device__ __forceinline__ int chunk_offset(int row, int ch) {
   return row * 2 * D + ((D == 64 ? ch ^ ((row >> 1) & 7) : ch ^ (row & 15)) << 4);
 }
 
-__device__ __forceinline__ uint32_t bf16_bits(float f) {
-  return static_cast<uint32_t>(__builtin_bit_cast(uint16_t, static_cast<__bf16>(f)));
-}
-__device__ __forceinline__ float bf16_value(uint32_t h) { return __uint_as_float(h << 16); }
-
-// One fp32 value as bf16 planes, whatever it is; true if it is an infinity or NaN (then the smaller planes are zero).
-__device__ __forceinline__ bool split_any(uint32_t bits, uint32_t* h) {
-  const float x = __uint_as_float(bits);
-  const uint32_t mag = bits & 0x7fffffffu;
-  if (mag >= 0x7f800000u) {
-    h[0] = (bits >> 16) | (mag > 0x7f800000u ? 0x40u : 0u);  // a NaN stays one
-    h[1] = h[2] = 0u;
-    return true;
-  }
-  h[0] = mag >= 0x7f000000u ? bits >> 16 : bf16_bits(x);  // truncated near the top of the range: rounding may overflow
-  const float r1 = x - bf16_value(h[0]);
-  h[1] = bf16_bits(r1);
-  h[2] = bf16_bits(r1 - bf16_value(h[1]));
-  return false;
-}
-// Four fp32 values as three planes of four bf16 values; true if one of them is an infinity or NaN.
-__device__ __forceinline__ bool split4(const uint4& w, uint2* p) {
+// Four fp32 values as three planes of four bf16 values, exact for zeros and for values in [2^-110, 2^127).
+__device__ __forceinline__ void split4(const uint4& w, uint2* p) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   auto pack = [](f32x2 v) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2)); };
@@ -106,33 +87,31 @@ __device__ __forceinline__ bool split4(const uint4& w, uint2* p) {
   p[0] = make_uint2(pack(a), pack(b));
   a = less(a, p[0].x);
   b = less(b, p[0].y);
-  // An infinity, a NaN or a value so large that its first plane rounds to infinity leaves a remainder that is not finite.
-  const bool top = !(fabsf(((a.x + a.y) + b.x) + b.y) < INFINITY);
   p[1] = make_uint2(pack(a), pack(b));
   a = less(a, p[1].x);
   b = less(b, p[1].y);
   p[2] = make_uint2(pack(a), pack(b));
-  if (!top) return false;
-  const uint32_t u[4] = {w.x, w.y, w.z, w.w};
-  uint32_t h[4][3];
+}
+// Whether values lie outside that range.  An offset from its lower end that wraps around for anything smaller, one maximum
+// over all of a thread's values and one comparison; only if that fails (zeros wrap around too) are they looked at one by one.
+constexpr uint32_t kPlanesFrom = 17u << 24, kPlanesTo = 254u << 24;  // twice the bits of 2^-110 and 2^127: no sign
+__device__ __forceinline__ uint32_t planes_offset(uint32_t bits) { return (bits << 1) - kPlanesFrom; }
+__device__ __forceinline__ uint32_t farthest(uint32_t far, const uint4& w) {
+  far = max(max(far, planes_offset(w.x)), planes_offset(w.y));
+  return max(max(far, planes_offset(w.z)), planes_offset(w.w));
+}
+template <int N> __device__ __forceinline__ bool outside_planes(uint32_t far, const uint4 (&w)[N]) {
+  if (__builtin_expect(far < kPlanesTo - kPlanesFrom, 1)) return false;
   bool odd = false;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) odd |= split_any(u[e], h[e]);
+  for (int i = 0; i < N; ++i) {
+    const uint32_t u[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
 #pragma unroll
-  for (int k = 0; k < 3; ++k) p[k] = make_uint2(h[0][k] | (h[1][k] << 16), h[2][k] | (h[3][k] << 16));
+    for (int e = 0; e < 4; ++e) odd |= (u[e] << 1) != 0u && planes_offset(u[e]) >= kPlanesTo - kPlanesFrom;
+  }
   return odd;
 }
-// Infinities and NaN of two packed bf16 values replaced by zero.
-__device__ __forceinline__ uint32_t finite2(uint32_t v) {
-  uint32_t r = v;
-  if ((v & 0x7f80u) == 0x7f80u) r &= 0xffff0000u;
-  if ((v & 0x7f800000u) == 0x7f800000u) r &= 0xffffu;
-  return r;
-}
-__device__ __forceinline__ uint4 finite8(uint4 v) {
-  asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));  // stays in the rare branch that asked for it
-  return make_uint4(finite2(v.x), finite2(v.y), finite2(v.z), finite2(v.w));
-}
+// An infinity or NaN in one of two packed bf16 values.
 __device__ __forceinline__ bool has_odd2(uint32_t v) {
   return (v & 0x7f80u) == 0x7f80u || (v & 0x7f800000u) == 0x7f800000u;
 }
@@ -164,9 +143,9 @@ template <int DT, int D, int ROWS> struct Pieces {
       w[i] = load16(base + h * stride + static_cast<size_t>(pos) * P::IN_ROW + (idx % P::CPR) * 16);
     }
   }
-  // Into the planes of a K or Q tile; true if this thread met an infinity or NaN (fp32 only: bf16 products need no care).
+  // Into the planes of a K or Q tile; true if this thread met a value they do not hold (fp32 only).
   __device__ __forceinline__ bool store(char* tile) const {
-    bool odd = false;
+    uint32_t far = 0;
 #pragma unroll
     for (int i = 0; i < P::PIECES; ++i) {
       const int idx = threadIdx.x + kThreads * i;
@@ -175,16 +154,18 @@ template <int DT, int D, int ROWS> struct Pieces {
         *reinterpret_cast<uint4*>(tile + chunk_offset<D>(row, c)) = w[i];
       } else {
         uint2 p[3];
-        odd |= split4(w[i], p);
+        split4(w[i], p);
+        far = farthest(far, w[i]);
         char* at = tile + chunk_offset<D>(row, c >> 1) + (c & 1) * 8;
 #pragma unroll
         for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(at + k * P::PLANE) = p[k];
       }
     }
-    return odd;
+    return DT == kF32 && outside_planes(far, w);
   }
-  // Into the planes of a V tile (rows of ROWV bytes).
+  // Into the planes of a V tile (rows of ROWV bytes); true if this thread met a value they do not hold, or an infinity or NaN.
   __device__ __forceinline__ bool store_values(char* tile) const {
+    uint32_t far = 0;
     bool odd = false;
 #pragma unroll
     for (int i = 0; i < P::PIECES; ++i) {
@@ -195,12 +176,13 @@ template <int DT, int D, int ROWS> struct Pieces {
         *reinterpret_cast<uint4*>(tile + row * P::ROWV + c * 16) = w[i];
       } else {
         uint2 p[3];
-        odd |= split4(w[i], p);
+        split4(w[i], p);
+        far = farthest(far, w[i]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(tile + k * P::PLANEV + row * P::ROWV + c * 8) = p[k];
       }
     }
-    return odd;
+    return odd || (DT == kF32 && outside_planes(far, w));
   }
 };
 
@@ -208,30 +190,35 @@ template <int DT, int D, int ROWS> struct Pieces {
 template <int DT, int D> struct Owned {
   using P = Planes<DT, D, 64>;
   uint4 f[P::NP][P::KS];
-  // true if the lane met an infinity or NaN
+  // true if the lane met a value that the planes do not hold
   __device__ __forceinline__ bool load(const char* base, int row, int last_row) {
     const int half = (threadIdx.x & (kWave - 1)) >> 5;
     const char* at = base + static_cast<size_t>(min(row, last_row)) * P::IN_ROW;
-    bool odd = false;
+    if constexpr (DT == kBF16) {
 #pragma unroll
-    for (int kk = 0; kk < P::KS; ++kk) {
-      if constexpr (DT == kBF16) {
-        f[0][kk] = load16(at + kk * 32 + half * 16);
-      } else {
+      for (int kk = 0; kk < P::KS; ++kk) f[0][kk] = load16(at + kk * 32 + half * 16);
+      return false;
+    } else {
+      uint32_t far = 0;
+      uint4 w[2 * P::KS];
+#pragma unroll
+      for (int kk = 0; kk < P::KS; ++kk) {
         uint2 a[3], b[3];
-        odd |= split4(load16(at + kk * 64 + half * 32), a);
-        odd |= split4(load16(at + kk * 64 + half * 32 + 16), b);
+        w[2 * kk] = load16(at + kk * 64 + half * 32);
+        w[2 * kk + 1] = load16(at + kk * 64 + half * 32 + 16);
+        far = farthest(farthest(far, w[2 * kk]), w[2 * kk + 1]);
+        split4(w[2 * kk], a);
+        split4(w[2 * kk + 1], b);
 #pragma unroll
         for (int k = 0; k < 3; ++k) f[k][kk] = make_uint4(a[k].x, a[k].y, b[k].x, b[k].y);
       }
+      return outside_planes(far, w);
     }
-    return odd;
   }
 };
 
-// Score tile: the 32 streamed rows of sub-tile `sub` against 32 owned rows.  ODD: an infinity or NaN is about (see the
-// head of the file).
-template <int DT, int D, int ROWS, bool ODD>
+// Score tile: the 32 streamed rows of sub-tile `sub` against 32 owned rows.
+template <int ROWS, int DT, int D>
 __device__ __forceinline__ f32x16 score_tile(const char* tile, int sub, const Owned<DT, D>& own) {
   using P = Planes<DT, D, ROWS>;
   const int lane = threadIdx.x & (kWave - 1);
@@ -251,22 +238,45 @@ __device__ __forceinline__ f32x16 score_tile(const char* tile, int sub, const Ow
 #pragma unroll
     for (int kk = 0; kk < P::KS; ++kk) {
       const uint4 h = frag(0, kk), m = frag(1, kk), l = frag(2, kk);
-      const uint4 hs = ODD ? finite8(h) : h, oh = ODD ? finite8(own.f[0][kk]) : own.f[0][kk];
-      small = mm(l, oh, small);
-      small = mm(hs, own.f[2][kk], small);
+      small = mm(l, own.f[0][kk], small);
+      small = mm(h, own.f[2][kk], small);
       acc = mm(h, own.f[0][kk], kk == 0 ? zero : acc);
       small = mm(m, own.f[1][kk], small);
-      small = mm(hs, own.f[1][kk], small);
-      small = mm(m, oh, small);
+      small = mm(h, own.f[1][kk], small);
+      small = mm(m, own.f[0][kk], small);
     }
     acc += small;
   }
   return acc;
 }
-template <int ROWS, int DT, int D>
-__device__ __forceinline__ f32x16 score_tile(bool odd, const char* tile, int sub, const Owned<DT, D>& own) {
-  if (DT == kF32 && odd) return score_tile<DT, D, ROWS, true>(tile, sub, own);
-  return score_tile<DT, D, ROWS, false>(tile, sub, own);
+// The same tile from the fp32 rows themselves: `row_at(i)` is the address of streamed row i of the sub-tile, `own_row` of the
+// lane's owned row.  Four streamed rows at a time, which keeps the registers of this rare path out of the kernel's way.
+template <int D, class RowAt>
+__device__ __forceinline__ f32x16 score_tile_plain(RowAt row_at, const char* own_row) {
+  const int half = (threadIdx.x & (kWave - 1)) >> 5;
+  f32x16 acc = {0};
+#pragma unroll 1
+  for (int g4 = 0; g4 < 4; ++g4) {
+    const char* at[4];
+    float dot[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) at[e] = row_at(8 * g4 + 4 * half + e);
+#pragma unroll 1
+    for (int c = 0; c < D * 4; c += 16) {
+      float x[4];
+      unpack16<kF32>(load16(own_row + c), x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float y[4];
+        unpack16<kF32>(load16(at[e] + c), y);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dot[e] = fmaf(x[k], y[k], dot[e]);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = (r >> 2) == g4 ? dot[r & 3] : acc[r];
+  }
+  return acc;
 }
 
 // Blocks of owned rows of a workgroup: paired, it takes the p-th longest and the p-th shortest (equal work whatever the
@@ -299,7 +309,7 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? 4 : D == 64 ? 3 : 2) void p
   constexpr int kOwn = Shares<PARTS>::kOwn, GROUPS = Shares<PARTS>::GROUPS;
   __shared__ __attribute__((aligned(16))) char tiles[2][P::TILE];
   __shared__ float other[2][PARTS == 2 ? kOwn : 1];
-  __shared__ int odd_s;
+  __shared__ int odd_s[2];  // number of the last tile in this buffer that holds values of no exact planes (fp32)
   int u, id;
   if (!locate_heads(a.units, a.group, a.pairs * a.ksplit, u, id)) return;
   const int seg = id % a.ksplit, pair_id = id / a.ksplit;
@@ -315,7 +325,8 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? 4 : D == 64 ? 3 : 2) void p
   const int w = a.recency_window;
   const float rb = a.recency_bias_log2;
   const int n_blocks = (len + kOwn - 1) / kOwn;
-  if (threadIdx.x == 0) odd_s = 0;
+  if (threadIdx.x == 0) odd_s[0] = odd_s[1] = 0;
+  int seq = 0;  // tiles so far
 
   for (int pass = 0; pass < 2; ++pass) {
     int blk;
@@ -331,23 +342,27 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? 4 : D == 64 ? 3 : 2) void p
     }
     Pieces<DT, D, P::TR> st;
     if (t_lo <= t_hi) st.load(Kb, t_lo * P::TR, len - 1);
-    __syncthreads();  // the previous block has finished with the tiles; odd_s is cleared
+    __syncthreads();  // the previous block has finished with the tiles and what goes with them; odd_s is cleared
     Owned<DT, D> own;
-    bool odd = own.load(Qb, qi, len - 1);
+    const bool odd_own = __builtin_amdgcn_ballot_w64(own.load(Qb, qi, len - 1)) != 0;
     float m = -INFINITY, l = 0.0f;
     for (int t = t_lo; t <= t_hi; ++t) {
-      char* const tile = tiles[(t - t_lo) & 1];
-      odd |= st.store(tile);
-      if (DT == kF32 && odd) odd_s = 1;
+      const int buf = (t - t_lo) & 1;
+      char* const tile = tiles[buf];
+      ++seq;
+      if (st.store(tile) && DT == kF32) odd_s[buf] = seq;
       __syncthreads();  // tile t is in LDS; everybody is done with tile t - 1, whose buffer tile t + 1 takes
       if (t + 1 <= t_hi) st.load(Kb, (t + 1) * P::TR, len - 1);
-      const bool odd_tile = DT == kF32 && __builtin_amdgcn_readfirstlane(odd_s) != 0;
+      const bool odd = DT == kF32 && (odd_own || __builtin_amdgcn_readfirstlane(odd_s[buf]) == seq);
 #pragma unroll
       for (int i = 0; i < P::SUBS / PARTS; ++i) {
         const int sub = part + PARTS * i;
         const int kb = t * P::TR + sub * 32;
         if (kb > qg + 31) continue;  // wholly above the diagonal
-        const f32x16 s = score_tile<P::TR>(odd_tile, tile, sub, own);
+        f32x16 s;
+        if (odd) s = score_tile_plain<D>([&](int i) { return Kb + static_cast<size_t>(min(kb + i, len - 1)) * P::IN_ROW; },
+                                         Qb + static_cast<size_t>(min(qi, len - 1)) * P::IN_ROW);
+        else s = score_tile<P::TR>(tile, sub, own);
         if (kb + 31 + w <= qg) lse_update<true>(s, sc, kb, half, qi, w, rb, m, l);
         else lse_update<false>(s, sc, kb, half, qi, w, rb, m, l);
       }
@@ -382,7 +397,7 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
   __shared__ __attribute__((aligned(16))) char tiles[2][P::TILE];
   __shared__ __attribute__((aligned(16))) float lse_s[2][P::TR], rinv_s[2][P::TR];  // rinv: 1 / (tokens the query attended)
   __shared__ float other[2][PARTS == 2 ? kOwn : 1];
-  __shared__ int odd_s;
+  __shared__ int odd_s[2];  // see prefill_rows_planes
   int u, id;
   if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;
@@ -402,7 +417,8 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
   const int w = a.recency_window;
   const float rb = a.recency_bias_log2;
   const int n_blocks = (len + kOwn - 1) / kOwn;
-  if (threadIdx.x == 0) odd_s = 0;
+  if (threadIdx.x == 0) odd_s[0] = odd_s[1] = 0;
+  int seq = 0;
 
   for (int pass = 0; pass < 2; ++pass) {
     int blk;
@@ -429,9 +445,9 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
       if (threadIdx.x < P::TR) st_lse = lse_u[static_cast<size_t>(lse_h) * a.L_max + min(t * QT + lse_q, len - 1)];
     };
     if (t_first <= t_last) fetch(t_last, 0);
-    __syncthreads();  // the previous block has finished with the tiles; odd_s is cleared
+    __syncthreads();  // the previous block has finished with the tiles and what goes with them; odd_s is cleared
     Owned<DT, D> own;
-    bool odd = own.load(Kb, kj, len - 1);
+    const bool odd_own = __builtin_amdgcn_ballot_w64(own.load(Kb, kj, len - 1)) != 0;
     float s1 = 0.0f, s2 = 0.0f;
     f32x16 pb[HEADS == 0 ? NSUB : 1];  // sums over the heads of a tile's probabilities
 
@@ -439,8 +455,8 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
     for (int t = t_last; t >= t_first; --t) {
       for (int h = 0; h < (HEADS == 0 ? G : 1); ++h) {
         char* const tile = tiles[b];
-        odd |= st.store(tile);
-        if (DT == kF32 && odd) odd_s = 1;
+        ++seq;
+        if (st.store(tile) && DT == kF32) odd_s[b] = seq;
         if (threadIdx.x < P::TR) {
           lse_s[b][threadIdx.x] = st_lse;
           if (count && HEADS == 1) rinv_s[b][threadIdx.x] = 1.0f / static_cast<float>(t * P::TR + static_cast<int>(threadIdx.x) + 1);
@@ -448,13 +464,27 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
         __syncthreads();
         if (HEADS == 0 && h + 1 < G) fetch(t, h + 1);
         else if (t > t_first) fetch(t - 1, 0);
-        const bool odd_tile = DT == kF32 && __builtin_amdgcn_readfirstlane(odd_s) != 0;
+        const bool odd = DT == kF32 && (odd_own || __builtin_amdgcn_readfirstlane(odd_s[b]) == seq);
 #pragma unroll
         for (int i = 0; i < NSUB; ++i) {
           const int sub = part + PARTS * i;
           const int ib = t * QT + sub * QS;  // first query position of the sub-tile; its last one is ib + QS - 1
           if (ib + QS - 1 < kg || ib >= len) continue;  // no query of the sub-tile reaches the wave's keys
-          const f32x16 c = score_tile<P::TR>(odd_tile, tile, sub, own);
+          f32x16 c;
+          if (odd) {
+            c = score_tile_plain<D>(
+                [&](int i) {
+                  int pos = ib + i, head = h;
+                  if constexpr (HEADS > 1) {
+                    GroupedRows<PER>::locate(i, pos, head);
+                    pos += ib;
+                  }
+                  return Qu + (static_cast<size_t>(head) * a.L_max + min(pos, len - 1)) * P::IN_ROW;
+                },
+                Kb + static_cast<size_t>(min(kj, len - 1)) * P::IN_ROW);
+          } else {
+            c = score_tile<P::TR>(tile, sub, own);
+          }
           const bool interior = ib + QS - 1 < len && ib >= kg + 31 + w;
           const float* lt = &lse_s[b][sub * 32];
           if constexpr (HEADS > 1) {
@@ -505,11 +535,22 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
   }
 }
 
+// Four consecutive elements of a row of V.
+template <int DT> __device__ __forceinline__ void load_values(const char* row, int at, float* v) {
+  if constexpr (DT == kF32) {
+    unpack16<kF32>(load16(row + at * 4), v);
+  } else {
+    const uint2 w = *reinterpret_cast<const uint2*>(row + at * 2);
+    v[0] = __uint_as_float(w.x << 16); v[1] = __uint_as_float(w.x & 0xffff0000u);
+    v[2] = __uint_as_float(w.y << 16); v[3] = __uint_as_float(w.y & 0xffff0000u);
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // pass 1 with the attention output O_i = sum_j P[i,j] v_j (see prefill_rows_out_mfma for the operand layouts).  The
 // probabilities are fp32 numbers and are taken apart into three planes: a bf16 V, which is one plane, takes three products
 // of 32 keys (one, of bf16 probabilities, misrounds 40 % of the outputs where three misround 0.03 %; 32 units x 2048 tokens:
-// whole call 106 us with one, 145 with three), an fp32 V, taken apart likewise, takes six.  Those six run on a chain of their
+// whole call 106 us with one, 131 with three), an fp32 V, taken apart likewise, takes six.  Those six run on a chain of their
 // own and are added to the output once, so an output component sees one rounding per 32 keys.
 template <int DT, int D, int PARTS>
 __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void prefill_rows_out_planes(PrefillArgs a) {
@@ -520,7 +561,7 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
   __shared__ __attribute__((aligned(16))) char tilesK[NBUF][P::TILE];
   __shared__ __attribute__((aligned(16))) char tilesV[NBUF][P::TILEV];
   __shared__ float other[2][PARTS == 2 ? GROUPS * kWave : 1];
-  __shared__ int odd_s, odd_v;
+  __shared__ int odd_s[NBUF], odd_v[NBUF];  // see prefill_rows_planes
   int u, blk_id;
   if (!locate_heads(a.units, a.group, a.pairs, u, blk_id)) return;
   const int uk = u / a.group;
@@ -532,6 +573,7 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
   const int half = lane >> 5, grp = wave % GROUPS, part = wave / GROUPS;
   const size_t ubase = static_cast<size_t>(u) * a.L_max;
   const size_t kbase = static_cast<size_t>(uk) * a.L_max;
+  const char* Qb = static_cast<const char*>(a.Q) + ubase * P::IN_ROW;
   const char* Kb = static_cast<const char*>(a.K) + kbase * P::IN_ROW;
   const char* Vb = static_cast<const char*>(a.V) + kbase * P::IN_ROW;
   const float sc = a.scale_log2;
@@ -540,13 +582,13 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
   const int q0 = blk * kOwn;
   const int qw0 = q0 + 32 * grp;
   const int qi = qw0 + (lane & 31);
-  if (threadIdx.x == 0) odd_s = odd_v = 0;
+  if (threadIdx.x < NBUF) odd_s[threadIdx.x] = odd_v[threadIdx.x] = -1;
   Pieces<DT, D, P::TR> stK, stV;
   stK.load(Kb, 0, len - 1);
   stV.load(Vb, 0, len - 1);
   __syncthreads();
   Owned<DT, D> own;
-  bool odd = own.load(static_cast<const char*>(a.Q) + ubase * P::IN_ROW, qi, len - 1);
+  const bool odd_own = __builtin_amdgcn_ballot_w64(own.load(Qb, qi, len - 1)) != 0;
   float m = -INFINITY, l = 0.0f;
   f32x16 o[DB];
 #pragma unroll
@@ -557,25 +599,28 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
 
   const int n_tiles = (min(len, q0 + kOwn) - 1) / P::TR + 1;
   for (int t = 0; t < n_tiles; ++t) {
-    char* const tileK = tilesK[NBUF == 2 ? t & 1 : 0];
-    char* const tileV = tilesV[NBUF == 2 ? t & 1 : 0];
+    const int buf = NBUF == 2 ? t & 1 : 0;
+    char* const tileK = tilesK[buf];
+    char* const tileV = tilesV[buf];
     if (NBUF == 1 && t > 0) __syncthreads();  // everybody is done with the previous tile
-    odd |= stK.store(tileK);
-    if (DT == kF32 && odd) odd_s = 1;
-    if (stV.store_values(tileV)) odd_v = 1;
+    if (stK.store(tileK) && DT == kF32) odd_s[buf] = t;
+    if (stV.store_values(tileV)) odd_v[buf] = t;
     __syncthreads();
     if (t + 1 < n_tiles) {
       stK.load(Kb, (t + 1) * P::TR, len - 1);
       stV.load(Vb, (t + 1) * P::TR, len - 1);
     }
-    const bool odd_tile = DT == kF32 && __builtin_amdgcn_readfirstlane(odd_s) != 0;
-    const bool odd_values = __builtin_amdgcn_readfirstlane(odd_v) != 0;
+    const bool odd = DT == kF32 && (odd_own || __builtin_amdgcn_readfirstlane(odd_s[buf]) == t);
+    const bool odd_values = __builtin_amdgcn_readfirstlane(odd_v[buf]) == t;
 #pragma unroll
     for (int i = 0; i < P::SUBS / PARTS; ++i) {
       const int sub = part + PARTS * i;
       const int kb = t * P::TR + sub * 32;
       if (kb > qw0 + 31) continue;  // wholly above the diagonal for every query of this wave
-      const f32x16 s = score_tile<P::TR>(odd_tile, tileK, sub, own);
+      f32x16 s;
+      if (odd) s = score_tile_plain<D>([&](int i) { return Kb + static_cast<size_t>(min(kb + i, len - 1)) * P::IN_ROW; },
+                                       Qb + static_cast<size_t>(min(qi, len - 1)) * P::IN_ROW);
+      else s = score_tile<P::TR>(tileK, sub, own);
       // ---- probabilities against the reference m (lazily raised: see prefill_rows_out_mfma) and their sum
       const bool interior = kb + 31 + w <= qw0;
       float pv[16];
@@ -623,6 +668,28 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
         }
       }
       l += sum;
+      // ---- O^T += V^T . P^T
+      if (odd_values) {  // V as it is, one key at a time, for the queries that see the key
+#pragma unroll 1
+        for (int key = 0; key < 32; ++key) {
+          float mine = 0.0f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mine = (8 * (r >> 2) + (r & 3)) == (key & ~4) ? pv[r] : mine;
+          const float pk = __shfl(mine, (lane & 31) + 32 * ((key >> 2) & 1), kWave);
+          if (kb + key > qi || kb + key >= len) continue;
+          const char* vr = Vb + static_cast<size_t>(kb + key) * P::IN_ROW;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+              float v[4];
+              load_values<DT>(vr, db * 32 + 8 * g4 + 4 * half, v);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[db][4 * g4 + e] = fmaf(pk, v[e], o[db][4 * g4 + e]);
+            }
+        }
+        continue;
+      }
       bf16x8 pf[3][2];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -631,80 +698,52 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
         pf[1][r >> 3][r & 7] = static_cast<__bf16>(r1);
         pf[2][r >> 3][r & 7] = static_cast<__bf16>(r1 - static_cast<float>(pf[1][r >> 3][r & 7]));
       }
-      // ---- O^T += V^T . P^T, two 16-key steps x DB blocks of 32 head dimensions
+      // two 16-key steps x DB blocks of 32 head dimensions
       auto values = [&](int plane, int ks, int db) {
         const char* vt = tileV + plane * P::PLANEV + (sub * 32 + ks * 16) * P::ROWV + tr_off + db * 64;
         const uint2 lo = lds_read_transposed(vt), hi = lds_read_transposed(vt + 8 * P::ROWV);
         return make_uint4(lo.x, lo.y, hi.x, hi.y);
       };
-      auto multiply = [&](auto odd_tag) {
-        constexpr bool ODD = decltype(odd_tag)::value;
-        auto p = [&](int plane, int ks) { return __builtin_bit_cast(uint4, pf[plane][ks]); };
-        if constexpr (DT == kBF16) {
+      auto p = [&](int plane, int ks) { return __builtin_bit_cast(uint4, pf[plane][ks]); };
+      if constexpr (DT == kBF16) {
 #pragma unroll
-          for (int ks = 0; ks < 2; ++ks) {
-            uint4 v[DB];
+        for (int ks = 0; ks < 2; ++ks) {
+          uint4 v[DB];
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
-              v[db] = values(0, ks, db);
-              if (ODD) v[db] = finite8(v[db]);
-            }
+          for (int db = 0; db < DB; ++db) v[db] = values(0, ks, db);
 #pragma unroll
-            for (int plane = 2; plane >= 0; --plane)  // the small terms first
+          for (int plane = 2; plane >= 0; --plane)  // the small terms first
 #pragma unroll
-              for (int db = 0; db < DB; ++db) o[db] = mm(v[db], p(plane, ks), o[db]);
-          }
-        } else {
-#pragma unroll
-          for (int d2 = 0; d2 < DB; d2 += 2) {  // two chains at a time
-            f32x16 c[2];
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {  // the small terms first, the hi x hi products last
-              uint4 h[2], mid[2], lo[2];
-#pragma unroll
-              for (int e = 0; e < 2; ++e) {
-                h[e] = values(0, ks, d2 + e);
-                if (ODD) h[e] = finite8(h[e]);
-                mid[e] = values(1, ks, d2 + e);
-                lo[e] = values(2, ks, d2 + e);
-              }
-#pragma unroll
-              for (int e = 0; e < 2; ++e) c[e] = mm(lo[e], p(0, ks), ks == 0 ? f32x16{0} : c[e]);
-#pragma unroll
-              for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(2, ks), c[e]);
-#pragma unroll
-              for (int e = 0; e < 2; ++e) c[e] = mm(mid[e], p(1, ks), c[e]);
-#pragma unroll
-              for (int e = 0; e < 2; ++e) c[e] = mm(mid[e], p(0, ks), c[e]);
-#pragma unroll
-              for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(1, ks), c[e]);
-#pragma unroll
-              for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(0, ks), c[e]);
-            }
-            o[d2] += c[0];
-            o[d2 + 1] += c[1];
-          }
+            for (int db = 0; db < DB; ++db) o[db] = mm(v[db], p(plane, ks), o[db]);
         }
-      };
-      if (!odd_values) {
-        multiply(std::integral_constant<bool, false>{});
       } else {
-        multiply(std::integral_constant<bool, true>{});
-        // infinities and NaN of V, one key at a time, for the queries that see the key
-        for (int key = 0; key < 32; ++key) {
-          float mine = 0.0f;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) mine = (8 * (r >> 2) + (r & 3)) == (key & ~4) ? pv[r] : mine;
-          const float pk = __shfl(mine, (lane & 31) + 32 * ((key >> 2) & 1), kWave);
-          if (kb + key > qi) continue;
-          const char* vr = tileV + (sub * 32 + key) * P::ROWV;
+        for (int d2 = 0; d2 < DB; d2 += 2) {  // two chains at a time
+          f32x16 c[2];
 #pragma unroll
-          for (int db = 0; db < DB; ++db)
+          for (int ks = 0; ks < 2; ++ks) {  // the small terms first, the hi x hi products last
+            uint4 h[2], mid[2], lo[2];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const uint32_t hv = *reinterpret_cast<const uint16_t*>(vr + (db * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * 2);
-              if ((hv & 0x7f80u) == 0x7f80u) o[db][r] += pk * bf16_value(hv);
+            for (int e = 0; e < 2; ++e) {
+              h[e] = values(0, ks, d2 + e);
+              mid[e] = values(1, ks, d2 + e);
+              lo[e] = values(2, ks, d2 + e);
             }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) c[e] = mm(lo[e], p(0, ks), ks == 0 ? f32x16{0} : c[e]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(2, ks), c[e]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) c[e] = mm(mid[e], p(1, ks), c[e]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) c[e] = mm(mid[e], p(0, ks), c[e]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(1, ks), c[e]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) c[e] = mm(h[e], p(0, ks), c[e]);
+          }
+          o[d2] += c[0];
+          o[d2 + 1] += c[1];
         }
       }
     }

@@ -187,3 +187,80 @@ def test_bf16_output_is_rounded_once(L, lens):
         want = orc.prefill_statistics(Q[u], K[u], V[u], n, 1.0 / math.sqrt(d), want_out=True).out
         exact = torch.from_numpy(want).bfloat16().float().numpy()
         assert np.mean(O[u, :n] != exact) < 0.02
+
+
+def _wild(kind, units, group, L, d, dtype, seed):
+    """Inputs of the kinds that bf16 planes do not hold, in the first units; the others are ordinary."""
+    rng = np.random.default_rng(seed)
+    Q = rng.standard_normal((units, group, L, d)).astype(np.float32)
+    K, V = (rng.standard_normal((units, L, d)).astype(np.float32) for _ in range(2))
+    if kind == "not finite":
+        Q[..., 3] = 1.0
+        K[0, 40, 3] = -np.inf                 # a key no query attends
+        K[1, L - 60, 3] = np.inf              # rows from there on are NaN
+        Q[2, group - 1, L // 2] = np.nan      # one row, and the statistics of the keys up to it
+        K[3, 10, 5] = np.nan
+    elif kind == "small keys":
+        K[:4] *= np.float32(1e-34)
+        Q[:4] *= np.float32(1e34)
+    elif kind == "small queries":
+        Q[:4] *= np.float32(1e-36)
+        K[:4] *= np.float32(1e36)
+    elif kind == "one small element":
+        Q[0, 0, 37, 11] = np.float32(1.2345e-36)
+        K[0, :, 11] *= np.float32(1e36)
+        Q[0, :, :37, 11] = Q[0, :, 38:, 11] = 0.0
+        if group > 1:
+            Q[0, 1:, 37, 11] = 0.0
+    else:
+        assert kind == "largest"
+        K[0, 5, 3] = np.finfo(np.float32).max
+        Q[0, :, :, 3] = np.float32(2.0 ** -127)
+    if dtype == "bf16":
+        Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
+    return Q, K, V
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+@pytest.mark.parametrize("units,L,group", [(6, 1100, 1), (140, 300, 1), (600, 300, 1), (6, 200, 3), (6, 333, 4)])
+@pytest.mark.parametrize("kind", ["not finite", "small keys", "small queries", "one small element", "largest"])
+def test_wild_inputs_without_output(dtype, d, units, L, group, kind, monkeypatch):
+    """Statistics of every schedule and grouping against the vector-ALU passes: what is not finite is the same, the rest within
+    1e-5 (fp32 sums of up to 1100 probabilities; 2e-5 of the logits' rounding at their size of up to ten)."""
+    P = TP._parity()
+    Q, K, V = _wild(kind, units, group, L, d, dtype, 11)
+    lens = [L - u % 3 for u in range(units)]
+    res = []
+    for simple in ("1", "0"):
+        monkeypatch.setenv("ROCO_PREFILL_SIMPLE", simple)
+        sess = P.make_session(units, d, L, 16, dtype)
+        if group == 1:
+            res.append(P.gpu_prefill(sess, Q[:, 0], K, V, lens, False)["stats"])
+        else:
+            res.append(P.gpu_prefill_gqa(sess, group, Q, K, V, lens, False)["stats"])
+    a, b = (np.asarray(r, np.float64) for r in res)
+    assert np.array_equal(np.isnan(a), np.isnan(b))
+    assert np.array_equal(np.isinf(a), np.isinf(b))
+    fine = np.isfinite(a)
+    np.testing.assert_allclose(b[fine], a[fine], rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_outputs_of_small_values_keep_fp32_precision(d):
+    """V down to fp32's subnormal range, queries and keys scaled against each other: an output is within 1e-5 of its row's
+    largest, and a few times 2^-149 where that is the unit of fp32 itself."""
+    P = TP._parity()
+    rng = np.random.default_rng(16)
+    units, L = 5, 700
+    Q, K, V = (rng.standard_normal((units, L, d)).astype(np.float32) for _ in range(3))
+    V[0] *= np.float32(1e-34)
+    V[1] *= np.float32(2.0 ** -136)
+    V[2, 1::2] *= np.float32(1e-35)
+    K[3], Q[3] = K[3] * np.float32(1e-35), Q[3] * np.float32(1e35)
+    sess = P.make_session(units, d, L, 5, "f32")
+    O = P.gpu_prefill(sess, Q, K, V, [L] * units, True)["O"].astype(np.float64)
+    for u in range(units):
+        want = orc.prefill_statistics(Q[u], K[u], V[u], L, 1.0 / math.sqrt(d), want_out=True).out
+        scale = np.max(np.abs(want), axis=1, keepdims=True)
+        # subnormal sums lose up to half a unit per addition, of random sign: 700 of them, sqrt(700) / 2
+        assert np.all(np.abs(O[u] - want) <= 1e-5 * scale + 16 * 2.0 ** -149), u
