@@ -18,11 +18,13 @@
 // or more workgroups per compute unit overlap the one pipe's work with the other's; nothing is pipelined by hand.
 //
 // What three planes do not hold exactly -- infinities and NaN, values from 2^127 on, which may round to infinity, nonzero
-// values below 2^-110, whose last bits are below bf16's range -- stays off the matrix cores: a wave that owns such a row, and every
-// wave for a streamed tile that holds one, multiplies the fp32 numbers themselves on the vector ALUs.  So does the product with
-// such values of V, an infinite bf16 one included, which may reach only the queries that see its key.  (32 units x 2048 tokens
-// of nothing but such values: 2.3 ms without and 3.4 with output for fp32 / 64, 3.8 and 11.6 for fp32 / 128, where the passes
-// of prefill_simple.hip take 2.1 and 4.2.  Probabilities below 2^-110 of their row's reference keep an error of 2^-134 of it.)
+// values below 2^-110, whose last bits are below bf16's range -- stays off the matrix cores: a wave that owns such a row, and
+// every wave for a streamed tile that holds one, multiplies the fp32 numbers themselves on the vector ALUs.  So does the
+// product with such values of V, and with infinite bf16 ones, which may reach only the queries that see their key.  (32 units
+// x 2048 tokens of nothing but such values: 2.3 ms without and 3.4 with output for fp32 / 64, 3.8 and 11.6 for fp32 / 128,
+// where the passes of prefill_simple.hip take 2.1 and 4.2.  Probabilities below 2^-110 of their row's reference keep an error
+// of 2^-134 of it.)  A tile with values of V from 2^65 on goes the same way, with its row's true maximum as the reference:
+// against a lazily raised one the unnormalised output may be 2^16 times larger, and overflow where the output does not.
 #include "kernels.hpp"
 #include "mfma.hpp"
 #include "prefill_tiles.hpp"
@@ -95,27 +97,23 @@ __device__ __forceinline__ void split4(const uint4& w, uint2* p) {
 // Whether values lie outside that range.  An offset from its lower end that wraps around for anything smaller, one maximum
 // over all of a thread's values and one comparison; only if that fails (zeros wrap around too) are they looked at one by one.
 constexpr uint32_t kPlanesFrom = 17u << 24, kPlanesTo = 254u << 24;  // twice the bits of 2^-110 and 2^127: no sign
+constexpr uint32_t kValuesTo = 192u << 24;                          // ... and of 2^65 (see the head of the file)
 __device__ __forceinline__ uint32_t planes_offset(uint32_t bits) { return (bits << 1) - kPlanesFrom; }
 __device__ __forceinline__ uint32_t farthest(uint32_t far, const uint4& w) {
   far = max(max(far, planes_offset(w.x)), planes_offset(w.y));
   return max(max(far, planes_offset(w.z)), planes_offset(w.w));
 }
-template <int N> __device__ __forceinline__ bool outside_planes(uint32_t far, const uint4 (&w)[N]) {
-  if (__builtin_expect(far < kPlanesTo - kPlanesFrom, 1)) return false;
+template <uint32_t TO, int N> __device__ __forceinline__ bool outside_planes(uint32_t far, const uint4 (&w)[N]) {
+  if (__builtin_expect(far < TO - kPlanesFrom, 1)) return false;
   bool odd = false;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const uint32_t u[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) odd |= (u[e] << 1) != 0u && planes_offset(u[e]) >= kPlanesTo - kPlanesFrom;
+    for (int e = 0; e < 4; ++e) odd |= (u[e] << 1) != 0u && planes_offset(u[e]) >= TO - kPlanesFrom;
   }
   return odd;
 }
-// An infinity or NaN in one of two packed bf16 values.
-__device__ __forceinline__ bool has_odd2(uint32_t v) {
-  return (v & 0x7f80u) == 0x7f80u || (v & 0x7f800000u) == 0x7f800000u;
-}
-
 __device__ __forceinline__ f32x16 mm(const uint4& x, const uint4& y, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
 }
@@ -161,18 +159,18 @@ template <int DT, int D, int ROWS> struct Pieces {
         for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(at + k * P::PLANE) = p[k];
       }
     }
-    return DT == kF32 && outside_planes(far, w);
+    return DT == kF32 && outside_planes<kPlanesTo>(far, w);
   }
-  // Into the planes of a V tile (rows of ROWV bytes); true if this thread met a value they do not hold, or an infinity or NaN.
+  // Into the planes of a V tile (rows of ROWV bytes); true if this thread met a value they do not hold or one from 2^65 on.
   __device__ __forceinline__ bool store_values(char* tile) const {
-    uint32_t far = 0;
-    bool odd = false;
+    uint32_t far = 0, large = 0;
 #pragma unroll
     for (int i = 0; i < P::PIECES; ++i) {
       const int idx = threadIdx.x + kThreads * i;
       const int row = idx / P::CPR, c = idx % P::CPR;
       if constexpr (DT == kBF16) {
-        odd |= has_odd2(w[i].x) || has_odd2(w[i].y) || has_odd2(w[i].z) || has_odd2(w[i].w);
+        // the two upper bits of the exponent fields: set from 2^65 on
+        large |= (w[i].x & (w[i].x << 1)) | (w[i].y & (w[i].y << 1)) | (w[i].z & (w[i].z << 1)) | (w[i].w & (w[i].w << 1));
         *reinterpret_cast<uint4*>(tile + row * P::ROWV + c * 16) = w[i];
       } else {
         uint2 p[3];
@@ -182,7 +180,8 @@ template <int DT, int D, int ROWS> struct Pieces {
         for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(tile + k * P::PLANEV + row * P::ROWV + c * 8) = p[k];
       }
     }
-    return odd || (DT == kF32 && outside_planes(far, w));
+    if constexpr (DT == kBF16) return (large & 0x40004000u) != 0u;
+    return outside_planes<kValuesTo>(far, w);
   }
 };
 
@@ -212,7 +211,7 @@ template <int DT, int D> struct Owned {
 #pragma unroll
         for (int k = 0; k < 3; ++k) f[k][kk] = make_uint4(a[k].x, a[k].y, b[k].x, b[k].y);
       }
-      return outside_planes(far, w);
+      return outside_planes<kPlanesTo>(far, w);
     }
   }
 };
@@ -550,7 +549,7 @@ template <int DT> __device__ __forceinline__ void load_values(const char* row, i
 // pass 1 with the attention output O_i = sum_j P[i,j] v_j (see prefill_rows_out_mfma for the operand layouts).  The
 // probabilities are fp32 numbers and are taken apart into three planes: a bf16 V, which is one plane, takes three products
 // of 32 keys (one, of bf16 probabilities, misrounds 40 % of the outputs where three misround 0.03 %; 32 units x 2048 tokens:
-// whole call 106 us with one, 131 with three), an fp32 V, taken apart likewise, takes six.  Those six run on a chain of their
+// whole call 106 us with one, 126 with three), an fp32 V, taken apart likewise, takes six.  Those six run on a chain of their
 // own and are added to the output once, so an output component sees one rounding per 32 keys.
 template <int DT, int D, int PARTS>
 __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void prefill_rows_out_planes(PrefillArgs a) {
@@ -626,7 +625,7 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
       float pv[16];
       float sum = 0.0f;
       bool done = false;
-      if (interior) {
+      if (interior && !odd_values) {
         const float neg = -m;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {

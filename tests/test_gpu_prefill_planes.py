@@ -264,3 +264,26 @@ def test_outputs_of_small_values_keep_fp32_precision(d):
         scale = np.max(np.abs(want), axis=1, keepdims=True)
         # subnormal sums lose up to half a unit per addition, of random sign: 700 of them, sqrt(700) / 2
         assert np.all(np.abs(O[u] - want) <= 1e-5 * scale + 16 * 2.0 ** -149), u
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+def test_large_values_under_rising_scores(dtype, d):
+    """V of 1e34 to 1e37 and logits that rise by 15 powers of two along the prompt: sums against an early reference would be
+    2^15 times larger than the outputs and overflow."""
+    P = TP._parity()
+    rng = np.random.default_rng(17)
+    units, L = 3, 900
+    Q, K, V = (rng.standard_normal((units, L, d)).astype(np.float32) for _ in range(3))
+    Q[..., 0] = 8.0
+    K[..., 0] = np.linspace(0.0, 15.0 * math.log(2.0) * math.sqrt(d) / 8.0, L, dtype=np.float32)
+    V *= np.array([1e34, 1e37, 1e20], np.float32)[:, None, None]
+    V[2, 400:405] *= np.float32(1e17)
+    if dtype == "bf16":
+        Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
+    sess = P.make_session(units, d, L, 5, dtype)
+    O = P.gpu_prefill(sess, Q, K, V, [L] * units, True)["O"].astype(np.float64)
+    # fp32: as for ordinary values (1e-5 of the row's largest); bf16: its rounding
+    tol = 1e-5 if dtype == "f32" else 2.0 ** -8
+    for u in range(units):
+        want = orc.prefill_statistics(Q[u], K[u], V[u], L, 1.0 / math.sqrt(d), want_out=True).out
+        assert np.all(np.abs(O[u] - want) <= tol * np.max(np.abs(want), axis=1, keepdims=True)), u
