@@ -251,22 +251,23 @@ def test_block_steps_of_fp32_head_dim_64_at_the_benchmark_shape():
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("block", [1, 4])
 def test_an_infinite_value_of_a_far_lower_logit_stays_in_the_output(dtype, d, block):
-    """The slots of one split lie 260 powers of two below the others, so that split's weight underflows: an infinity among
-    its values is not finite in the output (0 x inf on the device, inf in the oracle's wider range), and only there."""
+    """The slots of one split (the second of eight) lie 260 powers of two below the others, the new tokens included, so that
+    split's weight underflows: an infinity among its values is not finite in the output (0 x inf on the device, inf in the
+    oracle's wider range), and only there."""
     import paper_2402_06262_amd as roco
     P = _P()
     units, B = 2, 2048
     rng = np.random.default_rng(3)
     K = np.full((units, B, d), 4.0 * math.sqrt(128.0 / d), np.float32)
     V = round_to_bf16(rng.standard_normal((units, B, d)).astype(np.float32))
-    K[:, :256] *= -1.0
-    V[1, 100, 7] = np.inf
+    K[:, 256:512] *= -1.0
+    V[1, 300, 7] = np.inf
     sess = P.make_session(units, d, B, 1, dtype, policy=orc.Policy("oldest", "all"))
     P.gpu_prefill(sess, K, K, V, [B] * units, False)
     ws = torch.empty(roco.block_workspace_bytes(sess.params, block), dtype=torch.uint8, device="cuda")
     new = np.full((units, block, d), K[0, -1, 0], np.float32)
     out, slots, _ = P.gpu_encode_block(sess, block, new, new, new, [B] * units, ws)
-    assert np.array_equal(np.sort(slots[1]), np.arange(block))  # slot 100 is attended
+    assert np.array_equal(np.sort(slots[1]), np.arange(block))  # slot 300 is attended
     assert np.isfinite(out[0]).all()
     assert not np.isfinite(out[1, :, 7]).any()
     assert np.isfinite(np.delete(out[1], 7, axis=1)).all()
