@@ -47,7 +47,7 @@ static_assert(kMaxBlock == 2 * kQ, "a step holds at most two tiles of query rows
 template <int NT, bool LDS>
 __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
   extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
-  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint32_t scan_sh[NT / kWave + 1];
   __shared__ int slot_of[kMaxBlock];
   const int u = blockIdx.x, tid = threadIdx.x;
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
     const uint32_t m = min(static_cast<uint32_t>(n), static_cast<uint32_t>(a.pol.scope_size(a.scope, n)) + static_cast<uint32_t>(E) - 1u);
 #pragma unroll 1
     for (int phase = 0; phase < 2; ++phase) {
-      const KSmallest r = select_k_smallest<NT>(
+      const KSmallest r = select_k_smallest<NT, 1>(
           [&](int i) -> uint32_t {
             const uint32_t vk = var_key[i];
             return phase == 0 ? vk : scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
@@ -665,11 +665,13 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   constexpr int NT = kFinThreads;
   constexpr int kSlots = 2 * NT;  // slots per sweep
   extern __shared__ uint32_t lds_keys[];  // [2][B] ranking keys when B <= kMaxDecodeBudgetLds
-  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint2 best_sh[NT / kWave];
   __shared__ float2 norm[kMaxBlock];  // reference and 1 / sum of every query row
-  __shared__ float2 part_ml[kMaxBlockSplits * kMaxBlock];
-  __shared__ float weight[kMaxBlockSplits * kMaxBlock];
+  // the merge of the splits is done before the search begins
+  float2* const part_ml = reinterpret_cast<float2*>(sel_sh);                        // [kMaxBlockSplits * kMaxBlock]
+  float* const weight = reinterpret_cast<float*>(part_ml + kMaxBlockSplits * kMaxBlock);  // ditto
+  static_assert(3 * kMaxBlockSplits * kMaxBlock <= SelectLds<1>::kWords, "the merge fits the search's words");
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B, nq = a.queries, S = a.splits, QR = a.qrows;
   int n = a.n_used[u];
@@ -807,7 +809,7 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   // the victim a following single-token step would take
   if (full) {
     __syncthreads();
-    const int victim = select_victim_block<NT>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
+    const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
     if (tid == 0) a.next_slot[u] = victim;
   } else if (tid == 0) {
     a.next_slot[u] = -1;

@@ -164,27 +164,36 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // many are equal.  What it costs is its barriers and its passes over the keys, so the first digit is wide: sign, exponent
 // and the two leading mantissa bits spread a unit's variances or scores over bins of a quarter octave, and usually few
 // enough keys share the chosen one that no second digit is counted -- as soon as a bin holds at most kSelectRanked keys they
-// are gathered and searched without another barrier.  A thread clears the bins it owns while it reads them, so a digit takes three barriers.
+// are gathered and searched without another barrier.  A thread clears the bins it owns while it reads them, so a digit takes
+// three barriers.
 // The largest key, 0xffffffff, is the mark of elements that do not take part: it is neither counted (thousands of additions
 // to one bin would be served one after the other) nor gathered, also where its neighbours, the keys of attention sinks, are.
-// `sh` needs kSelectLdsWords words of LDS.  All threads of the block call it.
+// PER_WORD: bins in a word of LDS, 2 for up to 65535 keys.  It costs half a percent of a small step, but where the units'
+// ranking keys fill the LDS four KiB of it are a resident workgroup (decode step of bf16 / 128 with 512 units x 9400 slots 484
+// -> 459 us, 768 x 6000 453 -> 438).
+// `sh` needs SelectLds<PER_WORD>::kWords words of LDS.  All threads of the block call it.
 constexpr int kSelectBins = 2048;
 constexpr int kSelectRanked = 128;
-constexpr int kSelectLdsWords = kSelectBins + 16 + 8;
+template <int PER_WORD> struct SelectLds {
+  static constexpr int kBinWords = kSelectBins / PER_WORD;
+  static constexpr int kWords = kBinWords + 16 + 8;
+};
 static_assert(kSelectRanked == 2 * kWave, "two candidates per lane");
 
 // UNROLL: of the passes over the keys, 1 for keys in LDS (short code), more where they come from memory.
-template <int NT, int UNROLL, class KeyFn>
+template <int NT, int UNROLL, int PER_WORD, class KeyFn>
 __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, uint32_t* sh,
                              uint32_t& kth, uint32_t& n_less, uint32_t& n_equal) {
   static_assert(NT <= 1024 && kSelectBins % NT == 0, "whole bins per thread");
   constexpr int OWN = kSelectBins / NT;   // consecutive bins per thread
-  uint32_t* const wtot = sh + kSelectBins;        // totals of the waves' bins
+  static_assert(PER_WORD == 1 || (PER_WORD == 2 && OWN % 2 == 0), "whole words per thread");
+  constexpr int OWN_WORDS = OWN / PER_WORD;
+  uint32_t* const wtot = sh + SelectLds<PER_WORD>::kBinWords;  // totals of the waves' bins
   uint32_t* const res = wtot + 16;                // bin, keys below the bin, keys in the bin, candidates gathered
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   __syncthreads();  // `sh` may still be in use by a previous call
 #pragma unroll
-  for (int i = 0; i < OWN; ++i) sh[tid * OWN + i] = 0;
+  for (int i = 0; i < OWN_WORDS; ++i) sh[tid * OWN_WORDS + i] = 0;
   __syncthreads();
   uint32_t prefix = 0, mask = 0, kk = k, less = 0, neq = 0;
   auto takes_part = [&](uint32_t key) { return (key & mask) == prefix && key != 0xffffffffu; };
@@ -195,16 +204,20 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, ui
 #pragma unroll UNROLL
     for (int i = tid; i < n; i += NT) {
       const uint32_t key = key_of(i);
-      if (takes_part(key)) atomicAdd(&sh[(key >> shift) & digit], 1u);
+      const uint32_t bin = (key >> shift) & digit;
+      if (takes_part(key)) atomicAdd(&sh[bin / PER_WORD], PER_WORD == 2 ? 1u << (16 * (bin & 1)) : 1u);
     }
     __syncthreads();
     uint32_t h[OWN], sum = 0;
 #pragma unroll
-    for (int i = 0; i < OWN; ++i) {
-      h[i] = sh[tid * OWN + i];
-      sh[tid * OWN + i] = 0;  // ready for the next digit
-      sum += h[i];
+    for (int i = 0; i < OWN_WORDS; ++i) {
+      const uint32_t word = sh[tid * OWN_WORDS + i];
+      sh[tid * OWN_WORDS + i] = 0;  // ready for the next digit
+      h[PER_WORD * i] = PER_WORD == 2 ? word & 0xffffu : word;
+      if (PER_WORD == 2) h[PER_WORD * i + PER_WORD - 1] = word >> 16;
     }
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) sum += h[i];
     uint32_t excl = wave_inclusive_scan(sum);
     if (lane == kWave - 1) wtot[wave] = excl;
     excl -= sum;
@@ -280,7 +293,7 @@ struct KSmallest {
   }
 };
 
-template <int NT, int UNROLL = 1, class KeyFn>
+template <int NT, int PER_WORD, int UNROLL = 1, class KeyFn>
 __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t* sh) {
   // everything is wanted (the policies whose scope is the whole cache, say): nothing to select
   if (k >= static_cast<uint32_t>(n)) return KSmallest{0xffffffffu, 0xffffffffu};
@@ -292,7 +305,7 @@ __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t
   for (int round = 0; round < 2; ++round) {
     const uint32_t kth = r.kth;
     uint32_t found, n_less, n_equal;
-    radix_select<NT, UNROLL>(
+    radix_select<NT, UNROLL, PER_WORD>(
         [&](int i) {
           const uint32_t key = key_of(i);
           return round == 0 ? key : key == kth ? static_cast<uint32_t>(i) : 0xffffffffu;
@@ -311,11 +324,11 @@ __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t
 
 // Scope = `scope` lowest variance keys among [0, B); returns the slot of lowest MAS key inside it (lowest
 // slot on equal keys).  Every thread of the block calls it and gets the same answer.
-template <int NT>
+template <int NT, int PER_WORD>
 __device__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, int scope,
                                    uint32_t* sel_sh, uint2* best_sh) {
   const int tid = threadIdx.x;
-  const KSmallest sc = select_k_smallest<NT>([&](int i) { return var_key[i]; }, B,
+  const KSmallest sc = select_k_smallest<NT, PER_WORD>([&](int i) { return var_key[i]; }, B,
                                              static_cast<uint32_t>(scope), sel_sh);
   uint32_t key = 0xffffffffu, idx = 0xffffffffu;
 #pragma unroll 1

@@ -217,15 +217,17 @@ __device__ __forceinline__ void update_statistics(float* acc, float* acc2, float
 }
 
 // ------------------------------------------------------------------------------------------------
-// LDS: the ranking keys are in LDS (B <= kMaxDecodeBudgetLds).
-template <int DT, int D, int NT, bool LDS>
+// LDS: the ranking keys are in LDS (B <= kMaxDecodeBudgetLds).  kPerWord: see radix_select.
+template <int DT, int D, int NT, bool LDS, int kPerWord>
 __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
   extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
-  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<kPerWord>::kWords];
   __shared__ uint2 best_sh[NT / kWave];
-  __shared__ float mrg_m[kMaxSplits], mrg_l[kMaxSplits];
-  __shared__ float mrg_o[NT / D][D];
+  float* const mrg_o = reinterpret_cast<float*>(sel_sh);  // [NT / D][D]: the output is done before the search begins
+  float* const mrg_m = mrg_o + NT;                        // [kMaxSplits]
+  float* const mrg_l = mrg_m + kMaxSplits;                // ditto
   static_assert(NT >= kMaxSplits && NT % D == 0, "one thread per split, whole groups per dimension");
+  static_assert(NT + 2 * kMaxSplits <= SelectLds<kPerWord>::kWords, "the merge fits the search's words");
 
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B, S = a.splits;
@@ -259,12 +261,12 @@ __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
     float o = 0.0f;
 #pragma unroll 1
     for (int s = g; s < S; s += G) o += (mrg_m[s] > -INFINITY) ? po[s * D + dd] * fast_exp2(mrg_m[s] - M) : 0.0f;
-    mrg_o[g][dd] = o;
+    mrg_o[tid] = o;
     __syncthreads();
     if (tid < D) {
-      float sum = mrg_o[0][tid];
+      float sum = mrg_o[tid];
 #pragma unroll
-      for (int k = 1; k < G; ++k) sum += mrg_o[k][tid];
+      for (int k = 1; k < G; ++k) sum += mrg_o[k * D + tid];
       store_elem<DT>(a.out, static_cast<size_t>(u) * D + tid, sum * inv);
     }
   }
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
   update_statistics<NT, 1>(acc, acc2, cnt, z, n, B, slot, M, inv, full, mas_key, var_key, nullptr, sk);
   if (full) {
     __syncthreads();
-    const int victim = select_victim_block<NT>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
+    const int victim = select_victim_block<NT, kPerWord>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
     if (tid == 0) a.next_slot[u] = victim;
   }
 }
@@ -307,10 +309,11 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   constexpr int NT = kFusedThreads, WAVES = NT / kWave;
   constexpr int PASS = WAVES * U * G::R;
   extern __shared__ __attribute__((aligned(16))) uint32_t lds_dyn[];  // [2][B] ranking keys, then [B] base-2 logits
-  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint2 best_sh[WAVES];
   __shared__ float sm_m[WAVES], sm_l[WAVES];
-  __shared__ float sm_acc[WAVES][D];
+  float* const sm_acc = reinterpret_cast<float*>(sel_sh);  // [WAVES][D]: the output is done before the search begins
+  static_assert(WAVES * D <= SelectLds<1>::kWords, "the waves' sums fit the search's words");
 
   const int u = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   if (lane < G::LPR) {
     if (lane == 0) { sm_m[wave] = st.m; sm_l[wave] = st.l; }
 #pragma unroll
-    for (int e = 0; e < G::EPL; ++e) sm_acc[wave][lane * G::EPL + e] = st.acc[e];
+    for (int e = 0; e < G::EPL; ++e) sm_acc[wave * D + lane * G::EPL + e] = st.acc[e];
   }
   __syncthreads();  // also orders the waves' logit stores before the reads below
   float M = -INFINITY;
@@ -385,7 +388,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   if (tid < D) {
     float o = 0.0f;
 #pragma unroll
-    for (int s = 0; s < WAVES; ++s) o += (sm_m[s] > -INFINITY) ? sm_acc[s][tid] * fast_exp2(sm_m[s] - M) : 0.0f;
+    for (int s = 0; s < WAVES; ++s) o += (sm_m[s] > -INFINITY) ? sm_acc[s * D + tid] * fast_exp2(sm_m[s] - M) : 0.0f;
     store_elem<DT>(a.out, static_cast<size_t>(u) * D + tid, o * inv);
   }
 
@@ -400,7 +403,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
                             var_key, vec ? &ahead : nullptr, StepKeys{a.pol, pos, qp});
   if (full) {
     __syncthreads();
-    const int victim = select_victim_block<NT>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
+    const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
     if (tid == 0) a.next_slot[u] = victim;
   }
 }
@@ -409,7 +412,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
 __global__ __launch_bounds__(kFinishThreads) void select_victims(DecodeArgs a) {
   constexpr int NT = kFinishThreads;
   extern __shared__ uint32_t lds_keys[];
-  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint2 best_sh[NT / kWave];
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B;
@@ -427,7 +430,7 @@ __global__ __launch_bounds__(kFinishThreads) void select_victims(DecodeArgs a) {
   for (int i = tid; i < B; i += NT)
     ranking_keys(acc[i], acc2[i], cnt[i], by_pos ? pos[i] : 0, a.pol, mas_key[i], var_key[i]);
   __syncthreads();
-  const int victim = select_victim_block<NT>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
+  const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
   if (tid == 0) a.next_slot[u] = victim;
 }
 
@@ -472,11 +475,12 @@ void launch_attend(const DecodeArgs& a, hipStream_t s) {
   else hipLaunchKernelGGL((decode_attend<DT, D, U, false, false>), grid, block, 0, s, a);
 }
 
-template <int DT, int D, int NT>
+template <int DT, int D, int NT, int PER_WORD>
 hipError_t launch_finish(const DecodeArgs& a, size_t key_lds, hipStream_t s) {
-  if (!allow_key_lds(reinterpret_cast<const void*>(decode_finish<DT, D, NT, true>), key_lds)) return hipErrorInvalidValue;
-  if (key_lds != 0) hipLaunchKernelGGL((decode_finish<DT, D, NT, true>), dim3(a.units), dim3(NT), key_lds, s, a);
-  else hipLaunchKernelGGL((decode_finish<DT, D, NT, false>), dim3(a.units), dim3(NT), 0, s, a);
+  if (!allow_key_lds(reinterpret_cast<const void*>(decode_finish<DT, D, NT, true, PER_WORD>), key_lds))
+    return hipErrorInvalidValue;
+  if (key_lds != 0) hipLaunchKernelGGL((decode_finish<DT, D, NT, true, PER_WORD>), dim3(a.units), dim3(NT), key_lds, s, a);
+  else hipLaunchKernelGGL((decode_finish<DT, D, NT, false, 1>), dim3(a.units), dim3(NT), 0, s, a);
   return hipGetLastError();
 }
 
@@ -504,7 +508,10 @@ hipError_t launch_decode_t(const DecodeArgs& a, hipStream_t s) {
     // A unit's statistics and selection are one workgroup's work: 1024 threads when there is at most one unit per
     // compute unit and enough slots to share out (measured: faster from 1024 slots on, e.g. 34 -> 28 us per step at
     // 40 units x 4096 slots, 78 -> 64 at 64 x 8192), else 256.
-    return a.B >= 1024 && a.units <= 256 ? launch_finish<DT, D, 1024>(a, lds, s) : launch_finish<DT, D, kFinishThreads>(a, lds, s);
+    // Above the one-kernel step's budget the keys of two or three units nearly fill a compute unit's LDS: two bins per word.
+    if (a.B >= 1024 && a.units <= 256) return launch_finish<DT, D, 1024, 1>(a, lds, s);
+    if (a.B > kMaxFusedBudget) return launch_finish<DT, D, kFinishThreads, 2>(a, lds, s);
+    return launch_finish<DT, D, kFinishThreads, 1>(a, lds, s);
   }
 }
 

@@ -29,7 +29,7 @@ template <int LDS>
 __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) {
   constexpr int NT = kSelThreads;
   extern __shared__ uint32_t lds_keys[];  // [2][L_max] ranking keys when L_max <= kMaxDecodeBudgetLds
-  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint32_t scan_sh[NT / kWave + 1];
   __shared__ uint2 best_sh[NT / kWave];
   const int u = blockIdx.x, tid = threadIdx.x;
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
         next = KSmallest{0xffffffffu, 0xffffffffu};
         break;
       }
-      const KSmallest r = select_k_smallest<NT, kUnroll>(
+      const KSmallest r = select_k_smallest<NT, 1, kUnroll>(
           [&](int i) -> uint32_t {
             const uint32_t vk = var_key[i];
             if (phase == 0) return vk;
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kGatherThreads) void prefill_gather(PrefillArgs a) 
 __global__ __launch_bounds__(kSelThreads) void select_retained(DecodeArgs a, int keep, int32_t* mask_out) {
   constexpr int NT = kSelThreads;
   extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
-  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[kSelectLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B;
   const int n = min(a.n_used[u], B);
@@ -199,9 +199,9 @@ __global__ __launch_bounds__(kSelThreads) void select_retained(DecodeArgs a, int
   for (int i = tid; i < n; i += NT)
     ranking_keys(acc[i], acc2[i], cnt[i], by_pos ? pos[i] : 0, a.pol, mas_key[i], var_key[i]);
   __syncthreads();
-  const KSmallest scope = select_k_smallest<NT>([&](int i) { return var_key[i]; }, n, m, sel_sh);
+  const KSmallest scope = select_k_smallest<NT, 1>([&](int i) { return var_key[i]; }, n, m, sel_sh);
   auto key2 = [&](int i) -> uint32_t { return scope.has(var_key[i], i) ? mas_key[i] : 0xffffffffu; };
-  const KSmallest out = select_k_smallest<NT>(key2, n, E, sel_sh);
+  const KSmallest out = select_k_smallest<NT, 1>(key2, n, E, sel_sh);
   for (int i = tid; i < B; i += NT) mask[i] = (i < n && !out.has(key2(i), i)) ? 1 : 0;
 }
 

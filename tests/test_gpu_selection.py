@@ -183,3 +183,40 @@ def test_block_that_evicts_a_sink(dtype, d, n, scope):
     assert want[0] == 0
     for u in range(units):
         assert np.array_equal(np.sort(slots[u]), want) and np.array_equal(np.sort(evicted[u]), want)
+
+
+@pytest.mark.parametrize("B", [4100, 16384])
+@pytest.mark.parametrize("scope", [1, 900])
+def test_victims_of_more_units_than_compute_units_with_large_budgets(B, scope):
+    """The decode step whose search packs two bins into a word: its victims are those of the search of roco_select_victims on
+    the statistics that the step leaves, most of them equal (one value per unit but for the slots of a few others)."""
+    import paper_2402_06262_amd as roco
+    units, d = 257, 64
+    p = roco.RocoParams(units, d, B, scope, roco.ROCO_BF16)
+    c = roco.alloc_cache(p)
+    g = torch.Generator(device="cuda").manual_seed(B + scope)
+    c.K.zero_()  # every slot receives the same probability
+    c.V.normal_(generator=g)
+    c.pos.copy_(torch.arange(B, device="cuda", dtype=torch.int32).expand(units, B))
+    c.n_used.fill_(B)
+    c.stats[:, 0], c.stats[:, 1], c.stats[:, 2] = 1.0, 0.5, 64.0
+    some = torch.randint(0, B, (units, 700), generator=g, device="cuda")
+    c.stats[:, 1].scatter_(1, some, torch.rand((units, 700), generator=g, device="cuda") + 0.05)
+    c.stats[:, 0].scatter_(1, some, torch.rand((units, 700), generator=g, device="cuda") + 0.5)
+    c.next_slot.copy_(some[:, 0])
+    ws = torch.empty(roco.decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    q, k, v = (torch.randn((units, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    qpos = torch.full((units,), B, dtype=torch.int32, device="cuda")
+    roco.roco_decode_step(p, q, torch.zeros_like(k), v, qpos, c.K, c.V, c.stats, c.pos, c.n_used, c.next_slot,
+                          torch.empty_like(q), None, None, ws)
+    got = c.next_slot.clone()
+    fresh = torch.full_like(got, -9)
+    roco.roco_select_victims(p, c.stats, c.pos, c.n_used, fresh, ws)
+    assert torch.equal(got, fresh)
+    stats = c.stats.cpu().numpy()
+    for u in (0, 100, 256):
+        acc, acc2, cnt = stats[u]
+        mas = acc / cnt
+        # one fused multiply-add on the device: float64 holds the product of two fp32 numbers exactly
+        var = np.maximum(np.float32(0.0), ((acc2 / cnt).astype(np.float64) - mas.astype(np.float64) ** 2).astype(np.float32))
+        assert int(got[u]) == orc.select_victim(mas, var, scope)
