@@ -88,7 +88,7 @@ __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
             const uint32_t vk = var_key[i];
             return phase == 0 ? vk : scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
           },
-          n, phase == 0 ? m : static_cast<uint32_t>(E), sel_sh);
+          n, phase == 0 ? m : static_cast<uint32_t>(E), phase == 0 && a.pol.scope_is_window(), sel_sh);
       if (phase == 0) scope = r;
       else out = r;
     }
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   // the victim a following single-token step would take
   if (full) {
     __syncthreads();
-    const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
+    const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol, a.scope, sel_sh, best_sh);
     if (tid == 0) a.next_slot[u] = victim;
   } else if (tid == 0) {
     a.next_slot[u] = -1;

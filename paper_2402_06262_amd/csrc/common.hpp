@@ -120,6 +120,22 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
   return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), kWave - 1));
 }
 
+// Bitwise or over the 64 lanes of a wave, the same way.
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+  auto other = [](uint32_t x, auto ctrl, auto row_mask) {
+    return static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(x), decltype(ctrl)::value, decltype(row_mask)::value, 0xF, false));
+  };
+  using std::integral_constant;
+  v |= other(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});
+  v |= other(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+  v |= other(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+  v |= other(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+  v |= other(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});
+  v |= other(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), kWave - 1));
+}
+
 // Index of the smallest key over all threads of the block (the lowest index among equal keys): every thread brings its
 // own best and gets the answer.  `sh` needs one entry per wave.  The waves' minima are reduced by the code that made them.
 template <int NT> __device__ __forceinline__ uint32_t block_argmin(uint32_t key, uint32_t idx, uint2* sh) {
@@ -168,6 +184,10 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // three barriers.
 // The largest key, 0xffffffff, is the mark of elements that do not take part: it is neither counted (thousands of additions
 // to one bin would be served one after the other) nor gathered, also where its neighbours, the keys of attention sinks, are.
+// `small`: the keys are small numbers, positions or indices: the digits then start at the highest bit that is set in any of
+// them, which takes one more pass over the keys.  From the top they would all share the first bins, whose counts are served
+// one key after the other, and the search among the last candidates would walk through twenty empty bits (step of 4 heads on
+// 300 units x 64 slots under a window scope: 23.7 -> 16.9 us; 16 tokens on 64 units x 512 slots: 41.8 -> 33.8).
 // PER_WORD: bins in a word of LDS, 2 for up to 65535 keys.  It costs half a percent of a small step, but where the units'
 // ranking keys fill the LDS four KiB of it are a resident workgroup (decode step of bf16 / 128 with 512 units x 9400 slots 484
 // -> 459 us, 768 x 6000 453 -> 438).
@@ -182,7 +202,7 @@ static_assert(kSelectRanked == 2 * kWave, "two candidates per lane");
 
 // UNROLL: of the passes over the keys, 1 for keys in LDS (short code), more where they come from memory.
 template <int NT, int UNROLL, int PER_WORD, class KeyFn>
-__device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, uint32_t* sh,
+__device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, bool small, uint32_t* sh,
                              uint32_t& kth, uint32_t& n_less, uint32_t& n_equal) {
   static_assert(NT <= 1024 && kSelectBins % NT == 0, "whole bins per thread");
   constexpr int OWN = kSelectBins / NT;   // consecutive bins per thread
@@ -194,13 +214,26 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, ui
   __syncthreads();  // `sh` may still be in use by a previous call
 #pragma unroll
   for (int i = 0; i < OWN_WORDS; ++i) sh[tid * OWN_WORDS + i] = 0;
+  if (small) {
+    uint32_t any = 0;
+#pragma unroll UNROLL
+    for (int i = tid; i < n; i += NT) {
+      const uint32_t key = key_of(i);
+      any |= key != 0xffffffffu ? key : 0u;
+    }
+    any = wave_or(any);
+    if (lane == 0) wtot[wave] = any;
+  }
   __syncthreads();
+  int top = 32;  // bits that are still to be counted
+  if (small) top = 32 - __builtin_clz(wave_or(lane < NT / kWave ? wtot[lane] : 0u) | 1u);
   uint32_t prefix = 0, mask = 0, kk = k, less = 0, neq = 0;
   auto takes_part = [&](uint32_t key) { return (key & mask) == prefix && key != 0xffffffffu; };
 #pragma unroll 1
-  for (int pass = 0; pass < 3; ++pass) {
-    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
-    const uint32_t digit = pass < 2 ? 2047u : 1023u;
+  while (top > 0) {
+    const int shift = max(top - 11, 0);
+    const uint32_t digit = (1u << (top - shift)) - 1u;
+    top = shift;
 #pragma unroll UNROLL
     for (int i = tid; i < n; i += NT) {
       const uint32_t key = key_of(i);
@@ -246,35 +279,47 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, ui
     less += res[1];
     kk -= res[1];
     neq = res[2];
-    if (neq <= kSelectRanked && pass < 2) {
-      // Few candidates are left: they are gathered (into the bins, which are clear and not needed any more), and every
-      // wave finishes on its own, two candidates per lane, bit by bit from the top of what is left of the keys: the
-      // candidates with a zero there are the lower ones.  Ballots and scalar counts only, no further barrier, and the
-      // search ends as soon as one candidate is left.
+    if (neq <= kSelectRanked && shift > 0) {
+      // Few candidates are left: they are gathered (into the bins, which are clear and not needed any more), and a wave
+      // finishes on its own, two candidates per lane, bit by bit from the top of what is left of the keys: the candidates
+      // with a zero there are the lower ones.  Ballots and scalar counts only, and the search ends as soon as one candidate
+      // is left.  Up to four waves all do this, without a barrier; more would share the schedulers with one another, so
+      // the first one leaves the answer to the others (16 tokens on 64 units x 512 slots: 35.3 -> 32.4 us).
+      constexpr bool kOneWave = NT > 4 * kWave;
 #pragma unroll UNROLL
       for (int i = tid; i < n; i += NT) {
         const uint32_t key = key_of(i);
         if (takes_part(key)) sh[atomicAdd(&res[3], 1u)] = key;
       }
       __syncthreads();
-      const uint32_t c0 = sh[lane], c1 = sh[lane + kWave];
-      uint64_t in0 = neq >= 64 ? ~0ull : (1ull << neq) - 1ull;
-      uint64_t in1 = neq > 64 ? (neq == 128 ? ~0ull : (1ull << (neq - 64)) - 1ull) : 0ull;
-      uint32_t left = neq;
+      if (!kOneWave || wave == 0) {
+        const uint32_t c0 = sh[lane], c1 = sh[lane + kWave];
+        uint64_t in0 = neq >= 64 ? ~0ull : (1ull << neq) - 1ull;
+        uint64_t in1 = neq > 64 ? (neq == 128 ? ~0ull : (1ull << (neq - 64)) - 1ull) : 0ull;
+        uint32_t left = neq;
 #pragma unroll 1
-      for (int bit = shift - 1; bit >= 0 && left > 1; --bit) {
-        const uint64_t z0 = in0 & ~__builtin_amdgcn_ballot_w64((c0 >> bit) & 1u);
-        const uint64_t z1 = in1 & ~__builtin_amdgcn_ballot_w64((c1 >> bit) & 1u);
-        const uint32_t zeros = __builtin_popcountll(z0) + __builtin_popcountll(z1);
-        if (kk <= zeros) {
-          in0 = z0; in1 = z1; left = zeros;
-        } else {
-          in0 &= ~z0; in1 &= ~z1; left -= zeros;
-          kk -= zeros; less += zeros;
+        for (int bit = shift - 1; bit >= 0 && left > 1; --bit) {
+          const uint64_t z0 = in0 & ~__builtin_amdgcn_ballot_w64((c0 >> bit) & 1u);
+          const uint64_t z1 = in1 & ~__builtin_amdgcn_ballot_w64((c1 >> bit) & 1u);
+          const uint32_t zeros = __builtin_popcountll(z0) + __builtin_popcountll(z1);
+          if (kk <= zeros) {
+            in0 = z0; in1 = z1; left = zeros;
+          } else {
+            in0 &= ~z0; in1 &= ~z1; left -= zeros;
+            kk -= zeros; less += zeros;
+          }
         }
+        prefix = in0 != 0 ? __builtin_amdgcn_readlane(c0, __builtin_ctzll(in0))
+                          : __builtin_amdgcn_readlane(c1, __builtin_ctzll(in1));
+        neq = left;
+        if (kOneWave && lane == 0) { res[0] = prefix; res[1] = less; res[2] = neq; }
       }
-      prefix = in0 != 0 ? __builtin_amdgcn_readlane(c0, __builtin_ctzll(in0)) : __builtin_amdgcn_readlane(c1, __builtin_ctzll(in1));
-      neq = left;
+      if (kOneWave) {
+        __syncthreads();
+        prefix = res[0];
+        less = res[1];
+        neq = res[2];
+      }
       break;
     }
   }
@@ -294,7 +339,7 @@ struct KSmallest {
 };
 
 template <int NT, int PER_WORD, int UNROLL = 1, class KeyFn>
-__device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t* sh) {
+__device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, bool small, uint32_t* sh) {
   // everything is wanted (the policies whose scope is the whole cache, say): nothing to select
   if (k >= static_cast<uint32_t>(n)) return KSmallest{0xffffffffu, 0xffffffffu};
   // At most two rounds through one copy of the search (these kernels start cold: a second copy is instructions to fetch):
@@ -310,7 +355,7 @@ __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t
           const uint32_t key = key_of(i);
           return round == 0 ? key : key == kth ? static_cast<uint32_t>(i) : 0xffffffffu;
         },
-        n, take, sh, found, n_less, n_equal);
+        n, take, round == 1 || small, sh, found, n_less, n_equal);
     if (round == 1) {
       r.index_limit = found;
     } else {
@@ -325,11 +370,11 @@ __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t
 // Scope = `scope` lowest variance keys among [0, B); returns the slot of lowest MAS key inside it (lowest
 // slot on equal keys).  Every thread of the block calls it and gets the same answer.
 template <int NT, int PER_WORD>
-__device__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, int scope,
+__device__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, const Policy& pol, int scope,
                                    uint32_t* sel_sh, uint2* best_sh) {
   const int tid = threadIdx.x;
   const KSmallest sc = select_k_smallest<NT, PER_WORD>([&](int i) { return var_key[i]; }, B,
-                                             static_cast<uint32_t>(scope), sel_sh);
+                                             static_cast<uint32_t>(pol.scope_size(scope, B)), pol.scope_is_window(), sel_sh);
   uint32_t key = 0xffffffffu, idx = 0xffffffffu;
 #pragma unroll 1
   for (int i = tid; i < B; i += NT) {

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
   update_statistics<NT, 1>(acc, acc2, cnt, z, n, B, slot, M, inv, full, mas_key, var_key, nullptr, sk);
   if (full) {
     __syncthreads();
-    const int victim = select_victim_block<NT, kPerWord>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
+    const int victim = select_victim_block<NT, kPerWord>(var_key, mas_key, B, a.pol, a.scope, sel_sh, best_sh);
     if (tid == 0) a.next_slot[u] = victim;
   }
 }
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
                             var_key, vec ? &ahead : nullptr, StepKeys{a.pol, pos, qp});
   if (full) {
     __syncthreads();
-    const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
+    const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol, a.scope, sel_sh, best_sh);
     if (tid == 0) a.next_slot[u] = victim;
   }
 }
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(kFinishThreads) void select_victims(DecodeArgs a) {
   for (int i = tid; i < B; i += NT)
     ranking_keys(acc[i], acc2[i], cnt[i], by_pos ? pos[i] : 0, a.pol, mas_key[i], var_key[i]);
   __syncthreads();
-  const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol.scope_size(a.scope, B), sel_sh, best_sh);
+  const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol, a.scope, sel_sh, best_sh);
   if (tid == 0) a.next_slot[u] = victim;
 }
 

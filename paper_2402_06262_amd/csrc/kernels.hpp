@@ -26,6 +26,7 @@ struct Policy {
     if (importance == kImpCount) return old + (p * attended > 1.0f ? 1.0f : 0.0f);
     return old + p * p;
   }
+  __host__ __device__ bool scope_is_window() const { return scope_kind == kScopeWindow; }  // its keys are positions
   __host__ __device__ bool needs_pos() const { return importance == kImpOldest || scope_kind == kScopeWindow; }
   // number of tokens inside the scope when n are cached
   __host__ __device__ int scope_size(int scope, int n) const { return scope_kind == kScopeAll ? n : scope; }

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
             if (phase == 1) return in_scope;
             return E > 0 && out.has(in_scope, i) ? 0xffffffffu : vk;
           },
-          n, k, sel_sh);
+          n, k, phase != 1 && a.pol.scope_is_window(), sel_sh);
       if (phase == 0) scope = r;
       else if (phase == 1) out = r;
       else next = r;
@@ -199,9 +199,9 @@ __global__ __launch_bounds__(kSelThreads) void select_retained(DecodeArgs a, int
   for (int i = tid; i < n; i += NT)
     ranking_keys(acc[i], acc2[i], cnt[i], by_pos ? pos[i] : 0, a.pol, mas_key[i], var_key[i]);
   __syncthreads();
-  const KSmallest scope = select_k_smallest<NT, 1>([&](int i) { return var_key[i]; }, n, m, sel_sh);
+  const KSmallest scope = select_k_smallest<NT, 1>([&](int i) { return var_key[i]; }, n, m, a.pol.scope_is_window(), sel_sh);
   auto key2 = [&](int i) -> uint32_t { return scope.has(var_key[i], i) ? mas_key[i] : 0xffffffffu; };
-  const KSmallest out = select_k_smallest<NT, 1>(key2, n, E, sel_sh);
+  const KSmallest out = select_k_smallest<NT, 1>(key2, n, E, false, sel_sh);
   for (int i = tid; i < B; i += NT) mask[i] = (i < n && !out.has(key2(i), i)) ? 1 : 0;
 }
 

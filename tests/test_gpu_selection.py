@@ -220,3 +220,33 @@ def test_victims_of_more_units_than_compute_units_with_large_budgets(B, scope):
         # one fused multiply-add on the device: float64 holds the product of two fp32 numbers exactly
         var = np.maximum(np.float32(0.0), ((acc2 / cnt).astype(np.float64) - mas.astype(np.float64) ** 2).astype(np.float32))
         assert int(got[u]) == orc.select_victim(mas, var, scope)
+
+
+@pytest.mark.parametrize("n,top", [(5, 5), (64, 64), (700, 700), (130, 2048), (2048, 4097), (300, 1 << 22), (5000, 2 ** 31 - 1),
+                                   (16400, 2 ** 30)])
+def test_window_scopes_over_positions_of_every_size(n, top):
+    """The search over positions starts at the highest bit that any of them has: the lowest positions are in the scope, the
+    token of lowest score among them goes (equal scores: by slot)."""
+    import paper_2402_06262_amd as roco
+    units = 3
+    rng = np.random.default_rng([n, top % 1000])
+    pos = np.stack([rng.permutation(top)[:n] if top < 10000 else rng.permutation(np.unique(rng.integers(0, top, 2 * n)))[:n]
+                    for _ in range(units)]).astype(np.int32)
+    acc = rng.integers(1, 9, (units, n)).astype(np.float32)
+    stats = torch.from_numpy(np.stack([acc, acc, np.ones_like(acc)], axis=1)).cuda()
+    n_used = torch.full((units,), n, dtype=torch.int32, device="cuda")
+    for scope in sorted({1, 2, n // 2, n - 1, n}):
+        p = roco.RocoParams(units, 64, n, scope, roco.ROCO_F32, importance=roco.ROCO_IMPORTANCE_AAS,
+                            scope_kind=roco.ROCO_SCOPE_WINDOW)
+        ws = torch.empty(roco.decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        victim = torch.empty((units,), dtype=torch.int32, device="cuda")
+        mask = torch.empty((units, n), dtype=torch.int32, device="cuda")
+        dpos = torch.from_numpy(pos).cuda()
+        roco.roco_select_victims(p, stats, dpos, n_used, victim, ws)
+        keep = n // 3
+        roco.roco_select_retained(p, keep, stats, dpos, n_used, mask, ws)
+        for u in range(units):
+            assert int(victim[u]) == orc.select_victim(acc[u].astype(np.float64), pos[u].astype(np.float64), scope)
+            want = np.ones(n, np.int32)
+            want[orc.select_evictions(acc[u].astype(np.float64), pos[u].astype(np.float64), scope, n - keep)] = 0
+            assert np.array_equal(mask[u].cpu().numpy(), want)
