@@ -62,6 +62,14 @@ __device__ __forceinline__ uint4 load16_streaming(const void* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// The thread's index for code behind a kernel's main loop: what is derived from it is computed there, not kept in registers
+// through the loop.
+__device__ __forceinline__ int late_thread_id() {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+
 // ---------------------------------------------------------------- cross-lane
 // Lane exchange inside a 16-lane row through the data-parallel-primitive path of the vector ALU (no LDS
 // traffic).  CTRL: 0xB1 = swap neighbours, 0x4E = swap pairs, 0x141 = mirror each 8 lanes, 0x140 = mirror
@@ -210,7 +218,7 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, bo
   constexpr int OWN_WORDS = OWN / PER_WORD;
   uint32_t* const wtot = sh + SelectLds<PER_WORD>::kBinWords;  // totals of the waves' bins
   uint32_t* const res = wtot + 16;                // bin, keys below the bin, keys in the bin, candidates gathered
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int tid = late_thread_id(), lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   __syncthreads();  // `sh` may still be in use by a previous call
 #pragma unroll
   for (int i = 0; i < OWN_WORDS; ++i) sh[tid * OWN_WORDS + i] = 0;
@@ -372,7 +380,7 @@ __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, bool sma
 template <int NT, int PER_WORD>
 __device__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, const Policy& pol, int scope,
                                    uint32_t* sel_sh, uint2* best_sh) {
-  const int tid = threadIdx.x;
+  const int tid = late_thread_id();
   const KSmallest sc = select_k_smallest<NT, PER_WORD>([&](int i) { return var_key[i]; }, B,
                                              static_cast<uint32_t>(pol.scope_size(scope, B)), pol.scope_is_window(), sel_sh);
   uint32_t key = 0xffffffffu, idx = 0xffffffffu;

@@ -175,7 +175,7 @@ template <int NT, int PF>
 __device__ __forceinline__ void update_statistics(float* acc, float* acc2, float* cnt, const float* z, int n, int B,
                                                   int slot, float M, float inv, bool full, uint32_t* mas_key,
                                                   uint32_t* var_key, StatsAhead<NT, PF>* ahead, const StepKeys& sk) {
-  const int tid = threadIdx.x;
+  const int tid = late_thread_id();
   if ((B & 3) == 0) {
     // four adjacent slots per thread, 128-bit accesses on every plane
     if (ahead != nullptr) {
@@ -303,21 +303,25 @@ __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
 // statistics from the logits kept in LDS and choose the next victim.  Nothing but the final results is written
 // to global memory and no second launch is needed; the price is that a workgroup's selection phase does not
 // stream, so this shape is used when there are at least about two units per compute unit to overlap with.
+// With non-temporal loads a third workgroup fits a compute unit: 168 registers (but for biased bf16) and the keys and logits
+// of up to 4096 slots beside 4.2 KiB of static LDS.  Hence the late thread index behind the stream and two bins per word in
+// the search (600 units x 1023 slots of bf16 / 128: 60.5 us, with a register too many 64.6; 600 x 3854 of bf16 / 64: 122 us,
+// with one bin per word 131).
 template <int DT, int D, int U, bool BIAS, bool STREAMING>
 __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   using G = RowGeom<DT, D>;
   constexpr int NT = kFusedThreads, WAVES = NT / kWave;
   constexpr int PASS = WAVES * U * G::R;
   extern __shared__ __attribute__((aligned(16))) uint32_t lds_dyn[];  // [2][B] ranking keys, then [B] base-2 logits
-  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<2>::kWords];
   __shared__ uint2 best_sh[WAVES];
   __shared__ float sm_m[WAVES], sm_l[WAVES];
   float* const sm_acc = reinterpret_cast<float*>(sel_sh);  // [WAVES][D]: the output is done before the search begins
-  static_assert(WAVES * D <= SelectLds<1>::kWords, "the waves' sums fit the search's words");
+  static_assert(WAVES * D <= SelectLds<2>::kWords, "the waves' sums fit the search's words");
 
   const int u = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int c = lane % G::LPR;
+  const int stream_wave = static_cast<int>(threadIdx.x) / kWave;
+  const int c = static_cast<int>(threadIdx.x) % G::LPR;
   const int B = a.B;
   const int n0 = a.n_used[u];
   const bool was_full = n0 >= B;
@@ -368,10 +372,11 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   };
   const int passes = (n + PASS - 1) / PASS;
   const int rot = a.rotate ? static_cast<int>((static_cast<unsigned>(u) * 5u) % static_cast<unsigned>(passes)) : 0;
-  stream_attend<DT, D, U, BIAS, STREAMING>(qf, Kb, Vb, 0, n, passes, rot, PASS, wave * (U * G::R), bias, pos, z, slot,
+  stream_attend<DT, D, U, BIAS, STREAMING>(qf, Kb, Vb, 0, n, passes, rot, PASS, stream_wave * (U * G::R), bias, pos, z, slot,
                                            fix_k, fix_v, st);
   merge_groups_in_wave<DT, D>(st);
 
+  const int tid = late_thread_id(), lane = tid & (kWave - 1), wave = tid / kWave;
   if (lane < G::LPR) {
     if (lane == 0) { sm_m[wave] = st.m; sm_l[wave] = st.l; }
 #pragma unroll
@@ -403,7 +408,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
                             var_key, vec ? &ahead : nullptr, StepKeys{a.pol, pos, qp});
   if (full) {
     __syncthreads();
-    const int victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol, a.scope, sel_sh, best_sh);
+    const int victim = select_victim_block<NT, 2>(var_key, mas_key, B, a.pol, a.scope, sel_sh, best_sh);
     if (tid == 0) a.next_slot[u] = victim;
   }
 }
