@@ -154,15 +154,19 @@ hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s);
 hipError_t launch_prefill_attention_planes(int dtype, int head_dim, PrefillArgs& a, hipStream_t s);
 // Prompts of few scores: the vector-ALU row pass, one wave per query and as many waves as queries, is done before a
 // workgroup of the matrix-core pass has walked its tiles one after the other.  Row pass, us, vector against matrix:
-// fp32 / 64 with output 4 units x 256 tokens 12 / 20, 1 x 512 19 / 29, 16 x 128 11 / 15, but 16 x 256 23 / 20 and 256 x 48
-// 17 / 12; bf16 / 64 with output 4 x 128 8 / 10.5, 1 x 256 10.3 / 11.6, but 4 x 256 12.1 / 11.9; fp32 / 128 without output
-// 4 x 128 12.8 / 14.6, but 16 x 128 14.9 / 14.7 and 1 x 256 20 / 16; 2 x 140 of fp32 / 64 9.5 / 12.4, of / 128 13.8 / 14.7.
+//   fp32 / 64 with output (2^19 scores)   4 units x 256 tokens 12.5 / 18.9, 2 x 512 19.6 / 28.6, 16 x 128 10.2 / 14.3, but
+//                                         32 x 128 15.0 / 14.2 and 128 x 64 16.6 / 16.1
+//   fp32 / 128 with output (2^19)         8 x 256 24.5 / 38.0, 32 x 128 23.6 / 25.3, but 128 x 64 26.0 / 25.3
+//   bf16 / 64 with output (2^18)          4 x 256 10.8 / 12.5, 2 x 362 13.2 / 14.5, 16 x 128 9.5 / 10.3, but 64 x 64 9.8 / 8.9
+//   fp32 / 64 without (192 tokens, 2^17)  8 x 128 8.8 / 9.2, 4 x 150 9.7 / 10.9, 2 x 160 9.4 / 10.2, but 1 x 200 10.5 / 10.6
+//   fp32 / 128 without (128 tokens, 2^17) 8 x 128 12.8 / 14.6, 13 x 100 12.5 / 14.5, but 1 x 140 13.2 / 12.4 and 4 x 150
+//                                         15.0 / 13.5
 inline bool prefill_is_tiny(const PrefillArgs& a, double scores) {
   return static_cast<double>(a.units) * a.group * a.L_max * a.L_max <= scores;
 }
-inline bool prefill_rows_are_tiny(const PrefillArgs& a, bool fp32) {
-  if (a.O != nullptr) return prefill_is_tiny(a, fp32 ? 524288.0 : 131072.0);
-  return fp32 && a.L_max <= 144 && prefill_is_tiny(a, 131072.0);
+inline bool prefill_rows_are_tiny(const PrefillArgs& a, bool fp32, int head_dim) {
+  if (a.O != nullptr) return prefill_is_tiny(a, fp32 ? 524288.0 : 262144.0);
+  return fp32 && a.L_max <= (head_dim == 64 ? 192 : 128) && prefill_is_tiny(a, 131072.0);
 }
 void launch_prefill_rows_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);  // the row pass alone
 // second shares of PrefillArgs::ksplit / qsplit merged into the first ones

@@ -842,7 +842,7 @@ hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
   constexpr int kShared = kRows<DT, D> > 32 ? 2 : 1;  // a tile of one sub-tile has nothing to share
   constexpr int kTarget = DT == kBF16 ? 1024 : 512;
   constexpr bool kPartFirst = DT == kBF16;
-  if (!a.skip_rows && prefill_rows_are_tiny(a, DT == kF32)) {
+  if (!a.skip_rows && prefill_rows_are_tiny(a, DT == kF32, D)) {
     launch_prefill_rows_simple(DT, D, a, s);
   } else if (!a.skip_rows) {
     ProfScope ps(kProfPrefillRows, s);

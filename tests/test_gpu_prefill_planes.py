@@ -162,12 +162,15 @@ def test_ends_of_the_fp32_range(d, monkeypatch):
 
 
 def test_tiny_prompts_take_the_vector_passes_and_agree(monkeypatch):
-    """Both sides of the size rules: 64 tokens, 2^19 = units x heads x L^2 (fp32 with output), 2^17 (bf16 with output, fp32
-    without up to 128 tokens)."""
+    """Both sides of the size rules: 64 tokens (both passes, fp32), 2^19 = units x heads x L^2 (fp32 with output), 2^18 (bf16
+    with output), 2^17 and 128 or 192 tokens (fp32 / 128 and fp32 / 64 without)."""
     for units, L in ((2, 64), (2, 65), (8, 256), (9, 256)):
         TP.run_workload("f32", 64, units, [L] * units, L, L // 2, 5, 1, seed=units + L, tag="planes-tiny")
-    for units, L in ((8, 128), (9, 128), (2, 129)):
+    for units, L in ((8, 128), (9, 128), (2, 128), (2, 129)):
         TP.run_workload("f32", 128, units, [L] * units, L, L // 2, 5, 1, seed=units + L, want_out=False, tag="planes-tiny")
+    for units, L in ((8, 128), (9, 128), (2, 144), (2, 145), (3, 192), (3, 193), (4, 192)):
+        TP.run_workload("f32", 64, units, [L] * units, L, L // 2, 5, 1, seed=units + L, want_out=False, tag="planes-tiny")
+    for units, L in ((8, 128), (9, 128), (2, 129), (16, 128), (17, 128), (4, 256), (1, 513)):
         TP.run_workload("bf16", 64, units, [L] * units, L, L // 2, 5, 1, seed=units + L, tag="planes-tiny")
 
 
