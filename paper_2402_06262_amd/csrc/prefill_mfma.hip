@@ -43,23 +43,13 @@ template <int WAVES> struct Staged {
   uint4 w[Shape<WAVES>::kChunks];  // this thread's bytes of a 64 x 256 B tile
 };
 
-// Thread t copies the chunks (row = t / 16 + sweep * threads / 16, column chunk t % 16) of the tile.
+// Thread t holds the chunks (row = t / 16 + sweep * threads / 16, column chunk t % 16) of the tile.
 template <int WAVES>
-__device__ __forceinline__ void tile_load(Staged<WAVES>& s, const char* base, int row0, int last_row) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < Shape<WAVES>::kChunks; ++i) {
-    int row = row0 + (t >> 4) + Shape<WAVES>::kRowsPerSweep * i;
-    row = row < last_row ? row : last_row;  // clamp: rows past the end are masked by the caller
-    s.w[i] = load16(base + static_cast<size_t>(row) * kRowBytes + (t & 15) * 16);
-  }
-}
-template <int WAVES, int ROW = kLdsRow>
 __device__ __forceinline__ void tile_store(const Staged<WAVES>& s, char* lds) {
   const int t = threadIdx.x;
 #pragma unroll
   for (int i = 0; i < Shape<WAVES>::kChunks; ++i)
-    *reinterpret_cast<uint4*>(lds + ((t >> 4) + Shape<WAVES>::kRowsPerSweep * i) * ROW + (t & 15) * 16) = s.w[i];
+    *reinterpret_cast<uint4*>(lds + ((t >> 4) + Shape<WAVES>::kRowsPerSweep * i) * kLdsRow + (t & 15) * 16) = s.w[i];
 }
 
 // Two 32x32 score tiles: streamed rows [sub*32, sub*32+32) of the LDS tile against the wave's two groups of

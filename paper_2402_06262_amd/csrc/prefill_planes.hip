@@ -821,11 +821,6 @@ unsigned ids(const PrefillArgs& a, int heads, const Launch& l) {
 }
 
 template <int DT, int D, int PARTS>
-void launch_rows(const PrefillArgs& b, unsigned n, hipStream_t s) {
-  if (b.O != nullptr) hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, PARTS>), dim3(n), dim3(kThreads), 0, s, b);
-  else hipLaunchKernelGGL((prefill_rows_planes<DT, D, PARTS>), dim3(n), dim3(kThreads), 0, s, b);
-}
-template <int DT, int D, int PARTS>
 void launch_columns(const PrefillArgs& b, unsigned n, hipStream_t s) {
   switch (b.group) {
     case 1: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 1>), dim3(n), dim3(kThreads), 0, s, b); break;
@@ -846,14 +841,20 @@ hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
     launch_prefill_rows_simple(DT, D, a, s);
   } else if (!a.skip_rows) {
     ProfScope ps(kProfPrefillRows, s);
-    Launch l = schedule(static_cast<long long>(a.units) * a.group, a.L_max, kTarget, kShared == 2, a.group == 1, kPartFirst);
-    if (a.O != nullptr) l = {0, 0, 1, kShared};
-    if (a.O != nullptr) l.pairs = (a.L_max + 128 / l.parts - 1) / (128 / l.parts);
     PrefillArgs b = a;
-    b.pairs = l.pairs; b.paired = l.paired; b.ksplit = l.split;
-    if (l.parts == 2) launch_rows<DT, D, kShared>(b, ids(a, a.group, l), s);
-    else launch_rows<DT, D, 1>(b, ids(a, a.group, l), s);
-    if (l.split > 1) launch_merge_key_shares(b, s);
+    if (a.O != nullptr) {  // single blocks, head_dim 64 with waves that share them
+      constexpr int kOwn = Shares<kShared>::kOwn;
+      b.pairs = (a.L_max + kOwn - 1) / kOwn; b.paired = 0; b.ksplit = 1;
+      const unsigned n = ids(a, a.group, {b.pairs, 0, 1, kShared});
+      hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, kShared>), dim3(n), dim3(kThreads), 0, s, b);
+    } else {
+      const Launch l = schedule(static_cast<long long>(a.units) * a.group, a.L_max, kTarget, kShared == 2, a.group == 1, kPartFirst);
+      b.pairs = l.pairs; b.paired = l.paired; b.ksplit = l.split;
+      const dim3 grid(ids(a, a.group, l));
+      if (l.parts == 2) hipLaunchKernelGGL((prefill_rows_planes<DT, D, kShared>), grid, dim3(kThreads), 0, s, b);
+      else hipLaunchKernelGGL((prefill_rows_planes<DT, D, 1>), grid, dim3(kThreads), 0, s, b);
+      if (l.split > 1) launch_merge_key_shares(b, s);
+    }
   }
   ProfScope ps(kProfPrefillColumns, s);
   const Launch l = schedule(a.units, a.L_max, kTarget, kShared == 2, true, kPartFirst);
