@@ -12,10 +12,13 @@
 // rounding per 16 products at its own magnitude.  Six bf16 instructions cover 16 k-elements in 192 matrix cycles; the
 // fp32 instruction (32x32x2) needs 512.
 //
-// What bounds the passes: bf16 / head_dim 64 has 4 matrix instructions (128 cycles) per 32x32 tile against 16 x 16
-// vector cycles in the row pass and 16 x 20 in the column pass (multiply-add, exponential at half rate, additions), so
-// it is bound by vector issue; fp32 has 24 (head_dim 64) or 48 matrix instructions and is bound by the matrix pipe.  Two
-// or more workgroups per compute unit overlap the one pipe's work with the other's; nothing is pipelined by hand.
+// What bounds the passes (counters, 128 streams x 2048 tokens of bf16 / 64, four heads): a 32x32 tile takes 81 vector
+// instructions in the row pass and 98 in the column pass, 392 and 457 issue cycles where multiply-adds, exponentials and
+// additions alone need 256 and 320, against 128 matrix cycles.  The vector ALUs are busy 77 and 72 % of the time, the matrix
+// pipe 25 and 20 %, half of that beside a vector instruction, neither of them 11 and 18 %: vector issue above all, and what
+// one wave's chain of scores, exponentials and sums leaves idle although two to four workgroups per compute unit overlap.
+// fp32 / 64 (96 ragged units of up to 1000 tokens): vector ALUs 56 and 55 %, matrix pipe 38 and 34 %, neither 20 and 23 %:
+// exponentials and operand splitting, then products, and the start and end of short streams.  Nothing is pipelined by hand.
 //
 // What three planes do not hold exactly -- infinities and NaN, values from 2^127 on, which may round to infinity, nonzero
 // values below 2^-110, whose last bits are below bf16's range -- stays off the matrix cores: a wave that owns such a row, and
