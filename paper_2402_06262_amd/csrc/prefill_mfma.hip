@@ -1425,8 +1425,8 @@ hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
   b.pairs = b.paired ? (n_blocks + 1) / 2 : n_blocks;  // ids per unit
   b.qsplit = columns_query_shares(a, b.pairs);
   b.ksplit = a.group == 1 ? b.qsplit : 1;  // the second share's plane has no room for several heads
-  const dim3 grid(static_cast<unsigned>((a.units + 7) / 8 * 8 * b.pairs * b.qsplit));
-  const dim3 rows_grid(static_cast<unsigned>((a.units + 7) / 8 * 8 * a.group * b.pairs * b.ksplit));  // one id set per query head
+  const dim3 grid(workgroup_ids(a.units, b.pairs * b.qsplit));
+  const dim3 rows_grid(workgroup_ids(a.units, a.group * b.pairs * b.ksplit));  // one id set per query head
   if (!a.skip_rows) {
     ProfScope ps(kProfPrefillRows, s);
     hipLaunchKernelGGL(prefill_rows_mfma, rows_grid, dim3(WAVES * kWave), 0, s, b);
@@ -1452,7 +1452,7 @@ hipError_t launch_with_output(PrefillArgs& a, hipStream_t s) {
   b.pairs = (a.L_max + 127) / 128;  // workgroup ids per unit
   {
     ProfScope ps(kProfPrefillRows, s);
-    hipLaunchKernelGGL(prefill_rows_out_mfma, dim3(static_cast<unsigned>((a.units + 7) / 8 * 8 * a.group * b.pairs)),
+    hipLaunchKernelGGL(prefill_rows_out_mfma, dim3(workgroup_ids(a.units, a.group * b.pairs)),
                        dim3(256), 0, s, b);
   }
   constexpr int kOwn = Shape<4>::kOwn;
@@ -1463,7 +1463,7 @@ hipError_t launch_with_output(PrefillArgs& a, hipStream_t s) {
   c.qsplit = columns_query_shares(a, c.pairs);
   {
     ProfScope ps(kProfPrefillColumns, s);
-    const dim3 cgrid(static_cast<unsigned>((a.units + 7) / 8 * 8 * c.pairs * c.qsplit));
+    const dim3 cgrid(workgroup_ids(a.units, c.pairs * c.qsplit));
     if (a.group != 1) launch_columns_grouped<4>(c, cgrid, s);
     else if (a.pol.counts_above_average()) hipLaunchKernelGGL(prefill_columns_mfma<true>, cgrid, dim3(4 * kWave), 0, s, c);
     else hipLaunchKernelGGL(prefill_columns_mfma<false>, cgrid, dim3(4 * kWave), 0, s, c);

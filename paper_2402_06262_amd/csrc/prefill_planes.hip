@@ -820,7 +820,7 @@ Launch schedule(long long streams, int L_max, int target, bool may_part, bool ma
   return l;
 }
 unsigned ids(const PrefillArgs& a, int heads, const Launch& l) {
-  return static_cast<unsigned>((a.units + 7) / 8 * 8 * heads * l.pairs * l.split);
+  return mfma::workgroup_ids(a.units, heads * l.pairs * l.split);
 }
 
 template <int DT, int D, int PARTS>

@@ -10,22 +10,36 @@ namespace mfma {
 // Workgroup -> (unit, block-pair) mapping.  The hardware hands consecutive workgroup ids to the 8 accelerator
 // dies in turn and each die has its own L2, so the workgroups of one unit (which all stream the same K or Q
 // tiles, at about the same time) are given ids that are congruent modulo 8: they land on one die and all but
-// the first fetch of a tile hit its L2.  The grid is one-dimensional over ceil(units/8)*8 x pairs ids.
+// the first fetch of a tile hit its L2.  That holds for the units that fill all dies evenly, units / 8 * 8 of them; the
+// workgroups of the up to seven units left over are dealt to the dies in turn, since whole units would leave dies without
+// work (whole units on whole dies: 2 units x 8 heads x 4396 tokens of bf16 / 64 with output took 640 us, 3 x 8 x 2578 of
+// fp32 / 64 679, 22 x 8 x 3323 of bf16 / 128 592; now 363, 458 and 558).  The grid is one-dimensional over
+// workgroup_ids(units, pairs) ids.
+__host__ __device__ inline unsigned workgroup_ids(int units, int pairs) {
+  const unsigned even = static_cast<unsigned>(units) / 8 * 8, rest = static_cast<unsigned>(units) - even;
+  return even * pairs + (rest * pairs + 7) / 8 * 8;
+}
 __device__ __forceinline__ bool locate(int units, int pairs, int& unit, int& pair) {
-  const int lin = blockIdx.x;
-  const int die = lin & 7, seq = lin >> 3;
-  unit = (seq / pairs) * 8 + die;
-  pair = seq % pairs;
+  const int lin = blockIdx.x, even = units & ~7;
+  const int seq = lin >> 3;
+  if (seq * 8 < even * pairs) {
+    unit = (seq / pairs) * 8 + (lin & 7);
+    pair = seq % pairs;
+    return true;
+  }
+  const int k = lin - even * pairs;
+  unit = even + k / pairs;
+  pair = k % pairs;
   return unit < units;
 }
 // The same for (unit, query head) pairs, u = unit * group + head: the heads of a unit stream the same keys (and
-// values), so they all go to the die unit % 8.  The grid covers ceil(units / 8) * 8 * group * pairs ids.
+// values), so they share a die, one head after the other.  The grid covers workgroup_ids(units, group * pairs) ids.
 __device__ __forceinline__ bool locate_heads(int units, int group, int pairs, int& u, int& pair) {
-  int v;  // virtual index: die v % 8, and on a die the heads of one unit before the next unit's
-  if (!locate(((units + 7) / 8) * 8 * group, pairs, v, pair)) return false;
-  const int unit = (v / (8 * group)) * 8 + (v & 7), head = (v >> 3) % group;
-  u = unit * group + head;
-  return unit < units;
+  int unit, id;
+  if (!locate(units, group * pairs, unit, id)) return false;
+  u = unit * group + id / pairs;
+  pair = id % pairs;
+  return true;
 }
 
 // Online log-sum-exp update of one lane with the 16 scores of a tile.
