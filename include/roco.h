@@ -51,7 +51,7 @@ enum {
   ROCO_OK = 0,
   ROCO_EINVAL = -1,        /* null / misaligned pointer, budget < 1, scope outside [1, budget], ... */
   ROCO_EUNSUPPORTED = -2,  /* dtype or head_dim the kernels are not built for                       */
-  ROCO_EWORKSPACE = -3,    /* workspace smaller than the matching *_workspace_bytes() query        */
+  ROCO_EWORKSPACE = -3,    /* workspace smaller than the call needs (the *_workspace_bytes() query's answer never is) */
   ROCO_EHIP = -4,          /* a kernel launch failed (hipGetLastError)                             */
   ROCO_ESCRATCH = -5       /* roco_decode_step_static: the shape needs more than ROCO_STATIC_SCRATCH_BYTES */
 };
@@ -95,7 +95,9 @@ enum {
   ROCO_SCOPE_ALL = 2      /* every cached token; `scope` is ignored                                           */
 };
 
-/* Bytes of scratch the two calls need for these params (0 on invalid params). */
+/* Bytes of scratch the two calls need for these params (0 on invalid params).  For prompts of few units the prefill query
+ * answers with room for partial sums of up to 16 workgroups per block of keys; a call with less, down to
+ * 4 * units * L_max floats and units * group * L_max more (each rounded up to 256 bytes), runs on fewer workgroups. */
 size_t roco_prefill_workspace_bytes(const roco_params* params, int32_t L_max);
 size_t roco_decode_workspace_bytes(const roco_params* params);
 
@@ -387,10 +389,11 @@ int roco_probe_mfma(int32_t workgroups, int32_t iters, int32_t operands, float* 
  *   ROCO_STREAMING_LOADS=0|1   non-temporal loads of the cache rows (default: caches above 192 MiB)
  *   ROCO_PREFILL_SIMPLE=1      vector-ALU prefill passes for every dtype and head_dim
  *   ROCO_PREFILL_PAIRED=0|1    bf16 / head_dim 128: one block of rows per workgroup / a long and a short one (default 1)
- *   ROCO_PREFILL_QSPLIT=1|2    bf16 / head_dim 128: workgroups per block of rows in the two prefill passes (default: 2 with
- *                              few units)
+ *   ROCO_PREFILL_QSPLIT=1..16  bf16 / head_dim 128: workgroups per block of rows in the two prefill passes (default: more with
+ *                              fewer units)
  *   ROCO_PREFILL_GQA_RING=0    bf16 / head_dim 128: grouped-query column pass with register-staged tiles instead of the LDS
  *                              ring
+ *                              (any of the three also keeps short or few prompts on the kernels with 256 rows per workgroup)
  *   ROCO_BLOCK_SPLITS=n        splits of the budget in the block-wise / grouped steps (default: about 512 / units)
  *   ROCO_BLOCK_SINGLE=0        single-token block steps go through the preparing kernel like longer blocks
  */

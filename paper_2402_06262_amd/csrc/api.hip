@@ -7,6 +7,7 @@
 
 #include "../../include/roco.h"
 #include "kernels.hpp"
+#include "prefill_schedule.hpp"
 #include "profile.hpp"
 
 // Scratch of roco_decode_step_static: device memory that belongs to the library's code object, so the call needs no
@@ -63,13 +64,16 @@ DecodeLayout decode_layout(const roco_params* p) {
   return l;
 }
 
-// ---- prefill workspace: acc | acc2 | var_key | mas_key, each [units][L_max], then lse [units][group][L_max]
-struct PrefillLayout { size_t lse, acc, acc2, var_key, mas_key, total; };
-PrefillLayout prefill_layout(const roco_params* p, int32_t L_max, int32_t group) {
+// ---- prefill workspace: acc | acc2 | var_key | mas_key | further pairs of column sums, each [units][L_max], then lse
+// [units][group][L_max].  `shares` pairs in all: two are what a call needs, more let it use more of the chip (see
+// prefill_query_shares); a call takes as many as the workspace it is given has room for.
+struct PrefillLayout { size_t lse, plane, total; int shares; };
+PrefillLayout prefill_layout(const roco_params* p, int32_t L_max, int32_t group, int shares) {
   PrefillLayout l;
-  const size_t plane = align_up(static_cast<size_t>(p->units) * L_max * sizeof(float));
-  l.acc = 0; l.acc2 = plane; l.var_key = 2 * plane; l.mas_key = 3 * plane; l.lse = 4 * plane;
-  l.total = 4 * plane + align_up(static_cast<size_t>(p->units) * group * L_max * sizeof(float));
+  l.shares = shares;
+  l.plane = align_up(static_cast<size_t>(p->units) * L_max * sizeof(float));
+  l.lse = 2 * static_cast<size_t>(shares) * l.plane;
+  l.total = l.lse + align_up(static_cast<size_t>(p->units) * group * L_max * sizeof(float));
   return l;
 }
 
@@ -152,13 +156,13 @@ extern "C" {
 
 size_t roco_prefill_workspace_bytes(const roco_params* params, int32_t L_max) {
   if (check_params(params) != ROCO_OK || L_max < 1) return 0;
-  return prefill_layout(params, L_max, 1).total;
+  return prefill_layout(params, L_max, 1, prefill_query_shares(params->dtype, params->head_dim, params->units, 1, L_max)).total;
 }
 
 size_t roco_prefill_gqa_workspace_bytes(const roco_params* params, int32_t group, int32_t L_max) {
   if (check_params(params) != ROCO_OK || L_max < 1 || group < 1 || group > kMaxPrefillGroup) return 0;
   if (static_cast<long long>(params->units) * group > 65535) return 0;
-  return prefill_layout(params, L_max, group).total;
+  return prefill_layout(params, L_max, group, prefill_query_shares(params->dtype, params->head_dim, params->units, group, L_max)).total;
 }
 
 size_t roco_decode_workspace_bytes(const roco_params* params) {
@@ -190,8 +194,12 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
   for (const void* ptr : need)
     if (ptr == nullptr || !aligned16(ptr)) return ROCO_EINVAL;
   if (O != nullptr && !aligned16(O)) return ROCO_EINVAL;
-  const PrefillLayout lay = prefill_layout(params, L_max, group);
+  PrefillLayout lay = prefill_layout(params, L_max, group, 2);
   if (workspace_bytes < lay.total) return ROCO_EWORKSPACE;
+  for (int shares = prefill_query_shares(params->dtype, params->head_dim, params->units, group, L_max); shares > 2; shares /= 2) {
+    const PrefillLayout more = prefill_layout(params, L_max, group, shares);
+    if (workspace_bytes >= more.total) { lay = more; break; }
+  }
 
   PrefillArgs a;
   a.units = params->units; a.L_max = L_max; a.B = params->budget; a.scope = params->scope;
@@ -202,7 +210,8 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
   a.skip_rows = want_lse ? 1 : 0;
   a.qsplit = 1;
   a.ksplit = 1;
-  a.two_shares = 0;
+  a.shares = lay.shares;
+  a.shares_to_add = 1;
   a.scale_log2 = scale_log2(params);
   a.recency_window = params->recency_window;
   a.recency_bias_log2 = params->recency_bias * 1.4426950408889634f;
@@ -210,10 +219,11 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
   a.K_cache = K_cache; a.V_cache = V_cache; a.stats = stats; a.pos = pos; a.n_used = n_used; a.next_slot = next_slot; a.O = O;
   char* ws = static_cast<char*>(workspace);
   a.lse = reinterpret_cast<float*>(ws + lay.lse);
-  a.acc = reinterpret_cast<float*>(ws + lay.acc);
-  a.acc2 = reinterpret_cast<float*>(ws + lay.acc2);
-  a.var_key = reinterpret_cast<uint32_t*>(ws + lay.var_key);
-  a.mas_key = reinterpret_cast<uint32_t*>(ws + lay.mas_key);
+  a.plane = lay.plane / sizeof(float);
+  a.acc = reinterpret_cast<float*>(ws);
+  a.acc2 = a.sums_of(0, 1);
+  a.var_key = reinterpret_cast<uint32_t*>(a.sums_of(1, 0));
+  a.mas_key = reinterpret_cast<uint32_t*>(a.sums_of(1, 1));
 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   // (the matrix-core kernels address a unit's rows with 32-bit byte offsets: up to 4M tokens of 256 bytes)

@@ -76,6 +76,9 @@ struct DecodeArgs {
   uint32_t* keys;        // [units][2][B] ranking keys when B is too large for LDS, else unused
 };
 
+constexpr int kMaxKeyShares = 4;     // PrefillArgs::ksplit
+constexpr int kMaxQueryShares = 16;  // PrefillArgs::qsplit
+
 struct PrefillArgs {
   int units, L_max, B, scope;
   int group;             // query heads per unit (1 without grouped-query attention): Q and lse are [units][group][L_max]
@@ -83,9 +86,10 @@ struct PrefillArgs {
   int pairs;             // matrix-core path: workgroup ids per unit (set by its launcher)
   int paired;            // matrix-core path: 1 = long+short block per workgroup, 0 = one block, -1 = choose
   int skip_rows;         // 1: lse already holds the row normalisers, pass 1 is not run
-  int qsplit;            // matrix-core path: 1, or 2 = two workgroups share a block's queries (set by its launcher)
-  int ksplit;            // matrix-core path, row pass: 1, or 2 = two workgroups share a block's keys (ditto)
-  int two_shares;        // 1: acc / acc2 hold half of the column sums, var_key / mas_key the other (set by the passes' launcher)
+  int qsplit;            // matrix-core path: workgroups that share a block of keys, each with a part of the queries (set by its launcher)
+  int ksplit;            // matrix-core path, row pass: workgroups that share a block of queries (ditto)
+  int shares;            // pairs of planes for column sums that the workspace has, 2 at least
+  int shares_to_add;     // > 1: the column sums lie in that many shares, which the selection adds (set by the passes' launcher)
   float scale_log2;
   int recency_window;
   float recency_bias_log2;
@@ -98,10 +102,23 @@ struct PrefillArgs {
   void* O;               // may be null
   // workspace
   float* lse;            // [units][group][L_max]  base-2 log-sum-exp of every query row
-  float* acc;            // [units][L_max]
+  float* acc;            // [units][L_max]; acc, acc2, var_key, mas_key and what follows are planes of `plane` words side by side
   float* acc2;           // [units][L_max]
   uint32_t* var_key;     // [units][L_max]
   uint32_t* mas_key;     // [units][L_max]
+  size_t plane;
+  // where share `share` of a pass that several workgroups divide leaves its sums (which = 0: Acc, 1: Acc2): the first in acc and
+  // acc2, the second in the planes that the selection will later use for its ranking keys, further ones behind those
+  __host__ __device__ float* sums_of(int share, int which) const { return acc + static_cast<size_t>(2 * share + which) * plane; }
+  // ... and its row normalisers: the first where they belong, the others in the planes of the column sums, all heads together
+  __host__ __device__ float* lse_of_share(int share) const {
+    return share == 0 ? lse : acc + static_cast<size_t>(share - 1) * units * group * L_max;
+  }
+  // most shares whose normalisers have room there
+  int row_shares() const {
+    const size_t room = 1 + 2 * static_cast<size_t>(shares) * plane / (static_cast<size_t>(units) * group * L_max);
+    return room < kMaxKeyShares ? static_cast<int>(room) : kMaxKeyShares;
+  }
 };
 
 constexpr int kMaxBlock = 64;        // query rows (tokens x heads) per block-wise step: two 32-wide matrix tiles
@@ -149,9 +166,12 @@ hipError_t launch_set_overlap(int units, int slots_a, const int32_t* pos_a, cons
                               int slots_b, const int32_t* pos_b, const int32_t* mask_b, const int32_t* n_b, int max_pos,
                               int32_t* inter, int32_t* uni, hipStream_t s);
 hipError_t launch_prefill_attention_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);
-// The matrix-core passes: bf16 / 128, and the other forms.  Both may leave PrefillArgs::two_shares set for prefill_select.
+// The matrix-core passes: bf16 / 128, and the other forms.  Both may leave PrefillArgs::shares_to_add set for prefill_select.
 hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s);
 hipError_t launch_prefill_attention_planes(int dtype, int head_dim, PrefillArgs& a, hipStream_t s);
+struct PassPlan;  // prefill_schedule.hpp
+void launch_prefill_rows_planes_wide(const PrefillArgs& a, const PassPlan& plan, hipStream_t s);
+void launch_prefill_columns_planes_wide(PrefillArgs& a, const PassPlan& plan, hipStream_t s);
 // Prompts of few scores: the vector-ALU row pass, one wave per query and as many waves as queries, is done before a
 // workgroup of the matrix-core pass has walked its tiles one after the other.  Row pass, us, vector against matrix:
 //   fp32 / 64 with output (2^19 scores)   4 units x 256 tokens 12.5 / 18.9, 2 x 512 19.6 / 28.6, 16 x 128 10.2 / 14.3, but
@@ -169,12 +189,16 @@ inline bool prefill_rows_are_tiny(const PrefillArgs& a, bool fp32, int head_dim)
   return fp32 && a.L_max <= (head_dim == 64 ? 192 : 128) && prefill_is_tiny(a, 131072.0);
 }
 void launch_prefill_rows_simple(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);  // the row pass alone
-// second shares of PrefillArgs::ksplit / qsplit merged into the first ones
+// the shares of PrefillArgs::ksplit / qsplit merged into the first ones
 void launch_merge_key_shares(const PrefillArgs& a, hipStream_t s);
-// The selection adds the two shares of the column sums itself where it keeps its ranking keys in LDS, not in the planes of
-// the second share, and nothing else comes between; else a kernel of its own does (5 us of a call).
-inline bool selection_adds_shares(const PrefillArgs& a) { return a.L_max <= kMaxDecodeBudgetLds && !a.pol.keeps_last_score(); }
-void join_query_shares(PrefillArgs& a, hipStream_t s);
+// The selection adds the shares of the column sums itself where it keeps its ranking keys in LDS, not in the planes of the
+// second share, and nothing else comes between; else, and for more than two shares of more than 2048 tokens, a kernel of its
+// own does: 3 to 5 us of a call, which one workgroup per unit takes too for four shares of 4096 tokens (2 x 6872: selection 30
+// us with two shares, 36 with eight, 41 with sixteen), but not for a few hundred.
+inline bool selection_adds_shares(const PrefillArgs& a, int shares) {
+  return (shares <= 2 || a.L_max <= 2048) && a.L_max <= kMaxDecodeBudgetLds && !a.pol.keeps_last_score();
+}
+void join_query_shares(PrefillArgs& a, const PrefillArgs& pass, hipStream_t s);
 // overwrites PrefillArgs::acc2 with the attention row of each unit's last prompt token (kImpLast)
 hipError_t launch_lse_to_base2(const float* lse_ln, float* lse_log2, size_t n, hipStream_t s);
 hipError_t launch_prefill_last_row(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);

@@ -20,6 +20,7 @@
 
 #include "kernels.hpp"
 #include "mfma.hpp"
+#include "prefill_schedule.hpp"
 #include "prefill_tiles.hpp"
 #include "profile.hpp"
 #include "stream.hpp"
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rows_mfma(PrefillArgs a) {
   int u, id;  // u counts (unit, query head) pairs: with grouped-query attention a unit has a.group heads
   if (!locate_heads(a.units, a.group, a.pairs * a.ksplit, u, id)) return;
   const int seg = id % a.ksplit, pair_id = id / a.ksplit;  // which share of the keys, which blocks of queries
-  float* const lse_out = seg == 0 ? a.lse : a.acc;  // second share: see merge_key_shares (group = 1 only)
+  float* const lse_out = a.lse_of_share(seg);  // see merge_key_shares
   const int uk = u / a.group;  // the unit: its keys and its length
   const int len = a.len[uk];
   const int lane = threadIdx.x & (kWave - 1);
@@ -343,8 +344,7 @@ __global__ __launch_bounds__(256, 2) void prefill_columns_mfma(PrefillArgs a) {
   int u, id;
   if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;  // which share of the queries, which blocks of keys
-  float* const out1 = seg == 0 ? a.acc : reinterpret_cast<float*>(a.var_key);    // second share: see sum_query_shares
-  float* const out2 = seg == 0 ? a.acc2 : reinterpret_cast<float*>(a.mas_key);
+  float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int len = a.len[u];
   const int lane = threadIdx.x & (kWave - 1);
   const int half = lane >> 5;
@@ -605,8 +605,7 @@ __global__ __launch_bounds__(WAVES * kWave) void prefill_columns_gqa_mfma(Prefil
   int u, id;
   if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;  // which share of the queries, which blocks of keys
-  float* const out1 = seg == 0 ? a.acc : reinterpret_cast<float*>(a.var_key);    // second share: see sum_query_shares
-  float* const out2 = seg == 0 ? a.acc2 : reinterpret_cast<float*>(a.mas_key);
+  float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int G = a.group, HP = (G + 1) / 2;  // head pairs per block of 32 queries
   const float inv_heads = 1.0f / static_cast<float>(G);
   const int len = a.len[u];
@@ -733,8 +732,7 @@ __global__ __launch_bounds__(WAVES * kWave) void prefill_columns_gqa_pow2_mfma(P
   int u, id;
   if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;  // which share of the queries, which blocks of keys
-  float* const out1 = seg == 0 ? a.acc : reinterpret_cast<float*>(a.var_key);    // second share: see sum_query_shares
-  float* const out2 = seg == 0 ? a.acc2 : reinterpret_cast<float*>(a.mas_key);
+  float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int len = a.len[u];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int half = lane >> 5;
@@ -838,14 +836,12 @@ __global__ __launch_bounds__(256, 2) void prefill_columns_gqa_ring(PrefillArgs a
   constexpr int QT = GR::kPerTile, QS = GR::kPerSub;
   constexpr int NS = 4;          // ring stages
   constexpr int kLseStages = 8;  // see prefill_columns_mfma
-  static_assert(G == 2 || G == 4 || G == 8 || G == 16, "the heads of a position fill whole pairs of registers");
   __shared__ __attribute__((aligned(1024))) char ring[NS * kRingTileBytes];
   __shared__ __attribute__((aligned(256))) float lse_s[kLseStages][4][kTile];  // [stage][wave][row of the tile]
   int u, id;
   if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;
-  float* const out1 = seg == 0 ? a.acc : reinterpret_cast<float*>(a.var_key);    // second share: see sum_query_shares
-  float* const out2 = seg == 0 ? a.acc2 : reinterpret_cast<float*>(a.mas_key);
+  float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int len = a.len[u];
   const int lane = threadIdx.x & (kWave - 1);
   const int half = lane >> 5;
@@ -977,14 +973,26 @@ __global__ __launch_bounds__(256, 2) void prefill_columns_gqa_ring(PrefillArgs a
         float& hs = g == 0 ? ha : hc;
         float& sum1 = g == 0 ? s1a : s1b;
         float& sum2 = g == 0 ? s2a : s2b;
-        const float pa = fast_exp2(fmaf(y[r], sc, -comp(lv[r >> 2], r & 3)));
-        const float pb = fast_exp2(fmaf(y[r + 1], sc, -comp(lv[r >> 2], (r & 3) + 1)));
-        if (r % G == 0) hs = pa + pb;
-        else hs += pa + pb;
-        if ((r + 2) % G == 0) {  // the position's last two heads
+        auto add_mean = [&]() {  // of the position whose last head has been added
           const float pbar = hs * kInvG;
           sum1 += pbar;
           sum2 = fmaf(pbar, pbar, sum2);
+        };
+        auto prob = [&](int i) { return fast_exp2(fmaf(y[i], sc, -comp(lv[i >> 2], i & 3))); };
+        if constexpr (G % 2 == 0) {
+          if (r >= GR::kUsed) return;
+          const float pa = prob(r), pb = prob(r + 1);
+          if (r % G == 0) hs = pa + pb;
+          else hs += pa + pb;
+          if ((r + 2) % G == 0) add_mean();
+        } else {
+#pragma unroll
+          for (int i = r; i < r + 2; ++i) {
+            if (i >= GR::kUsed) return;
+            if (i % G == 0) hs = prob(i);
+            else hs += prob(i);
+            if ((i + 1) % G == 0) add_mean();
+          }
         }
       };
       auto pin = [&]() { asm volatile("" : "+v"(s1a), "+v"(s2a), "+v"(s1b), "+v"(s2b), "+v"(ha), "+v"(hc)); };
@@ -1025,29 +1033,44 @@ __global__ __launch_bounds__(256, 2) void prefill_columns_gqa_ring(PrefillArgs a
   }
 }
 
-// Row pass with few units: the keys of every block of queries are shared by two workgroups (PrefillArgs::ksplit = 2);
-// the second one leaves its log-sum-exp in the plane the column pass will overwrite later, and this kernel merges
-// the two: log2(2^a + 2^b).
+// Row pass with few units: the keys of every block of queries are shared by several workgroups (PrefillArgs::ksplit); all but
+// the first leave their log-sum-exp in planes that the column pass will overwrite later, and this kernel merges them in order:
+// log2(2^a + 2^b + ...).
 __global__ __launch_bounds__(256) void merge_key_shares(PrefillArgs a) {
-  const int u = blockIdx.y;
+  const int u = blockIdx.y;  // (unit, query head)
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.len[u]) return;
+  if (i >= a.len[u / a.group]) return;
   const size_t at = static_cast<size_t>(u) * a.L_max + i;
-  const float x = a.lse[at], y = a.acc[at];
-  const float top = fmaxf(x, y);
-  if (top > -INFINITY) a.lse[at] = top + log2f(fast_exp2(x - top) + fast_exp2(y - top));
+  float x[kMaxKeyShares];
+  float top = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < kMaxKeyShares; ++s) {
+    x[s] = s < a.ksplit ? a.lse_of_share(s)[at] : -INFINITY;
+    top = fmaxf(top, x[s]);
+  }
+  if (top > -INFINITY) {
+    float sum = 0.0f;
+#pragma unroll
+    for (int s = 0; s < kMaxKeyShares; ++s) sum += s < a.ksplit ? fast_exp2(x[s] - top) : 0.0f;
+    a.lse[at] = top + log2f(sum);
+  }
 }
 
-// With few units the queries of every block of keys are shared by two workgroups (PrefillArgs::qsplit = 2), so that
-// the chip has enough of them; the second one leaves its sums in the planes that the selection will later use for
-// its ranking keys, and this kernel adds them to the first one's: a fixed order, the same bits every run.
+// With few units the queries of every block of keys are shared by several workgroups (PrefillArgs::qsplit), so that the chip has
+// enough of them; each leaves its sums in planes of its own (PrefillArgs::sums_of), and this kernel adds them to the first one's:
+// a fixed order, the same bits every run.
 __global__ __launch_bounds__(256) void sum_query_shares(PrefillArgs a) {
   const int u = blockIdx.y;
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= a.len[u]) return;
   const size_t i = static_cast<size_t>(u) * a.L_max + j;
-  a.acc[i] += reinterpret_cast<const float*>(a.var_key)[i];
-  a.acc2[i] += reinterpret_cast<const float*>(a.mas_key)[i];
+  float s1 = a.acc[i], s2 = a.acc2[i];
+  for (int s = 1; s < a.qsplit; ++s) {
+    s1 += a.sums_of(s, 0)[i];
+    s2 += a.sums_of(s, 1)[i];
+  }
+  a.acc[i] = s1;
+  a.acc2[i] = s2;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1381,14 +1404,6 @@ __global__ __launch_bounds__(256, 2) void prefill_mix_probe(int tiles, float* si
   sink[static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x] = sum;
 }
 
-// Two workgroups per block of keys when one would leave the chip short of workgroups (fewer than four per compute
-// unit); ROCO_PREFILL_QSPLIT = 1 or 2 overrides.
-int columns_query_shares(const PrefillArgs& a, int pairs) {
-  const char* e = getenv("ROCO_PREFILL_QSPLIT");
-  if (e != nullptr && (e[0] == '1' || e[0] == '2')) return e[0] - '0';
-  return static_cast<long long>(a.units) * pairs < 1024 ? 2 : 1;
-}
-
 // Grouped column pass: the in-register head sum when the number of heads divides 16, else the general kernel.
 template <int WAVES>
 void launch_columns_grouped(const PrefillArgs& b, dim3 grid, hipStream_t s) {
@@ -1401,7 +1416,11 @@ void launch_columns_grouped(const PrefillArgs& b, dim3 grid, hipStream_t s) {
   if (ring_ok) {
     switch (b.group) {
       case 2: hipLaunchKernelGGL((prefill_columns_gqa_ring<2>), grid, block, 0, s, b); return;
+      case 3: hipLaunchKernelGGL((prefill_columns_gqa_ring<3>), grid, block, 0, s, b); return;
       case 4: hipLaunchKernelGGL((prefill_columns_gqa_ring<4>), grid, block, 0, s, b); return;
+      case 5: hipLaunchKernelGGL((prefill_columns_gqa_ring<5>), grid, block, 0, s, b); return;
+      case 6: hipLaunchKernelGGL((prefill_columns_gqa_ring<6>), grid, block, 0, s, b); return;
+      case 7: hipLaunchKernelGGL((prefill_columns_gqa_ring<7>), grid, block, 0, s, b); return;
       case 8: hipLaunchKernelGGL((prefill_columns_gqa_ring<8>), grid, block, 0, s, b); return;
       case 16: hipLaunchKernelGGL((prefill_columns_gqa_ring<16>), grid, block, 0, s, b); return;
       default: break;
@@ -1416,71 +1435,53 @@ void launch_columns_grouped(const PrefillArgs& b, dim3 grid, hipStream_t s) {
   }
 }
 
-template <int WAVES>
-hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
-  constexpr int kOwn = Shape<WAVES>::kOwn;
-  const int n_blocks = (a.L_max + kOwn - 1) / kOwn;
-  PrefillArgs b = a;
-  b.paired = a.paired >= 0 ? a.paired : 1;  // pairing measured faster than lock-step single blocks
-  b.pairs = b.paired ? (n_blocks + 1) / 2 : n_blocks;  // ids per unit
-  b.qsplit = columns_query_shares(a, b.pairs);
-  b.ksplit = a.group == 1 ? b.qsplit : 1;  // the second share's plane has no room for several heads
-  const dim3 grid(workgroup_ids(a.units, b.pairs * b.qsplit));
-  const dim3 rows_grid(workgroup_ids(a.units, a.group * b.pairs * b.ksplit));  // one id set per query head
-  if (!a.skip_rows) {
-    ProfScope ps(kProfPrefillRows, s);
-    hipLaunchKernelGGL(prefill_rows_mfma, rows_grid, dim3(WAVES * kWave), 0, s, b);
-    if (b.ksplit > 1)
-      launch_merge_key_shares(b, s);
-  }
-  {
-    ProfScope ps(kProfPrefillColumns, s);
-    if (a.group != 1) launch_columns_grouped<WAVES>(b, grid, s);
-    else if (a.pol.counts_above_average())
-      hipLaunchKernelGGL(prefill_columns_mfma<true>, grid, dim3(WAVES * kWave), 0, s, b);
-    else hipLaunchKernelGGL(prefill_columns_mfma<false>, grid, dim3(WAVES * kWave), 0, s, b);
-    if (b.qsplit > 1)
-      join_query_shares(a, s);
-  }
-  return hipGetLastError();
+// ROCO_PREFILL_QSPLIT (workgroups per block of rows), ROCO_PREFILL_PAIRED and ROCO_PREFILL_GQA_RING speak of the kernels of
+// this file: where one of them is set, both passes take these kernels (tests run them at every size).
+bool plan_override(const PrefillArgs& a, int most_split, PassPlan& plan) {
+  const char *q = getenv("ROCO_PREFILL_QSPLIT"), *ring = getenv("ROCO_PREFILL_GQA_RING");
+  if (q == nullptr && ring == nullptr && a.paired < 0) return false;
+  const int n_blocks = ceil_div(a.L_max, Shape<4>::kOwn);
+  int split = q != nullptr ? atoi(q) : static_cast<long long>(a.units) * ((n_blocks + 1) / 2) < 1024 ? 2 : 1;
+  split = split < 1 ? 1 : split > most_split ? most_split : split;
+  const int paired = a.paired >= 0 ? a.paired : 1;
+  plan = {true, 1, split, paired, paired ? (n_blocks + 1) / 2 : n_blocks};
+  return true;
 }
 
-// Rows pass that also writes O, followed by the ordinary columns pass.
-hipError_t launch_with_output(PrefillArgs& a, hipStream_t s) {
+void launch_rows(const PrefillArgs& a, hipStream_t s) {
+  PassPlan plan;
+  if (!plan_override(a, a.row_shares(), plan)) plan = plan_rows(kBF16, D, a.units, a.group, a.L_max, a.row_shares());
+  if (!plan.wide) return launch_prefill_rows_planes_wide(a, plan, s);
+  ProfScope ps(kProfPrefillRows, s);
   PrefillArgs b = a;
-  b.paired = 0;
-  b.pairs = (a.L_max + 127) / 128;  // workgroup ids per unit
-  {
-    ProfScope ps(kProfPrefillRows, s);
-    hipLaunchKernelGGL(prefill_rows_out_mfma, dim3(workgroup_ids(a.units, a.group * b.pairs)),
-                       dim3(256), 0, s, b);
-  }
-  constexpr int kOwn = Shape<4>::kOwn;
-  const int n_blocks = (a.L_max + kOwn - 1) / kOwn;
-  PrefillArgs c = a;
-  c.paired = 1;
-  c.pairs = (n_blocks + 1) / 2;
-  c.qsplit = columns_query_shares(a, c.pairs);
-  {
-    ProfScope ps(kProfPrefillColumns, s);
-    const dim3 cgrid(workgroup_ids(a.units, c.pairs * c.qsplit));
-    if (a.group != 1) launch_columns_grouped<4>(c, cgrid, s);
-    else if (a.pol.counts_above_average()) hipLaunchKernelGGL(prefill_columns_mfma<true>, cgrid, dim3(4 * kWave), 0, s, c);
-    else hipLaunchKernelGGL(prefill_columns_mfma<false>, cgrid, dim3(4 * kWave), 0, s, c);
-    if (c.qsplit > 1)
-      join_query_shares(a, s);
-  }
-  return hipGetLastError();
+  b.paired = plan.paired; b.pairs = plan.ids; b.ksplit = plan.split;
+  hipLaunchKernelGGL(prefill_rows_mfma, dim3(workgroup_ids(a.units, a.group * plan.ids * plan.split)), dim3(4 * kWave), 0, s, b);
+  if (plan.split > 1) launch_merge_key_shares(b, s);
+}
+
+void launch_columns(PrefillArgs& a, hipStream_t s) {
+  PassPlan plan;
+  if (!plan_override(a, a.shares, plan)) plan = plan_columns(kBF16, D, a.units, a.group, a.L_max, a.shares);
+  if (!plan.wide) return launch_prefill_columns_planes_wide(a, plan, s);
+  ProfScope ps(kProfPrefillColumns, s);
+  PrefillArgs b = a;
+  b.paired = plan.paired; b.pairs = plan.ids; b.qsplit = plan.split;
+  const dim3 grid(workgroup_ids(a.units, plan.ids * plan.split));
+  if (a.group != 1) launch_columns_grouped<4>(b, grid, s);
+  else if (a.pol.counts_above_average()) hipLaunchKernelGGL(prefill_columns_mfma<true>, grid, dim3(4 * kWave), 0, s, b);
+  else hipLaunchKernelGGL(prefill_columns_mfma<false>, grid, dim3(4 * kWave), 0, s, b);
+  join_query_shares(a, b, s);
 }
 
 }  // namespace
 
 void launch_merge_key_shares(const PrefillArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(merge_key_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(merge_key_shares, dim3((a.L_max + 255) / 256, static_cast<unsigned>(a.units) * a.group), dim3(256), 0, s, a);
 }
-void join_query_shares(PrefillArgs& a, hipStream_t s) {
-  if (selection_adds_shares(a)) a.two_shares = 1;
-  else hipLaunchKernelGGL(sum_query_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, a);
+void join_query_shares(PrefillArgs& a, const PrefillArgs& pass, hipStream_t s) {
+  if (pass.qsplit <= 1) return;
+  if (selection_adds_shares(a, pass.qsplit)) a.shares_to_add = pass.qsplit;
+  else hipLaunchKernelGGL(sum_query_shares, dim3((a.L_max + 255) / 256, a.units), dim3(256), 0, s, pass);
 }
 
 hipError_t launch_mfma_probe(int workgroups, int iters, int mode, float* sink, hipStream_t s) {
@@ -1497,10 +1498,17 @@ hipError_t launch_mfma_probe(int workgroups, int iters, int mode, float* sink, h
 }
 
 hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s) {
-  if (a.O != nullptr) return launch_with_output(a, s);
-  // 256 owned rows per workgroup (512 halved the streamed traffic but left one workgroup per compute unit, all of
-  // whose waves wait at the same barriers: measured slower on the serving workload).
-  return launch_t<4>(a, s);
+  if (a.O != nullptr) {
+    ProfScope ps(kProfPrefillRows, s);
+    PrefillArgs b = a;
+    b.paired = 0;
+    b.pairs = ceil_div(a.L_max, 128);
+    hipLaunchKernelGGL(prefill_rows_out_mfma, dim3(workgroup_ids(a.units, a.group * b.pairs)), dim3(256), 0, s, b);
+  } else if (!a.skip_rows) {
+    launch_rows(a, s);
+  }
+  launch_columns(a, s);
+  return hipGetLastError();
 }
 
 }  // namespace roco

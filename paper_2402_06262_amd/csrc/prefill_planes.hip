@@ -30,6 +30,7 @@
 // against a lazily raised one the unnormalised output may be 2^16 times larger, and overflow where the output does not.
 #include "kernels.hpp"
 #include "mfma.hpp"
+#include "prefill_schedule.hpp"
 #include "prefill_tiles.hpp"
 #include "profile.hpp"
 #include "stream.hpp"
@@ -133,14 +134,14 @@ template <int DT, int D, int ROWS> struct Pieces {
       w[i] = load16(base + static_cast<size_t>(row) * P::IN_ROW + (idx % P::CPR) * 16);
     }
   }
-  // Rows of a tile that holds TR / G query positions from `pos0` on for G heads (see GroupedRows), head h at base + h * stride.
+  // Rows of a tile that holds the query positions from `pos0` on for G heads (see GroupedRows), head h at base + h * stride.
   template <int G> __device__ __forceinline__ void load_heads(const char* base, size_t stride, int pos0, int last_pos) {
 #pragma unroll
     for (int i = 0; i < P::PIECES; ++i) {
       const int idx = threadIdx.x + kThreads * i;
       int ql, h;
-      GroupedRows<G>::locate(idx / P::CPR & 63, ql, h);
-      const int pos = min(pos0 + ql + (idx / P::CPR >> 6) * (64 / G), last_pos);
+      GroupedRows<G>::locate(idx / P::CPR, ql, h);
+      const int pos = min(pos0 + ql, last_pos);
       w[i] = load16(base + h * stride + static_cast<size_t>(pos) * P::IN_ROW + (idx % P::CPR) * 16);
     }
   }
@@ -297,25 +298,29 @@ __device__ __forceinline__ bool pick_block(bool paired, int pass, int pair_id, i
 
 // The four waves of a workgroup share its owned rows and the streamed tiles: PARTS = 1, every wave owns 32 rows of its own
 // and takes all sub-tiles of 32 streamed rows; PARTS = 2, waves w and w + 2 own the same 32 rows and take every other
-// sub-tile (twice the workgroups of half the length for the same rows), and their results meet in LDS at the end.
+// sub-tile (twice the workgroups of half the length for the same rows); PARTS = 4, all of them own the same 32 rows and take
+// one sub-tile in four.  Their results meet in LDS at the end.
 template <int PARTS> struct Shares {
   static constexpr int GROUPS = 4 / PARTS;
   static constexpr int kOwn = 32 * GROUPS;
 };
+// Rows of a streamed tile: every part has a sub-tile of its own.
+template <int DT, int D, int PARTS> constexpr int kTileRows = kRows<DT, D> > 32 * PARTS ? kRows<DT, D> : 32 * PARTS;
+template <int DT, int D, int PARTS> constexpr int kTileRowsSmall = kRowsSmall<DT, D> > 32 * PARTS ? kRowsSmall<DT, D> : 32 * PARTS;
 
 // ------------------------------------------------------------------------------------------------
 // pass 1: lse[i] = log2 sum_{j<=i} 2^(t_ij)
 template <int DT, int D, int PARTS>
-__global__ __launch_bounds__(kThreads, DT == kBF16 ? 4 : D == 64 ? 3 : 2) void prefill_rows_planes(PrefillArgs a) {
-  using P = Planes<DT, D, kRows<DT, D>>;
+__global__ __launch_bounds__(kThreads, D == 128 ? 2 : DT == kBF16 ? 4 : 3) void prefill_rows_planes(PrefillArgs a) {
+  using P = Planes<DT, D, kTileRows<DT, D, PARTS>>;
   constexpr int kOwn = Shares<PARTS>::kOwn, GROUPS = Shares<PARTS>::GROUPS;
   __shared__ __attribute__((aligned(16))) char tiles[2][P::TILE];
-  __shared__ float other[2][PARTS == 2 ? kOwn : 1];
+  __shared__ float other[2][PARTS > 1 ? PARTS - 1 : 1][PARTS > 1 ? kOwn : 1];
   __shared__ int odd_s[2];  // number of the last tile in this buffer that holds values of no exact planes (fp32)
   int u, id;
   if (!locate_heads(a.units, a.group, a.pairs * a.ksplit, u, id)) return;
   const int seg = id % a.ksplit, pair_id = id / a.ksplit;
-  float* const lse_out = seg == 0 ? a.lse : a.acc;  // second share: see merge_key_shares (group = 1 only)
+  float* const lse_out = a.lse_of_share(seg);  // see merge_key_shares
   const int uk = u / a.group;
   const int len = a.len[uk];
   const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
@@ -376,10 +381,13 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? 4 : D == 64 ? 3 : 2) void p
     };
     const float mo = __shfl_xor(m, 32, kWave), lo = __shfl_xor(l, 32, kWave);
     join(mo, lo);
-    if constexpr (PARTS == 2) {
-      if (part == 1 && half == 0) { other[0][32 * grp + lane] = m; other[1][32 * grp + lane] = l; }
+    if constexpr (PARTS > 1) {
+      if (part > 0 && half == 0) { other[0][part - 1][32 * grp + lane] = m; other[1][part - 1][32 * grp + lane] = l; }
       __syncthreads();
-      if (part == 0 && half == 0) join(other[0][32 * grp + lane], other[1][32 * grp + lane]);
+      if (part == 0 && half == 0) {
+#pragma unroll
+        for (int o = 0; o < PARTS - 1; ++o) join(other[0][o][32 * grp + lane], other[1][o][32 * grp + lane]);
+      }
     }
     if (part == 0 && half == 0 && qi < len) lse_out[ubase + qi] = m + log2f(l);  // -inf for a share without keys
   }
@@ -389,22 +397,25 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? 4 : D == 64 ? 3 : 2) void p
 // pass 2: Acc[j] = sum_i Pbar[i,j], Acc2[j] = sum_i Pbar[i,j]^2 (or the count of above-average queries), Pbar the mean over
 // the unit's query heads.  A workgroup owns a block of keys and walks the query tiles from the end of the prompt down to
 // its own keys; grouped, a tile position is taken head by head and the sum over the heads stays in the lane's registers.
-// HEADS: 1, or 0 for any group (head by head), or 2, 4, 8, 16 for that group with the head sum inside a result tile.
+// HEADS: 1, or 0 for any group (head by head), or 2 to 8 or 16 for that group with the head sum inside a result tile.
+// Waves per SIMD (fp32 / 128 with two parts: two tiles take 96 KiB).
 template <int DT, int D, int PARTS, int HEADS>
-__global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D == 64 && HEADS != 0 ? 3 : 2) void prefill_columns_planes(PrefillArgs a) {
-  using P = Planes<DT, D, HEADS == 0 ? kRowsSmall<DT, D> : kRows<DT, D>>;
+constexpr int kColumnWaves = DT == kF32 && D == 128 && PARTS > 1 ? 1 : D == 128 ? 2 : DT == kBF16 ? (HEADS != 0 ? 4 : 3) : HEADS != 0 ? 3 : 2;
+template <int DT, int D, int PARTS, int HEADS>
+__global__ __launch_bounds__(kThreads, (kColumnWaves<DT, D, PARTS, HEADS>)) void prefill_columns_planes(PrefillArgs a) {
+  using P = Planes<DT, D, HEADS == 0 ? kTileRowsSmall<DT, D, PARTS> : kTileRows<DT, D, PARTS>>;
   constexpr int kOwn = Shares<PARTS>::kOwn, GROUPS = Shares<PARTS>::GROUPS, NSUB = P::SUBS / PARTS;
   constexpr int PER = HEADS > 1 ? HEADS : 1;               // heads per query position of a tile
-  constexpr int QT = P::TR / PER, QS = 32 / PER;           // query positions per tile and per sub-tile
+  constexpr int QS = HEADS > 1 ? GroupedRows<PER>::kPerSub : 32;  // query positions per sub-tile
+  constexpr int QT = P::SUBS * QS;                                // ... and per tile
   __shared__ __attribute__((aligned(16))) char tiles[2][P::TILE];
   __shared__ __attribute__((aligned(16))) float lse_s[2][P::TR], rinv_s[2][P::TR];  // rinv: 1 / (tokens the query attended)
-  __shared__ float other[2][PARTS == 2 ? kOwn : 1];
+  __shared__ float other[2][PARTS > 1 ? PARTS - 1 : 1][PARTS > 1 ? kOwn : 1];
   __shared__ int odd_s[2];  // see prefill_rows_planes
   int u, id;
   if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;
-  float* const out1 = seg == 0 ? a.acc : reinterpret_cast<float*>(a.var_key);  // second share: see sum_query_shares
-  float* const out2 = seg == 0 ? a.acc2 : reinterpret_cast<float*>(a.mas_key);
+  float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int G = HEADS != 1 ? a.group : 1;
   const float inv_heads = 1.0f / static_cast<float>(G);
   const bool count = a.pol.counts_above_average();
@@ -439,8 +450,7 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
       int lse_h = h, lse_q = threadIdx.x;
       if constexpr (HEADS > 1) {
         st.template load_heads<PER>(Qu, static_cast<size_t>(a.L_max) * P::IN_ROW, t * QT, len - 1);
-        GroupedRows<PER>::locate(threadIdx.x & 63, lse_q, lse_h);
-        lse_q += (static_cast<int>(threadIdx.x) >> 6) * (64 / PER);
+        GroupedRows<PER>::locate(threadIdx.x, lse_q, lse_h);
       } else {
         st.load(Qu + static_cast<size_t>(h) * a.L_max * P::IN_ROW, t * QT, len - 1);
       }
@@ -528,10 +538,13 @@ __global__ __launch_bounds__(kThreads, DT == kBF16 ? (HEADS != 0 ? 4 : 3) : D ==
     }
     s1 += __shfl_xor(s1, 32, kWave);
     s2 += __shfl_xor(s2, 32, kWave);
-    if constexpr (PARTS == 2) {
-      if (part == 1 && half == 0) { other[0][32 * grp + lane] = s1; other[1][32 * grp + lane] = s2; }
+    if constexpr (PARTS > 1) {
+      if (part > 0 && half == 0) { other[0][part - 1][32 * grp + lane] = s1; other[1][part - 1][32 * grp + lane] = s2; }
       __syncthreads();
-      if (part == 0 && half == 0) { s1 += other[0][32 * grp + lane]; s2 += other[1][32 * grp + lane]; }
+      if (part == 0 && half == 0) {
+#pragma unroll
+        for (int o = 0; o < PARTS - 1; ++o) { s1 += other[0][o][32 * grp + lane]; s2 += other[1][o][32 * grp + lane]; }
+      }
     }
     if (part == 0 && half == 0 && kj < len) { out1[ubase + kj] = s1; out2[ubase + kj] = s2; }
   }
@@ -556,13 +569,13 @@ template <int DT> __device__ __forceinline__ void load_values(const char* row, i
 // own and are added to the output once, so an output component sees one rounding per 32 keys.
 template <int DT, int D, int PARTS>
 __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void prefill_rows_out_planes(PrefillArgs a) {
-  using P = Planes<DT, D, kRowsSmall<DT, D>>;
+  using P = Planes<DT, D, kTileRowsSmall<DT, D, PARTS>>;
   constexpr int kOwn = Shares<PARTS>::kOwn, GROUPS = Shares<PARTS>::GROUPS;
-  constexpr int NBUF = DT == kBF16 ? 2 : 1;  // fp32: one tile of K and V planes fills what two workgroups leave each other
+  constexpr int NBUF = DT == kBF16 && PARTS < 4 ? 2 : 1;  // else one tile of K and V planes fills what two workgroups leave each other
   constexpr int DB = D / 32;
   __shared__ __attribute__((aligned(16))) char tilesK[NBUF][P::TILE];
   __shared__ __attribute__((aligned(16))) char tilesV[NBUF][P::TILEV];
-  __shared__ float other[2][PARTS == 2 ? GROUPS * kWave : 1];
+  __shared__ float other[2][PARTS > 1 ? 2 * kWave : 1];
   __shared__ int odd_s[NBUF], odd_v[NBUF];  // see prefill_rows_planes
   int u, blk_id;
   if (!locate_heads(a.units, a.group, a.pairs, u, blk_id)) return;
@@ -751,21 +764,25 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
     }
   }
   l += __shfl_xor(l, 32, kWave);  // each lane half summed different keys of the same query
-  if constexpr (PARTS == 2) {  // waves w and w + 2 hold the sums over every other 32 keys of the same queries
-    static_assert(NBUF * P::TILE >= GROUPS * DB * 16 * kWave * 4, "the partner's output fits the K tiles");
-    float* const mo = reinterpret_cast<float*>(&tilesK[0][0]) + grp * (DB * 16 * kWave) + lane;
-    __syncthreads();  // everybody is done with the tiles
-    if (part == 1) {
+  // The parts hold sums over different keys of the same queries: the upper half of the waves hands its own to the lower half,
+  // until one wave per group is left.
+#pragma unroll
+  for (int left = PARTS / 2; left > 0; left /= 2) {
+    static_assert(PARTS == 1 || NBUF * P::TILE >= 2 * DB * 16 * kWave * 4, "the partners' outputs fit the K tiles");
+    const int to = wave % (GROUPS * left);  // the wave that takes the sums of wave to + GROUPS * left
+    float* const mo = reinterpret_cast<float*>(&tilesK[0][0]) + to * (DB * 16 * kWave) + lane;
+    __syncthreads();  // everybody is done with the tiles, or with the sums handed over before
+    if (part >= left && part < 2 * left) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mo[(db * 16 + r) * kWave] = o[db][r];
-      other[0][grp * kWave + lane] = m;
-      other[1][grp * kWave + lane] = l;
+      other[0][to * kWave + lane] = m;
+      other[1][to * kWave + lane] = l;
     }
     __syncthreads();
-    if (part == 1) return;
-    const float m1 = other[0][grp * kWave + lane], l1 = other[1][grp * kWave + lane];
+    if (part >= left) continue;
+    const float m1 = other[0][to * kWave + lane], l1 = other[1][to * kWave + lane];
     const float M = fmaxf(m, m1);
     // (a part that attended nothing has no sums; a weight that underflows still meets an infinite sum)
     const bool some0 = m > -INFINITY, some1 = m1 > -INFINITY;
@@ -778,7 +795,7 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
       for (int r = 0; r < 16; ++r)
         o[db][r] = (some0 ? o[db][r] * w0 : 0.0f) + (some1 ? mo[(db * 16 + r) * kWave] * w1 : 0.0f);
   }
-  if (qi < len) {
+  if (part == 0 && qi < len) {
     if (half == 0) a.lse[ubase + qi] = m + log2f(l);
     const float inv = 1.0f / l;
 #pragma unroll
@@ -799,36 +816,16 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
 }
 
 // ------------------------------------------------------------------------------------------------
-struct Launch { int pairs, paired, split, parts; };
-
-// Schedule of a pass over `streams` (unit, head) streams of up to L_max rows.  `target` workgroups fill the chip (all of
-// them resident); the base schedule has one per pair of a long and a short block of 128 owned rows.  Too few: the waves of
-// a workgroup share 64 rows (parts = 2), and / or two workgroups take half of a block's streamed tiles each (split = 2, where
-// the planes of the second share have room), and single blocks instead of pairs when even that leaves compute units idle.
-Launch schedule(long long streams, int L_max, int target, bool may_part, bool may_split, bool part_first) {
-  const int n128 = (L_max + 127) / 128;
-  const long long base = streams * ((n128 + 1) / 2);
-  Launch l = {0, 1, 1, 1};
-  if (base < target) {
-    const bool both = 2 * base < target;
-    if (may_part && (part_first || both || !may_split)) l.parts = 2;
-    if (may_split && (!part_first || both || !may_part) && n128 > 1) l.split = 2;
-  }
-  const int n_blocks = l.parts == 2 ? (L_max + 63) / 64 : n128;
-  l.paired = streams * ((n_blocks + 1) / 2) * l.split >= 256 ? 1 : 0;
-  l.pairs = l.paired ? (n_blocks + 1) / 2 : n_blocks;
-  return l;
-}
-unsigned ids(const PrefillArgs& a, int heads, const Launch& l) {
-  return mfma::workgroup_ids(a.units, heads * l.pairs * l.split);
-}
-
 template <int DT, int D, int PARTS>
-void launch_columns(const PrefillArgs& b, unsigned n, hipStream_t s) {
+void launch_columns_of_group(const PrefillArgs& b, unsigned n, hipStream_t s) {
   switch (b.group) {
     case 1: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 1>), dim3(n), dim3(kThreads), 0, s, b); break;
     case 2: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 2>), dim3(n), dim3(kThreads), 0, s, b); break;
+    case 3: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 3>), dim3(n), dim3(kThreads), 0, s, b); break;
     case 4: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 4>), dim3(n), dim3(kThreads), 0, s, b); break;
+    case 5: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 5>), dim3(n), dim3(kThreads), 0, s, b); break;
+    case 6: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 6>), dim3(n), dim3(kThreads), 0, s, b); break;
+    case 7: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 7>), dim3(n), dim3(kThreads), 0, s, b); break;
     case 8: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 8>), dim3(n), dim3(kThreads), 0, s, b); break;
     case 16: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 16>), dim3(n), dim3(kThreads), 0, s, b); break;
     default: hipLaunchKernelGGL((prefill_columns_planes<DT, D, PARTS, 0>), dim3(n), dim3(kThreads), 0, s, b); break;
@@ -836,39 +833,63 @@ void launch_columns(const PrefillArgs& b, unsigned n, hipStream_t s) {
 }
 
 template <int DT, int D>
-hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
-  constexpr int kShared = kRows<DT, D> > 32 ? 2 : 1;  // a tile of one sub-tile has nothing to share
-  constexpr int kTarget = DT == kBF16 ? 1024 : 512;
-  constexpr bool kPartFirst = DT == kBF16;
-  if (!a.skip_rows && prefill_rows_are_tiny(a, DT == kF32, D)) {
-    launch_prefill_rows_simple(DT, D, a, s);
-  } else if (!a.skip_rows) {
-    ProfScope ps(kProfPrefillRows, s);
-    PrefillArgs b = a;
-    if (a.O != nullptr) {
-      // Single blocks; with head_dim 64 two waves share 32 rows whatever the number of units.  Whole call, us, shared against a
-      // row block per wave: bf16 4 x 1024 tokens 44 / 54, 32 x 2048 117 / 134, 256 x 2048 589 / 619, but 1024 x 256 126 / 116;
-      // fp32 4 x 1024 78 / 97, 128 x 1024 253 / 255, but 256 x 1024 478 / 455, 256 x 2048 1588 / 1433 and 1024 x 256 246 / 206.
-      constexpr int kOwn = Shares<kShared>::kOwn;
-      b.pairs = (a.L_max + kOwn - 1) / kOwn; b.paired = 0; b.ksplit = 1;
-      const unsigned n = ids(a, a.group, {b.pairs, 0, 1, kShared});
-      hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, kShared>), dim3(n), dim3(kThreads), 0, s, b);
-    } else {
-      const Launch l = schedule(static_cast<long long>(a.units) * a.group, a.L_max, kTarget, kShared == 2, a.group == 1, kPartFirst);
-      b.pairs = l.pairs; b.paired = l.paired; b.ksplit = l.split;
-      const dim3 grid(ids(a, a.group, l));
-      if (l.parts == 2) hipLaunchKernelGGL((prefill_rows_planes<DT, D, kShared>), grid, dim3(kThreads), 0, s, b);
-      else hipLaunchKernelGGL((prefill_rows_planes<DT, D, 1>), grid, dim3(kThreads), 0, s, b);
-      if (l.split > 1) launch_merge_key_shares(b, s);
-    }
-  }
-  ProfScope ps(kProfPrefillColumns, s);
-  const Launch l = schedule(a.units, a.L_max, kTarget, kShared == 2, true, kPartFirst);
+void launch_rows(const PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
+  ProfScope ps(kProfPrefillRows, s);
   PrefillArgs b = a;
-  b.pairs = l.pairs; b.paired = l.paired; b.qsplit = l.split;
-  if (l.parts == 2) launch_columns<DT, D, kShared>(b, ids(a, 1, l), s);
-  else launch_columns<DT, D, 1>(b, ids(a, 1, l), s);
-  if (l.split > 1) join_query_shares(a, s);
+  b.pairs = plan.ids; b.paired = plan.paired; b.ksplit = plan.split;
+  const dim3 grid(mfma::workgroup_ids(a.units, a.group * plan.ids * plan.split));
+  switch (plan.parts) {
+    case 1: hipLaunchKernelGGL((prefill_rows_planes<DT, D, 1>), grid, dim3(kThreads), 0, s, b); break;
+    case 2: if constexpr (D == 64 || DT == kBF16) hipLaunchKernelGGL((prefill_rows_planes<DT, D, 2>), grid, dim3(kThreads), 0, s, b); break;
+    default: if constexpr (DT == kBF16) hipLaunchKernelGGL((prefill_rows_planes<DT, D, 4>), grid, dim3(kThreads), 0, s, b); break;
+  }
+  if (plan.split > 1) launch_merge_key_shares(b, s);
+}
+
+// The row pass with output takes single blocks.  Whole call, us, 64 owned rows (two waves share 32) against 128: bf16 / 64
+// 4 x 1024 tokens 44 / 54, 32 x 2048 117 / 134, 256 x 2048 589 / 619, but 1024 x 256 126 / 116; fp32 / 64 4 x 1024 78 / 97,
+// 128 x 1024 253 / 255, but 256 x 1024 478 / 455, 256 x 2048 1588 / 1433 and 1024 x 256 246 / 206.  Row pass, us: 32 owned rows
+// against 64 for bf16 / 64 1 x 4575 60 / 86, but 16 streams x 4396 194 / 163; 64 against 128 for fp32 / 128 7 x 2578 172 / 247,
+// but with more than one of its workgroups, which do not share a compute unit, 108 x 129 42 / 27.
+template <int DT, int D>
+void launch_rows_out(const PrefillArgs& a, hipStream_t s) {
+  ProfScope ps(kProfPrefillRows, s);
+  PrefillArgs b = a;
+  b.paired = 0; b.ksplit = 1;
+  const long long streams = static_cast<long long>(a.units) * a.group;
+  int parts = D == 64 ? 2 : streams * ceil_div(a.L_max, 64) <= 300 ? 2 : 1;
+  if (DT == kBF16 && streams * ceil_div(a.L_max, 64) < 512 && a.L_max > 384) parts = 4;
+  b.pairs = ceil_div(a.L_max, 128 / parts);
+  const dim3 grid(mfma::workgroup_ids(a.units, a.group * b.pairs));
+  switch (parts) {
+    case 1: if constexpr (D == 128) hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, 1>), grid, dim3(kThreads), 0, s, b); break;
+    case 2: hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, 2>), grid, dim3(kThreads), 0, s, b); break;
+    default: if constexpr (DT == kBF16) hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, 4>), grid, dim3(kThreads), 0, s, b); break;
+  }
+}
+
+template <int DT, int D>
+void launch_columns(PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
+  ProfScope ps(kProfPrefillColumns, s);
+  PrefillArgs b = a;
+  b.pairs = plan.ids; b.paired = plan.paired; b.qsplit = plan.split;
+  const unsigned n = mfma::workgroup_ids(a.units, plan.ids * plan.split);
+  switch (plan.parts) {
+    case 1: launch_columns_of_group<DT, D, 1>(b, n, s); break;
+    case 2: launch_columns_of_group<DT, D, 2>(b, n, s); break;
+    default: if constexpr (DT == kBF16) launch_columns_of_group<DT, D, 4>(b, n, s); break;
+  }
+  join_query_shares(a, b, s);
+}
+
+template <int DT, int D>
+hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
+  if (!a.skip_rows) {
+    if (prefill_rows_are_tiny(a, DT == kF32, D)) launch_prefill_rows_simple(DT, D, a, s);
+    else if (a.O != nullptr) launch_rows_out<DT, D>(a, s);
+    else launch_rows<DT, D>(a, plan_rows(DT, D, a.units, a.group, a.L_max, a.row_shares()), s);
+  }
+  launch_columns<DT, D>(a, plan_columns(DT, D, a.units, a.group, a.L_max, a.shares), s);
   return hipGetLastError();
 }
 
@@ -880,5 +901,8 @@ hipError_t launch_prefill_attention_planes(int dtype, int head_dim, PrefillArgs&
   if (dtype == kBF16 && head_dim == 64) return launch_t<kBF16, 64>(a, s);
   return hipErrorInvalidValue;
 }
+// bf16 / 128: the passes for which their plan does not ask for the kernels of prefill_mfma.hip
+void launch_prefill_rows_planes_wide(const PrefillArgs& a, const PassPlan& plan, hipStream_t s) { launch_rows<kBF16, 128>(a, plan, s); }
+void launch_prefill_columns_planes_wide(PrefillArgs& a, const PassPlan& plan, hipStream_t s) { launch_columns<kBF16, 128>(a, plan, s); }
 
 }  // namespace roco

@@ -10,9 +10,9 @@ namespace mfma {
 // Workgroup -> (unit, block-pair) mapping.  The hardware hands consecutive workgroup ids to the 8 accelerator
 // dies in turn and each die has its own L2, so the workgroups of one unit (which all stream the same K or Q
 // tiles, at about the same time) are given ids that are congruent modulo 8: they land on one die and all but
-// the first fetch of a tile hit its L2.  That holds for the units that fill all dies evenly, units / 8 * 8 of them; the
-// workgroups of the up to seven units left over are dealt to the dies in turn, since whole units would leave dies without
-// work (whole units on whole dies: 2 units x 8 heads x 4396 tokens of bf16 / 64 with output took 640 us, 3 x 8 x 2578 of
+// the first fetch of a tile hit its L2.  That holds for the units that fill all dies evenly, units / 8 * 8 of them.  Whole units
+// would leave dies without work if the up to seven units left over were treated so: those share the dies out evenly, four
+// units two dies each, two or six units four dies each, any other number all dies for every unit (whole units on whole dies: 2 units x 8 heads x 4396 tokens of bf16 / 64 with output took 640 us, 3 x 8 x 2578 of
 // fp32 / 64 679, 22 x 8 x 3323 of bf16 / 128 592; now 363, 458 and 558).  The grid is one-dimensional over
 // workgroup_ids(units, pairs) ids.
 __host__ __device__ inline unsigned workgroup_ids(int units, int pairs) {
@@ -27,8 +27,10 @@ __device__ __forceinline__ bool locate(int units, int pairs, int& unit, int& pai
     pair = seq % pairs;
     return true;
   }
-  const int k = lin - even * pairs;
-  unit = even + k / pairs;
+  const int rest = units & 7, groups = rest & -rest;  // of units and of dies: 1, 2 or 4
+  const int die = lin & 7, per = 8 / groups;          // dies of a group
+  const int k = (seq - (even >> 3) * pairs) * per + die / groups;  // among the workgroups of the die's group of units
+  unit = even + die % groups + groups * (k / pairs);
   pair = k % pairs;
   return unit < units;
 }
@@ -176,18 +178,20 @@ __device__ __forceinline__ void column_probs(const f32x16& s, const float* lse_t
   }
 }
 
-// Row order of a streamed tile that holds 64 / G query positions for all G heads of a group, G = 2, 4, 8 or 16: the heads
-// of a query land in G consecutive accumulator registers of a lane (register r of lane half hf holds row
-// 8 * (r / 4) + 4 * hf + r % 4 of a 32-row sub-tile; that row is given to query hf * 16 / G + r / G of the sub-tile, head
-// r % G), so the sum over the heads is a sum down a few registers of one result tile.
+// Row order of a streamed tile that holds 2 (16 / G) query positions per 32 rows for all G heads of a group, G <= 16: the
+// heads of a query land in G consecutive accumulator registers of a lane (register r of lane half hf holds row
+// 8 * (r / 4) + 4 * hf + r % 4 of a 32-row sub-tile; that row is given to query hf * (16 / G) + r / G of the sub-tile, head
+// r % G), so the sum over the heads is a sum down a few registers of one result tile.  Where G does not divide 16 the last
+// 16 % G registers of a lane repeat the row before them and are not looked at.
 template <int G> struct GroupedRows {
-  static constexpr int kPerHalf = 16 / G;      // queries per lane half in a 32-row sub-tile
-  static constexpr int kPerSub = 32 / G;       // query positions per sub-tile
-  static constexpr int kPerTile = 64 / G;      // query positions per 64-row tile
+  static constexpr int kPerHalf = 16 / G;         // queries per lane half in a 32-row sub-tile
+  static constexpr int kUsed = kPerHalf * G;      // registers of a lane that hold a score
+  static constexpr int kPerSub = 2 * kPerHalf;    // query positions per sub-tile
+  static constexpr int kPerTile = 2 * kPerSub;    // query positions per 64-row tile
   // LDS row of a tile -> local query position and head
   __device__ static void locate(int row, int& ql, int& h) {
     const int sub = row >> 5, rr = row & 31;
-    const int hf = (rr >> 2) & 1, r = 4 * (rr >> 3) + (rr & 3);
+    const int hf = (rr >> 2) & 1, reg = 4 * (rr >> 3) + (rr & 3), r = reg < kUsed ? reg : kUsed - 1;
     ql = sub * kPerSub + hf * kPerHalf + r / G;
     h = r % G;
   }
@@ -207,6 +211,7 @@ __device__ __forceinline__ void column_update_grouped(const f32x16& s, const flo
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = 4 * g4 + e;
+      if (r >= GroupedRows<G>::kUsed) continue;
       float x = fmaf(s[r], sc, -lv[e]);
       if (INTERIOR) {
         p[r] = fast_exp2(x);

@@ -25,7 +25,9 @@ constexpr int kGatherRows = 64;  // cache rows per gather workgroup
 // the three selections (scope, victims, first decode victim) share one copy of the search, loops over keys in LDS are not
 // unrolled, and where the keys are is a template parameter so that they are read with LDS instructions.
 // LDS: both keys of a token in LDS (2; up to 16384 tokens), the one of the scope (1; up to 32768), none (0).
-template <int LDS>
+// MANY: the column sums lie in more than two shares (LDS = 2).  They are added once, by the thread that will need the sums again
+// when it compacts, and left in the first one's planes; for two shares reading both again is faster.
+template <int LDS, bool MANY>
 __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) {
   constexpr int NT = kSelThreads;
   extern __shared__ uint32_t lds_keys[];  // [2][L_max] ranking keys when L_max <= kMaxDecodeBudgetLds
@@ -37,16 +39,26 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
   const int n = a.len[u];
   const size_t ubase = static_cast<size_t>(u) * a.L_max;
   // the column sums, in one or two shares
-  const bool two = LDS == 2 && a.two_shares != 0;
-  const float* const first1 = a.acc + ubase;
-  const float* const first2 = a.acc2 + ubase;
-  const float* const second1 = reinterpret_cast<const float*>(a.var_key) + ubase;
-  const float* const second2 = reinterpret_cast<const float*>(a.mas_key) + ubase;
+  const bool two = LDS == 2 && !MANY && a.shares_to_add == 2;
+  float* const first1 = a.acc + ubase;
+  float* const first2 = a.acc2 + ubase;
+  const float* const second1 = a.sums_of(1, 0) + ubase;
+  const float* const second2 = a.sums_of(1, 1) + ubase;
   auto sums = [&](int i) {
     float2 s = make_float2(first1[i], first2[i]);
     if (two) { s.x += second1[i]; s.y += second2[i]; }
     return s;
   };
+  if constexpr (MANY) {
+#pragma unroll 1
+    for (int i = tid; i < n; i += NT) {
+      float2 s = make_float2(first1[i], first2[i]);
+#pragma unroll 4
+      for (int k = 1; k < a.shares_to_add; ++k) { s.x += a.sums_of(k, 0)[ubase + i]; s.y += a.sums_of(k, 1)[ubase + i]; }
+      first1[i] = s.x;
+      first2[i] = s.y;
+    }
+  }
   // every radix pass reads every key: in LDS they cost a fraction of a trip to the L2 each
   uint32_t* const var_key = LDS > 0 ? lds_keys : a.var_key + ubase;
   uint32_t* const mas_key = LDS == 2 ? lds_keys + a.L_max : a.mas_key + ubase;
@@ -271,14 +283,15 @@ hipError_t launch_prefill_select_compact(int dtype, int head_dim, const PrefillA
     ProfScope ps(kProfPrefillSelect, s);
     const size_t key_lds = key_lds_bytes(a.L_max);
     if (key_lds != 0) {
-      if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<2>), key_lds)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(prefill_select<2>, dim3(a.units), dim3(kSelThreads), key_lds, s, a);
+      const auto kernel = a.shares_to_add > 2 ? prefill_select<2, true> : prefill_select<2, false>;
+      if (!allow_key_lds(reinterpret_cast<const void*>(kernel), key_lds)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(kernel, dim3(a.units), dim3(kSelThreads), key_lds, s, a);
     } else if (a.L_max <= 2 * kMaxDecodeBudgetLds) {  // one key per token still fits (40 units x 32768 tokens: 125 us against 200)
       const size_t one = static_cast<size_t>(a.L_max) * sizeof(uint32_t);
-      if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<1>), one)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(prefill_select<1>, dim3(a.units), dim3(kSelThreads), one, s, a);
+      if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<1, false>), one)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((prefill_select<1, false>), dim3(a.units), dim3(kSelThreads), one, s, a);
     } else {
-      hipLaunchKernelGGL(prefill_select<0>, dim3(a.units), dim3(kSelThreads), 0, s, a);
+      hipLaunchKernelGGL((prefill_select<0, false>), dim3(a.units), dim3(kSelThreads), 0, s, a);
     }
   }
   ProfScope ps(kProfPrefillGather, s);

@@ -1,7 +1,9 @@
-"""Prompts of few units: the workgroups of the units that do not fill all dies evenly are dealt to the dies one by one.  Every
-form and both passes, with and without output, against the vector-ALU passes (one wave per query, per key) on the same inputs."""
+"""Prompts of few units: the workgroups of the units that do not fill all dies evenly are dealt to the dies one by one, the waves
+of a workgroup share its rows and several workgroups share a block's tiles.  Every form and both passes, with and without
+output, against the vector-ALU passes (one wave per query, per key) on the same inputs."""
 import numpy as np
 import pytest
+import torch
 
 import test_gpu_parity as TP
 from inputs import round_to_bf16
@@ -43,3 +45,72 @@ def test_units_left_over_by_the_dies(monkeypatch, dtype, d, units, group, L):
     lens = [L - (7 * u) % (L // 3) for u in range(units)]
     for want_out in (False, True):
         _both_paths(monkeypatch, dtype, d, units, group, L, lens, window=24 if units == 7 else 0, want_out=want_out)
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+@pytest.mark.parametrize("units,group,L", [(1, 1, 2100), (2, 8, 600), (1, 3, 1300), (3, 5, 400), (2, 6, 500), (1, 7, 700),
+                                           (1, 9, 300), (40, 2, 257), (70, 3, 200)])
+def test_shared_blocks_and_every_group(monkeypatch, dtype, d, units, group, L):
+    """Two to sixteen shares of a block's tiles, two or four waves per 32 owned rows, and the heads of a group (those that do not
+    divide 16 leave registers of a result tile unused) summed inside a tile; 9 heads: the general kernel."""
+    lens = [L - (11 * u) % (L // 2) for u in range(units)]
+    _both_paths(monkeypatch, dtype, d, units, group, L, lens, window=24 if group == 3 else 0)
+
+
+@pytest.mark.parametrize("qsplit", ["1", "2", "8"])
+@pytest.mark.parametrize("group,L", [(1, 700), (3, 500), (5, 400), (6, 300), (7, 290), (8, 300)])
+def test_shares_of_the_wide_kernels(monkeypatch, qsplit, group, L):
+    monkeypatch.setenv("ROCO_PREFILL_QSPLIT", qsplit)
+    _both_paths(monkeypatch, "bf16", 128, 3, group, L, [L, L - 70, L // 2])
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+def test_a_smaller_workspace_takes_fewer_shares(dtype, d):
+    """What the query asked for before it knew of more than two shares is still enough; less is refused."""
+    import paper_2402_06262_amd as roco
+    units, group, L, B = 1, 2, 3000, 3000
+    P = TP._parity()
+    Q, K, V = _inputs(np.random.default_rng(5), dtype, units, group, L, d)
+    sess = P.make_session(units, d, B, 9, dtype)
+    want = P.gpu_prefill_gqa(sess, group, Q, K, V, [L])["stats"]
+    up = lambda n: (n + 255) // 256 * 256
+    least = 4 * up(4 * units * L) + up(4 * units * group * L)
+    assert least < sess.prefill_ws.nbytes
+    q, k, v = (P.to_dev(x, dtype) for x in (Q, K, V))
+    lens = torch.tensor([L], dtype=torch.int32, device="cuda")
+    c = sess.cache
+    for nbytes in (least, 2 * least, least - 1):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        c.stats.zero_()
+        call = lambda: roco.roco_prefill_compress_gqa(sess.params, group, q, k, v, lens, L, c.K, c.V, c.stats, c.pos, c.n_used,
+                                                      c.next_slot, None, ws)
+        if nbytes < least:
+            with pytest.raises(roco.RocoError):
+                call()
+            continue
+        call()
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(c.stats.cpu().numpy()[:, :2], want[:, :2], rtol=2e-5, atol=1e-7)
+
+
+def test_shares_of_a_prompt_whose_keys_do_not_fit_the_lds():
+    """Above 16384 tokens a kernel of its own adds the shares; the last-token score needs them added before it writes its row."""
+    import paper_2402_06262_amd as roco
+    L, B, d = 17000, 300, 128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    Q, K, V = (torch.randn((1, L, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    p = roco.RocoParams(1, d, B, 60, roco.ROCO_BF16)
+    res = []
+    for nbytes in (5 * 4 * L + 5 * 256, roco.prefill_workspace_bytes(p, L)):
+        c = roco.alloc_cache(p)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        roco.roco_prefill_compress(p, Q, K, V, torch.tensor([L], dtype=torch.int32, device="cuda"), L, c.K, c.V, c.stats, c.pos,
+                                   c.n_used, c.next_slot, None, ws)
+        torch.cuda.synchronize()
+        res.append(c)
+    a, b = res
+    same = (a.pos == b.pos).float().mean().item()
+    assert same > 0.9  # ties within rounding may move a token, and every slot behind it
+    if same == 1.0:
+        np.testing.assert_allclose(a.stats.cpu().numpy(), b.stats.cpu().numpy(), rtol=2e-5, atol=1e-7)
