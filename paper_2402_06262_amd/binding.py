@@ -1,7 +1,9 @@
-"""ctypes binding of libroco.so: same names as include/roco.h, argument marshalling only.
+"""Binding of libroco.so: same names as include/roco.h, argument marshalling only.
 
 PyTorch supplies device memory (`tensor.data_ptr()`) and the HIP stream
-(`torch.cuda.current_stream().cuda_stream`); no arithmetic of the method happens here.
+(`torch.cuda.current_stream().cuda_stream`); no arithmetic of the method happens here.  The library is loaded with ctypes; the
+arguments of the steps and prompts, the calls that a model makes per layer and token, are collected by the extension module
+`_native` (csrc/native_call.cpp), which is handed the addresses of the library's functions.
 """
 from __future__ import annotations
 
@@ -18,7 +20,10 @@ ROCO_SCOPE_STD, ROCO_SCOPE_WINDOW, ROCO_SCOPE_ALL = 0, 1, 2
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libroco.so"
+_NATIVE_NAME = "_native"
 _lib: Optional[ctypes.CDLL] = None
+_native = None  # the extension module ...
+_native_lib: Optional[ctypes.CDLL] = None  # ... and the library it is bound to
 
 
 class RocoError(RuntimeError):
@@ -118,6 +123,28 @@ def load_library() -> ctypes.CDLL:
     return lib
 
 
+def _bind_native(lib) -> None:
+    global _native, _native_lib
+    import importlib
+    import torch  # the extension reads tensors by their C++ side
+    native = importlib.import_module("." + _NATIVE_NAME, __package__)
+    address = lambda fn: ctypes.cast(fn, ctypes.c_void_p).value
+    native.bind(tuple(address(getattr(lib, name)) for name in (
+        "roco_prefill_compress", "roco_prefill_compress_gqa", "roco_prefill_compress_lse", "roco_decode_step",
+        "roco_decode_step_static", "roco_encode_block", "roco_encode_block_gqa", "roco_decode_step_gqa")),
+        torch.Tensor, torch.nn.Parameter, _ptr, _stream)
+    if _native is None and hasattr(os, "register_at_fork"):
+        os.register_at_fork(after_in_child=native.forget_gpu)  # a forked child is refused by torch, as before
+    _native, _native_lib = native, lib
+
+
+def _calls():
+    """The extension module, bound to the library; loads both on first use."""
+    if _native_lib is None or _native_lib is not _lib:
+        _bind_native(load_library())
+    return _native
+
+
 def roco_strerror(code: int) -> str:
     return load_library().roco_strerror(int(code)).decode()
 
@@ -172,18 +199,16 @@ def _ptr(t) -> Optional[int]:
 
 
 def _ptrs(*ts):
-    """Device addresses of several tensors: `_ptr` of each, without a call per tensor where all of them are tensors (a
-    small decode step takes less time than its fourteen calls did: 6.3 -> 5.6 us of host time)."""
-    try:
-        return [None if t is None else t.data_ptr() if t.is_contiguous() else _ptr(t) for t in ts]
-    except AttributeError:  # a plain address among them
-        return [_ptr(t) for t in ts]
+    return [_ptr(t) for t in ts]
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        current = torch.cuda.current_stream().cuda_stream
+        if _native is not None:  # from now on the extension asks for it itself
+            _native.use_gpu(torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+        return current
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -192,13 +217,8 @@ def _stream(stream) -> Optional[int]:
 def roco_prefill_compress(params: RocoParams, Q, K, V, length, L_max: int, K_cache, V_cache, stats, pos,
                           n_used, next_slot, O, workspace, workspace_bytes: Optional[int] = None, stream=None) -> None:
     """See include/roco.h.  Tensors are device tensors; `O` may be None."""
-    if workspace_bytes is None:
-        workspace_bytes = workspace.nbytes
-    rc = load_library().roco_prefill_compress(
-        ctypes.byref(params), *_ptrs(Q, K, V, length), int(L_max),
-        *_ptrs(K_cache, V_cache, stats, pos, n_used, next_slot, O, workspace),
-        int(workspace_bytes),
-        _stream(stream))
+    rc = _calls().prefill_compress(params, Q, K, V, length, L_max, K_cache, V_cache, stats, pos, n_used, next_slot, O,
+                                   workspace, workspace_bytes, stream)
     if rc != 0:
         raise RocoError(rc, "roco_prefill_compress")
 
@@ -207,13 +227,8 @@ def roco_decode_step(params: RocoParams, q, k_new, v_new, qpos, K_cache, V_cache
                      out, evicted_slot, evicted_pos, workspace, workspace_bytes: Optional[int] = None,
                      stream=None) -> None:
     """See include/roco.h.  `evicted_slot` / `evicted_pos` may be None."""
-    if workspace_bytes is None:
-        workspace_bytes = workspace.nbytes
-    rc = load_library().roco_decode_step(
-        ctypes.byref(params),
-        *_ptrs(q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot,
-               out, evicted_slot, evicted_pos, workspace),
-        int(workspace_bytes), _stream(stream))
+    rc = _calls().decode_step(params, q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot, out,
+                              evicted_slot, evicted_pos, workspace, workspace_bytes, stream)
     if rc != 0:
         raise RocoError(rc, "roco_decode_step")
 
@@ -221,11 +236,8 @@ def roco_decode_step(params: RocoParams, q, k_new, v_new, qpos, K_cache, V_cache
 def roco_decode_step_static(params: RocoParams, q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used,
                             next_slot, out, evicted_slot, evicted_pos, stream=None) -> None:
     """See include/roco.h: the decode step on the library's own static scratch (no workspace, no allocation)."""
-    rc = load_library().roco_decode_step_static(
-        ctypes.byref(params),
-        *_ptrs(q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot,
-               out, evicted_slot, evicted_pos),
-        _stream(stream))
+    rc = _calls().decode_step_static(params, q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot, out,
+                                     evicted_slot, evicted_pos, stream)
     if rc != 0:
         raise RocoError(rc, "roco_decode_step_static")
 
@@ -238,12 +250,8 @@ def roco_prefill_compress_gqa(params: RocoParams, group: int, Q, K, V, lens, L_m
                               n_used, next_slot, O, workspace, workspace_bytes: Optional[int] = None,
                               stream=None) -> None:
     """See include/roco.h: prefill with one-step eviction for key/value heads shared by `group` query heads."""
-    if workspace_bytes is None:
-        workspace_bytes = workspace.nbytes
-    rc = load_library().roco_prefill_compress_gqa(
-        ctypes.byref(params), int(group), *_ptrs(Q, K, V, lens), int(L_max),
-        *_ptrs(K_cache, V_cache, stats, pos, n_used, next_slot, O, workspace),
-        int(workspace_bytes), _stream(stream))
+    rc = _calls().prefill_compress_gqa(params, group, Q, K, V, lens, L_max, K_cache, V_cache, stats, pos, n_used, next_slot,
+                                       O, workspace, workspace_bytes, stream)
     if rc != 0:
         raise RocoError(rc, "roco_prefill_compress_gqa")
 
@@ -252,13 +260,8 @@ def roco_prefill_compress_lse(params: RocoParams, group: int, Q, K, V, lens, L_m
                               pos, n_used, next_slot, workspace, workspace_bytes: Optional[int] = None,
                               stream=None) -> None:
     """See include/roco.h: prefill-compress from row normalisers the caller's attention kernel already produced."""
-    if workspace_bytes is None:
-        workspace_bytes = workspace.nbytes
-    rc = load_library().roco_prefill_compress_lse(
-        ctypes.byref(params), int(group), *_ptrs(Q, K, V, lens), int(L_max),
-        *_ptrs(lse, K_cache, V_cache, stats, pos, n_used, next_slot, workspace),
-        int(workspace_bytes),
-        _stream(stream))
+    rc = _calls().prefill_compress_lse(params, group, Q, K, V, lens, L_max, lse, K_cache, V_cache, stats, pos, n_used,
+                                       next_slot, workspace, workspace_bytes, stream)
     if rc != 0:
         raise RocoError(rc, "roco_prefill_compress_lse")
 
@@ -279,13 +282,8 @@ def roco_encode_block(params: RocoParams, block: int, q, k_new, v_new, qpos0, K_
                       next_slot, out, evicted_slot, evicted_pos, workspace, workspace_bytes: Optional[int] = None,
                       stream=None) -> None:
     """See include/roco.h: free and encode `block` tokens within one eviction step."""
-    if workspace_bytes is None:
-        workspace_bytes = workspace.nbytes
-    rc = load_library().roco_encode_block(
-        ctypes.byref(params), int(block),
-        *_ptrs(q, k_new, v_new, qpos0, K_cache, V_cache, stats, pos, n_used, next_slot,
-               out, evicted_slot, evicted_pos, workspace),
-        int(workspace_bytes), _stream(stream))
+    rc = _calls().encode_block(params, block, q, k_new, v_new, qpos0, K_cache, V_cache, stats, pos, n_used, next_slot, out,
+                               evicted_slot, evicted_pos, workspace, workspace_bytes, stream)
     if rc != 0:
         raise RocoError(rc, "roco_encode_block")
 
@@ -294,13 +292,8 @@ def roco_encode_block_gqa(params: RocoParams, block: int, group: int, q, k_new, 
                           pos, n_used, next_slot, out, evicted_slot, evicted_pos, workspace,
                           workspace_bytes: Optional[int] = None, stream=None) -> None:
     """See include/roco.h: block-wise step of key/value heads shared by `group` query heads each."""
-    if workspace_bytes is None:
-        workspace_bytes = workspace.nbytes
-    rc = load_library().roco_encode_block_gqa(
-        ctypes.byref(params), int(block), int(group),
-        *_ptrs(q, k_new, v_new, qpos0, K_cache, V_cache, stats, pos, n_used, next_slot,
-               out, evicted_slot, evicted_pos, workspace),
-        int(workspace_bytes), _stream(stream))
+    rc = _calls().encode_block_gqa(params, block, group, q, k_new, v_new, qpos0, K_cache, V_cache, stats, pos, n_used,
+                                   next_slot, out, evicted_slot, evicted_pos, workspace, workspace_bytes, stream)
     if rc != 0:
         raise RocoError(rc, "roco_encode_block_gqa")
 
@@ -309,13 +302,8 @@ def roco_decode_step_gqa(params: RocoParams, group: int, q, k_new, v_new, qpos, 
                          next_slot, out, evicted_slot, evicted_pos, workspace, workspace_bytes: Optional[int] = None,
                          stream=None) -> None:
     """See include/roco.h: one decode step of key/value heads shared by `group` query heads each."""
-    if workspace_bytes is None:
-        workspace_bytes = workspace.nbytes
-    rc = load_library().roco_decode_step_gqa(
-        ctypes.byref(params), int(group),
-        *_ptrs(q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot,
-               out, evicted_slot, evicted_pos, workspace),
-        int(workspace_bytes), _stream(stream))
+    rc = _calls().decode_step_gqa(params, group, q, k_new, v_new, qpos, K_cache, V_cache, stats, pos, n_used, next_slot, out,
+                                  evicted_slot, evicted_pos, workspace, workspace_bytes, stream)
     if rc != 0:
         raise RocoError(rc, "roco_decode_step_gqa")
 

@@ -1,4 +1,4 @@
-"""Build libroco.so (gfx950) in-tree with hipcc.  `python -m paper_2402_06262_amd.build`."""
+"""Build libroco.so (gfx950) in-tree with hipcc, and the binding's extension module with the host compiler.  `python -m paper_2402_06262_amd.build`."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libroco.so")
+NATIVE_PATH = os.path.join(HERE, "_native.so")  # extension module of the binding (host code)
 SOURCES = ["api.hip", "decode.hip", "prefill_simple.hip", "prefill_mfma.hip", "prefill_planes.hip",
            "select_compact.hip", "block.hip", "profile.hip"]
 
@@ -44,9 +45,19 @@ def _run(cmd, verbose):
         raise RuntimeError(f"hipcc failed ({proc.returncode}):\n{out}")
 
 
+def _native_command():
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    flags = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    includes = [f"-I{d}" for d in cpp_extension.include_paths()] + [f"-I{sysconfig.get_paths()['include']}"]
+    libs = [f"-L{os.path.join(os.path.dirname(torch.__file__), 'lib')}", "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    return ["g++", *flags, *includes, os.path.join(CSRC, "native_call.cpp"), "-o", NATIVE_PATH, *libs]
+
+
 def build_library(verbose: bool = True) -> str:
     """Compile every HIP source (one hipcc process each, side by side) and link them into one shared library next to
-    this file; returns its path.  Objects go to a temporary folder: nothing but the library is left in the tree."""
+    this file; returns its path.  Objects go to a temporary folder: nothing but the library and the extension module is left in the tree."""
     from concurrent.futures import ThreadPoolExecutor
 
     hipcc = hipcc_path()
@@ -54,8 +65,8 @@ def build_library(verbose: bool = True) -> str:
     with tempfile.TemporaryDirectory(prefix="roco_build_") as tmp:
         objs = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
         cmds = [[hipcc, *compile_flags, "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
-        with ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 1)) as pool:
-            list(pool.map(lambda c: _run(c, verbose), cmds))
+        with ThreadPoolExecutor(max_workers=min(len(cmds) + 1, os.cpu_count() or 1)) as pool:
+            list(pool.map(lambda c: _run(c, verbose), [_native_command(), *cmds]))
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH], verbose)
     return LIB_PATH
 

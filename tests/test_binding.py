@@ -1,0 +1,86 @@
+"""Argument marshalling of the extension module behind the binding (no GPU: the calls are refused on the host)."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2402_06262_amd as roco
+from paper_2402_06262_amd import binding
+
+EINVAL, EWORKSPACE = -1, -3
+P = roco.RocoParams(4, 64, 128, 16, roco.ROCO_F32)
+
+
+def _decode(params=P, q=0x1000, ws=0x1000, workspace_bytes=0, stream=0, **kw):
+    a = dict(k_new=0x1000, v_new=0x1000, qpos=0x1000, K_cache=0x1000, V_cache=0x1000, stats=0x1000, pos=0x1000, n_used=0x1000,
+             next_slot=0x1000, out=0x1000, evicted_slot=None, evicted_pos=None)
+    a.update(kw)
+    roco.roco_decode_step(params, q, workspace=ws, workspace_bytes=workspace_bytes, stream=stream, **a)
+
+
+def _code(call, *a, **k):
+    with pytest.raises(roco.RocoError) as e:
+        call(*a, **k)
+    return e.value.code
+
+
+def test_addresses_none_and_sizes_reach_the_library():
+    assert _code(_decode) == EWORKSPACE                      # everything valid but the workspace's size
+    assert _code(_decode, q=None) == EINVAL
+    assert _code(_decode, q=0x1001) == EINVAL                # misaligned
+    assert _code(_decode, workspace_bytes=np.int64(5)) == EWORKSPACE
+    assert _code(_decode, params=roco.RocoParams(0, 64, 128, 16, roco.ROCO_F32)) == EINVAL
+    need = roco.decode_workspace_bytes(P)
+    assert _code(_decode, workspace_bytes=need - 1, ws=torch.empty(need, dtype=torch.uint8)) in (EWORKSPACE, EINVAL)
+
+
+def test_a_tensor_is_its_address_and_its_bytes():
+    small = torch.empty(64, dtype=torch.float32)
+    assert _code(_decode, q=small, ws=small, workspace_bytes=None) == EWORKSPACE
+    assert _code(_decode, q=small, ws=torch.nn.Parameter(small), workspace_bytes=None) == EWORKSPACE
+    assert _code(_decode, q=small.view(torch.uint8)[1:17], ws=small, workspace_bytes=None) == EINVAL  # its storage offset counts
+
+    class Sub(torch.Tensor):
+        pass
+
+    assert _code(_decode, q=small.as_subclass(Sub), ws=small, workspace_bytes=None) == EWORKSPACE
+
+
+def test_what_is_refused_stays_refused():
+    with pytest.raises(ValueError, match="contiguous"):
+        _decode(q=torch.empty(8, 8).t())
+    with pytest.raises(AttributeError):
+        _decode(q="address")
+    with pytest.raises(AttributeError):
+        _decode(workspace_bytes=None)                        # an address has no size
+    with pytest.raises(TypeError):
+        _decode(params=7)
+    with pytest.raises(TypeError):
+        roco.roco_decode_step(P, 1)
+
+
+@pytest.mark.parametrize("call,n", [("roco_encode_block", 1), ("roco_decode_step_gqa", 1), ("roco_encode_block_gqa", 2)])
+def test_steps_of_many(call, n):
+    fn = getattr(roco, call)
+    args = [0x1000] * 14
+    assert _code(fn, P, *[4] * n, *args, workspace_bytes=0, stream=0) == EWORKSPACE
+    assert _code(fn, P, *[0] * n, *args, workspace_bytes=0, stream=0) == EINVAL
+    assert _code(fn, P, *[np.int32(4)] * n, *args[:-1], torch.empty(16), stream=0) in (EINVAL, EWORKSPACE)
+
+
+def test_prompts_and_the_static_step():
+    a = [0x1000] * 8
+    assert _code(roco.roco_prefill_compress, P, *[0x1000] * 4, 64, *a, workspace_bytes=0, stream=0) == EWORKSPACE
+    assert _code(roco.roco_prefill_compress, P, *[0x1000] * 4, 0, *a, workspace_bytes=0, stream=0) == EINVAL
+    assert _code(roco.roco_prefill_compress_gqa, P, 2, *[0x1000] * 4, 64, *a, workspace_bytes=0, stream=0) == EWORKSPACE
+    assert _code(roco.roco_prefill_compress_lse, P, 2, *[0x1000] * 4, 64, *a, workspace_bytes=0, stream=0) == EWORKSPACE
+    assert _code(roco.roco_prefill_compress_lse, P, 2, *[0x1000] * 4, 64, None, *a[1:], workspace_bytes=0, stream=0) == EINVAL
+    assert _code(roco.roco_decode_step_static, P, *[0x1000] * 10, None, None, None, stream=0) == EINVAL  # no output
+
+
+def test_the_extension_follows_the_loaded_library(monkeypatch):
+    before = binding._calls()
+    monkeypatch.setattr(binding, "_lib", None)
+    assert binding._calls() is before and binding._native_lib is binding._lib is roco.load_library()
+    assert ctypes.sizeof(roco.RocoParams) == 44
