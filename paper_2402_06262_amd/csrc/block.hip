@@ -10,10 +10,10 @@
 //
 //   block_prepare : one workgroup per unit.  Victims (two exact radix selects), ordered slot assignment,
 //                   K / V rows of the block written into their slots, pos / statistics of those slots reset.
-//   block_attend  : grid (splits, units), two waves.  64-slot K and V tiles through LDS, each wave scores 32
-//                   slots against the block's queries on the matrix cores (score tile = K . Q^T, the query in
-//                   the lane; one or two tiles of 32 query rows, every K and V^T fragment read from LDS feeding
-//                   both), stores the base-2 logits, keeps an online softmax per query and accumulates
+//   block_attend  : grid (splits, units), two waves.  Each wave streams 32-slot tiles of K and V through LDS of its
+//                   own and scores them against the block's queries on the matrix cores (score tile = K . Q^T, the
+//                   query in the lane; one or two tiles of 32 query rows, every K and V^T fragment read from LDS
+//                   feeding both), stores the base-2 logits, keeps an online softmax per query and accumulates
 //                   O^T = V^T . P^T with V^T fragments from the LDS transpose read.
 //   block_attend_shared : the same for fp32 and head_dim 64, on the vector ALUs (see there).
 //   block_finish  : one workgroup per unit.  Merges the partials per query, writes the outputs, adds the
@@ -29,9 +29,13 @@
 #include "mfma.hpp"
 #include "profile.hpp"
 #include "stream.hpp"
+#include "tile_ring.hpp"
 
 namespace roco {
 namespace {
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 
 using namespace mfma;
 
@@ -138,50 +142,48 @@ __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-struct StagedKV {
-  uint4 k[8], v[8];  // this thread's 128 bytes of a 64 x 256 B tile of K and of V (128 threads)
+// K and V of a wave: 32 slots a tile, two tiles of each in LDS, private to the wave and filled by loads that go straight there
+// (tile_ring.hpp), so that nothing but the wave's own load counter orders the stream: no barrier, no staging registers, and the
+// buffer of an operand is requested again as soon as its tile has been used.  At least three operand tiles of a wave are on
+// their way at any time, 96 KiB per compute unit.  64-slot tiles staged through registers, with a barrier per tile and nothing in
+// flight between the arrival of a tile and the requests after the barrier, took 55.9 us where this takes 51.1 (233 units x 3
+// heads x 1644 slots), 54.5 / 49.1 (136 x 4 heads x 14 tokens x 1096), 183.9 / 174.4 (415 x 35 tokens x 2640), 125.2 / 123.8 at
+// 512 x 16 tokens x 2048, whose 64 MiB of logits cost 30 us between the reads.
+// K chunk c of row r lies in slot c ^ (r & 15), V chunk c in slot c ^ 4 (r & 3): see TileRing and OutRing.
+struct WaveTiles {
+  static constexpr int kSlots = 32;
+  static constexpr int kOperand = kSlots * kRowBytes;  // 8 KiB
+  static constexpr int kBytes = 4 * kOperand;          // K, K, V, V of one wave
+  static constexpr int kLoads = kOperand / 1024;       // wave-wide loads per operand tile
 };
-// `fresh` (or -1) is a slot whose row is taken from knew / vnew instead of the cache: the token a single-token step
-// is about to write there.  The address is selected, not the load, so there is no control flow around the loads.
 template <bool STREAMING>
-__device__ __forceinline__ void kv_load(StagedKV& s, const char* Kb, const char* Vb, int row0, int last_row,
-                                        int fresh, const char* knew, const char* vnew) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    int row = row0 + (t >> 4) + 8 * i;
-    row = row < last_row ? row : last_row;  // slots past the end are masked by the caller
-    const size_t off = static_cast<size_t>(row) * kRowBytes + (t & 15) * 16;
-    const char* kp = row == fresh ? knew + (t & 15) * 16 : Kb + off;
-    const char* vp = row == fresh ? vnew + (t & 15) * 16 : Vb + off;
-    s.k[i] = STREAMING ? load16_streaming(kp) : load16(kp);
-    s.v[i] = STREAMING ? load16_streaming(vp) : load16(vp);
-  }
+__device__ __forceinline__ void load16_to_lds_hint(v4i32 rsrc, uint32_t lds_addr, int voffset, int soffset) {
+  if (STREAMING)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 :: "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory", "m0");
+  else
+    load16_to_lds(rsrc, lds_addr, voffset, soffset);
 }
-__device__ __forceinline__ void kv_store(const StagedKV& s, char* tileK, char* tileV) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    *reinterpret_cast<uint4*>(tileK + ((t >> 4) + 8 * i) * kLdsRow + (t & 15) * 16) = s.k[i];
-    *reinterpret_cast<uint4*>(tileV + ((t >> 4) + 8 * i) * kLdsRowV + (t & 15) * 16) = s.v[i];
-  }
-}
+// The wave's LDS reads so far have returned: their tile may be overwritten.
+__device__ __forceinline__ void reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // NQT: tiles of 32 query rows (1 or 2).  The workspace planes are addressed with a.qrows = 32 NQT rows per unit.
-template <int NQT>
+// WINDOW: a recency bias is in force (the slots' positions come along with the K tiles).
+template <int NQT, bool STREAMING, bool WINDOW>
 __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
+  using T = WaveTiles;
   constexpr int QR = NQT * kQ;
-  extern __shared__ __attribute__((aligned(16))) char lds_dyn[];  // K[2] and V[2] tiles; reused for the merge
-  __shared__ __attribute__((aligned(16))) int32_t bidx_s[2][kTile];
-  __shared__ __attribute__((aligned(16))) int32_t pos_s[2][kTile];
+  constexpr int kSideLoads = WINDOW ? 2 : 1;  // block indices of a K tile's slots, and their positions
+  extern __shared__ __attribute__((aligned(1024))) char lds_dyn[];  // the two waves' tiles; reused for the merge
+  __shared__ __attribute__((aligned(256))) int32_t bidx_s[2][2][kWave], pos_s[WINDOW ? 2 : 1][2][kWave];  // [wave][buffer]
   __shared__ float merge_m[QR], merge_l[QR];
   const int u = blockIdx.y, split = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int half = lane >> 5, qi = lane & 31;  // this lane's query row inside a tile
   const int B = a.B, b = a.queries;
   // Usually block_prepare has run: n_used counts the block's tokens and their rows are in the cache.  A single-token
   // step skips it (BlockArgs::single): the token's slot is known from the state, its row is read from k_new / v_new
-  // and written into the cache by the workgroup that streams that slot, as in the token-wise decode kernels.
+  // and written into the cache by the wave that streams that slot, as in the token-wise decode kernels.
   int n = a.n_used[u];
   int fresh = -1;
   if (a.single) {
@@ -189,25 +191,62 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
     fresh = was_full ? min(max(a.next_slot[u], 0), B - 1) : n;
     n = was_full ? B : n + 1;
   }
-  const char* knew = static_cast<const char*>(a.k_new) + static_cast<size_t>(u) * kRowBytes;
-  const char* vnew = static_cast<const char*>(a.v_new) + static_cast<size_t>(u) * kRowBytes;
   const int row0 = split * a.rows_per_split;
   const int row1 = min(n, row0 + a.rows_per_split);
   const size_t pidx = static_cast<size_t>(u) * a.splits + split;
   char* Kb = static_cast<char*>(a.K) + static_cast<size_t>(u) * B * kRowBytes;
   char* Vb = static_cast<char*>(a.V) + static_cast<size_t>(u) * B * kRowBytes;
-  const int32_t* bidx = a.blk_idx + static_cast<size_t>(u) * B;
-  const int32_t* pos = a.pos + static_cast<size_t>(u) * B;
   float* z = a.z + static_cast<size_t>(u) * QR * B;
   const float sc = a.scale_log2;
   const int w = a.recency_window;
   const float rb = a.recency_bias_log2;
+  const int qp0 = a.qpos0[u];
   int ti[NQT], qp[NQT];  // this lane's block token per tile; the heads of a group share its position
 #pragma unroll
   for (int t2 = 0; t2 < NQT; ++t2) {
     ti[t2] = (kQ * t2 + qi) / a.heads;
-    qp[t2] = a.qpos0[u] + ti[t2];
+    qp[t2] = qp0 + ti[t2];
   }
+
+  // slots past the unit's last one come back as zeros (and are masked below)
+  const v4i32 kbuf = make_buffer(Kb, static_cast<uint32_t>(n) * kRowBytes);
+  const v4i32 vbuf = make_buffer(Vb, static_cast<uint32_t>(n) * kRowBytes);
+  const v4i32 bbuf = make_buffer(a.blk_idx + static_cast<size_t>(u) * B, static_cast<uint32_t>(B) * 4u);
+  const v4i32 pbuf = make_buffer(a.pos + static_cast<size_t>(u) * B, static_cast<uint32_t>(B) * 4u);
+  char* const my_tiles = lds_dyn + wave * T::kBytes;
+  const uint32_t tiles_addr = lds_address(my_tiles);
+  const uint32_t bidx_addr = lds_address(&bidx_s[wave][0][0]), pos_addr = lds_address(&pos_s[WINDOW ? wave : 0][0][0]);
+  int koff[4];  // rows 4 i + lane / 16 of a tile (and 16 further down)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 4 * i + (lane >> 4);
+    koff[i] = r * kRowBytes + (((lane & 15) ^ r) << 4);
+  }
+  const int voff = (lane >> 4) * kRowBytes + (((lane & 15) ^ ((lane >> 4) << 2)) << 4);
+  // The wave's tiles: every other one of the split, from a start that differs between workgroups, so that workgroups running
+  // side by side do not walk the memory channels in lock step (the online softmax does not care about the order).
+  const int n_tiles = row1 > row0 ? (row1 - row0 + T::kSlots - 1) / T::kSlots : 0;
+  const int mine = (n_tiles - wave + 1) / 2;
+  const int rot = mine > 0 ? static_cast<int>((static_cast<unsigned>(u) * 5u + static_cast<unsigned>(split) * 3u) %
+                                              static_cast<unsigned>(mine))
+                           : 0;
+  auto tile_row = [&](int t) { return row0 + (2 * (t + rot < mine ? t + rot : t + rot - mine) + wave) * T::kSlots; };
+  auto request_k = [&](int t) {
+    const int row = tile_row(t);
+    const uint32_t dst = tiles_addr + (t & 1) * T::kOperand;
+    const int soff = __builtin_amdgcn_readfirstlane(row * kRowBytes);
+#pragma unroll
+    for (int i = 0; i < T::kLoads; ++i) load16_to_lds_hint<STREAMING>(kbuf, dst + i * 1024, koff[i & 3], soff + (i >> 2) * 16 * kRowBytes);
+    const int side = __builtin_amdgcn_readfirstlane(row * 4);
+    load4_to_lds(bbuf, bidx_addr + (t & 1) * (kWave * 4), lane * 4, side);
+    if (WINDOW) load4_to_lds(pbuf, pos_addr + (t & 1) * (kWave * 4), lane * 4, side);
+  };
+  auto request_v = [&](int t) {
+    const uint32_t dst = tiles_addr + (2 + (t & 1)) * T::kOperand;
+    const int soff = __builtin_amdgcn_readfirstlane(tile_row(t) * kRowBytes);
+#pragma unroll
+    for (int i = 0; i < T::kLoads; ++i) load16_to_lds_hint<STREAMING>(vbuf, dst + i * 1024, voff, soff + i * 4 * kRowBytes);
+  };
 
   // B operand: the block's queries (lanes beyond the block reuse its last query; their results are dropped)
   uint4 own[NQT][kKSteps];
@@ -217,6 +256,8 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
 #pragma unroll
     for (int kk = 0; kk < kKSteps; ++kk) own[t2][kk] = load16(qrow + kk * 32 + half * 16);
   }
+  if (mine > 0) { request_k(0); request_v(0); }
+  if (mine > 1) { request_k(1); request_v(1); }
   float m[NQT], l[NQT];
   f32x16 o[NQT][4];
 #pragma unroll
@@ -226,62 +267,65 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
 #pragma unroll
     for (int db = 0; db < 4; ++db) o[t2][db] = f32x16{0};
   }
-  const int tr_off = transposed_fragment_offset();
-
-  const int n_tiles = row1 > row0 ? (row1 - row0 + kTile - 1) / kTile : 0;
-  StagedKV st;
-  int32_t st_bidx = -1, st_pos = 0;
-  // Tiles are visited from a start that differs between workgroups, so that workgroups running side by side do
-  // not walk the memory channels in lock step (the online softmax does not care about the order).
-  const int rot = n_tiles > 0 ? static_cast<int>((static_cast<unsigned>(u) * 5u + static_cast<unsigned>(split) * 3u) %
-                                                 static_cast<unsigned>(n_tiles))
-                              : 0;
-  auto tile_row = [&](int t) { return row0 + (t + rot < n_tiles ? t + rot : t + rot - n_tiles) * kTile; };
-  auto fetch = [&](int t) {
-    const int tr0 = tile_row(t);
-    if (a.streaming) kv_load<true>(st, Kb, Vb, tr0, n - 1, fresh, knew, vnew);
-    else kv_load<false>(st, Kb, Vb, tr0, n - 1, fresh, knew, vnew);
-    if (fresh >= tr0 && fresh < min(tr0 + kTile, row1)) {  // this tile holds the new token's slot: put the row there
+  // fragment reads: K row lane % 32, chunk 2 kk + half; V transposed, rows 4 half + (lane % 16) / 4 (+ 8), the lane's 8 bytes of
+  // columns 32 db + 16 (lane / 16 % 2) + 4 (lane % 4)
+  const int kfrag = (lane & 31) * kRowBytes + ((half ^ (lane & 15)) << 4);
+  int vfrag[4];
+  {
+    const int rr = (lane & 15) >> 2;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (tr0 + (tid >> 4) + 8 * i == fresh) {
-          const size_t off = static_cast<size_t>(fresh) * kRowBytes + (tid & 15) * 16;
-          *reinterpret_cast<uint4*>(Kb + off) = st.k[i];
-          *reinterpret_cast<uint4*>(Vb + off) = st.v[i];
-        }
-      }
-    }
-    if (tid < kTile) {
-      const int slot = min(tr0 + tid, n - 1);
-      st_bidx = a.single ? -1 : bidx[slot];
-      st_pos = slot == fresh ? a.qpos0[u] : pos[slot];
+    for (int db = 0; db < 4; ++db)
+      vfrag[db] = (4 * half + rr) * kRowBytes + ((db ^ rr) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+  }
+  // The new token's row of a single-token step, put over the old one in the tile and in the cache: 16 lanes.
+  auto put_row = [&](const void* rows, char* cache, char* tile, int slot_in_tile, int swizzle) {
+    if (lane < 16) {
+      const uint4 row = load16(static_cast<const char*>(rows) + static_cast<size_t>(u) * kRowBytes + lane * 16);
+      *reinterpret_cast<uint4*>(tile + slot_in_tile * kRowBytes + ((lane ^ swizzle) << 4)) = row;
+      *reinterpret_cast<uint4*>(cache + static_cast<size_t>(fresh) * kRowBytes + lane * 16) = row;
     }
   };
-  if (n_tiles > 0) fetch(0);
-  for (int t = 0; t < n_tiles; ++t) {
-    char* const tileK = lds_dyn + (t & 1) * kTileBytes;
-    char* const tileV = lds_dyn + 2 * kTileBytes + (t & 1) * kTileBytesV;
-    kv_store(st, tileK, tileV);
-    if (tid < kTile) { bidx_s[t & 1][tid] = st_bidx; pos_s[t & 1][tid] = st_pos; }
-    __syncthreads();
-    if (t + 1 < n_tiles) fetch(t + 1);
-    const int tr0 = tile_row(t);
-    const int sb = tr0 + 32 * wave;  // first slot of this wave's half-tile
-    if (sb < row1) {                               // wave-uniform
+
+  for (int t = 0; t < mine; ++t) {
+    char* const tileK = my_tiles + (t & 1) * T::kOperand;
+    char* const tileV = my_tiles + (2 + (t & 1)) * T::kOperand;
+    const int sb = tile_row(t);  // first slot of the tile
+    const bool holds_fresh = fresh >= sb && fresh < sb + T::kSlots;
+    // K(t) has landed; V(t), and K and V of the next tile, may still be on their way (and logits stored since, which the
+    // counter holds too: then a little more than K(t) has landed)
+    if (t + 1 < mine) wait_loads<3 * T::kLoads + kSideLoads>();
+    else wait_loads<T::kLoads>();
+    if (holds_fresh) {
+      put_row(a.k_new, Kb, tileK, fresh - sb, (fresh - sb) & 15);
+      if (WINDOW && lane == 0) pos_s[WINDOW ? wave : 0][t & 1][fresh - sb] = qp0;
+    }
     // ---- scores of 32 slots x 32 NQT queries: every K fragment feeds one accumulator chain per query tile
     f32x16 sacc[NQT];
     {
-      const char* p = tileK + (32 * wave + (lane & 31)) * kLdsRow + half * 16;
       const f32x16 zero = {0};
 #pragma unroll
       for (int kk = 0; kk < kKSteps; ++kk) {
-        const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p + kk * 32));
+        const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(tileK + (kfrag ^ (kk << 5))));
 #pragma unroll
         for (int t2 = 0; t2 < NQT; ++t2)
           sacc[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, __builtin_bit_cast(bf16x8, own[t2][kk]),
                                                              kk == 0 ? zero : sacc[t2], 0, 0, 0);
       }
     }
+    // index and position of the lane's 16 slots
+    int biv[16], psv[16];
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const int base = 8 * g4 + 4 * half;  // index inside the tile of 4 consecutive slots
+      const int4 bi = *reinterpret_cast<const int4*>(&bidx_s[wave][t & 1][base]);
+      biv[4 * g4] = bi.x; biv[4 * g4 + 1] = bi.y; biv[4 * g4 + 2] = bi.z; biv[4 * g4 + 3] = bi.w;
+      if (WINDOW) {
+        const int4 ps = *reinterpret_cast<const int4*>(&pos_s[WINDOW ? wave : 0][t & 1][base]);
+        psv[4 * g4] = ps.x; psv[4 * g4 + 1] = ps.y; psv[4 * g4 + 2] = ps.z; psv[4 * g4 + 3] = ps.w;
+      }
+    }
+    reads_done();
+    if (t + 2 < mine) request_k(t + 2);
     bf16x8 pfrag[NQT][2];
 #pragma unroll
     for (int t2 = 0; t2 < NQT; ++t2) {
@@ -291,24 +335,18 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
     float mb = -INFINITY;
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) {
-      const int base = 32 * wave + 8 * g4 + 4 * half;  // index inside the tile of 4 consecutive slots
-      const int4 bi = *reinterpret_cast<const int4*>(&bidx_s[t & 1][base]);
-      const int4 ps = *reinterpret_cast<const int4*>(&pos_s[t & 1][base]);
-      const int biv[4] = {bi.x, bi.y, bi.z, bi.w};
-      const int psv[4] = {ps.x, ps.y, ps.z, ps.w};
+      const int slot0 = sb + 8 * g4 + 4 * half;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int slot = tr0 + base + e;
         float x = sacc[t2][4 * g4 + e] * sc;
-        if (w > 0) {
-          const int dlt = qp[t2] - psv[e];
+        if (WINDOW) {
+          const int dlt = qp[t2] - psv[4 * g4 + e];
           if (dlt >= 0 && dlt < w) x += rb;
         }
-        if (slot >= row1 || biv[e] > ti[t2]) x = -INFINITY;
+        if (slot0 + e >= row1 || (!a.single && biv[4 * g4 + e] > ti[t2])) x = -INFINITY;
         tv[4 * g4 + e] = x;
         mb = fmaxf(mb, x);
       }
-      const int slot0 = tr0 + base;
       if (q < b && slot0 < row1) {  // logits of real queries and real slots are kept for the statistics
         *reinterpret_cast<float4*>(z + static_cast<size_t>(q) * B + slot0) =
             make_float4(tv[4 * g4], tv[4 * g4 + 1], tv[4 * g4 + 2], tv[4 * g4 + 3]);
@@ -335,21 +373,26 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
     }
     l[t2] += sum;
     }
-    // ---- O^T += V^T . P^T
+    // ---- O^T += V^T . P^T: V(t) has landed; K and V of the next tile, and K of the one after, may be on their way
+    if (t + 2 < mine) wait_loads<3 * T::kLoads + 2 * kSideLoads>();
+    else if (t + 1 < mine) wait_loads<2 * T::kLoads + kSideLoads>();
+    else wait_loads<0>();
+    if (holds_fresh) put_row(a.v_new, Vb, tileV, fresh - sb, ((fresh - sb) & 3) << 2);
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      const char* vt = tileV + (32 * wave + ks * 16) * kLdsRowV + tr_off;
+      const char* vt = tileV + ks * (16 * kRowBytes);
 #pragma unroll
       for (int db = 0; db < 4; ++db) {
-        const uint2 lo = lds_read_transposed(vt + db * 64);
-        const uint2 hi = lds_read_transposed(vt + 8 * kLdsRowV + db * 64);
+        const uint2 lo = lds_read_transposed(vt + vfrag[db]);
+        const uint2 hi = lds_read_transposed(vt + 8 * kRowBytes + vfrag[db]);
         const bf16x8 afrag = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
 #pragma unroll
         for (int t2 = 0; t2 < NQT; ++t2)
           o[t2][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag, pfrag[t2][ks], o[t2][db], 0, 0, 0);
       }
     }
-    }
+    reads_done();
+    if (t + 2 < mine) request_v(t + 2);
   }
 #pragma unroll
   for (int t2 = 0; t2 < NQT; ++t2) l[t2] += __shfl_xor(l[t2], 32, kWave);  // the lane halves summed different slots
@@ -864,6 +907,26 @@ hipError_t launch_block_shared(const BlockArgs& a, hipStream_t s) {
   return hipSuccess;
 }
 
+template <int NQT, bool STREAMING, bool WINDOW>
+hipError_t launch_block_attend_t(const BlockArgs& a, hipStream_t s) {
+  constexpr size_t kLds = 2 * WaveTiles::kBytes;  // 64 KiB, and what the kernel declares: above the default limit; set on every call
+  const void* fn = reinterpret_cast<const void*>(block_attend<NQT, STREAMING, WINDOW>);
+  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kLds)) != hipSuccess)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL((block_attend<NQT, STREAMING, WINDOW>), dim3(a.splits, a.units), dim3(kAttThreads), kLds, s, a);
+  return hipSuccess;
+}
+hipError_t launch_block_attend(const BlockArgs& a, hipStream_t s) {
+  ProfScope ps(kProfBlockAttend, s);
+  const bool two = a.qrows > kQ, window = a.recency_window > 0;
+  if (a.streaming) {
+    if (window) return two ? launch_block_attend_t<2, true, true>(a, s) : launch_block_attend_t<1, true, true>(a, s);
+    return two ? launch_block_attend_t<2, true, false>(a, s) : launch_block_attend_t<1, true, false>(a, s);
+  }
+  if (window) return two ? launch_block_attend_t<2, false, true>(a, s) : launch_block_attend_t<1, false, true>(a, s);
+  return two ? launch_block_attend_t<2, false, false>(a, s) : launch_block_attend_t<1, false, false>(a, s);
+}
+
 // dtype / head_dim other than bf16 / 128 take the vector-ALU attention
 hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStream_t s) {
   BlockArgs a = args;
@@ -873,13 +936,7 @@ hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStrea
   if (!allow_key_lds(reinterpret_cast<const void*>(block_prepare<512, true>), key_lds) ||
       !allow_key_lds(reinterpret_cast<const void*>(block_prepare<kPrepThreads, true>), key_lds))
     return hipErrorInvalidValue;
-  constexpr size_t kAttLds = 2 * static_cast<size_t>(kTileBytes + kTileBytesV);  // 74 KiB: above the default dynamic limit
   const bool mfma_path = dtype == kBF16 && head_dim == 128;
-  if (mfma_path) {  // set on every call: cheap, and right on whichever device is current
-    const void* fn = a.qrows > kQ ? reinterpret_cast<const void*>(block_attend<2>) : reinterpret_cast<const void*>(block_attend<1>);
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kAttLds)) != hipSuccess)
-      return hipErrorInvalidValue;
-  }
   if (!a.single) {
     ProfScope ps(kProfBlockPrepare, s);
     // Two 1024-thread workgroups do not run side by side on a compute unit here (measured: the second half of 512
@@ -890,11 +947,7 @@ hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStrea
     else hipLaunchKernelGGL((block_prepare<kPrepThreads, true>), grid, dim3(kPrepThreads), key_lds, s, a);
   }
   if (mfma_path) {
-    {
-      ProfScope ps(kProfBlockAttend, s);
-      if (a.qrows > kQ) hipLaunchKernelGGL(block_attend<2>, dim3(a.splits, a.units), dim3(kAttThreads), kAttLds, s, a);
-      else hipLaunchKernelGGL(block_attend<1>, dim3(a.splits, a.units), dim3(kAttThreads), kAttLds, s, a);
-    }
+    if (launch_block_attend(a, s) != hipSuccess) return hipErrorInvalidValue;
     launch_block_tail<kBF16, 128>(a, s);
   } else {
     hipError_t e = hipErrorInvalidValue;

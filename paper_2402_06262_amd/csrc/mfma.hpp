@@ -19,13 +19,6 @@ constexpr int kTile = 64;                // rows of K, V or Q per LDS tile
 constexpr int kRowBytes = D * 2;         // 256
 constexpr int kLdsRow = kRowBytes + 16;  // padded: 16 lanes x 16 B then hit distinct bank groups
 constexpr int kKSteps = D / 16;          // 8 matrix instructions per 32x32 tile
-constexpr int kTileBytes = kTile * kLdsRow;
-// V tiles that are read with the LDS transpose read take rows of 320 bytes: a 16-lane group of that read touches 4
-// consecutive rows x 32 bytes, and with 80-dword rows the 32 lanes served together fall on 64 distinct banks (with
-// the 272-byte rows of the K tiles, whose 128-bit row reads need that stride, half of the LDS cycles of those reads
-// were bank conflicts).
-constexpr int kLdsRowV = kRowBytes + 64;
-constexpr int kTileBytesV = kTile * kLdsRowV;
 
 __device__ __forceinline__ float max16(const f32x16& s) {
   float a = fmaxf(fmaxf(s[0], s[1]), s[2]);  // the compiler folds these into three-operand maxima
@@ -45,17 +38,6 @@ __device__ __forceinline__ float max16(const f32x16& s) {
 __device__ __forceinline__ uint2 lds_read_transposed(const char* p) {
   const v4i16 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(p));
   return __builtin_bit_cast(uint2, v);
-}
-
-// Per-lane byte offset of the transpose reads that build a V^T fragment (A operand: row = head dimension, 8 keys
-// per lane) from a row-major V tile: 16-lane group g = lane / 16 reads columns 16 * (g % 2) .. +15 of a
-// 32-column block and key rows 4 * (g / 2) .. +3; a second read 8 rows further down completes the 8 k-slots
-// (slots 0-3 = keys 4h..4h+3, slots 4-7 = keys 8+4h..8+4h+3 of a 16-key step, h = lane / 32: the order in which
-// the accumulator of a score tile holds its keys).
-__device__ __forceinline__ int transposed_fragment_offset() {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int i16 = lane & 15, grp = lane >> 4;
-  return ((grp >> 1) * 4 + (i16 >> 2)) * kLdsRowV + ((grp & 1) * 16 + (i16 & 3) * 4) * 2;
 }
 
 }  // namespace mfma

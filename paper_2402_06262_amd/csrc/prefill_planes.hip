@@ -66,7 +66,8 @@ template <int DT, int D, int ROWS> struct Planes {
   static constexpr int ROW = 2 * D;                         // bytes of a plane row
   static constexpr int PLANE = TR * ROW;
   static constexpr int TILE = NP * PLANE;
-  static constexpr int ROWV = ROW + 64;                     // V rows: transpose reads then hit distinct banks (mfma.hpp)
+  // V rows: a 16-lane group of a transpose read touches 4 rows x 32 bytes, which then lie on distinct banks
+  static constexpr int ROWV = ROW + 64;
   static constexpr int PLANEV = TR * ROWV;
   static constexpr int TILEV = NP * PLANEV;
   static constexpr int IN_ROW = D * (DT == kF32 ? 4 : 2);   // bytes of a row in memory

@@ -371,3 +371,14 @@ def test_grouped_and_block_steps_captured_in_a_hip_graph_replay_like_eager_steps
         torch.cuda.synchronize()
         for a, w in zip(snapshot(), want[r]):
             assert torch.equal(a, w), f"replay {r} differs from the eager calls"
+
+
+@pytest.mark.parametrize("B", [28, 32, 36, 64, 68, 100, 132, 196])
+@pytest.mark.parametrize("recency", [False, True])
+def test_edges_of_the_waves_tiles(B, recency, monkeypatch):
+    """bf16 / 128: waves stream 32-slot tiles of their own, two ahead.  Fills of 1 to B slots (no tile, one, an odd number for one
+    of the waves, a ragged last one), single tokens that overwrite a row of every tile, one and two tiles of query rows; one
+    workgroup per unit, so that a wave sees as many tiles as there are."""
+    monkeypatch.setenv("ROCO_BLOCK_SPLITS", "1")
+    blocks = [1, 8, 16, 3] + [16] * (B // 16) + [1] * 12 + [16, 9, 1]
+    drive(2, B, 7, 4, blocks, seed=B, recency=recency, tag=f"tiles-{B}-{recency}")
