@@ -212,6 +212,9 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
   a.ksplit = 1;
   a.shares = lay.shares;
   a.shares_to_add = 1;
+  a.lse_scale = 1.0f;
+  a.lse_given = nullptr;
+  a.row_bytes = 0;
   a.scale_log2 = scale_log2(params);
   a.recency_window = params->recency_window;
   a.recency_bias_log2 = params->recency_bias * 1.4426950408889634f;
@@ -232,10 +235,9 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
   // fp32 / 128 at 16 units x 48 tokens: 19 us against 29).
   const bool simple = env_int("ROCO_PREFILL_SIMPLE", 0) != 0 || (wide_bf16 && L_max > (1 << 22)) ||
                       (params->dtype == ROCO_F32 && L_max <= 64 && prefill_is_tiny(a, 524288.0));
-  if (want_lse) {  // the kernels keep base-2 normalisers
-    const size_t count = static_cast<size_t>(params->units) * group * L_max;
-    if (launch_lse_to_base2(lse_given, a.lse, count, s) != hipSuccess) return ROCO_EHIP;
-  }
+  // The kernels keep base-2 normalisers; the column pass of prefill_planes.hip rescales given ones itself.
+  a.lse_given = lse_given;
+  if (want_lse && (simple || a.pol.keeps_last_score()) && !rescale_given_lse(a, s)) return ROCO_EHIP;
   hipError_t e = simple      ? launch_prefill_attention_simple(params->dtype, params->head_dim, a, s)
                  : wide_bf16 ? launch_prefill_attention_mfma(a, s)
                              : launch_prefill_attention_planes(params->dtype, params->head_dim, a, s);

@@ -89,6 +89,7 @@ struct PrefillArgs {
   int qsplit;            // matrix-core path: workgroups that share a block of keys, each with a part of the queries (set by its launcher)
   int ksplit;            // matrix-core path, row pass: workgroups that share a block of queries (ditto)
   int shares;            // pairs of planes for column sums that the workspace has, 2 at least
+  int row_bytes;         // of K and V, for the selection (set by its launcher)
   int shares_to_add;     // > 1: the column sums lie in that many shares, which the selection adds (set by the passes' launcher)
   float scale_log2;
   int recency_window;
@@ -101,6 +102,8 @@ struct PrefillArgs {
   int32_t* next_slot;    // [units]
   void* O;               // may be null
   // workspace
+  const float* lse_given;  // roco_prefill_compress_lse: the caller's natural log-sum-exps until they have been rescaled to `lse`, else null
+  float lse_scale;         // what the column pass multiplies the normalisers by as it reads them: 1, or log2(e) for lse_given
   float* lse;            // [units][group][L_max]  base-2 log-sum-exp of every query row
   float* acc;            // [units][L_max]; acc, acc2, var_key, mas_key and what follows are planes of `plane` words side by side
   float* acc2;           // [units][L_max]
@@ -201,7 +204,14 @@ inline bool selection_adds_shares(const PrefillArgs& a, int shares) {
 void join_query_shares(PrefillArgs& a, const PrefillArgs& pass, hipStream_t s);
 // overwrites PrefillArgs::acc2 with the attention row of each unit's last prompt token (kImpLast)
 hipError_t launch_lse_to_base2(const float* lse_ln, float* lse_log2, size_t n, hipStream_t s);
+// writes PrefillArgs::lse from lse_given, if there is one left to rescale (one launch); false if the launch fails
+inline bool rescale_given_lse(PrefillArgs& a, hipStream_t s) {
+  if (a.lse_given == nullptr) return true;
+  const float* const given = a.lse_given;
+  a.lse_given = nullptr;
+  return launch_lse_to_base2(given, a.lse, static_cast<size_t>(a.units) * a.group * a.L_max, s) == hipSuccess;
+}
 hipError_t launch_prefill_last_row(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);
-hipError_t launch_prefill_select_compact(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s);
+hipError_t launch_prefill_select_compact(int dtype, int head_dim, PrefillArgs a, hipStream_t s);
 
 }  // namespace roco

@@ -1459,10 +1459,14 @@ void launch_rows(const PrefillArgs& a, hipStream_t s) {
   if (plan.split > 1) launch_merge_key_shares(b, s);
 }
 
-void launch_columns(PrefillArgs& a, hipStream_t s) {
+hipError_t launch_columns(PrefillArgs& a, hipStream_t s) {
   PassPlan plan;
   if (!plan_override(a, a.shares, plan)) plan = plan_columns(kBF16, D, a.units, a.group, a.L_max, a.shares);
-  if (!plan.wide) return launch_prefill_columns_planes_wide(a, plan, s);
+  if (!plan.wide) {
+    launch_prefill_columns_planes_wide(a, plan, s);
+    return hipGetLastError();
+  }
+  if (!rescale_given_lse(a, s)) return hipErrorLaunchFailure;
   ProfScope ps(kProfPrefillColumns, s);
   PrefillArgs b = a;
   b.paired = plan.paired; b.pairs = plan.ids; b.qsplit = plan.split;
@@ -1471,6 +1475,7 @@ void launch_columns(PrefillArgs& a, hipStream_t s) {
   else if (a.pol.counts_above_average()) hipLaunchKernelGGL(prefill_columns_mfma<true>, grid, dim3(4 * kWave), 0, s, b);
   else hipLaunchKernelGGL(prefill_columns_mfma<false>, grid, dim3(4 * kWave), 0, s, b);
   join_query_shares(a, b, s);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -1507,8 +1512,7 @@ hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s) {
   } else if (!a.skip_rows) {
     launch_rows(a, s);
   }
-  launch_columns(a, s);
-  return hipGetLastError();
+  return launch_columns(a, s);
 }
 
 }  // namespace roco

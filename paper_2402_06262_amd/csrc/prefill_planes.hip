@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kThreads, (kColumnWaves<DT, D, PARTS, HEADS>)) void
         ++seq;
         if (st.store(tile) && DT == kF32) odd_s[b] = seq;
         if (threadIdx.x < P::TR) {
-          lse_s[b][threadIdx.x] = st_lse;
+          lse_s[b][threadIdx.x] = st_lse * a.lse_scale;
           if (count && HEADS == 1) rinv_s[b][threadIdx.x] = 1.0f / static_cast<float>(t * P::TR + static_cast<int>(threadIdx.x) + 1);
         }
         __syncthreads();
@@ -874,6 +874,7 @@ void launch_columns(PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
   ProfScope ps(kProfPrefillColumns, s);
   PrefillArgs b = a;
   b.pairs = plan.ids; b.paired = plan.paired; b.qsplit = plan.split;
+  if (a.lse_given != nullptr) { b.lse = const_cast<float*>(a.lse_given); b.lse_scale = kLog2e; }  // read, never written here
   const unsigned n = mfma::workgroup_ids(a.units, plan.ids * plan.split);
   switch (plan.parts) {
     case 1: launch_columns_of_group<DT, D, 1>(b, n, s); break;

@@ -31,7 +31,8 @@ struct PassPlan {
 struct PlanRule {
   int resident;      // workgroups that run at a time, for rounds_split; 0: as many shares as bring paired_want workgroups
   int paired_want;   // workgroups that make pairs of blocks worth while
-  int paired_tiles;  // ... and the fewest tiles of a share of theirs
+  int paired_tiles;  // ... the fewest tiles of a share of theirs
+  int paired_split;  // ... and the most shares: beyond, single blocks of as many shares are twice the workgroups
   int single_want, single_tiles;  // the same for single blocks
   int most_parts;
 };
@@ -72,7 +73,7 @@ inline PassPlan plan_planes(long long streams, int L_max, const PlanRule& r, int
   PassPlan p = {false, 1, 1, 1, ceil_div(ceil_div(L_max, 128), 2)};
   const long long pairs = streams * p.ids;
   p.split = r.resident != 0 ? rounds_split(pairs, r.resident, tiles(1), 6.0, most_split) : power_of_two_from(r.paired_want, pairs);
-  if (p.split <= most_split && pairs * p.split >= r.paired_want && tiles(1) >= r.paired_tiles * p.split) return p;
+  if (p.split <= most_split && p.split <= r.paired_split && pairs * p.split >= r.paired_want && tiles(1) >= r.paired_tiles * p.split) return p;
   long long best = 0;
   for (int parts = 1; parts <= r.most_parts; parts *= 2) {
     const int ids = ceil_div(L_max, 128 / parts);
@@ -98,8 +99,8 @@ inline PassPlan plan_rows(int dtype, int head_dim, int units, int group, int L_m
     while (split > most_split) split /= 2;
     if (streams * ids * split >= 200 && ceil_div(L_max, 64) >= 8 * split) return {true, 1, split, 1, ids};
   }
-  const PlanRule r = dtype == 1 ? (head_dim == 64 ? PlanRule{0, 480, 2, 480, 2, 4} : PlanRule{0, 384, 4, 384, 3, 4})
-                                : (head_dim == 64 ? PlanRule{768, 480, 2, 1024, 3, 2} : PlanRule{512, 384, 6, 384, 3, 1});
+  const PlanRule r = dtype == 1 ? (head_dim == 64 ? PlanRule{0, 480, 2, 4, 480, 2, 4} : PlanRule{0, 384, 4, 4, 384, 3, 4})
+                                : (head_dim == 64 ? PlanRule{768, 480, 2, 4, 1024, 3, 2} : PlanRule{512, 384, 6, 4, 384, 3, 1});
   return plan_planes(streams, L_max, r, most_split,
                      [&](int parts) { return ceil_div(L_max, planes_tile_rows(dtype, head_dim, parts, false)); });
 }
@@ -111,8 +112,8 @@ inline PassPlan plan_columns(int dtype, int head_dim, int units, int group, int 
     const int split = rounds_split(static_cast<long long>(units) * ids, 512, tiles, 8.0, most_split);
     if (static_cast<long long>(units) * ids * split >= 250 && tiles >= 6 * split) return {true, 1, split, 1, ids};
   }
-  const PlanRule r = dtype == 1 ? (head_dim == 64 ? PlanRule{0, 1024, 4, 1024, 2, 4} : PlanRule{0, 360, 4, 480, 2, 4})
-                                : (head_dim == 64 ? PlanRule{768, 512, 2, 1024, 2, 2} : PlanRule{512, 512, 4, 480, 2, 2});
+  const PlanRule r = dtype == 1 ? (head_dim == 64 ? PlanRule{0, 1024, 4, 16, 1024, 2, 4} : PlanRule{0, 360, 4, 4, 480, 2, 4})
+                                : (head_dim == 64 ? PlanRule{768, 512, 2, 4, 1024, 2, 2} : PlanRule{512, 512, 4, 16, 480, 2, 2});
   return plan_planes(units, L_max, r, most_split, [&](int parts) {
     return column_tiles(planes_tile_rows(dtype, head_dim, parts, group > 1 && !heads_in_tile(group)), group, L_max);
   });

@@ -9,7 +9,7 @@
 //                     (radix select, no sorting), then an ordered prefix sum assigns cache slots and writes
 //                     pos[], the three statistics planes and n_used.
 //   prefill_gather  : grid (row blocks, units): copies the retained K / V rows into the cache, 16 bytes per
-//                     lane.
+//                     lane.  Few rows per unit are copied by prefill_select itself.
 #include "kernels.hpp"
 #include "profile.hpp"
 #include "stream.hpp"
@@ -27,9 +27,12 @@ constexpr int kGatherRows = 64;  // cache rows per gather workgroup
 // LDS: both keys of a token in LDS (2; up to 16384 tokens), the one of the scope (1; up to 32768), none (0).
 // MANY: the column sums lie in more than two shares (LDS = 2).  They are added once, by the thread that will need the sums again
 // when it compacts, and left in the first one's planes; for two shares reading both again is faster.
-template <int LDS, bool MANY>
+// GATHER: the retained K / V rows are copied here too, by way of the list of their positions in LDS (LDS = 2).  One launch less,
+// for units whose rows a compute unit copies in the time that a launch takes: see gathers_in_selection.
+template <int LDS, bool MANY, bool GATHER>
 __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) {
   constexpr int NT = kSelThreads;
+  static_assert(LDS == 2 || (!MANY && !GATHER), "the list and the sums replace keys in LDS");
   extern __shared__ uint32_t lds_keys[];  // [2][L_max] ranking keys when L_max <= kMaxDecodeBudgetLds
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint32_t scan_sh[NT / kWave + 1];
@@ -84,7 +87,6 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
   // Phase 0: the scope of the eviction; 1: the victims; 2: the scope of the first decode step, among the retained tokens
   // (whose keys do not change and whose order is that of their slots, so the compacted statistics need not be read back).
   KSmallest scope = {0u, 0u}, out = {0u, 0u}, next = {0u, 0u};
-  auto evicted = [&](int i) { return E > 0 && out.has(scope.has(var_key[i], i) ? mas_key[i] : 0xffffffffu, i); };
   if (n >= B) {
 #pragma unroll 1
     for (int phase = E > 0 ? 0 : 2; phase < 3; ++phase) {
@@ -120,7 +122,9 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
     const bool in = i < n;
     float2 s = make_float2(0.0f, 0.0f);
     if (in) s = sums(i);
-    const bool keep = in && !evicted(i);
+    // (the list of positions grows over keys that have been read: a token's own are read before the barrier)
+    const uint32_t vk = in && n >= B ? var_key[i] : 0u, mk = in && n >= B ? mas_key[i] : 0u;
+    const bool keep = in && !(E > 0 && out.has(scope.has(vk, i) ? mk : 0xffffffffu, i));
     const uint64_t votes = __builtin_amdgcn_ballot_w64(keep);
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     __syncthreads();  // the previous round's totals have been read
@@ -135,9 +139,11 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
       oacc[dst] = s.x;
       oacc2[dst] = s.y;
       ocnt[dst] = static_cast<float>(n - i);
-      if (n >= B && next.has(var_key[i], i)) {
-        const uint32_t k = mas_key[i];
-        if (k < best_key || best == 0xffffffffu) { best_key = k; best = static_cast<uint32_t>(i); best_slot = dst; }
+      if (GATHER) var_key[dst] = static_cast<uint32_t>(i);
+      if (n >= B && next.has(vk, i) && (mk < best_key || best == 0xffffffffu)) {
+        best_key = mk;
+        best = static_cast<uint32_t>(i);
+        best_slot = dst;
       }
     }
   }
@@ -147,6 +153,25 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
     oacc[i] = 0.0f;
     oacc2[i] = 0.0f;
     ocnt[i] = 0.0f;
+  }
+  if constexpr (GATHER) {
+    __syncthreads();  // the list is whole
+    const int lanes_log2 = __builtin_ctz(a.row_bytes) - 4;  // 16 bytes per lane, a power of two of lanes per row
+    const int rows = NT >> lanes_log2, col = (tid & ((1 << lanes_log2) - 1)) * 16;
+    const char* const Kin = static_cast<const char*>(a.K) + ubase * a.row_bytes + col;
+    const char* const Vin = static_cast<const char*>(a.V) + ubase * a.row_bytes + col;
+    char* const Kout = static_cast<char*>(a.K_cache) + static_cast<size_t>(u) * B * a.row_bytes + col;
+    char* const Vout = static_cast<char*>(a.V_cache) + static_cast<size_t>(u) * B * a.row_bytes + col;
+#pragma unroll 1
+    for (int slot = tid >> lanes_log2; slot < kept; slot += 2 * rows) {
+      const int other = min(slot + rows, kept - 1);  // (copied twice at the end: the same bytes)
+      const size_t src0 = static_cast<size_t>(var_key[slot]) * a.row_bytes, src1 = static_cast<size_t>(var_key[other]) * a.row_bytes;
+      const uint4 k0 = load16(Kin + src0), v0 = load16(Vin + src0), k1 = load16(Kin + src1), v1 = load16(Vin + src1);
+      *reinterpret_cast<uint4*>(Kout + static_cast<size_t>(slot) * a.row_bytes) = k0;
+      *reinterpret_cast<uint4*>(Vout + static_cast<size_t>(slot) * a.row_bytes) = v0;
+      *reinterpret_cast<uint4*>(Kout + static_cast<size_t>(other) * a.row_bytes) = k1;
+      *reinterpret_cast<uint4*>(Vout + static_cast<size_t>(other) * a.row_bytes) = v1;
+    }
   }
   if (tid == 0) a.n_used[u] = kept;
   if (kept < B) {
@@ -278,24 +303,34 @@ hipError_t launch_select_retained(const DecodeArgs& a, int keep, int32_t* mask, 
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_select_compact(int dtype, int head_dim, const PrefillArgs& a, hipStream_t s) {
+// Copying the rows in the selection saves a launch (2 us of host time, 4 us of the GPU's) and costs what one compute unit takes
+// for a unit's rows.  Whole call, us, in the selection against a kernel of its own, by KiB of K and V kept per unit: 32 (1 unit)
+// 15.8 / 19.0, 64 (165 units) 45.5 / 56.4, 138 (3) 23.3 / 25.6, 159 (34) 40.5 / 44.7, 250 (96) 102.9 / 109, but 364 (1) 103.7 /
+// 98.0 and 479 (3) 54.8 / 50.3.
+static bool gathers_in_selection(const PrefillArgs& a) { return 2ll * a.B * a.row_bytes <= 256 << 10; }
+
+hipError_t launch_prefill_select_compact(int dtype, int head_dim, PrefillArgs a, hipStream_t s) {
+  const int row_bytes = head_dim * (dtype == kBF16 ? 2 : 4);
+  a.row_bytes = row_bytes;
+  const bool gathered = key_lds_bytes(a.L_max) != 0 && gathers_in_selection(a);
   {
     ProfScope ps(kProfPrefillSelect, s);
     const size_t key_lds = key_lds_bytes(a.L_max);
     if (key_lds != 0) {
-      const auto kernel = a.shares_to_add > 2 ? prefill_select<2, true> : prefill_select<2, false>;
+      const auto kernel = gathered ? (a.shares_to_add > 2 ? prefill_select<2, true, true> : prefill_select<2, false, true>)
+                                   : (a.shares_to_add > 2 ? prefill_select<2, true, false> : prefill_select<2, false, false>);
       if (!allow_key_lds(reinterpret_cast<const void*>(kernel), key_lds)) return hipErrorInvalidValue;
       hipLaunchKernelGGL(kernel, dim3(a.units), dim3(kSelThreads), key_lds, s, a);
     } else if (a.L_max <= 2 * kMaxDecodeBudgetLds) {  // one key per token still fits (40 units x 32768 tokens: 125 us against 200)
       const size_t one = static_cast<size_t>(a.L_max) * sizeof(uint32_t);
-      if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<1, false>), one)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((prefill_select<1, false>), dim3(a.units), dim3(kSelThreads), one, s, a);
+      if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<1, false, false>), one)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((prefill_select<1, false, false>), dim3(a.units), dim3(kSelThreads), one, s, a);
     } else {
-      hipLaunchKernelGGL((prefill_select<0, false>), dim3(a.units), dim3(kSelThreads), 0, s, a);
+      hipLaunchKernelGGL((prefill_select<0, false, false>), dim3(a.units), dim3(kSelThreads), 0, s, a);
     }
   }
+  if (gathered) return hipGetLastError();
   ProfScope ps(kProfPrefillGather, s);
-  const int row_bytes = head_dim * (dtype == kBF16 ? 2 : 4);
   const dim3 grid((a.B + kGatherRows - 1) / kGatherRows, a.units);
   switch (row_bytes) {
     case 128: hipLaunchKernelGGL((prefill_gather<128>), grid, dim3(kGatherThreads), 0, s, a); break;

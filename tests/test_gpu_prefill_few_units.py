@@ -114,3 +114,12 @@ def test_shares_of_a_prompt_whose_keys_do_not_fit_the_lds():
     assert same > 0.9  # ties within rounding may move a token, and every slot behind it
     if same == 1.0:
         np.testing.assert_allclose(a.stats.cpu().numpy(), b.stats.cpu().numpy(), rtol=2e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("dtype,d,B", [("f32", 128, 256), ("f32", 128, 257), ("bf16", 64, 1024), ("bf16", 64, 1025), ("f32", 64, 1),
+                                       ("bf16", 128, 63)])
+def test_rows_copied_by_the_selection(dtype, d, B):
+    """Up to 256 KiB of kept rows per unit the selection copies them itself: at the limit and beyond it, one row, an odd number,
+    prompts shorter than the budget (nothing is ranked), one token."""
+    L = max(300, B + 90)
+    TP.run_workload(dtype, d, 5, [L, B, max(1, B - 1), 1, min(L, B + 1)], L, B, max(1, B // 3), 2, seed=B, tag=f"copy-{dtype}-{d}-{B}")
