@@ -50,7 +50,7 @@ static_assert(kMaxBlock == 2 * kQ, "a step holds at most two tiles of query rows
 // of the search: a launch starts with a cold instruction cache.
 template <int NT, bool LDS>
 __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
-  extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint32_t scan_sh[NT / kWave + 1];
   __shared__ int slot_of[kMaxBlock];
@@ -81,13 +81,22 @@ __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
   // one eviction from a full cache: the victim was already chosen when the statistics were last updated
   const int hint = (E == 1 && n == B) ? a.next_slot[u] : -1;
   if (E > 0 && hint < 0) {
+    // (B is a multiple of 4 on this path: four slots are inside the planes, and the keys behind the last slot are not read)
 #pragma unroll 1
-    for (int i = tid; i < n; i += NT) ranking_keys(acc[i], acc2[i], cnt[i], pos[i], a.pol, mas_key[i], var_key[i]);
+    for (int i = tid * 4; i < n; i += NT * 4) {
+      const float4 a1 = *reinterpret_cast<const float4*>(acc + i), a2 = *reinterpret_cast<const float4*>(acc2 + i);
+      const float4 cc = *reinterpret_cast<const float4*>(cnt + i);
+      const int4 pp = *reinterpret_cast<const int4*>(pos + i);
+      uint4 mk, vk;
+      ranking_keys<4>(&a1.x, &a2.x, &cc.x, &pp.x, a.pol, &mk.x, &vk.x);
+      *reinterpret_cast<uint4*>(mas_key + i) = mk;
+      *reinterpret_cast<uint4*>(var_key + i) = vk;
+    }
     __syncthreads();
     const uint32_t m = min(static_cast<uint32_t>(n), static_cast<uint32_t>(a.pol.scope_size(a.scope, n)) + static_cast<uint32_t>(E) - 1u);
 #pragma unroll 1
     for (int phase = 0; phase < 2; ++phase) {
-      const KSmallest r = select_k_smallest<NT, 1>(
+      const KSmallest r = select_k_smallest<NT, 1, 1>(
           [&](int i) -> uint32_t {
             const uint32_t vk = var_key[i];
             return phase == 0 ? vk : scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
@@ -707,7 +716,7 @@ template <int DT, int D, int R, bool LDS>
 __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   constexpr int NT = kFinThreads;
   constexpr int kSlots = 2 * NT;  // slots per sweep
-  extern __shared__ uint32_t lds_keys[];  // [2][B] ranking keys when B <= kMaxDecodeBudgetLds
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];  // [2][B] ranking keys when B <= kMaxDecodeBudgetLds
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint2 best_sh[NT / kWave];
   __shared__ float2 norm[kMaxBlock];  // reference and 1 / sum of every query row
@@ -840,13 +849,16 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   *reinterpret_cast<float2*>(acc + j) = make_float2(s1[0], s1[1]);
   *reinterpret_cast<float2*>(acc2 + j) = make_float2(s2[0], s2[1]);
   *reinterpret_cast<float2*>(cnt + j) = make_float2(sc[0], sc[1]);
-  if (full) {
+  if (full) {  // then both are slots of the unit
+    int pv[2] = {0, 0};
+    if (by_pos) {
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-      if (j + e < n)
-        ranking_keys(s1[e], s2[e], sc[e],
-                     j + e == fresh ? a.qpos0[u] : (by_pos ? a.pos[static_cast<size_t>(u) * B + j + e] : 0), a.pol,
-                     mas_key[j + e], var_key[j + e]);
+      for (int e = 0; e < 2; ++e) pv[e] = j + e == fresh ? a.qpos0[u] : a.pos[static_cast<size_t>(u) * B + j + e];
+    }
+    uint2 mk, vk;
+    ranking_keys<2>(s1, s2, sc, pv, a.pol, &mk.x, &vk.x);
+    *reinterpret_cast<uint2*>(mas_key + j) = mk;
+    *reinterpret_cast<uint2*>(var_key + j) = vk;
   }
   }
   // the victim a following single-token step would take

@@ -184,14 +184,17 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // ---------------------------------------------------------------- k-smallest selection
 // Non-negative IEEE floats order like their bit patterns read as uint32, so selection runs on
 // integers and is exact.  radix_select finds the k-th smallest key (k is 1-based, 1 <= k <= n) among
-// key_of(0..n-1), digits of 11, 11 and 10 bits from the top; it also returns how many keys are strictly smaller and how
-// many are equal.  What it costs is its barriers and its passes over the keys, so the first digit is wide: sign, exponent
-// and the two leading mantissa bits spread a unit's variances or scores over bins of a quarter octave, and usually few
-// enough keys share the chosen one that no second digit is counted -- as soon as a bin holds at most kSelectRanked keys they
-// are gathered and searched without another barrier.  A thread clears the bins it owns while it reads them, so a digit takes
-// three barriers.
+// key_of(0..n-1), digits of up to 11 bits from the top; it also returns how many keys are strictly smaller and how
+// many are equal.  What it costs is its barriers and its passes over the keys, so the first digit is wide: the exponent and
+// the three leading mantissa bits (no key has the top bit, the mark below apart) spread a unit's variances or scores over bins
+// of an eighth of an octave, and usually few enough keys share the chosen one that no second digit is counted -- as soon as a
+// bin holds at most kSelectRanked keys they are gathered and searched without another barrier.  A thread clears the bins it
+// owns while it reads them, so a digit takes three barriers.
+// AHEAD: keys per thread that a pass requests before it uses the first: four where they come from memory, and from LDS with few
+// threads (the step of 512 units x 2048 slots of bf16 / 128: 95.6 -> 94.1 us); with 1024 threads other waves fill the time, and
+// the longer code has to be fetched.
 // The largest key, 0xffffffff, is the mark of elements that do not take part: it is neither counted (thousands of additions
-// to one bin would be served one after the other) nor gathered, also where its neighbours, the keys of attention sinks, are.
+// to one bin would be served one after the other) nor gathered.
 // `small`: the keys are small numbers, positions or indices: the digits then start at the highest bit that is set in any of
 // them, which takes one more pass over the keys.  From the top they would all share the first bins, whose counts are served
 // one key after the other, and the search among the last candidates would walk through twenty empty bits (step of 4 heads on
@@ -208,8 +211,26 @@ template <int PER_WORD> struct SelectLds {
 };
 static_assert(kSelectRanked == 2 * kWave, "two candidates per lane");
 
-// UNROLL: of the passes over the keys, 1 for keys in LDS (short code), more where they come from memory.
-template <int NT, int UNROLL, int PER_WORD, class KeyFn>
+// f(key) for every key of this thread, in no particular order.
+template <int NT, int AHEAD, class KeyFn, class F>
+__device__ __forceinline__ void for_each_key(KeyFn key_of, int n, int tid, F f) {
+  if (AHEAD == 1 || n <= NT) {
+#pragma unroll 1
+    for (int i = tid; i < n; i += NT) f(key_of(i));
+    return;
+  }
+#pragma unroll 1
+  for (int i = tid; i < n; i += AHEAD * NT) {
+    uint32_t key[AHEAD];
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) key[j] = key_of(min(i + j * NT, n - 1));
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j)
+      if (i + j * NT < n) f(key[j]);
+  }
+}
+
+template <int NT, int PER_WORD, int AHEAD, class KeyFn>
 __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, bool small, uint32_t* sh,
                              uint32_t& kth, uint32_t& n_less, uint32_t& n_equal) {
   static_assert(NT <= 1024 && kSelectBins % NT == 0, "whole bins per thread");
@@ -224,16 +245,12 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, bo
   for (int i = 0; i < OWN_WORDS; ++i) sh[tid * OWN_WORDS + i] = 0;
   if (small) {
     uint32_t any = 0;
-#pragma unroll UNROLL
-    for (int i = tid; i < n; i += NT) {
-      const uint32_t key = key_of(i);
-      any |= key != 0xffffffffu ? key : 0u;
-    }
+    for_each_key<NT, AHEAD>(key_of, n, tid, [&](uint32_t key) { any |= key != 0xffffffffu ? key : 0u; });
     any = wave_or(any);
     if (lane == 0) wtot[wave] = any;
   }
   __syncthreads();
-  int top = 32;  // bits that are still to be counted
+  int top = 31;  // bits that are still to be counted
   if (small) top = 32 - __builtin_clz(wave_or(lane < NT / kWave ? wtot[lane] : 0u) | 1u);
   uint32_t prefix = 0, mask = 0, kk = k, less = 0, neq = 0;
   auto takes_part = [&](uint32_t key) { return (key & mask) == prefix && key != 0xffffffffu; };
@@ -242,12 +259,10 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, bo
     const int shift = max(top - 11, 0);
     const uint32_t digit = (1u << (top - shift)) - 1u;
     top = shift;
-#pragma unroll UNROLL
-    for (int i = tid; i < n; i += NT) {
-      const uint32_t key = key_of(i);
+    for_each_key<NT, AHEAD>(key_of, n, tid, [&](uint32_t key) {
       const uint32_t bin = (key >> shift) & digit;
       if (takes_part(key)) atomicAdd(&sh[bin / PER_WORD], PER_WORD == 2 ? 1u << (16 * (bin & 1)) : 1u);
-    }
+    });
     __syncthreads();
     uint32_t h[OWN], sum = 0;
 #pragma unroll
@@ -294,11 +309,9 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int n, uint32_t k, bo
       // is left.  Up to four waves all do this, without a barrier; more would share the schedulers with one another, so
       // the first one leaves the answer to the others (16 tokens on 64 units x 512 slots: 35.3 -> 32.4 us).
       constexpr bool kOneWave = NT > 4 * kWave;
-#pragma unroll UNROLL
-      for (int i = tid; i < n; i += NT) {
-        const uint32_t key = key_of(i);
+      for_each_key<NT, AHEAD>(key_of, n, tid, [&](uint32_t key) {
         if (takes_part(key)) sh[atomicAdd(&res[3], 1u)] = key;
-      }
+      });
       __syncthreads();
       if (!kOneWave || wave == 0) {
         const uint32_t c0 = sh[lane], c1 = sh[lane + kWave];
@@ -346,19 +359,79 @@ struct KSmallest {
   }
 };
 
-template <int NT, int PER_WORD, int UNROLL = 1, class KeyFn>
-__device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, bool small, uint32_t* sh) {
+// Up to kCountedKeys keys are not searched: every thread counts which of them do not follow its own, 64 at a time, and the one
+// that counts k is the last of the k smallest.  Two instructions per pair of keys instead of four barriers, the bins and the chain of
+// the search among the last candidates (128 keys in four waves 4800 -> 3100 cycles, 256 in
+// sixteen 5400 -> 4700).  Keys that are equal come in the order of their blocks; inside a block
+// they all count the same number, so if the boundary falls among such keys nobody counts k: false, and the search has to say
+// which of them belong.
+constexpr int kCountedKeys = 256;
+template <int NT, class KeyFn>
+__device__ __forceinline__ bool count_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t* sh, KSmallest& r) {
+  static_assert(NT % kCountedKeys == 0 && kCountedKeys % (2 * kWave) == 0, "whole waves count for a block of keys");
+  uint32_t* const counts = sh + kCountedKeys;
+  uint32_t* const res = counts + kCountedKeys;  // the key, 1 + its index
+  const int width = n <= kCountedKeys / 2 ? kCountedKeys / 2 : kCountedKeys;
+  const int parts = NT / width;  // threads that share the counting for a key
+  const int tid = late_thread_id(), mine = tid & (width - 1);
+  const int my_block = __builtin_amdgcn_readfirstlane(mine / kWave), part = __builtin_amdgcn_readfirstlane(tid / width);
+  __syncthreads();  // `sh` may still be in use by a previous call
+  if (tid < kCountedKeys) {
+    sh[tid] = tid < n ? key_of(tid) : 0xffffffffu;
+    counts[tid] = 0;
+  }
+  if (tid == 0) res[1] = 0;
+  __syncthreads();
+  const uint32_t key = sh[mine];
+  uint32_t count = 0;
+  if (my_block * kWave < n) {
+#pragma unroll 1
+    for (int block = part; block * kWave < n; block += parts) {
+      const uint4* const others = reinterpret_cast<const uint4*>(sh + block * kWave);
+      if (block <= my_block) {
+#pragma unroll 4
+        for (int j = 0; j < kWave / 4; ++j) {
+          const uint4 o = others[j];
+          count += (o.x <= key) + (o.y <= key) + (o.z <= key) + (o.w <= key);
+        }
+      } else {
+#pragma unroll 4
+        for (int j = 0; j < kWave / 4; ++j) {
+          const uint4 o = others[j];
+          count += (o.x < key) + (o.y < key) + (o.z < key) + (o.w < key);
+        }
+      }
+    }
+    if (parts > 1) atomicAdd(&counts[mine], count);
+  }
+  if (parts > 1) {
+    __syncthreads();
+    count = counts[mine];
+  }
+  if (part == 0 && mine < n && count == k && key != 0xffffffffu) {
+    res[0] = key;
+    atomicMax(&res[1], static_cast<uint32_t>(mine) + 1u);
+  }
+  __syncthreads();
+  if (res[1] == 0) return false;
+  r = KSmallest{res[0], res[1] - 1u};
+  return true;
+}
+
+template <int NT, int PER_WORD, int AHEAD, class KeyFn>
+__device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, bool small, uint32_t* sh) {
   // everything is wanted (the policies whose scope is the whole cache, say): nothing to select
   if (k >= static_cast<uint32_t>(n)) return KSmallest{0xffffffffu, 0xffffffffu};
   // At most two rounds through one copy of the search (these kernels start cold: a second copy is instructions to fetch):
   // the k-th smallest key, then, if ties straddle the boundary, which of the equal keys belong: the lowest indices.
   KSmallest r = {0u, 0xffffffffu};
+  if (n <= kCountedKeys && count_k_smallest<NT>(key_of, n, k, sh, r)) return r;
   uint32_t take = k;
 #pragma unroll 1
   for (int round = 0; round < 2; ++round) {
     const uint32_t kth = r.kth;
     uint32_t found, n_less, n_equal;
-    radix_select<NT, UNROLL, PER_WORD>(
+    radix_select<NT, PER_WORD, AHEAD>(
         [&](int i) {
           const uint32_t key = key_of(i);
           return round == 0 ? key : key == kth ? static_cast<uint32_t>(i) : 0xffffffffu;
@@ -378,10 +451,10 @@ __device__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, bool sma
 // Scope = `scope` lowest variance keys among [0, B); returns the slot of lowest MAS key inside it (lowest
 // slot on equal keys).  Every thread of the block calls it and gets the same answer.
 template <int NT, int PER_WORD>
-__device__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, const Policy& pol, int scope,
+__device__ __forceinline__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, const Policy& pol, int scope,
                                    uint32_t* sel_sh, uint2* best_sh) {
   const int tid = late_thread_id();
-  const KSmallest sc = select_k_smallest<NT, PER_WORD>([&](int i) { return var_key[i]; }, B,
+  const KSmallest sc = select_k_smallest<NT, PER_WORD, NT <= 4 * kWave ? 4 : 1>([&](int i) { return var_key[i]; }, B,
                                              static_cast<uint32_t>(pol.scope_size(scope, B)), pol.scope_is_window(), sel_sh);
   uint32_t key = 0xffffffffu, idx = 0xffffffffu;
 #pragma unroll 1
@@ -399,29 +472,45 @@ __device__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_
 // For RoCo these are the mean attention score and the attention variance, each operation rounded on its own
 // (no fused multiply-add), so that a single observation gives a variance of exactly zero:
 //   MAS = Acc/Count,  Var = max(0, Acc2/Count - MAS^2)          (section 4.3 of the paper)
-// A protected sink position gets the largest importance key below the marker 0xffffffff that the selections
-// use for "outside the scope".
+// A protected sink position gets the largest importance key without the top bit, which the search leaves out; 0xffffffff is the
+// marker that the selections use for "outside the scope".
+// N tokens at a time: the policy is asked for once, and the divisions, chains of ten dependent instructions, run side by side.
+template <int N>
+__device__ __forceinline__ void ranking_keys(const float* acc, const float* acc2, const float* count, const int* pos,
+                                             const Policy& pol, uint32_t* mas_key, uint32_t* var_key) {
+  const bool by_variance = pol.scope_kind == kScopeStd;
+  float mas[N];
+  if (by_variance || pol.importance == kImpMas) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      mas[e] = __fdiv_rn(acc[e], count[e]);
+      mas_key[e] = __float_as_uint(mas[e]) & 0x7fffffffu;
+    }
+  }
+  if (by_variance) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const float ex2 = __fdiv_rn(acc2[e], count[e]);
+      const float var = __fsub_rn(ex2, __fmul_rn(mas[e], mas[e]));
+      var_key[e] = var > 0.0f ? __float_as_uint(var) : 0u;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) var_key[e] = pol.scope_kind == kScopeWindow ? static_cast<uint32_t>(pos[e]) : 0u;
+  }
+  if (pol.importance != kImpMas) {
+    const bool oldest = pol.importance == kImpOldest, accumulated = pol.importance == kImpAas;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const float score = accumulated ? acc[e] : acc2[e];
+      mas_key[e] = oldest ? (pos[e] < pol.sinks ? 0x7fffffffu : static_cast<uint32_t>(pos[e]))
+                          : score > 0.0f ? __float_as_uint(score) : 0u;
+    }
+  }
+}
 __device__ __forceinline__ void ranking_keys(float acc, float acc2, float count, int pos, const Policy& pol,
                                              uint32_t& mas_key, uint32_t& var_key) {
-  const bool by_variance = pol.scope_kind == kScopeStd;
-  float mas = 0.0f;
-  if (by_variance || pol.importance == kImpMas) mas = __fdiv_rn(acc, count);
-  if (pol.importance == kImpMas) {
-    mas_key = __float_as_uint(mas);
-  } else if (pol.importance == kImpOldest) {
-    mas_key = pos < pol.sinks ? 0xfffffffeu : static_cast<uint32_t>(pos);
-  } else {
-    const float score = pol.importance == kImpAas ? acc : acc2;
-    mas_key = score > 0.0f ? __float_as_uint(score) : 0u;
-  }
-  var_key = 0u;
-  if (by_variance) {
-    const float ex2 = __fdiv_rn(acc2, count);
-    const float var = __fsub_rn(ex2, __fmul_rn(mas, mas));
-    if (var > 0.0f) var_key = __float_as_uint(var);
-  } else if (pol.scope_kind == kScopeWindow) {
-    var_key = static_cast<uint32_t>(pos);
-  }
+  ranking_keys<1>(&acc, &acc2, &count, &pos, pol, &mas_key, &var_key);
 }
 
 }  // namespace roco

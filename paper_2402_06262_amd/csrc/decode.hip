@@ -138,17 +138,26 @@ __device__ __forceinline__ void update_four(float4& a1, float4& a2, float4& cc, 
     pv[0] = pp.x; pv[1] = pp.y; pv[2] = pp.z; pv[3] = pp.w;
   }
   float s1[4] = {a1.x, a1.y, a1.z, a1.w}, s2[4] = {a2.x, a2.y, a2.z, a2.w}, sc[4] = {cc.x, cc.y, cc.z, cc.w};
+  const bool squares = !sk.pol.keeps_last_score() && !sk.pol.counts_above_average();
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int jj = j + e;
-    if (jj < n) {
-      if (jj == slot) { s1[e] = 0.0f; s2[e] = 0.0f; sc[e] = 0.0f; }
-      const float p = fast_exp2(zv[e] - M) * inv;
-      s1[e] += p;
-      s2[e] = sk.pol.second_statistic(s2[e], p, static_cast<float>(n));
-      sc[e] += 1.0f;
-      if (full) ranking_keys(s1[e], s2[e], sc[e], jj == slot ? sk.qpos : pv[e], sk.pol, mas_key[jj], var_key[jj]);
-    }
+    const bool fresh = j + e == slot;
+    // (behind the last slot: the logit is whatever the buffer holds, and the statistics stay)
+    const float p = fast_exp2(zv[e] - M) * inv;
+    const float t1 = (fresh ? 0.0f : s1[e]) + p, old2 = fresh ? 0.0f : s2[e];
+    const float t2 = squares ? old2 + p * p : sk.pol.second_statistic(old2, p, static_cast<float>(n));
+    const float tc = (fresh ? 0.0f : sc[e]) + 1.0f;
+    pv[e] = fresh ? sk.qpos : pv[e];
+    const bool in = j + e < n;
+    s1[e] = in ? t1 : s1[e];
+    s2[e] = in ? t2 : s2[e];
+    sc[e] = in ? tc : sc[e];
+  }
+  if (full) {  // then all four are slots of the unit
+    uint4 mk, vk;
+    ranking_keys<4>(s1, s2, sc, pv, sk.pol, &mk.x, &vk.x);
+    *reinterpret_cast<uint4*>(mas_key + j) = mk;
+    *reinterpret_cast<uint4*>(var_key + j) = vk;
   }
   a1 = make_float4(s1[0], s1[1], s1[2], s1[3]);
   a2 = make_float4(s2[0], s2[1], s2[2], s2[3]);
@@ -220,7 +229,7 @@ __device__ __forceinline__ void update_statistics(float* acc, float* acc2, float
 // LDS: the ranking keys are in LDS (B <= kMaxDecodeBudgetLds).  kPerWord: see radix_select.
 template <int DT, int D, int NT, bool LDS, int kPerWord>
 __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
-  extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<kPerWord>::kWords];
   __shared__ uint2 best_sh[NT / kWave];
   float* const mrg_o = reinterpret_cast<float*>(sel_sh);  // [NT / D][D]: the output is done before the search begins
@@ -416,7 +425,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kFinishThreads) void select_victims(DecodeArgs a) {
   constexpr int NT = kFinishThreads;
-  extern __shared__ uint32_t lds_keys[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint2 best_sh[NT / kWave];
   const int u = blockIdx.x, tid = threadIdx.x;

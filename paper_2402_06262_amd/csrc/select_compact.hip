@@ -33,7 +33,7 @@ template <int LDS, bool MANY, bool GATHER>
 __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) {
   constexpr int NT = kSelThreads;
   static_assert(LDS == 2 || (!MANY && !GATHER), "the list and the sums replace keys in LDS");
-  extern __shared__ uint32_t lds_keys[];  // [2][L_max] ranking keys when L_max <= kMaxDecodeBudgetLds
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];  // [2][L_max] ranking keys when L_max <= kMaxDecodeBudgetLds
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint32_t scan_sh[NT / kWave + 1];
   __shared__ uint2 best_sh[NT / kWave];
@@ -65,7 +65,6 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
   // every radix pass reads every key: in LDS they cost a fraction of a trip to the L2 each
   uint32_t* const var_key = LDS > 0 ? lds_keys : a.var_key + ubase;
   uint32_t* const mas_key = LDS == 2 ? lds_keys + a.L_max : a.mas_key + ubase;
-  constexpr int kUnroll = LDS == 2 ? 1 : 4;
   float* oacc = a.stats + static_cast<size_t>(u) * 3 * B;
   float* oacc2 = oacc + B;
   float* ocnt = oacc2 + B;
@@ -74,13 +73,32 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
   const int kept = n < B ? n : B;
   const uint32_t E = static_cast<uint32_t>(n - kept);
   if (n >= B) {
-#pragma unroll kUnroll
-    for (int i = tid; i < n; i += NT) {
-      uint32_t mk, vk;
-      const float2 s = sums(i);
-      ranking_keys(s.x, s.y, static_cast<float>(n - i), i, a.pol, mk, vk);
-      var_key[i] = vk;
-      mas_key[i] = mk;
+    auto make_keys = [&](int first, auto tokens) {  // the sums of all tokens are requested before the first is used
+      constexpr int N = decltype(tokens)::value;
+      float s1[N], s2[N], count[N];
+      int p[N];
+      uint32_t mk[N], vk[N];
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        p[e] = min(first + e * NT, n - 1);
+        const float2 s = sums(p[e]);
+        s1[e] = s.x; s2[e] = s.y;
+        count[e] = static_cast<float>(n - p[e]);
+      }
+      ranking_keys<N>(s1, s2, count, p, a.pol, mk, vk);
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        if (first + e * NT < n) {
+          var_key[p[e]] = vk[e];
+          mas_key[p[e]] = mk[e];
+        }
+      }
+    };
+    if (n <= NT) {
+      if (tid < n) make_keys(tid, std::integral_constant<int, 1>{});
+    } else {
+#pragma unroll 1
+      for (int i = tid; i < n; i += 4 * NT) make_keys(i, std::integral_constant<int, 4>{});
     }
     __syncthreads();
   }
@@ -97,7 +115,7 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
         next = KSmallest{0xffffffffu, 0xffffffffu};
         break;
       }
-      const KSmallest r = select_k_smallest<NT, 1, kUnroll>(
+      const KSmallest r = select_k_smallest<NT, 1, LDS == 2 ? 1 : 4>(
           [&](int i) -> uint32_t {
             const uint32_t vk = var_key[i];
             if (phase == 0) return vk;
@@ -116,12 +134,13 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
   uint32_t best_key = 0xffffffffu, best = 0xffffffffu;  // importance and position of the first decode victim
   uint32_t before = 0;  // retained tokens of earlier rounds
   uint32_t best_slot = 0;
+  float2 ahead = sums(min(tid, max(n - 1, 0)));  // of the next round: a trip to memory that its barriers hide
 #pragma unroll 1
   for (int base = 0; base < n; base += NT) {
     const int i = base + tid;
     const bool in = i < n;
-    float2 s = make_float2(0.0f, 0.0f);
-    if (in) s = sums(i);
+    const float2 s = ahead;
+    if (base + NT < n) ahead = sums(min(i + NT, n - 1));
     // (the list of positions grows over keys that have been read: a token's own are read before the barrier)
     const uint32_t vk = in && n >= B ? var_key[i] : 0u, mk = in && n >= B ? mas_key[i] : 0u;
     const bool keep = in && !(E > 0 && out.has(scope.has(vk, i) ? mk : 0xffffffffu, i));
@@ -214,7 +233,7 @@ __global__ __launch_bounds__(kGatherThreads) void prefill_gather(PrefillArgs a) 
 // for empty slots.
 __global__ __launch_bounds__(kSelThreads) void select_retained(DecodeArgs a, int keep, int32_t* mask_out) {
   constexpr int NT = kSelThreads;
-  extern __shared__ uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B;
@@ -236,9 +255,9 @@ __global__ __launch_bounds__(kSelThreads) void select_retained(DecodeArgs a, int
   for (int i = tid; i < n; i += NT)
     ranking_keys(acc[i], acc2[i], cnt[i], by_pos ? pos[i] : 0, a.pol, mas_key[i], var_key[i]);
   __syncthreads();
-  const KSmallest scope = select_k_smallest<NT, 1>([&](int i) { return var_key[i]; }, n, m, a.pol.scope_is_window(), sel_sh);
+  const KSmallest scope = select_k_smallest<NT, 1, 1>([&](int i) { return var_key[i]; }, n, m, a.pol.scope_is_window(), sel_sh);
   auto key2 = [&](int i) -> uint32_t { return scope.has(var_key[i], i) ? mas_key[i] : 0xffffffffu; };
-  const KSmallest out = select_k_smallest<NT, 1>(key2, n, E, false, sel_sh);
+  const KSmallest out = select_k_smallest<NT, 1, 1>(key2, n, E, false, sel_sh);
   for (int i = tid; i < B; i += NT) mask[i] = (i < n && !out.has(key2(i), i)) ? 1 : 0;
 }
 

@@ -250,3 +250,9 @@ def test_window_scopes_over_positions_of_every_size(n, top):
             want = np.ones(n, np.int32)
             want[orc.select_evictions(acc[u].astype(np.float64), pos[u].astype(np.float64), scope, n - keep)] = 0
             assert np.array_equal(mask[u].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("kind", ["equal", "low_bits", "middle_bits", "two_values", "wide"])
+@pytest.mark.parametrize("n", [65, 127, 130, 192, 255, 256, 257])
+def test_few_keys_are_counted(kind, n):
+    test_lowest_keys_go_first_and_ties_by_slot(kind, n)
