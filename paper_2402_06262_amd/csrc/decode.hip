@@ -30,6 +30,25 @@ constexpr int kAttendWaves = kAttendThreads / kWave;
 constexpr int kFinishThreads = kDecodeSelectThreads;
 constexpr int kFusedThreads = 256;  // with 8 rows in flight per lane group: two workgroups per compute unit
 
+// The new token's rows in LDS, a copy per wave: the wave whose block holds their slot finds them at hand, where a load would be
+// two trips to memory in the middle of its stream, each behind the rows that are already under way.  They are requested before the
+// stream's first loads and stored once those are under way.
+template <int DT, int D> struct NewRows {
+  using G = RowGeom<DT, D>;
+  static constexpr int kWords = 2 * G::ROW_BYTES / 4;  // per wave
+  uint4 k, v;
+  __device__ __forceinline__ void load(const DecodeArgs& a, size_t in_off) {
+    k = load16(static_cast<const char*>(a.k_new) + in_off);
+    v = load16(static_cast<const char*>(a.v_new) + in_off);
+  }
+  __device__ __forceinline__ void keep(uint32_t* mine, int c) const {  // (every group of lanes stores the same)
+    *reinterpret_cast<uint4*>(mine + c * 4) = k;
+    *reinterpret_cast<uint4*>(mine + kWords / 2 + c * 4) = v;
+  }
+  static __device__ __forceinline__ uint4 k_of(const uint32_t* mine, int c) { return *reinterpret_cast<const uint4*>(mine + c * 4); }
+  static __device__ __forceinline__ uint4 v_of(const uint32_t* mine, int c) { return *reinterpret_cast<const uint4*>(mine + kWords / 2 + c * 4); }
+};
+
 // ------------------------------------------------------------------------------------------------
 // BIAS: a recency bias is in force; STREAMING: non-temporal loads.  They are template parameters, not branches inside
 // one kernel, to keep each kernel's code (the unrolled, software-pipelined stream) small.
@@ -40,6 +59,8 @@ __global__ __launch_bounds__(kAttendThreads) void decode_attend(DecodeArgs a) {
   constexpr int PASS = kAttendWaves * U * G::R;
   __shared__ float sm_m[STREAMS], sm_l[STREAMS];
   __shared__ float sm_acc[STREAMS][D];
+  using New = NewRows<DT, D>;
+  __shared__ __attribute__((aligned(16))) uint32_t sm_new[STREAMS][New::kWords];
 
   const int u = blockIdx.y, split = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -50,8 +71,11 @@ __global__ __launch_bounds__(kAttendThreads) void decode_attend(DecodeArgs a) {
   const int n = full ? a.B : n0 + 1;
   const int row0 = split * a.rows_per_split;
   const int row1 = min(n, row0 + a.rows_per_split);
+  uint32_t* const new_rows = sm_new[wave];
 
   const size_t in_off = static_cast<size_t>(u) * G::ROW_BYTES + c * 16;
+  New fresh;
+  fresh.load(a, in_off);
   float qf[G::EPL];
   unpack16<DT>(load16(static_cast<const char*>(a.q) + in_off), qf);
 #pragma unroll
@@ -74,13 +98,13 @@ __global__ __launch_bounds__(kAttendThreads) void decode_attend(DecodeArgs a) {
   // in-place overwrite of the slot the new token takes: the cache never grows past B
   auto fix_k = [&](int row, uint4& kw, int col) {
     if (row == slot && row < row1) {
-      kw = load16(static_cast<const char*>(a.k_new) + in_off);
+      kw = New::k_of(new_rows, col);
       *reinterpret_cast<uint4*>(Kb + static_cast<size_t>(row) * G::ROW_BYTES + col * 16) = kw;
     }
   };
   auto fix_v = [&](int row, uint4& vw, int col) {
     if (row == slot && row < row1) {
-      vw = load16(static_cast<const char*>(a.v_new) + in_off);
+      vw = New::v_of(new_rows, col);
       *reinterpret_cast<uint4*>(Vb + static_cast<size_t>(row) * G::ROW_BYTES + col * 16) = vw;
     }
   };
@@ -89,8 +113,8 @@ __global__ __launch_bounds__(kAttendThreads) void decode_attend(DecodeArgs a) {
   const int rot = passes > 0 ? static_cast<int>((static_cast<unsigned>(u) * 5u + static_cast<unsigned>(split) * 3u) %
                                                 static_cast<unsigned>(passes))
                              : 0;
-  stream_attend<DT, D, U, BIAS, STREAMING>(qf, Kb, Vb, row0, row1, passes, a.rotate ? rot : 0, PASS, wave * (U * G::R),
-                                           bias, pos, z, slot, fix_k, fix_v, st);
+  stream_attend<DT, D, U, BIAS, STREAMING>(qf, Kb, Vb, row0, row1, row1, passes, a.rotate ? rot : 0, PASS, wave * (U * G::R),
+                                           bias, pos, z, slot, fix_k, fix_v, [&] { fresh.keep(new_rows, c); }, st);
   merge_groups_in_wave<DT, D>(st);
 
   if (lane < G::LPR) {
@@ -325,8 +349,10 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<2>::kWords];
   __shared__ uint2 best_sh[WAVES];
   __shared__ float sm_m[WAVES], sm_l[WAVES];
-  float* const sm_acc = reinterpret_cast<float*>(sel_sh);  // [WAVES][D]: the output is done before the search begins
-  static_assert(WAVES * D <= SelectLds<2>::kWords, "the waves' sums fit the search's words");
+  // a wave's words: the new token's rows while it streams, then its sums; the output is done before the search begins
+  using New = NewRows<DT, D>;
+  static_assert(New::kWords >= D && WAVES * New::kWords <= SelectLds<2>::kWords, "the waves' rows and sums fit the search's words");
+  float* const sm_acc = reinterpret_cast<float*>(sel_sh);
 
   const int u = blockIdx.x;
   const int stream_wave = static_cast<int>(threadIdx.x) / kWave;
@@ -340,8 +366,11 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   uint32_t* var_key = lds_dyn;
   uint32_t* mas_key = var_key + B;
   float* z = reinterpret_cast<float*>(lds_dyn + 2 * static_cast<size_t>(B));
+  uint32_t* const new_rows = sel_sh + stream_wave * New::kWords;
 
   const size_t in_off = static_cast<size_t>(u) * G::ROW_BYTES + c * 16;
+  New fresh;
+  fresh.load(a, in_off);
   float qf[G::EPL];
   unpack16<DT>(load16(static_cast<const char*>(a.q) + in_off), qf);
 #pragma unroll
@@ -351,7 +380,6 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   char* Vb = static_cast<char*>(a.V) + static_cast<size_t>(u) * B * G::ROW_BYTES;
   int32_t* pos = a.pos + static_cast<size_t>(u) * B;
   const int qp = a.qpos[u];
-  const int old_pos = pos[slot];
   const int w = a.recency_window;
   const float rb = a.recency_bias_log2;
 
@@ -359,7 +387,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   constexpr int PF = 512 / NT;  // covers B <= 2048; larger budgets load the rest after the stream
   StatsAhead<NT, PF> ahead;
   const bool vec = (B & 3) == 0;
-  if (vec) ahead.load(acc, acc + B, acc + 2 * static_cast<size_t>(B), n);
+  if (vec) ahead.load(acc, acc + B, acc + 2 * static_cast<size_t>(B), B);
 
   FlashState<G::EPL> st;
   st.reset();
@@ -369,27 +397,33 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   };
   auto fix_k = [&](int row, uint4& kw, int col) {
     if (row == slot && row < n) {
-      kw = load16(static_cast<const char*>(a.k_new) + in_off);
+      kw = New::k_of(new_rows, col);
       *reinterpret_cast<uint4*>(Kb + static_cast<size_t>(row) * G::ROW_BYTES + col * 16) = kw;
     }
   };
   auto fix_v = [&](int row, uint4& vw, int col) {
     if (row == slot && row < n) {
-      vw = load16(static_cast<const char*>(a.v_new) + in_off);
+      vw = New::v_of(new_rows, col);
       *reinterpret_cast<uint4*>(Vb + static_cast<size_t>(row) * G::ROW_BYTES + col * 16) = vw;
     }
   };
   const int passes = (n + PASS - 1) / PASS;
   const int rot = a.rotate ? static_cast<int>((static_cast<unsigned>(u) * 5u) % static_cast<unsigned>(passes)) : 0;
-  stream_attend<DT, D, U, BIAS, STREAMING>(qf, Kb, Vb, 0, n, passes, rot, PASS, stream_wave * (U * G::R), bias, pos, z, slot,
-                                           fix_k, fix_v, st);
+  int old_pos = 0;
+  stream_attend<DT, D, U, BIAS, STREAMING>(qf, Kb, Vb, 0, n, B, passes, rot, PASS, stream_wave * (U * G::R), bias, pos, z, slot,
+                                           fix_k, fix_v,
+                                           [&] {
+                                             fresh.keep(new_rows, c);
+                                             old_pos = pos[slot];
+                                           },
+                                           st);
   merge_groups_in_wave<DT, D>(st);
 
   const int tid = late_thread_id(), lane = tid & (kWave - 1), wave = tid / kWave;
   if (lane < G::LPR) {
     if (lane == 0) { sm_m[wave] = st.m; sm_l[wave] = st.l; }
 #pragma unroll
-    for (int e = 0; e < G::EPL; ++e) sm_acc[wave * D + lane * G::EPL + e] = st.acc[e];
+    for (int e = 0; e < G::EPL; ++e) sm_acc[wave * New::kWords + lane * G::EPL + e] = st.acc[e];
   }
   __syncthreads();  // also orders the waves' logit stores before the reads below
   float M = -INFINITY;
@@ -402,7 +436,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   if (tid < D) {
     float o = 0.0f;
 #pragma unroll
-    for (int s = 0; s < WAVES; ++s) o += (sm_m[s] > -INFINITY) ? sm_acc[s * D + tid] * fast_exp2(sm_m[s] - M) : 0.0f;
+    for (int s = 0; s < WAVES; ++s) o += (sm_m[s] > -INFINITY) ? sm_acc[s * New::kWords + tid] * fast_exp2(sm_m[s] - M) : 0.0f;
     store_elem<DT>(a.out, static_cast<size_t>(u) * D + tid, o * inv);
   }
 

@@ -52,12 +52,14 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 //               inside bias() would have to wait for every load issued before it, the next block's rows included;
 //   zptr        if not null, receives every base-2 logit once: zptr[row];
 //   special_row a row that must not take the branch-free path (the slot being overwritten), or -1;
-//   fix_k(row, kw, c) / fix_v(row, vw, c) may replace the loaded 16 bytes of that row.
-template <int DT, int D, int U, bool HAS_BIAS, bool STREAMING, class BiasFn, class FixK, class FixV>
+//   fix_k(row, kw, c) / fix_v(row, vw, c) may replace the loaded 16 bytes of that row;
+//   load_end    rows up to here may be loaded, whatever they hold: the first loads need not wait for row_end;
+//   meanwhile() runs once the first block's loads are under way.
+template <int DT, int D, int U, bool HAS_BIAS, bool STREAMING, class BiasFn, class FixK, class FixV, class Meanwhile>
 __device__ __forceinline__ void stream_attend(const float* qf, const char* Kbase, const char* Vbase,
-                                              int row_begin, int row_end, int passes, int rot, int pass_rows,
+                                              int row_begin, int row_end, int load_end, int passes, int rot, int pass_rows,
                                               int wave_off, BiasFn bias, const int32_t* aux, float* zptr, int special_row,
-                                              FixK fix_k, FixV fix_v, FlashState<RowGeom<DT, D>::EPL>& st) {
+                                              FixK fix_k, FixV fix_v, Meanwhile meanwhile, FlashState<RowGeom<DT, D>::EPL>& st) {
   using G = RowGeom<DT, D>;
   const int lane = threadIdx.x & (kWave - 1);
   const int g = lane / G::LPR, c = lane % G::LPR;
@@ -67,7 +69,7 @@ __device__ __forceinline__ void stream_attend(const float* qf, const char* Kbase
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int row = base + u * G::R + g;
-      const size_t off = static_cast<size_t>(row < row_end ? row : row_begin) * G::ROW_BYTES + c * 16;
+      const size_t off = static_cast<size_t>(row < load_end ? row : row_begin) * G::ROW_BYTES + c * 16;
       w[u] = STREAMING ? load16_streaming(base_ptr + off) : load16(base_ptr + off);
     }
   };
@@ -80,7 +82,7 @@ __device__ __forceinline__ void stream_attend(const float* qf, const char* Kbase
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int row = base + u * G::R + g;
-        aw[u] = aux[row < row_end ? row : row_begin];
+        aw[u] = aux[row < load_end ? row : row_begin];
       }
     }
   };
@@ -136,9 +138,8 @@ __device__ __forceinline__ void stream_attend(const float* qf, const char* Kbase
   auto accumulate = [&](int blk, uint4* vw, const float* t, float mb) {
     const int base = row_begin + blk * pass_rows + wave_off;
     if (!is_plain(base)) {
-      // Rows past the end were loaded from row_begin only to keep the address in range.  Their weight is 2^-inf = 0,
-      // but row_begin may be the very slot this step fills for the first time, whose bytes in the caller's buffer
-      // are arbitrary (0 x NaN is NaN): such rows contribute zeros, whatever was loaded.
+      // Rows past the end were loaded all the same.  Their weight is 2^-inf = 0, but the bytes of slots that no token has
+      // taken yet are arbitrary in the caller's buffer (0 x NaN is NaN): such rows contribute zeros, whatever was loaded.
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int row = base + u * G::R + g;
@@ -173,6 +174,7 @@ __device__ __forceinline__ void stream_attend(const float* qf, const char* Kbase
   issue_aux(blk);
   issue(blk, Kbase, kw);
   issue(blk, Vbase, vw);
+  meanwhile();
   for (int it = 0; it + 1 < passes; ++it) {
     const int nb = (blk + 1 == passes) ? 0 : blk + 1;
     scores(blk, kw, t, mb);
