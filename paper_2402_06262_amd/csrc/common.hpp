@@ -359,22 +359,23 @@ struct KSmallest {
   }
 };
 
-// Up to kCountedKeys keys are not searched: every thread counts which of them do not follow its own, 64 at a time, and the one
-// that counts k is the last of the k smallest.  Two instructions per pair of keys instead of four barriers, the bins and the chain of
-// the search among the last candidates (128 keys in four waves 4800 -> 3100 cycles, 256 in
-// sixteen 5400 -> 4700).  Keys that are equal come in the order of their blocks; inside a block
-// they all count the same number, so if the boundary falls among such keys nobody counts k: false, and the search has to say
-// which of them belong.
-constexpr int kCountedKeys = 256;
+// Up to kCountedKeys keys are not searched: the threads count for every key how many do not follow it, and the one that counts k
+// is the last of the k smallest.  Two instructions per pair of keys instead of four barriers, the bins and the chain of the search
+// among the last candidates (128 keys in four waves: 4800 -> 3100 cycles).  256 keys in sixteen waves take as long either way,
+// and on a compute unit that has several units' searches at a time longer (block_prepare of 674 units x 196 slots 10.8 -> 13.7 us).
+// Keys that are equal come in the order of their blocks of 64; inside a block they all count the same number, so if the boundary
+// falls among such keys nobody counts k: false, and the search has to say which of them belong.
+constexpr int kCountedKeys = 2 * kWave;
 template <int NT, class KeyFn>
 __device__ __forceinline__ bool count_k_smallest(KeyFn key_of, int n, uint32_t k, uint32_t* sh, KSmallest& r) {
-  static_assert(NT % kCountedKeys == 0 && kCountedKeys % (2 * kWave) == 0, "whole waves count for a block of keys");
+  constexpr int PARTS = NT / kCountedKeys;      // threads that share the counting for a key
+  constexpr int SHARE = kCountedKeys / PARTS;   // keys of each
+  static_assert(PARTS > 1 && kWave % SHARE == 0 && SHARE % 4 == 0, "a share lies in one block of keys");
   uint32_t* const counts = sh + kCountedKeys;
   uint32_t* const res = counts + kCountedKeys;  // the key, 1 + its index
-  const int width = n <= kCountedKeys / 2 ? kCountedKeys / 2 : kCountedKeys;
-  const int parts = NT / width;  // threads that share the counting for a key
-  const int tid = late_thread_id(), mine = tid & (width - 1);
-  const int my_block = __builtin_amdgcn_readfirstlane(mine / kWave), part = __builtin_amdgcn_readfirstlane(tid / width);
+  const int tid = late_thread_id(), mine = tid & (kCountedKeys - 1);
+  const int first = __builtin_amdgcn_readfirstlane(tid / kCountedKeys) * SHARE;
+  const bool earlier = first / kWave <= __builtin_amdgcn_readfirstlane(mine / kWave);  // (or the key's own block)
   __syncthreads();  // `sh` may still be in use by a previous call
   if (tid < kCountedKeys) {
     sh[tid] = tid < n ? key_of(tid) : 0xffffffffu;
@@ -383,32 +384,24 @@ __device__ __forceinline__ bool count_k_smallest(KeyFn key_of, int n, uint32_t k
   if (tid == 0) res[1] = 0;
   __syncthreads();
   const uint32_t key = sh[mine];
+  const uint4* const others = reinterpret_cast<const uint4*>(sh + first);
   uint32_t count = 0;
-  if (my_block * kWave < n) {
-#pragma unroll 1
-    for (int block = part; block * kWave < n; block += parts) {
-      const uint4* const others = reinterpret_cast<const uint4*>(sh + block * kWave);
-      if (block <= my_block) {
+  if (earlier) {
 #pragma unroll 4
-        for (int j = 0; j < kWave / 4; ++j) {
-          const uint4 o = others[j];
-          count += (o.x <= key) + (o.y <= key) + (o.z <= key) + (o.w <= key);
-        }
-      } else {
-#pragma unroll 4
-        for (int j = 0; j < kWave / 4; ++j) {
-          const uint4 o = others[j];
-          count += (o.x < key) + (o.y < key) + (o.z < key) + (o.w < key);
-        }
-      }
+    for (int j = 0; j < SHARE / 4; ++j) {
+      const uint4 o = others[j];
+      count += (o.x <= key) + (o.y <= key) + (o.z <= key) + (o.w <= key);
     }
-    if (parts > 1) atomicAdd(&counts[mine], count);
+  } else {
+#pragma unroll 4
+    for (int j = 0; j < SHARE / 4; ++j) {
+      const uint4 o = others[j];
+      count += (o.x < key) + (o.y < key) + (o.z < key) + (o.w < key);
+    }
   }
-  if (parts > 1) {
-    __syncthreads();
-    count = counts[mine];
-  }
-  if (part == 0 && mine < n && count == k && key != 0xffffffffu) {
+  atomicAdd(&counts[mine], count);
+  __syncthreads();
+  if (tid < n && counts[mine] == k && key != 0xffffffffu) {  // (n is at most kCountedKeys)
     res[0] = key;
     atomicMax(&res[1], static_cast<uint32_t>(mine) + 1u);
   }
