@@ -504,12 +504,19 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
   const int u = blockIdx.y, split = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int B = a.B, nq = a.queries, QR = a.qrows;  // QR: rows per unit of the workspace planes
-  const int n = a.n_used[u];  // block_prepare has run: the block's rows are in the cache and counted
+  // block_prepare has run: the block's rows are in the cache and counted -- or it is a single-token step without it, as in block_attend
+  int n = a.n_used[u];
+  int fresh = -1;
+  if (a.single) {
+    const bool was_full = n >= B;
+    fresh = was_full ? min(max(a.next_slot[u], 0), B - 1) : n;
+    n = was_full ? B : n + 1;
+  }
   const int row0 = split * a.rows_per_split;
   const int row1 = min(n, row0 + a.rows_per_split);
   const size_t pidx = static_cast<size_t>(u) * a.splits + split;
-  const char* Kb = static_cast<const char*>(a.K) + static_cast<size_t>(u) * B * G::ROW_BYTES;
-  const char* Vb = static_cast<const char*>(a.V) + static_cast<size_t>(u) * B * G::ROW_BYTES;
+  char* const Kb = static_cast<char*>(a.K) + static_cast<size_t>(u) * B * G::ROW_BYTES;
+  char* const Vb = static_cast<char*>(a.V) + static_cast<size_t>(u) * B * G::ROW_BYTES;
   const int32_t* bidx = a.blk_idx + static_cast<size_t>(u) * B;
   const int32_t* pos = a.pos + static_cast<size_t>(u) * B;
   float* z = a.z + static_cast<size_t>(u) * QR * B;
@@ -554,8 +561,8 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
     }
     if (tid < TR) {
       const int slot = min(tr0 + tid, n - 1);
-      fb = bidx[slot];
-      fp = pos[slot];
+      fb = a.single ? -1 : bidx[slot];
+      fp = slot == fresh ? qp0 : pos[slot];
     }
   };
 #pragma unroll
@@ -570,6 +577,18 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
       const int t = t0 + j;
       if (t >= n_tiles) break;
       const int tr0 = row0 + t * TR;
+      if (fresh >= tr0 && fresh < min(tr0 + TR, row1)) {  // a single token's row takes its slot, here and in the cache
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+          const int idx = tid + 256 * i, col = (idx % G::LPR) * 16;
+          if (tr0 + idx / G::LPR == fresh) {
+            pk[j][i] = load16(static_cast<const char*>(a.k_new) + static_cast<size_t>(u) * G::ROW_BYTES + col);
+            pv[j][i] = load16(static_cast<const char*>(a.v_new) + static_cast<size_t>(u) * G::ROW_BYTES + col);
+            *reinterpret_cast<uint4*>(Kb + static_cast<size_t>(fresh) * G::ROW_BYTES + col) = pk[j][i];
+            *reinterpret_cast<uint4*>(Vb + static_cast<size_t>(fresh) * G::ROW_BYTES + col) = pv[j][i];
+          }
+        }
+      }
 #pragma unroll
       for (int i = 0; i < CH; ++i) {
         const int idx = tid + 256 * i;
@@ -942,8 +961,9 @@ hipError_t launch_block_attend(const BlockArgs& a, hipStream_t s) {
 // dtype / head_dim other than bf16 / 128 take the vector-ALU attention
 hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStream_t s) {
   BlockArgs a = args;
-  // A single-token step on the matrix-core path needs no block_prepare.
-  a.single = (a.block == 1 && dtype == kBF16 && head_dim == 128 && !single_step_off()) ? 1 : 0;
+  // A single-token step needs no block_prepare (steps with / without it, us: 8 heads on 1 unit x 2340 slots of bf16 / 64 39.5 /
+  // 27.8, 2 heads on 140 x 3252 of fp32 / 128 142 / 135).
+  a.single = (a.block == 1 && !single_step_off()) ? 1 : 0;
   const size_t key_lds = key_lds_bytes(a.B);
   if (!allow_key_lds(reinterpret_cast<const void*>(block_prepare<512, true>), key_lds) ||
       !allow_key_lds(reinterpret_cast<const void*>(block_prepare<kPrepThreads, true>), key_lds))

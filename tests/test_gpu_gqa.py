@@ -92,6 +92,13 @@ def test_grouped_steps_on_the_vector_path(dtype, d):
           dtype=dtype, d=d)
 
 
+@pytest.mark.parametrize("dtype,d,group", [("f32", 64, 2), ("bf16", 64, 9), ("f32", 128, 33)])
+def test_single_tokens_on_the_vector_path(dtype, d, group, single_step):
+    """The new token's slot in every place of the 64-slot tiles, empty or taken, under a recency bias."""
+    drive(2, 136, 12, group, [1] * 200, seed=180 + d, recency=True, tag=f"gqa-single-{dtype}-{d}", single_token_entry=True,
+          dtype=dtype, d=d)
+
+
 def test_grouped_steps_with_recency_bias_and_a_larger_budget(single_step):
     drive(2, 1024, 48, 4, [8] * 130 + [1] * 8, seed=97, recency=True, tag="gqa-recency", single_token_entry=True)
 
