@@ -1,5 +1,6 @@
 // C ABI of the RoCo library: argument validation, workspace layout and kernel launches.
 // Nothing here allocates, frees or synchronises.
+#include <algorithm>
 #include <math.h>
 #include <stdlib.h>
 
@@ -85,9 +86,9 @@ BlockLayout block_layout(const roco_params* p) {
   size_t off = 0;
   l.blk_idx = off; off += align_up(U * B * sizeof(int32_t));
   l.z = off;       off += align_up(U * kMaxBlock * B * sizeof(float));
-  l.part_m = off;  off += align_up(U * kMaxBlockSplits * kMaxBlock * sizeof(float));
-  l.part_l = off;  off += align_up(U * kMaxBlockSplits * kMaxBlock * sizeof(float));
-  l.part_o = off;  off += align_up(U * kMaxBlockSplits * kMaxBlock * D * sizeof(float));
+  l.part_m = off;  off += align_up(U * kBlockPartials * sizeof(float));
+  l.part_l = off;  off += align_up(U * kBlockPartials * sizeof(float));
+  l.part_o = off;  off += align_up(U * kBlockPartials * D * sizeof(float));
   l.keys = off;    off += (p->budget > kMaxDecodeBudgetLds) ? align_up(U * 2 * B * sizeof(uint32_t)) : 0;
   l.total = off;
   return l;
@@ -390,14 +391,19 @@ int run_block(const roco_params* params, int tokens, int heads, const void* q, c
   a.units = params->units; a.B = params->budget; a.scope = params->scope;
   a.pol = policy_of(params);
   a.block = tokens; a.heads = heads; a.queries = tokens * heads;
-  a.qrows = a.queries > 32 ? 64 : 32;
+  a.qrows = params->dtype == ROCO_BF16 && params->head_dim == 128 ? 32 : 8;
+  while (a.qrows < a.queries) a.qrows *= 2;
   a.row_bytes = params->head_dim * (params->dtype == ROCO_BF16 ? 2 : 4);
   a.streaming = streaming_loads(params) ? 1 : 0;
   {  // split the budget into 64-slot-aligned ranges: two resident workgroups per compute unit measured best
-    // (more splits cost more partial results to write and merge than they gain in balance)
+    // (more splits cost more partial results to write and merge than they gain in balance).  Below 64 units no workgroup may be
+    // left for a second round, and beyond 24 splits merging them costs what the shorter walk saves.  Steps, us, with 8 / 12 / 16 / 24 / 32
+    // splits: 1 unit x 2340 slots x 8 heads of bf16 / 64 28.1 / 25.7 / 23.5 / 21.7 / 21.8, 7 x 3280 x 4 tokens of fp32 / 128
+    // 56 / 50 / 47 / 44 / 42, 3 x 4096 x 8 tokens of bf16 / 64 53 / 49 / 44 / 42 / 42, 8 x 3252 x 3 heads of bf16 / 128 26.1 / 24.5 /
+    // 24.0 (16 is what its 32 rows allow); but 40 x 4096 x 16 tokens of bf16 / 128 59.7 / 59.4 / 65.3.
     int want = env_int("ROCO_BLOCK_SPLITS", 0);
-    if (want <= 0) want = (512 + params->units - 1) / params->units;
-    if (want > kMaxBlockSplits) want = kMaxBlockSplits;
+    if (want <= 0) want = params->units < 64 ? std::min(512 / params->units, 24) : (512 + params->units - 1) / params->units;
+    if (want > kBlockPartials / a.qrows) want = kBlockPartials / a.qrows;
     const int max_by_rows = (params->budget + 63) / 64;
     if (want > max_by_rows) want = max_by_rows;
     if (want < 1) want = 1;

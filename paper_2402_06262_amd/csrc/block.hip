@@ -740,9 +740,9 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   __shared__ uint2 best_sh[NT / kWave];
   __shared__ float2 norm[kMaxBlock];  // reference and 1 / sum of every query row
   // the merge of the splits is done before the search begins
-  float2* const part_ml = reinterpret_cast<float2*>(sel_sh);                        // [kMaxBlockSplits * kMaxBlock]
-  float* const weight = reinterpret_cast<float*>(part_ml + kMaxBlockSplits * kMaxBlock);  // ditto
-  static_assert(3 * kMaxBlockSplits * kMaxBlock <= SelectLds<1>::kWords, "the merge fits the search's words");
+  float2* const part_ml = reinterpret_cast<float2*>(sel_sh);                        // [kBlockPartials]
+  float* const weight = reinterpret_cast<float*>(part_ml + kBlockPartials);  // ditto
+  static_assert(3 * kBlockPartials <= SelectLds<1>::kWords, "the merge fits the search's words");
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B, nq = a.queries, S = a.splits, QR = a.qrows;
   int n = a.n_used[u];
@@ -761,7 +761,7 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
 
   // The splits' normalisers of a query row come in with one load per (split, row) and are merged from LDS in split order;
   // a loop of dependent trips to memory per row would cost more than the rest of the merge.
-  static_assert(kMaxBlockSplits * kMaxBlock <= NT, "one thread per (split, row)");
+  static_assert(kBlockPartials <= NT, "one thread per (split, row)");
   const int my_row = tid & (QR - 1);  // (split, row) in the order of the planes
   const bool merges = tid < S * QR && my_row < nq;
   float2 mine = make_float2(-INFINITY, 0.0f);
@@ -792,20 +792,23 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
     if (a.evicted_slot) a.evicted_slot[u] = evicted ? fresh : -1;
     if (a.evicted_pos) a.evicted_pos[u] = evicted ? old_pos : -1;
   }
-  // outputs: all splits' partials of an element are requested together
+  // outputs: the partials of eight splits of an element are requested together
 #pragma unroll 1
   for (int idx = tid; idx < nq * D; idx += NT) {
     const int q = idx / D, dd = idx % D;
-    float part[kMaxBlockSplits];
-#pragma unroll
-    for (int s = 0; s < kMaxBlockSplits; ++s)
-      if (s < S) part[s] = po[(static_cast<size_t>(s) * QR + q) * D + dd];
     float o = 0.0f;
+#pragma unroll 1
+    for (int s0 = 0; s0 < S; s0 += 8) {
+      float part[8];
 #pragma unroll
-    for (int s = 0; s < kMaxBlockSplits; ++s) {
-      if (s < S) {
-        const float wgt = weight[s * QR + q];
-        o += wgt < 0.0f ? 0.0f : part[s] * wgt;
+      for (int i = 0; i < 8; ++i)
+        if (s0 + i < S) part[i] = po[(static_cast<size_t>(s0 + i) * QR + q) * D + dd];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (s0 + i < S) {
+          const float wgt = weight[(s0 + i) * QR + q];
+          o += wgt < 0.0f ? 0.0f : part[i] * wgt;
+        }
       }
     }
     store_elem<DT>(a.out, (static_cast<size_t>(u) * nq + q) * D + dd, o * norm[q].y);

@@ -125,7 +125,7 @@ struct PrefillArgs {
 };
 
 constexpr int kMaxBlock = 64;        // query rows (tokens x heads) per block-wise step: two 32-wide matrix tiles
-constexpr int kMaxBlockSplits = 8;   // split-K partials per unit of the block-wise step
+constexpr int kBlockPartials = 8 * kMaxBlock;  // split-K partials per unit of the block-wise step: splits times rows of the planes
 
 struct BlockArgs {
   int units, B, scope, block, splits, rows_per_split;
@@ -135,7 +135,7 @@ struct BlockArgs {
   int single;     // 1: single-token step without block_prepare (set by launch_block)
   int heads;    // query heads that share the unit's keys and values (1 without grouped-query attention)
   int queries;  // query rows per unit = block * heads <= 64; row r belongs to token r / heads, head r % heads
-  int qrows;    // rows per unit of the z / part_* planes: 32, or 64 when queries > 32
+  int qrows;    // rows per unit of the z / part_* planes, a power of two: 32 or 64 (bf16 / 128), else 8 to 64
   float scale_log2;
   int recency_window;
   float recency_bias_log2;

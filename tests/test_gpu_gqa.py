@@ -389,3 +389,13 @@ def test_edges_of_the_waves_tiles(B, recency, monkeypatch):
     monkeypatch.setenv("ROCO_BLOCK_SPLITS", "1")
     blocks = [1, 8, 16, 3] + [16] * (B // 16) + [1] * 12 + [16, 9, 1]
     drive(2, B, 7, 4, blocks, seed=B, recency=recency, tag=f"tiles-{B}-{recency}")
+
+
+@pytest.mark.parametrize("dtype,d,group,blocks", [("bf16", 64, 8, [1] * 3), ("f32", 128, 4, [2, 1, 2]), ("f32", 64, 1, [26, 9, 16]),
+                                                  ("bf16", 128, 3, [1, 10, 4]), ("bf16", 128, 1, [64, 33])])
+@pytest.mark.parametrize("splits", ["0", "13", "64"])
+def test_few_units_on_many_splits(dtype, d, group, blocks, splits, monkeypatch):
+    """Up to 26 partials per query row, as many as its rows of the planes leave room for, and splits without a slot."""
+    monkeypatch.setenv("ROCO_BLOCK_SPLITS", splits)
+    drive(2, 1604, 50, group, [64 // group] * (1604 // (64 // group)) + blocks, seed=190 + d, tag=f"splits-{dtype}-{d}-{splits}",
+          dtype=dtype, d=d)
