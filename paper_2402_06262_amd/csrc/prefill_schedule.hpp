@@ -107,7 +107,10 @@ inline PassPlan plan_rows(int dtype, int head_dim, int units, int group, int L_m
 
 inline PassPlan plan_columns(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
   if (dtype == 1 && head_dim == 128 && L_max <= 512 && units >= 480) return {true, 1, 1, 1, 1};
-  if (dtype == 1 && head_dim == 128 && L_max >= 1024) {
+  // 256 owned rows from four blocks on (three are an uneven pair), or two with several heads' tiles for each.  Whole prompts, us,
+  // with 128 / 256: 512 units x 800 tokens 212 / 187, 256 x 1000 131 / 117, 100 x 4 heads x 700 160 / 147, 64 x 1000 59 / 60; of three
+  // blocks 190 x 673 99.6 / 94.5, but prompts of up to 673 75.2 / 81.3, of up to 693 on 471 units 143 / 148, 130 x 640 62 / 66.
+  if (dtype == 1 && head_dim == 128 && (L_max > 768 || (group > 1 && L_max > 512))) {
     const int ids = ceil_div(ceil_div(L_max, 256), 2), tiles = column_tiles(64, group, L_max);
     const int split = rounds_split(static_cast<long long>(units) * ids, 512, tiles, 8.0, most_split);
     if (static_cast<long long>(units) * ids * split >= 250 && tiles >= 6 * split) return {true, 1, split, 1, ids};

@@ -57,6 +57,13 @@ def test_shared_blocks_and_every_group(monkeypatch, dtype, d, units, group, L):
     _both_paths(monkeypatch, dtype, d, units, group, L, lens, window=24 if group == 3 else 0)
 
 
+@pytest.mark.parametrize("units,group,L", [(130, 1, 768), (130, 1, 769), (130, 2, 512), (130, 3, 513), (40, 8, 769), (70, 5, 1023)])
+def test_owned_rows_of_a_column_block(monkeypatch, units, group, L):
+    """128 or 256: both sides of the rule."""
+    lens = [L - (13 * u) % (L // 2) for u in range(units)]
+    _both_paths(monkeypatch, "bf16", 128, units, group, L, lens)
+
+
 @pytest.mark.parametrize("qsplit", ["1", "2", "8"])
 @pytest.mark.parametrize("group,L", [(1, 700), (3, 500), (5, 400), (6, 300), (7, 290), (8, 300)])
 def test_shares_of_the_wide_kernels(monkeypatch, qsplit, group, L):
