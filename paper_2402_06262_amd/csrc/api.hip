@@ -213,6 +213,8 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
   a.ksplit = 1;
   a.shares = lay.shares;
   a.shares_to_add = 1;
+  a.lse_shares = 1;
+  a.lse_behind = 0;
   a.lse_scale = 1.0f;
   a.lse_given = nullptr;
   a.row_bytes = 0;
@@ -401,8 +403,11 @@ int run_block(const roco_params* params, int tokens, int heads, const void* q, c
     // splits: 1 unit x 2340 slots x 8 heads of bf16 / 64 28.1 / 25.7 / 23.5 / 21.7 / 21.8, 7 x 3280 x 4 tokens of fp32 / 128
     // 56 / 50 / 47 / 44 / 42, 3 x 4096 x 8 tokens of bf16 / 64 53 / 49 / 44 / 42 / 42, 8 x 3252 x 3 heads of bf16 / 128 26.1 / 24.5 /
     // 24.0 (16 is what its 32 rows allow); but 40 x 4096 x 16 tokens of bf16 / 128 59.7 / 59.4 / 65.3.
+    // Above 16 rows of fp32 / 128 the LDS has room for one workgroup: 24 x 3780 x 30 tokens with 8 / 10 / 12 splits 152 / 131 / 177,
+    // 48 x 3000 x 40 with 5 / 8 225 / 262, 60 x 2000 x 24 with 4 / 8 123 / 127.
+    const int resident = params->dtype == ROCO_F32 && params->head_dim == 128 && a.queries > 16 ? 256 : 512;
     int want = env_int("ROCO_BLOCK_SPLITS", 0);
-    if (want <= 0) want = params->units < 64 ? std::min(512 / params->units, 24) : (512 + params->units - 1) / params->units;
+    if (want <= 0) want = params->units < 64 ? std::max(1, std::min(resident / params->units, 24)) : (512 + params->units - 1) / params->units;
     if (want > kBlockPartials / a.qrows) want = kBlockPartials / a.qrows;
     const int max_by_rows = (params->budget + 63) / 64;
     if (want > max_by_rows) want = max_by_rows;
