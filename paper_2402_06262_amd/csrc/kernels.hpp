@@ -113,9 +113,12 @@ struct PrefillArgs {
   // where share `share` of a pass that several workgroups divide leaves its sums (which = 0: Acc, 1: Acc2): the first in acc and
   // acc2, the second in the planes that the selection will later use for its ranking keys, further ones behind those
   __host__ __device__ float* sums_of(int share, int which) const { return acc + static_cast<size_t>(2 * share + which) * plane; }
-  // ... and its row normalisers: the first where they belong, the others in the planes of the column sums, all heads together
+  // ... and its row normalisers: the first where they belong, the others in the planes of the column sums, all heads together:
+  // from the first plane on if they are merged before the column pass, behind the planes that it writes if it merges them itself
+  // as it reads them (lse_shares > 1; see columns_merge_normalisers)
+  int lse_shares, lse_behind;
   __host__ __device__ float* lse_of_share(int share) const {
-    return share == 0 ? lse : acc + static_cast<size_t>(share - 1) * units * group * L_max;
+    return share == 0 ? lse : acc + lse_behind * plane + static_cast<size_t>(share - 1) * units * group * L_max;
   }
   // most shares whose normalisers have room there
   int row_shares() const {

@@ -1041,19 +1041,11 @@ __global__ __launch_bounds__(256) void merge_key_shares(PrefillArgs a) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= a.len[u / a.group]) return;
   const size_t at = static_cast<size_t>(u) * a.L_max + i;
-  float x[kMaxKeyShares];
-  float top = -INFINITY;
+  float more[kMaxKeyShares - 1];
 #pragma unroll
-  for (int s = 0; s < kMaxKeyShares; ++s) {
-    x[s] = s < a.ksplit ? a.lse_of_share(s)[at] : -INFINITY;
-    top = fmaxf(top, x[s]);
-  }
-  if (top > -INFINITY) {
-    float sum = 0.0f;
-#pragma unroll
-    for (int s = 0; s < kMaxKeyShares; ++s) sum += s < a.ksplit ? fast_exp2(x[s] - top) : 0.0f;
-    a.lse[at] = top + log2f(sum);
-  }
+  for (int s = 1; s < kMaxKeyShares; ++s)
+    if (s < a.ksplit) more[s - 1] = a.lse_of_share(s)[at];
+  a.lse[at] = merged_normaliser(a.lse[at], more, a.ksplit);
 }
 
 // With few units the queries of every block of keys are shared by several workgroups (PrefillArgs::qsplit), so that the chip has
@@ -1448,20 +1440,19 @@ bool plan_override(const PrefillArgs& a, int most_split, PassPlan& plan) {
   return true;
 }
 
-void launch_rows(const PrefillArgs& a, hipStream_t s) {
+void launch_rows(PrefillArgs& a, const PassPlan& columns, hipStream_t s) {
   PassPlan plan;
   if (!plan_override(a, a.row_shares(), plan)) plan = plan_rows(kBF16, D, a.units, a.group, a.L_max, a.row_shares());
+  columns_merge_normalisers(a, plan, columns);
   if (!plan.wide) return launch_prefill_rows_planes_wide(a, plan, s);
   ProfScope ps(kProfPrefillRows, s);
   PrefillArgs b = a;
   b.paired = plan.paired; b.pairs = plan.ids; b.ksplit = plan.split;
   hipLaunchKernelGGL(prefill_rows_mfma, dim3(workgroup_ids(a.units, a.group * plan.ids * plan.split)), dim3(4 * kWave), 0, s, b);
-  if (plan.split > 1) launch_merge_key_shares(b, s);
+  if (plan.split > a.lse_shares) launch_merge_key_shares(b, s);
 }
 
-hipError_t launch_columns(PrefillArgs& a, hipStream_t s) {
-  PassPlan plan;
-  if (!plan_override(a, a.shares, plan)) plan = plan_columns(kBF16, D, a.units, a.group, a.L_max, a.shares);
+hipError_t launch_columns(PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
   if (!plan.wide) {
     launch_prefill_columns_planes_wide(a, plan, s);
     return hipGetLastError();
@@ -1503,6 +1494,8 @@ hipError_t launch_mfma_probe(int workgroups, int iters, int mode, float* sink, h
 }
 
 hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s) {
+  PassPlan columns;
+  if (!plan_override(a, a.shares, columns)) columns = plan_columns(kBF16, D, a.units, a.group, a.L_max, a.shares);
   if (a.O != nullptr) {
     ProfScope ps(kProfPrefillRows, s);
     PrefillArgs b = a;
@@ -1510,9 +1503,9 @@ hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s) {
     b.pairs = ceil_div(a.L_max, 128);
     hipLaunchKernelGGL(prefill_rows_out_mfma, dim3(workgroup_ids(a.units, a.group * b.pairs)), dim3(256), 0, s, b);
   } else if (!a.skip_rows) {
-    launch_rows(a, s);
+    launch_rows(a, columns, s);
   }
-  return launch_columns(a, s);
+  return launch_columns(a, columns, s);
 }
 
 }  // namespace roco

@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kThreads, (kColumnWaves<DT, D, PARTS, HEADS>)) void
       t_last = min(t_last, t_first + per - 1);
     }
     Pieces<DT, D, P::TR> st;
-    float st_lse = 0.0f;
+    float st_lse = 0.0f, st_more[kMaxKeyShares - 1];
     auto fetch = [&](int t, int h) {
       int lse_h = h, lse_q = threadIdx.x;
       if constexpr (HEADS > 1) {
@@ -455,7 +455,13 @@ __global__ __launch_bounds__(kThreads, (kColumnWaves<DT, D, PARTS, HEADS>)) void
       } else {
         st.load(Qu + static_cast<size_t>(h) * a.L_max * P::IN_ROW, t * QT, len - 1);
       }
-      if (threadIdx.x < P::TR) st_lse = lse_u[static_cast<size_t>(lse_h) * a.L_max + min(t * QT + lse_q, len - 1)];
+      if (threadIdx.x < P::TR) {
+        const size_t at = static_cast<size_t>(lse_h) * a.L_max + min(t * QT + lse_q, len - 1);
+        st_lse = lse_u[at];
+#pragma unroll
+        for (int k = 1; k < kMaxKeyShares; ++k)
+          if (k < a.lse_shares) st_more[k - 1] = (a.lse_of_share(k) + ubase * G)[at];
+      }
     };
     if (t_first <= t_last) fetch(t_last, 0);
     __syncthreads();  // the previous block has finished with the tiles and what goes with them; odd_s is cleared
@@ -471,6 +477,7 @@ __global__ __launch_bounds__(kThreads, (kColumnWaves<DT, D, PARTS, HEADS>)) void
         ++seq;
         if (st.store(tile) && DT == kF32) odd_s[b] = seq;
         if (threadIdx.x < P::TR) {
+          if (a.lse_shares > 1) st_lse = merged_normaliser(st_lse, st_more, a.lse_shares);
           lse_s[b][threadIdx.x] = st_lse * a.lse_scale;
           if (count && HEADS == 1) rinv_s[b][threadIdx.x] = 1.0f / static_cast<float>(t * P::TR + static_cast<int>(threadIdx.x) + 1);
         }
@@ -844,7 +851,7 @@ void launch_rows(const PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
     case 2: if constexpr (D == 64 || DT == kBF16) hipLaunchKernelGGL((prefill_rows_planes<DT, D, 2>), grid, dim3(kThreads), 0, s, b); break;
     default: if constexpr (DT == kBF16) hipLaunchKernelGGL((prefill_rows_planes<DT, D, 4>), grid, dim3(kThreads), 0, s, b); break;
   }
-  if (plan.split > 1) launch_merge_key_shares(b, s);
+  if (plan.split > a.lse_shares) launch_merge_key_shares(b, s);
 }
 
 // The row pass with output takes single blocks.  Whole call, us, 64 owned rows (two waves share 32) against 128: bf16 / 64
@@ -886,12 +893,17 @@ void launch_columns(PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
 
 template <int DT, int D>
 hipError_t launch_t(PrefillArgs& a, hipStream_t s) {
+  const PassPlan columns = plan_columns(DT, D, a.units, a.group, a.L_max, a.shares);
   if (!a.skip_rows) {
     if (prefill_rows_are_tiny(a, DT == kF32, D)) launch_prefill_rows_simple(DT, D, a, s);
     else if (a.O != nullptr) launch_rows_out<DT, D>(a, s);
-    else launch_rows<DT, D>(a, plan_rows(DT, D, a.units, a.group, a.L_max, a.row_shares()), s);
+    else {
+      const PassPlan rows = plan_rows(DT, D, a.units, a.group, a.L_max, a.row_shares());
+      columns_merge_normalisers(a, rows, columns);
+      launch_rows<DT, D>(a, rows, s);
+    }
   }
-  launch_columns<DT, D>(a, plan_columns(DT, D, a.units, a.group, a.L_max, a.shares), s);
+  launch_columns<DT, D>(a, columns, s);
   return hipGetLastError();
 }
 

@@ -234,4 +234,16 @@ __device__ __forceinline__ void column_update_grouped(const f32x16& s, const flo
 }
 
 }  // namespace mfma
+// The base-2 log-sum-exp of a row from those of its `shares` shares of keys (the first, and the others in `more`).
+__device__ __forceinline__ float merged_normaliser(float first, const float* more, int shares) {
+  float top = first;
+#pragma unroll
+  for (int k = 1; k < kMaxKeyShares; ++k) top = k < shares ? fmaxf(top, more[k - 1]) : top;
+  if (!(top > -INFINITY)) return first;
+  float sum = fast_exp2(first - top);
+#pragma unroll
+  for (int k = 1; k < kMaxKeyShares; ++k) sum += k < shares ? fast_exp2(more[k - 1] - top) : 0.0f;
+  return top + log2f(sum);
+}
+
 }  // namespace roco
