@@ -554,7 +554,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int idx = tid + 256 * i;
-      const int row = min(tr0 + idx / G::LPR, n - 1);  // slots past the end are masked below
+      const int row = min(tr0 + idx / G::LPR, n - 1);  // rows past the end are dealt with below
       const size_t off = static_cast<size_t>(row) * G::ROW_BYTES + (idx % G::LPR) * 16;
       fk[i] = a.streaming ? load16_streaming(Kb + off) : load16(Kb + off);
       fv[i] = a.streaming ? load16_streaming(Vb + off) : load16(Vb + off);
@@ -588,6 +588,14 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
             *reinterpret_cast<uint4*>(Vb + static_cast<size_t>(fresh) * G::ROW_BYTES + col) = pv[j][i];
           }
         }
+      }
+      // Rows behind the last slot are copies of one (their loads only had to stay in range), and that one may be the slot which a
+      // single token fills for the first time, whose bytes are arbitrary, or whose infinite value it overwrites: as V they are
+      // zeros, since a weight of 0 does not silence NaN or infinity.  (Scores of such rows are replaced, whatever they are.)
+      if (tr0 + TR > row1) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+          if (tr0 + (tid + 256 * i) / G::LPR >= row1) pv[j][i] = make_uint4(0u, 0u, 0u, 0u);
       }
 #pragma unroll
       for (int i = 0; i < CH; ++i) {
