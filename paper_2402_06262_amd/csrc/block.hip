@@ -225,13 +225,15 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
   char* const my_tiles = lds_dyn + wave * T::kBytes;
   const uint32_t tiles_addr = lds_address(my_tiles);
   const uint32_t bidx_addr = lds_address(&bidx_s[wave][0][0]), pos_addr = lds_address(&pos_s[WINDOW ? wave : 0][0][0]);
-  int koff[4];  // rows 4 i + lane / 16 of a tile (and 16 further down)
+  // This lane's chunks of a tile, rows 4 i + lane / 16.  All of a row's offset inside the tile is the lane's: the scalar offset is the
+  // tile's first row, which exists, so that rows behind the last one are out of range by the lane's offset alone (see load16_to_lds).
+  int koff[T::kLoads], voff[T::kLoads];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < T::kLoads; ++i) {
     const int r = 4 * i + (lane >> 4);
-    koff[i] = r * kRowBytes + (((lane & 15) ^ r) << 4);
+    koff[i] = r * kRowBytes + (((lane & 15) ^ (r & 15)) << 4);
+    voff[i] = r * kRowBytes + (((lane & 15) ^ ((r & 3) << 2)) << 4);
   }
-  const int voff = (lane >> 4) * kRowBytes + (((lane & 15) ^ ((lane >> 4) << 2)) << 4);
   // The wave's tiles: every other one of the split, from a start that differs between workgroups, so that workgroups running
   // side by side do not walk the memory channels in lock step (the online softmax does not care about the order).
   const int n_tiles = row1 > row0 ? (row1 - row0 + T::kSlots - 1) / T::kSlots : 0;
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
     const uint32_t dst = tiles_addr + (t & 1) * T::kOperand;
     const int soff = __builtin_amdgcn_readfirstlane(row * kRowBytes);
 #pragma unroll
-    for (int i = 0; i < T::kLoads; ++i) load16_to_lds_hint<STREAMING>(kbuf, dst + i * 1024, koff[i & 3], soff + (i >> 2) * 16 * kRowBytes);
+    for (int i = 0; i < T::kLoads; ++i) load16_to_lds_hint<STREAMING>(kbuf, dst + i * 1024, koff[i], soff);
     const int side = __builtin_amdgcn_readfirstlane(row * 4);
     load4_to_lds(bbuf, bidx_addr + (t & 1) * (kWave * 4), lane * 4, side);
     if (WINDOW) load4_to_lds(pbuf, pos_addr + (t & 1) * (kWave * 4), lane * 4, side);
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
     const uint32_t dst = tiles_addr + (2 + (t & 1)) * T::kOperand;
     const int soff = __builtin_amdgcn_readfirstlane(tile_row(t) * kRowBytes);
 #pragma unroll
-    for (int i = 0; i < T::kLoads; ++i) load16_to_lds_hint<STREAMING>(vbuf, dst + i * 1024, voff, soff + i * 4 * kRowBytes);
+    for (int i = 0; i < T::kLoads; ++i) load16_to_lds_hint<STREAMING>(vbuf, dst + i * 1024, voff[i], soff);
   };
 
   // B operand: the block's queries (lanes beyond the block reuse its last query; their results are dropped)

@@ -41,7 +41,8 @@ __device__ __forceinline__ v4i32 make_buffer(const void* base, uint32_t bytes) {
 }
 
 // Wave-wide load, 16 bytes per lane: lane i's bytes from buffer offset voffset + soffset go to LDS address
-// lds_addr + 16 i.  lds_addr and soffset are wave-uniform.
+// lds_addr + 16 i.  lds_addr and soffset are wave-uniform.  The hardware holds voffset against the buffer's size less soffset:
+// soffset lies inside the buffer in every call, and what may lie behind its end is part of voffset.
 __device__ __forceinline__ void load16_to_lds(v4i32 rsrc, uint32_t lds_addr, int voffset, int soffset) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :: "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory", "m0");

@@ -1,5 +1,6 @@
 """Block-wise and grouped steps on caches whose unused slots hold any bytes: K, V and statistics of every slot that no token has
-taken are 0xFF (NaN in fp32 and in bf16) before each step, from the first token until the budget is reached and evictions begin."""
+taken, and those of a unit's worth of memory behind the last unit, are 0xFF (NaN in fp32 and in bf16) before each step, from the
+first token until the budget is reached and evictions begin."""
 import math
 
 import numpy as np
@@ -12,7 +13,7 @@ from inputs import round_to_bf16
 
 pytestmark = pytest.mark.gpu
 
-VECTOR_FORMS = [("f32", 64), ("bf16", 64), ("f32", 128)]
+FORMS = [("f32", 64), ("bf16", 64), ("f32", 128), ("bf16", 128)]
 
 
 def _steps(dtype, d, B, group, blocks, seed):
@@ -26,6 +27,10 @@ def _steps(dtype, d, B, group, blocks, seed):
     if dtype == "bf16":
         Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
     sess = P.make_session(units, d, B, s, dtype)
+    behind = [torch.zeros((units + 1, B, d), dtype=P.torch_dtype(dtype), device="cuda") for _ in range(2)]
+    for x in behind:
+        x[units].view(torch.uint8).fill_(0xFF)
+    sess.cache.K, sess.cache.V = (x[:units] for x in behind)
     states, ties, t = TG.empty_states(units, B, d), P.TieCount(), 0
     for b in blocks:
         TP._poison_unused(sess.cache, [min(t, B)] * units)
@@ -51,7 +56,7 @@ def _steps(dtype, d, B, group, blocks, seed):
     return sess
 
 
-@pytest.mark.parametrize("dtype,d", VECTOR_FORMS)
+@pytest.mark.parametrize("dtype,d", FORMS)
 @pytest.mark.parametrize("group", [1, 3])
 @pytest.mark.parametrize("blocks", [[1] * 150, [5, 1, 20, 1, 9, 1, 1, 21, 13, 1, 1, 20, 9, 1, 21, 20, 1, 7, 1]], ids=["tokens", "blocks"])
 def test_bytes_of_unused_slots_reach_nothing(dtype, d, group, blocks):
@@ -59,7 +64,7 @@ def test_bytes_of_unused_slots_reach_nothing(dtype, d, group, blocks):
     _steps(dtype, d, 132, group, blocks, seed=700 + d + group)
 
 
-@pytest.mark.parametrize("dtype,d", VECTOR_FORMS)
+@pytest.mark.parametrize("dtype,d", FORMS)
 @pytest.mark.parametrize("B", [68, 100])
 def test_the_row_that_a_token_overwrites_is_gone(dtype, d, B):
     """The last slot of a cache that ends inside a tile is overwritten: its infinite value reaches nothing."""
