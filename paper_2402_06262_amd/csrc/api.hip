@@ -411,7 +411,7 @@ int run_block(const roco_params* params, int tokens, int heads, const void* q, c
     if (want > kBlockPartials / a.qrows) want = kBlockPartials / a.qrows;
     const int max_by_rows = (params->budget + 63) / 64;
     if (want > max_by_rows) want = max_by_rows;
-    if (want < 1) want = 1;
+    want = std::max(want, (params->budget + kMaxSplitRows - 1) / kMaxSplitRows);  // at most 4, for which there always is room
     int rows = (params->budget + want - 1) / want;
     rows = (rows + 63) / 64 * 64;
     a.splits = (params->budget + rows - 1) / rows;

@@ -217,9 +217,11 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
     qp[t2] = qp0 + ti[t2];
   }
 
-  // slots past the unit's last one come back as zeros (and are masked below)
-  const v4i32 kbuf = make_buffer(Kb, static_cast<uint32_t>(n) * kRowBytes);
-  const v4i32 vbuf = make_buffer(Vb, static_cast<uint32_t>(n) * kRowBytes);
+  // The split's rows: slots past the unit's last one come back as zeros (and are masked below).  A descriptor's size and offsets
+  // have 32 bits, which the rows of a split fit (kMaxSplitRows), not those of a unit.
+  const uint32_t split_bytes = static_cast<uint32_t>(max(row1 - row0, 0)) * kRowBytes;
+  const v4i32 kbuf = make_buffer(Kb + static_cast<size_t>(row0) * kRowBytes, split_bytes);
+  const v4i32 vbuf = make_buffer(Vb + static_cast<size_t>(row0) * kRowBytes, split_bytes);
   const v4i32 bbuf = make_buffer(a.blk_idx + static_cast<size_t>(u) * B, static_cast<uint32_t>(B) * 4u);
   const v4i32 pbuf = make_buffer(a.pos + static_cast<size_t>(u) * B, static_cast<uint32_t>(B) * 4u);
   char* const my_tiles = lds_dyn + wave * T::kBytes;
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
   auto request_k = [&](int t) {
     const int row = tile_row(t);
     const uint32_t dst = tiles_addr + (t & 1) * T::kOperand;
-    const int soff = __builtin_amdgcn_readfirstlane(row * kRowBytes);
+    const int soff = __builtin_amdgcn_readfirstlane((row - row0) * kRowBytes);
 #pragma unroll
     for (int i = 0; i < T::kLoads; ++i) load16_to_lds_hint<STREAMING>(kbuf, dst + i * 1024, koff[i], soff);
     const int side = __builtin_amdgcn_readfirstlane(row * 4);
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(kAttThreads) void block_attend(BlockArgs a) {
   };
   auto request_v = [&](int t) {
     const uint32_t dst = tiles_addr + (2 + (t & 1)) * T::kOperand;
-    const int soff = __builtin_amdgcn_readfirstlane(tile_row(t) * kRowBytes);
+    const int soff = __builtin_amdgcn_readfirstlane((tile_row(t) - row0) * kRowBytes);
 #pragma unroll
     for (int i = 0; i < T::kLoads; ++i) load16_to_lds_hint<STREAMING>(vbuf, dst + i * 1024, voff[i], soff);
   };

@@ -129,6 +129,7 @@ struct PrefillArgs {
 
 constexpr int kMaxBlock = 64;        // query rows (tokens x heads) per block-wise step: two 32-wide matrix tiles
 constexpr int kBlockPartials = 8 * kMaxBlock;  // split-K partials per unit of the block-wise step: splits times rows of the planes
+constexpr int kMaxSplitRows = 1 << 22;  // slots of a split of the block-wise step: 2^30 bytes of a bf16 / 128 operand
 
 struct BlockArgs {
   int units, B, scope, block, splits, rows_per_split;
