@@ -3,7 +3,8 @@
 PyTorch supplies device memory (`tensor.data_ptr()`) and the HIP stream
 (`torch.cuda.current_stream().cuda_stream`); no arithmetic of the method happens here.  The library is loaded with ctypes; the
 arguments of the steps and prompts, the calls that a model makes per layer and token, are collected by the extension module
-`_native` (csrc/native_call.cpp), which is handed the addresses of the library's functions.
+`_native` (csrc/native_call.cpp), which is handed the addresses of the library's functions.  Where there is no extension (a tree
+with the library only, or addresses and streams passed by a program without PyTorch) they go through ctypes like the other calls.
 """
 from __future__ import annotations
 
@@ -22,7 +23,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libroco.so"
 _NATIVE_NAME = "_native"
 _lib: Optional[ctypes.CDLL] = None
-_native = None  # the extension module ...
+_native = None  # the extension module, if there is one
+_marshal = None  # what collects the arguments of the steps and prompts: the extension module or _PlainCalls ...
 _native_lib: Optional[ctypes.CDLL] = None  # ... and the library it is bound to
 
 
@@ -123,11 +125,38 @@ def load_library() -> ctypes.CDLL:
     return lib
 
 
+class _PlainCalls:
+    """The extension's functions by ctypes alone, a few microseconds slower a call."""
+
+    # which of a function's arguments behind the parameters are integers; the others are tensors or addresses
+    INTEGERS = {"prefill_compress": (4,), "prefill_compress_gqa": (0, 5), "prefill_compress_lse": (0, 5), "decode_step": (),
+                "decode_step_static": (), "encode_block": (0,), "encode_block_gqa": (0, 1), "decode_step_gqa": (0,)}
+
+    def __init__(self, lib):
+        for name, integers in self.INTEGERS.items():
+            setattr(self, name, self._function(getattr(lib, "roco_" + name), integers, name != "decode_step_static"))
+
+    @staticmethod
+    def _function(fn, integers, has_workspace):
+        def call(params, *args):
+            *args, stream = args
+            size = ()
+            if has_workspace:
+                *args, workspace_bytes = args
+                size = (int(args[-1].nbytes if workspace_bytes is None else workspace_bytes),)
+            return fn(ctypes.byref(params), *[int(a) if i in integers else _ptr(a) for i, a in enumerate(args)], *size, _stream(stream))
+        return call
+
+
 def _bind_native(lib) -> None:
-    global _native, _native_lib
+    global _native, _marshal, _native_lib
     import importlib
-    import torch  # the extension reads tensors by their C++ side
-    native = importlib.import_module("." + _NATIVE_NAME, __package__)
+    try:
+        import torch  # the extension reads tensors by their C++ side
+        native = importlib.import_module("." + _NATIVE_NAME, __package__)
+    except ImportError:
+        _marshal, _native_lib = _PlainCalls(lib), lib
+        return
     address = lambda fn: ctypes.cast(fn, ctypes.c_void_p).value
     native.bind(tuple(address(getattr(lib, name)) for name in (
         "roco_prefill_compress", "roco_prefill_compress_gqa", "roco_prefill_compress_lse", "roco_decode_step",
@@ -135,14 +164,14 @@ def _bind_native(lib) -> None:
         torch.Tensor, torch.nn.Parameter, _ptr, _stream)
     if _native is None and hasattr(os, "register_at_fork"):
         os.register_at_fork(after_in_child=native.forget_gpu)  # a forked child is refused by torch, as before
-    _native, _native_lib = native, lib
+    _native, _marshal, _native_lib = native, native, lib
 
 
 def _calls():
-    """The extension module, bound to the library; loads both on first use."""
+    """The extension module (or its stand-in), bound to the library; loads both on first use."""
     if _native_lib is None or _native_lib is not _lib:
         _bind_native(load_library())
-    return _native
+    return _marshal
 
 
 def roco_strerror(code: int) -> str:

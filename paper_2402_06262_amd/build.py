@@ -45,14 +45,18 @@ def _run(cmd, verbose):
         raise RuntimeError(f"hipcc failed ({proc.returncode}):\n{out}")
 
 
-def _native_command():
+def _native_commands():
+    """One command, or none where the extension has no PyTorch to be built against (the binding then uses ctypes alone)."""
     import sysconfig
-    import torch
+    try:
+        import torch
+    except ImportError:
+        return []
     from torch.utils import cpp_extension
     flags = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
     includes = [f"-I{d}" for d in cpp_extension.include_paths()] + [f"-I{sysconfig.get_paths()['include']}"]
     libs = [f"-L{os.path.join(os.path.dirname(torch.__file__), 'lib')}", "-lc10", "-ltorch_cpu", "-ltorch_python"]
-    return ["g++", *flags, *includes, os.path.join(CSRC, "native_call.cpp"), "-o", NATIVE_PATH, *libs]
+    return [["g++", *flags, *includes, os.path.join(CSRC, "native_call.cpp"), "-o", NATIVE_PATH, *libs]]
 
 
 def build_library(verbose: bool = True) -> str:
@@ -66,7 +70,7 @@ def build_library(verbose: bool = True) -> str:
         objs = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
         cmds = [[hipcc, *compile_flags, "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
         with ThreadPoolExecutor(max_workers=min(len(cmds) + 1, os.cpu_count() or 1)) as pool:
-            list(pool.map(lambda c: _run(c, verbose), [_native_command(), *cmds]))
+            list(pool.map(lambda c: _run(c, verbose), [*_native_commands(), *cmds]))
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH], verbose)
     return LIB_PATH
 

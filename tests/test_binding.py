@@ -1,5 +1,6 @@
 """Argument marshalling of the extension module behind the binding (no GPU: the calls are refused on the host)."""
 import ctypes
+import sys
 
 import numpy as np
 import pytest
@@ -84,3 +85,25 @@ def test_the_extension_follows_the_loaded_library(monkeypatch):
     monkeypatch.setattr(binding, "_lib", None)
     assert binding._calls() is before and binding._native_lib is binding._lib is roco.load_library()
     assert ctypes.sizeof(roco.RocoParams) == 44
+
+
+@pytest.mark.parametrize("check", [test_addresses_none_and_sizes_reach_the_library, test_a_tensor_is_its_address_and_its_bytes,
+                                   test_what_is_refused_stays_refused, test_prompts_and_the_static_step])
+def test_a_tree_without_the_extension(monkeypatch, check):
+    """Only the library is built: the same calls by ctypes alone."""
+    monkeypatch.setattr(binding, "_NATIVE_NAME", "_not_built")
+    monkeypatch.setattr(binding, "_native_lib", None)
+    monkeypatch.setattr(binding, "_marshal", None, raising=False)
+    check()
+    assert isinstance(binding._marshal, binding._PlainCalls)
+
+
+@pytest.mark.parametrize("call,n", [("roco_encode_block", 1), ("roco_decode_step_gqa", 1), ("roco_encode_block_gqa", 2)])
+def test_steps_of_many_without_the_extension(monkeypatch, call, n):
+    monkeypatch.setattr(binding, "_native_lib", None)
+    monkeypatch.setattr(binding, "_marshal", None, raising=False)
+    monkeypatch.setitem(sys.modules, "torch", None)  # plain addresses need no PyTorch
+    args = [0x1000] * 14
+    assert _code(getattr(roco, call), P, *[4] * n, *args, workspace_bytes=0, stream=0) == EWORKSPACE
+    assert _code(getattr(roco, call), P, *[0] * n, *args, workspace_bytes=0, stream=0) == EINVAL
+    assert isinstance(binding._marshal, binding._PlainCalls)
