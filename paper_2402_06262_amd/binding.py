@@ -161,7 +161,7 @@ def _bind_native(lib) -> None:
     native.bind(tuple(address(getattr(lib, name)) for name in (
         "roco_prefill_compress", "roco_prefill_compress_gqa", "roco_prefill_compress_lse", "roco_decode_step",
         "roco_decode_step_static", "roco_encode_block", "roco_encode_block_gqa", "roco_decode_step_gqa")),
-        torch.Tensor, torch.nn.Parameter, _ptr, _stream)
+        torch.Tensor, torch.nn.Parameter, RocoParams, _ptr, _stream)
     if _native is None and hasattr(os, "register_at_fork"):
         os.register_at_fork(after_in_child=native.forget_gpu)  # a forked child is refused by torch, as before
     _native, _marshal, _native_lib = native, native, lib

@@ -16,6 +16,7 @@ namespace {
 
 // ------------------------------------------------------------------ what binding.py hands over once
 PyObject* g_tensor_types[2];  // torch.Tensor, torch.nn.Parameter: exactly these are read without a call
+PyObject* g_params_type;      // binding.RocoParams
 PyObject* g_pointer;          // binding._ptr: everything else
 PyObject* g_current_stream;   // binding._stream: anything but an address, and the current stream before it is known how to ask
 PyObject* g_raw_stream;       // torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice: set once the GPU is in use
@@ -115,18 +116,18 @@ void* stream_of(PyObject* o) {
   return s;
 }
 
-// The parameters' structure, a ctypes object, read through the buffer it exports and copied: 44 bytes.
+// The parameters' structure, a ctypes object of binding.py's class (or one derived from it), read through the buffer it exports and
+// copied: its first 44 bytes.
 roco_params params_of(PyObject* o) {
-  Py_buffer view;
-  if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw Failed{};
   roco_params p;
-  const bool whole = view.len == static_cast<Py_ssize_t>(sizeof(p));
-  if (whole) std::memcpy(&p, view.buf, sizeof(p));
-  PyBuffer_Release(&view);
-  if (!whole) {
+  Py_buffer view;
+  if (!PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(g_params_type))) {
     PyErr_SetString(PyExc_TypeError, "roco: params must be a RocoParams");
     throw Failed{};
   }
+  if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw Failed{};
+  std::memcpy(&p, view.buf, sizeof(p));  // (a derived structure has its own fields behind)
+  PyBuffer_Release(&view);
   return p;
 }
 
@@ -253,12 +254,12 @@ PyObject* prefill_compress_lse(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// bind(addresses, tensor, parameter, _ptr, _stream); use_gpu(getCurrentRawStream, getDevice)
+// bind(addresses, tensor, parameter, RocoParams, _ptr, _stream); use_gpu(getCurrentRawStream, getDevice)
 PyObject* bind(PyObject*, PyObject* args) {
   unsigned long long f[8];
-  PyObject *tensor, *parameter, *ptr, *stream;
-  if (!PyArg_ParseTuple(args, "(KKKKKKKK)OOOO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &f[7], &tensor, &parameter, &ptr,
-                        &stream))
+  PyObject *tensor, *parameter, *params, *ptr, *stream;
+  if (!PyArg_ParseTuple(args, "(KKKKKKKK)OOO!OO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &f[7], &tensor, &parameter,
+                        &PyType_Type, &params, &ptr, &stream))
     return nullptr;
   g_fn.prefill = reinterpret_cast<decltype(g_fn.prefill)>(f[0]);
   g_fn.prefill_gqa = reinterpret_cast<decltype(g_fn.prefill_gqa)>(f[1]);
@@ -268,9 +269,10 @@ PyObject* bind(PyObject*, PyObject* args) {
   g_fn.block = reinterpret_cast<decltype(g_fn.block)>(f[5]);
   g_fn.block_gqa = reinterpret_cast<decltype(g_fn.block_gqa)>(f[6]);
   g_fn.decode_gqa = reinterpret_cast<decltype(g_fn.decode_gqa)>(f[7]);
-  Py_INCREF(tensor); Py_INCREF(parameter); Py_INCREF(ptr); Py_INCREF(stream);
+  Py_INCREF(tensor); Py_INCREF(parameter); Py_INCREF(params); Py_INCREF(ptr); Py_INCREF(stream);
   Py_XSETREF(g_tensor_types[0], tensor);
   Py_XSETREF(g_tensor_types[1], parameter);
+  Py_XSETREF(g_params_type, params);
   Py_XSETREF(g_pointer, ptr);
   Py_XSETREF(g_current_stream, stream);
   Py_RETURN_NONE;

@@ -107,3 +107,14 @@ def test_steps_of_many_without_the_extension(monkeypatch, call, n):
     assert _code(getattr(roco, call), P, *[4] * n, *args, workspace_bytes=0, stream=0) == EWORKSPACE
     assert _code(getattr(roco, call), P, *[0] * n, *args, workspace_bytes=0, stream=0) == EINVAL
     assert isinstance(binding._marshal, binding._PlainCalls)
+
+
+class _MoreParams(roco.RocoParams):
+    _fields_ = [("layer", ctypes.c_int32)]
+
+
+def test_parameters_are_the_structure_or_one_derived_from_it():
+    assert _code(_decode, params=_MoreParams(4, 64, 128, 16, roco.ROCO_F32)) == EWORKSPACE
+    for other in (bytes(44), bytearray(44), np.zeros(11, np.int32), (ctypes.c_int32 * 11)(), ctypes.pointer(P), None):
+        with pytest.raises(TypeError):
+            _decode(params=other)
