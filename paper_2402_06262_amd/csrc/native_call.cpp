@@ -41,11 +41,7 @@ const at::Tensor* tensor_of(PyObject* o) {
   return type == g_tensor_types[0] || type == g_tensor_types[1] ? &THPVariable_Unpack(o) : nullptr;
 }
 
-void* address_of_int(PyObject* o) {
-  void* const p = PyLong_AsVoidPtr(o);
-  if (p == nullptr && PyErr_Occurred()) throw Failed{};
-  return p;
-}
+void* address_of_int(PyObject* o) { return reinterpret_cast<void*>(PyLong_AsUnsignedLongLongMask(o)); }
 
 void* pointer(PyObject* o) {
   if (o == Py_None) return nullptr;
@@ -71,17 +67,13 @@ void* pointer(PyObject* o) {
   return p;
 }
 
-long long integer(PyObject* o) {
-  if (PyLong_CheckExact(o)) {
-    const long long v = PyLong_AsLongLong(o);
-    if (v == -1 && PyErr_Occurred()) throw Failed{};
-    return v;
-  }
+// The low 64 bits, as ctypes takes them: sizes from 2^63 on are sizes.
+unsigned long long integer(PyObject* o) {
+  if (PyLong_CheckExact(o)) return PyLong_AsUnsignedLongLongMask(o);
   PyObject* const n = PyNumber_Long(o);  // as int(o)
   if (n == nullptr) throw Failed{};
-  const long long v = PyLong_AsLongLong(n);
+  const unsigned long long v = PyLong_AsUnsignedLongLongMask(n);
   Py_DECREF(n);
-  if (v == -1 && PyErr_Occurred()) throw Failed{};
   return v;
 }
 int32_t int32_of(PyObject* o) { return static_cast<int32_t>(integer(o)); }
@@ -91,9 +83,14 @@ size_t bytes(PyObject* size, PyObject* workspace) {
   if (const at::Tensor* t = tensor_of(workspace)) return t->nbytes();
   PyObject* const n = PyObject_GetAttrString(workspace, "nbytes");
   if (n == nullptr) throw Failed{};
-  const size_t v = static_cast<size_t>(PyLong_AsSize_t(n));
+  size_t v;
+  try {
+    v = static_cast<size_t>(integer(n));
+  } catch (const Failed&) {
+    Py_DECREF(n);
+    throw;
+  }
   Py_DECREF(n);
-  if (v == static_cast<size_t>(-1) && PyErr_Occurred()) throw Failed{};
   return v;
 }
 

@@ -118,3 +118,22 @@ def test_parameters_are_the_structure_or_one_derived_from_it():
     for other in (bytes(44), bytearray(44), np.zeros(11, np.int32), (ctypes.c_int32 * 11)(), ctypes.pointer(P), None):
         with pytest.raises(TypeError):
             _decode(params=other)
+
+
+def test_integers_have_the_width_of_their_arguments():
+    """Beyond it they wrap, as in a C call: a size from 2^63 on is a size, 2^32 + 64 tokens are 64."""
+    assert _code(_decode, q=None, workspace_bytes=2 ** 64 - 1) == EINVAL
+    assert _code(_decode, q=None, workspace_bytes=-1) == EINVAL
+    assert _code(_decode, workspace_bytes=2 ** 64) == EWORKSPACE
+    assert _code(roco.roco_prefill_compress, P, *[0x1000] * 4, 2 ** 72 + 64, *[0x1000] * 8, workspace_bytes=0, stream=0) == EWORKSPACE
+
+    class Sized:
+        nbytes = np.int64(5)
+
+        def is_contiguous(self):
+            return True
+
+        def data_ptr(self):
+            return 0x1000
+
+    assert _code(_decode, ws=Sized(), workspace_bytes=None) == EWORKSPACE
