@@ -480,6 +480,20 @@ template <int D> struct SharedTile {
   }
 };
 
+// The slot that the token of a single-token step overwrites in a full unit whose next_slot is negative: a cache that its owner has
+// put together without roco_select_victims.  By the statistics as they stand, which no kernel has touched yet, as block_prepare
+// chooses; the keys are formed as the search reads them, since this is not the path that has to be fast.
+template <int NT>
+__device__ __forceinline__ int victim_by_statistics(const float* stats, const int32_t* pos, int B, Policy pol, int scope, uint32_t* sel_sh,
+                                                 uint2* best_sh) {
+  auto keys = [&](int i) {
+    uint32_t mas_key, var_key;
+    ranking_keys(stats[i], stats[B + i], stats[2 * static_cast<size_t>(B) + i], pos[i], pol, mas_key, var_key);
+    return make_uint2(mas_key, var_key);
+  };
+  return select_victim<NT, 1>([&](int i) { return keys(i).y; }, [&](int i) { return keys(i).x; }, B, pol, scope, sel_sh, best_sh);
+}
+
 // QMAX: most query rows the instantiation takes (8, 16, 32 or 64).  The smaller ones need fewer registers and less LDS,
 // so more workgroups fit a compute unit, and they keep two tiles in flight per workgroup instead of one.
 template <int DT, int D, int QMAX>
@@ -513,7 +527,14 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
   int fresh = -1;
   if (a.single) {
     const bool was_full = n >= B;
-    fresh = was_full ? min(max(a.next_slot[u], 0), B - 1) : n;
+    fresh = was_full ? min(a.next_slot[u], B - 1) : n;
+    if (fresh < 0) {  // (the tiles are not in use yet)
+      uint32_t* const sel_sh = reinterpret_cast<uint32_t*>(lds_f);
+      fresh = victim_by_statistics<256>(a.stats + static_cast<size_t>(u) * 3 * B, a.pos + static_cast<size_t>(u) * B, B, a.pol, a.scope,
+                                        sel_sh, reinterpret_cast<uint2*>(sel_sh + SelectLds<1>::kWords));
+      __syncthreads();
+    }
+    if (split == 0 && tid == 0) a.blk_idx[static_cast<size_t>(u) * B] = fresh;  // for block_finish
     n = was_full ? B : n + 1;
   }
   const int row0 = split * a.rows_per_split;
@@ -747,6 +768,7 @@ template <int DT, int D, int R, bool LDS>
 __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   constexpr int NT = kFinThreads;
   constexpr int kSlots = 2 * NT;  // slots per sweep
+  constexpr bool kMatrix = DT == kBF16 && D == 128;
   extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];  // [2][B] ranking keys when B <= kMaxDecodeBudgetLds
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
   __shared__ uint2 best_sh[NT / kWave];
@@ -762,7 +784,8 @@ __global__ __launch_bounds__(kFinThreads, 8) void block_finish(BlockArgs a) {
   bool evicted = false;
   if (a.single) {
     evicted = n >= B;
-    fresh = evicted ? min(max(a.next_slot[u], 0), B - 1) : n;
+    // (behind block_attend_shared: the slot it has chosen)
+    fresh = !kMatrix ? a.blk_idx[static_cast<size_t>(u) * B] : evicted ? min(max(a.next_slot[u], 0), B - 1) : n;
     n = evicted ? B : n + 1;
   }
   const int heads = a.heads;

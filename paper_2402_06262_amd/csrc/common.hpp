@@ -443,21 +443,26 @@ __device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint
 
 // Scope = `scope` lowest variance keys among [0, B); returns the slot of lowest MAS key inside it (lowest
 // slot on equal keys).  Every thread of the block calls it and gets the same answer.
-template <int NT, int PER_WORD>
-__device__ __forceinline__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, const Policy& pol, int scope,
-                                   uint32_t* sel_sh, uint2* best_sh) {
+template <int NT, int PER_WORD, class VarFn, class MasFn>
+__device__ __forceinline__ int select_victim(VarFn var_key_of, MasFn mas_key_of, int B, const Policy& pol, int scope, uint32_t* sel_sh,
+                                             uint2* best_sh) {
   const int tid = late_thread_id();
-  const KSmallest sc = select_k_smallest<NT, PER_WORD, NT <= 4 * kWave ? 4 : 1>([&](int i) { return var_key[i]; }, B,
+  const KSmallest sc = select_k_smallest<NT, PER_WORD, NT <= 4 * kWave ? 4 : 1>(var_key_of, B,
                                              static_cast<uint32_t>(pol.scope_size(scope, B)), pol.scope_is_window(), sel_sh);
   uint32_t key = 0xffffffffu, idx = 0xffffffffu;
 #pragma unroll 1
   for (int i = tid; i < B; i += NT) {
-    if (sc.has(var_key[i], i)) {
-      const uint32_t k = mas_key[i];
+    if (sc.has(var_key_of(i), i)) {
+      const uint32_t k = mas_key_of(i);
       if (k < key || idx == 0xffffffffu) { key = k; idx = static_cast<uint32_t>(i); }
     }
   }
   return static_cast<int>(block_argmin<NT>(key, idx, best_sh));
+}
+template <int NT, int PER_WORD>
+__device__ __forceinline__ int select_victim_block(const uint32_t* var_key, const uint32_t* mas_key, int B, const Policy& pol, int scope,
+                                                   uint32_t* sel_sh, uint2* best_sh) {
+  return select_victim<NT, PER_WORD>([&](int i) { return var_key[i]; }, [&](int i) { return mas_key[i]; }, B, pol, scope, sel_sh, best_sh);
 }
 
 // Ranking keys of one cached token: the token of lowest importance key among the tokens of lowest scope key
