@@ -51,6 +51,12 @@ WORST_OUT = {"f32": [0.0, 0.0], "bf16": [0.0, 0.0]}
 TIE_LOG: List[tuple] = []
 
 
+def _off(g: np.ndarray, o: np.ndarray, tol) -> np.ndarray:
+    """Where g is not within tol of o: NaN is not, unless o is NaN too; infinities are if they are the same."""
+    with np.errstate(invalid="ignore"):
+        return ~((np.abs(g - o) <= tol) | (g == o) | (np.isnan(g) & np.isnan(o)))
+
+
 def assert_out_close(g: np.ndarray, o: np.ndarray, dtype: str, what: str):
     g, o = np.asarray(g, np.float64), np.asarray(o, np.float64)
     rms = math.sqrt(float(np.mean(o * o))) if o.size else 0.0
@@ -60,7 +66,7 @@ def assert_out_close(g: np.ndarray, o: np.ndarray, dtype: str, what: str):
         w = WORST_OUT[dtype]
         w[0] = max(w[0], float(np.max(err / np.maximum(tol, 1e-300))))
         w[1] = max(w[1], float(np.max(err / np.maximum(OUT_RTOL[dtype] * np.maximum(np.abs(o), 1e-3 * rms), 1e-300))))
-    bad = np.abs(g - o) > tol
+    bad = _off(g, o, tol)
     assert not bad.any(), f"{what}: {int(bad.sum())} of {o.size} outside tolerance; worst |g-o|/tol = " \
                           f"{float(np.max(np.abs(g - o) / np.maximum(tol, 1e-300))):.3g}"
 
@@ -73,7 +79,7 @@ def assert_stat_close(g: np.ndarray, o: np.ndarray, what: str):
     tol = STAT_RTOL * np.maximum(np.abs(o), STAT_FLOOR)
     if o.size:
         WORST_STAT[0] = max(WORST_STAT[0], float(np.max(np.abs(g - o) / np.maximum(np.abs(o), STAT_FLOOR))))
-    bad = np.abs(g - o) > tol
+    bad = _off(g, o, tol)
     assert not bad.any(), f"{what}: {int(bad.sum())} of {o.size} outside tolerance; worst rel = " \
                           f"{float(np.max(np.abs(g - o) / np.maximum(np.abs(o), STAT_FLOOR))):.3g}"
 
@@ -136,7 +142,7 @@ def _near_threshold(p: np.ndarray, n_attended: int) -> np.ndarray:
 
 
 def assert_count_close(g: np.ndarray, o: np.ndarray, slack: np.ndarray, what: str):
-    bad = np.abs(np.asarray(g, dtype=np.float64) - o) > slack
+    bad = _off(np.asarray(g, dtype=np.float64), np.asarray(o, dtype=np.float64), slack)
     assert not bad.any(), f"{what}: thresholded counts differ by more than the near-threshold events at {np.flatnonzero(bad)[:8]}"
 _SCOPE_KIND = {"std": 0, "window": 1, "all": 2}
 

@@ -100,27 +100,60 @@ def test_a_smaller_workspace_takes_fewer_shares(dtype, d):
         np.testing.assert_allclose(c.stats.cpu().numpy()[:, :2], want[:, :2], rtol=2e-5, atol=1e-7)
 
 
-def test_shares_of_a_prompt_whose_keys_do_not_fit_the_lds():
-    """Above 16384 tokens a kernel of its own adds the shares; the last-token score needs them added before it writes its row."""
+@pytest.mark.parametrize("importance", ["MAS", "LAST", "COUNT"])
+def test_shares_of_a_prompt_whose_keys_do_not_fit_the_lds(importance):
+    """Above 16384 tokens a kernel of its own adds the shares; the last-token score needs them added before it writes its row.
+    Two shares (the smallest workspace) against all that the query asks for, at the positions that both keep."""
     import paper_2402_06262_amd as roco
     L, B, d = 17000, 300, 128
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
     Q, K, V = (torch.randn((1, L, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
-    p = roco.RocoParams(1, d, B, 60, roco.ROCO_BF16)
-    res = []
-    for nbytes in (5 * 4 * L + 5 * 256, roco.prefill_workspace_bytes(p, L)):
+    p = roco.RocoParams(1, d, B, 60, roco.ROCO_BF16, importance=getattr(roco, "ROCO_IMPORTANCE_" + importance),
+                        scope_kind=roco.ROCO_SCOPE_STD if importance == "MAS" else roco.ROCO_SCOPE_ALL)
+    least = 5 * 4 * L + 5 * 256
+    assert roco.prefill_workspace_bytes(p, L) > least + 2 * 4 * L  # more than two shares
+    stats = []
+    for nbytes in (least, roco.prefill_workspace_bytes(p, L)):
         c = roco.alloc_cache(p)
-        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
         roco.roco_prefill_compress(p, Q, K, V, torch.tensor([L], dtype=torch.int32, device="cuda"), L, c.K, c.V, c.stats, c.pos,
                                    c.n_used, c.next_slot, None, ws)
         torch.cuda.synchronize()
-        res.append(c)
-    a, b = res
-    same = (a.pos == b.pos).float().mean().item()
-    assert same > 0.9  # ties within rounding may move a token, and every slot behind it
-    if same == 1.0:
-        np.testing.assert_allclose(a.stats.cpu().numpy(), b.stats.cpu().numpy(), rtol=2e-5, atol=1e-7)
+        stats.append(dict(zip(c.pos[0].tolist(), c.stats[0].t().cpu().numpy())))
+    a, b = stats
+    both = sorted(a.keys() & b.keys())
+    assert len(both) >= 0.98 * B  # ranking keys that agree within rounding may go either way
+    x, y = (np.stack([s[i] for i in both]) for s in stats)
+    np.testing.assert_allclose(x[:, 0], y[:, 0], rtol=2e-5, atol=1e-7)
+    assert np.array_equal(x[:, 2], y[:, 2])
+    if importance == "COUNT":  # a probability within rounding of 1 / (i + 1) may be counted or not: about one in 10^6
+        assert np.max(np.abs(x[:, 1] - y[:, 1])) <= 2
+    else:
+        np.testing.assert_allclose(x[:, 1], y[:, 1], rtol=2e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("dtype,d", FORMS)
+@pytest.mark.parametrize("importance", ["ltas", "aqas"])
+@pytest.mark.parametrize("units,group,L", [(1, 1, 2100), (2, 3, 600), (1, 5, 500), (2, 6, 400), (1, 7, 700), (2, 9, 300), (3, 8, 300)])
+def test_scores_in_the_second_plane(monkeypatch, dtype, d, importance, units, group, L):
+    """The last query's attention and the counted queries, over shared blocks and every group: against the vector-ALU passes."""
+    from oracle.roco_oracle import Policy
+    P = TP._parity()
+    Q, K, V = _inputs(np.random.default_rng(units * 1000 + L + group), dtype, units, group, L, d)
+    lens = [L - (11 * u) % (L // 2) for u in range(units)]
+    res = []
+    for simple in ("1", "0"):
+        monkeypatch.setenv("ROCO_PREFILL_SIMPLE", simple)
+        sess = P.make_session(units, d, L, 9, dtype, policy=Policy(importance, "all"))
+        res.append(P.gpu_prefill_gqa(sess, group, Q, K, V, lens)["stats"])
+    want, got = res
+    np.testing.assert_allclose(got[:, 0], want[:, 0], rtol=2e-5, atol=1e-7)
+    if importance == "aqas":  # see above; a few hundred thousand probabilities
+        off = np.abs(got[:, 1] - want[:, 1])
+        assert off.max() <= 1 and off.sum() <= 5
+    else:
+        np.testing.assert_allclose(got[:, 1], want[:, 1], rtol=2e-5, atol=1e-7)
 
 
 @pytest.mark.parametrize("dtype,d,B", [("f32", 128, 256), ("f32", 128, 257), ("bf16", 64, 1024), ("bf16", 64, 1025), ("f32", 64, 1),

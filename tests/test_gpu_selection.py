@@ -254,5 +254,28 @@ def test_window_scopes_over_positions_of_every_size(n, top):
 
 @pytest.mark.parametrize("kind", ["equal", "low_bits", "middle_bits", "two_values", "wide"])
 @pytest.mark.parametrize("n", [65, 127, 130, 192, 255, 256, 257])
-def test_few_keys_are_counted(kind, n):
+def test_few_keys(kind, n):
     test_lowest_keys_go_first_and_ties_by_slot(kind, n)
+
+
+@pytest.mark.parametrize("kind", ["equal", "low_bits", "two_values", "wide"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129])
+def test_few_keys_are_counted(kind, n):
+    """Up to 128 keys are counted instead of searched, in blocks of 64: every number of victims, so that the boundary falls between
+    equal keys of one block and of both."""
+    import paper_2402_06262_amd as roco
+    units = 2
+    rng = np.random.default_rng([n, len(kind), 7])
+    p = roco.RocoParams(units, 64, n, 1, roco.ROCO_F32, importance=roco.ROCO_IMPORTANCE_AAS, scope_kind=roco.ROCO_SCOPE_ALL)
+    acc = np.stack([_keys(kind, n, rng) for _ in range(units)])
+    stats = torch.from_numpy(np.stack([acc, acc, np.ones_like(acc)], axis=1)).cuda()
+    n_used = torch.full((units,), n, dtype=torch.int32, device="cuda")
+    masks = torch.empty((n, units, n), dtype=torch.int32, device="cuda")
+    ws = torch.empty(roco.decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    for keep in range(n):
+        mask = torch.empty((units, n), dtype=torch.int32, device="cuda")
+        roco.roco_select_retained(p, keep, stats, None, n_used, mask, ws)
+        masks[keep] = mask
+    rank = np.argsort(np.argsort(acc, axis=1, kind="stable"), axis=1)
+    want = (rank[None] >= n - np.arange(n)[:, None, None]).astype(np.int32)
+    assert np.array_equal(masks.cpu().numpy(), want)
