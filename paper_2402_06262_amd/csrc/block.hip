@@ -40,7 +40,7 @@ namespace {
 using namespace mfma;
 
 constexpr int kPrepThreads = 1024;  // 512 when the units outnumber the compute units (see launch_block)
-constexpr int kAttThreads = 128;  // two waves: one 32-slot half of a 64-slot tile each
+constexpr int kAttThreads = 128;  // two waves: every other 32-slot tile each
 constexpr int kFinThreads = 1024;
 constexpr int kQ = 32;            // query rows per matrix tile
 static_assert(kMaxBlock == 2 * kQ, "a step holds at most two tiles of query rows");

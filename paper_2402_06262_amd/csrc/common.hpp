@@ -186,7 +186,7 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // integers and is exact.  radix_select finds the k-th smallest key (k is 1-based, 1 <= k <= n) among
 // key_of(0..n-1), digits of up to 11 bits from the top; it also returns how many keys are strictly smaller and how
 // many are equal.  What it costs is its barriers and its passes over the keys, so the first digit is wide: the exponent and
-// the three leading mantissa bits (no key has the top bit, the mark below apart) spread a unit's variances or scores over bins
+// the three leading mantissa bits (no key has the top bit, but the mark and, under `small`, negative positions) spread a unit's variances or scores over bins
 // of an eighth of an octave, and usually few enough keys share the chosen one that no second digit is counted -- as soon as a
 // bin holds at most kSelectRanked keys they are gathered and searched without another barrier.  A thread clears the bins it
 // owns while it reads them, so a digit takes three barriers.
@@ -470,8 +470,8 @@ __device__ __forceinline__ int select_victim_block(const uint32_t* var_key, cons
 // For RoCo these are the mean attention score and the attention variance, each operation rounded on its own
 // (no fused multiply-add), so that a single observation gives a variance of exactly zero:
 //   MAS = Acc/Count,  Var = max(0, Acc2/Count - MAS^2)          (section 4.3 of the paper)
-// A protected sink position gets the largest importance key without the top bit, which the search leaves out; 0xffffffff is the
-// marker that the selections use for "outside the scope".
+// A protected sink position gets the largest importance key without the top bit, which the search leaves out (so does a negative
+// position, which is below any number of sinks); 0xffffffff is the marker that the selections use for "outside the scope".
 // N tokens at a time: the policy is asked for once, and the divisions, chains of ten dependent instructions, run side by side.
 template <int N>
 __device__ __forceinline__ void ranking_keys(const float* acc, const float* acc2, const float* count, const int* pos,

@@ -821,13 +821,14 @@ __global__ __launch_bounds__(WAVES * kWave) void prefill_columns_gqa_pow2_mfma(P
   }
 }
 
-// The grouped column pass on the tile ring, for G = 2, 4, 8, 16 heads and the sum-of-squares second statistic: the
+// The grouped column pass on the tile ring, for G = 2 to 8 or 16 heads and the sum-of-squares second statistic: the
 // shape of prefill_columns_mfma (keys owned in groups w and 7 - w, query tiles walked downwards through a four-stage
 // ring filled by loads that go straight to LDS, the rectangle software-pipelined on four accumulators) with the tile
-// composition of prefill_columns_gqa_pow2_mfma (64 / G query positions for all G heads, the heads of a position in G
-// consecutive accumulator registers of a lane).  Which (head, position) a tile row holds is a constant of the lane
-// that loads it, so the gather over the G query arrays costs nothing: it is the lane's buffer offset.  In the
-// rectangle the head sum of a position is carried over the G / 2 slices of the pipelined step that hold its heads.
+// composition of prefill_columns_gqa_pow2_mfma (GroupedRows: 4 (16 / G) query positions for all G heads, the heads of a
+// position in G consecutive accumulator registers of a lane; with 3, 5, 6 or 7 heads the last 16 % G registers are not
+// looked at).  Which (head, position) a tile row holds is a constant of the lane that loads it, so the gather over the G
+// query arrays costs nothing: it is the lane's buffer offset.  In the rectangle the head sum of a position is carried
+// over the slices of the pipelined step, two registers each, that hold its heads.
 // The tiles near the diagonal and the ragged end of the prompt take the plain form, one barrier per tile.
 template <int G>
 __global__ __launch_bounds__(256, 2) void prefill_columns_gqa_ring(PrefillArgs a) {
@@ -1396,12 +1397,13 @@ __global__ __launch_bounds__(256, 2) void prefill_mix_probe(int tiles, float* si
   sink[static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x] = sum;
 }
 
-// Grouped column pass: the in-register head sum when the number of heads divides 16, else the general kernel.
+// Grouped column pass: the in-register head sum for 2 to 8 or 16 heads on the ring, and where the ring does not apply for the
+// numbers of heads that divide 16; else the general kernel.
 template <int WAVES>
 void launch_columns_grouped(const PrefillArgs& b, dim3 grid, hipStream_t s) {
   const dim3 block(WAVES * kWave);
-  // The ring-fed kernel where it applies: sum-of-squares second statistic, a power-of-two group, and all of a unit's
-  // query rows inside a 32-bit byte offset.  ROCO_PREFILL_GQA_RING=0 keeps the register-staged kernels (tests run both).
+  // The ring-fed kernel where it applies: sum-of-squares second statistic, 2 to 8 or 16 heads, and all of a unit's query
+  // rows inside a 32-bit byte offset.  ROCO_PREFILL_GQA_RING=0 keeps the register-staged kernels (tests run both).
   const char* e = getenv("ROCO_PREFILL_GQA_RING");
   const bool ring_ok = !(e != nullptr && e[0] == '0') && !b.pol.counts_above_average() &&
                        static_cast<long long>(b.group) * b.L_max * kRowBytes < (1ll << 31);

@@ -12,9 +12,9 @@ namespace mfma {
 // tiles, at about the same time) are given ids that are congruent modulo 8: they land on one die and all but
 // the first fetch of a tile hit its L2.  That holds for the units that fill all dies evenly, units / 8 * 8 of them.  Whole units
 // would leave dies without work if the up to seven units left over were treated so: those share the dies out evenly, four
-// units two dies each, two or six units four dies each, any other number all dies for every unit (whole units on whole dies: 2 units x 8 heads x 4396 tokens of bf16 / 64 with output took 640 us, 3 x 8 x 2578 of
-// fp32 / 64 679, 22 x 8 x 3323 of bf16 / 128 592; now 363, 458 and 558).  The grid is one-dimensional over
-// workgroup_ids(units, pairs) ids.
+// units two dies each, two or six units four dies each, any other number all dies for every unit (whole units on whole
+// dies: 2 units x 8 heads x 4396 tokens of bf16 / 64 with output took 640 us, 3 x 8 x 2578 of fp32 / 64 679, 22 x 8 x
+// 3323 of bf16 / 128 592; now 363, 458 and 558).  The grid is one-dimensional over workgroup_ids(units, pairs) ids.
 __host__ __device__ inline unsigned workgroup_ids(int units, int pairs) {
   const unsigned even = static_cast<unsigned>(units) / 8 * 8, rest = static_cast<unsigned>(units) - even;
   return even * pairs + (rest * pairs + 7) / 8 * 8;
