@@ -11,21 +11,29 @@ namespace mfma {
 // dies in turn and each die has its own L2, so the workgroups of one unit (which all stream the same K or Q
 // tiles, at about the same time) are given ids that are congruent modulo 8: they land on one die and all but
 // the first fetch of a tile hit its L2.  That holds for the units that fill all dies evenly, units / 8 * 8 of them.  Whole units
-// would leave dies without work if the up to seven units left over were treated so: those share the dies out evenly, four
-// units two dies each, two or six units four dies each, any other number all dies for every unit (whole units on whole
-// dies: 2 units x 8 heads x 4396 tokens of bf16 / 64 with output took 640 us, 3 x 8 x 2578 of fp32 / 64 679, 22 x 8 x
-// 3323 of bf16 / 128 592; now 363, 458 and 558).  The grid is one-dimensional over workgroup_ids(units, pairs) ids.
+// would leave dies without work if the few units left over were treated so: those share the dies out evenly, four
+// units two dies each, two or six units four dies each, any other number all dies for every unit (whole units on whole dies: 2
+// units x 8 heads x 4396 tokens of bf16 / 64 with output took 640 us, 3 x 8 x 2578 of fp32 / 64 679; now 363 and 458).  Seven,
+// or six behind others, leave so few dies without work that a unit's own L2 is worth more.  Whole prompts with shared dies
+// against whole ones, geometric means over the four forms and 400 to 3000 tokens, full / of different lengths: 7 units
+// 1.11 / 1.01, 14 1.04 / 1.02, 15 1.06 / 1.05, 23 1.06 / 1.03, 46 1.02 / 1.00, 47 1.04 / 1.01, 215 1.00 / 1.01; but 6 units
+// 1.00 / 0.99, five left over (5, 13, 21) 0.98 to 1.01 and fewer (9, 12, 20, 25, 28, 36, 100 units) 0.94 to 0.99.  The grid
+// is one-dimensional over workgroup_ids(units, pairs) ids.
+__host__ __device__ inline int units_on_whole_dies(int units) {  // (or two more than there are)
+  return units < 7 ? 0 : (units + 2) & ~7;
+}
 __host__ __device__ inline unsigned workgroup_ids(int units, int pairs) {
-  const unsigned even = static_cast<unsigned>(units) / 8 * 8, rest = static_cast<unsigned>(units) - even;
+  const unsigned even = static_cast<unsigned>(units_on_whole_dies(units)), all = static_cast<unsigned>(units);
+  const unsigned rest = all > even ? all - even : 0;
   return even * pairs + (rest * pairs + 7) / 8 * 8;
 }
 __device__ __forceinline__ bool locate(int units, int pairs, int& unit, int& pair) {
-  const int lin = blockIdx.x, even = units & ~7;
+  const int lin = blockIdx.x, even = units_on_whole_dies(units);
   const int seq = lin >> 3;
   if (seq * 8 < even * pairs) {
     unit = (seq / pairs) * 8 + (lin & 7);
     pair = seq % pairs;
-    return true;
+    return unit < units;
   }
   const int rest = units & 7, groups = rest & -rest;  // of units and of dies: 1, 2 or 4
   const int die = lin & 7, per = 8 / groups;          // dies of a group

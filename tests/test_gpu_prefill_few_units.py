@@ -40,7 +40,8 @@ def _both_paths(monkeypatch, dtype, d, units, group, L, lens, window=0, want_out
 
 
 @pytest.mark.parametrize("dtype,d", FORMS)
-@pytest.mark.parametrize("units,group,L", [(1, 1, 700), (7, 1, 290), (9, 3, 270), (3, 4, 530), (15, 1, 129)])
+@pytest.mark.parametrize("units,group,L", [(1, 1, 700), (7, 1, 290), (9, 3, 270), (3, 4, 530), (15, 1, 129), (6, 2, 270),
+                                           (13, 1, 300), (22, 1, 140)])
 def test_units_left_over_by_the_dies(monkeypatch, dtype, d, units, group, L):
     lens = [L - (7 * u) % (L // 3) for u in range(units)]
     for want_out in (False, True):
