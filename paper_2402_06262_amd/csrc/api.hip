@@ -207,6 +207,7 @@ int run_prefill(const roco_params* params, int group, const void* Q, const void*
   a.group = group;
   a.pol = policy_of(params);
   a.pairs = 0;
+  a.whole = 0;
   a.paired = env_int("ROCO_PREFILL_PAIRED", -1);
   a.skip_rows = want_lse ? 1 : 0;
   a.qsplit = 1;

@@ -84,6 +84,7 @@ struct PrefillArgs {
   int group;             // query heads per unit (1 without grouped-query attention): Q and lse are [units][group][L_max]
   Policy pol;
   int pairs;             // matrix-core path: workgroup ids per unit (set by its launcher)
+  int whole;             // ... and the units whose workgroups all go to one die (ditto; see locate)
   int paired;            // matrix-core path: 1 = long+short block per workgroup, 0 = one block, -1 = choose
   int skip_rows;         // 1: lse already holds the row normalisers, pass 1 is not run
   int qsplit;            // matrix-core path: workgroups that share a block of keys, each with a part of the queries (set by its launcher)

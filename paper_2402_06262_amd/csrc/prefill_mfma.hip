@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rows_mfma(PrefillArgs a) {
   constexpr int NS = 4;  // ring stages: a tile is requested three tiles of work ahead of its use
   __shared__ __attribute__((aligned(1024))) char ring[NS * kRingTileBytes];
   int u, id;  // u counts (unit, query head) pairs: with grouped-query attention a unit has a.group heads
-  if (!locate_heads(a.units, a.group, a.pairs * a.ksplit, u, id)) return;
+  if (!locate_heads(a.units, a.whole, a.group, a.pairs * a.ksplit, u, id)) return;
   const int seg = id % a.ksplit, pair_id = id / a.ksplit;  // which share of the keys, which blocks of queries
   float* const lse_out = a.lse_of_share(seg);  // see merge_key_shares
   const int uk = u / a.group;  // the unit: its keys and its length
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(256, 2) void prefill_columns_mfma(PrefillArgs a) {
   __shared__ __attribute__((aligned(256))) float lse_s[kLseStages][4][kTile];  // [stage][wave][query of the tile]
   __shared__ __attribute__((aligned(16))) float rinv_s[COUNT ? kLseStages : 1][COUNT ? kTile : 4];  // 1 / (i + 1)
   int u, id;
-  if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
+  if (!locate(a.units, a.whole, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;  // which share of the queries, which blocks of keys
   float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int len = a.len[u];
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(WAVES * kWave) void prefill_columns_gqa_mfma(Prefil
   __shared__ __attribute__((aligned(16))) char lds[2][kTile * kLdsRow];
   __shared__ __attribute__((aligned(16))) float lse_s[2][kTile];
   int u, id;
-  if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
+  if (!locate(a.units, a.whole, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;  // which share of the queries, which blocks of keys
   float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int G = a.group, HP = (G + 1) / 2;  // head pairs per block of 32 queries
@@ -730,7 +730,7 @@ __global__ __launch_bounds__(WAVES * kWave) void prefill_columns_gqa_pow2_mfma(P
   __shared__ __attribute__((aligned(16))) char lds[2][kTile * kLdsRow];
   __shared__ __attribute__((aligned(16))) float lse_s[2][kTile];
   int u, id;
-  if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
+  if (!locate(a.units, a.whole, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;  // which share of the queries, which blocks of keys
   float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int len = a.len[u];
@@ -840,7 +840,7 @@ __global__ __launch_bounds__(256, 2) void prefill_columns_gqa_ring(PrefillArgs a
   __shared__ __attribute__((aligned(1024))) char ring[NS * kRingTileBytes];
   __shared__ __attribute__((aligned(256))) float lse_s[kLseStages][4][kTile];  // [stage][wave][row of the tile]
   int u, id;
-  if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
+  if (!locate(a.units, a.whole, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;
   float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int len = a.len[u];
@@ -1095,7 +1095,7 @@ __global__ __launch_bounds__(256, 3) void prefill_rows_out_mfma(PrefillArgs a) {
   constexpr int NS = OutRing::kStages;
   __shared__ __attribute__((aligned(1024))) char ring[NS * OutRing::kStageBytes];
   int u, blk_id;
-  if (!locate_heads(a.units, a.group, a.pairs, u, blk_id)) return;  // u counts (unit, query head) pairs
+  if (!locate_heads(a.units, a.whole, a.group, a.pairs, u, blk_id)) return;  // u counts (unit, query head) pairs
   const int uk = u / a.group;  // the unit: its keys, values and length
   const int len = a.len[uk];
   const int n_blocks = (len + kOwnQ - 1) / kOwnQ;
@@ -1442,6 +1442,8 @@ bool plan_override(const PrefillArgs& a, int most_split, PassPlan& plan) {
   return true;
 }
 
+constexpr int kResident = 2;  // workgroups of the passes that a compute unit holds
+
 void launch_rows(PrefillArgs& a, const PassPlan& columns, hipStream_t s) {
   PassPlan plan;
   if (!plan_override(a, a.row_shares(), plan)) plan = plan_rows(kBF16, D, a.units, a.group, a.L_max, a.row_shares());
@@ -1450,7 +1452,9 @@ void launch_rows(PrefillArgs& a, const PassPlan& columns, hipStream_t s) {
   ProfScope ps(kProfPrefillRows, s);
   PrefillArgs b = a;
   b.paired = plan.paired; b.pairs = plan.ids; b.ksplit = plan.split;
-  hipLaunchKernelGGL(prefill_rows_mfma, dim3(workgroup_ids(a.units, a.group * plan.ids * plan.split)), dim3(4 * kWave), 0, s, b);
+  const int ids = a.group * plan.ids * plan.split;
+  b.whole = units_on_whole_dies(a.units, ids, kResident);
+  hipLaunchKernelGGL(prefill_rows_mfma, dim3(workgroup_ids(a.units, b.whole, ids)), dim3(4 * kWave), 0, s, b);
   if (plan.split > a.lse_shares) launch_merge_key_shares(b, s);
 }
 
@@ -1463,7 +1467,9 @@ hipError_t launch_columns(PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
   ProfScope ps(kProfPrefillColumns, s);
   PrefillArgs b = a;
   b.paired = plan.paired; b.pairs = plan.ids; b.qsplit = plan.split;
-  const dim3 grid(workgroup_ids(a.units, plan.ids * plan.split));
+  const int ids = plan.ids * plan.split;
+  b.whole = units_on_whole_dies(a.units, ids, kResident);
+  const dim3 grid(workgroup_ids(a.units, b.whole, ids));
   if (a.group != 1) launch_columns_grouped<4>(b, grid, s);
   else if (a.pol.counts_above_average()) hipLaunchKernelGGL(prefill_columns_mfma<true>, grid, dim3(4 * kWave), 0, s, b);
   else hipLaunchKernelGGL(prefill_columns_mfma<false>, grid, dim3(4 * kWave), 0, s, b);
@@ -1503,7 +1509,8 @@ hipError_t launch_prefill_attention_mfma(PrefillArgs& a, hipStream_t s) {
     PrefillArgs b = a;
     b.paired = 0;
     b.pairs = ceil_div(a.L_max, 128);
-    hipLaunchKernelGGL(prefill_rows_out_mfma, dim3(workgroup_ids(a.units, a.group * b.pairs)), dim3(256), 0, s, b);
+    b.whole = units_on_whole_dies(a.units, a.group * b.pairs, 3);
+    hipLaunchKernelGGL(prefill_rows_out_mfma, dim3(workgroup_ids(a.units, b.whole, a.group * b.pairs)), dim3(256), 0, s, b);
   } else if (!a.skip_rows) {
     launch_rows(a, columns, s);
   }

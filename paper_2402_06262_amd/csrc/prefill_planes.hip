@@ -319,7 +319,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : DT == kBF16 ? 4 : 3) void 
   __shared__ float other[2][PARTS > 1 ? PARTS - 1 : 1][PARTS > 1 ? kOwn : 1];
   __shared__ int odd_s[2];  // number of the last tile in this buffer that holds values of no exact planes (fp32)
   int u, id;
-  if (!locate_heads(a.units, a.group, a.pairs * a.ksplit, u, id)) return;
+  if (!locate_heads(a.units, a.whole, a.group, a.pairs * a.ksplit, u, id)) return;
   const int seg = id % a.ksplit, pair_id = id / a.ksplit;
   float* const lse_out = a.lse_of_share(seg);  // see merge_key_shares
   const int uk = u / a.group;
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kThreads, (kColumnWaves<DT, D, PARTS, HEADS>)) void
   __shared__ float other[2][PARTS > 1 ? PARTS - 1 : 1][PARTS > 1 ? kOwn : 1];
   __shared__ int odd_s[2];  // see prefill_rows_planes
   int u, id;
-  if (!locate(a.units, a.pairs * a.qsplit, u, id)) return;
+  if (!locate(a.units, a.whole, a.pairs * a.qsplit, u, id)) return;
   const int seg = id % a.qsplit, pair_id = id / a.qsplit;
   float *const out1 = a.sums_of(seg, 0), *const out2 = a.sums_of(seg, 1);
   const int G = HEADS != 1 ? a.group : 1;
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(kThreads, DT == kF32 && D == 128 ? 1 : 2) void pref
   __shared__ float other[2][PARTS > 1 ? 2 * kWave : 1];
   __shared__ int odd_s[NBUF], odd_v[NBUF];  // see prefill_rows_planes
   int u, blk_id;
-  if (!locate_heads(a.units, a.group, a.pairs, u, blk_id)) return;
+  if (!locate_heads(a.units, a.whole, a.group, a.pairs, u, blk_id)) return;
   const int uk = u / a.group;
   const int len = a.len[uk];
   const int n_blocks = (len + kOwn - 1) / kOwn;
@@ -840,12 +840,17 @@ void launch_columns_of_group(const PrefillArgs& b, unsigned n, hipStream_t s) {
   }
 }
 
+// Workgroups of the passes that a compute unit holds (fp32 / 128 with two parts: one).
+template <int DT, int D> constexpr int kResident = D == 128 ? 2 : DT == kBF16 ? 4 : 3;
+
 template <int DT, int D>
 void launch_rows(const PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
   ProfScope ps(kProfPrefillRows, s);
   PrefillArgs b = a;
   b.pairs = plan.ids; b.paired = plan.paired; b.ksplit = plan.split;
-  const dim3 grid(mfma::workgroup_ids(a.units, a.group * plan.ids * plan.split));
+  const int ids = a.group * plan.ids * plan.split;
+  b.whole = mfma::units_on_whole_dies(a.units, ids, kResident<DT, D>);
+  const dim3 grid(mfma::workgroup_ids(a.units, b.whole, ids));
   switch (plan.parts) {
     case 1: hipLaunchKernelGGL((prefill_rows_planes<DT, D, 1>), grid, dim3(kThreads), 0, s, b); break;
     case 2: if constexpr (D == 64 || DT == kBF16) hipLaunchKernelGGL((prefill_rows_planes<DT, D, 2>), grid, dim3(kThreads), 0, s, b); break;
@@ -868,7 +873,8 @@ void launch_rows_out(const PrefillArgs& a, hipStream_t s) {
   int parts = D == 64 ? 2 : streams * ceil_div(a.L_max, 64) <= 300 ? 2 : 1;
   if (DT == kBF16 && streams * ceil_div(a.L_max, 64) < 512 && a.L_max > 384) parts = 4;
   b.pairs = ceil_div(a.L_max, 128 / parts);
-  const dim3 grid(mfma::workgroup_ids(a.units, a.group * b.pairs));
+  b.whole = mfma::units_on_whole_dies(a.units, a.group * b.pairs, D == 128 ? 1 : DT == kBF16 && parts == 2 ? 3 : 2);
+  const dim3 grid(mfma::workgroup_ids(a.units, b.whole, a.group * b.pairs));
   switch (parts) {
     case 1: if constexpr (D == 128) hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, 1>), grid, dim3(kThreads), 0, s, b); break;
     case 2: hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, 2>), grid, dim3(kThreads), 0, s, b); break;
@@ -882,7 +888,9 @@ void launch_columns(PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
   PrefillArgs b = a;
   b.pairs = plan.ids; b.paired = plan.paired; b.qsplit = plan.split;
   if (a.lse_given != nullptr) { b.lse = const_cast<float*>(a.lse_given); b.lse_scale = kLog2e; }  // read, never written here
-  const unsigned n = mfma::workgroup_ids(a.units, plan.ids * plan.split);
+  const int ids = plan.ids * plan.split;
+  b.whole = mfma::units_on_whole_dies(a.units, ids, DT == kF32 && D == 128 && plan.parts == 2 ? 1 : kResident<DT, D>);
+  const unsigned n = mfma::workgroup_ids(a.units, b.whole, ids);
   switch (plan.parts) {
     case 1: launch_columns_of_group<DT, D, 1>(b, n, s); break;
     case 2: launch_columns_of_group<DT, D, 2>(b, n, s); break;

@@ -14,39 +14,45 @@ namespace mfma {
 // would leave dies without work if the few units left over were treated so: those share the dies out evenly, four
 // units two dies each, two or six units four dies each, any other number all dies for every unit (whole units on whole dies: 2
 // units x 8 heads x 4396 tokens of bf16 / 64 with output took 640 us, 3 x 8 x 2578 of fp32 / 64 679; now 363 and 458).  Seven,
-// or six behind others, leave so few dies without work that a unit's own L2 is worth more.  Whole prompts with shared dies
-// against whole ones, geometric means over the four forms and 400 to 3000 tokens, full / of different lengths: 7 units
-// 1.11 / 1.01, 14 1.04 / 1.02, 15 1.06 / 1.05, 23 1.06 / 1.03, 46 1.02 / 1.00, 47 1.04 / 1.01, 215 1.00 / 1.01; but 6 units
-// 1.00 / 0.99, five left over (5, 13, 21) 0.98 to 1.01 and fewer (9, 12, 20, 25, 28, 36, 100 units) 0.94 to 0.99.  The grid
-// is one-dimensional over workgroup_ids(units, pairs) ids.
-__host__ __device__ inline int units_on_whole_dies(int units) {  // (or two more than there are)
-  return units < 7 ? 0 : (units + 2) & ~7;
+// or six behind others, leave so few dies without work that a unit's own L2 is worth more, if the unit more that a die then has
+// does not make for one more round of workgroups (38 x 6597 tokens of bf16 / 128: 65 workgroups on dies that hold 64, 480 us
+// against 604) and all dies are done within three rounds.  260 prompts of 7 to 126 units in all forms, shared against whole
+// dies, geometric means: one round 1.03, two 1.03, three 1.02, more 0.99; six units by themselves and five left over 0.99 to
+// 1.01, fewer (9, 12, 20, 25, 28, 36, 100 units) 0.94 to 0.99.  The grid is one-dimensional over workgroup_ids(units, whole,
+// pairs) ids.
+// whole: the units that go to whole dies, a multiple of 8 (up to two more than there are); resident: workgroups that a compute
+// unit holds.
+inline int units_on_whole_dies(int units, int pairs, int resident) {
+  const int even = units & ~7;
+  if (units < 7 || units - even < 6) return even;
+  const long long holds = 32ll * resident, more = static_cast<long long>(even / 8 + 1) * pairs;
+  const long long shared = (static_cast<long long>(units) * pairs + 7) / 8, rounds = (more + holds - 1) / holds;
+  return rounds <= 3 && rounds == (shared + holds - 1) / holds ? even + 8 : even;
 }
-__host__ __device__ inline unsigned workgroup_ids(int units, int pairs) {
-  const unsigned even = static_cast<unsigned>(units_on_whole_dies(units)), all = static_cast<unsigned>(units);
-  const unsigned rest = all > even ? all - even : 0;
-  return even * pairs + (rest * pairs + 7) / 8 * 8;
+inline unsigned workgroup_ids(int units, int whole, int pairs) {
+  const unsigned rest = units > whole ? static_cast<unsigned>(units - whole) : 0u;
+  return static_cast<unsigned>(whole) * pairs + (rest * pairs + 7) / 8 * 8;
 }
-__device__ __forceinline__ bool locate(int units, int pairs, int& unit, int& pair) {
-  const int lin = blockIdx.x, even = units_on_whole_dies(units);
-  const int seq = lin >> 3;
-  if (seq * 8 < even * pairs) {
+__device__ __forceinline__ bool locate(int units, int whole, int pairs, int& unit, int& pair) {
+  const int lin = blockIdx.x, seq = lin >> 3;
+  if (seq * 8 < whole * pairs) {
     unit = (seq / pairs) * 8 + (lin & 7);
     pair = seq % pairs;
     return unit < units;
   }
   const int rest = units & 7, groups = rest & -rest;  // of units and of dies: 1, 2 or 4
   const int die = lin & 7, per = 8 / groups;          // dies of a group
-  const int k = (seq - (even >> 3) * pairs) * per + die / groups;  // among the workgroups of the die's group of units
-  unit = even + die % groups + groups * (k / pairs);
+  const int k = (seq - (whole >> 3) * pairs) * per + die / groups;  // among the workgroups of the die's group of units
+  unit = whole + die % groups + groups * (k / pairs);
   pair = k % pairs;
   return unit < units;
 }
 // The same for (unit, query head) pairs, u = unit * group + head: the heads of a unit stream the same keys (and
-// values), so they share a die, one head after the other.  The grid covers workgroup_ids(units, group * pairs) ids.
-__device__ __forceinline__ bool locate_heads(int units, int group, int pairs, int& u, int& pair) {
+// values), so they share a die, one head after the other.  The grid covers workgroup_ids(units, whole, group * pairs)
+// ids.
+__device__ __forceinline__ bool locate_heads(int units, int whole, int group, int pairs, int& u, int& pair) {
   int unit, id;
-  if (!locate(units, group * pairs, unit, id)) return false;
+  if (!locate(units, whole, group * pairs, unit, id)) return false;
   u = unit * group + id / pairs;
   pair = id % pairs;
   return true;
