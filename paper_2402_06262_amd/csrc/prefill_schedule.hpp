@@ -10,13 +10,18 @@
 //   parts    the four waves of a workgroup share 64 or 32 owned rows (see Shares in prefill_planes.hip).
 // More shares are more workgroups for the rounds in which they fill the chip, the last of which may be nearly empty, against
 // what a share costs by itself (its owned rows, its first tiles, its sums): six to eight tiles' time (`rounds_split`).
-// The constants are those of least regret over 310 prompts with every schedule timed (1 to 1024 units, 1 to 8 heads, 100 to
-// 16384 tokens, ragged and not): what they pick takes 5 % longer than the best schedule.  Column pass, us, with two shares and
-// 64 owned rows at most -> now:
+// Column pass, us, with two shares and 64 owned rows at most -> now:
 //   1 unit  x 8 heads x 3852 tokens of fp32 / 128  823 -> 125     2 units x 8 x 4396 of bf16 / 64   178 -> 60
 //   3 units x 8 heads x 515 tokens of bf16 / 128    73 -> 12      1 unit  x 4 x 426 of bf16 / 128    30 -> 8
+// These rules count workgroups, and where workgroups are about as many as the chip holds a count says little: 24 units x 2500
+// tokens of fp32 / 128 took 344 us where pairs in two shares take 270, 100 x <= 1500 of bf16 / 128 124 against 116.  So what they
+// pick is held against the schedule of one or two shares that serves many units, by an estimate of both passes' time
+// (`estimate`), and left where that is clearly less: 619 prompts of 1 to 1000 units, the rules alone against this, geometric mean
+// 1.01, between 0.93 and 1.25.
 #pragma once
 #include "kernels.hpp"
+
+#include <math.h>
 
 namespace roco {
 
@@ -90,7 +95,7 @@ inline PassPlan plan_planes(long long streams, int L_max, const PlanRule& r, int
 }
 
 // dtype 0 = fp32, 1 = bf16
-inline PassPlan plan_rows(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
+inline PassPlan filling_rows(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
   const long long streams = static_cast<long long>(units) * group;
   if (dtype == 1 && head_dim == 128) {
     const int ids = ceil_div(ceil_div(L_max, 256), 2);
@@ -105,7 +110,7 @@ inline PassPlan plan_rows(int dtype, int head_dim, int units, int group, int L_m
                      [&](int parts) { return ceil_div(L_max, planes_tile_rows(dtype, head_dim, parts, false)); });
 }
 
-inline PassPlan plan_columns(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
+inline PassPlan filling_columns(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
   if (dtype == 1 && head_dim == 128 && L_max <= 512 && units >= 480) return {true, 1, 1, 1, 1};
   // 256 owned rows from four blocks on (three are an uneven pair), or two with several heads' tiles for each.  Whole prompts, us,
   // with 128 / 256: 512 units x 800 tokens 212 / 187, 256 x 1000 131 / 117, 100 x 4 heads x 700 160 / 147, 64 x 1000 59 / 60; of three
@@ -120,6 +125,92 @@ inline PassPlan plan_columns(int dtype, int head_dim, int units, int group, int 
   return plan_planes(units, L_max, r, most_split, [&](int parts) {
     return column_tiles(planes_tile_rows(dtype, head_dim, parts, group > 1 && !heads_in_tile(group)), group, L_max);
   });
+}
+
+// The schedule of one or two shares: the wide kernels' pairs for bf16 / 128; else pairs of blocks of 128 rows, with 64 rows
+// (where the waves can share them) and / or two shares where `target` workgroups are not reached, and single blocks where even
+// that leaves compute units idle.
+inline PassPlan plan_of_two_shares(int dtype, int head_dim, long long streams, int units, int L_max, bool may_split) {
+  if (dtype == 1 && head_dim == 128) {
+    const int ids = ceil_div(ceil_div(L_max, 256), 2);
+    return {true, 1, may_split && static_cast<long long>(units) * ids < 1024 ? 2 : 1, 1, ids};
+  }
+  const int target = dtype == 1 ? 1024 : 512, blocks = ceil_div(L_max, 128);
+  const bool may_part = dtype == 1 || head_dim == 64;
+  const long long pairs = streams * ceil_div(blocks, 2);
+  PassPlan p = {false, 1, 1, 1, 0};
+  if (pairs < target) {
+    const bool both = 2 * pairs < target;
+    if (may_part && (dtype == 1 || both || !may_split)) p.parts = 2;
+    if (may_split && (dtype == 0 || both) && blocks > 1) p.split = 2;
+  }
+  const int own = ceil_div(L_max, 128 / p.parts);
+  p.paired = streams * ceil_div(own, 2) * p.split >= 256 ? 1 : 0;
+  p.ids = p.paired ? ceil_div(own, 2) : own;
+  return p;
+}
+
+// What a pass's workgroups cost, in the time that a compute unit full of them takes for a tile of each of its workgroups.  Fitted
+// to 800 prompts with every schedule timed (1 to 1000 units, 1 to 9 heads, 134 to 7300 tokens, ragged and not).
+struct PassCost {
+  int resident;               // workgroups that a compute unit holds
+  float tile[3], wide;        // a streamed tile with 1, 2, 4 parts; of the wide kernels
+  float own, own_wide;        // what comes with a block of owned rows: the rows, the first tiles, the sums
+  float alone;                // how much longer than its share of a full compute unit's time a workgroup takes by itself
+};
+
+// Time of the pass if its workgroups are `share` of those of the plan.  tiles: streamed tiles of the longest block.
+inline float estimate(const PassCost& c, const PassPlan& p, long long streams, int L_max, int tiles, float share) {
+  constexpr float kUnits = 256.0f;  // compute units
+  const int blocks = ceil_div(L_max, p.wide ? 256 : 128 / p.parts);
+  const float n = share * static_cast<float>(streams) * static_cast<float>(p.ids) * static_cast<float>(p.split);
+  const float resident = static_cast<float>(p.wide ? 2 : c.resident), own = p.wide ? c.own_wide : c.own;
+  const float walk = (p.wide ? c.wide : c.tile[p.parts >> 1]) * static_cast<float>(tiles) / static_cast<float>(p.split);
+  const float mean = walk * static_cast<float>(blocks + 1) / static_cast<float>(2 * blocks) + own, longest = walk + own;
+  if (p.paired) {  // all alike: rounds, of which the last may leave compute units with fewer workgroups, or without
+    const float full = floorf(n / (kUnits * resident)), left = ceilf(n / kUnits - full * resident);
+    return (blocks == 1 ? longest : 2.0f * mean) * (full * resident + (left <= 0.0f ? 0.0f : left < c.alone ? c.alone : left));
+  }
+  // The longest first: where all run at a time some compute unit has the longest of every rank, else short ones fill the end.
+  if (n > kUnits * resident) return mean * n / kUnits + 1.25f * longest;
+  const float ranks = mean * n / kUnits + 2.0f * (longest - mean);
+  return ranks > c.alone * longest ? ranks : c.alone * longest;
+}
+
+// `filling`, unless the schedule of two shares is estimated to take 6 % less.  (Three quarters of the workgroups: prompts
+// of different lengths, which the host does not know.)  tiles(plan): streamed tiles of the longest block.
+template <class TilesFn>
+inline PassPlan quicker_plan(const PassPlan& filling, const PassPlan& two, const PassCost& filling_cost, const PassCost& two_cost,
+                             long long streams, int L_max, int most_split, TilesFn tiles) {
+  if (two.split > most_split) return filling;
+  const auto time = [&](const PassCost& c, const PassPlan& p) {
+    return estimate(c, p, streams, L_max, tiles(p), 1.0f) + 0.5f * estimate(c, p, streams, L_max, tiles(p), 0.75f);
+  };
+  return time(two_cost, two) < 0.94f * time(filling_cost, filling) ? two : filling;
+}
+
+inline PassPlan plan_rows(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
+  static constexpr PassCost kCost[2][2] = {{{3, {1.0f, 0.65f, 1.0f}, 0.0f, 0.75f, 0.0f, 1.4f}, {2, {1.0f, 1.0f, 1.0f}, 0.0f, 1.5f, 0.0f, 1.8f}},
+                                           {{4, {1.0f, 0.6f, 0.35f}, 0.0f, 0.5f, 0.0f, 1.6f}, {2, {1.0f, 0.65f, 0.6f}, 0.6f, 0.75f, 1.5f, 1.4f}}};
+  const PassCost& cost = kCost[dtype][head_dim == 128];
+  const long long streams = static_cast<long long>(units) * group;
+  return quicker_plan(filling_rows(dtype, head_dim, units, group, L_max, most_split),
+                      plan_of_two_shares(dtype, head_dim, streams, units, L_max, group == 1), cost, cost, streams, L_max, most_split,
+                      [&](const PassPlan& p) { return ceil_div(L_max, p.wide ? 64 : planes_tile_rows(dtype, head_dim, p.parts, false)); });
+}
+
+inline PassPlan plan_columns(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
+  static constexpr PassCost kCost[2][2] = {{{3, {1.0f, 0.65f, 1.0f}, 0.0f, 1.0f, 0.0f, 2.4f}, {2, {1.0f, 1.8f, 1.0f}, 0.0f, 2.0f, 0.0f, 1.8f}},
+                                           {{4, {1.0f, 0.55f, 0.5f}, 0.0f, 1.0f, 0.0f, 2.4f}, {2, {1.0f, 0.65f, 0.8f}, 0.6f, 0.75f, 1.5f, 1.4f}}};
+  const PassPlan filling = filling_columns(dtype, head_dim, units, group, L_max, most_split);
+  const PassCost& cost = kCost[dtype][head_dim == 128];
+  PassCost alone = cost;
+  if (dtype == 0 && head_dim == 128 && filling.parts == 2) alone.resident = 1;  // (tiles of 64 rows fill the LDS)
+  return quicker_plan(filling, plan_of_two_shares(dtype, head_dim, units, units, L_max, true), alone, cost, units, L_max, most_split,
+                      [&](const PassPlan& p) {
+                        const bool small = group > 1 && !heads_in_tile(group);
+                        return column_tiles(p.wide ? 64 : planes_tile_rows(dtype, head_dim, p.parts, small), group, L_max);
+                      });
 }
 
 // Whether the column pass merges the normalisers of a row pass that several workgroups divided, as it stages them: the kernels

@@ -58,9 +58,16 @@ def test_shared_blocks_and_every_group(monkeypatch, dtype, d, units, group, L):
     _both_paths(monkeypatch, dtype, d, units, group, L, lens, window=24 if group == 3 else 0)
 
 
+@pytest.mark.parametrize("dtype,d", FORMS)
+@pytest.mark.parametrize("units,group,L", [(9, 1, 140), (34, 1, 1207), (66, 2, 334), (37, 2, 237), (122, 2, 140), (25, 3, 431)])
+def test_schedules_of_two_shares(monkeypatch, dtype, d, units, group, L):
+    """Numbers of units at which one form or another is estimated quicker with two shares at most than with what fills the chip."""
+    _both_paths(monkeypatch, dtype, d, units, group, L, [L - (11 * u) % (L // 2) for u in range(units)])
+
+
 @pytest.mark.parametrize("units,group,L", [(130, 1, 768), (130, 1, 769), (130, 2, 512), (130, 3, 513), (40, 8, 769), (70, 5, 1023)])
 def test_owned_rows_of_a_column_block(monkeypatch, units, group, L):
-    """128 or 256: both sides of the rule."""
+    """128 or 256, with and without shares."""
     lens = [L - (13 * u) % (L // 2) for u in range(units)]
     _both_paths(monkeypatch, "bf16", 128, units, group, L, lens)
 
