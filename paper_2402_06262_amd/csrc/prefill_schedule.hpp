@@ -177,8 +177,9 @@ inline float estimate(const PassCost& c, const PassPlan& p, long long streams, i
   return ranks > c.alone * longest ? ranks : c.alone * longest;
 }
 
-// `filling`, unless the schedule of two shares is estimated to take 6 % less.  (Three quarters of the workgroups: prompts
-// of different lengths, which the host does not know.)  tiles(plan): streamed tiles of the longest block.
+// `filling`, unless the schedule of two shares is estimated to take 6 % less, or anything less where both are the wide kernels'
+// pairs, whose times the estimate does not have to compare with those of other kernels.  (Three quarters of the workgroups:
+// prompts of different lengths, which the host does not know.)  tiles(plan): streamed tiles of the longest block.
 template <class TilesFn>
 inline PassPlan quicker_plan(const PassPlan& filling, const PassPlan& two, const PassCost& filling_cost, const PassCost& two_cost,
                              long long streams, int L_max, int most_split, TilesFn tiles) {
@@ -186,7 +187,7 @@ inline PassPlan quicker_plan(const PassPlan& filling, const PassPlan& two, const
   const auto time = [&](const PassCost& c, const PassPlan& p) {
     return estimate(c, p, streams, L_max, tiles(p), 1.0f) + 0.5f * estimate(c, p, streams, L_max, tiles(p), 0.75f);
   };
-  return time(two_cost, two) < 0.94f * time(filling_cost, filling) ? two : filling;
+  return time(two_cost, two) < (filling.wide && two.wide ? 1.0f : 0.94f) * time(filling_cost, filling) ? two : filling;
 }
 
 inline PassPlan plan_rows(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
