@@ -396,7 +396,8 @@ int roco_probe_mfma(int32_t workgroups, int32_t iters, int32_t operands, float* 
  *                              (any of the three also keeps short or few prompts on the kernels with 256 rows per workgroup)
  *   ROCO_BLOCK_SPLITS=n        splits of the budget in the block-wise / grouped steps (default: about 512 / units from 64 units on;
  *                              below, 512 / units and 24 at most, or 256 / units with more than 16 query rows of fp32 /
- *                              head_dim 128; no split has more than 2^22 slots)
+ *                              head_dim 128; bf16 / head_dim 128: 8 at most, or up to 16 of at least 256 slots with up to 16
+ *                              query rows and 256 / units; no split has more than 2^22 slots)
  *   ROCO_BLOCK_SINGLE=0        single-token block steps go through the preparing kernel like longer blocks
  */
 

@@ -400,15 +400,25 @@ int run_block(const roco_params* params, int tokens, int heads, const void* q, c
   a.streaming = streaming_loads(params) ? 1 : 0;
   {  // split the budget into 64-slot-aligned ranges: two resident workgroups per compute unit measured best
     // (more splits cost more partial results to write and merge than they gain in balance).  Below 64 units no workgroup may be
-    // left for a second round, and beyond 24 splits merging them costs what the shorter walk saves.  Steps, us, with 8 / 12 / 16 / 24 / 32
-    // splits: 1 unit x 2340 slots x 8 heads of bf16 / 64 28.1 / 25.7 / 23.5 / 21.7 / 21.8, 7 x 3280 x 4 tokens of fp32 / 128
-    // 56 / 50 / 47 / 44 / 42, 3 x 4096 x 8 tokens of bf16 / 64 53 / 49 / 44 / 42 / 42, 8 x 3252 x 3 heads of bf16 / 128 26.1 / 24.5 /
-    // 24.0 (16 is what its 32 rows allow); but 40 x 4096 x 16 tokens of bf16 / 128 59.7 / 59.4 / 65.3.
+    // left for a second round.
+    // bf16 / 128 streams a split through tiles that arrive ahead, so that shorter splits gain little and their partials cost more:
+    // 8, or up to 16 of at least 256 slots where the rows are few and every workgroup has a compute unit to itself.  Steps, us, with
+    // 5 / 8 / 10 to 16 splits: 40 units x 640 slots x 8 tokens of 4 heads 34.3 / - / 38.5, 25 x 912 x 30 tokens 40.0 / 40.1 / 44.9,
+    // 25 x 912 x 4 tokens 27.8 / 26.9 / 29.2, 40 x 4000 x 4 heads - / 34.0 / 39.9, but 8 x 4000 x 4 heads - / 28.7 / 25.9.
+    // The others stop at 24 splits, beyond which merging them costs what the shorter walk saves, with 8 / 12 / 16 / 24 / 32 splits: 1
+    // unit x 2340 slots x 8 heads of bf16 / 64 28.1 / 25.7 / 23.5 / 21.7 / 21.8, 7 x 3280 x 4 tokens of fp32 / 128 56 / 50 / 47 /
+    // 44 / 42, 3 x 4096 x 8 tokens of bf16 / 64 53 / 49 / 44 / 42 / 42.
     // Above 16 rows of fp32 / 128 the LDS has room for one workgroup: 24 x 3780 x 30 tokens with 8 / 10 / 12 splits 152 / 131 / 177,
     // 48 x 3000 x 40 with 5 / 8 225 / 262, 60 x 2000 x 24 with 4 / 8 123 / 127.
+    const bool matrix = params->dtype == ROCO_BF16 && params->head_dim == 128;
     const int resident = params->dtype == ROCO_F32 && params->head_dim == 128 && a.queries > 16 ? 256 : 512;
     int want = env_int("ROCO_BLOCK_SPLITS", 0);
-    if (want <= 0) want = params->units < 64 ? std::max(1, std::min(resident / params->units, 24)) : (512 + params->units - 1) / params->units;
+    if (want <= 0) {
+      want = params->units < 64 ? resident / params->units : (512 + params->units - 1) / params->units;
+      int most = 24;
+      if (matrix) most = a.queries > 16 ? 8 : std::max(8, std::min({16, 256 / params->units, params->budget / 256}));
+      want = std::max(1, std::min(want, most));
+    }
     if (want > kBlockPartials / a.qrows) want = kBlockPartials / a.qrows;
     const int max_by_rows = (params->budget + 63) / 64;
     if (want > max_by_rows) want = max_by_rows;
