@@ -496,8 +496,13 @@ __device__ __forceinline__ int victim_by_statistics(const float* stats, const in
 
 // QMAX: most query rows the instantiation takes (8, 16, 32 or 64).  The smaller ones need fewer registers and less LDS,
 // so more workgroups fit a compute unit, and they keep two tiles in flight per workgroup instead of one.
-template <int DT, int D, int QMAX>
-__global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(BlockArgs a) {
+// SINGLE: a single-token step without block_prepare (BlockArgs::single).  What it needs besides is kept out of the other steps'
+// kernels, whose registers decide how many workgroups a compute unit holds: in one kernel for both, bf16 / 64 with 32 rows took
+// 207 instead of 166, two workgroups instead of three (551 units x 1488 slots x 17 tokens 350 us against 252).  The single-token
+// kernels of bf16 / 64 for 16 and 32 rows are held to three workgroups too (300 units x 744 slots x 16 heads 56.2 us, 66.5 with
+// two; x 24 heads 73.7, 99.0 with two).
+template <int DT, int D, int QMAX, bool SINGLE>
+__global__ __launch_bounds__(256, (D != 64 ? 1 : DT == kBF16 && (QMAX == 16 || QMAX == 32) ? 3 : 2)) void block_attend_shared(BlockArgs a) {
   using G = RowGeom<DT, D>;
   using T = SharedTile<D>;
   constexpr int TR = T::kRows, KS = T::kStride, WAVES = 4;
@@ -525,7 +530,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
   // block_prepare has run: the block's rows are in the cache and counted -- or it is a single-token step without it, as in block_attend
   int n = a.n_used[u];
   int fresh = -1;
-  if (a.single) {
+  if constexpr (SINGLE) {
     const bool was_full = n >= B;
     fresh = was_full ? min(a.next_slot[u], B - 1) : n;
     if (fresh < 0) {  // (the tiles are not in use yet)
@@ -586,8 +591,8 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
     }
     if (tid < TR) {
       const int slot = min(tr0 + tid, n - 1);
-      fb = a.single ? -1 : bidx[slot];
-      fp = slot == fresh ? qp0 : pos[slot];
+      fb = SINGLE ? -1 : bidx[slot];
+      fp = SINGLE && slot == fresh ? qp0 : pos[slot];
     }
   };
 #pragma unroll
@@ -602,7 +607,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
       const int t = t0 + j;
       if (t >= n_tiles) break;
       const int tr0 = row0 + t * TR;
-      if (fresh >= tr0 && fresh < min(tr0 + TR, row1)) {  // a single token's row takes its slot, here and in the cache
+      if (SINGLE && fresh >= tr0 && fresh < min(tr0 + TR, row1)) {  // a single token's row takes its slot, here and in the cache
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
           const int idx = tid + 256 * i, col = (idx % G::LPR) * 16;
@@ -616,8 +621,9 @@ __global__ __launch_bounds__(256, (D == 64 ? 2 : 1)) void block_attend_shared(Bl
       }
       // Rows behind the last slot are copies of one (their loads only had to stay in range), and that one may be the slot which a
       // single token fills for the first time, whose bytes are arbitrary, or whose infinite value it overwrites: as V they are
-      // zeros, since a weight of 0 does not silence NaN or infinity.  (Scores of such rows are replaced, whatever they are.)
-      if (tr0 + TR > row1) {
+      // zeros, since a weight of 0 does not silence NaN or infinity.  (Scores of such rows are replaced, whatever they are.  In the
+      // other steps block_prepare has written that slot.)
+      if (SINGLE && tr0 + TR > row1) {
 #pragma unroll
         for (int i = 0; i < CH; ++i)
           if (tr0 + (tid + 256 * i) / G::LPR >= row1) pv[j][i] = make_uint4(0u, 0u, 0u, 0u);
@@ -952,14 +958,18 @@ void launch_block_tail(const BlockArgs& a, hipStream_t s) {
   else launch_block_finish<DT, D, 2>(a, s);
 }
 
-template <int DT, int D, int QMAX>
-hipError_t launch_block_shared_q(const BlockArgs& a, hipStream_t s) {
+template <int DT, int D, int QMAX, bool SINGLE>
+hipError_t launch_block_shared_t(const BlockArgs& a, hipStream_t s) {
   const size_t lds = SharedTile<D>::lds_bytes(QMAX);  // 37 to 114 KiB: the limit is set on every call
-  const void* fn = reinterpret_cast<const void*>(block_attend_shared<DT, D, QMAX>);
+  const void* fn = reinterpret_cast<const void*>(block_attend_shared<DT, D, QMAX, SINGLE>);
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL((block_attend_shared<DT, D, QMAX>), dim3(a.splits, a.units), dim3(256), lds, s, a);
+  hipLaunchKernelGGL((block_attend_shared<DT, D, QMAX, SINGLE>), dim3(a.splits, a.units), dim3(256), lds, s, a);
   return hipSuccess;
+}
+template <int DT, int D, int QMAX>
+hipError_t launch_block_shared_q(const BlockArgs& a, hipStream_t s) {
+  return a.single ? launch_block_shared_t<DT, D, QMAX, true>(a, s) : launch_block_shared_t<DT, D, QMAX, false>(a, s);
 }
 
 template <int DT, int D>
