@@ -57,6 +57,7 @@ inline int planes_tile_rows(int dtype, int head_dim, int parts, bool small) {
 // Streamed tiles of a whole column pass for the first keys: with a group's heads inside a result tile, two times 16 / group
 // query positions per 32 rows.
 inline bool heads_in_tile(int group) { return (group >= 2 && group <= 8) || group == 16; }
+inline int heads_one_by_one(int group) { return heads_in_tile(group) ? 1 : group; }
 inline int column_tiles(int tile_rows, int group, int L_max) {
   if (heads_in_tile(group)) return ceil_div(L_max, tile_rows / 32 * 2 * (16 / group));
   return ceil_div(L_max, tile_rows) * group;
@@ -73,17 +74,21 @@ inline int rounds_split(long long workgroups, int resident, int tiles, double ow
   return split;
 }
 
+// heads: of a tile position that is taken head by head (the general grouped column pass), else 1.  A share then consists of whole
+// positions, and what a share costs by itself it costs for each of them: 64 units x 15 heads x 1000 tokens of fp32 / 128 were cut
+// into eight shares, column pass 910 us against 815 in two; 16 x 9 x 300 of bf16 / 64 into sixteen of five positions, 27.2 against 23.3.
 template <class TilesFn>
-inline PassPlan plan_planes(long long streams, int L_max, const PlanRule& r, int most_split, TilesFn tiles) {
+inline PassPlan plan_planes(long long streams, int L_max, const PlanRule& r, int most_split, int heads, TilesFn tiles) {
+  const auto positions = [&](int parts) { return tiles(parts) / heads; };
   PassPlan p = {false, 1, 1, 1, ceil_div(ceil_div(L_max, 128), 2)};
   const long long pairs = streams * p.ids;
-  p.split = r.resident != 0 ? rounds_split(pairs, r.resident, tiles(1), 6.0, most_split) : power_of_two_from(r.paired_want, pairs);
-  if (p.split <= most_split && p.split <= r.paired_split && pairs * p.split >= r.paired_want && tiles(1) >= r.paired_tiles * p.split) return p;
+  p.split = r.resident != 0 ? rounds_split(pairs, r.resident, tiles(1), 6.0 * heads, most_split) : power_of_two_from(r.paired_want, pairs);
+  if (p.split <= most_split && p.split <= r.paired_split && pairs * p.split >= r.paired_want && tiles(1) >= r.paired_tiles * p.split && p.split <= positions(1)) return p;
   long long best = 0;
   for (int parts = 1; parts <= r.most_parts; parts *= 2) {
     const int ids = ceil_div(L_max, 128 / parts);
     int split = power_of_two_from(r.single_want, streams * ids);
-    while (split > 1 && (split > most_split || tiles(parts) < r.single_tiles * split)) split /= 2;
+    while (split > 1 && (split > most_split || tiles(parts) < r.single_tiles * split || split > positions(parts))) split /= 2;
     const long long total = streams * ids * split;
     if (2 * total >= 3 * best) {  // more waves per block only where they bring half as many workgroups again
       best = total;
@@ -106,7 +111,7 @@ inline PassPlan filling_rows(int dtype, int head_dim, int units, int group, int 
   }
   const PlanRule r = dtype == 1 ? (head_dim == 64 ? PlanRule{0, 480, 2, 4, 480, 2, 4} : PlanRule{0, 384, 4, 4, 384, 3, 4})
                                 : (head_dim == 64 ? PlanRule{768, 480, 2, 4, 1024, 3, 2} : PlanRule{512, 384, 6, 4, 384, 3, 1});
-  return plan_planes(streams, L_max, r, most_split,
+  return plan_planes(streams, L_max, r, most_split, 1,
                      [&](int parts) { return ceil_div(L_max, planes_tile_rows(dtype, head_dim, parts, false)); });
 }
 
@@ -122,8 +127,8 @@ inline PassPlan filling_columns(int dtype, int head_dim, int units, int group, i
   }
   const PlanRule r = dtype == 1 ? (head_dim == 64 ? PlanRule{0, 1024, 4, 16, 1024, 2, 4} : PlanRule{0, 360, 4, 4, 480, 2, 4})
                                 : (head_dim == 64 ? PlanRule{768, 512, 2, 4, 1024, 2, 2} : PlanRule{512, 512, 4, 16, 480, 2, 2});
-  return plan_planes(units, L_max, r, most_split, [&](int parts) {
-    return column_tiles(planes_tile_rows(dtype, head_dim, parts, group > 1 && !heads_in_tile(group)), group, L_max);
+  return plan_planes(units, L_max, r, most_split, heads_one_by_one(group), [&](int parts) {
+    return column_tiles(planes_tile_rows(dtype, head_dim, parts, heads_one_by_one(group) > 1), group, L_max);
   });
 }
 
@@ -157,6 +162,7 @@ struct PassCost {
   float tile[3], wide;        // a streamed tile with 1, 2, 4 parts; of the wide kernels
   float own, own_wide;        // what comes with a block of owned rows: the rows, the first tiles, the sums
   float alone;                // how much longer than its share of a full compute unit's time a workgroup takes by itself
+  float tail = 1.25f;         // longest blocks that the end of more single blocks than run at a time lasts
 };
 
 // Time of the pass if its workgroups are `share` of those of the plan.  tiles: streamed tiles of the longest block.
@@ -172,7 +178,7 @@ inline float estimate(const PassCost& c, const PassPlan& p, long long streams, i
     return (blocks == 1 ? longest : 2.0f * mean) * (full * resident + (left <= 0.0f ? 0.0f : left < c.alone ? c.alone : left));
   }
   // The longest first: where all run at a time some compute unit has the longest of every rank, else short ones fill the end.
-  if (n > kUnits * resident) return mean * n / kUnits + 1.25f * longest;
+  if (n > kUnits * resident) return mean * n / kUnits + (p.split == 1 ? c.tail : 1.25f) * longest;
   const float ranks = mean * n / kUnits + 2.0f * (longest - mean);
   return ranks > c.alone * longest ? ranks : c.alone * longest;
 }
@@ -191,7 +197,7 @@ inline PassPlan quicker_plan(const PassPlan& filling, const PassPlan& two, const
 }
 
 inline PassPlan plan_rows(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
-  static constexpr PassCost kCost[2][2] = {{{3, {1.0f, 0.65f, 1.0f}, 0.0f, 0.75f, 0.0f, 1.4f}, {2, {1.0f, 1.0f, 1.0f}, 0.0f, 1.5f, 0.0f, 1.8f}},
+  static constexpr PassCost kCost[2][2] = {{{3, {1.0f, 0.65f, 1.0f}, 0.0f, 0.75f, 0.0f, 1.4f}, {2, {1.0f, 1.0f, 1.0f}, 0.0f, 1.5f, 0.0f, 1.8f, 1.8f}},
                                            {{4, {1.0f, 0.6f, 0.35f}, 0.0f, 0.5f, 0.0f, 1.6f}, {2, {1.0f, 0.65f, 0.6f}, 0.6f, 0.75f, 1.5f, 1.4f}}};
   const PassCost& cost = kCost[dtype][head_dim == 128];
   const long long streams = static_cast<long long>(units) * group;
@@ -201,15 +207,22 @@ inline PassPlan plan_rows(int dtype, int head_dim, int units, int group, int L_m
 }
 
 inline PassPlan plan_columns(int dtype, int head_dim, int units, int group, int L_max, int most_split) {
-  static constexpr PassCost kCost[2][2] = {{{3, {1.0f, 0.65f, 1.0f}, 0.0f, 1.0f, 0.0f, 2.4f}, {2, {1.0f, 1.8f, 1.0f}, 0.0f, 2.0f, 0.0f, 1.8f}},
+  static constexpr PassCost kCost[2][2] = {{{3, {1.0f, 0.65f, 1.0f}, 0.0f, 1.0f, 0.0f, 2.4f}, {2, {1.0f, 1.8f, 1.0f}, 0.0f, 2.0f, 0.0f, 1.8f, 1.8f}},
                                            {{4, {1.0f, 0.55f, 0.5f}, 0.0f, 1.0f, 0.0f, 2.4f}, {2, {1.0f, 0.65f, 0.8f}, 0.6f, 0.75f, 1.5f, 1.4f}}};
   const PassPlan filling = filling_columns(dtype, head_dim, units, group, L_max, most_split);
-  const PassCost& cost = kCost[dtype][head_dim == 128];
+  PassCost cost = kCost[dtype][head_dim == 128];
+  const int heads = heads_one_by_one(group);
+  if (heads > 1) {
+    // (the wide kernel has no pipelined form for such groups: 64 units x 15 heads x 1000 tokens 735 us against 535)
+    if (dtype == 1 && head_dim == 128) return filling;
+    cost.own *= static_cast<float>(heads);
+    if (dtype == 1) cost.tile[0] = 1.15f;  // (spills 40 registers)
+  }
   PassCost alone = cost;
   if (dtype == 0 && head_dim == 128 && filling.parts == 2) alone.resident = 1;  // (tiles of 64 rows fill the LDS)
   return quicker_plan(filling, plan_of_two_shares(dtype, head_dim, units, units, L_max, true), alone, cost, units, L_max, most_split,
                       [&](const PassPlan& p) {
-                        const bool small = group > 1 && !heads_in_tile(group);
+                        const bool small = heads_one_by_one(group) > 1;
                         return column_tiles(p.wide ? 64 : planes_tile_rows(dtype, head_dim, p.parts, small), group, L_max);
                       });
 }
