@@ -864,6 +864,12 @@ void launch_rows(const PrefillArgs& a, const PassPlan& plan, hipStream_t s) {
 // 128 x 1024 253 / 255, but 256 x 1024 478 / 455, 256 x 2048 1588 / 1433 and 1024 x 256 246 / 206.  Row pass, us: 32 owned rows
 // against 64 for bf16 / 64 1 x 4575 60 / 86, but 16 streams x 4396 194 / 163; 64 against 128 for fp32 / 128 7 x 2578 172 / 247,
 // but with more than one of its workgroups, which do not share a compute unit, 108 x 129 42 / 27.
+// Left-over units that share dies are streamed through one die's L2 together.  The fp32 output pass, one or two workgroups per
+// compute unit, does not hide what then misses it: with long prompts five or more left over are worth the idle dies (5 units x 2
+// heads x 4000 tokens of fp32 / 128 1018 us shared, 690 whole; 43 prompts of 5, 13, 21 and 29 units: geometric mean 1.04, between
+// 0.98 and 1.48).  Three behind others are not: 11 x 2 x 2000 0.89, 19 x 2 x 2000 0.92.
+inline bool shared_units_miss_the_l2(int units, long long unit_bytes) { return unit_bytes >= (3 << 19) && (units & 7) >= 5; }
+
 template <int DT, int D>
 void launch_rows_out(const PrefillArgs& a, hipStream_t s) {
   ProfScope ps(kProfPrefillRows, s);
@@ -874,6 +880,7 @@ void launch_rows_out(const PrefillArgs& a, hipStream_t s) {
   if (DT == kBF16 && streams * ceil_div(a.L_max, 64) < 512 && a.L_max > 384) parts = 4;
   b.pairs = ceil_div(a.L_max, 128 / parts);
   b.whole = mfma::units_on_whole_dies(a.units, a.group * b.pairs, D == 128 ? 1 : DT == kBF16 && parts == 2 ? 3 : 2);
+  if (DT == kF32 && shared_units_miss_the_l2(a.units, 2ll * a.L_max * D * 4)) b.whole = (a.units + 7) & ~7;
   const dim3 grid(mfma::workgroup_ids(a.units, b.whole, a.group * b.pairs));
   switch (parts) {
     case 1: if constexpr (D == 128) hipLaunchKernelGGL((prefill_rows_out_planes<DT, D, 1>), grid, dim3(kThreads), 0, s, b); break;
