@@ -186,10 +186,10 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // integers and is exact.  radix_select finds the k-th smallest key (k is 1-based, 1 <= k <= n) among
 // key_of(0..n-1), digits of up to 11 bits from the top; it also returns how many keys are strictly smaller and how
 // many are equal.  What it costs is its barriers and its passes over the keys, so the first digit is wide: the exponent and
-// the three leading mantissa bits (no key has the top bit, but the mark and, under `small`, negative positions) spread a unit's variances or scores over bins
-// of an eighth of an octave, and usually few enough keys share the chosen one that no second digit is counted -- as soon as a
-// bin holds at most kSelectRanked keys they are gathered and searched without another barrier.  A thread clears the bins it
-// owns while it reads them, so a digit takes three barriers.
+// the three leading mantissa bits (no key has the top bit, but the mark and, under `small`, negative positions) spread a
+// unit's variances or scores over bins of an eighth of an octave, and usually few enough keys share the chosen one that no
+// second digit is counted -- as soon as a bin holds at most kSelectRanked keys they are gathered and searched without another
+// barrier.  A thread clears the bins it owns while it reads them, so a digit takes three barriers.
 // AHEAD: keys per thread that a pass requests before it uses the first: four where they come from memory, and from LDS with few
 // threads (the step of 512 units x 2048 slots of bf16 / 128: 95.6 -> 94.1 us); with 1024 threads other waves fill the time, and
 // the longer code has to be fetched.
