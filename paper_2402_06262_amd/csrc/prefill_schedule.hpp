@@ -16,8 +16,8 @@
 // These rules count workgroups, and where workgroups are about as many as the chip holds a count says little: 24 units x 2500
 // tokens of fp32 / 128 took 344 us where pairs in two shares take 270, 100 x <= 1500 of bf16 / 128 124 against 116.  So what they
 // pick is held against the schedule of one or two shares that serves many units, by an estimate of both passes' time
-// (`estimate`), and left where that is clearly less: 619 prompts of 1 to 1000 units, the rules alone against this, geometric mean
-// 1.01, between 0.93 and 1.25.
+// (`estimate`), and left where that is less.  Whole prompts against one or two shares everywhere: 240 of 1 to 1000 units geometric
+// mean 1.49, lowest 0.96; 420 of bf16 / 128 1.36 and 0.92; 120 of groups of 9 to 40 heads 1.88 and 0.95.
 #pragma once
 #include "kernels.hpp"
 
