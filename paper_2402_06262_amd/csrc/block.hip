@@ -20,16 +20,15 @@
 //                   statistics of all rows to every slot and chooses the victim a following single-token step
 //                   would take.
 //
+// Steps of bf16 / 128 with up to 32 query rows mostly take one kernel instead (block_fused.hpp).
+//
 // The same three kernels serve grouped-query attention (section 5.3, "Extension to Grouped-Query Attention"):
 // g query heads share the unit's keys and values, the query rows are (token, head) pairs, and the statistics
 // receive, once per token, the mean of its g heads' probabilities (BlockArgs::heads).
 #include <cstdlib>
 
-#include "kernels.hpp"
-#include "mfma.hpp"
+#include "block_steps.hpp"
 #include "profile.hpp"
-#include "stream.hpp"
-#include "tile_ring.hpp"
 
 namespace roco {
 namespace {
@@ -46,8 +45,7 @@ constexpr int kQ = 32;            // query rows per matrix tile
 static_assert(kMaxBlock == 2 * kQ, "a step holds at most two tiles of query rows");
 
 // ------------------------------------------------------------------------------------------------
-// LDS: the ranking keys are in LDS (B <= kMaxDecodeBudgetLds), here and in block_finish.  The two selections share one copy
-// of the search: a launch starts with a cold instruction cache.
+// LDS: the ranking keys are in LDS (B <= kMaxDecodeBudgetLds), here and in block_finish.
 template <int NT, bool LDS>
 __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];  // [2][B] when B <= kMaxDecodeBudgetLds
@@ -57,97 +55,22 @@ __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
   const int u = blockIdx.x, tid = threadIdx.x;
   const int B = a.B, b = a.block;
   const int n = a.n_used[u];
-  const int E = max(0, n + b - B);
-  const int n_new = min(B, n + b);
   float* acc = a.stats + static_cast<size_t>(u) * 3 * B;
   float* acc2 = acc + B;
   float* cnt = acc2 + B;
-  int32_t* pos = a.pos + static_cast<size_t>(u) * B;
   int32_t* bidx = a.blk_idx + static_cast<size_t>(u) * B;
   uint32_t* const var_key = LDS ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
   uint32_t* const mas_key = var_key + B;
 
-  // The block's K / V rows (16 bytes per lane, a power of two of lanes per row) are requested now and stored at the end: the
-  // first NT / lanes rows are under way while the victims are chosen (16 tokens on 512 units: 23.4 -> 21.5 us).
-  const int lanes_log2 = __builtin_ctz(a.row_bytes) - 4;
-  const int my_row = tid >> lanes_log2, my_col = (tid & ((1 << lanes_log2) - 1)) * 16;
-  const size_t in_base = static_cast<size_t>(u) * b * a.row_bytes + my_col;
-  auto new_row = [&](const void* rows, int i) { return load16(static_cast<const char*>(rows) + in_base + static_cast<size_t>(i) * a.row_bytes); };
-  const int safe_row = min(my_row, b - 1);
-  uint4 k_row = new_row(a.k_new, safe_row), v_row = new_row(a.v_new, safe_row);
-
-  if (tid < kMaxBlock) slot_of[tid] = 0;
-  KSmallest scope = {0u, 0u}, out = {0u, 0u};
-  // one eviction from a full cache: the victim was already chosen when the statistics were last updated
-  const int hint = (E == 1 && n == B) ? a.next_slot[u] : -1;
-  if (E > 0 && hint < 0) {
-    // (B is a multiple of 4 on this path: four slots are inside the planes, and the keys behind the last slot are not read)
-#pragma unroll 1
-    for (int i = tid * 4; i < n; i += NT * 4) {
-      const float4 a1 = *reinterpret_cast<const float4*>(acc + i), a2 = *reinterpret_cast<const float4*>(acc2 + i);
-      const float4 cc = *reinterpret_cast<const float4*>(cnt + i);
-      const int4 pp = *reinterpret_cast<const int4*>(pos + i);
-      uint4 mk, vk;
-      ranking_keys<4>(&a1.x, &a2.x, &cc.x, &pp.x, a.pol, &mk.x, &vk.x);
-      *reinterpret_cast<uint4*>(mas_key + i) = mk;
-      *reinterpret_cast<uint4*>(var_key + i) = vk;
-    }
-    __syncthreads();
-    const uint32_t m = min(static_cast<uint32_t>(n), static_cast<uint32_t>(a.pol.scope_size(a.scope, n)) + static_cast<uint32_t>(E) - 1u);
-#pragma unroll 1
-    for (int phase = 0; phase < 2; ++phase) {
-      const KSmallest r = select_k_smallest<NT, 1, 1>(
-          [&](int i) -> uint32_t {
-            const uint32_t vk = var_key[i];
-            return phase == 0 ? vk : scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
-          },
-          n, phase == 0 ? m : static_cast<uint32_t>(E), phase == 0 && a.pol.scope_is_window(), sel_sh);
-      if (phase == 0) scope = r;
-      else out = r;
-    }
-  }
-  auto is_target = [&](int j) -> bool {
-    if (j >= n) return j < n_new;  // still-empty slot taken by the block
-    if (E == 0) return false;
-    if (hint >= 0) return j == hint;
-    const uint32_t k2 = scope.has(var_key[j], j) ? mas_key[j] : 0xffffffffu;
-    return out.has(k2, j);
-  };
-  // ordered assignment: thread t owns the contiguous slots [t*c, (t+1)*c); the i-th target gets block token i
-  const int c = (B + NT - 1) / NT;
-  const int lo = min(B, tid * c), hi = min(B, lo + c);
-  uint32_t mine = 0;
-#pragma unroll 1
-  for (int j = lo; j < hi; ++j) mine += (j < n_new && is_target(j)) ? 1u : 0u;
-  uint32_t total;
-  uint32_t rank = block_exclusive_scan<NT>(mine, scan_sh, total);
-  const int qp0 = a.qpos0[u];
-#pragma unroll 1
-  for (int j = lo; j < hi; ++j) {
-    int bi = -1;
-    if (j < n_new && is_target(j) && rank < static_cast<uint32_t>(b)) {
-      bi = static_cast<int>(rank++);
-      slot_of[bi] = j;
-      const bool held = j < n;  // the slot held a token that is now evicted
-      if (a.evicted_slot) a.evicted_slot[static_cast<size_t>(u) * b + bi] = held ? j : -1;
-      if (a.evicted_pos) a.evicted_pos[static_cast<size_t>(u) * b + bi] = held ? pos[j] : -1;
-      pos[j] = qp0 + bi;
+  take_slots<NT, 1>(a, u, n, var_key, mas_key, sel_sh, scan_sh, slot_of, [&](int j, int bi) {
+    if (bi >= 0) {
       acc[j] = 0.0f;
       acc2[j] = 0.0f;
       cnt[j] = 0.0f;
     }
     bidx[j] = bi;
-  }
-  __syncthreads();
-#pragma unroll 1
-  for (int i = my_row; i < b;) {
-    const size_t dst = (static_cast<size_t>(u) * B + slot_of[i]) * a.row_bytes + my_col;
-    *reinterpret_cast<uint4*>(static_cast<char*>(a.K) + dst) = k_row;
-    *reinterpret_cast<uint4*>(static_cast<char*>(a.V) + dst) = v_row;
-    i += NT >> lanes_log2;
-    if (i < b) { k_row = new_row(a.k_new, i); v_row = new_row(a.v_new, i); }
-  }
-  if (tid == 0) a.n_used[u] = n_new;
+  });
+  if (tid == 0) a.n_used[u] = min(B, n + b);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -165,17 +88,6 @@ struct WaveTiles {
   static constexpr int kBytes = 4 * kOperand;          // K, K, V, V of one wave
   static constexpr int kLoads = kOperand / 1024;       // wave-wide loads per operand tile
 };
-template <bool STREAMING>
-__device__ __forceinline__ void load16_to_lds_hint(v4i32 rsrc, uint32_t lds_addr, int voffset, int soffset) {
-  if (STREAMING)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                 :: "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory", "m0");
-  else
-    load16_to_lds(rsrc, lds_addr, voffset, soffset);
-}
-// The wave's LDS reads so far have returned: their tile may be overwritten.
-__device__ __forceinline__ void reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
 // NQT: tiles of 32 query rows (1 or 2).  The workspace planes are addressed with a.qrows = 32 NQT rows per unit.
 // WINDOW: a recency bias is in force (the slots' positions come along with the K tiles).
 template <int NQT, bool STREAMING, bool WINDOW>
@@ -1017,6 +929,8 @@ hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStrea
       !allow_key_lds(reinterpret_cast<const void*>(block_prepare<kPrepThreads, true>), key_lds))
     return hipErrorInvalidValue;
   const bool mfma_path = dtype == kBF16 && head_dim == 128;
+  hipError_t fused;
+  if (mfma_path && launch_block_fused(a, s, fused)) return fused != hipSuccess ? fused : hipGetLastError();
   if (!a.single) {
     ProfScope ps(kProfBlockPrepare, s);
     // Two 1024-thread workgroups do not run side by side on a compute unit here (measured: the second half of 512

@@ -1,0 +1,66 @@
+// When the one-kernel step of block_fused.hpp is taken, with its shapes of eight waves and 16 query rows.
+#include <cstdlib>
+
+#include "block_fused.hpp"
+
+namespace roco {
+namespace fused {
+
+template hipError_t launch<8, 1, 4>(const BlockArgs&, hipStream_t);
+template hipError_t launch<8, 1, 8>(const BlockArgs&, hipStream_t);
+template hipError_t launch<8, 1, 16>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<4, 1, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<4, 1, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<4, 1, 16>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<8, 2, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<8, 2, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<4, 2, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<4, 2, 8>(const BlockArgs&, hipStream_t);
+
+using Launch = hipError_t (*)(const BlockArgs&, hipStream_t);
+
+// The shape for W waves: the fewest tiles per wave that hold the unit's slots, null if none does.
+template <int W, int NQ, int ZT, int... MORE>
+Launch shape_for(const BlockArgs& a) {
+  if (Shape<W, NQ, ZT>::takes(a)) return launch<W, NQ, ZT>;
+  if constexpr (sizeof...(MORE) > 0) return shape_for<W, NQ, MORE...>(a);
+  return nullptr;
+}
+
+// One workgroup per unit needs units enough, or caches so small that the launches it saves count for more.  Against the three
+// kernels, us per step:
+//   up to 16 rows, B <= 1024: always (1 unit x 120 slots x 16 heads 13.7 / 9.2, 4 x 368 x 16 tokens 26.4 / 22.7, 20 x 944 x 2 heads
+//   17.6 / 16.7, 161 x 228 x 16 heads 25.1 / 13.8); B <= 2048 from 72 units on (48 x 1536 x 4 heads 25.0 / 28.1, 64 x 2048 x 4 heads
+//   32.6 / 34.6, 80 x 1536 x 4 heads 30.7 / 29.9, 128 x 2048 x 4 heads 45.9 / 38.4), B <= 4096 from 80 on (64 x 3072 x 4 heads
+//   41.3 / 48.2, 80 x 3072 55.6 / 50.1, 192 x 4096 117 / 76).
+//   17 to 32 rows, B <= 1024: always (1 x 892 x 21 tokens 32.1 / 32.0, 511 x 132 x 20 rows 45.9 / 27.8); B <= 2048 from 72 to 256
+//   units, where none waits for a second round (62 x 2044 x 28 rows 53.0 / 54.6, 96 x 2048 x 32 78.2 / 72.4, 256 x 2048 x 32 108 / 85,
+//   264 x 1664 x 29 121 / 128).
+// Four waves, two workgroups to a compute unit, where the units are more than the compute units (512 x 16 tokens x 2048 with eight
+// 119.7, with four 110.8; 356 x 2 heads x 132 23.0 / 14.1) and where a cache is a tile or two per wave (1 x 120 x 16 heads 10.1 / 9.2),
+// else eight (256 x 16 tokens x 2048 58.7 / 67.8, 128 x 4 heads x 2048 38.4 / 43.0).
+// ROCO_BLOCK_FUSED=8, 4, 0: eight waves, four, three kernels (tests run all); so does a number of splits that is asked for.
+Launch choose(const BlockArgs& a) {
+  const bool one = a.queries <= kQ16;
+  const Launch eight = one ? shape_for<8, 1, 4, 8, 16>(a) : shape_for<8, 2, 4, 8>(a);
+  const Launch four = one ? shape_for<4, 1, 4, 8, 16>(a) : shape_for<4, 2, 4, 8>(a);
+  const char* const asked = getenv("ROCO_BLOCK_FUSED");
+  if (asked != nullptr && *asked != 0) return asked[0] == '8' ? eight : asked[0] == '4' ? four : nullptr;
+  if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
+  const bool pairs = four != nullptr && (a.units > 256 || a.B <= 256);
+  const int least = a.B <= 1024 ? 0 : a.B <= 2048 ? 72 : 80;
+  if (a.units < least || (!one && !pairs && a.units > 256)) return nullptr;
+  return pairs ? four : eight;
+}
+
+}  // namespace fused
+
+bool launch_block_fused(const BlockArgs& a, hipStream_t s, hipError_t& e) {
+  const fused::Launch step = fused::choose(a);
+  if (step == nullptr) return false;
+  ProfScope ps(kProfBlockAttend, s);
+  e = step(a, s);
+  return true;
+}
+
+}  // namespace roco

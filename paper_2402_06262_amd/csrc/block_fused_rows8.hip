@@ -1,0 +1,9 @@
+// The shapes of block_fused.hpp for 17 to 32 query rows, eight waves.
+#include "block_fused.hpp"
+
+namespace roco {
+namespace fused {
+template hipError_t launch<8, 2, 4>(const BlockArgs&, hipStream_t);
+template hipError_t launch<8, 2, 8>(const BlockArgs&, hipStream_t);
+}  // namespace fused
+}  // namespace roco

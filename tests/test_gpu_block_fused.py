@@ -1,0 +1,86 @@
+"""Steps of bf16 / 128 in one kernel (up to 32 query rows) and in three: the same step, at the edges of the tiles, of the waves' shares
+and of the logits that registers and LDS hold."""
+import numpy as np
+import pytest
+import torch
+
+import test_gpu_gqa as TG
+from inputs import round_to_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(params=["8", "4", "0"], ids=["eight-waves", "four-waves", "three-kernels"])
+def kernels(request, monkeypatch):
+    monkeypatch.setenv("ROCO_BLOCK_FUSED", request.param)
+    return request.param
+
+
+@pytest.mark.parametrize("B", [4, 28, 32, 36, 124, 128, 132, 256, 260, 1028])
+def test_caches_that_end_at_the_edges_of_the_tiles(B, kernels):
+    """From the first token on, in lock-step with the oracle: 1, 7 and 16 rows; then 18 and 32."""
+    s = max(1, B // 8)
+    fill = [16] * (B // 16) + [7, 1, 16, 9, 1] if B >= 16 else [3, 4, 1, 2, 1]
+    TG.drive(2, B, s, 1, [min(b, B) for b in fill], seed=900 + B, recency=B % 128 == 4, tag=f"edge-{B}")
+    if B >= 16:
+        TG.drive(2, B, s, 4, [8] * min(B // 8, 20) + [8, 1, 4, 1], seed=950 + B, tag=f"edge-{B}-g4")
+
+
+POLICIES = [(0, 0, 0), (1, 2, 0), (0, 1, 0), (2, 2, 4), (3, 2, 0), (4, 1, 0)]  # importance, scope kind, sinks
+
+
+@pytest.mark.parametrize("B", [508, 512, 516, 1020, 1024, 1028, 2044, 2048, 2052, 4096])
+@pytest.mark.parametrize("block,group", [(1, 1), (1, 4), (1, 16), (16, 1), (3, 5), (2, 8), (1, 17), (32, 1), (5, 6)])
+def test_one_kernel_and_three_take_the_same_step(B, block, group, monkeypatch):
+    """Caches from full to nearly empty, with a recency bias and without, under every kind of policy: the same slots and positions bit
+    for bit.  Tolerances: bf16 outputs differ by a rounding or two (2^-7 of the row's largest); the statistics by fp32 sums in another
+    order (a logit of up to 2^7 in powers of two has an error of 2^-16, which is that of the probability)."""
+    import paper_2402_06262_amd as roco
+    units, d, seed = 5, 128, B + 64 * block + group
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    imp, kind, sinks = POLICIES[seed % len(POLICIES)]
+    window = 64 if (B // 4 + block + group) % 3 == 0 else 0
+    p = roco.RocoParams(units, d, B, max(1, B // 8), roco.ROCO_BF16, 0.0, window, 0.5 if window else 0.0, imp, kind, sinks)
+    fills = torch.tensor([B, B - 1, B // 2 + 1, max(0, B - block), 0], dtype=torch.int32, device="cuda")
+    live = torch.arange(B, device="cuda")[None] < fills[:, None]
+    K, V = rnd(units, B, d).bfloat16(), rnd(units, B, d).bfloat16()
+    count = (1.0 + torch.randint(0, 100, (units, B), generator=g, device="cuda")).float()
+    acc = torch.rand((units, B), generator=g, device="cuda") * count * 0.01
+    stats = torch.stack([acc, acc * acc / count * (1.0 + torch.rand((units, B), generator=g, device="cuda")), count], 1)
+    pos = torch.where(live, torch.arange(B, device="cuda", dtype=torch.int32)[None], -1).int()
+    q = rnd(units, block, group, d).bfloat16()
+    k_new, v_new = rnd(units, block, d).bfloat16(), rnd(units, block, d).bfloat16()
+    got = {}
+    for path in ("0", "8", "4"):
+        monkeypatch.setenv("ROCO_BLOCK_FUSED", path)
+        c = roco.alloc_cache(p)
+        c.K.copy_(K); c.V.copy_(V); c.stats.copy_(stats * live[:, None]); c.pos.copy_(pos); c.n_used.copy_(fills)
+        ws = torch.full((roco.block_workspace_bytes(p, block),), 0xFF, dtype=torch.uint8, device="cuda")
+        wd = torch.empty(roco.decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        roco.roco_select_victims(p, c.stats, c.pos, c.n_used, c.next_slot, wd)
+        out = torch.zeros((units, block, group, d), dtype=torch.bfloat16, device="cuda")
+        es, ep = (torch.full((units, block), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+        roco.roco_encode_block_gqa(p, block, group, q, k_new, v_new, fills.clone(), c.K, c.V, c.stats, c.pos, c.n_used, c.next_slot, out, es,
+                                   ep, ws)
+        torch.cuda.synchronize()
+        got[path] = dict(K=c.K, V=c.V, pos=c.pos, n_used=c.n_used, es=es, ep=ep, out=out.float(), stats=c.stats, next=c.next_slot)
+    for path in ("8", "4"):
+        a, b = got["0"], got[path]
+        for name in ("K", "V", "pos", "n_used", "es", "ep"):
+            same = torch.equal(a[name], b[name])
+            assert same, (path, name)
+        bad = ((a["out"] - b["out"]).abs().amax(-1) > 2.0 ** -7 * a["out"].abs().amax(-1)).any().item()
+        assert not bad, (path, "out")
+        held = torch.arange(B, device="cuda")[None] < b["n_used"][:, None]
+        for i in range(3):
+            x, y = a["stats"][:, i][held], b["stats"][:, i][held]
+            if i == 1 and imp == 4:  # counts of probabilities above average: one within 1e-4 of it may fall on either side
+                assert ((x - y).abs() > 0).float().mean().item() < 0.002 and ((x - y).abs().max().item() <= 1.0)
+            else:
+                rel = ((x - y).abs() / x.abs().clamp_min(1e-6)).max().item() if x.numel() else 0.0
+                assert rel <= (0.0 if i == 2 else 1e-4), (path, i, rel)
+        full = b["n_used"] == B
+        assert torch.equal(b["next"] >= 0, full), path
+        differ = (a["next"] != b["next"]).sum().item()
+        assert differ <= 1, (path, "next victim", a["next"], b["next"])
