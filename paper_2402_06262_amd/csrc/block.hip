@@ -20,7 +20,7 @@
 //                   statistics of all rows to every slot and chooses the victim a following single-token step
 //                   would take.
 //
-// Steps of bf16 / 128 with up to 32 query rows mostly take one kernel instead (block_fused.hpp).
+// Steps of bf16 / 128 mostly take one or two kernels that keep the logits on the compute unit instead (block_fused.hpp).
 //
 // The same three kernels serve grouped-query attention (section 5.3, "Extension to Grouped-Query Attention"):
 // g query heads share the unit's keys and values, the query rows are (token, head) pairs, and the statistics
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(NT, 8) void block_prepare(BlockArgs a) {
   uint32_t* const var_key = LDS ? lds_keys : a.keys + static_cast<size_t>(u) * 2 * B;
   uint32_t* const mas_key = var_key + B;
 
-  take_slots<NT, 1>(a, u, n, var_key, mas_key, sel_sh, scan_sh, slot_of, [&](int j, int bi) {
+  take_slots<NT, 1, true>(a, u, n, var_key, mas_key, sel_sh, scan_sh, slot_of, [&](int j, int bi) {
     if (bi >= 0) {
       acc[j] = 0.0f;
       acc2[j] = 0.0f;

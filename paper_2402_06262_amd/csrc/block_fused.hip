@@ -16,6 +16,8 @@ extern template hipError_t launch<8, 2, 4>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<8, 2, 8>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<4, 2, 4>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<4, 2, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<8>(const BlockArgs&, hipStream_t);
 
 using Launch = hipError_t (*)(const BlockArgs&, hipStream_t);
 
@@ -27,7 +29,21 @@ Launch shape_for(const BlockArgs& a) {
   return nullptr;
 }
 
-// One workgroup per unit needs units enough, or caches so small that the launches it saves count for more.  Against the three
+// 33 to 64 rows: each half of the tokens in a workgroup of its own, where the pairs take one round and the stream, which both read,
+// is long enough.  Against the three kernels, us per step: 128 units x 2048 slots x 16 tokens of 4 heads 95 / 66, 48 x 1024 x 16 of 4
+// 53 / 37, 4 x 476 x 48 39.9 / 34.1, 7 x 1804 x 19 of 2 48.0 / 46.6; two rounds: 160 x 1024 x 10 of 4 74 / 67, 256 x 1536 x 16 of 4
+// 115 / 101, but 176 x 584 x 41 66 / 68, 140 x 248 x 46 53 / 57; more: 512 x 1536 x 10 of 4 166 / 175, 423 x 244 x 61 77 / 125.
+Launch choose_halves(const BlockArgs& a) {
+  const BlockArgs half = half_step(a);
+  if (a.block < 2 || a.pol.keeps_last_score() || a.pol.counts_above_average()) return nullptr;
+  const Launch two = Shape<8, 2, 4>::takes(half) ? launch_halves<4> : Shape<8, 2, 8>::takes(half) ? launch_halves<8> : nullptr;
+  const char* const asked = getenv("ROCO_BLOCK_FUSED");
+  if (asked != nullptr && *asked != 0) return asked[0] == '0' ? nullptr : two;
+  if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
+  return a.units <= 128 || (a.units <= 256 && a.B > 768) ? two : nullptr;
+}
+
+// Up to 32 rows.  One workgroup per unit needs units enough, or caches so small that the launches it saves count for more.  Against the three
 // kernels, us per step:
 //   up to 16 rows, B <= 1024: always (1 unit x 120 slots x 16 heads 13.7 / 9.2, 4 x 368 x 16 tokens 26.4 / 22.7, 20 x 944 x 2 heads
 //   17.6 / 16.7, 161 x 228 x 16 heads 25.1 / 13.8); B <= 2048 from 72 units on (48 x 1536 x 4 heads 25.0 / 28.1, 64 x 2048 x 4 heads
@@ -41,6 +57,7 @@ Launch shape_for(const BlockArgs& a) {
 // else eight (256 x 16 tokens x 2048 58.7 / 67.8, 128 x 4 heads x 2048 38.4 / 43.0).
 // ROCO_BLOCK_FUSED=8, 4, 0: eight waves, four, three kernels (tests run all); so does a number of splits that is asked for.
 Launch choose(const BlockArgs& a) {
+  if (a.queries > 2 * kQ16) return choose_halves(a);
   const bool one = a.queries <= kQ16;
   const Launch eight = one ? shape_for<8, 1, 4, 8, 16>(a) : shape_for<8, 2, 4, 8>(a);
   const Launch four = one ? shape_for<4, 1, 4, 8, 16>(a) : shape_for<4, 2, 4, 8>(a);

@@ -11,6 +11,10 @@
 //   statistics  the probabilities go to LDS, where the tiles were; every thread adds the rows of its slots, and the next victim is chosen
 //   outputs     V streamed once against the registers.  Probabilities are taken as sums of two bf16 numbers, 16 bits of each: the matrix
 //               cores idle, and rounded to one they made half of the output's error (2.1e-3 against 64 bits, 1.7e-3 so)
+// 33 to 64 rows: two workgroups per unit, each with half of the tokens (HALVES).  Both stream K and V, which one of them finds in
+// their die's L2, and both evict, alike; they leave their sums of probabilities and squares to block_book, which adds them to the
+// statistics and does what depends on or changes the state that both have read (128 units x 2048 x 16 tokens of 4 heads 95 -> 66 us).
+//
 // V is only waited for by the outputs, and nothing waits for them: every other group of eight units streams K before it evicts and V
 // before its statistics, so that on the whole some workgroups use the memory while others rank (512 units x 2048 slots x 16 tokens:
 // 125 us with one order for all, 118 with turns at the eviction, 111 with both).
@@ -57,10 +61,13 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   return r;
 }
 
+// Where half `h` of a unit's tokens leaves its sums of probabilities and, behind them, of their squares.
+__device__ __forceinline__ float* part_sums(const BlockArgs& a, int u, int h) { return a.z + (static_cast<size_t>(u) * 2 + h) * 2 * a.B; }
+
 // W waves.  NQ tiles of 16 query rows.  ZT: tiles of a wave whose logits its registers hold (32 W ZT slots in all).
 // SINGLE: one token; its slot is known from the state.  lds_slots: slots whose probabilities the LDS takes at a time, a multiple of 32 W,
 // four to a thread.  v_room: there is room for the first tiles of V beside them.
-template <int W, int NQ, int ZT, bool SINGLE, bool STREAMING, bool WINDOW>
+template <int W, int NQ, int ZT, bool SINGLE, bool STREAMING, bool WINDOW, bool HALVES = false>
 __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds_slots, int v_room) {
   constexpr int NT = W * kWave;
   constexpr int QR = NQ * kQ16;
@@ -74,12 +81,17 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   __shared__ int slot_of[kMaxBlock];
   __shared__ __attribute__((aligned(256))) int32_t pos_s[WINDOW ? W : 1][2][kWave];
   __shared__ float m_s[W][QR], l_s[W][QR];
-  __shared__ float new_s[SINGLE ? 1 : QR][SINGLE ? 1 : QR];   // base-2 logits of the block's own tokens
+  __shared__ float new_s[SINGLE ? 1 : QR][SINGLE ? 1 : HALVES ? kMaxBlock : QR];  // base-2 logits of the block's own tokens
   __shared__ __attribute__((aligned(16))) signed char bidx_s[SINGLE ? 16 : 32 * W * ZT];  // block token that a slot holds, or -1
-  const int u = blockIdx.x;
+  const int u = !HALVES ? blockIdx.x : (blockIdx.x >> 4 << 3) + (blockIdx.x & 7);  // a unit's halves share a die's L2
+  if (HALVES && u >= a.units) return;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int qi = lane & 15, g = lane >> 4;
-  const int B = a.B, nq = a.queries, heads = a.heads;
+  const int B = a.B, heads = a.heads;
+  const int tok0 = HALVES && (blockIdx.x & 8) != 0 ? (a.block + 1) / 2 : 0;  // this workgroup's tokens
+  const int toks = !HALVES ? a.block : tok0 != 0 ? a.block - tok0 : (a.block + 1) / 2;
+  const int nq = HALVES ? toks * heads : a.queries;
+  const size_t first_row = static_cast<size_t>(u) * a.queries + tok0 * heads;
   const int n_old = a.n_used[u];
   const int n = min(B, n_old + a.block);
   const int qp0 = a.qpos0[u];
@@ -132,7 +144,7 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   uint4 own[NQ][4];
 #pragma unroll
   for (int t2 = 0; t2 < NQ; ++t2) {
-    const char* qrow = static_cast<const char*>(a.q) + (static_cast<size_t>(u) * nq + min(kQ16 * t2 + qi, nq - 1)) * kRowBytes;
+    const char* qrow = static_cast<const char*>(a.q) + (first_row + min(kQ16 * t2 + qi, nq - 1)) * kRowBytes;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) own[t2][kk] = load16(qrow + kk * 64 + g * 16);
   }
@@ -140,7 +152,7 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   const int w = a.recency_window;
   int qp[NQ];  // this lane's position per query tile; the heads of a group share it
 #pragma unroll
-  for (int t2 = 0; t2 < NQ; ++t2) qp[t2] = qp0 + (SINGLE ? 0 : (kQ16 * t2 + qi) / heads);
+  for (int t2 = 0; t2 < NQ; ++t2) qp[t2] = qp0 + (SINGLE ? 0 : tok0 + (kQ16 * t2 + qi) / heads);
   auto logit = [&](float score, int t2, int p) {
     float x = score * sc;
     if (WINDOW) {
@@ -173,7 +185,10 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   // ---- the eviction, before or behind the scores; its keys lie in the second stage
   auto evict = [&]() {
     uint32_t* const keys = reinterpret_cast<uint32_t*>(lds + W * kTileBytes);
-    take_slots<NT, PER_WORD>(a, u, n_old, keys, keys + B, sel_sh, scan_sh, slot_of, [&](int j, int bi) { bidx_s[j] = static_cast<signed char>(bi); });
+    take_slots<NT, PER_WORD, !HALVES>(a, u, n_old, keys, keys + B, sel_sh, scan_sh, slot_of, [&](int j, int bi) {
+      bidx_s[j] = static_cast<signed char>(bi);
+      if (HALVES && tok0 == 0) a.blk_idx[static_cast<size_t>(u) * B + j] = bi;
+    });
     __syncthreads();  // the keys have been used, the block's rows are in the cache
   };
   if (evict_first) evict();
@@ -262,7 +277,7 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
     a2 = *reinterpret_cast<const float4*>(acc2 + j);
     cc = *reinterpret_cast<const float4*>(cnt + j);
   };
-  load_stats(0);
+  if (!HALVES) load_stats(0);
   if (v_ahead && mine > 0) request_v(0);
 
   // ---- the block's own tokens take the place of what the slots held
@@ -369,9 +384,13 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
       __syncthreads();
       const int j = c0 + tid * 4;
       const float4 b1 = a1, b2 = a2, bc = cc;
-      load_stats(c0 + lds_slots);
+      if (!HALVES) load_stats(c0 + lds_slots);
       if (tid * 4 < lds_slots && j < n) {
         float s1[4] = {b1.x, b1.y, b1.z, b1.w}, s2[4] = {b2.x, b2.y, b2.z, b2.w}, sc4[4] = {bc.x, bc.y, bc.z, bc.w};
+        if (HALVES) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s1[e] = s2[e] = 0.0f;
+        }
         int bi[4] = {-1, -1, -1, -1};
         if (!SINGLE) {
           const int b4 = *reinterpret_cast<const int*>(bidx_s + j);
@@ -388,7 +407,7 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             s1[e] += p[e];
-            if (squares) s2[e] += p[e] * p[e];
+            if (HALVES || squares) s2[e] += p[e] * p[e];
             else if (bi[e] <= t) s2[e] = a.pol.second_statistic(s2[e], p[e], static_cast<float>(n - a.block + t + 1));
           }
         };
@@ -404,7 +423,7 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
           }
         } else {
 #pragma unroll 1
-          for (int t = 0; t < a.block; ++t) {
+          for (int t = 0; t < toks; ++t) {
             float4 mean = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll 4
             for (int h = 0; h < heads; ++h, prob += prow) {
@@ -413,6 +432,12 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
             }
             add(t, mean);
           }
+        }
+        if (HALVES) {  // block_book adds both halves' sums
+          float* const part = part_sums(a, u, tok0 != 0);
+          *reinterpret_cast<float4*>(part + j) = make_float4(s1[0], s1[1], s1[2], s1[3]);
+          *reinterpret_cast<float4*>(part + B + j) = make_float4(s2[0], s2[1], s2[2], s2[3]);
+          continue;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -441,11 +466,11 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
     }
     // the victim a following single-token step would take
     int victim = -1;
-    if (full) {
+    if (!HALVES && full) {
       __syncthreads();
       victim = select_victim_block<NT, PER_WORD>(var_key, mas_key, B, a.pol, a.scope, sel_sh, best_sh);
     }
-    if (tid == 0) {
+    if (!HALVES && tid == 0) {
       a.next_slot[u] = victim;
       a.n_used[u] = n;
       if (SINGLE) {
@@ -533,7 +558,7 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
       uint2 r;
       r.x = f32_to_bf16(sum.x) | static_cast<uint32_t>(f32_to_bf16(sum.y)) << 16;
       r.y = f32_to_bf16(sum.z) | static_cast<uint32_t>(f32_to_bf16(sum.w)) << 16;
-      *reinterpret_cast<uint2*>(static_cast<char*>(a.out) + (static_cast<size_t>(u) * nq * D + idx) * 2) = r;
+      *reinterpret_cast<uint2*>(static_cast<char*>(a.out) + (first_row * D + idx) * 2) = r;
     }
   };
 
@@ -553,6 +578,61 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   }
 }
 
+// Behind the two halves of a step: adds their sums to the statistics, books the tokens' slots and chooses the next victim.
+constexpr int kBookThreads = 512;
+template <int NT>
+__global__ __launch_bounds__(NT, 2) void block_book(BlockArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // [2][B] ranking keys
+  __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
+  __shared__ uint2 best_sh[NT / kWave];
+  const int u = blockIdx.x, tid = threadIdx.x, B = a.B;
+  const int n_old = a.n_used[u], n = min(B, n_old + a.block), qp0 = a.qpos0[u];
+  float* const acc = a.stats + static_cast<size_t>(u) * 3 * B;
+  const float *const p0 = part_sums(a, u, 0), *const p1 = part_sums(a, u, 1);
+  uint32_t* const var_key = reinterpret_cast<uint32_t*>(lds);
+  uint32_t* const mas_key = var_key + B;
+  const bool full = n >= B;
+#pragma unroll 1
+  for (int j = tid * 4; j < n; j += NT * 4) {
+    auto at = [&](const float* plane) { return *reinterpret_cast<const f32x4*>(plane + j); };
+    const f32x4 o1 = at(acc), o2 = at(acc + B), oc = at(acc + 2 * B);
+    float s1[4] = {o1.x, o1.y, o1.z, o1.w}, s2[4] = {o2.x, o2.y, o2.z, o2.w}, sc[4] = {oc.x, oc.y, oc.z, oc.w};
+    const f32x4 a1 = at(p0) + at(p1), a2 = at(p0 + B) + at(p1 + B);
+    const int4 b4 = *reinterpret_cast<const int4*>(a.blk_idx + static_cast<size_t>(u) * B + j);
+    const int4 p4 = *reinterpret_cast<const int4*>(a.pos + static_cast<size_t>(u) * B + j);
+    const int bi[4] = {b4.x, b4.y, b4.z, b4.w};
+    int pv[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (j + e >= n) continue;  // slots that do not exist keep what they hold
+      const bool fresh = bi[e] >= 0;
+      s1[e] = (fresh ? 0.0f : s1[e]) + a1[e];
+      s2[e] = (fresh ? 0.0f : s2[e]) + a2[e];
+      sc[e] = (fresh ? 0.0f : sc[e]) + static_cast<float>(a.block - max(bi[e], 0));  // older tokens were attended by all
+      if (fresh) {
+        book_slot(a, u, n_old, j + e, bi[e]);
+        pv[e] = qp0 + bi[e];
+      }
+    }
+    *reinterpret_cast<float4*>(acc + j) = make_float4(s1[0], s1[1], s1[2], s1[3]);
+    *reinterpret_cast<float4*>(acc + B + j) = make_float4(s2[0], s2[1], s2[2], s2[3]);
+    *reinterpret_cast<float4*>(acc + 2 * B + j) = make_float4(sc[0], sc[1], sc[2], sc[3]);
+    if (full) {  // then all four are slots of the unit
+      uint4 mk, vk;
+      ranking_keys<4>(s1, s2, sc, pv, a.pol, &mk.x, &vk.x);
+      *reinterpret_cast<uint4*>(mas_key + j) = mk;
+      *reinterpret_cast<uint4*>(var_key + j) = vk;
+    }
+  }
+  int victim = -1;
+  __syncthreads();  // every thread has read n_used
+  if (full) victim = select_victim_block<NT, 1>(var_key, mas_key, B, a.pol, a.scope, sel_sh, best_sh);
+  if (tid == 0) {
+    a.next_slot[u] = victim;
+    a.n_used[u] = n;
+  }
+}
+
 constexpr size_t kLdsOfUnit = 160 << 10;  // of a compute unit
 
 template <int W, int NQ, int ZT> struct Shape {
@@ -561,7 +641,7 @@ template <int W, int NQ, int ZT> struct Shape {
   // what block_fused declares statically, at most
   static size_t fixed(const BlockArgs& a) {
     const size_t qr = NQ * kQ16;
-    const size_t own = a.single ? qr * 4 + 16 : qr * qr * 4 + kStep * ZT;
+    const size_t own = a.single ? qr * 4 + 16 : qr * (a.block > static_cast<int>(qr) || a.queries < a.block * a.heads ? kMaxBlock : qr) * 4 + kStep * ZT;
     return SelectLds<W == 4 ? 2 : 1>::kWords * 4 + (a.recency_window > 0 ? W * 512 : 512) + 2 * W * qr * 4 + qr * 4 + own + 1024;
   }
   // slots whose probabilities the LDS takes at a time beside the unit's ranking keys, and `ahead` bytes of V; 0: none
@@ -580,6 +660,12 @@ template <int W, int NQ, int ZT> struct Shape {
   }
   static bool takes(const BlockArgs& a) { return a.B <= kStep * ZT && a.queries <= kQ16 * NQ && slots(a, 0) > 0; }
 };
+
+// The larger half of a step's tokens, as a step of its own.
+inline BlockArgs half_step(BlockArgs a) {
+  a.queries = (a.block + 1) / 2 * a.heads;
+  return a;
+}
 
 template <int W, int NQ, int ZT, bool SINGLE, bool STREAMING, bool WINDOW>
 hipError_t launch_t(const BlockArgs& a, hipStream_t s) {
@@ -601,6 +687,26 @@ hipError_t launch(const BlockArgs& a, hipStream_t s) {
   }
   if (a.streaming) return window ? launch_t<W, NQ, ZT, false, true, true>(a, s) : launch_t<W, NQ, ZT, false, true, false>(a, s);
   return window ? launch_t<W, NQ, ZT, false, false, true>(a, s) : launch_t<W, NQ, ZT, false, false, false>(a, s);
+}
+
+template <int ZT, bool STREAMING, bool WINDOW>
+hipError_t launch_halves_t(const BlockArgs& a, const BlockArgs& half, hipStream_t s) {
+  using S = Shape<8, 2, ZT>;
+  const size_t lds = S::lds(half);
+  const void* fn = reinterpret_cast<const void*>(block_fused<8, 2, ZT, false, STREAMING, WINDOW, true>);
+  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL((block_fused<8, 2, ZT, false, STREAMING, WINDOW, true>), dim3((a.units + 7) / 8 * 16), dim3(8 * kWave), lds, s, a,
+                     S::slots(half, S::v_ahead(half) ? S::kStage : 0), S::v_ahead(half) ? 1 : 0);
+  hipLaunchKernelGGL((block_book<kBookThreads>), dim3(a.units), dim3(kBookThreads), key_lds_bytes(a.B), s, a);
+  return hipSuccess;
+}
+template <int ZT>
+hipError_t launch_halves(const BlockArgs& a, hipStream_t s) {
+  const BlockArgs half = half_step(a);
+  const bool window = a.recency_window > 0;
+  if (a.streaming) return window ? launch_halves_t<ZT, true, true>(a, half, s) : launch_halves_t<ZT, true, false>(a, half, s);
+  return window ? launch_halves_t<ZT, false, true>(a, half, s) : launch_halves_t<ZT, false, false>(a, half, s);
 }
 
 }  // namespace fused

@@ -8,11 +8,20 @@
 
 namespace roco {
 
-// The step's E = max(0, n + b - B) victims (two exact searches), the slots its tokens take, their K / V rows in the cache, pos, and
-// the record of what was evicted.  place(j, bi) says of every slot which block token it now holds (-1: an older one, or none).
+// Slot j of a unit that held n tokens takes block token bi: pos, and the record of what was evicted.
+__device__ __forceinline__ void book_slot(const BlockArgs& a, int u, int n, int j, int bi) {
+  int32_t* const pos = a.pos + static_cast<size_t>(u) * a.B;
+  const bool held = j < n;  // the slot held a token that is now evicted
+  if (a.evicted_slot) a.evicted_slot[static_cast<size_t>(u) * a.block + bi] = held ? j : -1;
+  if (a.evicted_pos) a.evicted_pos[static_cast<size_t>(u) * a.block + bi] = held ? pos[j] : -1;
+  pos[j] = a.qpos0[u] + bi;
+}
+
+// The step's E = max(0, n + b - B) victims (two exact searches), the slots its tokens take, their K / V rows in the cache and, with
+// BOOK, book_slot.  place(j, bi) says of every slot which block token it now holds (-1: an older one, or none).
 // The ranking keys lie in var_key[B] and mas_key[B].  The two selections share one copy of the search: a launch starts with a cold
 // instruction cache.  Ends with a barrier behind the last write of slot_of, not behind the rows.
-template <int NT, int PER_WORD, class Place>
+template <int NT, int PER_WORD, bool BOOK, class Place>
 __device__ __forceinline__ void take_slots(const BlockArgs& a, int u, int n, uint32_t* var_key, uint32_t* mas_key, uint32_t* sel_sh,
                                            uint32_t* scan_sh, int* slot_of, Place place) {
   const int tid = threadIdx.x;
@@ -22,7 +31,7 @@ __device__ __forceinline__ void take_slots(const BlockArgs& a, int u, int n, uin
   const float* acc = a.stats + static_cast<size_t>(u) * 3 * B;
   const float* acc2 = acc + B;
   const float* cnt = acc2 + B;
-  int32_t* pos = a.pos + static_cast<size_t>(u) * B;
+  const int32_t* pos = a.pos + static_cast<size_t>(u) * B;
 
   // The block's K / V rows (16 bytes per lane, a power of two of lanes per row) are requested now and stored at the end: the
   // first NT / lanes rows are under way while the victims are chosen (16 tokens on 512 units: 23.4 -> 21.5 us).
@@ -78,17 +87,13 @@ __device__ __forceinline__ void take_slots(const BlockArgs& a, int u, int n, uin
   for (int j = lo; j < hi; ++j) mine += (j < n_new && is_target(j)) ? 1u : 0u;
   uint32_t total;
   uint32_t rank = block_exclusive_scan<NT>(mine, scan_sh, total);
-  const int qp0 = a.qpos0[u];
 #pragma unroll 1
   for (int j = lo; j < hi; ++j) {
     int bi = -1;
     if (j < n_new && is_target(j) && rank < static_cast<uint32_t>(b)) {
       bi = static_cast<int>(rank++);
       slot_of[bi] = j;
-      const bool held = j < n;  // the slot held a token that is now evicted
-      if (a.evicted_slot) a.evicted_slot[static_cast<size_t>(u) * b + bi] = held ? j : -1;
-      if (a.evicted_pos) a.evicted_pos[static_cast<size_t>(u) * b + bi] = held ? pos[j] : -1;
-      pos[j] = qp0 + bi;
+      if (BOOK) book_slot(a, u, n, j, bi);
     }
     place(j, bi);
   }
