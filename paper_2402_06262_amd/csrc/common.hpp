@@ -207,9 +207,10 @@ constexpr int kSelectBins = 2048;
 constexpr int kSelectRanked = 128;
 template <int PER_WORD> struct SelectLds {
   static constexpr int kBinWords = kSelectBins / PER_WORD;
-  static constexpr int kWords = kBinWords + 16 + 8;
+  static constexpr int kWords = kBinWords + (PER_WORD == 2 ? kSelectRanked : 16) + 8;  // (what fine_select needs is in both)
 };
 static_assert(kSelectRanked == 2 * kWave, "two candidates per lane");
+
 
 // f(key) for every key of this thread, in no particular order.
 template <int NT, int AHEAD, class KeyFn, class F>
@@ -411,6 +412,89 @@ __device__ __forceinline__ bool count_k_smallest(KeyFn key_of, int n, uint32_t k
   return true;
 }
 
+// Where the ranking keys usually lie, between 2^-52 and 2^12, one digit of 1/32 of an octave leaves so few candidates that no second one
+// has to be counted (1/16, with half of the bins, does not: such searches end here in vain), and its 2048 bins, two to a word, are few
+// enough for up to eight waves to scan them each by itself: four barriers instead of eight.  Cycles for the 65th / 1024th of 2048 keys:
+// 256 threads 7670 / 7220 -> 6390 / 5840, 512 threads 6900 / 6400 -> 6160 / 5200; 1024 threads 6430 / 5480 -> 5960 / 5150, which the
+// sixteen waves' scans make up for with fewer keys, and decode_finish lost half a microsecond by the longer code.  What is left are
+// the additions to the bins, served a few at a time.  Steps: 128 units x 4 heads x 2048 slots 38.4 -> 37.7 us, 512 x 16 tokens x
+// 2048 110.6 -> 109.1.
+// False if the k-th smallest key lies outside or among more than kSelectRanked candidates: then the search above has to find it.
+constexpr int kFineBins = 2048, kFineShift = 18;
+constexpr uint32_t kFineFrom = (127u - 52u) << 23;
+static_assert(kFineBins / 2 + kSelectRanked + 4 <= SelectLds<2>::kWords, "the bins, the candidates and four words");
+template <int NT, int AHEAD, class KeyFn>
+__device__ __forceinline__ bool fine_select(KeyFn key_of, int n, uint32_t k, uint32_t* sh, uint32_t& kth, uint32_t& n_less, uint32_t& n_equal) {
+  uint32_t* const list = sh + kFineBins / 2;
+  uint32_t* const res = list + kSelectRanked;  // candidates gathered; the key, keys below it, keys equal to it
+  const int tid = late_thread_id(), lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  auto bin_of = [](uint32_t key) { return min((max(key, kFineFrom) - kFineFrom) >> kFineShift, static_cast<uint32_t>(kFineBins - 1)); };
+  __syncthreads();  // `sh` may still be in use by a previous call
+  if (tid < kFineBins / 8) *reinterpret_cast<uint4*>(sh + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) res[0] = 0;
+  __syncthreads();
+  for_each_key<NT, AHEAD>(key_of, n, tid, [&](uint32_t key) {
+    const uint32_t bin = bin_of(key);
+    if (key != 0xffffffffu) atomicAdd(&sh[bin >> 1], 1u << (16 * (bin & 1)));
+  });
+  __syncthreads();
+  // 32 bins per lane
+  uint32_t pairs = 0;  // (at most 65535 keys)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint4 w = *reinterpret_cast<const uint4*>(sh + 16 * lane + 4 * i);
+    pairs += w.x + w.y + w.z + w.w;
+  }
+  const uint32_t mine = (pairs & 0xffffu) + (pairs >> 16);
+  const uint32_t upto = wave_inclusive_scan(mine);
+  const uint64_t reach = __builtin_amdgcn_ballot_w64(upto >= k);
+  if (reach == 0) return false;  // among the keys that are not counted
+  const int owner = __builtin_ctzll(reach);
+  uint32_t less = __builtin_amdgcn_readlane(upto - mine, owner);
+  const uint32_t word = sh[16 * owner + ((lane & 31) >> 1)];
+  const uint32_t count = lane < 32 ? ((lane & 1) ? word >> 16 : word & 0xffffu) : 0u;
+  const uint32_t inside = wave_inclusive_scan(count);
+  const int off = __builtin_ctzll(__builtin_amdgcn_ballot_w64(less + inside >= k));
+  const uint32_t cand = __builtin_amdgcn_readlane(count, off);
+  less += __builtin_amdgcn_readlane(inside, off) - cand;
+  const uint32_t bin = static_cast<uint32_t>(32 * owner + off);
+  if (bin == 0 || bin == kFineBins - 1 || cand > kSelectRanked) return false;
+  for_each_key<NT, AHEAD>(key_of, n, tid, [&](uint32_t key) {
+    if (bin_of(key) == bin && key != 0xffffffffu) list[atomicAdd(&res[0], 1u)] = key;
+  });
+  __syncthreads();
+  constexpr bool kOneWave = NT > 4 * kWave;  // (as above)
+  uint32_t kk = k - less, left = cand;
+  if (!kOneWave || wave == 0) {
+    const uint32_t c0 = list[lane], c1 = list[lane + kWave];
+    uint64_t in0 = cand >= 64 ? ~0ull : (1ull << cand) - 1ull;
+    uint64_t in1 = cand > 64 ? (cand == 128 ? ~0ull : (1ull << (cand - 64)) - 1ull) : 0ull;
+#pragma unroll 1
+    for (int bit = kFineShift - 1; bit >= 0 && left > 1; --bit) {
+      const uint64_t z0 = in0 & ~__builtin_amdgcn_ballot_w64((c0 >> bit) & 1u);
+      const uint64_t z1 = in1 & ~__builtin_amdgcn_ballot_w64((c1 >> bit) & 1u);
+      const uint32_t zeros = __builtin_popcountll(z0) + __builtin_popcountll(z1);
+      if (kk <= zeros) {
+        in0 = z0; in1 = z1; left = zeros;
+      } else {
+        in0 &= ~z0; in1 &= ~z1; left -= zeros;
+        kk -= zeros; less += zeros;
+      }
+    }
+    kth = in0 != 0 ? __builtin_amdgcn_readlane(c0, __builtin_ctzll(in0)) : __builtin_amdgcn_readlane(c1, __builtin_ctzll(in1));
+    if (kOneWave && lane == 0) { res[1] = kth; res[2] = less; res[3] = left; }
+  }
+  if (kOneWave) {
+    __syncthreads();
+    kth = res[1];
+    less = res[2];
+    left = res[3];
+  }
+  n_less = less;
+  n_equal = left;
+  return true;
+}
+
 template <int NT, int PER_WORD, int AHEAD, class KeyFn>
 __device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, bool small, uint32_t* sh) {
   // everything is wanted (the policies whose scope is the whole cache, say): nothing to select
@@ -424,12 +508,15 @@ __device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint
   for (int round = 0; round < 2; ++round) {
     const uint32_t kth = r.kth;
     uint32_t found, n_less, n_equal;
-    radix_select<NT, PER_WORD, AHEAD>(
-        [&](int i) {
-          const uint32_t key = key_of(i);
-          return round == 0 ? key : key == kth ? static_cast<uint32_t>(i) : 0xffffffffu;
-        },
-        n, take, round == 1 || small, sh, found, n_less, n_equal);
+    bool done = false;
+    if constexpr (NT <= 512) done = round == 0 && !small && n <= 65535 && fine_select<NT, AHEAD>(key_of, n, take, sh, found, n_less, n_equal);
+    if (!done)
+      radix_select<NT, PER_WORD, AHEAD>(
+          [&](int i) {
+            const uint32_t key = key_of(i);
+            return round == 0 ? key : key == kth ? static_cast<uint32_t>(i) : 0xffffffffu;
+          },
+          n, take, round == 1 || small, sh, found, n_less, n_equal);
     if (round == 1) {
       r.index_limit = found;
     } else {

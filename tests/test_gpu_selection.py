@@ -279,3 +279,38 @@ def test_few_keys_are_counted(kind, n):
     rank = np.argsort(np.argsort(acc, axis=1, kind="stable"), axis=1)
     want = (rank[None] >= n - np.arange(n)[:, None, None]).astype(np.int32)
     assert np.array_equal(masks.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("kind", ["equal", "low_bits", "middle_bits", "two_values", "wide", "bin_of_128", "bin_of_129", "ends"])
+@pytest.mark.parametrize("n", [129, 257, 1000, 2048, 5000])
+def test_last_of_the_scope(kind, n):
+    """The victim is the last token of the scope: importance falls as the scope's key grows.  Keys that share one bin of the search of
+    up to eight waves or fill it to the last candidate, and keys at and beyond the ends of its bins (2^-52 and 2^12)."""
+    import paper_2402_06262_amd as roco
+    rng = np.random.default_rng([n, len(kind), 9])
+    units = 3
+    var = np.stack([_keys(kind, n, rng) if kind in ("equal", "low_bits", "middle_bits", "two_values", "wide") else
+                    rng.uniform(2.0, 4.0, n).astype(np.float32) for _ in range(units)])
+    if kind.startswith("bin_of"):
+        m = int(kind[-3:])
+        for u in range(units):  # m keys inside one bin of 2^18 bit patterns, the others above and below
+            at = rng.choice(n, min(m, n), replace=False)
+            var[u] = np.where(rng.random(n) < 0.5, var[u], var[u] / 64)
+            var[u, at] = (np.float32(0.5).view(np.uint32) + rng.choice(1 << 18, at.size, replace=False).astype(np.uint32)).view(np.float32)
+    if kind == "ends":
+        e = rng.choice(np.array([0.0, 2.0 ** -60, 2.0 ** -52, 1.01 * 2.0 ** -52, 2.0 ** -51, 4000.0, 4095.9, 4096.0, 5000.0]), (units, n))
+        var = (e * rng.choice([1.0, 1.0 + 2.0 ** -20], (units, n))).astype(np.float32)
+    order = np.argsort(var, axis=1, kind="stable")
+    rank = np.argsort(order, axis=1)
+    # acc / count is far below the resolution of acc2 / count; the importance is the oldest position
+    pos = (n - 1 - rank).astype(np.int32)
+    stats = np.zeros((units, 3, n), np.float32)
+    stats[:, 1], stats[:, 2] = var, 1.0
+    dpos, dstats = torch.from_numpy(pos).cuda(), torch.from_numpy(stats).cuda()
+    n_used = torch.full((units,), n, dtype=torch.int32, device="cuda")
+    for scope in sorted({1, 2, n // 32 + 1, n // 3, n // 2, n - 1, 64, 65, 128, 129} & set(range(1, n + 1))):
+        p = roco.RocoParams(units, 64, n, scope, roco.ROCO_F32, importance=roco.ROCO_IMPORTANCE_OLDEST)
+        victim = torch.empty((units,), dtype=torch.int32, device="cuda")
+        ws = torch.empty(roco.decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        roco.roco_select_victims(p, dstats, dpos, n_used, victim, ws)
+        assert np.array_equal(victim.cpu().numpy(), order[:, scope - 1]), (kind, n, scope)
