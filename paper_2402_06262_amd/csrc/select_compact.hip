@@ -22,7 +22,7 @@ constexpr int kGatherThreads = 256;
 constexpr int kGatherRows = 64;  // cache rows per gather workgroup
 
 // A launch of this kernel starts with a cold instruction cache and walks through its code once, so the code is kept short:
-// the three selections (scope, victims, first decode victim) share one copy of the search, loops over keys in LDS are not
+// the two selections (scope, victims) share one copy of the search, loops over keys in LDS are not
 // unrolled, and where the keys are is a template parameter so that they are read with LDS instructions.
 // LDS: both keys of a token in LDS (2; up to 16384 tokens), the one of the scope (1; up to 32768), none (0).
 // MANY: the column sums lie in more than two shares (LDS = 2).  They are added once, by the thread that will need the sums again
@@ -102,38 +102,32 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
     }
     __syncthreads();
   }
-  // Phase 0: the scope of the eviction; 1: the victims; 2: the scope of the first decode step, among the retained tokens
-  // (whose keys do not change and whose order is that of their slots, so the compacted statistics need not be read back).
-  KSmallest scope = {0u, 0u}, out = {0u, 0u}, next = {0u, 0u};
+  // Phase 0: the scope of the eviction; 1: the victims.  The scope of the first decode step needs no search of its own: the s + E - 1
+  // tokens of lowest scope key less the E victims, all of them among these, and the next one, the lowest outside (prompts of 256 /
+  // 1000 / 2048 / 4096 tokens: 2.2 / 2.5 / 3.1 / 4.6 us).  Without an eviction phase 0 finds that scope.
+  KSmallest scope = {0u, 0u}, out = {0u, 0u};
   if (n >= B) {
 #pragma unroll 1
-    for (int phase = E > 0 ? 0 : 2; phase < 3; ++phase) {
+    for (int phase = 0; phase < (E > 0 ? 2 : 1); ++phase) {
       const uint32_t k = phase == 1 ? E
-                         : phase == 0 ? min(static_cast<uint32_t>(n), static_cast<uint32_t>(a.pol.scope_size(a.scope, n)) + E - 1u)
-                                      : static_cast<uint32_t>(a.pol.scope_size(a.scope, B));
-      if (phase == 2 && k >= static_cast<uint32_t>(kept)) {  // every retained token is in the scope
-        next = KSmallest{0xffffffffu, 0xffffffffu};
-        break;
-      }
+                         : E > 0    ? min(static_cast<uint32_t>(n), static_cast<uint32_t>(a.pol.scope_size(a.scope, n)) + E - 1u)
+                                    : static_cast<uint32_t>(a.pol.scope_size(a.scope, B));
       const KSmallest r = select_k_smallest<NT, 1, LDS == 2 ? 1 : 4>(
           [&](int i) -> uint32_t {
             const uint32_t vk = var_key[i];
             if (phase == 0) return vk;
-            const uint32_t in_scope = E > 0 && scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
-            if (phase == 1) return in_scope;
-            return E > 0 && out.has(in_scope, i) ? 0xffffffffu : vk;
+            return scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
           },
-          n, k, phase != 1 && a.pol.scope_is_window(), sel_sh);
+          n, k, phase == 0 && a.pol.scope_is_window(), sel_sh);
       if (phase == 0) scope = r;
-      else if (phase == 1) out = r;
-      else next = r;
+      else out = r;
     }
   }
   // ordered compaction, NT positions at a time: a token's slot is the number of retained tokens before it, counted by ballots
   // inside a wave and by the waves' totals in LDS before it
-  uint32_t best_key = 0xffffffffu, best = 0xffffffffu;  // importance and position of the first decode victim
+  uint32_t best_key = 0xffffffffu, best = 0xffffffffu, best_slot = 0;  // the least important retained token of the scope
+  uint32_t next_key = 0xffffffffu, next = 0xffffffffu, next_slot = 0, next_mas = 0;  // the token of lowest scope key outside
   uint32_t before = 0;  // retained tokens of earlier rounds
-  uint32_t best_slot = 0;
   float2 ahead = sums(min(tid, max(n - 1, 0)));  // of the next round: a trip to memory that its barriers hide
 #pragma unroll 1
   for (int base = 0; base < n; base += NT) {
@@ -143,7 +137,8 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
     if (base + NT < n) ahead = sums(min(i + NT, n - 1));
     // (the list of positions grows over keys that have been read: a token's own are read before the barrier)
     const uint32_t vk = in && n >= B ? var_key[i] : 0u, mk = in && n >= B ? mas_key[i] : 0u;
-    const bool keep = in && !(E > 0 && out.has(scope.has(vk, i) ? mk : 0xffffffffu, i));
+    const bool inside = scope.has(vk, i);
+    const bool keep = in && !(E > 0 && out.has(inside ? mk : 0xffffffffu, i));
     const uint64_t votes = __builtin_amdgcn_ballot_w64(keep);
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     __syncthreads();  // the previous round's totals have been read
@@ -159,10 +154,16 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
       oacc2[dst] = s.y;
       ocnt[dst] = static_cast<float>(n - i);
       if (GATHER) var_key[dst] = static_cast<uint32_t>(i);
-      if (n >= B && next.has(vk, i) && (mk < best_key || best == 0xffffffffu)) {
+      if (inside && (mk < best_key || best == 0xffffffffu)) {
         best_key = mk;
         best = static_cast<uint32_t>(i);
         best_slot = dst;
+      }
+      if (!inside && (vk < next_key || next == 0xffffffffu)) {
+        next_key = vk;
+        next = static_cast<uint32_t>(i);
+        next_slot = dst;
+        next_mas = mk;
       }
     }
   }
@@ -172,6 +173,24 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
     oacc[i] = 0.0f;
     oacc2[i] = 0.0f;
     ocnt[i] = 0.0f;
+  }
+  if (tid == 0) a.n_used[u] = kept;
+  // The first decode step on a full cache needs its victim.  (Before the rows are copied: a barrier waits for every store before it,
+  // 3 to 4 us where the copies are long.)
+  if (kept == B) {
+    if (E > 0) {
+      const uint32_t last = block_argmin<NT>(next_key, next, best_sh);  // 0xffffffff: nobody is outside
+      if (last == next && next != 0xffffffffu && (next_mas < best_key || best == 0xffffffffu || (next_mas == best_key && next < best))) {
+        best_key = next_mas;
+        best = next;
+        best_slot = next_slot;
+      }
+      __syncthreads();  // (best_sh is used again)
+    }
+    const uint32_t victim = block_argmin<NT>(best_key, best, best_sh);
+    if (victim == best) a.next_slot[u] = static_cast<int>(best_slot);  // its owner knows which slot it went to
+  } else if (tid == 0) {
+    a.next_slot[u] = -1;
   }
   if constexpr (GATHER) {
     __syncthreads();  // the list is whole
@@ -192,14 +211,6 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
       *reinterpret_cast<uint4*>(Vout + static_cast<size_t>(other) * a.row_bytes) = v1;
     }
   }
-  if (tid == 0) a.n_used[u] = kept;
-  if (kept < B) {
-    if (tid == 0) a.next_slot[u] = -1;
-    return;
-  }
-  // the first decode step on a full cache needs its victim
-  const uint32_t victim = block_argmin<NT>(best_key, best, best_sh);
-  if (victim == best) a.next_slot[u] = static_cast<int>(best_slot);  // its owner knows which slot it went to
 }
 
 template <int ROW_BYTES>
