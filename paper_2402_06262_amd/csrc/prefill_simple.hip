@@ -8,6 +8,8 @@
 //   pass 2: one wave per key column j streams queries j..len-1, recomputes the logit and accumulates
 //           Acc[j] = sum_i P[i,j] and Acc2[j] = sum_i P[i,j]^2 in fp32            (section 4.3)
 // Count[j] = len - j has a closed form and is not accumulated.  The L x L matrix is never stored.
+#include <cstdlib>
+
 #include "kernels.hpp"
 #include "profile.hpp"
 #include "stream.hpp"
@@ -19,14 +21,19 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kUnroll = 4;
 
-template <int DT, int D>
+// WPR waves share a query row, each with every WPR-th block of keys: one, or all four of a workgroup.  What bounds a prompt of few rows
+// is the chain of a wave's trips to the L2, a block of 16 (bf16 / 64: 32) keys each; with more rows than the chip holds waves of, the
+// merge costs more than the shorter chain gains (see launch_rows_t).
+template <int DT, int D, int WPR>
 __global__ __launch_bounds__(kThreads) void prefill_rows_simple(PrefillArgs a) {
   using G = RowGeom<DT, D>;
+  static_assert(WPR == 1 || WPR == kWaves, "a row is one wave's or the workgroup's");
   const int uq = blockIdx.y;       // (unit, query head)
   const int uk = uq / a.group;     // the unit: its keys, values and length
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int c = lane % G::LPR;
-  const int i = blockIdx.x * kWaves + wave;
+  const int part = WPR == 1 ? 0 : wave;
+  const int i = WPR == 1 ? blockIdx.x * kWaves + wave : blockIdx.x;
   const int len = a.len[uk];
   if (i >= len) return;
   const size_t ubase = static_cast<size_t>(uq) * a.L_max;
@@ -44,11 +51,34 @@ __global__ __launch_bounds__(kThreads) void prefill_rows_simple(PrefillArgs a) {
   auto bias = [&](int row, int) -> float { return (i - row < w) ? rb : 0.0f; };  // row <= i here
   auto fix = [](int, uint4&, int) {};
   constexpr int PASS = kUnroll * G::R;
+  const int passes = (i + WPR * PASS - part * PASS) / (WPR * PASS);  // blocks of this wave, of keys up to i
   if (w > 0)
-    stream_attend<DT, D, kUnroll, true, false>(qf, Kb, Vb, 0, i + 1, i + 1, (i + PASS) / PASS, 0, PASS, 0, bias, nullptr, nullptr, -1, fix, fix, [] {}, st);
+    stream_attend<DT, D, kUnroll, true, false>(qf, Kb, Vb, 0, i + 1, i + 1, passes, 0, WPR * PASS, part * PASS, bias, nullptr, nullptr, -1, fix, fix, [] {}, st);
   else
-    stream_attend<DT, D, kUnroll, false, false>(qf, Kb, Vb, 0, i + 1, i + 1, (i + PASS) / PASS, 0, PASS, 0, bias, nullptr, nullptr, -1, fix, fix, [] {}, st);
+    stream_attend<DT, D, kUnroll, false, false>(qf, Kb, Vb, 0, i + 1, i + 1, passes, 0, WPR * PASS, part * PASS, bias, nullptr, nullptr, -1, fix, fix, [] {}, st);
   merge_groups_in_wave<DT, D>(st);
+  if constexpr (WPR > 1) {  // the first wave merges the others, in their order
+    __shared__ float part_s[WPR][G::LPR][G::EPL + 2];
+    if (wave > 0 && lane < G::LPR) {
+      float* const p = part_s[wave][lane];
+      p[G::EPL] = st.m;
+      p[G::EPL + 1] = st.l;
+#pragma unroll
+      for (int e = 0; e < G::EPL; ++e) p[e] = st.acc[e];
+    }
+    __syncthreads();
+    if (wave > 0 || lane >= G::LPR) return;
+#pragma unroll
+    for (int k = 1; k < WPR; ++k) {
+      const float* const p = part_s[k][lane];
+      const float m_o = p[G::EPL], m_new = fmaxf(st.m, m_o);
+      const float f0 = (st.m > -INFINITY) ? fast_exp2(st.m - m_new) : 0.0f, f1 = (m_o > -INFINITY) ? fast_exp2(m_o - m_new) : 0.0f;
+      st.l = st.l * f0 + p[G::EPL + 1] * f1;
+#pragma unroll
+      for (int e = 0; e < G::EPL; ++e) st.acc[e] = st.acc[e] * f0 + p[e] * f1;
+      st.m = m_new;
+    }
+  }
   if (lane == 0) a.lse[ubase + i] = st.m + log2f(st.l);
   if (a.O != nullptr && lane < G::LPR) {
     const float inv = 1.0f / st.l;
@@ -131,8 +161,15 @@ __global__ __launch_bounds__(kThreads) void prefill_columns_simple(PrefillArgs a
 template <int DT, int D>
 void launch_rows_t(const PrefillArgs& a, hipStream_t s) {
   ProfScope ps(kProfPrefillRows, s);
-  const dim3 grid((a.L_max + kWaves - 1) / kWaves, static_cast<unsigned>(a.units) * a.group);
-  hipLaunchKernelGGL((prefill_rows_simple<DT, D>), grid, dim3(kThreads), 0, s, a);
+  // Whole calls with output, us, one wave / four waves per row: fp32 / 64 4 units x 256 tokens 26.7 / 24.6, 2 x 512 35.0 / 29.0, 1 x 700
+  // 43.1 / 31.8, 8 x 256 28.3 / 27.4, but 16 x 128 21.6 / 22.0, 30 x 128 25.3 / 27.5; fp32 / 128 8 x 256 44.1 / 37.7, 16 x 128 30.6 / 28.8;
+  // bf16 / 64 4 x 256 21.4 / 20.9, 1 x 500 27.9 / 22.1, 8 x 120 16.5 / 17.4.
+  const unsigned heads = static_cast<unsigned>(a.units) * a.group;
+  const char* const asked = getenv("ROCO_PREFILL_WAVES_PER_ROW");
+  const bool four = asked != nullptr && *asked != 0 ? asked[0] == '4' : static_cast<double>(heads) * a.L_max <= (a.L_max >= 256 || D == 128 ? 2048.0 : 1024.0) &&
+                           (DT == kF32 || a.L_max > 128);
+  if (four) hipLaunchKernelGGL((prefill_rows_simple<DT, D, kWaves>), dim3(a.L_max, heads), dim3(kThreads), 0, s, a);
+  else hipLaunchKernelGGL((prefill_rows_simple<DT, D, 1>), dim3((a.L_max + kWaves - 1) / kWaves, heads), dim3(kThreads), 0, s, a);
 }
 
 template <int DT, int D>

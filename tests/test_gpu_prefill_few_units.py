@@ -1,6 +1,8 @@
 """Prompts of few units: the workgroups of the units that do not fill all dies evenly are dealt to the dies one by one, the waves
 of a workgroup share its rows and several workgroups share a block's tiles.  Every form and both passes, with and without
 output, against the vector-ALU passes (one wave per query, per key) on the same inputs."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -171,3 +173,22 @@ def test_rows_copied_by_the_selection(dtype, d, B):
     prompts shorter than the budget (nothing is ranked), one token."""
     L = max(300, B + 90)
     TP.run_workload(dtype, d, 5, [L, B, max(1, B - 1), 1, min(L, B + 1)], L, B, max(1, B // 3), 2, seed=B, tag=f"copy-{dtype}-{d}-{B}")
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("waves", ["1", "4"])
+def test_waves_that_share_a_row(dtype, d, waves, monkeypatch):
+    """Prompts that end before, at and behind the blocks of keys that the four waves of a row take in turn."""
+    monkeypatch.setenv("ROCO_PREFILL_SIMPLE", "1")
+    monkeypatch.setenv("ROCO_PREFILL_WAVES_PER_ROW", waves)
+    P, rng = TP._parity(), np.random.default_rng(d + int(waves))
+    lens = [1, 15, 16, 17, 31, 33, 63, 64, 65, 96, 127, 128, 129, 161]
+    L, B, s, sc = max(lens), 20, 5, 1.0 / math.sqrt(d)
+    Q, K, V = (rng.standard_normal((len(lens), L, d)).astype(np.float32) for _ in range(3))
+    if dtype == "bf16":
+        Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
+    for window in (0, 24):
+        sess = P.make_session(len(lens), d, B, s, dtype, 0.0, window, 0.5 if window else 0.0)
+        g = P.gpu_prefill(sess, Q, K, V, lens, True)
+        for u in range(len(lens)):
+            P.check_prefill_unit(g, u, Q[u], K[u], V[u], lens[u], B, s, sc, dtype, window, 0.5 if window else 0.0)
