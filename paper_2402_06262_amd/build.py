@@ -12,9 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libroco.so")
 NATIVE_PATH = os.path.join(HERE, "_native.so")  # extension module of the binding (host code)
 SOURCES = ["api.hip", "decode.hip", "prefill_simple.hip", "prefill_mfma.hip", "prefill_planes.hip",
-           "select_compact.hip", "block.hip", "block_fused.hip", "block_fused_pairs.hip",
-           "block_fused_rows8.hip", "block_fused_rows4.hip",
-           "block_fused_halves.hip", "profile.hip"]
+           "select_compact.hip", "block.hip", "block_fused.hip", "profile.hip"]
+SOURCES += [f"block_fused_{shape}_{d}.hip" for d in (128, 64) for shape in ("eight", "pairs", "rows8", "rows4", "halves")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -20,7 +20,7 @@
 //                   statistics of all rows to every slot and chooses the victim a following single-token step
 //                   would take.
 //
-// Steps of bf16 / 128 mostly take one or two kernels that keep the logits on the compute unit instead (block_fused.hpp).
+// Steps of bf16 mostly take one or two kernels that keep the logits on the compute unit instead (block_fused.hpp).
 //
 // The same three kernels serve grouped-query attention (section 5.3, "Extension to Grouped-Query Attention"):
 // g query heads share the unit's keys and values, the query rows are (token, head) pairs, and the statistics
@@ -392,20 +392,6 @@ template <int D> struct SharedTile {
   }
 };
 
-// The slot that the token of a single-token step overwrites in a full unit whose next_slot is negative: a cache that its owner has
-// put together without roco_select_victims.  By the statistics as they stand, which no kernel has touched yet, as block_prepare
-// chooses; the keys are formed as the search reads them, since this is not the path that has to be fast.
-template <int NT>
-__device__ __forceinline__ int victim_by_statistics(const float* stats, const int32_t* pos, int B, Policy pol, int scope, uint32_t* sel_sh,
-                                                 uint2* best_sh) {
-  auto keys = [&](int i) {
-    uint32_t mas_key, var_key;
-    ranking_keys(stats[i], stats[B + i], stats[2 * static_cast<size_t>(B) + i], pos[i], pol, mas_key, var_key);
-    return make_uint2(mas_key, var_key);
-  };
-  return select_victim<NT, 1>([&](int i) { return keys(i).y; }, [&](int i) { return keys(i).x; }, B, pol, scope, sel_sh, best_sh);
-}
-
 // QMAX: most query rows the instantiation takes (8, 16, 32 or 64).  The smaller ones need fewer registers and less LDS,
 // so more workgroups fit a compute unit, and they keep two tiles in flight per workgroup instead of one.
 // SINGLE: a single-token step without block_prepare (BlockArgs::single).  What it needs besides is kept out of the other steps'
@@ -447,7 +433,7 @@ __global__ __launch_bounds__(256, (D != 64 ? 1 : DT == kBF16 && (QMAX == 16 || Q
     fresh = was_full ? min(a.next_slot[u], B - 1) : n;
     if (fresh < 0) {  // (the tiles are not in use yet)
       uint32_t* const sel_sh = reinterpret_cast<uint32_t*>(lds_f);
-      fresh = victim_by_statistics<256>(a.stats + static_cast<size_t>(u) * 3 * B, a.pos + static_cast<size_t>(u) * B, B, a.pol, a.scope,
+      fresh = victim_by_statistics<256, 1>(a.stats + static_cast<size_t>(u) * 3 * B, a.pos + static_cast<size_t>(u) * B, B, a.pol, a.scope,
                                         sel_sh, reinterpret_cast<uint2*>(sel_sh + SelectLds<1>::kWords));
       __syncthreads();
     }
@@ -930,7 +916,7 @@ hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStrea
     return hipErrorInvalidValue;
   const bool mfma_path = dtype == kBF16 && head_dim == 128;
   hipError_t fused;
-  if (mfma_path && launch_block_fused(a, s, fused)) return fused != hipSuccess ? fused : hipGetLastError();
+  if (dtype == kBF16 && launch_block_fused(head_dim, a, s, fused)) return fused != hipSuccess ? fused : hipGetLastError();
   if (!a.single) {
     ProfScope ps(kProfBlockPrepare, s);
     // Two 1024-thread workgroups do not run side by side on a compute unit here (measured: the second half of 512

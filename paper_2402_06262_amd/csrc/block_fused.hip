@@ -1,4 +1,4 @@
-// When the one-kernel step of block_fused.hpp is taken, with its shapes of eight waves and 16 query rows.
+// When the one-kernel step of block_fused.hpp is taken, and in which shape.
 #include <cstdlib>
 
 #include "block_fused.hpp"
@@ -6,45 +6,63 @@
 namespace roco {
 namespace fused {
 
-template hipError_t launch<8, 1, 4>(const BlockArgs&, hipStream_t);
-template hipError_t launch<8, 1, 8>(const BlockArgs&, hipStream_t);
-template hipError_t launch<8, 1, 16>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch<4, 1, 4>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch<4, 1, 8>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch<4, 1, 16>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch<8, 2, 4>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch<8, 2, 8>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch<4, 2, 4>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch<4, 2, 8>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch_halves<4>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch_halves<8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 4, 1, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 4, 1, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 4, 1, 16>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 8, 2, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 8, 2, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 4, 2, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 4, 2, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 8, 1, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 8, 1, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<128, 8, 1, 16>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<128, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<128, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 4, 1, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 4, 1, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 4, 1, 16>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 8, 2, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 8, 2, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 4, 2, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 4, 2, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 8, 1, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 8, 1, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch<64, 8, 1, 16>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<64, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<64, 8>(const BlockArgs&, hipStream_t);
 
 using Launch = hipError_t (*)(const BlockArgs&, hipStream_t);
 
 // The shape for W waves: the fewest tiles per wave that hold the unit's slots, null if none does.
-template <int W, int NQ, int ZT, int... MORE>
+template <int HD, int W, int NQ, int ZT, int... MORE>
 Launch shape_for(const BlockArgs& a) {
-  if (Shape<W, NQ, ZT>::takes(a)) return launch<W, NQ, ZT>;
-  if constexpr (sizeof...(MORE) > 0) return shape_for<W, NQ, MORE...>(a);
+  if (Shape<HD, W, NQ, ZT>::takes(a)) return launch<HD, W, NQ, ZT>;
+  if constexpr (sizeof...(MORE) > 0) return shape_for<HD, W, NQ, MORE...>(a);
   return nullptr;
 }
 
 // 33 to 64 rows: each half of the tokens in a workgroup of its own, where the pairs take one round and the stream, which both read,
-// is long enough.  Against the three kernels, us per step: 128 units x 2048 slots x 16 tokens of 4 heads 95 / 66, 48 x 1024 x 16 of 4
-// 53 / 37, 4 x 476 x 48 39.9 / 34.1, 7 x 1804 x 19 of 2 48.0 / 46.6; two rounds: 160 x 1024 x 10 of 4 74 / 67, 256 x 1536 x 16 of 4
-// 115 / 101, but 176 x 584 x 41 66 / 68, 140 x 248 x 46 53 / 57; more: 512 x 1536 x 10 of 4 166 / 175, 423 x 244 x 61 77 / 125.
+// is long enough.  Against the three kernels, us per step, bf16 / 128: 128 units x 2048 slots x 16 tokens of 4 heads 95 / 64, 48 x 1024
+// x 16 of 4 53 / 37, 4 x 476 x 48 39.9 / 34.1, 7 x 1804 x 19 of 2 48.0 / 46.6; two rounds: 160 x 1024 x 10 of 4 74 / 67, 256 x 1536 x
+// 16 of 4 115 / 101, but 176 x 584 x 41 66 / 68, 140 x 248 x 46 53 / 57; more: 512 x 1536 x 10 of 4 166 / 175, 423 x 244 x 61 77 / 125.
+// bf16 / 64, whose three kernels do not use the matrix cores: 127 x 836 x 40 103 / 35, 254 x 132 x 25 of 2 60 / 44, 724 x 1240 x 12 of
+// 4 488 / 170, 827 x 232 x 44 156 / 150, but 878 x 144 x 46 133 / 151, 758 x 104 x 46 95 / 124.
+template <int HD>
 Launch choose_halves(const BlockArgs& a) {
   const BlockArgs half = half_step(a);
   if (a.block < 2 || a.pol.keeps_last_score() || a.pol.counts_above_average()) return nullptr;
-  const Launch two = Shape<8, 2, 4>::takes(half) ? launch_halves<4> : Shape<8, 2, 8>::takes(half) ? launch_halves<8> : nullptr;
+  const Launch two = Shape<HD, 8, 2, 4>::takes(half)   ? launch_halves<HD, 4>
+                     : Shape<HD, 8, 2, 8>::takes(half) ? launch_halves<HD, 8>
+                                                       : nullptr;
   const char* const asked = getenv("ROCO_BLOCK_FUSED");
   if (asked != nullptr && *asked != 0) return asked[0] == '0' ? nullptr : two;
   if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
+  if (HD == 64) return a.units <= 256 || a.B >= 224 ? two : nullptr;
   return a.units <= 128 || (a.units <= 256 && a.B > 768) ? two : nullptr;
 }
 
-// Up to 32 rows.  One workgroup per unit needs units enough, or caches so small that the launches it saves count for more.  Against the three
-// kernels, us per step:
+// Up to 32 rows.  One workgroup per unit needs units enough, or caches so small that the launches it saves count for more.  Against the
+// three kernels, us per step, bf16 / 128:
 //   up to 16 rows, B <= 1024: always (1 unit x 120 slots x 16 heads 13.7 / 9.2, 4 x 368 x 16 tokens 26.4 / 22.7, 20 x 944 x 2 heads
 //   17.6 / 16.7, 161 x 228 x 16 heads 25.1 / 13.8); B <= 2048 from 72 units on (48 x 1536 x 4 heads 25.0 / 28.1, 64 x 2048 x 4 heads
 //   32.6 / 34.6, 80 x 1536 x 4 heads 30.7 / 29.9, 128 x 2048 x 4 heads 45.9 / 38.4), B <= 4096 from 80 on (64 x 3072 x 4 heads
@@ -52,28 +70,32 @@ Launch choose_halves(const BlockArgs& a) {
 //   17 to 32 rows, B <= 1024: always (1 x 892 x 21 tokens 32.1 / 32.0, 511 x 132 x 20 rows 45.9 / 27.8); B <= 2048 from 72 to 256
 //   units, where none waits for a second round (62 x 2044 x 28 rows 53.0 / 54.6, 96 x 2048 x 32 78.2 / 72.4, 256 x 2048 x 32 108 / 85,
 //   264 x 1664 x 29 121 / 128).
+// bf16 / 64, half of the bytes: B <= 2048 always (3 units x 1656 slots x 2 heads 19.7 / 16.8, 2 x 1764 x 22 tokens 37.7 / 36.3, 171 x 992 x
+//   16 heads 46.7 / 17.9, 518 x 1904 x 20 rows 302 / 125), B <= 4096 from 24 units on (17 x 3632 x 8 rows 43.0 / 45.7, 26 x 3580 x 3
+//   tokens 42.0 / 41.6, 128 x 3500 x 8 heads 70.5 / 39.4).
 // Four waves, two workgroups to a compute unit, where the units are more than the compute units (512 x 16 tokens x 2048 with eight
 // 119.7, with four 110.8; 356 x 2 heads x 132 23.0 / 14.1) and where a cache is a tile or two per wave (1 x 120 x 16 heads 10.1 / 9.2),
 // else eight (256 x 16 tokens x 2048 58.7 / 67.8, 128 x 4 heads x 2048 38.4 / 43.0).
 // ROCO_BLOCK_FUSED=8, 4, 0: eight waves, four, three kernels (tests run all); so does a number of splits that is asked for.
+template <int HD>
 Launch choose(const BlockArgs& a) {
-  if (a.queries > 2 * kQ16) return choose_halves(a);
+  if (a.queries > 2 * kQ16) return choose_halves<HD>(a);
   const bool one = a.queries <= kQ16;
-  const Launch eight = one ? shape_for<8, 1, 4, 8, 16>(a) : shape_for<8, 2, 4, 8>(a);
-  const Launch four = one ? shape_for<4, 1, 4, 8, 16>(a) : shape_for<4, 2, 4, 8>(a);
+  const Launch eight = one ? shape_for<HD, 8, 1, 4, 8, 16>(a) : shape_for<HD, 8, 2, 4, 8>(a);
+  const Launch four = one ? shape_for<HD, 4, 1, 4, 8, 16>(a) : shape_for<HD, 4, 2, 4, 8>(a);
   const char* const asked = getenv("ROCO_BLOCK_FUSED");
   if (asked != nullptr && *asked != 0) return asked[0] == '8' ? eight : asked[0] == '4' ? four : nullptr;
   if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
   const bool pairs = four != nullptr && (a.units > 256 || a.B <= 256);
-  const int least = a.B <= 1024 ? 0 : a.B <= 2048 ? 72 : 80;
-  if (a.units < least || (!one && !pairs && a.units > 256)) return nullptr;
+  const int least = HD == 64 ? (a.B <= 2048 ? 0 : 24) : a.B <= 1024 ? 0 : a.B <= 2048 ? 72 : 80;
+  if (a.units < least || (HD == 128 && !one && !pairs && a.units > 256)) return nullptr;
   return pairs ? four : eight;
 }
 
 }  // namespace fused
 
-bool launch_block_fused(const BlockArgs& a, hipStream_t s, hipError_t& e) {
-  const fused::Launch step = fused::choose(a);
+bool launch_block_fused(int head_dim, const BlockArgs& a, hipStream_t s, hipError_t& e) {
+  const fused::Launch step = head_dim == 128 ? fused::choose<128>(a) : fused::choose<64>(a);
   if (step == nullptr) return false;
   ProfScope ps(kProfBlockAttend, s);
   e = step(a, s);

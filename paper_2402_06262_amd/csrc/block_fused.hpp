@@ -1,4 +1,4 @@
-// The whole step of a unit in one workgroup, for bf16 / 128: block-wise evict-and-encode and grouped single tokens whose logits stay
+// The whole step of a unit in one workgroup, for bf16: block-wise evict-and-encode and grouped single tokens whose logits stay
 // on the compute unit.
 //
 // The three kernels of block.hip pass the logits through memory, because the statistics need every row's normaliser, which is known
@@ -36,15 +36,35 @@ namespace fused {
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 
-using namespace mfma;
+using mfma::bf16x8;
+using mfma::lds_address;
+using mfma::lds_read_transposed;
+using mfma::load16_to_lds_hint;
+using mfma::load4_to_lds;
+using mfma::make_buffer;
+using mfma::reads_done;
+using mfma::v4i32;
+using mfma::wait_loads;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kTileSlots = 32;                     // slots of a tile of K or V: one wave's
-constexpr int kTileBytes = kTileSlots * kRowBytes;  // 8 KiB
-constexpr int kTileLoads = kTileBytes / 1024;       // wave-wide loads
-constexpr int kQ16 = 16;                           // query rows per matrix tile
-constexpr int kOutRow = D + 4;                     // floats per row of a wave's output in LDS
+constexpr int kTileSlots = 32;  // slots of a tile of K or V: one wave's
+constexpr int kQ16 = 16;         // query rows per matrix tile
+
+// Geometry of bf16 rows of HD elements.
+template <int HD> struct Rows {
+  static constexpr int kBytes = 2 * HD;
+  static constexpr int kChunks = kBytes / 16;             // 16-byte chunks: lanes per row of a load
+  static constexpr int kPerLoad = kWave / kChunks;        // rows of a wave-wide load
+  static constexpr int kTile = kTileSlots * kBytes;       // bytes of a tile
+  static constexpr int kLoads = kTile / 1024;             // wave-wide loads of a tile
+  static constexpr int kSteps = HD / 32, kBlocks = HD / 16;  // of the matrix instruction: k-steps of a score, blocks of dimensions
+  static constexpr int kOut = HD + 4;                     // floats per row of a wave's output in LDS
+  // K chunk c of row r lies in slot c ^ swizzle_k(r), V chunk c in slot c ^ swizzle_v(r): 16 lanes that read a chunk of K of 16 rows,
+  // and 32 that read 32 bytes of V of 8 rows, fall on distinct banks (256 bytes: two rows of 64 elements, one of 128).
+  static __device__ __forceinline__ int swizzle_k(int r) { return HD == 128 ? r & 15 : (r >> 1) & 7; }
+  static __device__ __forceinline__ int swizzle_v(int r) { return HD == 128 ? ((r & 3) << 2) ^ (((r >> 2) & 1) << 1) : ((r >> 1) & 3) << 1; }
+};
 
 // The 16x16x32 instruction as used here: lane l supplies row (l % 16) and the 8 consecutive k-elements from 8 (l / 16) on, for A and
 // for B alike; register r of the result belongs to A-row 4 (l / 16) + r and B-row (l % 16).  Scores: A = 16 slots of K, B = the
@@ -67,10 +87,12 @@ __device__ __forceinline__ float* part_sums(const BlockArgs& a, int u, int h) { 
 // W waves.  NQ tiles of 16 query rows.  ZT: tiles of a wave whose logits its registers hold (32 W ZT slots in all).
 // SINGLE: one token; its slot is known from the state.  lds_slots: slots whose probabilities the LDS takes at a time, a multiple of 32 W,
 // four to a thread.  v_room: there is room for the first tiles of V beside them.
-template <int W, int NQ, int ZT, bool SINGLE, bool STREAMING, bool WINDOW, bool HALVES = false>
+template <int HD, int W, int NQ, int ZT, bool SINGLE, bool STREAMING, bool WINDOW, bool HALVES = false>
 __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds_slots, int v_room) {
+  using R = Rows<HD>;
   constexpr int NT = W * kWave;
   constexpr int QR = NQ * kQ16;
+  constexpr int kRowBytes = R::kBytes, kTileBytes = R::kTile, kTileLoads = R::kLoads;
   constexpr int kSide = WINDOW ? 1 : 0;  // the positions of a K tile's slots come along
   constexpr int PER_WORD = W == 4 ? 2 : 1;
   constexpr bool TURNS = ZT > 4 && NQ == 1;  // little to stream, or no registers to spare: the code for both orders costs more than they gain
@@ -96,7 +118,14 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   const int n = min(B, n_old + a.block);
   const int qp0 = a.qpos0[u];
   const bool evicted = n_old >= B;
-  const int fresh = !SINGLE ? -1 : evicted ? min(max(a.next_slot[u], 0), B - 1) : n_old;
+  int fresh = -1;
+  if (SINGLE) {
+    fresh = evicted ? min(a.next_slot[u], B - 1) : n_old;
+    if (HD == 64 && fresh < 0)  // (bf16 / 128 takes slot 0)
+      fresh = victim_by_statistics<NT, PER_WORD>(a.stats + static_cast<size_t>(u) * 3 * B, a.pos + static_cast<size_t>(u) * B, B, a.pol, a.scope,
+                                                 sel_sh, best_sh);
+    fresh = max(fresh, 0);
+  }
   char* const Kb = static_cast<char*>(a.K) + static_cast<size_t>(u) * B * kRowBytes;
   char* const Vb = static_cast<char*>(a.V) + static_cast<size_t>(u) * B * kRowBytes;
   int32_t* const pos = a.pos + static_cast<size_t>(u) * B;
@@ -107,22 +136,21 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   const v4i32 pbuf = make_buffer(pos, static_cast<uint32_t>(B) * 4u);
   char* const tiles = lds + wave * kTileBytes;  // stage s: W tiles further
   const uint32_t tiles_addr = lds_address(tiles), pos_addr = lds_address(&pos_s[WINDOW ? wave : 0][0][0]);
-  // K chunk c of row r lies in slot c ^ r, V chunk c in slot c ^ 4 (r % 4) ^ 2 (r / 4 % 2): the fragment reads of 16 lanes fall on
-  // distinct banks.  The scalar offset is the tile's first row, which exists (see load16_to_lds).
+  // (the scalar offset of a request is the tile's first row, which exists: see load16_to_lds)
   const int n_tiles = (n + kTileSlots - 1) / kTileSlots;
   const int mine = (n_tiles - wave + W - 1) / W;
   const int rot = mine > 0 ? static_cast<int>((static_cast<unsigned>(u) * 5u) % static_cast<unsigned>(mine)) : 0;
   auto tile_of = [&](int t) { return t + rot < mine ? t + rot : t + rot - mine; };  // index among the wave's tiles
   auto tile_row = [&](int t) { return (tile_of(t) * W + wave) * kTileSlots; };
-  auto swizzle_v = [](int r) { return ((r & 3) << 2) ^ (((r >> 2) & 1) << 1); };
+  const int load_row = lane / R::kChunks, load_slot = lane % R::kChunks;  // of a wave-wide load
   auto request_k = [&](int t) {
     const int row = tile_row(t);
     const int soff = __builtin_amdgcn_readfirstlane(row * kRowBytes);
     const uint32_t dst = tiles_addr + (t & 1) * (W * kTileBytes);
 #pragma unroll
     for (int i = 0; i < kTileLoads; ++i) {
-      const int r = 4 * i + g;
-      load16_to_lds_hint<STREAMING>(kbuf, dst + i * 1024, r * kRowBytes + ((qi ^ (r & 15)) << 4), soff);
+      const int r = R::kPerLoad * i + load_row;
+      load16_to_lds_hint<STREAMING>(kbuf, dst + i * 1024, r * kRowBytes + ((load_slot ^ R::swizzle_k(r)) << 4), soff);
     }
     if (WINDOW) load4_to_lds(pbuf, pos_addr + (t & 1) * (kWave * 4), lane * 4, __builtin_amdgcn_readfirstlane(row * 4));
   };
@@ -131,8 +159,8 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
     const uint32_t dst = tiles_addr + (t & 1) * (W * kTileBytes);
 #pragma unroll
     for (int i = 0; i < kTileLoads; ++i) {
-      const int r = 4 * i + g;
-      load16_to_lds_hint<STREAMING>(vbuf, dst + i * 1024, r * kRowBytes + ((qi ^ swizzle_v(r)) << 4), soff);
+      const int r = R::kPerLoad * i + load_row;
+      load16_to_lds_hint<STREAMING>(vbuf, dst + i * 1024, r * kRowBytes + ((load_slot ^ R::swizzle_v(r)) << 4), soff);
     }
   };
   const bool mine_first = !TURNS || (u & 8) == 0;  // neighbours on a die take turns (see above)
@@ -141,12 +169,12 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   if (mine > 0 && !evict_first) request_k(0);
 
   // B operand: the queries (lanes beyond the step's repeat its last one; their results are dropped)
-  uint4 own[NQ][4];
+  uint4 own[NQ][R::kSteps];
 #pragma unroll
   for (int t2 = 0; t2 < NQ; ++t2) {
     const char* qrow = static_cast<const char*>(a.q) + (first_row + min(kQ16 * t2 + qi, nq - 1)) * kRowBytes;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) own[t2][kk] = load16(qrow + kk * 64 + g * 16);
+    for (int kk = 0; kk < R::kSteps; ++kk) own[t2][kk] = load16(qrow + kk * 64 + g * 16);
   }
   const float sc = a.scale_log2, rb = a.recency_bias_log2;
   const int w = a.recency_window;
@@ -166,14 +194,14 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
 #pragma unroll 1
     for (int t0 = 0; t0 < a.block; t0 += kQ16) {
       const char* krow = static_cast<const char*>(a.k_new) + (static_cast<size_t>(u) * a.block + min(t0 + qi, a.block - 1)) * kRowBytes;
-      uint4 kn[4];
+      uint4 kn[R::kSteps];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) kn[kk] = load16(krow + kk * 64 + g * 16);
+      for (int kk = 0; kk < R::kSteps; ++kk) kn[kk] = load16(krow + kk * 64 + g * 16);
 #pragma unroll
       for (int t2 = 0; t2 < NQ; ++t2) {
         f32x4 s = f32x4{0};
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) s = mfma16(kn[kk], own[t2][kk], s);
+        for (int kk = 0; kk < R::kSteps; ++kk) s = mfma16(kn[kk], own[t2][kk], s);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int tok = t0 + 4 * g + e;  // a query does not see later tokens of the block
@@ -194,7 +222,7 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
   if (evict_first) evict();
   // A single token's row, put over what its slot held, in the tile if it is there and in the cache: 16 lanes.
   auto put_row = [&](const void* rows, char* cache, char* tile, int slot_in_tile, int swizzle) {
-    if (static_cast<unsigned>(slot_in_tile) < static_cast<unsigned>(kTileSlots) && lane < 16) {
+    if (static_cast<unsigned>(slot_in_tile) < static_cast<unsigned>(kTileSlots) && lane < R::kChunks) {
       const uint4 row = load16(static_cast<const char*>(rows) + static_cast<size_t>(u) * kRowBytes + lane * 16);
       *reinterpret_cast<uint4*>(tile + slot_in_tile * kRowBytes + ((lane ^ swizzle) << 4)) = row;
       *reinterpret_cast<uint4*>(cache + static_cast<size_t>(fresh) * kRowBytes + lane * 16) = row;
@@ -210,7 +238,7 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
     // ---- scores
     if (mine > 0 && evict_first) request_k(0);
     if (mine > 1) request_k(1);
-    const int kfrag = qi * kRowBytes + ((g ^ qi) << 4);
+    const int kfrag = qi * kRowBytes + ((g ^ R::swizzle_k(qi)) << 4);
 #pragma unroll 1
     for (int t = 0; t < mine; ++t) {
       const int sb = tile_row(t);
@@ -218,10 +246,10 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
       char* const tile = tiles + (t & 1) * (W * kTileBytes);
       if (t + 1 < mine) wait_loads<kTileLoads + kSide>();
       else wait_loads<0>();
-      if (SINGLE) put_row(a.k_new, Kb, tile, fresh - sb, (fresh - sb) & 15);
+      if (SINGLE) put_row(a.k_new, Kb, tile, fresh - sb, R::swizzle_k(fresh - sb));
       f32x4 s[NQ][2];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
+      for (int kk = 0; kk < R::kSteps; ++kk) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const uint4 kf = *reinterpret_cast<const uint4*>(tile + h * 16 * kRowBytes + (kfrag ^ (kk << 6)));
@@ -487,14 +515,14 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
     // ---- O^T = V^T . P^T
     if (!v_ahead && mine > 0) request_v(0);
     if (mine > 1) request_v(1);
-    f32x4 o[NQ][8];
+    f32x4 o[NQ][R::kBlocks];
 #pragma unroll
     for (int t2 = 0; t2 < NQ; ++t2)
 #pragma unroll
-      for (int db = 0; db < 8; ++db) o[t2][db] = f32x4{0};
+      for (int db = 0; db < R::kBlocks; ++db) o[t2][db] = f32x4{0};
     // V^T of dimensions 0..15: rows 4 g + lane / 4 % 4 of either half of the tile, 8 bytes from column 4 (lane % 4) on
     const int vrow = 4 * g + (qi >> 2);
-    const int vfrag = vrow * kRowBytes + (swizzle_v(vrow) << 4) + (qi & 3) * 8;
+    const int vfrag = vrow * kRowBytes + (R::swizzle_v(vrow) << 4) + (qi & 3) * 8;
 #pragma unroll 1
     for (int t = 0; t < mine; ++t) {
       const int zt = tile_of(t), sb = tile_row(t);
@@ -526,10 +554,10 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
       }
       if (t + 1 < mine) wait_loads<kTileLoads>();
       else wait_loads<0>();
-      if (SINGLE) put_row(a.v_new, Vb, tile, fresh - sb, swizzle_v(fresh - sb));
+      if (SINGLE) put_row(a.v_new, Vb, tile, fresh - sb, R::swizzle_v(fresh - sb));
 #pragma unroll
-      for (int db = 0; db < 8; ++db) {
-        const char* const vt = tile + (vfrag ^ ((db >> 1) << 6) ^ ((db & 1) << 5));
+      for (int db = 0; db < R::kBlocks; ++db) {
+        const char* const vt = tile + (vfrag ^ (db << 5));
         const uint2 lo = lds_read_transposed(vt), hi = lds_read_transposed(vt + 16 * kRowBytes);
         const uint4 vf = make_uint4(lo.x, lo.y, hi.x, hi.y);
 #pragma unroll
@@ -539,26 +567,26 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
       if (t + 2 < mine) request_v(t + 2);
     }
     __syncthreads();  // nobody needs the tiles any more
-    float* const outs = reinterpret_cast<float*>(lds);  // [W][QR][kOutRow]
+    float* const outs = reinterpret_cast<float*>(lds);  // [W][QR][R::kOut]
 #pragma unroll
     for (int t2 = 0; t2 < NQ; ++t2) {
       const int q = kQ16 * t2 + qi;
       if (q < nq) {
 #pragma unroll
-        for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4*>(outs + (wave * QR + q) * kOutRow + 16 * db + 4 * g) = o[t2][db];
+        for (int db = 0; db < R::kBlocks; ++db) *reinterpret_cast<f32x4*>(outs + (wave * QR + q) * R::kOut + 16 * db + 4 * g) = o[t2][db];
       }
     }
     __syncthreads();
 #pragma unroll 1
-    for (int idx = tid * 4; idx < nq * D; idx += NT * 4) {
-      const int q = idx / D, dd = idx % D;
+    for (int idx = tid * 4; idx < nq * HD; idx += NT * 4) {
+      const int q = idx / HD, dd = idx % HD;
       f32x4 sum = f32x4{0};
 #pragma unroll
-      for (int i = 0; i < W; ++i) sum += *reinterpret_cast<const f32x4*>(outs + (i * QR + q) * kOutRow + dd);
+      for (int i = 0; i < W; ++i) sum += *reinterpret_cast<const f32x4*>(outs + (i * QR + q) * R::kOut + dd);
       uint2 r;
       r.x = f32_to_bf16(sum.x) | static_cast<uint32_t>(f32_to_bf16(sum.y)) << 16;
       r.y = f32_to_bf16(sum.z) | static_cast<uint32_t>(f32_to_bf16(sum.w)) << 16;
-      *reinterpret_cast<uint2*>(static_cast<char*>(a.out) + (first_row * D + idx) * 2) = r;
+      *reinterpret_cast<uint2*>(static_cast<char*>(a.out) + (first_row * HD + idx) * 2) = r;
     }
   };
 
@@ -635,7 +663,7 @@ __global__ __launch_bounds__(NT, 2) void block_book(BlockArgs a) {
 
 constexpr size_t kLdsOfUnit = 160 << 10;  // of a compute unit
 
-template <int W, int NQ, int ZT> struct Shape {
+template <int HD, int W, int NQ, int ZT> struct Shape {
   static constexpr int kStep = kTileSlots * W;
   static size_t bytes_of(const BlockArgs& a, int slots) { return (2 * static_cast<size_t>(a.B) + static_cast<size_t>(a.queries) * (slots + 4)) * 4; }
   // what block_fused declares statically, at most
@@ -651,11 +679,11 @@ template <int W, int NQ, int ZT> struct Shape {
     while (s > 0 && bytes_of(a, s) > most) s -= kStep;
     return s;
   }
-  static constexpr size_t kStage = W * kTileBytes;
+  static constexpr size_t kStage = W * Rows<HD>::kTile;
   // whether the first tiles of V may be on their way meanwhile
   static bool v_ahead(const BlockArgs& a) { return W == 8 && slots(a, kStage) >= std::min(a.B, 4 * W * kWave); }
   static size_t lds(const BlockArgs& a) {
-    const size_t outs = static_cast<size_t>(W) * NQ * kQ16 * kOutRow * sizeof(float), ahead = v_ahead(a) ? kStage : 0;
+    const size_t outs = static_cast<size_t>(W) * NQ * kQ16 * Rows<HD>::kOut * sizeof(float), ahead = v_ahead(a) ? kStage : 0;
     return std::max({2 * kStage, outs, ahead + bytes_of(a, slots(a, ahead))});
   }
   static bool takes(const BlockArgs& a) { return a.B <= kStep * ZT && a.queries <= kQ16 * NQ && slots(a, 0) > 0; }
@@ -667,46 +695,46 @@ inline BlockArgs half_step(BlockArgs a) {
   return a;
 }
 
-template <int W, int NQ, int ZT, bool SINGLE, bool STREAMING, bool WINDOW>
+template <int HD, int W, int NQ, int ZT, bool SINGLE, bool STREAMING, bool WINDOW>
 hipError_t launch_t(const BlockArgs& a, hipStream_t s) {
-  using S = Shape<W, NQ, ZT>;
+  using S = Shape<HD, W, NQ, ZT>;
   const size_t lds = S::lds(a);
-  const void* fn = reinterpret_cast<const void*>(block_fused<W, NQ, ZT, SINGLE, STREAMING, WINDOW>);
+  const void* fn = reinterpret_cast<const void*>(block_fused<HD, W, NQ, ZT, SINGLE, STREAMING, WINDOW>);
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL((block_fused<W, NQ, ZT, SINGLE, STREAMING, WINDOW>), dim3(a.units), dim3(W * kWave), lds, s, a,
+  hipLaunchKernelGGL((block_fused<HD, W, NQ, ZT, SINGLE, STREAMING, WINDOW>), dim3(a.units), dim3(W * kWave), lds, s, a,
                      S::slots(a, S::v_ahead(a) ? S::kStage : 0), S::v_ahead(a) ? 1 : 0);
   return hipSuccess;
 }
-template <int W, int NQ, int ZT>
+template <int HD, int W, int NQ, int ZT>
 hipError_t launch(const BlockArgs& a, hipStream_t s) {
   const bool window = a.recency_window > 0;
   if (a.single) {
-    if (a.streaming) return window ? launch_t<W, NQ, ZT, true, true, true>(a, s) : launch_t<W, NQ, ZT, true, true, false>(a, s);
-    return window ? launch_t<W, NQ, ZT, true, false, true>(a, s) : launch_t<W, NQ, ZT, true, false, false>(a, s);
+    if (a.streaming) return window ? launch_t<HD, W, NQ, ZT, true, true, true>(a, s) : launch_t<HD, W, NQ, ZT, true, true, false>(a, s);
+    return window ? launch_t<HD, W, NQ, ZT, true, false, true>(a, s) : launch_t<HD, W, NQ, ZT, true, false, false>(a, s);
   }
-  if (a.streaming) return window ? launch_t<W, NQ, ZT, false, true, true>(a, s) : launch_t<W, NQ, ZT, false, true, false>(a, s);
-  return window ? launch_t<W, NQ, ZT, false, false, true>(a, s) : launch_t<W, NQ, ZT, false, false, false>(a, s);
+  if (a.streaming) return window ? launch_t<HD, W, NQ, ZT, false, true, true>(a, s) : launch_t<HD, W, NQ, ZT, false, true, false>(a, s);
+  return window ? launch_t<HD, W, NQ, ZT, false, false, true>(a, s) : launch_t<HD, W, NQ, ZT, false, false, false>(a, s);
 }
 
-template <int ZT, bool STREAMING, bool WINDOW>
+template <int HD, int ZT, bool STREAMING, bool WINDOW>
 hipError_t launch_halves_t(const BlockArgs& a, const BlockArgs& half, hipStream_t s) {
-  using S = Shape<8, 2, ZT>;
+  using S = Shape<HD, 8, 2, ZT>;
   const size_t lds = S::lds(half);
-  const void* fn = reinterpret_cast<const void*>(block_fused<8, 2, ZT, false, STREAMING, WINDOW, true>);
+  const void* fn = reinterpret_cast<const void*>(block_fused<HD, 8, 2, ZT, false, STREAMING, WINDOW, true>);
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL((block_fused<8, 2, ZT, false, STREAMING, WINDOW, true>), dim3((a.units + 7) / 8 * 16), dim3(8 * kWave), lds, s, a,
+  hipLaunchKernelGGL((block_fused<HD, 8, 2, ZT, false, STREAMING, WINDOW, true>), dim3((a.units + 7) / 8 * 16), dim3(8 * kWave), lds, s, a,
                      S::slots(half, S::v_ahead(half) ? S::kStage : 0), S::v_ahead(half) ? 1 : 0);
   hipLaunchKernelGGL((block_book<kBookThreads>), dim3(a.units), dim3(kBookThreads), key_lds_bytes(a.B), s, a);
   return hipSuccess;
 }
-template <int ZT>
+template <int HD, int ZT>
 hipError_t launch_halves(const BlockArgs& a, hipStream_t s) {
   const BlockArgs half = half_step(a);
   const bool window = a.recency_window > 0;
-  if (a.streaming) return window ? launch_halves_t<ZT, true, true>(a, half, s) : launch_halves_t<ZT, true, false>(a, half, s);
-  return window ? launch_halves_t<ZT, false, true>(a, half, s) : launch_halves_t<ZT, false, false>(a, half, s);
+  if (a.streaming) return window ? launch_halves_t<HD, ZT, true, true>(a, half, s) : launch_halves_t<HD, ZT, true, false>(a, half, s);
+  return window ? launch_halves_t<HD, ZT, false, true>(a, half, s) : launch_halves_t<HD, ZT, false, false>(a, half, s);
 }
 
 }  // namespace fused

@@ -1,0 +1,9 @@
+// Shapes of block_fused.hpp for bf16 / 128 with 33 to 64 query rows, half of the tokens in each of two workgroups.
+#include "block_fused.hpp"
+
+namespace roco {
+namespace fused {
+template hipError_t launch_halves<128, 4>(const BlockArgs&, hipStream_t);
+template hipError_t launch_halves<128, 8>(const BlockArgs&, hipStream_t);
+}  // namespace fused
+}  // namespace roco

@@ -108,6 +108,20 @@ __device__ __forceinline__ void take_slots(const BlockArgs& a, int u, int n, uin
   }
 }
 
+// The slot that the token of a single-token step overwrites in a full unit whose next_slot is negative: a cache that its owner has
+// put together without roco_select_victims.  By the statistics as they stand, which no kernel has touched yet, as block_prepare
+// chooses; the keys are formed as the search reads them, since this is not the path that has to be fast.
+template <int NT, int PER_WORD>
+__device__ __forceinline__ int victim_by_statistics(const float* stats, const int32_t* pos, int B, Policy pol, int scope, uint32_t* sel_sh,
+                                                 uint2* best_sh) {
+  auto keys = [&](int i) {
+    uint32_t mas_key, var_key;
+    ranking_keys(stats[i], stats[B + i], stats[2 * static_cast<size_t>(B) + i], pos[i], pol, mas_key, var_key);
+    return make_uint2(mas_key, var_key);
+  };
+  return select_victim<NT, PER_WORD>([&](int i) { return keys(i).y; }, [&](int i) { return keys(i).x; }, B, pol, scope, sel_sh, best_sh);
+}
+
 #pragma clang diagnostic ignored "-Winline-asm"
 namespace mfma {
 

@@ -160,8 +160,8 @@ struct BlockArgs {
   uint32_t* keys;                  // [units][2][B] when B is too large for LDS
 };
 hipError_t launch_block(int dtype, int head_dim, const BlockArgs& a, hipStream_t s);  // B % 4 == 0
-// The step of bf16 / 128 in one kernel, if that is the quicker way (BlockArgs::single is set); else false and nothing is launched.
-bool launch_block_fused(const BlockArgs& a, hipStream_t s, hipError_t& e);
+// The step of bf16 in one or two kernels, if that is the quicker way (BlockArgs::single is set); else false and nothing is launched.
+bool launch_block_fused(int head_dim, const BlockArgs& a, hipStream_t s, hipError_t& e);
 
 // dtype: 0 = f32, 1 = bf16; head_dim: 64 or 128.  Each returns hipGetLastError() of its launches.
 hipError_t launch_decode(int dtype, int head_dim, const DecodeArgs& a, hipStream_t s);

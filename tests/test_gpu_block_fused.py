@@ -1,4 +1,4 @@
-"""Steps of bf16 / 128 in one kernel (two above 32 query rows) and in three: the same step, at the edges of the tiles, of the waves' shares
+"""Steps of bf16 in one kernel (two above 32 query rows) and in three: the same step, at the edges of the tiles, of the waves' shares
 and of the logits that registers and LDS hold."""
 import numpy as np
 import pytest
@@ -16,29 +16,31 @@ def kernels(request, monkeypatch):
     return request.param
 
 
+@pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("B", [4, 28, 32, 36, 124, 128, 132, 256, 260, 1028])
-def test_caches_that_end_at_the_edges_of_the_tiles(B, kernels):
+def test_caches_that_end_at_the_edges_of_the_tiles(B, d, kernels):
     """From the first token on, in lock-step with the oracle: 1 to 16 rows; up to 32; up to 64."""
     s = max(1, B // 8)
     fill = [16] * (B // 16) + [7, 1, 16, 9, 1] if B >= 16 else [3, 4, 1, 2, 1]
-    TG.drive(2, B, s, 1, [min(b, B) for b in fill], seed=900 + B, recency=B % 128 == 4, tag=f"edge-{B}")
+    TG.drive(2, B, s, 1, [min(b, B) for b in fill], seed=900 + B, recency=B % 128 == 4, tag=f"edge-{B}-{d}", d=d)
     if B >= 16:
-        TG.drive(2, B, s, 4, [8] * min(B // 8, 20) + [8, 1, 4, 1], seed=950 + B, tag=f"edge-{B}-g4")
-        TG.drive(9, B, s, 4, [min(16, B)] * min(B // 16, 6) + [13, 9, 1], seed=970 + B, recency=B % 64 == 0, tag=f"edge-{B}-halves")
+        TG.drive(2, B, s, 4, [8] * min(B // 8, 20) + [8, 1, 4, 1], seed=950 + B, tag=f"edge-{B}-{d}-g4", d=d)
+        TG.drive(9, B, s, 4, [min(16, B)] * min(B // 16, 6) + [13, 9, 1], seed=970 + B, recency=B % 64 == 0, tag=f"edge-{B}-{d}-halves", d=d)
 
 
 POLICIES = [(0, 0, 0), (1, 2, 0), (0, 1, 0), (2, 2, 4), (3, 2, 0), (4, 1, 0)]  # importance, scope kind, sinks
 
 
+@pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("B", [508, 512, 516, 1020, 1024, 1028, 2044, 2048, 2052, 4096])
 @pytest.mark.parametrize("block,group", [(1, 1), (1, 4), (1, 16), (16, 1), (3, 5), (2, 8), (1, 17), (32, 1), (5, 6), (33, 1), (64, 1),
                                          (16, 4), (3, 16), (9, 7), (17, 3)])
-def test_one_kernel_and_three_take_the_same_step(B, block, group, monkeypatch):
+def test_one_kernel_and_three_take_the_same_step(B, block, group, d, monkeypatch):
     """Caches from full to nearly empty, with a recency bias and without, under every kind of policy: the same slots and positions bit
     for bit.  Tolerances: bf16 outputs differ by a rounding or two (2^-7 of the row's largest); the statistics by fp32 sums in another
     order (a logit of up to 2^7 in powers of two has an error of 2^-16, which is that of the probability)."""
     import paper_2402_06262_amd as roco
-    units, d, seed = 5, 128, B + 64 * block + group
+    units, seed = 5, B + 64 * block + group
     g = torch.Generator(device="cuda").manual_seed(seed)
     rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda")
     imp, kind, sinks = POLICIES[seed % len(POLICIES)]
