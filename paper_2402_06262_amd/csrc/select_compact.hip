@@ -178,8 +178,8 @@ __global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) 
   // The first decode step on a full cache needs its victim.  (Before the rows are copied: a barrier waits for every store before it,
   // 3 to 4 us where the copies are long.)
   if (kept == B) {
-    if (E > 0) {
-      const uint32_t last = block_argmin<NT>(next_key, next, best_sh);  // 0xffffffff: nobody is outside
+    if (E > 0 && scope.kth != 0xffffffffu) {  // (else the scope is everything)
+      const uint32_t last = block_argmin<NT>(next_key, next, best_sh);
       if (last == next && next != 0xffffffffu && (next_mas < best_key || best == 0xffffffffu || (next_mas == best_key && next < best))) {
         best_key = next_mas;
         best = next;
