@@ -16,8 +16,9 @@ extern template hipError_t launch<128, 4, 2, 8>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<128, 8, 1, 4>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<128, 8, 1, 8>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<128, 8, 1, 16>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch_halves<128, 4>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch_halves<128, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<128, 4, 1, 16>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<128, 8, 2, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<128, 8, 2, 8>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<64, 4, 1, 4>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<64, 4, 1, 8>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<64, 4, 1, 16>(const BlockArgs&, hipStream_t);
@@ -28,8 +29,8 @@ extern template hipError_t launch<64, 4, 2, 8>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<64, 8, 1, 4>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<64, 8, 1, 8>(const BlockArgs&, hipStream_t);
 extern template hipError_t launch<64, 8, 1, 16>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch_halves<64, 4>(const BlockArgs&, hipStream_t);
-extern template hipError_t launch_halves<64, 8>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<64, 8, 2, 4>(const BlockArgs&, hipStream_t);
+extern template hipError_t launch_halves<64, 8, 2, 8>(const BlockArgs&, hipStream_t);
 
 using Launch = hipError_t (*)(const BlockArgs&, hipStream_t);
 
@@ -51,8 +52,8 @@ template <int HD>
 Launch choose_halves(const BlockArgs& a) {
   const BlockArgs half = half_step(a);
   if (a.block < 2 || a.pol.keeps_last_score() || a.pol.counts_above_average()) return nullptr;
-  const Launch two = Shape<HD, 8, 2, 4>::takes(half)   ? launch_halves<HD, 4>
-                     : Shape<HD, 8, 2, 8>::takes(half) ? launch_halves<HD, 8>
+  const Launch two = Shape<HD, 8, 2, 4>::takes(half)   ? launch_halves<HD, 8, 2, 4>
+                     : Shape<HD, 8, 2, 8>::takes(half) ? launch_halves<HD, 8, 2, 8>
                                                        : nullptr;
   const char* const asked = getenv("ROCO_BLOCK_FUSED");
   if (asked != nullptr && *asked != 0) return asked[0] == '0' ? nullptr : two;
@@ -67,16 +68,18 @@ Launch choose_halves(const BlockArgs& a) {
 //   17.6 / 16.7, 161 x 228 x 16 heads 25.1 / 13.8); B <= 2048 from 72 units on (48 x 1536 x 4 heads 25.0 / 28.1, 64 x 2048 x 4 heads
 //   32.6 / 34.6, 80 x 1536 x 4 heads 30.7 / 29.9, 128 x 2048 x 4 heads 45.9 / 38.4), B <= 4096 from 80 on (64 x 3072 x 4 heads
 //   41.3 / 48.2, 80 x 3072 55.6 / 50.1, 192 x 4096 117 / 76).
-//   17 to 32 rows, B <= 1024: always (1 x 892 x 21 tokens 32.1 / 32.0, 511 x 132 x 20 rows 45.9 / 27.8); B <= 2048 from 72 to 256
-//   units, where none waits for a second round (62 x 2044 x 28 rows 53.0 / 54.6, 96 x 2048 x 32 78.2 / 72.4, 256 x 2048 x 32 108 / 85,
-//   264 x 1664 x 29 121 / 128).
+//   17 to 32 rows, B <= 1024: always (1 x 892 x 21 tokens 32.1 / 32.0, 511 x 132 x 20 rows 45.9 / 27.8); B <= 2048 from 65 units on (62 x
+//   2044 x 28 rows 53.0 / 54.6, 65 x 2048 x 6 of 4 58.4 / 53.1, 140 x 1712 x 32 85 / 72, 256 x 2048 x 32 108 / 85, 447 x 2048 x 5 of 4 156 / 131).
+//   Above 24 rows, where eight waves' workgroups do not fill a round or do not fit it, half of the tokens in each of two workgroups of
+//   four waves (three kernels / eight waves / halves): 65 x 2048 x 32 69 / 70 / 60, 97 x 1628 x 32 74 / 67 / 57, 264 x 1536 x 32 115 / 123 /
+//   109, 512 x 2048 x 32 184 / 170 / 168, 697 x 1792 x 32 264 / 231 / 220; but 140 x 1352 x 6 of 4 66 / 49 / 54, 400 x 1960 x 17 143 / 132 / 144.
 // bf16 / 64, half of the bytes: B <= 2048 always (3 units x 1656 slots x 2 heads 19.7 / 16.8, 2 x 1764 x 22 tokens 37.7 / 36.3, 171 x 992 x
 //   16 heads 46.7 / 17.9, 518 x 1904 x 20 rows 302 / 125), B <= 4096 from 24 units on (17 x 3632 x 8 rows 43.0 / 45.7, 26 x 3580 x 3
 //   tokens 42.0 / 41.6, 128 x 3500 x 8 heads 70.5 / 39.4).
 // Four waves, two workgroups to a compute unit, where the units are more than the compute units (512 x 16 tokens x 2048 with eight
 // 119.7, with four 110.8; 356 x 2 heads x 132 23.0 / 14.1) and where a cache is a tile or two per wave (1 x 120 x 16 heads 10.1 / 9.2),
 // else eight (256 x 16 tokens x 2048 58.7 / 67.8, 128 x 4 heads x 2048 38.4 / 43.0).
-// ROCO_BLOCK_FUSED=8, 4, 0: eight waves, four, three kernels (tests run all); so does a number of splits that is asked for.
+// ROCO_BLOCK_FUSED=8, 4, 2, 0: eight waves, four, halves, three kernels (tests run all); so does a number of splits that is asked for.
 template <int HD>
 Launch choose(const BlockArgs& a) {
   if (a.queries > 2 * kQ16) return choose_halves<HD>(a);
@@ -84,11 +87,17 @@ Launch choose(const BlockArgs& a) {
   const Launch eight = one ? shape_for<HD, 8, 1, 4, 8, 16>(a) : shape_for<HD, 8, 2, 4, 8>(a);
   const Launch four = one ? shape_for<HD, 4, 1, 4, 8, 16>(a) : shape_for<HD, 4, 2, 4, 8>(a);
   const char* const asked = getenv("ROCO_BLOCK_FUSED");
-  if (asked != nullptr && *asked != 0) return asked[0] == '8' ? eight : asked[0] == '4' ? four : nullptr;
+  Launch halves = nullptr;
+  if constexpr (HD == 128) {
+    if (!one && a.block > 1 && !a.pol.keeps_last_score() && !a.pol.counts_above_average() && Shape<HD, 4, 1, 16>::takes(half_step(a)))
+      halves = launch_halves<HD, 4, 1, 16>;
+  }
+  if (asked != nullptr && *asked != 0) return asked[0] == '2' ? halves : asked[0] == '8' ? eight : asked[0] == '4' ? four : nullptr;
   if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
   const bool pairs = four != nullptr && (a.units > 256 || a.B <= 256);
-  const int least = HD == 64 ? (a.B <= 2048 ? 0 : 24) : a.B <= 1024 ? 0 : a.B <= 2048 ? 72 : 80;
-  if (a.units < least || (HD == 128 && !one && !pairs && a.units > 256)) return nullptr;
+  if (halves != nullptr && a.B > 1024 && a.queries > 24 && (a.units > 256 || (a.units > 64 && a.units <= 128))) return halves;
+  const int least = HD == 64 ? (a.B <= 2048 ? 0 : 24) : a.B <= 1024 ? 0 : a.B <= 2048 ? (one ? 72 : 65) : 80;
+  if (a.units < least || (HD == 128 && !pairs && a.queries > 24 && a.units > 256)) return nullptr;
   return pairs ? four : eight;
 }
 

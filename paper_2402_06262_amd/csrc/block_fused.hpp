@@ -11,9 +11,10 @@
 //   statistics  the probabilities go to LDS, where the tiles were; every thread adds the rows of its slots, and the next victim is chosen
 //   outputs     V streamed once against the registers.  Probabilities are taken as sums of two bf16 numbers, 16 bits of each: the matrix
 //               cores idle, and rounded to one they made half of the output's error (2.1e-3 against 64 bits, 1.7e-3 so)
-// 33 to 64 rows: two workgroups per unit, each with half of the tokens (HALVES).  Both stream K and V, which one of them finds in
-// their die's L2, and both evict, alike; they leave their sums of probabilities and squares to block_book, which adds them to the
-// statistics and does what depends on or changes the state that both have read (128 units x 2048 x 16 tokens of 4 heads 95 -> 66 us).
+// 33 to 64 rows, and 25 to 32 over more than 1024 slots: two workgroups per unit, each with half of the tokens (HALVES).  Both stream
+// K and V, which one of them finds in their die's L2, and both evict, alike; they leave their sums of probabilities and squares to
+// block_book, which adds them to the statistics and does what depends on or changes the state that both have read (128 units x 2048 x
+// 16 tokens of 4 heads 95 -> 66 us).
 //
 // V is only waited for by the outputs, and nothing waits for them: every other group of eight units streams K before it evicts and V
 // before its statistics, so that on the whole some workgroups use the memory while others rank (512 units x 2048 slots x 16 tokens:
@@ -717,24 +718,24 @@ hipError_t launch(const BlockArgs& a, hipStream_t s) {
   return window ? launch_t<HD, W, NQ, ZT, false, false, true>(a, s) : launch_t<HD, W, NQ, ZT, false, false, false>(a, s);
 }
 
-template <int HD, int ZT, bool STREAMING, bool WINDOW>
+template <int HD, int W, int NQ, int ZT, bool STREAMING, bool WINDOW>
 hipError_t launch_halves_t(const BlockArgs& a, const BlockArgs& half, hipStream_t s) {
-  using S = Shape<HD, 8, 2, ZT>;
+  using S = Shape<HD, W, NQ, ZT>;
   const size_t lds = S::lds(half);
-  const void* fn = reinterpret_cast<const void*>(block_fused<HD, 8, 2, ZT, false, STREAMING, WINDOW, true>);
+  const void* fn = reinterpret_cast<const void*>(block_fused<HD, W, NQ, ZT, false, STREAMING, WINDOW, true>);
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL((block_fused<HD, 8, 2, ZT, false, STREAMING, WINDOW, true>), dim3((a.units + 7) / 8 * 16), dim3(8 * kWave), lds, s, a,
+  hipLaunchKernelGGL((block_fused<HD, W, NQ, ZT, false, STREAMING, WINDOW, true>), dim3((a.units + 7) / 8 * 16), dim3(W * kWave), lds, s, a,
                      S::slots(half, S::v_ahead(half) ? S::kStage : 0), S::v_ahead(half) ? 1 : 0);
   hipLaunchKernelGGL((block_book<kBookThreads>), dim3(a.units), dim3(kBookThreads), key_lds_bytes(a.B), s, a);
   return hipSuccess;
 }
-template <int HD, int ZT>
+template <int HD, int W, int NQ, int ZT>
 hipError_t launch_halves(const BlockArgs& a, hipStream_t s) {
   const BlockArgs half = half_step(a);
   const bool window = a.recency_window > 0;
-  if (a.streaming) return window ? launch_halves_t<HD, ZT, true, true>(a, half, s) : launch_halves_t<HD, ZT, true, false>(a, half, s);
-  return window ? launch_halves_t<HD, ZT, false, true>(a, half, s) : launch_halves_t<HD, ZT, false, false>(a, half, s);
+  if (a.streaming) return window ? launch_halves_t<HD, W, NQ, ZT, true, true>(a, half, s) : launch_halves_t<HD, W, NQ, ZT, true, false>(a, half, s);
+  return window ? launch_halves_t<HD, W, NQ, ZT, false, true>(a, half, s) : launch_halves_t<HD, W, NQ, ZT, false, false>(a, half, s);
 }
 
 }  // namespace fused

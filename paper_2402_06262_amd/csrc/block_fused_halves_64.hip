@@ -3,7 +3,7 @@
 
 namespace roco {
 namespace fused {
-template hipError_t launch_halves<64, 4>(const BlockArgs&, hipStream_t);
-template hipError_t launch_halves<64, 8>(const BlockArgs&, hipStream_t);
+template hipError_t launch_halves<64, 8, 2, 4>(const BlockArgs&, hipStream_t);
+template hipError_t launch_halves<64, 8, 2, 8>(const BlockArgs&, hipStream_t);
 }  // namespace fused
 }  // namespace roco

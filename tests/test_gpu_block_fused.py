@@ -10,7 +10,7 @@ from inputs import round_to_bf16
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(params=["8", "4", "0"], ids=["eight-waves", "four-waves", "three-kernels"])
+@pytest.fixture(params=["8", "4", "2", "0"], ids=["eight-waves", "four-waves", "halves", "three-kernels"])
 def kernels(request, monkeypatch):
     monkeypatch.setenv("ROCO_BLOCK_FUSED", request.param)
     return request.param
@@ -56,7 +56,7 @@ def test_one_kernel_and_three_take_the_same_step(B, block, group, d, monkeypatch
     q = rnd(units, block, group, d).bfloat16()
     k_new, v_new = rnd(units, block, d).bfloat16(), rnd(units, block, d).bfloat16()
     got = {}
-    for path in ("0", "8", "4"):
+    for path in ("0", "8", "4", "2"):
         monkeypatch.setenv("ROCO_BLOCK_FUSED", path)
         c = roco.alloc_cache(p)
         c.K.copy_(K); c.V.copy_(V); c.stats.copy_(stats * live[:, None]); c.pos.copy_(pos); c.n_used.copy_(fills)
@@ -69,7 +69,7 @@ def test_one_kernel_and_three_take_the_same_step(B, block, group, d, monkeypatch
                                    ep, ws)
         torch.cuda.synchronize()
         got[path] = dict(K=c.K, V=c.V, pos=c.pos, n_used=c.n_used, es=es, ep=ep, out=out.float(), stats=c.stats, next=c.next_slot)
-    for path in ("8", "4"):
+    for path in ("8", "4", "2"):
         a, b = got["0"], got[path]
         for name in ("K", "V", "pos", "n_used", "es", "ep"):
             same = torch.equal(a[name], b[name])
