@@ -10,6 +10,8 @@
 //                     pos[], the three statistics planes and n_used.
 //   prefill_gather  : grid (row blocks, units): copies the retained K / V rows into the cache, 16 bytes per
 //                     lane.  Few rows per unit are copied by prefill_select itself.
+#include <cstdlib>
+
 #include "kernels.hpp"
 #include "profile.hpp"
 #include "stream.hpp"
@@ -29,9 +31,8 @@ constexpr int kGatherRows = 64;  // cache rows per gather workgroup
 // when it compacts, and left in the first one's planes; for two shares reading both again is faster.
 // GATHER: the retained K / V rows are copied here too, by way of the list of their positions in LDS (LDS = 2).  One launch less,
 // for units whose rows a compute unit copies in the time that a launch takes: see gathers_in_selection.
-template <int LDS, bool MANY, bool GATHER>
-__global__ __launch_bounds__(kSelThreads, 8) void prefill_select(PrefillArgs a) {
-  constexpr int NT = kSelThreads;
+template <int LDS, bool MANY, bool GATHER, int NT = kSelThreads>
+__global__ __launch_bounds__(NT, 8) void prefill_select(PrefillArgs a) {
   static_assert(LDS == 2 || (!MANY && !GATHER), "the list and the sums replace keys in LDS");
   extern __shared__ __attribute__((aligned(16))) uint32_t lds_keys[];  // [2][L_max] ranking keys when L_max <= kMaxDecodeBudgetLds
   __shared__ __attribute__((aligned(16))) uint32_t sel_sh[SelectLds<1>::kWords];
@@ -339,6 +340,18 @@ hipError_t launch_select_retained(const DecodeArgs& a, int keep, int32_t* mask, 
 // 98.0 and 479 (3) 54.8 / 50.3.
 static bool gathers_in_selection(const PrefillArgs& a) { return 2ll * a.B * a.row_bytes <= 256 << 10; }
 
+// Whether a selection takes 512 threads instead of 1024.  Its searches are then of one digit behind four barriers (see fine_select), and a
+// barrier is one of 8 waves; but a compute unit that has one workgroup then has half of the loads in flight.  Whole calls in us, 1024 / 512:
+// up to 512 tokens 4 units x 256 of fp32 / 64 with output 24.6 / 23.1, 1 x 100 17.9 / 17.2, 300 x 300 of bf16 / 64 39.0 / 35.8, 2000 x 300
+// 166 / 150; longer ones 24 x 966 32.4 / 33.1, 32 x 2048 82.4 / 83.7 (256 threads: 91.0), but where units outnumber the compute units
+// 538 x 738 137.6 / 131.1, 1100 x 1024 364.7 / 356.7, 520 x 2000 550.5 / 545.4; 512 x 3072 1411 / 1416.
+// ROCO_SELECT_THREADS=512, 1024: that many (the tests run both).
+static bool few_threads_select(const PrefillArgs& a) {
+  const char* const asked = getenv("ROCO_SELECT_THREADS");
+  if (asked != nullptr && *asked != 0) return asked[0] == '5';
+  return a.L_max <= 512 || (a.units > 256 && a.L_max <= 2048);
+}
+
 hipError_t launch_prefill_select_compact(int dtype, int head_dim, PrefillArgs a, hipStream_t s) {
   const int row_bytes = head_dim * (dtype == kBF16 ? 2 : 4);
   a.row_bytes = row_bytes;
@@ -347,10 +360,16 @@ hipError_t launch_prefill_select_compact(int dtype, int head_dim, PrefillArgs a,
     ProfScope ps(kProfPrefillSelect, s);
     const size_t key_lds = key_lds_bytes(a.L_max);
     if (key_lds != 0) {
-      const auto kernel = gathered ? (a.shares_to_add > 2 ? prefill_select<2, true, true> : prefill_select<2, false, true>)
-                                   : (a.shares_to_add > 2 ? prefill_select<2, true, false> : prefill_select<2, false, false>);
-      if (!allow_key_lds(reinterpret_cast<const void*>(kernel), key_lds)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(kernel, dim3(a.units), dim3(kSelThreads), key_lds, s, a);
+      const auto launch = [&](auto threads) {
+        constexpr int NT = decltype(threads)::value;
+        const auto kernel = gathered ? (a.shares_to_add > 2 ? prefill_select<2, true, true, NT> : prefill_select<2, false, true, NT>)
+                                     : (a.shares_to_add > 2 ? prefill_select<2, true, false, NT> : prefill_select<2, false, false, NT>);
+        if (!allow_key_lds(reinterpret_cast<const void*>(kernel), key_lds)) return false;
+        hipLaunchKernelGGL(kernel, dim3(a.units), dim3(NT), key_lds, s, a);
+        return true;
+      };
+      const bool launched = few_threads_select(a) ? launch(std::integral_constant<int, 512>{}) : launch(std::integral_constant<int, kSelThreads>{});
+      if (!launched) return hipErrorInvalidValue;
     } else if (a.L_max <= 2 * kMaxDecodeBudgetLds) {  // one key per token still fits (40 units x 32768 tokens: 125 us against 200)
       const size_t one = static_cast<size_t>(a.L_max) * sizeof(uint32_t);
       if (!allow_key_lds(reinterpret_cast<const void*>(prefill_select<1, false, false>), one)) return hipErrorInvalidValue;

@@ -192,3 +192,20 @@ def test_waves_that_share_a_row(dtype, d, waves, monkeypatch):
         g = P.gpu_prefill(sess, Q, K, V, lens, True)
         for u in range(len(lens)):
             P.check_prefill_unit(g, u, Q[u], K[u], V[u], lens[u], B, s, sc, dtype, window, 0.5 if window else 0.0)
+
+
+@pytest.mark.parametrize("threads", ["512", "1024"])
+@pytest.mark.parametrize("dtype,d,B", [("f32", 64, 40), ("bf16", 64, 512), ("bf16", 128, 513), ("f32", 128, 600)])
+def test_threads_of_the_selection(dtype, d, B, threads, monkeypatch):
+    """Prompts that end before, at and behind the rounds of 512 and 1024 positions; rows copied by the selection and behind it."""
+    monkeypatch.setenv("ROCO_SELECT_THREADS", threads)
+    P, rng = TP._parity(), np.random.default_rng(d + B)
+    lens = [1, 64, 511, 512, 513, 1023, 1024, 1025, 1030]
+    L, s, sc = max(lens), max(1, B // 8), 1.0 / math.sqrt(d)
+    Q, K, V = (rng.standard_normal((len(lens), L, d)).astype(np.float32) for _ in range(3))
+    if dtype == "bf16":
+        Q, K, V = round_to_bf16(Q), round_to_bf16(K), round_to_bf16(V)
+    sess = P.make_session(len(lens), d, B, s, dtype, 0.0, 0, 0.0)
+    g = P.gpu_prefill(sess, Q, K, V, lens, True)
+    for u in range(len(lens)):
+        P.check_prefill_unit(g, u, Q[u], K[u], V[u], lens[u], B, s, sc, dtype, 0, 0.0)
