@@ -9,7 +9,7 @@
 //   eviction    of several tokens (take_slots); before K or after it
 //   normalisers the waves' maxima, then sums, through LDS; the registers then hold probabilities
 //   statistics  the probabilities go to LDS, where the tiles were; every thread adds the rows of its slots, and the next victim is chosen
-//   outputs     V streamed once against the registers.  Probabilities are taken as sums of two bf16 numbers, 16 bits of each: the matrix
+//   outputs     V streamed once against the registers.  Probabilities are taken as sums of two bf16 numbers (split_positive): the matrix
 //               cores idle, and rounded to one they made half of the output's error (2.1e-3 against 64 bits, 1.7e-3 so)
 // 33 to 64 rows, and 25 to 32 over more than 1024 slots: two workgroups per unit, each with half of the tokens (HALVES).  Both stream
 // K and V, which one of them finds in their die's L2, and both evict, alike; they leave their sums of probabilities and squares to
@@ -80,6 +80,25 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   float r;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
+}
+
+// Eight probabilities as sums of two bf16 numbers, to within 2^-16 of each.  Both are above zero where the probability is: the first is the
+// largest bf16 number below it, the second at least the smallest of all.  So an infinite value keeps its sign in both products; rounded
+// to the nearest, half of the remainders are zero or negative, and inf - inf or 0 inf is NaN.
+__device__ __forceinline__ void split_positive(const f32x4 (&p)[2], uint4& hi, uint4& lo) {
+  uint32_t h[8];
+  bf16x8 l;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t bits = __float_as_uint(p[e >> 2][e & 3]);
+    const uint32_t least = min(bits, 0x10000u);  // of a nonzero number; (fp32 has bf16's exponents)
+    const uint32_t below = (max(bits, 1u) - 1u) & 0xffff0000u;
+    h[e] = max(below, least);
+    l[e] = static_cast<__bf16>(__uint_as_float(max(__float_as_uint(p[e >> 2][e & 3] - __uint_as_float(below)), least)));
+  }
+  const auto upper = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); };  // the upper halves of both
+  hi = make_uint4(upper(h[0], h[1]), upper(h[2], h[3]), upper(h[4], h[5]), upper(h[6], h[7]));
+  lo = __builtin_bit_cast(uint4, l);
 }
 
 // Where half `h` of a unit's tokens leaves its sums of probabilities and, behind them, of their squares.
@@ -540,19 +559,9 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
           }
         }
       }
-      uint4 p_hi[NQ], p_lo[NQ];  // the probabilities as sums of two bf16 numbers: 16 bits of each
+      uint4 p_hi[NQ], p_lo[NQ];
 #pragma unroll
-      for (int t2 = 0; t2 < NQ; ++t2) {
-        bf16x8 hi, lo;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float p = x[t2][e >> 2][e & 3];
-          hi[e] = static_cast<__bf16>(p);
-          lo[e] = static_cast<__bf16>(p - static_cast<float>(hi[e]));
-        }
-        p_hi[t2] = __builtin_bit_cast(uint4, hi);
-        p_lo[t2] = __builtin_bit_cast(uint4, lo);
-      }
+      for (int t2 = 0; t2 < NQ; ++t2) split_positive(x[t2], p_hi[t2], p_lo[t2]);
       if (t + 1 < mine) wait_loads<kTileLoads>();
       else wait_loads<0>();
       if (SINGLE) put_row(a.v_new, Vb, tile, fresh - sb, R::swizzle_v(fresh - sb));
