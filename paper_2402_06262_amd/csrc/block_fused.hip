@@ -46,8 +46,9 @@ Launch shape_for(const BlockArgs& a) {
 // is long enough.  Against the three kernels, us per step, bf16 / 128: 128 units x 2048 slots x 16 tokens of 4 heads 95 / 64, 48 x 1024
 // x 16 of 4 53 / 37, 4 x 476 x 48 39.9 / 34.1, 7 x 1804 x 19 of 2 48.0 / 46.6; two rounds: 160 x 1024 x 10 of 4 74 / 67, 256 x 1536 x
 // 16 of 4 115 / 101, but 176 x 584 x 41 66 / 68, 140 x 248 x 46 53 / 57; more: 512 x 1536 x 10 of 4 166 / 175, 423 x 244 x 61 77 / 125.
-// bf16 / 64, whose three kernels do not use the matrix cores: 127 x 836 x 40 103 / 35, 254 x 132 x 25 of 2 60 / 44, 724 x 1240 x 12 of
-// 4 488 / 170, 827 x 232 x 44 156 / 150, but 878 x 144 x 46 133 / 151, 758 x 104 x 46 95 / 124.
+// bf16 / 64, whose three kernels do not use the matrix cores: 128 x 96 x 48 39.2 / 27.5, 180 x 132 x 33 52.9 / 43.7, 256 x 160 x 64 66.3 /
+// 56.6, 256 x 96 x 12 of 4 39.2 / 34.0, 400 x 260 x 64 126 / 108, 800 x 224 x 33 147 / 136; but up to 128 slots 180 x 64 x 48 36.9 / 47.9,
+// 256 x 128 x 33 39.9 / 40.9, and 878 x 144 x 46 133 / 151, 758 x 104 x 46 95 / 124.
 template <int HD>
 Launch choose_halves(const BlockArgs& a) {
   const BlockArgs half = half_step(a);
@@ -58,7 +59,7 @@ Launch choose_halves(const BlockArgs& a) {
   const char* const asked = getenv("ROCO_BLOCK_FUSED");
   if (asked != nullptr && *asked != 0) return asked[0] == '0' ? nullptr : two;
   if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
-  if (HD == 64) return a.units <= 256 || a.B >= 224 ? two : nullptr;
+  if (HD == 64) return a.units <= 128 || (a.units <= 256 && (a.B > 128 || a.heads >= 4)) || a.B >= 224 ? two : nullptr;
   return a.units <= 128 || (a.units <= 256 && a.B > 768) ? two : nullptr;
 }
 
@@ -73,9 +74,11 @@ Launch choose_halves(const BlockArgs& a) {
 //   Above 24 rows, where eight waves' workgroups do not fill a round or do not fit it, half of the tokens in each of two workgroups of
 //   four waves (three kernels / eight waves / halves): 65 x 2048 x 32 69 / 70 / 60, 97 x 1628 x 32 74 / 67 / 57, 264 x 1536 x 32 115 / 123 /
 //   109, 512 x 2048 x 32 184 / 170 / 168, 697 x 1792 x 32 264 / 231 / 220; but 140 x 1352 x 6 of 4 66 / 49 / 54, 400 x 1960 x 17 143 / 132 / 144.
-// bf16 / 64, half of the bytes: B <= 2048 always (3 units x 1656 slots x 2 heads 19.7 / 16.8, 2 x 1764 x 22 tokens 37.7 / 36.3, 171 x 992 x
-//   16 heads 46.7 / 17.9, 518 x 1904 x 20 rows 302 / 125), B <= 4096 from 24 units on (17 x 3632 x 8 rows 43.0 / 45.7, 26 x 3580 x 3
-//   tokens 42.0 / 41.6, 128 x 3500 x 8 heads 70.5 / 39.4).
+// bf16 / 64, half of the bytes: B <= 2048 always (10 units x 1508 slots x 4 heads 19.0 / 17.0, 1 x 1800 x 24 tokens 44.0 / 42.7, 171 x 992 x
+//   16 heads 46.7 / 17.9), but for more than 24 rows of more than 1536 slots on few units (1 x 2048 x 32 48.7 / 52.4, 12 x 1800 x 32 51.5 /
+//   52.2, 24 x 2048 x 32 56.8 / 53.5).  B <= 4096 from 40 units on (24 x 4096 x 4 heads 31.1 / 33.5, 32 x 3000 x 4 tokens 39.2 / 39.7,
+//   44 x 3000 x 4 heads 34.2 / 29.4, 44 x 2052 x 4 tokens 36.5 / 34.4, 110 x 4096 x 8 heads 72.7 / 35.6), of single tokens of 8 and more
+//   heads from 24 on (24 x 3000 x 8 29.6 / 29.0, x 16 37.1 / 29.5).
 // Four waves, two workgroups to a compute unit, where the units are more than the compute units (512 x 16 tokens x 2048 with eight
 // 119.7, with four 110.8; 356 x 2 heads x 132 23.0 / 14.1) and where a cache is a tile or two per wave (1 x 120 x 16 heads 10.1 / 9.2),
 // else eight (256 x 16 tokens x 2048 58.7 / 67.8, 128 x 4 heads x 2048 38.4 / 43.0).
@@ -96,7 +99,8 @@ Launch choose(const BlockArgs& a) {
   if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
   const bool pairs = four != nullptr && (a.units > 256 || a.B <= 256);
   if (halves != nullptr && a.B > 1024 && a.queries > 24 && (a.units > 256 || (a.units > 64 && a.units <= 128))) return halves;
-  const int least = HD == 64 ? (a.B <= 2048 ? 0 : 24) : a.B <= 1024 ? 0 : a.B <= 2048 ? (one ? 72 : 65) : 80;
+  const int least = HD == 64 ? (a.B > 2048 ? (a.block == 1 && a.queries >= 8 ? 24 : 40) : a.B > 1536 && a.queries > 24 ? 24 : 0)
+                             : a.B <= 1024 ? 0 : a.B <= 2048 ? (one ? 72 : 65) : 80;
   if (a.units < least || (HD == 128 && !pairs && a.queries > 24 && a.units > 256)) return nullptr;
   return pairs ? four : eight;
 }

@@ -9,8 +9,9 @@
 //   eviction    of several tokens (take_slots); before K or after it
 //   normalisers the waves' maxima, then sums, through LDS; the registers then hold probabilities
 //   statistics  the probabilities go to LDS, where the tiles were; every thread adds the rows of its slots, and the next victim is chosen
-//   outputs     V streamed once against the registers.  Probabilities are taken as sums of two bf16 numbers (split_positive): the matrix
-//               cores idle, and rounded to one they made half of the output's error (2.1e-3 against 64 bits, 1.7e-3 so)
+//   outputs     V streamed once against the registers.  Probabilities are taken as sums of bf16 numbers (split_positive): the matrix
+//               cores idle.  Two for head_dim 128, where rounded to one they made half of the output's error (2.1e-3 against 64 bits,
+//               1.7e-3 so); three for head_dim 64, whose three kernels multiply all 24 bits on the vector ALUs
 // 33 to 64 rows, and 25 to 32 over more than 1024 slots: two workgroups per unit, each with half of the tokens (HALVES).  Both stream
 // K and V, which one of them finds in their die's L2, and both evict, alike; they leave their sums of probabilities and squares to
 // block_book, which adds them to the statistics and does what depends on or changes the state that both have read (128 units x 2048 x
@@ -61,6 +62,7 @@ template <int HD> struct Rows {
   static constexpr int kLoads = kTile / 1024;             // wave-wide loads of a tile
   static constexpr int kSteps = HD / 32, kBlocks = HD / 16;  // of the matrix instruction: k-steps of a score, blocks of dimensions
   static constexpr int kOut = HD + 4;                     // floats per row of a wave's output in LDS
+  static constexpr int kPlanes = HD == 128 ? 2 : 3;       // bf16 numbers of a probability
   // K chunk c of row r lies in slot c ^ swizzle_k(r), V chunk c in slot c ^ swizzle_v(r): 16 lanes that read a chunk of K of 16 rows,
   // and 32 that read 32 bytes of V of 8 rows, fall on distinct banks (256 bytes: two rows of 64 elements, one of 128).
   static __device__ __forceinline__ int swizzle_k(int r) { return HD == 128 ? r & 15 : (r >> 1) & 7; }
@@ -82,23 +84,37 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   return r;
 }
 
-// Eight probabilities as sums of two bf16 numbers, to within 2^-16 of each.  Both are above zero where the probability is: the first is the
-// largest bf16 number below it, the second at least the smallest of all.  So an infinite value keeps its sign in both products; rounded
-// to the nearest, half of the remainders are zero or negative, and inf - inf or 0 inf is NaN.
-__device__ __forceinline__ void split_positive(const f32x4 (&p)[2], uint4& hi, uint4& lo) {
-  uint32_t h[8];
-  bf16x8 l;
+// Eight probabilities as sums of N bf16 numbers: to within 2^-16 of each for two of them, exactly for three (but for bits below 2^-133).
+// All of them are above zero where the probability is: each but the last is the largest bf16 number below what those before it leave
+// over, the last at least the smallest of all.  So an infinite value keeps its sign in every product; rounded to the nearest, half of
+// the remainders are zero or negative, and inf - inf or 0 inf is NaN.
+template <int N>
+__device__ __forceinline__ void split_positive(const f32x4 (&p)[2], uint4 (&planes)[N]) {
+  uint32_t word[N][8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const uint32_t bits = __float_as_uint(p[e >> 2][e & 3]);
-    const uint32_t least = min(bits, 0x10000u);  // of a nonzero number; (fp32 has bf16's exponents)
-    const uint32_t below = (max(bits, 1u) - 1u) & 0xffff0000u;
-    h[e] = max(below, least);
-    l[e] = static_cast<__bf16>(__uint_as_float(max(__float_as_uint(p[e >> 2][e & 3] - __uint_as_float(below)), least)));
+    float left = p[e >> 2][e & 3];
+    const uint32_t least = min(__float_as_uint(left), 0x10000u);  // of a nonzero number; (fp32 has bf16's exponents)
+#pragma unroll
+    for (int i = 0; i < N - 1; ++i) {
+      const uint32_t below = (max(__float_as_uint(left), 1u) - 1u) & 0xffff0000u;
+      left -= __uint_as_float(below);
+      word[i][e] = max(below, least);
+    }
+    word[N - 1][e] = max(__float_as_uint(left), least);
   }
-  const auto upper = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); };  // the upper halves of both
-  hi = make_uint4(upper(h[0], h[1]), upper(h[2], h[3]), upper(h[4], h[5]), upper(h[6], h[7]));
-  lo = __builtin_bit_cast(uint4, l);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (N == 2 && i == 1) {
+      bf16x8 r;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) r[e] = static_cast<__bf16>(__uint_as_float(word[i][e]));
+      planes[i] = __builtin_bit_cast(uint4, r);
+    } else {  // bf16 numbers already: the upper halves of the words
+      const auto pair = [&](int e) { return __builtin_amdgcn_perm(word[i][e + 1], word[i][e], 0x07060302u); };
+      planes[i] = make_uint4(pair(0), pair(2), pair(4), pair(6));
+    }
+  }
 }
 
 // Where half `h` of a unit's tokens leaves its sums of probabilities and, behind them, of their squares.
@@ -559,9 +575,9 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
           }
         }
       }
-      uint4 p_hi[NQ], p_lo[NQ];
+      uint4 p[NQ][R::kPlanes];
 #pragma unroll
-      for (int t2 = 0; t2 < NQ; ++t2) split_positive(x[t2], p_hi[t2], p_lo[t2]);
+      for (int t2 = 0; t2 < NQ; ++t2) split_positive(x[t2], p[t2]);
       if (t + 1 < mine) wait_loads<kTileLoads>();
       else wait_loads<0>();
       if (SINGLE) put_row(a.v_new, Vb, tile, fresh - sb, R::swizzle_v(fresh - sb));
@@ -571,7 +587,9 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
         const uint2 lo = lds_read_transposed(vt), hi = lds_read_transposed(vt + 16 * kRowBytes);
         const uint4 vf = make_uint4(lo.x, lo.y, hi.x, hi.y);
 #pragma unroll
-        for (int t2 = 0; t2 < NQ; ++t2) o[t2][db] = mfma16(vf, p_hi[t2], mfma16(vf, p_lo[t2], o[t2][db]));
+        for (int i = R::kPlanes - 1; i >= 0; --i)
+#pragma unroll
+          for (int t2 = 0; t2 < NQ; ++t2) o[t2][db] = mfma16(vf, p[t2][i], o[t2][db]);
       }
       reads_done();
       if (t + 2 < mine) request_v(t + 2);

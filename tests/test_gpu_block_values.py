@@ -1,4 +1,5 @@
-"""Block and grouped steps of bf16 on values that are not finite."""
+"""Block and grouped steps of bf16 on values that show what a probability is multiplied as: infinities, and differences far below the
+precision of a bf16 number."""
 import pytest
 import torch
 
@@ -34,6 +35,15 @@ def _step(d, K, V, q, k_new, v_new, importance, scope_kind):
     return out.float(), c
 
 
+def _reference(c, q, block):
+    """Outputs in 64 bits from the rows that the step has left in the cache: query i sees the block's tokens 0..i."""
+    units, B, d = c.K.shape
+    x = torch.einsum("utgd,ubd->utgb", q.double().cpu(), c.K.double().cpu()) / d ** 0.5
+    tok = (c.pos.cpu() - B)[:, None, None, :]  # of the block's tokens; negative: an older one
+    seen = tok <= torch.arange(block)[None, :, None, None]
+    return torch.softmax(x.masked_fill(~seen, float("-inf")), dim=-1), seen
+
+
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("B,block,group", [(192, 1, 4), (1024, 5, 3), (2048, 16, 1), (2048, 1, 8), (512, 32, 1), (1100, 27, 1), (1536, 16, 4)])
 def test_infinite_values_stay_infinite(B, block, group, d, kernels):
@@ -64,3 +74,25 @@ def test_infinite_values_stay_infinite(B, block, group, d, kernels):
     same = torch.where(want == 0, torch.isfinite(out), (out == want) | (torch.isnan(out) & torch.isnan(want)))
     bad = (~same).nonzero()
     assert bad.numel() == 0, (bad[:8].tolist(), out[tuple(bad[0].tolist())].item(), len(bad))
+
+
+@pytest.mark.parametrize("B,block,group", [(256, 16, 1), (1024, 1, 5), (2048, 4, 4), (256, 30, 1), (1536, 13, 4)])
+def test_probabilities_of_head_dim_64_keep_their_bits(B, block, group, kernels):
+    """Neighbouring slots differ by 2^-12 in their logits and have values of 1 and -1: an output is the difference of two
+    probabilities, 2^-12 of them.  Logits of up to 8 round by 2^-22.5 of a probability, exponentials by 2^-23, each twice: 2^-8.8 of
+    the difference, and bf16 rounds it by 2^-9; held to the double of the sum.  (16 bits of the probabilities: 0.06, 8 bits: 30.)"""
+    units, d = 17, 64
+    g = torch.Generator(device="cuda").manual_seed(B + block)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda").bfloat16()
+    K, V = rnd(units, B, d), torch.zeros((units, B, d), device="cuda").bfloat16()
+    q, k_new, v_new = rnd(units, block, group, d), rnd(units, block, d), torch.zeros((units, block, d), device="cuda").bfloat16()
+    q[..., 0] = 0.25
+    K[:, 1::2] = K[:, 0::2]
+    K[:, 0::2, 0], K[:, 1::2, 0] = 1.0, 1.0 + 2.0 ** -7
+    for i in range(d):
+        V[:, 64 + 2 * i, i], V[:, 65 + 2 * i, i] = 1.0, -1.0
+    out, c = _step(d, K, V, q, k_new, v_new, 2, 2)
+    prob, _ = _reference(c, q, block)
+    want = torch.einsum("utgb,ubd->utgd", prob, c.V.double().cpu())
+    worst = ((out.double().cpu() - want).abs() / want.abs()).max().item()
+    assert worst <= 2.0 ** -7, worst
