@@ -47,8 +47,9 @@ Launch shape_for(const BlockArgs& a) {
 // x 16 of 4 53 / 37, 4 x 476 x 48 39.9 / 34.1, 7 x 1804 x 19 of 2 48.0 / 46.6.  Two rounds, above 768 slots: 256 x 1300 x 16 of 4 107 / 80,
 // 130 x 2048 x 32 of 2 103.1 / 103.0, 256 x 2048 x 32 of 2 136 / 130; tokens of one head have twice the sums to add, and the three kernels
 // fill their rounds badly with the three splits that 171 to 240 units get (180 x 2048 x 33 105 / 95, 220 x 1536 x 64 123 / 103) but well
-// beside them (150 x 1536 x 48 86 / 90, 161 x 1100 x 64 88 / 91, 256 x 780 x 33 60.6 / 65.6, 256 x 2048 x 64 138 / 143; 256 x 2048 x 17 of 2 111 / 115); up to 768 slots 176 x 584 x 41 66 / 68,
-// 140 x 248 x 46 53 / 57; more rounds: 512 x 1536 x 10 of 4 166 / 175, 423 x 244 x 61 77 / 125.
+// beside them (150 x 1536 x 48 86 / 90, 161 x 1100 x 64 88 / 91, 256 x 780 x 33 60.6 / 65.6, 256 x 2048 x 64 138 / 143; 256 x 2048 x 17
+// of 2 111 / 115); up to 768 slots 176 x 584 x 41 66 / 68, 140 x 248 x 46 53 / 57; more rounds: 512 x 1536 x 10 of 4 166 / 175, 423 x 244
+// x 61 77 / 125.
 // bf16 / 64, whose three kernels do not use the matrix cores: 128 x 96 x 48 39.2 / 27.5, 180 x 132 x 33 52.9 / 43.7, 256 x 160 x 64 66.3 /
 // 56.6, 256 x 96 x 12 of 4 39.2 / 34.0, 400 x 260 x 64 126 / 108, 800 x 224 x 33 147 / 136; but up to 128 slots 180 x 64 x 48 36.9 / 47.9,
 // 256 x 128 x 33 39.9 / 40.9, and 878 x 144 x 46 133 / 151, 758 x 104 x 46 95 / 124.

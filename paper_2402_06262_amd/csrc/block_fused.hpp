@@ -405,17 +405,21 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
     if (g == 0) l_s[wave][kQ16 * t2 + qi] = l;
   }
   __syncthreads();
+  bool odd = false;  // one of the lane's rows is NaN
 #pragma unroll
   for (int t2 = 0; t2 < NQ; ++t2) {
     float L = 0.0f;
 #pragma unroll
     for (int i = 0; i < W; ++i) L += l_s[i][kQ16 * t2 + qi];
+    odd = odd || !(L < INFINITY);
     const float inv = 1.0f / L;
 #pragma unroll
     for (int i = 0; i < ZT; ++i)
 #pragma unroll
       for (int h = 0; h < 2; ++h) z[i][t2][h] *= inv;
   }
+
+  const bool odd_rows = !SINGLE && __builtin_amdgcn_ballot_w64(odd) != 0;  // (every wave has all rows)
 
   auto statistics = [&]() {
     // ---- statistics: every slot receives, per block token that attended it, the head-mean of the probabilities
@@ -446,6 +450,14 @@ __global__ __launch_bounds__(W * kWave, 2) void block_fused(BlockArgs a, int lds
         }
       }
       __syncthreads();
+      if (odd_rows) {  // what a row of NaN did not attend is not NaN (asked here, not at every addition: 512 x 16 tokens x 2048 112 us, 109 so)
+#pragma unroll 1
+        for (int i = tid; i < nq * a.block; i += NT) {
+          const int q = i / a.block, tok = i % a.block, slot = slot_of[tok] - c0;
+          if (tok > tok0 + q / heads && static_cast<unsigned>(slot) < static_cast<unsigned>(lds_slots)) pl[static_cast<size_t>(q) * prow + slot] = 0.0f;
+        }
+        __syncthreads();
+      }
       const int j = c0 + tid * 4;
       const float4 b1 = a1, b2 = a2, bc = cc;
       if (!HALVES) load_stats(c0 + lds_slots);

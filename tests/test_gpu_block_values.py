@@ -1,5 +1,5 @@
-"""Block and grouped steps of bf16 on values that show what a probability is multiplied as: infinities, and differences far below the
-precision of a bf16 number."""
+"""Block and grouped steps of bf16 on values that show what a probability is multiplied as: infinities, differences far below the
+precision of a bf16 number, and queries of NaN."""
 import pytest
 import torch
 
@@ -96,3 +96,27 @@ def test_probabilities_of_head_dim_64_keep_their_bits(B, block, group, kernels):
     want = torch.einsum("utgb,ubd->utgd", prob, c.V.double().cpu())
     worst = ((out.double().cpu() - want).abs() / want.abs()).max().item()
     assert worst <= 2.0 ** -7, worst
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("B,block,group", [(256, 16, 1), (1024, 5, 3), (2048, 16, 1), (2048, 27, 1), (1024, 16, 4), (2048, 40, 1)])
+def test_a_query_of_nan_leaves_later_tokens_alone(B, block, group, d, kernels):
+    """The statistics of a block's tokens behind a query of NaN, which does not see them, come from the queries that do."""
+    units, at = 17, block // 2
+    g = torch.Generator(device="cuda").manual_seed(B + block)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda").bfloat16()
+    K, V, q = rnd(units, B, d), rnd(units, B, d), rnd(units, block, group, d)
+    q[:, at] = float("nan")
+    out, c = _step(d, K, V, q, rnd(units, block, d), rnd(units, block, d), 2, 2)
+    tok = c.pos - B
+    later = tok > at
+    assert (later.sum(1) == block - 1 - at).all()
+    prob, seen = _reference(c, q, block)
+    mean = torch.where(seen, prob, 0.0).mean(2)  # [units, block, B] of the heads
+    for plane, want in ((0, mean), (1, mean ** 2)):
+        want = torch.where(tok.cpu()[:, None] <= torch.arange(block)[None, :, None], want, 0.0).sum(1)
+        got = c.stats[:, plane].double().cpu()
+        rel = ((got - want).abs() / want.abs().clamp_min(1e-6))[later.cpu()]
+        assert torch.isfinite(got[later.cpu()]).all(), plane
+        assert rel.max().item() <= 1e-4
+    assert torch.isnan(c.stats[:, 0][~later & (tok < at)]).all() and torch.isnan(out[:, at]).all() and torch.isfinite(out[:, :at]).all()
