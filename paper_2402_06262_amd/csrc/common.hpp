@@ -207,10 +207,9 @@ constexpr int kSelectBins = 2048;
 constexpr int kSelectRanked = 128;
 template <int PER_WORD> struct SelectLds {
   static constexpr int kBinWords = kSelectBins / PER_WORD;
-  static constexpr int kWords = kBinWords + (PER_WORD == 2 ? kSelectRanked : 16) + 8;  // (what fine_select needs is in both)
+  static constexpr int kWords = kBinWords + 16 + 8;
 };
 static_assert(kSelectRanked == 2 * kWave, "two candidates per lane");
-
 
 // f(key) for every key of this thread, in no particular order.
 template <int NT, int AHEAD, class KeyFn, class F>
@@ -422,11 +421,14 @@ __device__ __forceinline__ bool count_k_smallest(KeyFn key_of, int n, uint32_t k
 // False if the k-th smallest key lies outside or among more than kSelectRanked candidates: then the search above has to find it.
 constexpr int kFineBins = 2048, kFineShift = 18;
 constexpr uint32_t kFineFrom = (127u - 52u) << 23;
-static_assert(kFineBins / 2 + kSelectRanked + 4 <= SelectLds<2>::kWords, "the bins, the candidates and four words");
-template <int NT, int AHEAD, class KeyFn>
+template <int NT, int PER_WORD, int AHEAD, class KeyFn>
 __device__ __forceinline__ bool fine_select(KeyFn key_of, int n, uint32_t k, uint32_t* sh, uint32_t& kth, uint32_t& n_less, uint32_t& n_equal) {
-  uint32_t* const list = sh + kFineBins / 2;
-  uint32_t* const res = list + kSelectRanked;  // candidates gathered; the key, keys below it, keys equal to it
+  // The candidates have words of their own where bins of a word each leave them; else they take bins that have been read, behind one
+  // barrier more: with words of their own the one-kernel decode step would lose its third workgroup at the largest budgets.
+  constexpr bool kOwnWords = kFineBins / 2 + 4 + kSelectRanked <= SelectLds<PER_WORD>::kWords;
+  uint32_t* const res = sh + kFineBins / 2;  // candidates gathered; the key, keys below it, keys equal to it
+  uint32_t* const list = kOwnWords ? res + 4 : sh;
+  static_assert(kFineBins / 2 + 4 <= SelectLds<PER_WORD>::kWords && kSelectRanked <= kFineBins / 2, "the bins and four words");
   const int tid = late_thread_id(), lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   auto bin_of = [](uint32_t key) { return min((max(key, kFineFrom) - kFineFrom) >> kFineShift, static_cast<uint32_t>(kFineBins - 1)); };
   __syncthreads();  // `sh` may still be in use by a previous call
@@ -459,6 +461,7 @@ __device__ __forceinline__ bool fine_select(KeyFn key_of, int n, uint32_t k, uin
   less += __builtin_amdgcn_readlane(inside, off) - cand;
   const uint32_t bin = static_cast<uint32_t>(32 * owner + off);
   if (bin == 0 || bin == kFineBins - 1 || cand > kSelectRanked) return false;
+  if (!kOwnWords) __syncthreads();  // every wave has read the bins
   for_each_key<NT, AHEAD>(key_of, n, tid, [&](uint32_t key) {
     if (bin_of(key) == bin && key != 0xffffffffu) list[atomicAdd(&res[0], 1u)] = key;
   });
@@ -509,7 +512,7 @@ __device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint
     const uint32_t kth = r.kth;
     uint32_t found, n_less, n_equal;
     bool done = false;
-    if constexpr (NT <= 512) done = round == 0 && !small && n <= 65535 && fine_select<NT, AHEAD>(key_of, n, take, sh, found, n_less, n_equal);
+    if constexpr (NT <= 512) done = round == 0 && !small && n <= 65535 && fine_select<NT, PER_WORD, AHEAD>(key_of, n, take, sh, found, n_less, n_equal);
     if (!done)
       radix_select<NT, PER_WORD, AHEAD>(
           [&](int i) {

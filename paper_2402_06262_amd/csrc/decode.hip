@@ -337,7 +337,7 @@ __global__ __launch_bounds__(NT) void decode_finish(DecodeArgs a) {
 // to global memory and no second launch is needed; the price is that a workgroup's selection phase does not
 // stream, so this shape is used when there are at least about two units per compute unit to overlap with.
 // With non-temporal loads a third workgroup fits a compute unit: 168 registers (but for biased bf16) and the keys and logits
-// of up to 4096 slots beside 4.2 KiB of static LDS.  Hence the late thread index behind the stream and two bins per word in
+// of up to 4096 slots beside 4.2 KiB of static LDS, in units of 1280 bytes.  Hence the late thread index behind the stream and two bins per word in
 // the search (600 units x 1023 slots of bf16 / 128: 60.5 us, with a register too many 64.6; 600 x 3854 of bf16 / 64: 122 us,
 // with one bin per word 131).
 template <int DT, int D, int U, bool BIAS, bool STREAMING>
@@ -352,6 +352,8 @@ __global__ __launch_bounds__(kFusedThreads) void decode_fused(DecodeArgs a) {
   // a wave's words: the new token's rows while it streams, then its sums; the output is done before the search begins
   using New = NewRows<DT, D>;
   static_assert(New::kWords >= D && WAVES * New::kWords <= SelectLds<2>::kWords, "the waves' rows and sums fit the search's words");
+  constexpr int kLds = 12 * kMaxFusedBudget + SelectLds<2>::kWords * 4 + WAVES * 16, kLdsUnit = 1280;
+  static_assert(3 * ((kLds + kLdsUnit - 1) / kLdsUnit * kLdsUnit) <= 160 << 10, "three workgroups of the largest budget");
   float* const sm_acc = reinterpret_cast<float*>(sel_sh);
 
   const int u = blockIdx.x;
