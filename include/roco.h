@@ -398,7 +398,8 @@ int roco_probe_mfma(int32_t workgroups, int32_t iters, int32_t operands, float* 
  *                              below, 512 / units and 24 at most, or 256 / units with more than 16 query rows of fp32 /
  *                              head_dim 128; bf16 / head_dim 128: 8 at most, or up to 16 of at least 256 slots with up to 16
  *                              query rows and 256 / units; no split has more than 2^22 slots)
- *   ROCO_BLOCK_SINGLE=0        single-token block steps go through the preparing kernel like longer blocks
+ *   ROCO_BLOCK_SINGLE=0        single-token block steps go through the preparing kernel like longer blocks (bf16 too, whatever
+ *                              ROCO_BLOCK_FUSED says)
  */
 
 /* Static description of a return code. */

@@ -916,7 +916,8 @@ hipError_t launch_block(int dtype, int head_dim, const BlockArgs& args, hipStrea
     return hipErrorInvalidValue;
   const bool mfma_path = dtype == kBF16 && head_dim == 128;
   hipError_t fused;
-  if (dtype == kBF16 && launch_block_fused(head_dim, a, s, fused)) return fused != hipSuccess ? fused : hipGetLastError();
+  const bool prepared = a.block == 1 && !a.single;  // is asked for
+  if (dtype == kBF16 && !prepared && launch_block_fused(head_dim, a, s, fused)) return fused != hipSuccess ? fused : hipGetLastError();
   if (!a.single) {
     ProfScope ps(kProfBlockPrepare, s);
     // Two 1024-thread workgroups do not run side by side on a compute unit here (measured: the second half of 512

@@ -88,3 +88,44 @@ def test_one_kernel_and_three_take_the_same_step(B, block, group, d, monkeypatch
         assert torch.equal(b["next"] >= 0, full), path
         differ = (a["next"] != b["next"]).sum().item()
         assert differ <= 1, (path, "next victim", a["next"], b["next"])
+
+
+def _launches(run):
+    """How often `run` launches the preparing, the attention and the finishing kernel of a block step."""
+    import paper_2402_06262_amd as roco
+    counts = []
+    for kernel in (8, 9, 10):  # ROCO_PROF_BLOCK_PREPARE, _ATTEND, _FINISH
+        roco.roco_profile_kernel(kernel)
+        try:
+            run()
+            counts.append(roco.roco_profile_read()[1])
+        finally:
+            roco.roco_profile_kernel(-1)
+    return counts
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("block,group,default,prepared,split", [(1, 4, [0, 1, 0], [1, 1, 1], [0, 1, 1]), (1, 1, [0, 1, 0], [1, 1, 1], [0, 1, 1]),
+                                                                (5, 3, [0, 1, 0], [0, 1, 0], [1, 1, 1]), (12, 4, [0, 1, 0], [0, 1, 0], [1, 1, 1])])
+def test_switches_choose_the_kernels(block, group, default, prepared, split, d, monkeypatch):
+    """As include/roco.h says: a single token that asks for the preparing kernel gets it, and splits are those of the three kernels."""
+    import paper_2402_06262_amd as roco
+    units, B = 3, 256
+    p = roco.RocoParams(units, d, B, 16, roco.ROCO_BF16)
+    c = roco.alloc_cache(p)
+    ws = torch.empty(roco.block_workspace_bytes(p, block), dtype=torch.uint8, device="cuda")
+    q = torch.randn((units, block, group, d), device="cuda").bfloat16()
+    k = torch.randn((units, block, d), device="cuda").bfloat16()
+    at = torch.zeros(units, dtype=torch.int32, device="cuda")
+
+    def run():
+        roco.roco_encode_block_gqa(p, block, group, q, k, k, at, c.K, c.V, c.stats, c.pos, c.n_used, c.next_slot, torch.empty_like(q), None,
+                                   None, ws)
+
+    for env, want in (({}, default), ({"ROCO_BLOCK_SINGLE": "0"}, prepared), ({"ROCO_BLOCK_SINGLE": "1"}, default), ({"ROCO_BLOCK_SPLITS": "2"}, split),
+                      ({"ROCO_BLOCK_FUSED": "0"}, split), ({"ROCO_BLOCK_FUSED": "8", "ROCO_BLOCK_SPLITS": "2"}, default)):
+        with monkeypatch.context() as m:
+            for name, value in env.items():
+                m.setenv(name, value)
+            got = _launches(run)
+        assert got == want, (env, got)
