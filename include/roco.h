@@ -249,8 +249,8 @@ int roco_decode_step_static(const roco_params* params,
  * workspace        roco_block_workspace_bytes(params, block) bytes: sized for the largest step (64 query rows per
  *                  unit), so that one workspace serves every block size and group size of a unit count and budget
  * Supported: budget a multiple of 4 (else ROCO_EUNSUPPORTED).  K and V are streamed once per block for every dtype
- * and head_dim: bf16 with head_dim 128 on the matrix cores, the others on the vector ALUs (which bound steps of
- * more than about 8 query rows).
+ * and head_dim (twice, mostly from cache, where two workgroups share a unit): bf16 on the matrix cores, where the logits of a step fit
+ * a compute unit or head_dim is 128, the others on the vector ALUs (which bound steps of more than about 8 query rows).
  */
 size_t roco_block_workspace_bytes(const roco_params* params, int32_t block);
 int roco_encode_block(const roco_params* params, int32_t block,
@@ -397,9 +397,17 @@ int roco_probe_mfma(int32_t workgroups, int32_t iters, int32_t operands, float* 
  *   ROCO_BLOCK_SPLITS=n        splits of the budget in the block-wise / grouped steps (default: about 512 / units from 64 units on;
  *                              below, 512 / units and 24 at most, or 256 / units with more than 16 query rows of fp32 /
  *                              head_dim 128; bf16 / head_dim 128: 8 at most, or up to 16 of at least 256 slots with up to 16
- *                              query rows and 256 / units; no split has more than 2^22 slots)
+ *                              query rows and 256 / units; no split has more than 2^22 slots); n > 0 also
+ *                              keeps bf16 on the three kernels that have splits, unless ROCO_BLOCK_FUSED says otherwise
  *   ROCO_BLOCK_SINGLE=0        single-token block steps go through the preparing kernel like longer blocks (bf16 too, whatever
  *                              ROCO_BLOCK_FUSED says)
+ *   ROCO_BLOCK_FUSED=8|4|2|0   block-wise / grouped steps of bf16: one kernel of eight waves per unit / of four / two workgroups
+ *                              per unit with half of the tokens each, and a kernel that adds their sums / three kernels; above 32
+ *                              query rows 8, 4 and 2 are all two workgroups; a step that the shape does not hold takes three kernels
+ *                              (default: by units, budget, rows and head_dim)
+ *   ROCO_SELECT_THREADS=512|1024  threads of the prompt selection (default: 512 for prompts of up to 512 tokens, and of up to 2048
+ *                              with more than 256 units)
+ *   ROCO_PREFILL_WAVES_PER_ROW=1|4  waves that share a query row of the vector row pass (default: four for few rows)
  */
 
 /* Static description of a return code. */

@@ -34,6 +34,12 @@ extern template hipError_t launch_halves<64, 8, 2, 8>(const BlockArgs&, hipStrea
 
 using Launch = hipError_t (*)(const BlockArgs&, hipStream_t);
 
+// Splits belong to the three kernels: whoever asks for a number of them gets those (0 asks for none).
+static bool asks_for_splits() {
+  const char* const e = getenv("ROCO_BLOCK_SPLITS");
+  return e != nullptr && atoi(e) > 0;
+}
+
 // The shape for W waves: the fewest tiles per wave that hold the unit's slots, null if none does.
 template <int HD, int W, int NQ, int ZT, int... MORE>
 Launch shape_for(const BlockArgs& a) {
@@ -62,7 +68,7 @@ Launch choose_halves(const BlockArgs& a) {
                                                        : nullptr;
   const char* const asked = getenv("ROCO_BLOCK_FUSED");
   if (asked != nullptr && *asked != 0) return asked[0] == '0' ? nullptr : two;
-  if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
+  if (asks_for_splits()) return nullptr;
   if (HD == 64) return a.units <= 128 || (a.units <= 256 && (a.B > 128 || a.heads >= 4)) || a.B >= 224 ? two : nullptr;
   const bool two_rounds = a.heads >= 4 || (a.heads > 1 && a.queries > 48) || (a.units > 170 && a.units < 240);
   return a.units <= 128 || (a.units <= 256 && a.B > 768 && two_rounds) ? two : nullptr;
@@ -87,7 +93,8 @@ Launch choose_halves(const BlockArgs& a) {
 // Four waves, two workgroups to a compute unit, where the units are more than the compute units (512 x 16 tokens x 2048 with eight
 // 119.7, with four 110.8; 356 x 2 heads x 132 23.0 / 14.1) and where a cache is a tile or two per wave (1 x 120 x 16 heads 10.1 / 9.2),
 // else eight (256 x 16 tokens x 2048 58.7 / 67.8, 128 x 4 heads x 2048 38.4 / 43.0).
-// ROCO_BLOCK_FUSED=8, 4, 2, 0: eight waves, four, halves, three kernels (tests run all); so does a number of splits that is asked for.
+// ROCO_BLOCK_FUSED=8, 4, 2, 0: eight waves, four, halves, three kernels (tests run all); a shape that does not take the step leaves it to
+// the three kernels.
 template <int HD>
 Launch choose(const BlockArgs& a) {
   if (a.queries > 2 * kQ16) return choose_halves<HD>(a);
@@ -101,7 +108,7 @@ Launch choose(const BlockArgs& a) {
       halves = launch_halves<HD, 4, 1, 16>;
   }
   if (asked != nullptr && *asked != 0) return asked[0] == '2' ? halves : asked[0] == '8' ? eight : asked[0] == '4' ? four : nullptr;
-  if (getenv("ROCO_BLOCK_SPLITS") != nullptr) return nullptr;
+  if (asks_for_splits()) return nullptr;
   const bool pairs = four != nullptr && (a.units > 256 || a.B <= 256);
   if (halves != nullptr && a.B > 1024 && a.queries > 24 && (a.units > 256 || (a.units > 64 && a.units <= 128))) return halves;
   const int least = HD == 64 ? (a.B > 2048 ? (a.block == 1 && a.queries >= 8 ? 24 : 40) : a.B > 1536 && a.queries > 24 ? 24 : 0)

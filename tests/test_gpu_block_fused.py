@@ -108,7 +108,8 @@ def _launches(run):
 @pytest.mark.parametrize("block,group,default,prepared,split", [(1, 4, [0, 1, 0], [1, 1, 1], [0, 1, 1]), (1, 1, [0, 1, 0], [1, 1, 1], [0, 1, 1]),
                                                                 (5, 3, [0, 1, 0], [0, 1, 0], [1, 1, 1]), (12, 4, [0, 1, 0], [0, 1, 0], [1, 1, 1])])
 def test_switches_choose_the_kernels(block, group, default, prepared, split, d, monkeypatch):
-    """As include/roco.h says: a single token that asks for the preparing kernel gets it, and splits are those of the three kernels."""
+    """As include/roco.h says: no preparing kernel left out of a single token that asks for it, splits in the kernels that have them, and
+    none asked for by 0."""
     import paper_2402_06262_amd as roco
     units, B = 3, 256
     p = roco.RocoParams(units, d, B, 16, roco.ROCO_BF16)
@@ -122,7 +123,8 @@ def test_switches_choose_the_kernels(block, group, default, prepared, split, d, 
         roco.roco_encode_block_gqa(p, block, group, q, k, k, at, c.K, c.V, c.stats, c.pos, c.n_used, c.next_slot, torch.empty_like(q), None,
                                    None, ws)
 
-    for env, want in (({}, default), ({"ROCO_BLOCK_SINGLE": "0"}, prepared), ({"ROCO_BLOCK_SINGLE": "1"}, default), ({"ROCO_BLOCK_SPLITS": "2"}, split),
+    for env, want in (({}, default), ({"ROCO_BLOCK_SPLITS": "0"}, default), ({"ROCO_BLOCK_SPLITS": ""}, default),
+                      ({"ROCO_BLOCK_SINGLE": "0"}, prepared), ({"ROCO_BLOCK_SINGLE": "1"}, default), ({"ROCO_BLOCK_SPLITS": "2"}, split),
                       ({"ROCO_BLOCK_FUSED": "0"}, split), ({"ROCO_BLOCK_FUSED": "8", "ROCO_BLOCK_SPLITS": "2"}, default)):
         with monkeypatch.context() as m:
             for name, value in env.items():

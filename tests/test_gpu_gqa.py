@@ -402,11 +402,12 @@ def test_few_units_on_many_splits(dtype, d, group, blocks, splits, monkeypatch):
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("f32", 128)])
-@pytest.mark.parametrize("group,B,splits", [(1, 100, "0"), (4, 100, "0"), (2, 1604, "7"), (3, 20000, "0")])
+@pytest.mark.parametrize("group,B,splits", [(1, 100, "0"), (4, 100, "0"), (8, 1604, "0"), (17, 516, "0"), (2, 1604, "7"), (3, 20000, "0")])
 @pytest.mark.parametrize("policy", [(0, 0, 0), (2, 1, 0), (1, 2, 0)], ids=["roco", "oldest-window", "accumulated"])
 def test_full_caches_without_a_chosen_victim(dtype, d, group, B, splits, policy, monkeypatch, single_step):
     """One token on a full cache that its owner has put together without roco_select_victims (next_slot is -1, as alloc_cache
-    leaves it): the victim is chosen from the statistics as they stand, as the rule of the block-wise step says."""
+    leaves it): the victim is chosen from the statistics as they stand, as the rule of the block-wise step says (bf16: by the one
+    kernel, of four waves and of eight, but for 20000 slots, given splits and the preparing kernel)."""
     import paper_2402_06262_amd as roco
     monkeypatch.setenv("ROCO_BLOCK_SPLITS", splits)
     units, g = 3, torch.Generator(device="cuda").manual_seed(B + d)
