@@ -707,24 +707,30 @@ template <int HD, int W, int NQ, int ZT> struct Shape {
   static constexpr int kStep = kTileSlots * W;
   static size_t bytes_of(const BlockArgs& a, int slots) { return (2 * static_cast<size_t>(a.B) + static_cast<size_t>(a.queries) * (slots + 4)) * 4; }
   // what block_fused declares statically, at most
-  static size_t fixed(const BlockArgs& a) {
+  static constexpr size_t fixed(bool single, bool window, bool halves) {
     const size_t qr = NQ * kQ16;
-    const size_t own = a.single ? qr * 4 + 16 : qr * (a.block > static_cast<int>(qr) || a.queries < a.block * a.heads ? kMaxBlock : qr) * 4 + kStep * ZT;
-    return SelectLds<W == 4 ? 2 : 1>::kWords * 4 + (a.recency_window > 0 ? W * 512 : 512) + 2 * W * qr * 4 + qr * 4 + own + 1024;
+    const size_t own = single ? qr * 4 + 16 : qr * (halves ? kMaxBlock : qr) * 4 + kStep * ZT;
+    return SelectLds<W == 4 ? 2 : 1>::kWords * 4 + (window ? W * 512 : 512) + 2 * W * qr * 4 + qr * 4 + own + 1024;
   }
+  // The dynamic LDS of any step, the limit that every launch of a kernel sets: one that followed the step could be lowered by another
+  // thread's before the launch.  (Four waves: two workgroups share a compute unit.)
+  static constexpr size_t most(bool single, bool window, bool halves) { return kLdsOfUnit / (8 / W) - fixed(single, window, halves); }
+  static size_t most(const BlockArgs& a) { return most(a.single != 0, a.recency_window > 0, a.queries < a.block * a.heads); }
   // slots whose probabilities the LDS takes at a time beside the unit's ranking keys, and `ahead` bytes of V; 0: none
   static int slots(const BlockArgs& a, size_t ahead) {
-    const size_t most = kLdsOfUnit / (8 / W) - fixed(a) - ahead;  // four waves: two workgroups share a compute unit
+    const size_t room = most(a) - ahead;
     int s = std::min((a.B + kStep - 1) / kStep * kStep, 4 * W * kWave);
-    while (s > 0 && bytes_of(a, s) > most) s -= kStep;
+    while (s > 0 && bytes_of(a, s) > room) s -= kStep;
     return s;
   }
   static constexpr size_t kStage = W * Rows<HD>::kTile;
   // whether the first tiles of V may be on their way meanwhile
   static bool v_ahead(const BlockArgs& a) { return W == 8 && slots(a, kStage) >= std::min(a.B, 4 * W * kWave); }
+  static constexpr size_t kOuts = static_cast<size_t>(W) * NQ * kQ16 * Rows<HD>::kOut * sizeof(float);
+  static_assert(std::max(2 * kStage, kOuts) <= std::min(most(false, true, W == 8), most(true, true, false)), "tiles and outputs fit");
   static size_t lds(const BlockArgs& a) {
-    const size_t outs = static_cast<size_t>(W) * NQ * kQ16 * Rows<HD>::kOut * sizeof(float), ahead = v_ahead(a) ? kStage : 0;
-    return std::max({2 * kStage, outs, ahead + bytes_of(a, slots(a, ahead))});
+    const size_t ahead = v_ahead(a) ? kStage : 0;
+    return std::max({2 * kStage, kOuts, ahead + bytes_of(a, slots(a, ahead))});
   }
   static bool takes(const BlockArgs& a) { return a.B <= kStep * ZT && a.queries <= kQ16 * NQ && slots(a, 0) > 0; }
 };
@@ -740,7 +746,7 @@ hipError_t launch_t(const BlockArgs& a, hipStream_t s) {
   using S = Shape<HD, W, NQ, ZT>;
   const size_t lds = S::lds(a);
   const void* fn = reinterpret_cast<const void*>(block_fused<HD, W, NQ, ZT, SINGLE, STREAMING, WINDOW>);
-  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(S::most(SINGLE, WINDOW, false))) != hipSuccess)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL((block_fused<HD, W, NQ, ZT, SINGLE, STREAMING, WINDOW>), dim3(a.units), dim3(W * kWave), lds, s, a,
                      S::slots(a, S::v_ahead(a) ? S::kStage : 0), S::v_ahead(a) ? 1 : 0);
@@ -762,7 +768,7 @@ hipError_t launch_halves_t(const BlockArgs& a, const BlockArgs& half, hipStream_
   using S = Shape<HD, W, NQ, ZT>;
   const size_t lds = S::lds(half);
   const void* fn = reinterpret_cast<const void*>(block_fused<HD, W, NQ, ZT, false, STREAMING, WINDOW, true>);
-  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(S::most(false, WINDOW, true))) != hipSuccess)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL((block_fused<HD, W, NQ, ZT, false, STREAMING, WINDOW, true>), dim3((a.units + 7) / 8 * 16), dim3(W * kWave), lds, s, a,
                      S::slots(half, S::v_ahead(half) ? S::kStage : 0), S::v_ahead(half) ? 1 : 0);

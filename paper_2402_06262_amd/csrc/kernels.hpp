@@ -40,14 +40,15 @@ constexpr size_t kDefaultDynamicLds = 65536;  // LDS a kernel may use without ra
 constexpr size_t kStaticLdsAllowance = 16384;  // upper bound on the statically declared LDS of the kernels that ask
 
 // Dynamic LDS for the ranking keys of one unit (0: they go to the workspace); raises the kernel's limit when the
-// request, together with what the kernel declares statically, may be above the default one.  Returns false if the
-// runtime refuses.
+// request, together with what the kernel declares statically, may be above the default one -- to the most that any call asks for,
+// since another thread's smaller call might lower it again before the launch.  Returns false if the runtime refuses.
 inline size_t key_lds_bytes(int B) {
   return B <= kMaxDecodeBudgetLds ? static_cast<size_t>(B) * 2 * sizeof(uint32_t) : 0;
 }
 inline bool allow_key_lds(const void* kernel, size_t bytes) {
+  constexpr size_t kMost = static_cast<size_t>(kMaxDecodeBudgetLds) * 2 * sizeof(uint32_t);
   if (bytes + kStaticLdsAllowance <= kDefaultDynamicLds) return true;
-  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)) == hipSuccess;
+  return bytes <= kMost && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kMost)) == hipSuccess;
 }
 
 struct DecodeArgs {
