@@ -67,7 +67,7 @@ __device__ __forceinline__ void take_slots(const BlockArgs& a, int u, int n, uin
             const uint32_t vk = var_key[i];
             return phase == 0 ? vk : scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
           },
-          n, phase == 0 ? m : static_cast<uint32_t>(E), phase == 0 && a.pol.scope_is_window(), sel_sh);
+          n, phase == 0 ? m : static_cast<uint32_t>(E), phase == 0 && a.pol.scope_is_window(), sel_sh, phase == 0 || a.pol.spreads_importance());
       if (phase == 0) scope = r;
       else out = r;
     }
@@ -119,7 +119,7 @@ __device__ __forceinline__ int victim_by_statistics(const float* stats, const in
     ranking_keys(stats[i], stats[B + i], stats[2 * static_cast<size_t>(B) + i], pos[i], pol, mas_key, var_key);
     return make_uint2(mas_key, var_key);
   };
-  return select_victim<NT, PER_WORD>([&](int i) { return keys(i).y; }, [&](int i) { return keys(i).x; }, B, pol, scope, sel_sh, best_sh);
+  return select_victim<NT, PER_WORD, false>([&](int i) { return keys(i).y; }, [&](int i) { return keys(i).x; }, B, pol, scope, sel_sh, best_sh);
 }
 
 #pragma clang diagnostic ignored "-Winline-asm"

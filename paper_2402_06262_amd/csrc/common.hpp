@@ -498,8 +498,10 @@ __device__ __forceinline__ bool fine_select(KeyFn key_of, int n, uint32_t k, uin
   return true;
 }
 
-template <int NT, int PER_WORD, int AHEAD, class KeyFn>
-__device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, bool small, uint32_t* sh) {
+// FINE, spread: the keys may lie where fine_select finds them.  Positions and counts do not (a prompt of 1207 tokens under an oldest-first
+// policy lost 0.5 us to searches in vain), and a search that is hardly ever made is not worth the code.
+template <int NT, int PER_WORD, int AHEAD, bool FINE = true, class KeyFn>
+__device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint32_t k, bool small, uint32_t* sh, bool spread = true) {
   // everything is wanted (the policies whose scope is the whole cache, say): nothing to select
   if (k >= static_cast<uint32_t>(n)) return KSmallest{0xffffffffu, 0xffffffffu};
   // At most two rounds through one copy of the search (these kernels start cold: a second copy is instructions to fetch):
@@ -512,7 +514,7 @@ __device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint
     const uint32_t kth = r.kth;
     uint32_t found, n_less, n_equal;
     bool done = false;
-    if constexpr (NT <= 512) done = round == 0 && !small && n <= 65535 && fine_select<NT, PER_WORD, AHEAD>(key_of, n, take, sh, found, n_less, n_equal);
+    if constexpr (FINE && NT <= 512) done = round == 0 && spread && !small && n <= 65535 && fine_select<NT, PER_WORD, AHEAD>(key_of, n, take, sh, found, n_less, n_equal);
     if (!done)
       radix_select<NT, PER_WORD, AHEAD>(
           [&](int i) {
@@ -533,11 +535,11 @@ __device__ __forceinline__ KSmallest select_k_smallest(KeyFn key_of, int n, uint
 
 // Scope = `scope` lowest variance keys among [0, B); returns the slot of lowest MAS key inside it (lowest
 // slot on equal keys).  Every thread of the block calls it and gets the same answer.
-template <int NT, int PER_WORD, class VarFn, class MasFn>
+template <int NT, int PER_WORD, bool FINE = true, class VarFn, class MasFn>
 __device__ __forceinline__ int select_victim(VarFn var_key_of, MasFn mas_key_of, int B, const Policy& pol, int scope, uint32_t* sel_sh,
                                              uint2* best_sh) {
   const int tid = late_thread_id();
-  const KSmallest sc = select_k_smallest<NT, PER_WORD, NT <= 4 * kWave ? 4 : 1>(var_key_of, B,
+  const KSmallest sc = select_k_smallest<NT, PER_WORD, NT <= 4 * kWave ? 4 : 1, FINE>(var_key_of, B,
                                              static_cast<uint32_t>(pol.scope_size(scope, B)), pol.scope_is_window(), sel_sh);
   uint32_t key = 0xffffffffu, idx = 0xffffffffu;
 #pragma unroll 1

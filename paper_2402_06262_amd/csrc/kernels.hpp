@@ -26,6 +26,8 @@ struct Policy {
     if (importance == kImpCount) return old + (p * attended > 1.0f ? 1.0f : 0.0f);
     return old + p * p;
   }
+  // its keys are probabilities or sums of them, not positions or counts
+  __host__ __device__ bool spreads_importance() const { return importance != kImpOldest && importance != kImpCount; }
   __host__ __device__ bool scope_is_window() const { return scope_kind == kScopeWindow; }  // its keys are positions
   __host__ __device__ bool needs_pos() const { return importance == kImpOldest || scope_kind == kScopeWindow; }
   // number of tokens inside the scope when n are cached

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(NT, 8) void prefill_select(PrefillArgs a) {
             if (phase == 0) return vk;
             return scope.has(vk, i) ? mas_key[i] : 0xffffffffu;
           },
-          n, k, phase == 0 && a.pol.scope_is_window(), sel_sh);
+          n, k, phase == 0 && a.pol.scope_is_window(), sel_sh, phase == 0 || a.pol.spreads_importance());
       if (phase == 0) scope = r;
       else out = r;
     }
