@@ -89,7 +89,9 @@ Launch choose_halves(const BlockArgs& a) {
 //   16 heads 46.7 / 17.9), but for more than 24 rows of more than 1536 slots on few units (1 x 2048 x 32 48.7 / 52.4, 12 x 1800 x 32 51.5 /
 //   52.2, 24 x 2048 x 32 56.8 / 53.5).  B <= 4096 from 40 units on (24 x 4096 x 4 heads 31.1 / 33.5, 32 x 3000 x 4 tokens 39.2 / 39.7,
 //   44 x 3000 x 4 heads 34.2 / 29.4, 44 x 2052 x 4 tokens 36.5 / 34.4, 110 x 4096 x 8 heads 72.7 / 35.6), of single tokens of 8 and more
-//   heads from 24 on (24 x 3000 x 8 29.6 / 29.0, x 16 37.1 / 29.5).
+//   heads from 24 on (24 x 3000 x 8 29.6 / 29.0, x 16 37.1 / 29.5).  A recency window, whose bias is one workgroup's work here, moves
+//   these lines (4 x 1024 x 2 heads 16.1 / 13.8, but 4 x 2048 x 2 heads 20.0 / 21.6, 4 x 2048 x 24 tokens 47.3 / 49.5, 32 x 2048 x 2 heads
+//   21.4 / 22.1, 44 x 2052 x 2 25.4 / 27.3, 32 x 3000 x 8 30.8 / 33.4).
 // Four waves, two workgroups to a compute unit, where the units are more than the compute units (512 x 16 tokens x 2048 with eight
 // 119.7, with four 110.8; 356 x 2 heads x 132 23.0 / 14.1) and where a cache is a tile or two per wave (1 x 120 x 16 heads 10.1 / 9.2),
 // else eight (256 x 16 tokens x 2048 58.7 / 67.8, 128 x 4 heads x 2048 38.4 / 43.0).
@@ -111,8 +113,14 @@ Launch choose(const BlockArgs& a) {
   if (asks_for_splits()) return nullptr;
   const bool pairs = four != nullptr && (a.units > 256 || a.B <= 256);
   if (halves != nullptr && a.B > 1024 && a.queries > 24 && (a.units > 256 || (a.units > 64 && a.units <= 128))) return halves;
-  const int least = HD == 64 ? (a.B > 2048 ? (a.block == 1 && a.queries >= 8 ? 24 : 40) : a.B > 1536 && a.queries > 24 ? 24 : 0)
-                             : a.B <= 1024 ? 0 : a.B <= 2048 ? (one ? 72 : 65) : 80;
+  int least = 0;
+  if (HD == 64) {
+    const bool window = a.recency_window > 0, wide = a.block == 1 && a.queries >= 8;
+    if (a.B > 2048) least = window ? (wide ? 40 : 60) : wide ? 24 : 40;
+    else if (a.B > 1536) least = window ? 40 : a.queries > 24 ? 24 : 0;
+  } else if (a.B > 1024) {
+    least = a.B <= 2048 ? (one ? 72 : 65) : 80;
+  }
   if (a.units < least || (HD == 128 && !pairs && a.queries > 24 && a.units > 256)) return nullptr;
   return pairs ? four : eight;
 }
