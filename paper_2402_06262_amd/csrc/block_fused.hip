@@ -57,8 +57,9 @@ Launch shape_for(const BlockArgs& a) {
 // of 2 111 / 115); up to 768 slots 176 x 584 x 41 66 / 68, 140 x 248 x 46 53 / 57; more rounds: 512 x 1536 x 10 of 4 166 / 175, 423 x 244
 // x 61 77 / 125.
 // bf16 / 64, whose three kernels do not use the matrix cores: 128 x 96 x 48 39.2 / 27.5, 180 x 132 x 33 52.9 / 43.7, 256 x 160 x 64 66.3 /
-// 56.6, 256 x 96 x 12 of 4 39.2 / 34.0, 400 x 260 x 64 126 / 108, 800 x 224 x 33 147 / 136; but up to 128 slots 180 x 64 x 48 36.9 / 47.9,
-// 256 x 128 x 33 39.9 / 40.9, and 878 x 144 x 46 133 / 151, 758 x 104 x 46 95 / 124.
+// 56.6, 256 x 96 x 12 of 4 39.2 / 34.0, 400 x 260 x 64 126 / 108, 800 x 224 x 33 147 / 136; but where their workgroups of 64 slots are
+// resident at once and the pairs are not 180 x 64 x 48 36.9 / 47.9, 256 x 128 x 33 39.9 / 40.9, 155 x 168 x 56 49.3 / 53.6; and 878 x 144 x 46
+// 133 / 151, 758 x 104 x 46 95 / 124.
 template <int HD>
 Launch choose_halves(const BlockArgs& a) {
   const BlockArgs half = half_step(a);
@@ -69,7 +70,10 @@ Launch choose_halves(const BlockArgs& a) {
   const char* const asked = getenv("ROCO_BLOCK_FUSED");
   if (asked != nullptr && *asked != 0) return asked[0] == '0' ? nullptr : two;
   if (asks_for_splits()) return nullptr;
-  if (HD == 64) return a.units <= 128 || (a.units <= 256 && (a.B > 128 || a.heads >= 4)) || a.B >= 224 ? two : nullptr;
+  if (HD == 64) {
+    const bool resident = a.units * ((a.B + 63) / 64) <= 512;  // the three kernels' workgroups
+    return a.units <= 128 || (a.units <= 256 && (!resident || a.heads >= 4)) || a.B >= 224 ? two : nullptr;
+  }
   const bool two_rounds = a.heads >= 4 || (a.heads > 1 && a.queries > 48) || (a.units > 170 && a.units < 240);
   return a.units <= 128 || (a.units <= 256 && a.B > 768 && two_rounds) ? two : nullptr;
 }
