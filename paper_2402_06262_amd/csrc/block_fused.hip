@@ -49,7 +49,7 @@ Launch shape_for(const BlockArgs& a) {
 }
 
 // 33 to 64 rows: each half of the tokens in a workgroup of its own, where the pairs take one round and the stream, which both read,
-// is long enough.  Against the three kernels, us per step, bf16 / 128: 128 units x 2048 slots x 16 tokens of 4 heads 95 / 64, 48 x 1024
+// is long enough.  Against the three kernels, us per step, bf16 / 128: 128 units x 2048 slots x 16 tokens of 4 heads 95 / 65, 48 x 1024
 // x 16 of 4 53 / 37, 4 x 476 x 48 39.9 / 34.1, 7 x 1804 x 19 of 2 48.0 / 46.6.  Two rounds, above 768 slots: 256 x 1300 x 16 of 4 107 / 80,
 // 130 x 2048 x 32 of 2 103.1 / 103.0, 256 x 2048 x 32 of 2 136 / 130; tokens of one head have twice the sums to add, and the three kernels
 // fill their rounds badly with the three splits that 171 to 240 units get (180 x 2048 x 33 105 / 95, 220 x 1536 x 64 123 / 103) but well
@@ -57,7 +57,7 @@ Launch shape_for(const BlockArgs& a) {
 // of 2 111 / 115); up to 768 slots 176 x 584 x 41 66 / 68, 140 x 248 x 46 53 / 57; more rounds: 512 x 1536 x 10 of 4 166 / 175, 423 x 244
 // x 61 77 / 125.
 // bf16 / 64, whose three kernels do not use the matrix cores: 128 x 96 x 48 39.2 / 27.5, 180 x 132 x 33 52.9 / 43.7, 256 x 160 x 64 66.3 /
-// 56.6, 256 x 96 x 12 of 4 39.2 / 34.0, 400 x 260 x 64 126 / 108, 800 x 224 x 33 147 / 136; but where their workgroups of 64 slots are
+// 56.6, 256 x 96 x 12 of 4 39.2 / 34.0, 400 x 260 x 64 126 / 108, 800 x 224 x 33 146 / 139; but where their workgroups of 64 slots are
 // resident at once and the pairs are not 180 x 64 x 48 36.9 / 47.9, 256 x 128 x 33 39.9 / 40.9, 155 x 168 x 56 49.3 / 53.6; and 878 x 144 x 46
 // 133 / 151, 758 x 104 x 46 95 / 124.
 template <int HD>
@@ -90,9 +90,9 @@ Launch choose_halves(const BlockArgs& a) {
 //   four waves (three kernels / eight waves / halves): 65 x 2048 x 32 69 / 70 / 60, 97 x 1628 x 32 74 / 67 / 57, 264 x 1536 x 32 115 / 123 /
 //   109, 512 x 2048 x 32 184 / 170 / 168, 697 x 1792 x 32 264 / 231 / 220; but 140 x 1352 x 6 of 4 66 / 49 / 54, 400 x 1960 x 17 143 / 132 / 144.
 // bf16 / 64, half of the bytes: B <= 2048 always (10 units x 1508 slots x 4 heads 19.0 / 17.0, 1 x 1800 x 24 tokens 44.0 / 42.7, 171 x 992 x
-//   16 heads 46.7 / 17.9), but for more than 24 rows of more than 1536 slots on few units (1 x 2048 x 32 48.7 / 52.4, 12 x 1800 x 32 51.5 /
+//   16 heads 47.0 / 16.5, 518 x 1904 x 20 rows 308 / 144), but for more than 24 rows of more than 1536 slots on few units (1 x 2048 x 32 48.7 / 52.4, 12 x 1800 x 32 51.5 /
 //   52.2, 24 x 2048 x 32 56.8 / 53.5).  B <= 4096 from 40 units on (24 x 4096 x 4 heads 31.1 / 33.5, 32 x 3000 x 4 tokens 39.2 / 39.7,
-//   44 x 3000 x 4 heads 34.2 / 29.4, 44 x 2052 x 4 tokens 36.5 / 34.4, 110 x 4096 x 8 heads 72.7 / 35.6), of single tokens of 8 and more
+//   44 x 3000 x 4 heads 34.2 / 29.4, 44 x 2052 x 4 tokens 36.5 / 34.4, 110 x 4096 x 8 heads 73.2 / 36.9), of single tokens of 8 and more
 //   heads from 24 on (24 x 3000 x 8 29.6 / 29.0, x 16 37.1 / 29.5).  A recency window, whose bias is one workgroup's work here, moves
 //   these lines (4 x 1024 x 2 heads 16.1 / 13.8, but 4 x 2048 x 2 heads 20.0 / 21.6, 4 x 2048 x 24 tokens 47.3 / 49.5, 32 x 2048 x 2 heads
 //   21.4 / 22.1, 44 x 2052 x 2 25.4 / 27.3, 32 x 3000 x 8 30.8 / 33.4).

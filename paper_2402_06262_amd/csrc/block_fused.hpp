@@ -12,18 +12,18 @@
 //   outputs     V streamed once against the registers.  Probabilities are taken as sums of bf16 numbers (split_positive): the matrix
 //               cores idle.  Two for head_dim 128, where rounded to one they made half of the output's error (2.1e-3 against 64 bits,
 //               1.7e-3 so); three for head_dim 64, whose three kernels multiply all 24 bits on the vector ALUs
-// 33 to 64 rows, and 25 to 32 over more than 1024 slots: two workgroups per unit, each with half of the tokens (HALVES).  Both stream
+// 33 to 64 rows, and 25 to 32 over more than 1024 slots of head_dim 128: two workgroups per unit, each with half of the tokens (HALVES).  Both stream
 // K and V, which one of them finds in their die's L2, and both evict, alike; they leave their sums of probabilities and squares to
 // block_book, which adds them to the statistics and does what depends on or changes the state that both have read (128 units x 2048 x
-// 16 tokens of 4 heads 95 -> 66 us).
+// 16 tokens of 4 heads 95 -> 65 us).
 //
 // V is only waited for by the outputs, and nothing waits for them: every other group of eight units streams K before it evicts and V
 // before its statistics, so that on the whole some workgroups use the memory while others rank (512 units x 2048 slots x 16 tokens:
 // 125 us with one order for all, 118 with turns at the eviction, 111 with both).
 //
 // What bounds it: a compute unit takes 49 GB/s alone, 41 when half of the chip's units do (5.2 TB/s), 24 when all do (6.1 TB/s), so a
-// workgroup per unit streams as fast as several once the units cover half of the chip: 128 x 4 heads x 2048 slots 45.9 -> 38.4 us (26
-// of them the stream, 4 the search for the next victim), 512 x 16 tokens x 2048 163 -> 111 (88 the stream).
+// workgroup per unit streams as fast as several once the units cover half of the chip: 128 x 4 heads x 2048 slots 45.9 -> 37.6 us (26
+// of them the stream, 4 the search for the next victim), 512 x 16 tokens x 2048 163 -> 109 (88 the stream).
 // A launch begins with a cold instruction cache, and what is fetched once costs a third of a microsecond per KiB: chains over all of a
 // wave's tiles only move registers, everything else is done once, on the tile moved.
 #pragma once
