@@ -69,7 +69,7 @@ Launch choose_halves(const BlockArgs& a) {
                                                        : nullptr;
   const char* const asked = getenv("ROCO_BLOCK_FUSED");
   if (asked != nullptr && *asked != 0) return asked[0] == '0' ? nullptr : two;
-  if (asks_for_splits()) return nullptr;
+  if (two == nullptr || asks_for_splits()) return nullptr;
   if (HD == 64) {
     const bool resident = a.units * ((a.B + 63) / 64) <= 512;  // the three kernels' workgroups
     return a.units <= 128 || (a.units <= 256 && (!resident || a.heads >= 4)) || a.B >= 224 ? two : nullptr;
